@@ -10,6 +10,7 @@
  *   for each rank r:  tagc_compress(PHASE_INDEX)    sparsify + create_index
  *   tagc_aggregate(PHASE_INDEX)                     All-Reduce(index) as OR (or add)
  *   for each rank r:  tagc_compress(PHASE_SKETCH)   compress -> Count Sketch
+ *                     (or tagc_compress_ranks: all ranks in the same launches)
  *   tagc_aggregate(PHASE_SKETCH)                    Reduce as element-wise sum
  *   tagc_decompress                                 peeling_decompress
  *
@@ -306,6 +307,17 @@ int tagc_plan_upload(const tagc_plan_t *plan, void *table_dev, void *stream);
 int tagc_compress(const tagc_plan_t *plan, uint32_t phase, const void *grad_dev,
                   const tagc_rank_buffers *rank,
                   const tagc_shared_buffers *shared, void *stream);
+
+/*
+ * tagc_compress for n_ranks ranks on one GPU: equal to
+ *   for r in 0 .. n_ranks-1: tagc_compress(plan, phase, grads[r], &ranks[r], shared, stream)
+ * with the ranks' work in the same launches.  A launch's ramp-up, tail and turn-around
+ * (about 5 us) are then paid once and not once per rank.  grads: host array of n_ranks
+ * device pointers (not read, may be NULL, in PHASE_SKETCH); ranks: host array.
+ */
+int tagc_compress_ranks(const tagc_plan_t *plan, uint32_t phase, const void *const *grads,
+                        const tagc_rank_buffers *ranks, uint32_t n_ranks,
+                        const tagc_shared_buffers *shared, void *stream);
 
 /*
  * tagc_compress for callers that cannot allocate device memory or bring a

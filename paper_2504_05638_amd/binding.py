@@ -29,7 +29,7 @@ TAGC_FLAG_OVERFLOW = 2
 TAGC_STATIC_WORKSPACE_BYTES = 16 << 20
 
 EXPORTS = ["tagc_plan", "tagc_plan_destroy", "tagc_plan_sizes",
-           "tagc_plan_upload", "tagc_compress", "tagc_compress_static", "tagc_feedback_apply", "tagc_aggregate",
+           "tagc_plan_upload", "tagc_compress", "tagc_compress_ranks", "tagc_compress_static", "tagc_feedback_apply", "tagc_aggregate",
            "tagc_decompress", "tagc_reduce_decompress", "tagc_profile_enable", "tagc_profile_read",
            "tagc_hash_host", "tagc_strerror"]
 
@@ -123,6 +123,10 @@ def lib():
         L.tagc_compress.argtypes = [vp, C.c_uint32, vp,
                                     C.POINTER(tagc_rank_buffers),
                                     C.POINTER(tagc_shared_buffers), vp]
+        L.tagc_compress_ranks.restype = C.c_int
+        L.tagc_compress_ranks.argtypes = [vp, C.c_uint32, C.POINTER(vp),
+                                          C.POINTER(tagc_rank_buffers), C.c_uint32,
+                                          C.POINTER(tagc_shared_buffers), vp]
         L.tagc_compress_static.restype = C.c_int
         L.tagc_compress_static.argtypes = L.tagc_compress.argtypes
         L.tagc_aggregate.restype = C.c_int
@@ -198,6 +202,15 @@ def tagc_compress(plan, phase, grad_dev, rank: tagc_rank_buffers,
                                C.byref(shared), stream), "tagc_compress")
 
 
+def tagc_compress_ranks(plan, phase, grads_dev, ranks, shared: tagc_shared_buffers,
+                        stream: int = 0, n_ranks=None):
+    """tagc_compress for the first n_ranks (default: all) of `ranks`, in the same launches."""
+    n = len(ranks) if n_ranks is None else n_ranks
+    grads = (C.c_void_p * n)(*grads_dev) if grads_dev is not None else None
+    _check(lib().tagc_compress_ranks(plan, phase, grads, _rank_array(ranks), n,
+                                     C.byref(shared), stream), "tagc_compress_ranks")
+
+
 def tagc_compress_static(plan, phase, grad_dev, rank: tagc_rank_buffers,
                          shared: tagc_shared_buffers, stream: int = 0):
     """tagc_compress on the library's own workspace (rank.workspace is ignored)."""
@@ -211,10 +224,15 @@ def tagc_feedback_apply(plan, rank: tagc_rank_buffers, shared: tagc_shared_buffe
            "tagc_feedback_apply")
 
 
+def _rank_array(ranks):
+    """A C array of rank buffers: `ranks` itself if it is one already."""
+    return ranks if isinstance(ranks, C.Array) else (tagc_rank_buffers * len(ranks))(*ranks)
+
+
 def tagc_aggregate(plan, phase, ranks, shared: tagc_shared_buffers,
-                   stream: int = 0):
-    arr = (tagc_rank_buffers * len(ranks))(*ranks)
-    _check(lib().tagc_aggregate(plan, phase, arr, len(ranks), C.byref(shared),
+                   stream: int = 0, n_ranks=None):
+    n = len(ranks) if n_ranks is None else n_ranks
+    _check(lib().tagc_aggregate(plan, phase, _rank_array(ranks), n, C.byref(shared),
                                 stream), "tagc_aggregate")
 
 
@@ -225,9 +243,9 @@ def tagc_decompress(plan, shared: tagc_shared_buffers, idx_out, val_out,
 
 
 def tagc_reduce_decompress(plan, ranks, shared: tagc_shared_buffers, idx_out, val_out,
-                           dense_out=None, stream: int = 0):
-    arr = (tagc_rank_buffers * len(ranks))(*ranks)
-    _check(lib().tagc_reduce_decompress(plan, arr, len(ranks), C.byref(shared), idx_out,
+                           dense_out=None, stream: int = 0, n_ranks=None):
+    n = len(ranks) if n_ranks is None else n_ranks
+    _check(lib().tagc_reduce_decompress(plan, _rank_array(ranks), n, C.byref(shared), idx_out,
                                         val_out, dense_out, stream), "tagc_reduce_decompress")
 
 

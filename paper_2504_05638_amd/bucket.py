@@ -71,7 +71,7 @@ class TagcBucket:
             self.sh_bounds.data_ptr(), self.sh_ws.data_ptr(),
             self.sh_status.data_ptr())
         self.rank_ws = al("rank_ws", z.rank_workspace_bytes)  # ranks run in turn
-        self.rk = []
+        self.rk = (B.tagc_rank_buffers * n_ranks)()
         self._rk_tensors = []
         for r in range(n_ranks):
             t = dict(idx=al("idx%d" % r, z.rank_idx_bytes),
@@ -88,10 +88,10 @@ class TagcBucket:
                                        dtype=torch.float32 if dtype == B.TAGC_F32
                                        else torch.bfloat16)
             self._rk_tensors.append(t)
-            self.rk.append(B.tagc_rank_buffers(
+            self.rk[r] = B.tagc_rank_buffers(
                 t["idx"].data_ptr(), t["val"].data_ptr(), t["cnt"].data_ptr(),
                 t["bitmap"].data_ptr(), t["sketch"].data_ptr(),
-                self.rank_ws.data_ptr(), t["acc"].data_ptr() if error_feedback else None))
+                self.rank_ws.data_ptr(), t["acc"].data_ptr() if error_feedback else None)
         self.out_idx = al("out_idx", z.out_idx_bytes)
         self.out_val = al("out_val", z.out_val_bytes)
         self.out_dense = al("out_dense", z.out_dense_bytes) if dense else None
@@ -144,19 +144,37 @@ class TagcBucket:
         B.tagc_compress(self.plan, B.TAGC_PHASE_INDEX, grad.data_ptr(), self.rk[r],
                         self.shared, _stream_ptr(stream))
 
+    def compress_index_all(self, grads, stream=None):
+        """compress_index of ranks 0 .. len(grads)-1, in the same launches."""
+        if not grads:
+            return
+        if len(grads) > self.n_ranks:
+            raise ValueError("%d gradients, the bucket has buffers for %d ranks"
+                             % (len(grads), self.n_ranks))
+        for g in grads:
+            self._check_grad(g)
+        B.tagc_compress_ranks(self.plan, B.TAGC_PHASE_INDEX, [g.data_ptr() for g in grads],
+                              self.rk, self.shared, _stream_ptr(stream), len(grads))
+
+    def compress_sketch_all(self, n_ranks=None, stream=None):
+        """compress_sketch of the first n_ranks ranks, in the same launches."""
+        B.tagc_compress_ranks(self.plan, B.TAGC_PHASE_SKETCH, None, self.rk, self.shared,
+                              _stream_ptr(stream), self._n(n_ranks))
+
+    def _n(self, n_ranks):
+        return min(n_ranks or self.n_ranks, self.n_ranks)
+
     def aggregate_index(self, n_ranks=None, stream=None):
-        B.tagc_aggregate(self.plan, B.TAGC_PHASE_INDEX,
-                         self.rk[:n_ranks or self.n_ranks], self.shared,
-                         _stream_ptr(stream))
+        B.tagc_aggregate(self.plan, B.TAGC_PHASE_INDEX, self.rk, self.shared,
+                         _stream_ptr(stream), self._n(n_ranks))
 
     def compress_sketch(self, r, stream=None):
         B.tagc_compress(self.plan, B.TAGC_PHASE_SKETCH, None, self.rk[r], self.shared,
                         _stream_ptr(stream))
 
     def aggregate_sketch(self, n_ranks=None, stream=None):
-        B.tagc_aggregate(self.plan, B.TAGC_PHASE_SKETCH,
-                         self.rk[:n_ranks or self.n_ranks], self.shared,
-                         _stream_ptr(stream))
+        B.tagc_aggregate(self.plan, B.TAGC_PHASE_SKETCH, self.rk, self.shared,
+                         _stream_ptr(stream), self._n(n_ranks))
 
     def decompress(self, stream=None, whole_device=False):
         plan = self.plan_whole if whole_device and self.plan_whole is not None else self.plan
@@ -168,20 +186,19 @@ class TagcBucket:
     def reduce_decompress(self, n_ranks=None, stream=None, whole_device=False):
         """Sketch sum and decode in one call (the summed sketch is never written)."""
         plan = self.plan_whole if whole_device and self.plan_whole is not None else self.plan
-        B.tagc_reduce_decompress(plan, self.rk[:n_ranks or self.n_ranks], self.shared,
+        B.tagc_reduce_decompress(plan, self.rk, self.shared,
                                  self.out_idx.data_ptr(), self.out_val.data_ptr(),
                                  self.out_dense.data_ptr() if self.out_dense is not None else None,
-                                 _stream_ptr(stream))
+                                 _stream_ptr(stream), self._n(n_ranks))
 
     def run(self, grads, stream=None, whole_device_decode=False, fused=False):
         """The whole hot path for one bucket; grads[r] is rank r's buffer.  `fused`: the
         sketches are summed by the decoder (tagc_reduce_decompress)."""
         n = len(grads)
-        for r in range(n):
-            self.compress_index(r, grads[r], stream)
+        stream = stream if stream is not None else torch.cuda.current_stream()
+        self.compress_index_all(grads, stream)
         self.aggregate_index(n, stream)
-        for r in range(n):
-            self.compress_sketch(r, stream)
+        self.compress_sketch_all(n, stream)
         if fused:
             self.reduce_decompress(n, stream, whole_device_decode)
         else:

@@ -164,6 +164,24 @@ __device__ inline void wait_own_memory_ops()
     __builtin_amdgcn_s_waitcnt(0x0F70);
 }
 
+// Row `i` of a kernel's first argument, an array of structs passed by value: read where it
+// lies, in the kernel argument segment (explicit arguments lie there in declaration order),
+// because indexing the argument itself with a run-time number would copy all of it to the
+// stack first.
+template <typename Row>
+__device__ inline const __attribute__((address_space(4))) Row *batch_row(uint32_t i)
+{
+    return (const __attribute__((address_space(4))) Row *)__builtin_amdgcn_kernarg_segment_ptr() + i;
+}
+
+// A pointer the kernel read from memory has no address space the compiler knows, and accesses
+// through it would be flat ones, which can only be waited for all at once.
+template <typename T>
+__device__ inline T *as_global(T *p)
+{
+    return (T *)(__attribute__((address_space(1))) T *)p;
+}
+
 __device__ inline uint64_t ld_agent(const uint64_t *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -293,22 +293,33 @@ static int check_shared(const tagc_shared_buffers *s)
     return TAGC_OK;
 }
 
+extern "C" int tagc_compress_ranks(const tagc_plan_t *p, uint32_t phase, const void *const *grads,
+                                   const tagc_rank_buffers *ranks, uint32_t n_ranks,
+                                   const tagc_shared_buffers *sh, void *stream)
+{
+    if (!p || !ranks || n_ranks == 0) return TAGC_EINVAL;
+    int rc = TAGC_OK;
+    for (uint32_t r = 0; r < n_ranks && !rc; ++r) rc = check_rank(&ranks[r]);
+    if (!rc) rc = check_shared(sh);
+    if (rc) return rc;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (phase == TAGC_PHASE_INDEX) {
+        if (!grads) return TAGC_EINVAL;
+        for (uint32_t r = 0; r < n_ranks; ++r)
+            if (!grads[r] || !aligned16(grads[r])) return TAGC_EINVAL;
+        for (uint32_t r = 0; r < n_ranks && !rc; ++r)
+            rc = launch_sparsify(p, grads[r], &ranks[r], sh, s);
+        return rc;
+    }
+    if (phase == TAGC_PHASE_SKETCH) return launch_encode(p, ranks, n_ranks, sh, s);
+    return TAGC_EINVAL;
+}
+
 extern "C" int tagc_compress(const tagc_plan_t *p, uint32_t phase, const void *grad,
                              const tagc_rank_buffers *rk, const tagc_shared_buffers *sh,
                              void *stream)
 {
-    if (!p) return TAGC_EINVAL;
-    int rc = check_rank(rk);
-    if (rc) return rc;
-    rc = check_shared(sh);
-    if (rc) return rc;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    if (phase == TAGC_PHASE_INDEX) {
-        if (!grad || !aligned16(grad)) return TAGC_EINVAL;
-        return launch_sparsify(p, grad, rk, sh, s);
-    }
-    if (phase == TAGC_PHASE_SKETCH) return launch_encode(p, rk, sh, s);
-    return TAGC_EINVAL;
+    return tagc_compress_ranks(p, phase, &grad, rk, 1, sh, stream);
 }
 
 extern "C" int tagc_compress_static(const tagc_plan_t *p, uint32_t phase, const void *grad,
