@@ -379,13 +379,11 @@ def main():
     def run_subset(tb, grads, s=None, phases=phases):
         """The calls of one bucket that --only-phases (or `phases`) names."""
         if "index" in phases:
-            for r in range(N):
-                tb.compress_index(r, grads[r], s)
+            tb.compress_index_all(grads, s)
         if "agg_index" in phases:
             tb.aggregate_index(N, s)
         if "sketch" in phases:
-            for r in range(N):
-                tb.compress_sketch(r, s)
+            tb.compress_sketch_all(N, s)
         if fused and "decode" in phases:
             tb.reduce_decompress(N, s)
         else:

@@ -222,7 +222,9 @@ typedef struct tagc_rank_buffers {
                            and, for float32 cells, 48 KiB behind them that
                            tagc_reduce_decompress may read (never use)         */
     void *workspace;    /* [rank_workspace_bytes] scratch, may be shared by ranks
-                           processed one after another on one stream           */
+                           processed one after another on one stream; ranks
+                           with workspaces of their own go together in
+                           tagc_compress_ranks                                 */
     void *acc;          /* NULL, or [grad_elems] of the plan's dtype: the rank's
                            gradient accumulator (Algorithm 1: acc in, acc_next
                            out, in place).  Together with `bitmap` it is the
@@ -236,10 +238,10 @@ typedef struct tagc_shared_buffers {
     const void *table;  /* [table_bytes] filled by tagc_plan_upload and from then
                            on written by the library only: behind the segment
                            rows PHASE_INDEX keeps the plan's device state there
-                           (one pre-threshold per segment, carried from call to
-                           call as a speed hint that results never depend on;
-                           counters and candidate histograms that every call
-                           leaves at zero again).  PHASE_INDEX calls that share
+                           (per rank slot and segment one pre-threshold, carried
+                           from call to call as a speed hint that results never
+                           depend on; counters and candidate histograms that
+                           every call leaves at zero again).  PHASE_INDEX calls that share
                            a table must not overlap in time                    */
     uint32_t *bitmap;   /* [bitmap_words] merged Index                          */
     float *sketch;      /* [sketch_cells_capacity] summed Count Sketch          */
@@ -312,8 +314,11 @@ int tagc_compress(const tagc_plan_t *plan, uint32_t phase, const void *grad_dev,
  * tagc_compress for n_ranks ranks on one GPU: equal to
  *   for r in 0 .. n_ranks-1: tagc_compress(plan, phase, grads[r], &ranks[r], shared, stream)
  * with the ranks' work in the same launches.  A launch's ramp-up, tail and turn-around
- * (about 5 us) are then paid once and not once per rank.  grads: host array of n_ranks
- * device pointers (not read, may be NULL, in PHASE_SKETCH); ranks: host array.
+ * (about 5 us) are then paid once and not once per rank.  In PHASE_INDEX neighbouring ranks
+ * go together as far as their workspaces differ (ranks that share one take turns) and each
+ * carries pre-thresholds of its own; in the first call after an upload they take turns and hand
+ * them on from rank to rank.  grads: host array of n_ranks device pointers
+ * (not read, may be NULL, in PHASE_SKETCH); ranks: host array.
  */
 int tagc_compress_ranks(const tagc_plan_t *plan, uint32_t phase, const void *const *grads,
                         const tagc_rank_buffers *ranks, uint32_t n_ranks,

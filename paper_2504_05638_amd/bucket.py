@@ -25,6 +25,8 @@ def _bytes(n, device):
 class TagcBucket:
     """One gradient bucket: plan + device buffers for `n_ranks` simulated ranks."""
 
+    _WORKSPACES_BYTES = 4 << 30
+
     def __init__(self, segments, dtype, n_ranks, sizing_milli=3000,
                  sizing=B.TAGC_SIZE_LOAD_FACTOR, seed=0, part_unknowns=0,
                  part_cells=0, device="cuda", dense=False, share=None, min_bytes=None,
@@ -70,7 +72,11 @@ class TagcBucket:
             self.sh_sketch.data_ptr(), self.sh_header.data_ptr(),
             self.sh_bounds.data_ptr(), self.sh_ws.data_ptr(),
             self.sh_status.data_ptr())
-        self.rank_ws = al("rank_ws", z.rank_workspace_bytes)  # ranks run in turn
+        # a workspace per rank, so that the ranks' sparsifiers share their launches; large buckets
+        # fill the device with fewer ranks at a time, and get no more than a few GiB of them
+        # (ranks that share one are sparsified one after the other)
+        n_ws = max(1, min(n_ranks, 32, self._WORKSPACES_BYTES // max(int(z.rank_workspace_bytes), 1)))
+        self.rank_ws = [al("rank_ws%d" % i, z.rank_workspace_bytes) for i in range(n_ws)]
         self.rk = (B.tagc_rank_buffers * n_ranks)()
         self._rk_tensors = []
         for r in range(n_ranks):
@@ -91,7 +97,7 @@ class TagcBucket:
             self.rk[r] = B.tagc_rank_buffers(
                 t["idx"].data_ptr(), t["val"].data_ptr(), t["cnt"].data_ptr(),
                 t["bitmap"].data_ptr(), t["sketch"].data_ptr(),
-                self.rank_ws.data_ptr(), t["acc"].data_ptr() if error_feedback else None)
+                self.rank_ws[r % n_ws].data_ptr(), t["acc"].data_ptr() if error_feedback else None)
         self.out_idx = al("out_idx", z.out_idx_bytes)
         self.out_val = al("out_val", z.out_val_bytes)
         self.out_dense = al("out_dense", z.out_dense_bytes) if dense else None

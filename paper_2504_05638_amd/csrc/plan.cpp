@@ -195,8 +195,9 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
     z.grad_elems = grad_elems;
     // header, one row per compressed segment, then the plan's device state (pre-thresholds,
     // arrival counters, candidate histograms: see TableState)
+    p->slots = std::min(cfg->n_ranks, kMaxRanksPerPass);
     z.table_bytes = 32 + 32 * std::max<uint64_t>(L, 1) +
-                    round_up(4 * table_state_words(std::max<uint64_t>(L, 1)), 16);
+                    4 * p->slots * table_slot_words(std::max<uint64_t>(L, 1));
     z.rank_idx_bytes = round_up(4 * std::max<uint64_t>(K, 1), 16);
     z.rank_val_bytes = z.rank_idx_bytes;
     // counts first, then (from the Index aggregation on) the A+1 positions at which the
@@ -264,9 +265,9 @@ extern "C" int tagc_plan_upload(const tagc_plan_t *p, void *table_dev, void *str
     // PHASE_INDEX call samples
     if (!p->table.empty() &&
         hipMemsetAsync(static_cast<char *>(table_dev) + 32 + p->table.size() * sizeof(SegDev), 0,
-                       4 * table_state_words(p->table.size()), s) != hipSuccess)
+                       4 * p->slots * table_slot_words(p->table.size()), s) != hipSuccess)
         return TAGC_EHIP;
-    p->sample_pending.store(1, std::memory_order_relaxed);
+    p->used.store(0, std::memory_order_relaxed);
     return TAGC_OK;
 }
 
@@ -307,9 +308,7 @@ extern "C" int tagc_compress_ranks(const tagc_plan_t *p, uint32_t phase, const v
         if (!grads) return TAGC_EINVAL;
         for (uint32_t r = 0; r < n_ranks; ++r)
             if (!grads[r] || !aligned16(grads[r])) return TAGC_EINVAL;
-        for (uint32_t r = 0; r < n_ranks && !rc; ++r)
-            rc = launch_sparsify(p, grads[r], &ranks[r], sh, s);
-        return rc;
+        return launch_sparsify(p, grads, ranks, n_ranks, sh, s);
     }
     if (phase == TAGC_PHASE_SKETCH) return launch_encode(p, ranks, n_ranks, sh, s);
     return TAGC_EINVAL;

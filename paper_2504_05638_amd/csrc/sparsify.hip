@@ -58,6 +58,58 @@ namespace {
 
 constexpr int kF32 = TAGC_F32, kBF16 = TAGC_BF16;
 
+// What a launch needs to know of one rank.  A launch takes a batch of ranks, blockIdx.y being the
+// rank's row: ranks are independent of each other up to the Index merge, and a launch of one
+// rank's work spends a good part of its time starting, draining and turning round (a rank's
+// scan of 405 MB streams for 57 us and takes 80).
+struct SparsifyRank {
+    const char *grad;
+    char *acc;             // error feedback: the accumulator, or NULL
+    const uint32_t *sent;  // error feedback: the Index the rank's previous call left
+    char *ws;              // the rank's workspace
+    uint32_t *idx;
+    float *val;
+    uint32_t *bitmap;      // 1-bit Index (in the workspace if the wire takes 4-bit counters)
+    uint32_t *wire;        // the rank's Index as it goes on the wire
+    uint32_t *cnt;
+    uint32_t slot;         // the rank's slot of the table's device state
+    uint32_t from;         // the slot whose carried pre-thresholds it starts from
+};
+struct SparsifyBatch {
+    SparsifyRank r[kMaxRanksPerPass];
+};
+static_assert(sizeof(SparsifyBatch) <= 3072, "kernel arguments are limited to 4 KiB");
+
+// Where things are in a rank's workspace, and how many candidate slots it has.
+struct WsLayout {
+    uint64_t hist1d, hist2, group_cnt, sel, tile_cnt, sc_cnt, chunk_info, cand, n_slots;
+};
+
+// The row of the rank a workgroup works for, its pointers known to be global memory.
+struct RankView {
+    const char *grad;
+    char *acc;
+    const uint32_t *sent;
+    char *ws;
+    uint32_t *idx;
+    float *val;
+    uint32_t *bitmap;
+    uint32_t *wire;
+    uint32_t *cnt;
+    uint32_t slot, from;
+    // what is sparsified: the gradient, or the sums in the accumulator
+    __device__ inline const char *src() const { return acc ? acc : grad; }
+    template <typename T>
+    __device__ inline T *at(uint64_t offset) const { return reinterpret_cast<T *>(ws + offset); }
+};
+__device__ inline RankView rank_view()
+{
+    const auto *r = batch_row<SparsifyRank>(blockIdx.y);
+    return RankView{as_global(r->grad), as_global(r->acc),    as_global(r->sent), as_global(r->ws),
+                    as_global(r->idx),  as_global(r->val),    as_global(r->bitmap),
+                    as_global(r->wire), as_global(r->cnt),    r->slot,            r->from};
+}
+
 __global__ void __launch_bounds__(256) fill_zero_kernel(uint4 *p, uint64_t n16, uint32_t *cnt,
                                                         uint32_t n_cnt)
 {
@@ -157,9 +209,12 @@ __device__ inline uint32_t unsent_word(uint32_t a, uint32_t bits, uint32_t j)
 // input from acc.  Workgroups stride over each such segment.
 template <int DTYPE>
 __global__ void __launch_bounds__(256)
-accumulate_kernel(const char *__restrict__ grad, const uint32_t *__restrict__ table, char *acc,
-                  const SentMap sent)
+accumulate_kernel(const SparsifyBatch, const uint32_t *__restrict__ table, uint32_t wire4)
 {
+    const RankView rv = rank_view();
+    const char *grad = rv.grad;
+    char *acc = rv.acc;
+    const SentMap sent{rv.sent, wire4};
     constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
     constexpr uint32_t VEC = 16 / EB;
     const uint32_t L = table[0];
@@ -344,19 +399,16 @@ __device__ inline bool select_bins_streamed(const uint32_t *hist, uint32_t need,
 
 // ---------------------------------------------------------------- prepare
 
-// First call after the table's upload (and plans without a scan to clear for them).  One
-// workgroup per compressed segment: segments on the candidate route that have no
-// pre-threshold yet get one from a strided sample of 16-byte vectors: the sample bin above
-// which  k*S/n + 5*sqrt(k*S/n) + 16  sampled entries lie.  The margin makes it very unlikely
-// that fewer than k entries of the whole segment pass the pre-threshold; if that still
-// happens the selection notices and re-routes the segment.  A sample that holds too few
-// non-zeros to say anything leaves the segment without one: it takes the dense route this
-// time, whose histogram then provides it.  The remaining workgroups clear the histograms of
-// the dense route when there is no scan to do it.
+// First call after the table's upload.  One workgroup per compressed segment:
+// segments on the candidate route that have no pre-threshold yet get one from a strided sample
+// of 16-byte vectors: the sample bin above which  k*S/n + 5*sqrt(k*S/n) + 16  sampled entries
+// lie.  The margin makes it very unlikely that fewer than k entries of the whole segment pass
+// the pre-threshold; if that still happens the selection notices and re-routes the segment.
+// A sample that holds too few non-zeros to say anything leaves the segment without one: it
+// takes the dense route this time, whose histogram then provides it.
 template <int DTYPE>
 __global__ void __launch_bounds__(kHistThreads)
-prepare_kernel(const char *__restrict__ grad, const char *acc, const SentMap sent,
-               uint32_t *table, uint4 *zero_base, uint64_t zero_n16)
+prepare_kernel(const SparsifyBatch, uint32_t *table, uint32_t wire4)
 {
     extern __shared__ uint32_t h[];
     __shared__ uint32_t smem[32];
@@ -364,17 +416,12 @@ prepare_kernel(const char *__restrict__ grad, const char *acc, const SentMap sen
     constexpr uint32_t VEC = 16 / EB;
     const uint32_t L = table[0];
     const uint32_t tid = threadIdx.x;
-    if (blockIdx.x >= L) {
-        const uint32_t fb = blockIdx.x - L, nfb = gridDim.x - L;
-        const uint4 z = make_uint4(0, 0, 0, 0);
-        for (uint64_t i = uint64_t(fb) * kHistThreads + tid; i < zero_n16;
-             i += uint64_t(nfb) * kHistThreads)
-            zero_base[i] = z;
-        return;
-    }
+    const RankView rv = rank_view();
+    const char *grad = rv.grad, *acc = rv.acc;
+    const SentMap sent{rv.sent, wire4};
     const uint32_t l = blockIdx.x;
     const SegDev sd = reinterpret_cast<const SegDev *>(table + 8)[l];
-    const TableState ts = table_state(table, L);
+    const TableState ts = table_state(table, L, rv.slot);
     if (sd.k == 0 || sd.n == 0 || !(sd.flags & kSegFast) || ts.hint[l]) return;
     for (uint32_t i = tid; i < kBins1; i += kHistThreads) h[i] = 0;
     __syncthreads();
@@ -476,7 +523,7 @@ __device__ inline uint32_t next_hint(uint32_t bin2, uint32_t prev, uint32_t watc
 
 template <int DTYPE>
 __device__ inline void select_window(uint32_t l, const SegDev &sd, uint32_t blo,
-                                     const TableState ts, SelDev *sel, uint32_t *smem /* >= 32 */)
+                                     const TableState ts, const TableState from, SelDev *sel, uint32_t *smem /* >= 32 */)
 {
     constexpr uint32_t BPT = kWinBins / kSpillThreads;  // consecutive bins per thread
     static_assert(BPT * kSpillThreads == kWinBins, "every thread owns BPT bins of the window");
@@ -490,7 +537,7 @@ __device__ inline void select_window(uint32_t l, const SegDev &sd, uint32_t blo,
     }
     const uint32_t above_w = win[kWinBins], nf = win[kWinBins + 1];
     const uint32_t raised = ts.raised[l], overflow = ts.reroute[l];
-    const uint32_t prev = ts.prev[l], wt = ts.watch[l];  // (requested with the rest)
+    const uint32_t prev = from.prev[l], wt = from.watch[l];  // (requested with the rest)
     __syncthreads();  // everybody has read what thread 0 clears next
     if (tid == 0) {
         win[kWinBins] = win[kWinBins + 1] = 0;
@@ -537,7 +584,8 @@ __device__ inline void select_window(uint32_t l, const SegDev &sd, uint32_t blo,
         // was tuned), the threshold lies above the window, slots overflowed, or there was no
         // pre-threshold: dense route, whose histogram also provides the next pre-threshold.
         r.route = 1;
-        if (blo != 0 && !overflow && above_w < sd.k) ts.watch[l] = kWatchCalls;
+        ts.watch[l] = blo != 0 && !overflow && above_w < sd.k ? kWatchCalls : wt;
+        ts.prev[l] = prev;
         ts.hint[l] = 0;
         sel[l] = r;
         return;
@@ -547,7 +595,7 @@ __device__ inline void select_window(uint32_t l, const SegDev &sd, uint32_t blo,
     const uint32_t bin2 = bin2_w != 0xFFFFFFFFu ? max(blo + bin2_w, 1u) : max(floor_bin, 2u) - 1u;
     ts.hint[l] = next_hint(bin2, prev, wt);
     ts.prev[l] = bin2;
-    if (wt) ts.watch[l] = wt - 1;
+    ts.watch[l] = wt ? wt - 1 : 0u;
     if (nf) atomicAdd(&ts.glob[1], nf);
     const uint32_t T_bin = blo + bin_w;
     if (DTYPE == kBF16) {
@@ -563,13 +611,21 @@ __device__ inline void select_window(uint32_t l, const SegDev &sd, uint32_t blo,
     sel[l] = r;
 }
 
-template <int DTYPE>
+// ACC: with a gradient accumulator (all ranks of a launch have one, or none).
+template <int DTYPE, bool ACC>
 __global__ void __launch_bounds__(kSpillThreads)
-scan_spill_kernel(const char *__restrict__ grad, char *acc, const SentMap sent,
-                  uint32_t *table, SelDev *sel, uint32_t *__restrict__ cand,
-                  uint2 *__restrict__ chunk_info, uint64_t n_slots_total, uint32_t CAP,
-                  uint4 *zero_base, uint64_t zero_n16)
+scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t CAP,
+                  uint64_t zero_n16, uint32_t wire4)
 {
+    const RankView rv = rank_view();
+    const char *__restrict__ grad = rv.grad;
+    char *acc = ACC ? rv.acc : nullptr;
+    const SentMap sent{rv.sent, wire4};
+    SelDev *sel = rv.at<SelDev>(wl.sel);
+    uint32_t *__restrict__ cand = rv.at<uint32_t>(wl.cand);
+    uint2 *__restrict__ chunk_info = rv.at<uint2>(wl.chunk_info);
+    const uint64_t n_slots_total = wl.n_slots;
+    uint4 *zero_base = rv.at<uint4>(0);
     constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
     constexpr uint32_t VEC = 16 / EB;
     constexpr uint32_t ROWS = kCandRows;
@@ -588,7 +644,7 @@ scan_spill_kernel(const char *__restrict__ grad, char *acc, const SentMap sent,
     const uint32_t L = table[0];
     const uint32_t total_chunks = table[4] * kCandChunksPerSuper;
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
-    const TableState ts = table_state(table, L);
+    const TableState ts = table_state(table, L, rv.slot), from = table_state(table, L, rv.from);
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     // wave-uniform by construction; saying so keeps chunk addresses in scalar registers
     const uint32_t wib = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -672,11 +728,11 @@ scan_spill_kernel(const char *__restrict__ grad, char *acc, const SentMap sent,
         // With an accumulator (error feedback) the segment is streamed all the same: this
         // pass is also the one that turns acc into grad + acc, which the dense route then
         // reads instead of the gradient.  Its candidates are then never used.
-        const uint32_t hint = ts.hint[l];
+        const uint32_t hint = from.hint[l];
         const uint32_t blo = hint ? hint : 0x7F7Fu;  // 1 <= blo <= 0x7FFF
-        if (hint || acc) {
+        if (hint || ACC) {
             const char *base = grad + sd.offset * EB;
-            char *abase = acc ? acc + sd.offset * EB : nullptr;
+            char *abase = ACC ? acc + sd.offset * EB : nullptr;
             // The wave's own pre-threshold: starts at the segment's and goes up when a chunk
             // holds more candidates than it has slots (see below).
             uint32_t blo_w = blo, swar_add = (0x8000u - blo) * 0x10001u;
@@ -755,13 +811,13 @@ scan_spill_kernel(const char *__restrict__ grad, char *acc, const SentMap sent,
             uint32_t w[ROWS][4], aw[ROWS][4], sb[ROWS];
             if (lo + wib < hi) {
                 load_chunk(base, lo + wib, w);
-                if (acc) {
+                if (ACC) {
                     load_chunk(abase, lo + wib, aw);
                     load_sent(lo + wib, sb);
                 }
             }
             for (uint32_t ch = lo + wib; ch < hi; ch += NW) {
-                if (acc) {  // error feedback: sparsify grad + acc, and keep the sums
+                if (ACC) {  // error feedback: sparsify grad + acc, and keep the sums
 #pragma unroll
                     for (uint32_t r = 0; r < ROWS; ++r)
 #pragma unroll
@@ -796,12 +852,12 @@ scan_spill_kernel(const char *__restrict__ grad, char *acc, const SentMap sent,
                 }
                 if (ch + NW < hi) {  // in flight during the rest
                     load_chunk(base, ch + NW, w);
-                    if (acc) {
+                    if (ACC) {
                         load_chunk(abase, ch + NW, aw);
                         load_sent(ch + NW, sb);
                     }
                 }
-                if (acc) store_chunk(ch);
+                if (ACC) store_chunk(ch);
                 // slot of each lane's first candidate per row: one scan over the four
                 // row counts packed in 16-bit fields (a row holds at most 512 candidates)
                 uint32_t p01, p23, total;
@@ -934,7 +990,7 @@ scan_spill_kernel(const char *__restrict__ grad, char *acc, const SentMap sent,
         __syncthreads();
         if (s_last) {  // uniform
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            select_window<DTYPE>(l, sd, hint, ts, sel, s_sel);
+            select_window<DTYPE>(l, sd, hint, ts, from, sel, s_sel);
         }
         __syncthreads();
     }
@@ -1076,8 +1132,12 @@ constexpr uint32_t kHistNetThreads = 256;
 
 template <int DTYPE, uint32_t WBINS, uint32_t NT>
 __global__ void __launch_bounds__(NT)
-hist1_kernel(const char *__restrict__ grad, uint32_t *table, SelDev *sel, uint32_t *hist)
+hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
 {
+    const RankView rv = rank_view();
+    const char *grad = rv.src();
+    SelDev *sel = rv.at<SelDev>(wl.sel);
+    uint32_t *hist = rv.at<uint32_t>(wl.hist1d);
     extern __shared__ uint32_t h[];
     __shared__ uint32_t s_sel[32];
     __shared__ uint32_t s_last;
@@ -1086,7 +1146,7 @@ hist1_kernel(const char *__restrict__ grad, uint32_t *table, SelDev *sel, uint32
     const uint32_t L = table[0];
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     if (!any_dense_route(segs, sel, L)) return;
-    const TableState ts = table_state(table, L);
+    const TableState ts = table_state(table, L, rv.slot);
     const uint32_t tid = threadIdx.x;
     for (uint32_t i = tid; i < WBINS; i += NT) h[i] = 0;
     __syncthreads();
@@ -1151,9 +1211,12 @@ hist1_kernel(const char *__restrict__ grad, uint32_t *table, SelDev *sel, uint32
 
 // fp32, dense route: histogram of the low 16 key bits of the entries in the threshold bin.
 __global__ void __launch_bounds__(256)
-hist2_kernel(const char *__restrict__ grad, const uint32_t *__restrict__ table,
-             const SelDev *__restrict__ sel, uint32_t *__restrict__ hist2)
+hist2_kernel(const SparsifyBatch, const uint32_t *__restrict__ table, const WsLayout wl)
 {
+    const RankView rv = rank_view();
+    const char *grad = rv.src();
+    const SelDev *sel = rv.at<SelDev>(wl.sel);
+    uint32_t *hist2 = rv.at<uint32_t>(wl.hist2);
     const uint32_t L = table[0];
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     if (!any_dense_route(segs, sel, L)) return;
@@ -1194,10 +1257,15 @@ hist2_kernel(const char *__restrict__ grad, const uint32_t *__restrict__ table,
 
 // fp32, candidate route: the same histogram from the spilled candidates.
 __global__ void __launch_bounds__(256)
-hist2c_kernel(const uint32_t *__restrict__ table, const SelDev *__restrict__ sel,
-              const uint32_t *__restrict__ cand, const uint2 *__restrict__ chunk_info,
-              uint32_t n_slots_total, uint32_t CAP, uint32_t *__restrict__ hist2)
+hist2c_kernel(const SparsifyBatch, const uint32_t *__restrict__ table, const WsLayout wl,
+              uint32_t CAP)
 {
+    const RankView rv = rank_view();
+    const SelDev *sel = rv.at<SelDev>(wl.sel);
+    const uint32_t *cand = rv.at<uint32_t>(wl.cand);
+    const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
+    const uint32_t n_slots_total = uint32_t(wl.n_slots);
+    uint32_t *hist2 = rv.at<uint32_t>(wl.hist2);
     constexpr uint32_t CHUNK = 64 * 4 * kCandRows;
     const uint32_t L = table[0];
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
@@ -1223,8 +1291,11 @@ hist2c_kernel(const uint32_t *__restrict__ table, const SelDev *__restrict__ sel
 }
 
 __global__ void __launch_bounds__(kHistThreads)
-select2_kernel(uint32_t *table, const uint32_t *__restrict__ hist2, SelDev *__restrict__ sel)
+select2_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
 {
+    const RankView rv = rank_view();
+    SelDev *sel = rv.at<SelDev>(wl.sel);
+    const uint32_t *hist2 = rv.at<uint32_t>(wl.hist2);
     __shared__ uint32_t smem[32];
     const uint32_t l = blockIdx.x;
     const SegDev sd = reinterpret_cast<const SegDev *>(table + 8)[l];
@@ -1238,7 +1309,7 @@ select2_kernel(uint32_t *table, const uint32_t *__restrict__ hist2, SelDev *__re
     if (!found) {  // cannot happen when both histograms saw the same data
         bin = 0;
         above = total;
-        atomicOr(&table_state(table, table[0]).glob[0], TAGC_FLAG_OVERFLOW);
+        atomicOr(&table_state(table, table[0], rv.slot).glob[0], TAGC_FLAG_OVERFLOW);
     }
     r.T = (r.bin1 << 16) | bin;
     r.G = r.G1 + above;
@@ -1277,8 +1348,8 @@ __device__ inline uint32_t segment_count(const SegDev &sd, const SelDev *sel, ui
 
 // The rank's count words, from the selections and what the call's kernels accumulated in
 // the table (which goes back to zero); by one workgroup of the last kernel.
-__device__ inline void write_rank_counts(uint32_t *table, const SelDev *sel, uint32_t *cnt,
-                                         uint32_t *smem /* >= 8 */)
+__device__ inline void write_rank_counts(uint32_t *table, uint32_t slot, const SelDev *sel,
+                                         uint32_t *cnt, uint32_t *smem /* >= 8 */)
 {
     const uint32_t L = table[0];
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
@@ -1290,7 +1361,7 @@ __device__ inline void write_rank_counts(uint32_t *table, const SelDev *sel, uin
     }
     total = block_sum<uint32_t, kEmitThreads / 64>(total, smem);
     if (threadIdx.x == 0) {
-        const TableState ts = table_state(table, L);
+        const TableState ts = table_state(table, L, slot);
         cnt[TAGC_CNT_TOTAL] = total;
         cnt[TAGC_CNT_FLAGS] = ts.glob[0];
         cnt[TAGC_CNT_NONFINITE] = ts.glob[1];
@@ -1950,49 +2021,53 @@ static_assert(kEmitThreads == kCompactThreads, "one launch for both parts");
 
 template <int DTYPE, uint32_t COMPACT_ROWS, bool WIDE>
 __global__ void __launch_bounds__(kEmitThreads)
-count_kernel(uint32_t n_emit, const char *grad, const uint32_t *__restrict__ table,
-             const SelDev *__restrict__ sel, const uint32_t *__restrict__ cand,
-             const uint2 *__restrict__ chunk_info, uint64_t n_slots_total, uint32_t CAP,
-             uint64_t *sc_cnt, uint64_t *tile_cnt, uint64_t *group_cnt)
+count_kernel(const SparsifyBatch, uint32_t n_emit, const uint32_t *__restrict__ table,
+             const WsLayout wl, uint32_t CAP)
 {
+    const RankView rv = rank_view();
+    const SelDev *sel = rv.at<SelDev>(wl.sel);
     if (blockIdx.x < n_emit) {
+        const uint32_t *cand = rv.at<uint32_t>(wl.cand);
+        const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
+        uint64_t *sc_cnt = rv.at<uint64_t>(wl.sc_cnt);
         if (WIDE)
             emit_wide_body<DTYPE, false, 32>(blockIdx.x, n_emit, table, sel, cand, chunk_info,
-                                         n_slots_total, CAP, sc_cnt, nullptr, nullptr, nullptr);
+                                             wl.n_slots, CAP, sc_cnt, nullptr, nullptr, nullptr);
         else
-            emit_body<DTYPE, false>(blockIdx.x, n_emit, table, sel, cand, chunk_info,
-                                    n_slots_total, CAP, sc_cnt, nullptr, nullptr, nullptr);
+            emit_body<DTYPE, false>(blockIdx.x, n_emit, table, sel, cand, chunk_info, wl.n_slots,
+                                    CAP, sc_cnt, nullptr, nullptr, nullptr);
     } else
-        compact_body<DTYPE, COMPACT_ROWS, false>(blockIdx.x - n_emit, gridDim.x - n_emit, grad,
-                                                 table, sel, tile_cnt, group_cnt, nullptr, nullptr,
-                                                 nullptr);
+        compact_body<DTYPE, COMPACT_ROWS, false>(
+            blockIdx.x - n_emit, gridDim.x - n_emit, rv.src(), table, sel,
+            rv.at<uint64_t>(wl.tile_cnt), rv.at<uint64_t>(wl.group_cnt), nullptr, nullptr, nullptr);
 }
 
 template <int DTYPE, uint32_t COMPACT_ROWS, bool WIDE>
 __global__ void __launch_bounds__(kEmitThreads)
     __attribute__((amdgpu_waves_per_eu(COMPACT_ROWS == 2 ? 7 : 6, 8)))
-place_kernel(uint32_t n_emit, const char *grad, uint32_t *table,
-             const SelDev *__restrict__ sel, const uint32_t *__restrict__ cand,
-             const uint2 *__restrict__ chunk_info, uint64_t n_slots_total, uint32_t CAP,
-             uint64_t *sc_cnt, uint64_t *tile_cnt, uint64_t *group_cnt,
-             uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
-             uint32_t *__restrict__ bitmap, uint32_t *cnt)
+place_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t *table, const WsLayout wl, uint32_t CAP)
 {
+    const RankView rv = rank_view();
+    const SelDev *sel = rv.at<SelDev>(wl.sel);
     if (blockIdx.x == gridDim.x - 1) {  // (any one workgroup: the last has the least to do)
         __shared__ uint32_t s_cnt[8];
-        write_rank_counts(table, sel, cnt, s_cnt);
+        write_rank_counts(table, rv.slot, sel, rv.cnt, s_cnt);
     }
     if (blockIdx.x < n_emit) {
+        const uint32_t *cand = rv.at<uint32_t>(wl.cand);
+        const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
+        uint64_t *sc_cnt = rv.at<uint64_t>(wl.sc_cnt);
         if (WIDE)
             emit_wide_body<DTYPE, true, 16>(blockIdx.x, n_emit, table, sel, cand, chunk_info,
-                                        n_slots_total, CAP, sc_cnt, idx_out, val_out, bitmap);
+                                            wl.n_slots, CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
         else
-            emit_body<DTYPE, true>(blockIdx.x, n_emit, table, sel, cand, chunk_info,
-                                   n_slots_total, CAP, sc_cnt, idx_out, val_out, bitmap);
+            emit_body<DTYPE, true>(blockIdx.x, n_emit, table, sel, cand, chunk_info, wl.n_slots,
+                                   CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
     } else
-        compact_body<DTYPE, COMPACT_ROWS, true>(blockIdx.x - n_emit, gridDim.x - n_emit, grad,
-                                                table, sel, tile_cnt, group_cnt, idx_out, val_out,
-                                                bitmap);
+        compact_body<DTYPE, COMPACT_ROWS, true>(blockIdx.x - n_emit, gridDim.x - n_emit, rv.src(),
+                                                table, sel, rv.at<uint64_t>(wl.tile_cnt),
+                                                rv.at<uint64_t>(wl.group_cnt), rv.idx, rv.val,
+                                                rv.bitmap);
 }
 
 template <typename K>
@@ -2064,8 +2139,11 @@ __device__ __forceinline__ uint32_t spread8(uint32_t b)  // bit p of a byte -> b
 }
 
 __global__ void __launch_bounds__(256)
-widen4_kernel(const uint32_t *__restrict__ map, uint32_t n_words, uint32_t *__restrict__ wire)
+widen4_kernel(const SparsifyBatch, uint32_t n_words)
 {
+    const RankView rv = rank_view();
+    const uint32_t *__restrict__ map = rv.bitmap;
+    uint32_t *__restrict__ wire = rv.wire;
     const uint32_t w = blockIdx.x * 256 + threadIdx.x;
     if (w >= n_words) return;
     const uint32_t m = map[w];
@@ -2074,97 +2152,107 @@ widen4_kernel(const uint32_t *__restrict__ map, uint32_t n_words, uint32_t *__re
                          spread8((m >> 16) & 0xFFu), spread8(m >> 24)));
 }
 
-template <int DTYPE>
-int launch_sparsify_t(const tagc_plan_t *p, const void *grad, const tagc_rank_buffers *rk,
-                      const tagc_shared_buffers *sh, hipStream_t s)
+WsLayout ws_layout(const tagc_plan_t *p)
 {
-    const uint32_t L = uint32_t(p->table.size());
-    // the table is the plan's device state as well (pre-thresholds, counters): written here
-    uint32_t *table = static_cast<uint32_t *>(const_cast<void *>(sh->table));
-    char *ws = static_cast<char *>(rk->workspace);
-    uint32_t *hist1d = reinterpret_cast<uint32_t *>(ws + p->ws.hist1d);
-    uint32_t *hist2 = reinterpret_cast<uint32_t *>(ws + p->ws.hist2);
-    uint64_t *tile_cnt = reinterpret_cast<uint64_t *>(ws + p->ws.tile_cnt);
-    uint64_t *group_cnt = reinterpret_cast<uint64_t *>(ws + p->ws.group_cnt);
-    uint64_t *sc_cnt = reinterpret_cast<uint64_t *>(ws + p->ws.sc_cnt);
-    SelDev *sel = reinterpret_cast<SelDev *>(ws + p->ws.sel);
-    uint2 *chunk_info = reinterpret_cast<uint2 *>(ws + p->ws.chunk_info);
-    uint32_t *cand = reinterpret_cast<uint32_t *>(ws + p->ws.cand);
-    const uint64_t n_slots = uint64_t(p->total_sc) * kCandChunksPerSuper * p->cand_cap;
-    const char *g = static_cast<const char *>(grad);
+    return WsLayout{p->ws.hist1d,   p->ws.hist2,  p->ws.group_cnt,  p->ws.sel,
+                    p->ws.tile_cnt, p->ws.sc_cnt, p->ws.chunk_info, p->ws.cand,
+                    uint64_t(p->total_sc) * kCandChunksPerSuper * p->cand_cap};
+}
+
+SparsifyRank sparsify_rank(const tagc_plan_t *p, const void *grad, const tagc_rank_buffers &rk,
+                           uint32_t slot, uint32_t from)
+{
+    char *ws = static_cast<char *>(rk.workspace);
     // with 4-bit counters on the wire the 1-bit Index is built in the workspace and widened
+    return SparsifyRank{static_cast<const char *>(grad),
+                        static_cast<char *>(rk.acc),
+                        rk.bitmap,
+                        ws,
+                        rk.idx,
+                        rk.val,
+                        p->cfg.index_mode == TAGC_INDEX_ADD4
+                            ? reinterpret_cast<uint32_t *>(ws + p->ws.bitmap1)
+                            : rk.bitmap,
+                        rk.bitmap,
+                        rk.cnt,
+                        slot,
+                        from};
+}
+
+// The first kernels of PHASE_INDEX, up to every segment's threshold (fp32: its upper half), for
+// n ranks with workspaces and table slots of their own, all with an accumulator (`acc`) or none
+// with one.  `sample`: no pre-threshold is known yet.
+//
+// Error feedback: scan_spill (candidate route) and accumulate_kernel (all other segments) turn
+// acc into grad + acc; whoever reads the input after them reads it from acc.  Both read acc
+// through the Index this rank's previous call left in rk->bitmap (what was sent reads as 0)
+// before place / widen4 overwrite that Index with the new one.
+template <int DTYPE>
+int launch_select(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, bool acc, bool sample,
+                  uint32_t *table, hipStream_t s)
+{
+    const WsLayout wl = ws_layout(p);
     const bool wide = p->cfg.index_mode == TAGC_INDEX_ADD4;
-    uint32_t *bitmap1 = wide ? reinterpret_cast<uint32_t *>(ws + p->ws.bitmap1) : rk->bitmap;
-    // Error feedback: scan_spill (candidate route) and accumulate_kernel (all other segments)
-    // turn acc into grad + acc; whoever reads the input after them reads it from acc.  Both
-    // read acc through the Index this rank's previous call left in rk->bitmap (what was
-    // sent reads as 0) before place / widen4 overwrite that Index with the new one.
-    char *acc = static_cast<char *>(rk->acc);
-    const char *src = acc ? acc : g;
-    const SentMap sent{rk->bitmap, wide ? 1u : 0u};
     const int cus = device_cu_count();
     const size_t lds_hist = kBins1 * sizeof(uint32_t);
     static bool a_prepare = false, a_hist = false;
-    static int occ_place[2][2] = {{0, 0}, {0, 0}};
-
-    if (L == 0 || (p->total_sc == 0 && p->total_tiles == 0)) {
-        // nothing is compressed (or every compressed segment is empty): only the counts
-        // have to read zero
-        ProfileScope ps("fill_zero", s);
-        fill_zero_kernel<<<1, 256, 0, s>>>(reinterpret_cast<uint4 *>(ws), 0, rk->cnt,
-                                           TAGC_CNT_SEG0 + L);
-        return hip_ok(hipGetLastError());
-    }
     if (allow_lds(prepare_kernel<DTYPE>, lds_hist, &a_prepare) ||
         allow_lds(hist1_kernel<DTYPE, kBins1, kHistThreads>, lds_hist, &a_hist))
         return TAGC_EHIP;
+    // `total` workgroups shared out to the ranks
+    auto per_rank = [&](uint32_t total) { return std::max(1u, total / n); };
     if (acc && p->any_nonfast) {
         ProfileScope ps("accumulate", s);
-        accumulate_kernel<DTYPE><<<cus * 4, 256, 0, s>>>(g, table, acc, sent);
+        accumulate_kernel<DTYPE><<<dim3(per_rank(cus * 4), n), 256, 0, s>>>(sb, table, wide);
     }
-    // the dense route's histograms are cleared by the scan as it starts, or, where there is
-    // no scan, by prepare; which also samples pre-thresholds on the first call after an upload
-    const uint64_t zero_n16 = p->zero_bytes / 16;
-    const bool sample = p->sample_pending.exchange(0, std::memory_order_relaxed) != 0;
-    if (sample || !p->total_sc) {
+    if (sample) {
         ProfileScope ps("prepare", s);
-        const uint64_t n16 = p->total_sc ? 0 : zero_n16;
-        const uint32_t fill_blocks = uint32_t(
-            std::max<uint64_t>(1, std::min<uint64_t>((n16 + kHistThreads - 1) / kHistThreads, cus)));
-        prepare_kernel<DTYPE><<<L + fill_blocks, kHistThreads, lds_hist, s>>>(
-            g, acc, sent, table, reinterpret_cast<uint4 *>(ws), n16);
+        prepare_kernel<DTYPE><<<dim3(uint32_t(p->table.size()), n), kHistThreads, lds_hist, s>>>(
+            sb, table, wide);
     }
-    if (p->total_sc) {
+    {
         ProfileScope ps("scan_spill", s);
-        scan_spill_kernel<DTYPE><<<cus * kSpillWgsPerCU, kSpillThreads, 0, s>>>(
-            g, acc, sent, table, sel, cand, chunk_info, n_slots, p->cand_cap,
-            reinterpret_cast<uint4 *>(ws), zero_n16);
+        auto scan = acc ? scan_spill_kernel<DTYPE, true> : scan_spill_kernel<DTYPE, false>;
+        scan<<<dim3(per_rank(cus * kSpillWgsPerCU), n), kSpillThreads, 0, s>>>(
+            sb, table, wl, p->cand_cap, p->zero_bytes / 16, wide);
     }
     {
         // leaves at once unless a segment is on the dense route (by plan, or because the
         // scan's selection sent it there)
         ProfileScope ps("hist1", s);
         if (p->static_dense)
-            hist1_kernel<DTYPE, kBins1, kHistThreads><<<cus, kHistThreads, lds_hist, s>>>(
-                src, table, sel, hist1d);
+            hist1_kernel<DTYPE, kBins1, kHistThreads>
+                <<<dim3(per_rank(cus), n), kHistThreads, lds_hist, s>>>(sb, table, wl);
         else
             hist1_kernel<DTYPE, kHistWindow, kHistNetThreads>
-                <<<cus * (kHistThreads / kHistNetThreads), kHistNetThreads,
-                   kHistWindow * sizeof(uint32_t), s>>>(src, table, sel, hist1d);
+                <<<dim3(per_rank(cus * (kHistThreads / kHistNetThreads)), n), kHistNetThreads,
+                   kHistWindow * sizeof(uint32_t), s>>>(sb, table, wl);
     }
+    return TAGC_OK;
+}
+
+// The rest of PHASE_INDEX for the same ranks: the thresholds' lower half (fp32), counts, output.
+template <int DTYPE>
+int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uint32_t *table,
+                  hipStream_t s)
+{
+    const WsLayout wl = ws_layout(p);
+    const uint32_t L = uint32_t(p->table.size());
+    const int cus = device_cu_count();
+    static int occ_place[2][2] = {{0, 0}, {0, 0}};
+    auto per_rank = [&](uint32_t total) { return std::max(1u, total / n); };
     if (DTYPE == kF32) {
-        if (p->total_sc) {
+        {
             ProfileScope ps("hist2c", s);
-            hist2c_kernel<<<cus * 4, 256, 0, s>>>(table, sel, cand, chunk_info, uint32_t(n_slots),
-                                                  p->cand_cap, hist2);
+            hist2c_kernel<<<dim3(per_rank(cus * 4), n), 256, 0, s>>>(sb, table, wl, p->cand_cap);
         }
         {
             ProfileScope ps("hist2", s);
-            hist2_kernel<<<cus * 8, 256, 0, s>>>(src, table, sel, hist2);
+            hist2_kernel<<<dim3(per_rank(cus * 8), n), 256, 0, s>>>(sb, table, wl);
         }
         {
             ProfileScope ps("select2", s);
-            select2_kernel<<<L, kHistThreads, 0, s>>>(table, hist2, sel);
+            select2_kernel<<<dim3(L, n), kHistThreads, 0, s>>>(sb, table, wl);
         }
     }
     {
@@ -2186,26 +2274,73 @@ int launch_sparsify_t(const tagc_plan_t *p, const void *grad, const tagc_rank_bu
         // tiles in turns then.
         const uint32_t n_compact =
             p->static_dense ? p->total_tiles
-                            : std::min<uint32_t>(p->total_tiles, uint32_t(cus) * uint32_t(occ));
+                            : std::min<uint32_t>(p->total_tiles,
+                                                 per_rank(uint32_t(cus) * uint32_t(occ)));
         {
             ProfileScope ps("count", s);
-            count<<<n_emit + n_compact, kEmitThreads, 0, s>>>(
-                n_emit, src, table, sel, cand, chunk_info, n_slots, p->cand_cap, sc_cnt, tile_cnt,
-                group_cnt);
+            count<<<dim3(n_emit + n_compact, n), kEmitThreads, 0, s>>>(sb, n_emit, table, wl,
+                                                                       p->cand_cap);
         }
         {
             ProfileScope ps("place", s);
-            place<<<n_emit + n_compact, kEmitThreads, 0, s>>>(
-                n_emit, src, table, sel, cand, chunk_info, n_slots, p->cand_cap, sc_cnt, tile_cnt,
-                group_cnt, rk->idx, rk->val, bitmap1, rk->cnt);
+            place<<<dim3(n_emit + n_compact, n), kEmitThreads, 0, s>>>(sb, n_emit, table, wl,
+                                                                       p->cand_cap);
         }
     }
-    if (wide && p->n_c) {
+    if (p->cfg.index_mode == TAGC_INDEX_ADD4 && p->n_c) {
         ProfileScope ps("widen4", s);
         const uint32_t n_words = uint32_t(p->n_c / 32);
-        widen4_kernel<<<(n_words + 255) / 256, 256, 0, s>>>(bitmap1, n_words, rk->bitmap);
+        widen4_kernel<<<dim3((n_words + 255) / 256, n), 256, 0, s>>>(sb, n_words);
     }
     return hip_ok(hipGetLastError());
+}
+
+// PHASE_INDEX of n ranks with workspaces and table slots (slot0 and following) of their own.
+template <int DTYPE>
+int launch_sparsify_t(const tagc_plan_t *p, const void *const *grads, const tagc_rank_buffers *ranks,
+                      uint32_t n, uint32_t slot0, const tagc_shared_buffers *sh, hipStream_t s)
+{
+    const uint32_t L = uint32_t(p->table.size());
+    // the table is the plan's device state as well (pre-thresholds, counters): written here
+    uint32_t *table = static_cast<uint32_t *>(const_cast<void *>(sh->table));
+    if (L == 0 || (p->total_sc == 0 && p->total_tiles == 0)) {
+        // nothing is compressed (or every compressed segment is empty): only the counts
+        // have to read zero
+        for (uint32_t r = 0; r < n; ++r) {
+            ProfileScope ps("fill_zero", s);
+            fill_zero_kernel<<<1, 256, 0, s>>>(static_cast<uint4 *>(ranks[r].workspace), 0,
+                                               ranks[r].cnt, TAGC_CNT_SEG0 + L);
+        }
+        return hip_ok(hipGetLastError());
+    }
+    const bool acc = ranks[0].acc != nullptr;
+    SparsifyBatch sb{};
+    SparsifyBatch part{};  // the ranks whose thresholds are launched next
+    uint32_t n_part = 0;
+    bool sample = false;
+    auto select = [&]() -> int {
+        if (!n_part) return TAGC_OK;
+        const int rc = launch_select<DTYPE>(p, part, n_part, acc, sample, table, s);
+        n_part = 0;
+        sample = false;
+        return rc;
+    };
+    for (uint32_t r = 0; r < n; ++r) {
+        // A rank whose slot of the table's state has not been used since the upload starts
+        // from the pre-thresholds of the rank before it (slot 0: from a sample), so it has
+        // to wait for those: one launch of the first kernels each, just this once.
+        const uint32_t slot = (slot0 + r) % p->slots, bit = 1u << slot;
+        const bool fresh = !(p->used.fetch_or(bit, std::memory_order_relaxed) & bit);
+        if (fresh)
+            if (const int rc = select()) return rc;
+        sb.r[r] = part.r[n_part++] =
+            sparsify_rank(p, grads[r], ranks[r], slot, fresh && slot ? slot - 1 : slot);
+        sample = fresh && slot == 0;
+        if (fresh)
+            if (const int rc = select()) return rc;
+    }
+    if (const int rc = select()) return rc;
+    return launch_output<DTYPE>(p, sb, n, table, s);
 }
 
 }  // namespace
@@ -2223,11 +2358,28 @@ int launch_feedback_apply(const tagc_plan_t *p, const tagc_rank_buffers *rk,
     return hip_ok(hipGetLastError());
 }
 
-int launch_sparsify(const tagc_plan_t *p, const void *grad, const tagc_rank_buffers *rk,
-                    const tagc_shared_buffers *sh, hipStream_t s)
+int launch_sparsify(const tagc_plan_t *p, const void *const *grads, const tagc_rank_buffers *ranks,
+                    uint32_t n_ranks, const tagc_shared_buffers *sh, hipStream_t s)
 {
-    return p->cfg.dtype == TAGC_BF16 ? launch_sparsify_t<kBF16>(p, grad, rk, sh, s)
-                                     : launch_sparsify_t<kF32>(p, grad, rk, sh, s);
+    for (uint32_t r0 = 0; r0 < n_ranks;) {
+        // The longest run of ranks that can go together: workspaces of their own (ranks that
+        // share one have to take turns), a slot of the table's state each, and all with an
+        // accumulator or none with one.
+        uint32_t n = 1;
+        auto joins = [&](uint32_t r) {
+            if ((ranks[r].acc != nullptr) != (ranks[r0].acc != nullptr)) return false;
+            for (uint32_t q = r0; q < r; ++q)
+                if (ranks[q].workspace == ranks[r].workspace) return false;
+            return true;
+        };
+        while (r0 + n < n_ranks && n < p->slots && joins(r0 + n)) ++n;
+        const int rc = p->cfg.dtype == TAGC_BF16
+                           ? launch_sparsify_t<kBF16>(p, grads + r0, ranks + r0, n, r0, sh, s)
+                           : launch_sparsify_t<kF32>(p, grads + r0, ranks + r0, n, r0, sh, s);
+        if (rc) return rc;
+        r0 += n;
+    }
+    return TAGC_OK;
 }
 
 // ------------------------------------------------ workspace without a caller

@@ -85,7 +85,7 @@ struct Workspace {  // byte offsets inside a rank workspace
     uint64_t sel, tile_cnt, sc_cnt, chunk_info, cand, bitmap1, total;
 };
 
-// Device state of a plan, kept behind the segment rows of its table: all zero after
+// Device state of a plan (per rank slot), kept behind the segment rows of its table: all zero after
 // tagc_plan_upload, and every PHASE_INDEX call leaves it as it found it except for the
 // pre-thresholds, which are what is carried from call to call.  It lives with the table and
 // not in a rank workspace because nobody but the library writes the table: counters that
@@ -101,16 +101,21 @@ struct TableState {
     uint32_t *glob;      // [8] flags, non-finite inputs, dense-route segments of the call
     uint32_t *win;       // [L][kWinWords] candidate histograms
 };
-__host__ __device__ inline TableState table_state(uint32_t *table, uint32_t L)
+// A table holds one such state per rank slot: ranks whose work is in the same launches
+// (tagc_compress_ranks) must not share counters, and each then carries its own pre-thresholds.
+constexpr uint64_t table_slot_words(uint64_t L)
 {
-    // behind the 32-byte rows: the histograms (a multiple of 32 bytes each), then the rest
-    uint32_t *w = table + 8 + 8 * size_t(L);
+    return L * kWinWords + 8 + (7 * L + 7) / 8 * 8;
+}
+__host__ __device__ inline TableState table_state(uint32_t *table, uint32_t L, uint32_t slot)
+{
+    // behind the 32-byte rows, per slot: the histograms (a multiple of 32 bytes each), the rest
+    uint32_t *w = table + 8 + 8 * size_t(L) + slot * table_slot_words(L);
     uint32_t *p = w + size_t(L) * kWinWords + 8;
     return TableState{p,         p + L,     p + 2 * L, p + 3 * L, p + 4 * L,
                       p + 5 * L, p + 6 * L, p - 8,     w};
 }
 static_assert(kWinWords % 8 == 0, "histograms stay 32-byte aligned");
-constexpr uint64_t table_state_words(uint64_t L) { return 7 * L + 8 + L * kWinWords; }
 
 }  // namespace tagc
 
@@ -132,8 +137,9 @@ struct tagc_plan_s {
     uint32_t P_cap, T_cap;
     tagc::Workspace ws;
     uint64_t zero_bytes;                      // prefix of the rank workspace cleared per call
-    // the table was uploaded and no PHASE_INDEX call has sampled pre-thresholds for it yet
-    mutable std::atomic<uint32_t> sample_pending{0};
+    uint32_t slots;                           // rank slots of the table's device state
+    // rank slots that a PHASE_INDEX call has used since the table was uploaded (one bit each)
+    mutable std::atomic<uint32_t> used{0xFFFFFFFFu};
     uint64_t n_chunks;                        // popcount chunks of the Index
     tagc_sizes sizes;
 };
@@ -186,8 +192,8 @@ int device_cu_count();
 
 // ------------------------------------------------------ stage entry points
 
-int launch_sparsify(const tagc_plan_t *p, const void *grad, const tagc_rank_buffers *rk,
-                    const tagc_shared_buffers *sh, hipStream_t s);
+int launch_sparsify(const tagc_plan_t *p, const void *const *grads, const tagc_rank_buffers *ranks,
+                    uint32_t n_ranks, const tagc_shared_buffers *sh, hipStream_t s);
 int launch_feedback_apply(const tagc_plan_t *p, const tagc_rank_buffers *rk,
                           const tagc_shared_buffers *sh, hipStream_t s);
 int launch_encode(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32_t n_ranks,
