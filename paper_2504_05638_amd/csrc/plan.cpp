@@ -65,15 +65,27 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
         if (mu > kFastMaxCandFrac * p->chunk_elems) return 0;
         return uint32_t(round_up(uint64_t(mu + 6.0 * sqrt(mu) + 16.0), 32));
     };
+    // Dense route: whether one workgroup's registers (and 16-bit counts) hold the segment.
+    auto small = [&](uint64_t length) {
+        return length <= std::min<uint64_t>(65535, uint64_t(kSmallVecs) * kSmallThreads * p->vec_elems);
+    };
     // Compaction tile of the dense route: four 16-byte vectors per thread where that route
     // is planned work, two where it is only the safety net of re-routed segments -- the
     // kernel it shares with the candidate route's last pass then needs few enough
     // registers for one more workgroup per CU.
+    p->any_fast = p->small_dense = false;
+    p->span_dense = 0;
     for (uint32_t l = 0; l < n_seg; ++l) {
         const tagc_segment &s = segs[l];
         if (!(s.flags & TAGC_SEG_COMPRESS) || s.keep_ppm > 1000000u || s.length == 0) continue;
-        if ((unsigned __int128)s.length * s.keep_ppm / 1000000u && !fast_slots(s))
+        if (!uint64_t((unsigned __int128)s.length * s.keep_ppm / 1000000u)) continue;
+        if (fast_slots(s)) {
+            p->any_fast = true;
+        } else {
             p->static_dense = true;
+            if (small(s.length)) p->small_dense = true;
+            else p->span_dense += s.length;
+        }
     }
     p->compact_rows = p->static_dense ? 4 : 2;
     p->tile_elems = kCompactThreads * p->vec_elems * p->compact_rows;
@@ -98,13 +110,13 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
             d.n = uint32_t(s.length);
             d.c_off = uint32_t(c);
             d.k = uint32_t((unsigned __int128)s.length * s.keep_ppm / 1000000u);
-            d.tile_start = uint32_t(tiles);
             d.flags = (s.offset % p->vec_elems) == 0 ? kSegAligned : 0;
             if (const uint32_t cap = fast_slots(s)) {
                 d.flags |= kSegFast;
                 p->cand_cap = std::max(p->cand_cap, cap);
             }
             if (d.n && !(d.flags & kSegFast)) p->any_nonfast = true;
+            if (d.k && !(d.flags & kSegFast) && small(d.n)) d.flags |= kSegSmall;
             d.sc_start = uint32_t(scs);
             scs += ceil_div(s.length, uint64_t(p->chunk_elems) * kCandChunksPerSuper);
             p->table.push_back(d);
@@ -113,6 +125,16 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
             grad_elems = std::max(grad_elems, s.offset + s.length);
             K += d.k;
             tiles += ceil_div(s.length, p->tile_elems);
+        }
+        // compaction tiles: the segments the scan never reads first, then the others
+        uint64_t at = 0;
+        for (const bool fast : {false, true}) {
+            if (fast) p->plan_tiles = uint32_t(at);
+            for (SegDev &d : p->table) {
+                if (((d.flags & kSegFast) != 0) != fast) continue;
+                d.tile_start = uint32_t(at);
+                at += ceil_div(d.n, p->tile_elems);
+            }
         }
     } catch (const std::bad_alloc &) {
         delete p;

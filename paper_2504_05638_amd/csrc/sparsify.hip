@@ -28,7 +28,7 @@
 //
 //  dense route (segments that are short, unaligned, keep more than ~3 %, have no
 //  pre-threshold yet, or were re-routed; three reads)
-//    hist1        exact histogram of the top 15 key bits of every entry, in LDS; the
+//    hist1        exact histogram of the top 15 key bits of every entry, in LDS windows; the
 //                 workgroup that completes a segment's histogram selects its threshold
 //    hist2/select2 fp32 only, as above
 //    count        survivors of every tile of the gradient
@@ -48,6 +48,7 @@
 // table, which only the library writes: whoever reads them last puts them back to zero, so
 // no call spends a launch on clearing (see TableState).
 #include <mutex>
+#include <type_traits>
 
 #include "device_utils.h"
 #include "tagc_internal.h"
@@ -255,146 +256,80 @@ accumulate_kernel(const SparsifyBatch, const uint32_t *__restrict__ table, uint3
 
 // ----------------------------------------------------------------- select
 
-// Largest bin b with  sum_{x >= b} hist[x] >= need  (need >= 1).  1024 threads, thread t
-// owns the BPT consecutive bins starting at t*BPT.  Returns false if the whole histogram
-// holds fewer than `need`; *total_out is the histogram's sum either way.  A second count
-// `need2` (0 = none) is located in the same pass: *bin2_out is the largest bin with at
-// least need2 entries at or above it, or 0xFFFFFFFF if the histogram holds fewer.  So is,
-// on request, the number of entries in the bins from `tail_from` upwards.  Bins below
-// `floor_bin` count as empty.
-template <int BPT>
-__device__ inline bool select_bins(const uint32_t *hist, uint32_t need, uint32_t *bin_out,
-                                   uint32_t *above_out, uint32_t *at_out, uint32_t *total_out,
-                                   uint32_t *smem /* >= 24 words */, uint32_t need2 = 0,
-                                   uint32_t *bin2_out = nullptr, uint32_t tail_from = 0,
-                                   uint32_t *tail_out = nullptr, uint32_t floor_bin = 0)
+// For each of two counts `want` (0 = not asked): the largest bin b with
+// sum_{x >= b} get(x) >= want, the entries in higher bins and those in b; bin = kNoBin if all
+// bins together hold fewer.  By a workgroup of NT threads, thread t owning the BPT consecutive
+// bins from t * BPT, whose sum it passes as `own`; the thread whose bins hold the answer leaves
+// its number, and one wave reads those bins side by side.
+constexpr uint32_t kNoBin = 0xFFFFFFFFu;
+struct BinFound {
+    uint32_t bin, above, at;
+};
+template <uint32_t NT, uint32_t BPT, typename Get>
+__device__ inline void select_top(Get &&get, uint32_t own, const uint32_t (&want)[2],
+                                  BinFound (&found)[2], uint32_t *total_out,
+                                  uint32_t *smem /* >= 32 words */)
 {
-    const uint32_t t = threadIdx.x;
-    const uint4 *hv = reinterpret_cast<const uint4 *>(hist + uint64_t(t) * BPT);
-    uint32_t bins[BPT];
-    uint32_t s = 0;
-#pragma unroll
-    for (int i = 0; i < BPT / 4; ++i) {
-        const uint4 v = hv[i];
-        bins[4 * i] = v.x; bins[4 * i + 1] = v.y; bins[4 * i + 2] = v.z; bins[4 * i + 3] = v.w;
-    }
-    // bins below `floor_bin` are read as empty (their counts are incomplete when part of the
-    // scan ran with a higher pre-threshold)
-#pragma unroll
-    for (int b = 0; b < BPT; ++b) {
-        if (t * BPT + b < floor_bin) bins[b] = 0;
-        s += bins[b];
-    }
+    static_assert(NT >= 128, "a wave per count");
+    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     uint32_t total;
-    uint32_t prefix = block_excl_scan<uint32_t, kHistThreads / 64>(s, &total, smem);
-    uint32_t suffix = total - prefix;  // bins of this thread and all higher ones
-    if (t == 0) {
-        smem[19] = 0xFFFFFFFFu;
-        smem[20] = 0;
+    const uint32_t prefix = block_excl_scan<uint32_t, NT / 64>(own, &total, smem);
+    const uint32_t suffix = total - prefix;  // bins of this thread and all higher ones
+    if (t < 2) smem[16 + 4 * t] = smem[17 + 4 * t] = kNoBin;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < 2; ++i)
+        if (want[i] && suffix >= want[i] && suffix - own < want[i]) {
+            smem[16 + 4 * i] = t;
+            smem[18 + 4 * i] = suffix - own;
+        }
+    __syncthreads();
+    uint32_t owner = kNoBin, acc = 0;
+    if (wave < 2) {
+        owner = smem[16 + 4 * wave];
+        acc = smem[18 + 4 * wave];
+    }
+    __syncthreads();  // (the words are written again below)
+    if (owner != kNoBin) {  // wave-uniform
+        const uint32_t need = wave ? want[1] : want[0];
+        constexpr int NB = (BPT + 63) / 64;  // looked at 64 at a time, from the top down
+#pragma unroll
+        for (int k = NB - 1; k >= 0; --k) {
+            const uint32_t b = uint32_t(k) * 64 + lane;
+            const uint32_t c = b < BPT ? get(owner * BPT + b) : 0u;
+            const uint32_t inc = wave_incl_scan<uint32_t>(c);
+            const uint32_t tot = __builtin_amdgcn_readlane(inc, 63);
+            const uint32_t above = acc + tot - inc;
+            if (above < need && above + c >= need) {
+                smem[16 + 4 * wave] = owner * BPT + b;
+                smem[17 + 4 * wave] = above;
+                smem[18 + 4 * wave] = c;
+            }
+            acc += tot;
+        }
+    } else if (wave < 2 && lane == 0) {
+        smem[16 + 4 * wave] = kNoBin;
     }
     __syncthreads();
-    // entries in the bins from `tail_from` (a multiple of BPT) upwards, if asked for
-    if (tail_out && t * BPT >= tail_from && s) atomicAdd(&smem[20], s);
-    if (total >= need && suffix >= need && suffix - s < need) {
-        uint32_t acc = suffix - s;
-        bool done = false;
 #pragma unroll
-        for (int b = BPT - 1; b >= 0; --b) {
-            const uint32_t c = bins[b];
-            if (!done && acc + c >= need) {
-                smem[16] = t * BPT + b;
-                smem[17] = acc;
-                smem[18] = c;
-                done = true;
-            }
-            if (!done) acc += c;
-        }
-    }
-    if (need2 && total >= need2 && suffix >= need2 && suffix - s < need2) {
-        uint32_t acc = suffix - s;
-        bool done = false;
-#pragma unroll
-        for (int b = BPT - 1; b >= 0; --b) {
-            const uint32_t c = bins[b];
-            if (!done && acc + c >= need2) {
-                smem[19] = t * BPT + b;
-                done = true;
-            }
-            if (!done) acc += c;
-        }
-    }
-    __syncthreads();
-    *bin_out = smem[16];
-    *above_out = smem[17];
-    *at_out = smem[18];
+    for (uint32_t i = 0; i < 2; ++i)
+        found[i] = BinFound{smem[16 + 4 * i], smem[17 + 4 * i], smem[18 + 4 * i]};
     *total_out = total;
-    if (bin2_out) *bin2_out = smem[19];
-    if (tail_out) *tail_out = smem[20];
     __syncthreads();
-    return total >= need;
 }
 
-// The same for a workgroup of NT < 1024 threads (32768 bins: thread t owns the 32768 / NT
-// consecutive bins from t * 32768 / NT), without the bins in registers: every thread adds up
-// its bins as they stream by, and the one thread whose bins hold the answer reads them a
-// second time from the top down.  For kernels that are launched on the off-chance and nearly
-// always leave at once: what such a launch costs on a busy device is finding a compute unit
-// with room for its workgroup, and four waves of few registers fit where sixteen do not.
-template <uint32_t NT>
-__device__ inline bool select_bins_streamed(const uint32_t *hist, uint32_t need, uint32_t *bin_out,
-                                            uint32_t *above_out, uint32_t *at_out,
-                                            uint32_t *total_out, uint32_t *smem /* >= 24 words */,
-                                            uint32_t need2, uint32_t *bin2_out,
-                                            uint32_t tail_from, uint32_t *tail_out)
+// sum of the BPT bins a thread owns of an array in memory
+template <uint32_t BPT>
+__device__ inline uint32_t own_bins(const uint32_t *hist)
 {
-    constexpr uint32_t BPT = kBins1 / NT;
-    static_assert(BPT % 4 == 0 && BPT * NT == kBins1, "whole 16-byte groups of bins per thread");
-    const uint32_t t = threadIdx.x;
-    const uint4 *hv = reinterpret_cast<const uint4 *>(hist + uint64_t(t) * BPT);
+    const uint4 *hv = reinterpret_cast<const uint4 *>(hist + threadIdx.x * BPT);
     uint32_t s = 0;
+#pragma unroll 8
     for (uint32_t i = 0; i < BPT / 4; ++i) {
         const uint4 v = hv[i];
         s += v.x + v.y + v.z + v.w;
     }
-    uint32_t total;
-    const uint32_t prefix = block_excl_scan<uint32_t, NT / 64>(s, &total, smem);
-    const uint32_t suffix = total - prefix;  // bins of this thread and all higher ones
-    if (t == 0) {
-        smem[19] = 0xFFFFFFFFu;
-        smem[20] = 0;
-    }
-    __syncthreads();
-    if (tail_out && t * BPT >= tail_from && s) atomicAdd(&smem[20], s);
-    // largest bin of this thread with at least `want` entries at or above it
-    auto locate = [&](uint32_t want, uint32_t *bin, uint32_t *above, uint32_t *at) {
-        uint32_t acc = suffix - s;
-        for (int i = int(BPT / 4) - 1; i >= 0; --i) {
-            const uint4 v = hv[i];
-            const uint32_t c[4] = {v.x, v.y, v.z, v.w};
-            for (int e = 3; e >= 0; --e) {
-                if (acc + c[e] >= want) {
-                    *bin = t * BPT + 4 * uint32_t(i) + uint32_t(e);
-                    if (above) *above = acc;
-                    if (at) *at = c[e];
-                    return;
-                }
-                acc += c[e];
-            }
-        }
-    };
-    if (total >= need && suffix >= need && suffix - s < need)
-        locate(need, &smem[16], &smem[17], &smem[18]);
-    if (need2 && total >= need2 && suffix >= need2 && suffix - s < need2)
-        locate(need2, &smem[19], nullptr, nullptr);
-    __syncthreads();
-    *bin_out = smem[16];
-    *above_out = smem[17];
-    *at_out = smem[18];
-    *total_out = total;
-    if (bin2_out) *bin2_out = smem[19];
-    if (tail_out) *tail_out = smem[20];
-    __syncthreads();
-    return total >= need;
+    return s;
 }
 
 // ---------------------------------------------------------------- prepare
@@ -451,10 +386,13 @@ prepare_kernel(const SparsifyBatch, uint32_t *table, uint32_t wire4)
     __syncthreads();
     const float ks = float(double(sd.k) * double(S * VEC) / double(sd.n));
     const uint32_t need = uint32_t(ks + 5.0f * sqrtf(ks) + 16.0f) + 1u;
-    uint32_t bin, above, at, total;
-    const bool found = select_bins<32>(h, need, &bin, &above, &at, &total, smem);
+    uint32_t total;
+    BinFound f[2];
+    constexpr uint32_t BPT = kBins1 / kHistThreads;
+    select_top<kHistThreads, BPT>([&](uint32_t b) { return h[b]; }, own_bins<BPT>(h), {need, 0u}, f,
+                                  &total, smem);
     // bin 0 (|g| < 2^-133) is never a candidate
-    if (tid == 0 && found) ts.hint[l] = max(bin, 1u);
+    if (tid == 0 && f[0].bin != kNoBin) ts.hint[l] = max(f[0].bin, 1u);
 }
 
 // ------------------------------------------------------------- scan_spill
@@ -1005,207 +943,326 @@ __device__ inline bool on_dense_route(const SegDev &sd, const SelDev *sel, uint3
     return !(sd.flags & kSegFast) || sel[l].route != 0;
 }
 
-// true iff some segment is on the dense route.  Every thread reads the same words, so the
-// loads are scalar and the answer is uniform without a barrier.
+// true iff some segment is on the dense route: lane i looks at segments i, i + 64, ...
 __device__ inline bool any_dense_route(const SegDev *segs, const SelDev *sel, uint32_t L)
 {
     bool any = false;
-    for (uint32_t l = 0; l < L; ++l) any |= on_dense_route(segs[l], sel, l);
-    return any;
+    for (uint32_t l = threadIdx.x & 63; l < L; l += 64) any |= on_dense_route(segs[l], sel, l);
+    return __ballot(any) != 0;
 }
 
 // ------------------------------------------------------------------ hist1
 
-// LDS histogram of the dense route: `WBINS` counters for the bins from `base` upwards; an
-// entry outside that window goes straight to the global histogram `gh`.
-template <uint32_t WBINS>
-struct HistWin {
-    uint32_t *h, *gh;
-    uint32_t base;
-    __device__ inline void add(uint32_t bin) const
-    {
-        if (WBINS == kBins1) {
-            atomicAdd(&h[bin], 1u);
-        } else {
-            const uint32_t wi = bin - base;
-            if (wi < WBINS) atomicAdd(&h[wi], 1u);
-            else atomicAdd(&gh[bin], 1u);
+// The dense route reads any 16-byte vector of a segment, aligned or not (memory instructions
+// take any alignment; a wave's kilobyte then touches one cache line more).
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ inline uint4 ld_stream_any(const char *p)
+{
+    const u32x4_any v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// entries rel .. rel + VEC - 1 of a segment of n entries, those past its end as 0
+template <int DTYPE>
+__device__ inline uint4 load_vec(const char *base, uint32_t rel, uint32_t n)
+{
+    constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
+    constexpr uint32_t VEC = 16 / EB;
+    if (rel + VEC <= n) return ld_stream_any(base + uint64_t(rel) * EB);
+    uint32_t w[4] = {0, 0, 0, 0};
+    if (rel < n) {
+#pragma unroll
+        for (uint32_t e = 0; e < VEC; ++e) {
+            if (rel + e >= n) continue;
+            const uint32_t b = load_elem_bits(base, uint64_t(rel) + e, DTYPE);
+            if (DTYPE == kBF16) w[e >> 1] |= (b >> 16) << (16 * (e & 1));
+            else w[e] = b;
         }
     }
-};
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
 
-template <int DTYPE, uint32_t WBINS>
-__device__ inline void hist_word(uint32_t w, const HistWin<WBINS> &hw)
+// fn(level-1 bin of the key, key) for the VEC entries of a vector, exact zeros left out
+template <int DTYPE, typename Fn>
+__device__ inline void for_keys(uint4 v, Fn &&fn)
 {
-    if (DTYPE == kBF16) {
-        uint32_t a = w & 0x7FFFu, b = (w >> 16) & 0x7FFFu;
-        if (a) hw.add(a);
-        if (b) hw.add(b);
-    } else {
-        uint32_t key = w & 0x7FFFFFFFu;
-        if (key) hw.add(key >> 16);
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4;
+#pragma unroll
+    for (uint32_t e = 0; e < VEC; ++e) {
+        const uint32_t key = vec_elem_bits<DTYPE>(w, e) & 0x7FFFFFFFu;
+        if (key) fn(key >> 16, key);
     }
 }
 
-template <int DTYPE, uint32_t WBINS>
-__device__ inline void hist_vec(uint4 v, const HistWin<WBINS> &hw)
+// What a dense-route segment's level-1 histogram says: writes the selection (fp32: its upper
+// half) and, for a segment that was re-routed, the pre-threshold for the next call, the bin
+// above which about 1.3 k entries lie (what the slots per chunk are sized for).  One thread.
+template <int DTYPE>
+__device__ inline SelDev dense_selection(uint32_t l, const SegDev &sd, const BinFound &k_th,
+                                         const BinFound &want, uint32_t total, uint32_t nonfinite,
+                                         const TableState ts)
 {
-    hist_word<DTYPE>(v.x, hw);
-    hist_word<DTYPE>(v.y, hw);
-    hist_word<DTYPE>(v.z, hw);
-    hist_word<DTYPE>(v.w, hw);
-}
-
-template <uint32_t WBINS>
-__device__ inline void hist_elem(uint32_t f32bits, const HistWin<WBINS> &hw)
-{
-    uint32_t key = f32bits & 0x7FFFFFFFu;
-    if (key) hw.add(key >> 16);
-}
-
-// Threshold bin of one dense-route segment from the 32768-bin histogram of all its entries,
-// by a whole workgroup of NT threads.  Also leaves the pre-threshold for the next
-// call on this plan: the bin above which about 1.3 k entries lie (what the slots per chunk
-// are sized for).
-template <int DTYPE, uint32_t NT>
-__device__ inline void select_dense(uint32_t l, const SegDev &sd, const uint32_t *hist,
-                                    SelDev *sel, const TableState ts,
-                                    uint32_t *smem /* >= 32 words */)
-{
-    const uint32_t *h = hist + uint64_t(l) * kBins1;
-    uint32_t bin, above, at, total, bin2, nf;
-    const bool fast = (sd.flags & kSegFast) != 0;
-    const uint32_t want = fast ? uint32_t(1.3f * float(sd.k)) + 1u : 0u;
-    // nf: inputs with an all-ones exponent fall into bins >= 0x7F80
-    const bool found =
-        NT == kHistThreads
-            ? select_bins<32>(h, sd.k, &bin, &above, &at, &total, smem, want, &bin2, 0x7F80u, &nf)
-            : select_bins_streamed<NT>(h, sd.k, &bin, &above, &at, &total, smem, want, &bin2,
-                                       0x7F80u, &nf);
-    if (threadIdx.x != 0) return;
-    if (fast) {
+    if (sd.flags & kSegFast) {
         // fewer non-zeros than 1.3 k in the whole segment: everything is a candidate
-        const uint32_t b2 = bin2 != 0xFFFFFFFFu ? max(bin2, 1u) : 1u;
+        const uint32_t b2 = want.bin != kNoBin ? max(want.bin, 1u) : 1u;
         // after a miss (the scale fell below what the carried pre-threshold admits) the next
         // calls extrapolate the fall instead of trusting the last value
         ts.hint[l] = next_hint(b2, ts.prev[l], ts.watch[l]);
         ts.prev[l] = b2;
     }
-    if (nf) atomicAdd(&ts.glob[1], nf);
+    if (nonfinite) atomicAdd(&ts.glob[1], nonfinite);
     atomicAdd(&ts.glob[2], 1u);
     SelDev r{};
     r.route = 1;
-    if (!found) {  // fewer non-zeros than k: keep every non-zero
+    if (k_th.bin == kNoBin) {  // fewer non-zeros than k: keep every non-zero
         r.T = 0;
         r.quota = 0;
         r.G = total;
         r.cnt = total;
     } else if (DTYPE == kBF16) {
-        r.T = bin << 16;
+        r.T = k_th.bin << 16;
+        r.G = k_th.above;
+        r.quota = sd.k - k_th.above;
+        r.cnt = sd.k;
+    } else {
+        r.bin1 = k_th.bin;
+        r.G1 = k_th.above;
+        r.need2 = 1;
+    }
+    return r;
+}
+__device__ inline uint32_t carried_count(const SegDev &sd)
+{
+    return (sd.flags & kSegFast) ? uint32_t(1.3f * float(sd.k)) + 1u : 0u;
+}
+
+// A segment that one workgroup can hold in its registers: all of it is read once, histogrammed
+// in LDS (two 16-bit counts per word: a segment has fewer than 65536 entries), and, in fp32,
+// the low 16 key bits of the threshold bin found by two rounds of 256 bins over the same
+// registers.  Nothing of it goes through global memory and nobody waits for anybody: with a
+// histogram in memory such a segment cost the device a pass of clearing, 256 workgroups'
+// flushes and an arrival count (five segments of 400 to 11,000 fp32 entries, three ranks: 75 us
+// over two launches; 15 in one in this form, a third of it the time a launch takes).
+template <int DTYPE>
+__device__ __forceinline__ void select_small(uint32_t l, const SegDev &sd, const char *base,
+                                             SelDev *sel, const TableState ts, uint32_t *h16,
+                                             uint32_t *smem)
+{
+    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4;
+    constexpr uint32_t NT = kSmallThreads;
+    const uint32_t tid = threadIdx.x;
+    uint4 v[kSmallVecs];
+#pragma unroll
+    for (uint32_t i = 0; i < kSmallVecs; ++i) v[i] = load_vec<DTYPE>(base, (i * NT + tid) * VEC, sd.n);
+    for (uint32_t i = tid; i < kBins1 / 8; i += NT)
+        reinterpret_cast<uint4 *>(h16)[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kSmallVecs; ++i)
+        for_keys<DTYPE>(v[i], [&](uint32_t bin, uint32_t) {
+            atomicAdd(&h16[bin >> 1], 1u << (16 * (bin & 1u)));
+        });
+    __syncthreads();
+    // a thread's bins are BPT / 2 consecutive words, read from a different one on in every
+    // lane (or all lanes would meet in the same LDS banks)
+    constexpr uint32_t BPT = kBins1 / NT, WPT = BPT / 2;
+    uint32_t two = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < WPT; ++i) two += h16[tid * WPT + ((i + tid) % WPT)];
+    const uint32_t own = (two & 0xFFFFu) + (two >> 16);  // (a segment's total fits 16 bits)
+    if (tid == 0) smem[32] = 0;
+    __syncthreads();
+    if (tid * BPT >= 0x7F80u && own) atomicAdd(&smem[32], own);  // all-ones exponents
+    uint32_t total;
+    BinFound f[2];
+    auto get = [&](uint32_t b) { return (h16[b >> 1] >> (16 * (b & 1u))) & 0xFFFFu; };
+    select_top<NT, BPT>(get, own, {sd.k, carried_count(sd)}, f, &total, smem);
+    if (DTYPE == kBF16 || f[0].bin == kNoBin) {  // uniform
+        if (tid == 0) sel[l] = dense_selection<DTYPE>(l, sd, f[0], f[1], total, smem[32], ts);
+        return;
+    }
+    // fp32: eight key bits a round
+    uint32_t above = f[0].above, prefix = f[0].bin;  // key >> shift of the bin looked into
+#pragma unroll
+    for (uint32_t round = 0; round < 2; ++round) {
+        const uint32_t shift = 16 - 8 * round;
+        if (tid < 256) h16[tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t i = 0; i < kSmallVecs; ++i)
+            for_keys<DTYPE>(v[i], [&](uint32_t, uint32_t key) {
+                if ((key >> shift) == prefix) atomicAdd(&h16[(key >> (shift - 8)) & 0xFFu], 1u);
+            });
+        __syncthreads();
+        uint32_t tot2;
+        BinFound g[2];
+        select_top<NT, 1>([&](uint32_t b) { return h16[b]; }, tid < 256 ? h16[tid] : 0u,
+                          {sd.k - above, 0u}, g, &tot2, smem);
+        above += g[0].above;
+        prefix = (prefix << 8) | g[0].bin;
+    }
+    if (tid == 0) {
+        SelDev r = dense_selection<DTYPE>(l, sd, f[0], f[1], total, smem[32], ts);
+        r.T = prefix;
         r.G = above;
         r.quota = sd.k - above;
         r.cnt = sd.k;
-    } else {
-        r.bin1 = bin;
-        r.G1 = above;
-        r.need2 = 1;
+        r.need2 = 0;
+        sel[l] = r;
     }
-    sel[l] = r;
 }
 
-// Dense route: one workgroup per CU, all entries of every dense-route segment.  Leaves at
-// once when no segment is on the dense route.  The workgroup that completes a segment's
-// histogram selects its threshold right away, while the others go on with the next segment:
-// no separate selection launch.
+// Dense route: thresholds of the segments the scan does not select for, by plan or because its
+// selection re-routed them.  The last `n_span` workgroups of a rank share the entries of its
+// longer segments out in contiguous spans of tiles, each adding what it counted in LDS to the
+// segment's histogram in the workspace; whoever completes that histogram selects right away.
+// The first workgroups (SMALL: the plan has such segments) take a short segment each.
 //
-// WBINS = 32768: all counters in LDS (128 KiB), for plans with dense-route segments.  A plan
-// without any launches the kernel only as the safety net of re-routed segments, and a
-// workgroup that needs most of a compute unit's LDS has to wait, on a busy device, until
-// one is that free -- just to find that there is nothing to do.  Such plans use WBINS = 4096
-// (16 KiB): the 32 octaves around the segment's last pre-threshold, where all but a
-// vanishing part of a gradient lies; the rest is added to the global histogram directly.
-// And workgroups of 256 threads, four per CU: with buckets in flight on other streams a
-// 1024-thread workgroup found room 7 us later on average, per rank and bucket, 3.3 ms per
-// step of the 7B workload -- for a launch that reads two table rows and leaves.
-constexpr uint32_t kHistWindow = 4096;
-constexpr uint32_t kHistNetThreads = 256;
-
-template <int DTYPE, uint32_t WBINS, uint32_t NT>
-__global__ void __launch_bounds__(NT)
-hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
+// The LDS histogram is a window of 4096 bins, 32 octaves of magnitude, that every workgroup puts
+// where its own first vectors lie; what falls outside goes to the histogram in memory directly.
+// With all 32768 bins in LDS (128 KiB) a compute unit held one workgroup, which cleared and
+// searched that much for every segment: 95 us for four ranks of 9 M bf16 entries in five
+// segments, against 47 in this form (of which reading them takes 12: the rest is LDS adds, one
+// per entry).
+//
+// A plan without such segments launches the kernel only as the safety net of re-routed ones,
+// where it leaves at once: small workgroups find room on a busy device, a launch of
+// 1024-thread ones cost 7 us with other buckets in flight.
+template <int DTYPE, bool SMALL>
+__global__ void __launch_bounds__(SMALL ? kSmallThreads : kDenseThreads)
+hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t n_span)
 {
+    constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
+    constexpr uint32_t VEC = 16 / EB;
+    constexpr uint32_t NT = SMALL ? kSmallThreads : kDenseThreads;
+    constexpr uint32_t BPT = kBins1 / NT;
+    constexpr uint32_t TILE = NT * VEC * kDenseRows;
+    static_assert(0x7F80u % BPT == 0, "a thread's bins are all finite or none is");
+    __shared__ uint32_t h[SMALL ? kBins1 / 2 : kHistWindow];
+    __shared__ uint32_t smem[40];
+    __shared__ uint32_t s_last, s_top;
     const RankView rv = rank_view();
     const char *grad = rv.src();
     SelDev *sel = rv.at<SelDev>(wl.sel);
-    uint32_t *hist = rv.at<uint32_t>(wl.hist1d);
-    extern __shared__ uint32_t h[];
-    __shared__ uint32_t s_sel[32];
-    __shared__ uint32_t s_last;
-    constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
-    constexpr uint32_t VEC = 16 / EB;
     const uint32_t L = table[0];
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
-    if (!any_dense_route(segs, sel, L)) return;
     const TableState ts = table_state(table, L, rv.slot);
-    const uint32_t tid = threadIdx.x;
-    for (uint32_t i = tid; i < WBINS; i += NT) h[i] = 0;
-    __syncthreads();
-    for (uint32_t l = 0; l < L; ++l) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t n_small = gridDim.x - n_span;
+    if (blockIdx.x == 0) {  // the tile groups' counts are added to by the next kernel
+        uint64_t *gc = rv.at<uint64_t>(wl.group_cnt);
+        for (uint32_t i = tid; i <= table[1] / kTileGroup; i += NT) gc[i] = 0;
+    }
+    if (SMALL && blockIdx.x < n_small) {
+        const uint32_t l = blockIdx.x;
         const SegDev sd = segs[l];
-        if (!on_dense_route(sd, sel, l)) continue;
-        const char *base = grad + sd.offset * EB;
-        uint32_t *gh = hist + uint64_t(l) * kBins1;
-        // window: 24 octaves below to 8 above the bin the last call's 1.3 k largest entries
-        // began at; without one, magnitudes from 2^-30 to 4
-        const uint32_t prev = ts.prev[l];
-        const HistWin<WBINS> hw{h, gh, WBINS == kBins1 ? 0u
-                                          : (prev ? (prev > 3072u ? min(prev - 3072u, kBins1 - WBINS) : 0u)
-                                                  : 97u * 128u)};
-        if (sd.flags & kSegAligned) {
-            const uint4 *vp = reinterpret_cast<const uint4 *>(base);
-            const uint64_t nvec = sd.n / VEC;
-            const uint64_t stride = uint64_t(gridDim.x) * NT;
-            uint64_t v = uint64_t(blockIdx.x) * NT + tid;
-            for (; v + 3 * stride < nvec; v += 4 * stride) {
-                const uint4 a = ld_stream(vp + v), b = ld_stream(vp + v + stride),
-                            c = ld_stream(vp + v + 2 * stride), d = ld_stream(vp + v + 3 * stride);
-                hist_vec<DTYPE>(a, hw);
-                hist_vec<DTYPE>(b, hw);
-                hist_vec<DTYPE>(c, hw);
-                hist_vec<DTYPE>(d, hw);
+        if (sd.k != 0 && (sd.flags & kSegSmall))
+            select_small<DTYPE>(l, sd, grad + sd.offset * EB, sel, ts, h, smem);
+        return;
+    }
+    // tiles of the segment of row l that go through here
+    auto tiles_of = [&](uint32_t l) -> uint32_t {
+        if (l >= L) return 0u;
+        const SegDev sd = segs[l];
+        if ((sd.flags & kSegSmall) || !on_dense_route(sd, sel, l)) return 0u;
+        return (sd.n + TILE - 1) / TILE;
+    };
+    uint32_t all = 0;  // (every wave adds them up for itself; < 2^22 segments of < 2^19 tiles)
+    for (uint32_t l = lane; l < (L + 63) / 64 * 64; l += 64) all += tiles_of(l);
+    all = wave_sum(all);
+    if (all == 0) return;
+    const uint32_t span = (all + n_span - 1) / n_span;
+    const uint32_t g0 = (blockIdx.x - n_small) * span, g1 = min(g0 + span, all);
+    if (g0 >= all) return;
+    bool clear = false;
+    uint32_t first = 0;  // tiles of the segments before
+    for (uint32_t l0 = 0; l0 < L && first < g1; l0 += 64) {
+        const uint32_t mine = tiles_of(l0 + lane), inc = wave_incl_scan<uint32_t>(mine);
+        // segments of this block of 64 rows whose tiles meet the workgroup's
+        uint64_t meet = __ballot(mine && first + inc > g0 && first + inc - mine < g1);
+        for (; meet; meet &= meet - 1) {
+            const uint32_t j = uint32_t(__builtin_ctzll(meet)), l = l0 + j;
+            const uint32_t nt = __builtin_amdgcn_readlane(mine, j);
+            const uint32_t s0 = first + __builtin_amdgcn_readlane(inc, j) - nt;
+            const SegDev sd = segs[l];
+            const char *base = grad + sd.offset * EB;
+            uint32_t *gh = rv.at<uint32_t>(wl.hist1d) + uint64_t(l) * kBins1;
+            const uint32_t t0 = max(g0, s0) - s0, t1 = min(g1, s0 + nt) - s0;
+            auto load_tile = [&](uint32_t t, uint4 (&v)[kDenseRows]) {
+#pragma unroll
+                for (uint32_t r = 0; r < kDenseRows; ++r)
+                    v[r] = load_vec<DTYPE>(base, t * TILE + (r * NT + tid) * VEC, sd.n);
+            };
+            uint4 v[kDenseRows];
+            load_tile(t0, v);
+            if (!clear)
+                for (uint32_t i = tid; i < kHistWindow; i += NT) h[i] = 0;
+            clear = true;
+            // The window: from 8 octaves above the smallest of the waves' largest finite keys
+            // (an odd outlier moves one wave's) 32 octaves down.
+            if (tid == 0) s_top = 0x7F7Fu;
+            uint32_t top = 0;
+#pragma unroll
+            for (uint32_t r = 0; r < kDenseRows; ++r)
+                for_keys<DTYPE>(v[r], [&](uint32_t bin, uint32_t) {
+                    if (bin < 0x7F80u) top = max(top, bin);
+                });
+#pragma unroll
+            for (uint32_t d = 32; d >= 1; d >>= 1) top = max(top, uint32_t(__shfl_xor(top, d, 64)));
+            __syncthreads();
+            if (lane == 0 && top) atomicMin(&s_top, top);
+            __syncthreads();
+            const uint32_t end = min(s_top + 1024u, kBins1);
+            const uint32_t wbase = end > kHistWindow ? end - kHistWindow : 0u;
+            for (uint32_t t = t0; t < t1; ++t) {
+                uint4 cur[kDenseRows];
+#pragma unroll
+                for (uint32_t r = 0; r < kDenseRows; ++r) cur[r] = v[r];
+                if (t + 1 < t1) load_tile(t + 1, v);  // on its way while this one is counted
+#pragma unroll
+                for (uint32_t r = 0; r < kDenseRows; ++r)
+                    for_keys<DTYPE>(cur[r], [&](uint32_t bin, uint32_t) {
+                        const uint32_t w = bin - wbase;
+                        if (w < kHistWindow) atomicAdd(&h[w], 1u);
+                        else atomicAdd(&gh[bin], 1u);
+                    });
             }
-            for (; v < nvec; v += stride) hist_vec<DTYPE>(ld_stream(vp + v), hw);
-            if (blockIdx.x == 0) {
-                uint64_t i = nvec * VEC + tid;
-                if (i < sd.n) hist_elem(load_elem_bits(base, i, DTYPE), hw);
+            __syncthreads();
+            for (uint32_t i = tid; i < kHistWindow; i += NT) {
+                const uint32_t c = h[i];
+                if (c) {
+                    atomicAdd(&gh[wbase + i], c);
+                    h[i] = 0;
+                }
             }
-        } else {
-            for (uint64_t i = uint64_t(blockIdx.x) * NT + tid; i < sd.n;
-                 i += uint64_t(gridDim.x) * NT)
-                hist_elem(load_elem_bits(base, i, DTYPE), hw);
-        }
-        __syncthreads();
-        for (uint32_t i = tid; i < WBINS; i += NT) {
-            uint32_t c = h[i];
-            if (c) {
-                atomicAdd(&gh[hw.base + i], c);
-                h[i] = 0;
+            // The histogram updates are device-scope atomics, performed where every CU sees
+            // them; a thread only has to wait until its own have been acknowledged before the
+            // workgroup is counted as arrived.  The workgroup that arrives last drops what it
+            // may hold of the histogram in its caches and selects.
+            wait_own_memory_ops();
+            __syncthreads();
+            if (tid == 0) {
+                const uint32_t expected = (s0 + nt - 1) / span - s0 / span + 1u;
+                s_last = atomicAdd(&ts.arrive_d[l], 1u) == expected - 1u;
             }
-        }
-        // The histogram updates are device-scope atomics, performed where every CU sees
-        // them; a thread only has to wait until its own have been acknowledged before the
-        // workgroup is counted as arrived.  The workgroup that arrives last drops what it may
-        // hold of the histogram in its caches and selects.
-        wait_own_memory_ops();
-        __syncthreads();
-        if (tid == 0) s_last = atomicAdd(&ts.arrive_d[l], 1u) == gridDim.x - 1;
-        __syncthreads();
-        if (s_last) {  // uniform
+            __syncthreads();
+            if (!s_last) continue;  // uniform
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            if (tid == 0) ts.arrive_d[l] = 0;  // for the next call
-            select_dense<DTYPE, NT>(l, sd, hist, sel, ts, s_sel);
+            const uint32_t own = own_bins<BPT>(gh);
+            if (tid == 0) {
+                ts.arrive_d[l] = 0;  // for the next call
+                smem[32] = 0;
+            }
+            __syncthreads();
+            if (tid * BPT >= 0x7F80u && own) atomicAdd(&smem[32], own);  // all-ones exponents
+            uint32_t total;
+            BinFound f[2];
+            select_top<NT, BPT>([&](uint32_t b) { return gh[b]; }, own, {sd.k, carried_count(sd)},
+                                f, &total, smem);
+            if (tid == 0) sel[l] = dense_selection<DTYPE>(l, sd, f[0], f[1], total, smem[32], ts);
         }
-        __syncthreads();
+        first += __builtin_amdgcn_readlane(inc, 63);
     }
 }
 
@@ -1302,11 +1359,15 @@ select2_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
     if (sd.k == 0 || sd.n == 0) return;
     SelDev r = sel[l];
     if (!r.need2) return;
-    uint32_t bin, above, at, total;
-    bool found =
-        select_bins<64>(hist2 + uint64_t(l) * kBins2, sd.k - r.G1, &bin, &above, &at, &total, smem);
+    const uint32_t *h = hist2 + uint64_t(l) * kBins2;
+    constexpr uint32_t BPT = kBins2 / kHistThreads;
+    uint32_t total;
+    BinFound f[2];
+    select_top<kHistThreads, BPT>([&](uint32_t b) { return h[b]; }, own_bins<BPT>(h),
+                                  {sd.k - r.G1, 0u}, f, &total, smem);
     if (threadIdx.x != 0) return;
-    if (!found) {  // cannot happen when both histograms saw the same data
+    uint32_t bin = f[0].bin, above = f[0].above;
+    if (bin == kNoBin) {  // cannot happen when both histograms saw the same data
         bin = 0;
         above = total;
         atomicOr(&table_state(table, table[0], rv.slot).glob[0], TAGC_FLAG_OVERFLOW);
@@ -1396,8 +1457,19 @@ __device__ inline void write_rank_counts(uint32_t *table, uint32_t slot, const S
 constexpr uint32_t kEmitStage = 800;  // survivors of an item that go through LDS
 static_assert(kEmitThreads == 128 * kEmitItems, "two waves per item");
 
+template <int DTYPE>
+struct EmitLds {
+    static constexpr uint32_t kWords = 64 * (DTYPE == kBF16 ? 8 : 4) * kCandRows *
+                                       kCandChunksPerSuper / 32;
+    uint32_t bits[kEmitItems][kWords];
+    // staged survivor: value bits and position in the super-chunk (16 bits); bf16 packs
+    // both in one word, like a candidate slot
+    uint32_t st_a[kEmitItems][kEmitStage];
+    uint16_t st_b[kEmitItems][DTYPE == kF32 ? kEmitStage : 2];
+};
+
 template <int DTYPE, bool PLACE>
-__device__ __forceinline__ void emit_body(uint32_t bid, uint32_t nb,
+__device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid, uint32_t nb,
                                  const uint32_t *__restrict__ table,
                                  const SelDev *__restrict__ sel,
             const uint32_t *__restrict__ cand, const uint2 *__restrict__ chunk_info,
@@ -1410,11 +1482,9 @@ __device__ __forceinline__ void emit_body(uint32_t bid, uint32_t nb,
     constexpr uint32_t SC_ELEMS = CHUNK * kCandChunksPerSuper;
     constexpr uint32_t SC_WORDS = SC_ELEMS / 32;
     constexpr int NI = kEmitItems;
-    __shared__ uint32_t bits[PLACE ? NI : 1][PLACE ? SC_WORDS : 1];
-    // staged survivor: value bits and position in the super-chunk (16 bits); bf16 packs
-    // both in one word, like a candidate slot
-    __shared__ uint32_t st_a[PLACE ? NI : 1][PLACE ? kEmitStage : 1];
-    __shared__ uint16_t st_b[PLACE ? NI : 1][PLACE && DTYPE == kF32 ? kEmitStage : 2];
+    auto *bits = lds->bits;  // (place only, as the rest of *lds)
+    auto *st_a = lds->st_a;
+    auto *st_b = lds->st_b;
     static_assert(SC_ELEMS <= 65536, "a position in the super-chunk fits 16 bits");
     __shared__ uint32_t s_gt[2 * NI], s_eq[2 * NI];
     __shared__ uint64_t s_sum[2 * NI];
@@ -1819,48 +1889,81 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
 
 // Dense route, count and place, over the gradient itself: one tile of kCompactThreads x ROWS
 // 16-byte vectors per workgroup and turn.  Also writes the (all-zero) Index words of the
-// segments that keep nothing.
-template <int DTYPE, uint32_t ROWS, bool PLACE>
-__device__ __forceinline__ void compact_body(uint32_t bid, uint32_t nb, const char *grad,
-                                    const uint32_t *__restrict__ table,
-               const SelDev *__restrict__ sel, uint64_t *tile_cnt, uint64_t *group_cnt,
-               uint32_t *__restrict__ idx_out,
-               float *__restrict__ val_out, uint32_t *__restrict__ bitmap)
+// segments that keep nothing.  The segments the scan never reads have the first `plan_tiles`
+// tiles, one workgroup each; the workgroups behind take those of re-routed segments in turns.
+//
+// STAGED (a plan with dense-route segments): a tile's survivors are gathered in LDS and leave as
+// contiguous stores; entry by entry each store instruction would touch every cache line a
+// wave's part of the output covers (8.7 M entries of which two fifths are kept, 4 ranks: place
+// 78 us that way, 54 in this).
+template <int DTYPE, bool STAGED>
+struct CompactLds {
+    static constexpr uint32_t kStage = STAGED ? kCompactThreads * (DTYPE == kBF16 ? 8 : 4) * 4 : 1;
+    uint32_t v[kStage];  // bf16: value and position in the tile in one word
+    uint16_t p[DTYPE == kF32 ? kStage : 1];
+};
+
+template <int DTYPE, uint32_t ROWS, bool PLACE, bool STAGED>
+__device__ __forceinline__ void compact_body(CompactLds<DTYPE, STAGED> *lds, uint32_t bid, uint32_t nb, uint32_t plan_tiles,
+                                             const char *grad, const uint32_t *__restrict__ table,
+                                             const SelDev *__restrict__ sel, uint64_t *tile_cnt,
+                                             uint64_t *group_cnt, uint32_t *__restrict__ idx_out,
+                                             float *__restrict__ val_out,
+                                             uint32_t *__restrict__ bitmap)
 {
-    constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
-    constexpr uint32_t VEC = 16 / EB;
+    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4;
     constexpr uint32_t ROW_ELEMS = kCompactThreads * VEC;
     constexpr uint32_t TILE = ROW_ELEMS * ROWS;
     constexpr uint32_t LPW = 32 / VEC;  // lanes that share one Index word
-    __shared__ uint64_t s_scan[2 * (kCompactThreads / 64)];
-    __shared__ uint64_t s_excl;
-    __shared__ uint32_t s_base;
+    constexpr uint32_t NWV = kCompactThreads / 64;
+    static_assert(TILE <= 8192 && ROWS <= 4, "counts of a tile fit 16 bits, of its rows two words");
+    static_assert(!STAGED || TILE == CompactLds<DTYPE, STAGED>::kStage, "room for all of a tile");
+    uint32_t *st_v = lds->v;
+    uint16_t *st_p = lds->p;
+    __shared__ uint32_t s_wave[NWV][4];
+    __shared__ uint64_t s_sum[NWV];
 
     const uint32_t L = table[0], total_tiles = table[1];
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
-    // anything to do at all?  (uniform: every thread reads the same words)
-    bool any = false;
-    for (uint32_t l = 0; l < L; ++l) {
-        const SegDev sd = segs[l];
-        any |= on_dense_route(sd, sel, l) || (PLACE && sd.n != 0 && sd.k == 0);
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // tiles plan_tiles and following are work only if a segment has been re-routed
+    const bool net = bid >= plan_tiles;
+    if (net) {
+        bool any = false;
+        for (uint32_t l = lane; l < L; l += 64)
+            any |= (segs[l].flags & kSegFast) && on_dense_route(segs[l], sel, l);
+        if (__ballot(any) == 0) return;
     }
-    if (!any) return;
-    const uint32_t tid = threadIdx.x;
+    const uint32_t step = net ? nb - plan_tiles : total_tiles;
 
-    for (uint32_t t = bid; t < total_tiles; t += nb) {
-        const uint32_t l = segment_of(L, t, [&](uint32_t i) { return segs[i].tile_start; });
+    for (uint32_t t = bid; t < total_tiles; t += step) {
+        // ---- the tile's segment, and the pairs of the segments before it
+        uint32_t l = 0, seg_base = 0;
+        for (uint32_t l0 = 0; l0 < L; l0 += 64) {
+            bool mine = false;
+            if (l0 + lane < L) {
+                const SegDev sd = segs[l0 + lane];
+                mine = t >= sd.tile_start && t - sd.tile_start < (sd.n + TILE - 1) / TILE;
+            }
+            const uint64_t bal = __ballot(mine);
+            if (bal) {
+                l = l0 + uint32_t(__builtin_ctzll(bal));
+                break;
+            }
+        }
         const SegDev sd = segs[l];
         const bool dense = on_dense_route(sd, sel, l);
         // (the candidate route writes the other segments that keep something; a segment that
         // keeps nothing only needs its Index words, which place writes as zeros)
-        if (!dense && !(PLACE && sd.n != 0 && sd.k == 0)) continue;  // uniform
+        if (!dense && !(PLACE && sd.k == 0)) continue;  // uniform
         SelDev se{};
         if (dense) se = sel[l];
         const uint32_t base_rel = (t - sd.tile_start) * TILE;
-        if (base_rel >= sd.n) continue;  // (tile_start of several empty segments coincides)
-        const char *base = grad + sd.offset * EB;
+        const char *base = grad + sd.offset * (DTYPE == kBF16 ? 2 : 4);
 
-        // ---- load (rows of 256 16-byte vectors, lane-contiguous)
+        // ---- load (rows of 256 16-byte vectors, lane-contiguous) and classify.  Elements past
+        // the end are loaded as 0 and never kept.
         uint32_t w[ROWS][4];
         uint32_t gtm[ROWS], eqm[ROWS];
 #pragma unroll
@@ -1871,63 +1974,51 @@ __device__ __forceinline__ void compact_body(uint32_t bid, uint32_t nb, const ch
         if (se.cnt != 0) {
 #pragma unroll
             for (uint32_t r = 0; r < ROWS; ++r) {
-                const uint32_t rel = base_rel + r * ROW_ELEMS + tid * VEC;
-                if (rel >= sd.n) continue;
-                if ((sd.flags & kSegAligned) && rel + VEC <= sd.n) {
-                    const uint4 q =
-                        ld_stream(reinterpret_cast<const uint4 *>(base + uint64_t(rel) * EB));
-                    w[r][0] = q.x; w[r][1] = q.y; w[r][2] = q.z; w[r][3] = q.w;
-                } else {
-                    const uint32_t cntv = min(VEC, sd.n - rel);
-#pragma unroll
-                    for (uint32_t e = 0; e < VEC; ++e) {
-                        if (e >= cntv) continue;
-                        const uint32_t b = load_elem_bits(base, uint64_t(rel) + e, DTYPE);
-                        if (DTYPE == kBF16) w[r][e >> 1] |= (b >> 16) << (16 * (e & 1));
-                        else w[r][e] = b;
-                    }
-                }
+                const uint4 q = load_vec<DTYPE>(base, base_rel + r * ROW_ELEMS + tid * VEC, sd.n);
+                w[r][0] = q.x; w[r][1] = q.y; w[r][2] = q.z; w[r][3] = q.w;
             }
-            // ---- classify.  Elements past the end were loaded as 0 and are never kept.
 #pragma unroll
             for (uint32_t r = 0; r < ROWS; ++r) {
 #pragma unroll
                 for (uint32_t e = 0; e < VEC; ++e) {
                     const uint32_t key = vec_elem_bits<DTYPE>(w[r], e) & 0x7FFFFFFFu;
-                    if (key > se.T) gtm[r] |= 1u << e;
-                    else if (key == se.T && se.quota) eqm[r] |= 1u << e;
+                    gtm[r] |= uint32_t(key > se.T) << e;
+                    eqm[r] |= uint32_t(key == se.T) << e;
                 }
+                if (!se.quota) eqm[r] = 0;
             }
-        }
-        uint64_t g = 0, q = 0;
-#pragma unroll
-        for (uint32_t r = 0; r < ROWS; ++r) {
-            g |= uint64_t(__popc(gtm[r])) << (16 * r);
-            q |= uint64_t(__popc(eqm[r])) << (16 * r);
-        }
-        // ---- workgroup scan of both packed counters (row totals stay below 2^16)
-        uint64_t gtot, qtot;
-        const uint64_t gex =
-            block_excl_scan<uint64_t, kCompactThreads / 64>(g, &gtot, s_scan);
-        const uint64_t qex =
-            block_excl_scan<uint64_t, kCompactThreads / 64>(q, &qtot, s_scan);
-        uint32_t Gr[ROWS], Er[ROWS], Gt = 0, Et = 0;
-#pragma unroll
-        for (uint32_t r = 0; r < ROWS; ++r) {
-            Gr[r] = uint32_t(gtot >> (16 * r)) & 0xFFFFu;
-            Er[r] = uint32_t(qtot >> (16 * r)) & 0xFFFFu;
-            Gt += Gr[r];
-            Et += Er[r];
         }
         if (!PLACE) {
             // the tile's counts, and added to those of its group of kTileGroup tiles (groups
             // are cut from the bucket's tile numbers, whatever the segments)
+            uint32_t both = 0;
+#pragma unroll
+            for (uint32_t r = 0; r < ROWS; ++r) both += __popc(gtm[r]) | (__popc(eqm[r]) << 16);
+            const uint32_t inc = wave_incl_scan<uint32_t>(both);
+            if (lane == 63) s_wave[wave][0] = inc;
+            __syncthreads();
             if (tid == 0) {
-                const uint64_t v = (uint64_t(Gt) << 31) | Et;
+                uint32_t sum = 0;
+#pragma unroll
+                for (uint32_t i = 0; i < NWV; ++i) sum += s_wave[i][0];
+                const uint64_t v = (uint64_t(sum & 0xFFFFu) << 31) | (sum >> 16);
                 tile_cnt[t] = v;
                 atomicAdd(reinterpret_cast<unsigned long long *>(&group_cnt[t / kTileGroup]), v);
             }
-            continue;  // (block_excl_scan ends with a barrier: s_scan may be reused)
+            __syncthreads();
+            continue;
+        }
+        // ---- order inside the tile: the rows' counts, two to a word
+        uint32_t own[4] = {0, 0, 0, 0}, inc[4];  // above rows 0/1, 2/3; ties rows 0/1, 2/3
+#pragma unroll
+        for (uint32_t r = 0; r < ROWS; ++r) {
+            own[r >> 1] |= __popc(gtm[r]) << (16 * (r & 1));
+            own[2 + (r >> 1)] |= __popc(eqm[r]) << (16 * (r & 1));
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            inc[i] = wave_incl_scan<uint32_t>(own[i]);
+            if (lane == 63) s_wave[wave][i] = inc[i];
         }
         // ---- add up the counts of the segment's earlier tiles: whole groups that lie inside
         // the segment by their sums, the tiles before and after them one by one (a few
@@ -1945,58 +2036,69 @@ __device__ __forceinline__ void compact_body(uint32_t bid, uint32_t nb, const ch
                     for (uint32_t j = t0 + tid; j < t; j += kCompactThreads) sum += tile_cnt[j];
                 }
             }
-            sum = block_sum<uint64_t, kCompactThreads / 64>(sum, s_scan);
+            sum = wave_sum<uint64_t>(sum);
+            if (lane == 0) s_sum[wave] = sum;
             uint32_t sb = 0;
-            if (tid < 64) {
-                for (uint32_t i = tid; i < l; i += 64) sb += segment_count(segs[i], sel, i);
-                sb = wave_sum<uint32_t>(sb);
-            }
-            if (tid == 0) {
-                s_excl = sum;
-                s_base = sb;
-            }
+            for (uint32_t i = lane; i < l; i += 64) sb += segment_count(segs[i], sel, i);
+            seg_base = wave_sum<uint32_t>(sb);
         }
         __syncthreads();
-        const uint64_t ex = s_excl;
-        const uint32_t seg_base = s_base;
-        uint32_t grun = uint32_t(ex >> 31), erun = uint32_t(ex & 0x7FFFFFFFu);
+        uint32_t tot[4] = {0, 0, 0, 0}, ex[4];
+        uint64_t before = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) ex[i] = inc[i] - own[i];
+#pragma unroll
+        for (uint32_t q = 0; q < NWV; ++q) {
+            before += s_sum[q];
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) {
+                const uint32_t x = s_wave[q][i];
+                if (q < wave) ex[i] += x;
+                tot[i] += x;
+            }
+        }
+        uint32_t grun = uint32_t(before >> 31), erun = uint32_t(before & 0x7FFFFFFFu);
+        const uint32_t tile_pos = grun + min(erun, se.quota);  // first survivor, in the segment
 
-        // ---- emit pairs and Index words
+        // ---- pairs and Index words
         uint32_t keepm[ROWS];
 #pragma unroll
         for (uint32_t r = 0; r < ROWS; ++r) {
-            uint32_t gb = grun + (uint32_t(gex >> (16 * r)) & 0xFFFFu);
-            uint32_t eb = erun + (uint32_t(qex >> (16 * r)) & 0xFFFFu);
-            const uint32_t rel = base_rel + r * ROW_ELEMS + tid * VEC;
+            const uint32_t sh = 16 * (r & 1);
+            uint32_t gb = grun + ((ex[r >> 1] >> sh) & 0xFFFFu);
+            uint32_t eb = erun + ((ex[2 + (r >> 1)] >> sh) & 0xFFFFu);
+            const uint32_t rel_t = r * ROW_ELEMS + tid * VEC;  // position in the tile
             uint32_t km = gtm[r];
-            uint32_t m = gtm[r] | eqm[r];
-            while (m) {
-                const uint32_t e = __builtin_ctz(m);
-                m &= m - 1;
-                uint32_t pos;
-                bool keep;
-                if ((gtm[r] >> e) & 1u) {
-                    pos = gb + min(eb, se.quota);
-                    keep = true;
-                    ++gb;
+            auto keep_entry = [&](uint32_t e, uint32_t bits, uint32_t pos) {
+                if (STAGED) {
+                    if (DTYPE == kBF16) {
+                        st_v[pos - tile_pos] = bits | (rel_t + e);
+                    } else {
+                        st_v[pos - tile_pos] = bits;
+                        st_p[DTYPE == kF32 ? pos - tile_pos : 0] = uint16_t(rel_t + e);
+                    }
                 } else {
-                    pos = gb + eb;
-                    keep = eb < se.quota;
-                    ++eb;
-                }
-                if (keep) {
-                    km |= 1u << e;
-                    uint32_t bits = 0;
-#pragma unroll
-                    for (uint32_t j = 0; j < VEC; ++j)
-                        if (j == e) bits = vec_elem_bits<DTYPE>(w[r], j);
-                    idx_out[seg_base + pos] = sd.c_off + rel + e;
+                    idx_out[seg_base + pos] = sd.c_off + base_rel + rel_t + e;
                     val_out[seg_base + pos] = __uint_as_float(bits);
+                }
+            };
+#pragma unroll
+            for (uint32_t e = 0; e < VEC; ++e) {
+                const uint32_t bits = vec_elem_bits<DTYPE>(w[r], e);
+                if ((gtm[r] >> e) & 1u) {
+                    keep_entry(e, bits, gb + min(eb, se.quota));
+                    ++gb;
+                } else if ((eqm[r] >> e) & 1u) {
+                    if (eb < se.quota) {
+                        km |= 1u << e;
+                        keep_entry(e, bits, gb + eb);
+                    }
+                    ++eb;
                 }
             }
             keepm[r] = km;
-            grun += Gr[r];
-            erun += Er[r];
+            grun += (tot[r >> 1] >> sh) & 0xFFFFu;
+            erun += (tot[2 + (r >> 1)] >> sh) & 0xFFFFu;
         }
 #pragma unroll
         for (uint32_t r = 0; r < ROWS; ++r) {
@@ -2007,7 +2109,19 @@ __device__ __forceinline__ void compact_body(uint32_t bid, uint32_t nb, const ch
             const uint32_t rel0 = rel - (tid & (LPW - 1)) * VEC;  // first element of the word
             if ((tid & (LPW - 1)) == 0 && rel0 < sd.n) bitmap[(sd.c_off + rel0) >> 5] = v;
         }
-        __syncthreads();  // s_excl / s_base are rewritten by the next iteration
+        __syncthreads();
+        if (STAGED) {
+            const uint32_t n_out = grun + min(erun, se.quota) - tile_pos;
+            uint32_t *io = idx_out + seg_base + tile_pos;
+            float *vo = val_out + seg_base + tile_pos;
+            for (uint32_t i = tid; i < n_out; i += kCompactThreads) {
+                const uint32_t a = st_v[i];
+                const uint32_t rel = DTYPE == kBF16 ? (a & 0xFFFFu) : st_p[DTYPE == kF32 ? i : 0];
+                io[i] = sd.c_off + base_rel + rel;
+                vo[i] = __uint_as_float(DTYPE == kBF16 ? (a & 0xFFFF0000u) : a);
+            }
+            __syncthreads();  // LDS is reused by the next iteration
+        }
     }
 }
 
@@ -2021,8 +2135,8 @@ static_assert(kEmitThreads == kCompactThreads, "one launch for both parts");
 
 template <int DTYPE, uint32_t COMPACT_ROWS, bool WIDE>
 __global__ void __launch_bounds__(kEmitThreads)
-count_kernel(const SparsifyBatch, uint32_t n_emit, const uint32_t *__restrict__ table,
-             const WsLayout wl, uint32_t CAP)
+count_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles,
+             const uint32_t *__restrict__ table, const WsLayout wl, uint32_t CAP)
 {
     const RankView rv = rank_view();
     const SelDev *sel = rv.at<SelDev>(wl.sel);
@@ -2034,19 +2148,30 @@ count_kernel(const SparsifyBatch, uint32_t n_emit, const uint32_t *__restrict__ 
             emit_wide_body<DTYPE, false, 32>(blockIdx.x, n_emit, table, sel, cand, chunk_info,
                                              wl.n_slots, CAP, sc_cnt, nullptr, nullptr, nullptr);
         else
-            emit_body<DTYPE, false>(blockIdx.x, n_emit, table, sel, cand, chunk_info, wl.n_slots,
+            emit_body<DTYPE, false>(nullptr, blockIdx.x, n_emit, table, sel, cand, chunk_info, wl.n_slots,
                                     CAP, sc_cnt, nullptr, nullptr, nullptr);
     } else
-        compact_body<DTYPE, COMPACT_ROWS, false>(
-            blockIdx.x - n_emit, gridDim.x - n_emit, rv.src(), table, sel,
+        compact_body<DTYPE, COMPACT_ROWS, false, false>(
+            nullptr, blockIdx.x - n_emit, gridDim.x - n_emit, plan_tiles, rv.src(), table, sel,
             rv.at<uint64_t>(wl.tile_cnt), rv.at<uint64_t>(wl.group_cnt), nullptr, nullptr, nullptr);
 }
 
 template <int DTYPE, uint32_t COMPACT_ROWS, bool WIDE>
 __global__ void __launch_bounds__(kEmitThreads)
     __attribute__((amdgpu_waves_per_eu(COMPACT_ROWS == 2 ? 7 : 6, 8)))
-place_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t *table, const WsLayout wl, uint32_t CAP)
+place_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles, uint32_t *table,
+             const WsLayout wl, uint32_t CAP)
 {
+    constexpr bool STAGED = COMPACT_ROWS == 4;
+    union Lds {
+        EmitLds<DTYPE> emit;
+        CompactLds<DTYPE, STAGED> compact;
+    };
+    union LdsWide {
+        uint32_t wide;
+        CompactLds<DTYPE, STAGED> compact;
+    };
+    __shared__ typename std::conditional<WIDE, LdsWide, Lds>::type lds;
     const RankView rv = rank_view();
     const SelDev *sel = rv.at<SelDev>(wl.sel);
     if (blockIdx.x == gridDim.x - 1) {  // (any one workgroup: the last has the least to do)
@@ -2057,17 +2182,16 @@ place_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t *table, const WsLayo
         const uint32_t *cand = rv.at<uint32_t>(wl.cand);
         const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
         uint64_t *sc_cnt = rv.at<uint64_t>(wl.sc_cnt);
-        if (WIDE)
+        if constexpr (WIDE)
             emit_wide_body<DTYPE, true, 16>(blockIdx.x, n_emit, table, sel, cand, chunk_info,
                                             wl.n_slots, CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
         else
-            emit_body<DTYPE, true>(blockIdx.x, n_emit, table, sel, cand, chunk_info, wl.n_slots,
+            emit_body<DTYPE, true>(&lds.emit, blockIdx.x, n_emit, table, sel, cand, chunk_info, wl.n_slots,
                                    CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
     } else
-        compact_body<DTYPE, COMPACT_ROWS, true>(blockIdx.x - n_emit, gridDim.x - n_emit, rv.src(),
-                                                table, sel, rv.at<uint64_t>(wl.tile_cnt),
-                                                rv.at<uint64_t>(wl.group_cnt), rv.idx, rv.val,
-                                                rv.bitmap);
+        compact_body<DTYPE, COMPACT_ROWS, true, STAGED>(
+            &lds.compact, blockIdx.x - n_emit, gridDim.x - n_emit, plan_tiles, rv.src(), table, sel,
+            rv.at<uint64_t>(wl.tile_cnt), rv.at<uint64_t>(wl.group_cnt), rv.idx, rv.val, rv.bitmap);
 }
 
 template <typename K>
@@ -2195,10 +2319,8 @@ int launch_select(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, boo
     const bool wide = p->cfg.index_mode == TAGC_INDEX_ADD4;
     const int cus = device_cu_count();
     const size_t lds_hist = kBins1 * sizeof(uint32_t);
-    static bool a_prepare = false, a_hist = false;
-    if (allow_lds(prepare_kernel<DTYPE>, lds_hist, &a_prepare) ||
-        allow_lds(hist1_kernel<DTYPE, kBins1, kHistThreads>, lds_hist, &a_hist))
-        return TAGC_EHIP;
+    static bool a_prepare = false;
+    if (allow_lds(prepare_kernel<DTYPE>, lds_hist, &a_prepare)) return TAGC_EHIP;
     // `total` workgroups shared out to the ranks
     auto per_rank = [&](uint32_t total) { return std::max(1u, total / n); };
     if (acc && p->any_nonfast) {
@@ -2210,23 +2332,27 @@ int launch_select(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, boo
         prepare_kernel<DTYPE><<<dim3(uint32_t(p->table.size()), n), kHistThreads, lds_hist, s>>>(
             sb, table, wide);
     }
-    {
+    if (p->any_fast || p->span_dense) {
+        // (also clears the histograms in memory; short segments need neither)
         ProfileScope ps("scan_spill", s);
         auto scan = acc ? scan_spill_kernel<DTYPE, true> : scan_spill_kernel<DTYPE, false>;
         scan<<<dim3(per_rank(cus * kSpillWgsPerCU), n), kSpillThreads, 0, s>>>(
             sb, table, wl, p->cand_cap, p->zero_bytes / 16, wide);
     }
     {
-        // leaves at once unless a segment is on the dense route (by plan, or because the
-        // scan's selection sent it there)
+        // Two workgroups of 512 threads per compute unit for work that is certain, as many as
+        // there are tiles of a few KiB at most; the net of re-routed segments leaves at once
+        // nearly always.
         ProfileScope ps("hist1", s);
-        if (p->static_dense)
-            hist1_kernel<DTYPE, kBins1, kHistThreads>
-                <<<dim3(per_rank(cus), n), kHistThreads, lds_hist, s>>>(sb, table, wl);
-        else
-            hist1_kernel<DTYPE, kHistWindow, kHistNetThreads>
-                <<<dim3(per_rank(cus * (kHistThreads / kHistNetThreads)), n), kHistNetThreads,
-                   kHistWindow * sizeof(uint32_t), s>>>(sb, table, wl);
+        const bool small = p->small_dense;
+        const uint32_t threads = small ? kSmallThreads : kDenseThreads;
+        const uint32_t most = per_rank(uint32_t(cus) * 2048 / (threads * 2));
+        const uint64_t tile = uint64_t(threads) * p->vec_elems * kDenseRows;
+        const uint32_t planned = uint32_t(std::min<uint64_t>(most, (p->span_dense + tile - 1) / tile));
+        const uint32_t n_span = std::max(p->any_fast ? most : 1u, planned);
+        const dim3 grid(n_span + (small ? uint32_t(p->table.size()) : 0u), n);
+        auto hist1 = small ? hist1_kernel<DTYPE, true> : hist1_kernel<DTYPE, false>;
+        hist1<<<grid, threads, 0, s>>>(sb, table, wl, n_span);
     }
     return TAGC_OK;
 }
@@ -2241,7 +2367,7 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
     const int cus = device_cu_count();
     static int occ_place[2][2] = {{0, 0}, {0, 0}};
     auto per_rank = [&](uint32_t total) { return std::max(1u, total / n); };
-    if (DTYPE == kF32) {
+    if (DTYPE == kF32 && (p->any_fast || p->span_dense)) {
         {
             ProfileScope ps("hist2c", s);
             hist2c_kernel<<<dim3(per_rank(cus * 4), n), 256, 0, s>>>(sb, table, wl, p->cand_cap);
@@ -2267,24 +2393,21 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
         if (occ <= 0) return TAGC_EHIP;
         // emit_body: kEmitItems super-chunks per workgroup; emit_wide_body: one per wave
         const uint32_t per_wg = wd ? kEmitThreads / 64 : uint32_t(kEmitItems);
-        const uint32_t n_emit = (p->total_sc + per_wg - 1) / per_wg;
-        // Dense route: one tile per workgroup when dense-route work is certain.  When no
-        // segment is planned for this route the part is only a safety net for re-routed
-        // segments and nearly always exits at once: a grid that fits the device takes the
-        // tiles in turns then.
-        const uint32_t n_compact =
-            p->static_dense ? p->total_tiles
-                            : std::min<uint32_t>(p->total_tiles,
-                                                 per_rank(uint32_t(cus) * uint32_t(occ)));
+        const uint32_t n_emit = p->any_fast ? (p->total_sc + per_wg - 1) / per_wg : 0;
+        // Dense route: one tile per workgroup where the work is certain.  The tiles of the
+        // candidate route's segments are only a safety net for re-routed ones and the
+        // workgroups for them nearly always exit at once: a grid that fits the device takes
+        // those tiles in turns.
+        const uint32_t n_net = std::min<uint32_t>(p->total_tiles - p->plan_tiles,
+                                                  per_rank(uint32_t(cus) * uint32_t(occ)));
+        const dim3 grid(n_emit + p->plan_tiles + n_net, n);
         {
             ProfileScope ps("count", s);
-            count<<<dim3(n_emit + n_compact, n), kEmitThreads, 0, s>>>(sb, n_emit, table, wl,
-                                                                       p->cand_cap);
+            count<<<grid, kEmitThreads, 0, s>>>(sb, n_emit, p->plan_tiles, table, wl, p->cand_cap);
         }
         {
             ProfileScope ps("place", s);
-            place<<<dim3(n_emit + n_compact, n), kEmitThreads, 0, s>>>(sb, n_emit, table, wl,
-                                                                       p->cand_cap);
+            place<<<grid, kEmitThreads, 0, s>>>(sb, n_emit, p->plan_tiles, table, wl, p->cand_cap);
         }
     }
     if (p->cfg.index_mode == TAGC_INDEX_ADD4 && p->n_c) {

@@ -17,6 +17,11 @@ constexpr uint32_t kBins1 = 32768;   // top 15 key bits: all of a bf16 key, key>
 constexpr uint32_t kBins2 = 65536;   // low 16 key bits (fp32 only)
 constexpr uint32_t kHistThreads = 1024;
 constexpr uint32_t kCompactThreads = 256;
+constexpr uint32_t kDenseThreads = 256;   // dense route's histogram; ...
+constexpr uint32_t kSmallThreads = 1024;  // ... of a plan with segments one workgroup holds
+constexpr uint32_t kDenseRows = 4;        // 16-byte vectors per thread and tile of it
+constexpr uint32_t kSmallVecs = 8;        // 16-byte vectors per thread such a segment has at most
+constexpr uint32_t kHistWindow = 4096;
 constexpr uint32_t kCandRows = 4;        // 16-byte vectors per lane per candidate chunk
 constexpr uint32_t kCandChunksPerSuper = 32;  // chunks one emit workgroup handles
 constexpr uint32_t kEmitThreads = 256;
@@ -52,11 +57,12 @@ struct SegDev {
     uint32_t c_off;       // c-index of element 0 (multiple of 32)
     uint32_t k;           // keep count
     uint32_t tile_start;  // first compaction tile of this segment (dense path)
-    uint32_t flags;       // kSegAligned | kSegFast
+    uint32_t flags;       // kSegAligned | kSegFast | kSegSmall
     uint32_t sc_start;    // first super-chunk of this segment (candidate path)
 };
 constexpr uint32_t kSegAligned = 1;  // offset is a multiple of the 16-byte vector
 constexpr uint32_t kSegFast = 2;     // eligible for the single-read candidate path
+constexpr uint32_t kSegSmall = 4;    // one workgroup's registers hold the whole segment
 static_assert(sizeof(SegDev) == 32, "SegDev layout");
 
 // Result of the threshold search for one segment (device memory).  Written for every
@@ -127,11 +133,15 @@ struct tagc_plan_s {
     uint32_t compact_rows;                    // 16-byte vectors per thread per compaction tile (2 or 4)
     uint32_t tile_elems;                      // elements per compaction tile
     uint32_t total_tiles;
+    uint32_t plan_tiles;                      // tiles of the segments scan_spill never reads, the first ones
     uint32_t total_sc;                        // super-chunks of the candidate path
     uint32_t chunk_elems, cand_cap;           // elements / candidate slots per chunk
     uint32_t cnt_ranges;                      // word offset of the partition ranges in a rank's cnt buffer
     bool any_nonfast;                         // some non-empty segment is never streamed by scan_spill
     bool static_dense;                        // some segment with k > 0 never takes the candidate route
+    bool any_fast;                            // some segment takes it
+    bool small_dense;                         // some dense-route segment is kSegSmall
+    uint64_t span_dense;                      // entries of the dense-route segments that are not
     bool emit_wide;                           // chunks hold hundreds of candidates: a wave per super-chunk in count / place
     uint64_t n_real, n_c, K, U_cap, A_cap, m_cap;
     uint32_t P_cap, T_cap;
