@@ -12,9 +12,9 @@
 //
 // The rounds are driven by cells, not by polling unknowns.  Besides its value every cell
 // keeps one 32-bit word: (sum of the local ranks of its unresolved unknowns) << 15 | degree.
-// When the degree is 1 the upper field *is* the remaining unknown, so a queue of the cells
-// whose degree has just become 1 is all a round needs; one atomic subtract removes an
-// unknown from a cell and tells, by the old degree, whether the cell joins the queue.
+// When the degree is 1 the upper field *is* the remaining unknown, so a queue of the unknowns
+// that have just become the last of a cell is all a round needs; one compare-and-swap removes
+// an unknown from a cell and tells, by the old degree, whether another one joins the queue.
 // Total work is proportional to the unknowns, not to unknowns x rounds.
 #include <type_traits>
 
@@ -59,19 +59,6 @@ __device__ inline Cells cells_of(uint32_t i, uint32_t m_sub, uint32_t sw0, uint3
     r.c[2] = 2 * m_sub + hash_slot(i, sw2, m_sub, &n2);
     r.neg = n0 | (n1 << 1) | (n2 << 2);
     return r;
-}
-
-// Appends `value` to the queue for every active lane with `pred`; one LDS atomic per wave.
-__device__ inline void queue_push(bool pred, uint32_t value, uint32_t *count, uint16_t *queue)
-{
-    const uint64_t bal = __ballot(pred);
-    if (bal == 0) return;
-    const uint32_t lane = lane_id();
-    const uint32_t leader = __builtin_ctzll(bal);
-    uint32_t base = 0;
-    if (lane == leader) base = atomicAdd(count, uint32_t(__popcll(bal)));
-    base = __shfl(base, leader, 64);
-    if (pred) queue[base + uint32_t(__popcll(bal & ((1ull << lane) - 1ull)))] = uint16_t(value);
 }
 
 // Enumerates the set bits of the merged Index in ascending order into idx_out.  One
@@ -121,86 +108,272 @@ enumerate_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words,
         if (base + i < U) idx_out[base + i] = stage[i];
 }
 
-// Appends up to three values per lane (those whose predicate holds) with one LDS atomic
-// per wave; `queue` points at the first free slot of the round, `count` at the number of
-// slots the round has taken so far.  Safe in divergent code: only the active lanes take part.
-__device__ inline void queue_push3(bool p0, uint32_t v0, bool p1, uint32_t v1, bool p2,
-                                   uint32_t v2, uint32_t *count, uint16_t *queue)
+// A partition in LDS.  A cell is 64 bits: value bits in the low half, meta word in the high one.
+//
+// kPacked: an unknown keeps where its cells are and their signs, in 40 bits (sub-tables of 4096
+// cells at most); else its c-index, from which they are hashed anew.  Once resolved, its word
+// holds its value.  Hashing an unknown again was a third of the vector instructions of the
+// rounds (three 32-bit multiplies per hash, at quarter rate).
+//
+// A queue entry is an unknown and which of its three cells it is alone in.
+template <bool kPacked>
+struct PartLds {
+    unsigned long long *cell;  // [T_cap]
+    uint32_t *word;            // [P_cap] packed slots or c-index, then the value
+    uint32_t *claimed;         // [P_cap/32 + 1] unknowns that are, or were, in the queue
+    uint16_t *queue;           // unknown | sub-table of the cell << kUnknownBits, each unknown once
+    uint8_t *rest;             // [P_cap] packed: slot_2 >> 8, and the signs in bits 4 .. 6
+    uint32_t m_sub, sw0, sw1, sw2;
+    static constexpr uint32_t kUnknownBits = kPacked ? 13 : 14;
+    static_assert(kDefaultPartUnknowns <= 1u << 13 && kMaxPartUnknowns <= 1u << 14, "queue entry");
+    static_assert(kDefaultPartCells <= 3u << 12, "packed slots are 12 bits");
+
+    __device__ __forceinline__ PartLds(void *lds, uint32_t T_cap, uint32_t P_cap)
+    {
+        cell = static_cast<unsigned long long *>(lds);
+        word = reinterpret_cast<uint32_t *>(cell + T_cap);
+        claimed = word + P_cap;
+        queue = reinterpret_cast<uint16_t *>(claimed + P_cap / 32 + 1);
+        rest = reinterpret_cast<uint8_t *>(queue + P_cap);
+    }
+    __device__ __forceinline__ uint32_t *value(uint32_t c) const
+    {
+        return reinterpret_cast<uint32_t *>(cell + c);
+    }
+    __device__ __forceinline__ uint32_t *meta(uint32_t c) const { return value(c) + 1; }
+    // unknown u has c-index i: keeps what of_unknown needs, and returns the cells
+    __device__ __forceinline__ Cells place(uint32_t u, uint32_t i) const
+    {
+        const Cells cl = cells_of(i, m_sub, sw0, sw1, sw2);
+        if (kPacked) {
+            const uint32_t s1 = cl.c[1] - m_sub, s2 = cl.c[2] - 2 * m_sub;
+            word[u] = cl.c[0] | (s1 << 12) | (s2 << 24);
+            rest[u] = uint8_t((s2 >> 8) | (cl.neg << 4));
+        } else {
+            word[u] = i;
+        }
+        return cl;
+    }
+    // an unresolved unknown's cells
+    __device__ __forceinline__ Cells of_unknown(uint32_t u) const
+    {
+        const uint32_t w = word[u];
+        if (!kPacked) return cells_of(w, m_sub, sw0, sw1, sw2);
+        const uint32_t b = rest[u];
+        Cells r;
+        r.c[0] = w & 0xFFFu;
+        r.c[1] = m_sub + ((w >> 12) & 0xFFFu);
+        r.c[2] = 2 * m_sub + ((w >> 24) | ((b & 0xFu) << 8));
+        r.neg = b >> 4;
+        return r;
+    }
+};
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
 {
-    const uint64_t b0 = __ballot(p0), b1 = __ballot(p1), b2 = __ballot(p2);
-    const uint32_t n0 = __popcll(b0), n1 = __popcll(b1), n2 = __popcll(b2);
-    if (n0 + n1 + n2 == 0) return;
-    const uint32_t lane = lane_id();
-    const uint64_t lt = (1ull << lane) - 1ull;
-    const uint32_t leader = __builtin_ctzll(__ballot(true));
-    uint32_t base = 0;
-    if (lane == leader) base = atomicAdd(count, n0 + n1 + n2);
-    base = __shfl(base, leader, 64);
-    if (p0) queue[base + uint32_t(__popcll(b0 & lt))] = uint16_t(v0);
-    if (p1) queue[base + n0 + uint32_t(__popcll(b1 & lt))] = uint16_t(v1);
-    if (p2) queue[base + n0 + n1 + uint32_t(__popcll(b2 & lt))] = uint16_t(v2);
+    return __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0));
 }
 
-
-// One entry of a round's queue: cell q, which had degree 1 when it was queued.  If it still
-// has, and its unknown has not been reached through another cell already, the unknown's
-// value is read there and taken out of its three cells; cells that thereby reach degree 1
-// are queued for the next round.  Called by any subset of a wave's lanes.
-__device__ __forceinline__ void resolve_entry(uint32_t q, unsigned long long *cell,
-                                              uint32_t *claimed, uint32_t *idx,
-                                              uint32_t *any_now, uint32_t *n_next,
-                                              uint16_t *next_queue, uint32_t m_sub,
-                                              uint32_t sw0, uint32_t sw1, uint32_t sw2)
+// First free of n slots taken off *count, by the first active lane for its wave (n uniform).
+__device__ __forceinline__ uint32_t take_slots(uint32_t *count, uint32_t n)
 {
-    const unsigned long long oq = cell[q];
-    const uint32_t m = uint32_t(oq >> 32);
-    if ((m & kDegMask) != 1u) return;  // emptied since it was queued
-    const uint32_t u = m >> 15, bit = 1u << (u & 31);
-    if (atomicOr(&claimed[u >> 5], bit) & bit) return;  // reached through another cell
-    *any_now = 1;
-    const Cells cl = cells_of(idx[u], m_sub, sw0, sw1, sw2);
-    const uint32_t c[3] = {cl.c[0], cl.c[1], cl.c[2]};
-    const uint32_t neg = cl.neg;
-    const uint32_t j = c[0] == q ? 0u : (c[1] == q ? 1u : 2u);
-    const float cv = __uint_as_float(uint32_t(oq));
-    const float x = ((neg >> j) & 1u) ? -cv : cv;
-    idx[u] = __float_as_uint(x);  // the c-index has done its job: keep the value there
-    const unsigned long long dec = (unsigned long long)((u << 15) + 1u) << 32;
-    unsigned long long o[3], r[3];
+    const uint32_t leader = __builtin_ctzll(__ballot(true));
+    uint32_t at = 0;
+    // (an address the compiler cannot tell to be uniform: it would wrap the one lane's add in
+    // the dozen instructions that combine a whole wave's)
+    __attribute__((address_space(3))) uint32_t *lds = (__attribute__((address_space(3))) uint32_t *)count;
+    asm("" : "+v"(lds));
+    if (lane_id() == leader)
+        at = __hip_atomic_fetch_add((uint32_t *)lds, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return __builtin_amdgcn_readlane(at, leader);
+}
+
+// The first round's queue: the unknowns alone in a cell from the start, each with the first
+// sub-table where it is.  Thread t looks at the cells t, t + NT, ... of every sub-table, kSlots of
+// them at most, all at once; one LDS atomic per wave.  Whoever sets an unknown's bit in `claimed`
+// queues it; the sub-tables take turns, so that which of its cells an unknown is read from does
+// not depend on the order of the waves (cells that were rounded on the wire differ).
+template <uint32_t NT, uint32_t kSlots, bool kPacked, typename Barrier>
+__device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t tid,
+                                            uint32_t *count, Barrier &&barrier)
+{
+    uint32_t u[3][kSlots], mine = 0, n = 0;
+    static_assert(3 * kSlots <= 32, "a bit per cell");
 #pragma unroll
-    for (int k = 0; k < 3; ++k) o[k] = uint32_t(k) == j ? oq : cell[c[k]];
+    for (uint32_t j = 0; j < 3; ++j)
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const float nv = __uint_as_float(uint32_t(o[k])) + (((neg >> k) & 1u) ? x : -x);
-        r[k] = atomicCAS(&cell[c[k]], o[k],
-                         ((o[k] - dec) & 0xFFFFFFFF00000000ull) | __float_as_uint(nv));
-    }
+        for (uint32_t q = 0; q < kSlots; ++q) {
+            const uint32_t c = tid + q * NT;
+            u[j][q] = c < p.m_sub ? *p.meta(j * p.m_sub + c) : 0u;
+        }
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        while (r[k] != o[k]) {  // another unknown of the round got there first: redo
-            o[k] = r[k];
-            const float nv = __uint_as_float(uint32_t(o[k])) + (((neg >> k) & 1u) ? x : -x);
-            r[k] = atomicCAS(&cell[c[k]], o[k],
-                             ((o[k] - dec) & 0xFFFFFFFF00000000ull) | __float_as_uint(nv));
+    for (uint32_t j = 0; j < 3; ++j) {
+        uint32_t had[kSlots];
+        if (j) barrier();
+#pragma unroll
+        for (uint32_t q = 0; q < kSlots; ++q) {
+            had[q] = 0xFFFFFFFFu;
+            const bool one = (u[j][q] & kDegMask) == 1u;
+            u[j][q] >>= 15;
+            if (one) had[q] = atomicOr(&p.claimed[u[j][q] >> 5], 1u << (u[j][q] & 31));
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < kSlots; ++q) {
+            const bool queued = !((had[q] >> (u[j][q] & 31)) & 1u);
+            mine |= uint32_t(queued) << (j * kSlots + q);
+            n += __popcll(__ballot(queued));
         }
     }
-    queue_push3((uint32_t(o[0] >> 32) & kDegMask) == 2u, c[0],
-                (uint32_t(o[1] >> 32) & kDegMask) == 2u, c[1],
-                (uint32_t(o[2] >> 32) & kDegMask) == 2u, c[2], n_next, next_queue);
+    if (n == 0) return;
+    uint32_t at = take_slots(count, n);
+#pragma unroll
+    for (uint32_t j = 0; j < 3; ++j)
+#pragma unroll
+        for (uint32_t q = 0; q < kSlots; ++q) {
+            const bool queued = (mine >> (j * kSlots + q)) & 1u;
+            const uint64_t bal = __ballot(queued);
+            if (queued) p.queue[at + lanes_below(bal)] = uint16_t(u[j][q] | (j << p.kUnknownBits));
+            at += uint32_t(__popcll(bal));
+        }
+}
+
+// One queue entry: an unknown that is alone in its cell `own`.  Its value is read there (nobody
+// else touches a cell of degree 1) and taken out of its two other cells; an unknown that is
+// thereby left alone in one is queued for the next round.  Called by any subset of a wave's lanes.
+//
+// A round is a chain of dependent LDS accesses: entry -> slots -> own value, the other cells' values
+// and their degrees (counted down on the way) -> the new values, and claims for the next queue ->
+// queue.  Every link goes out for all cells together, and the values are swapped right behind
+// their reading: cells are shared by unknowns that leave in the same round, and a swap that finds
+// another value has to be made again.  With value and degree in one 64-bit swap, whose reading
+// lay a few dozen instructions back, most waves had several of those in a row.  Rounds of a
+// partition, clocks, before and after: 8192 unknowns in 12288 cells (11 rounds) 47.6 K -> 38.3 K;
+// in 10776 cells (21 rounds) 61.9 K -> 50.0 K; one-bucket decodes of the latter 767 -> 656 us.
+template <bool kPacked>
+__device__ __forceinline__ void resolve_unknown(const PartLds<kPacked> &p, uint32_t entry,
+                                                uint32_t *n_next, uint16_t *next_queue)
+{
+    constexpr int kScope = __HIP_MEMORY_SCOPE_WORKGROUP;
+    const uint32_t u = entry & ((1u << p.kUnknownBits) - 1u), j = entry >> p.kUnknownBits;
+    const Cells cl = p.of_unknown(u);
+    const uint32_t k[2] = {j == 0 ? 1u : 0u, j == 2 ? 1u : 2u};  // the sub-tables of the others
+    const uint32_t own = j == 0 ? cl.c[0] : (j == 1 ? cl.c[1] : cl.c[2]);
+    const uint32_t c[2] = {j == 0 ? cl.c[1] : cl.c[0], j == 2 ? cl.c[1] : cl.c[2]};
+    const uint32_t dec = (u << 15) + 1u;
+    uint32_t was[2], v[2], r[2], t[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        was[i] = __hip_atomic_fetch_sub(p.meta(c[i]), dec, __ATOMIC_RELAXED, kScope);
+    const uint32_t x = __hip_atomic_load(p.value(own), __ATOMIC_RELAXED, kScope) ^
+                       ((cl.neg >> j) << 31);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) v[i] = __hip_atomic_load(p.value(c[i]), __ATOMIC_RELAXED, kScope);
+    p.word[u] = x;
+    auto minus = [&](int i) { return __float_as_uint(__uint_as_float(v[i]) - __uint_as_float(t[i])); };
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        t[i] = x ^ ((cl.neg >> k[i]) << 31);
+        r[i] = atomicCAS(p.value(c[i]), v[i], minus(i));
+    }
+    // Cells that came down to one unknown: was - dec is (that unknown << 15) | 1.  It is claimed
+    // in the order of the sub-tables: of two cells that it is left alone in now, it is read from
+    // the first (which a wave's lanes settle by this order, and waves by who is first).
+    uint32_t had[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, left[2];
+    bool two[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        two[i] = (was[i] & kDegMask) == 2u;
+        left[i] = (was[i] - dec) >> 15;
+    }
+    auto claim = [&](uint32_t w) { return atomicOr(&p.claimed[w >> 5], 1u << (w & 31)); };
+    if (two[0] & (j != 0)) had[0] = claim(left[0]);
+    const uint32_t mid = j == 0 ? left[0] : left[1];
+    if ((j == 0 ? two[0] : two[1]) & (j != 1)) had[1] = claim(mid);
+    if (two[1] & (j != 2)) had[2] = claim(left[1]);
+    while ((r[0] != v[0]) | (r[1] != v[1])) {
+        // again, both together (one that was made already puts what it finds back)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const bool made = r[i] == v[i];
+            if (made) t[i] = 0u;
+            v[i] = r[i];
+            r[i] = atomicCAS(p.value(c[i]), v[i], made ? v[i] : minus(i));
+        }
+    }
+    const bool push[2] = {!(((j == 0 ? had[1] : had[0]) >> (left[0] & 31)) & 1u),
+                          !(((j == 2 ? had[1] : had[2]) >> (left[1] & 31)) & 1u)};
+    const uint64_t b0 = __ballot(push[0]), b1 = __ballot(push[1]);
+    const uint32_t n0 = __popcll(b0), n1 = __popcll(b1);
+    if (n0 + n1 == 0) return;
+    const uint32_t at = take_slots(n_next, n0 + n1);
+    if (push[0]) next_queue[at + lanes_below(b0)] = uint16_t(left[0] | (k[0] << p.kUnknownBits));
+    if (push[1]) next_queue[at + n0 + lanes_below(b1)] = uint16_t(left[1] | (k[1] << p.kUnknownBits));
+}
+
+// The rounds of a partition whose first queue has s_n[1] entries, by NT threads that meet at
+// `barrier`: one barrier per round.  The queue's [head, tail) holds the unknowns that the round
+// before left alone in a cell.  A cell of degree 1 is touched by its own unknown only, so that
+// one may read its value there at any time; every other cell is only ever changed by atomics.
+// Removals of a round run concurrently with its readings, which changes
+// neither the set of unknowns the round resolves (an unknown left alone in a cell now is queued
+// for the next round) nor, beyond rounding order, their values.
+// s_n: per round the number of unknowns it queued for the next one, three slots used in turn:
+// round r reads what round r-1 left in slot r%3 and adds to slot (r+1)%3, so a wave that is late
+// into round r never sees what faster waves of the same round already write; the slot nobody
+// touches in round r is cleared by thread 0 for its next use.  Returns the unknowns resolved.
+template <uint32_t NT, bool kPacked, typename Barrier>
+__device__ __forceinline__ uint32_t peel_rounds(const PartLds<kPacked> &p, uint32_t tid,
+                                                uint32_t (&s_n)[3], uint32_t &max_rounds,
+                                                Barrier &&barrier)
+{
+    uint32_t head = 0;
+    for (uint32_t r = 1;; ++r) {
+        barrier();  // queue, counts and cells of the previous round are complete
+        const uint32_t tail = head + s_n[r % 3];
+        if (tail == head) {
+            max_rounds = max(max_rounds, r - 1);
+            return head;
+        }
+        if (tid == 0) s_n[(r + 2) % 3] = 0;  // read in round r-1, added to again in round r+1
+        for (uint32_t e = head + tid; e < tail; e += NT)
+            resolve_unknown(p, p.queue[e], &s_n[(r + 1) % 3], p.queue + tail);
+        head = tail;
+    }
+}
+
+// Output value of unknown u: unknowns never reached stay at 0 or, when the plan asks for it, are
+// the median of their three signed readings of the cells as the rounds left them.
+template <bool kPacked>
+__device__ __forceinline__ float unknown_value(const PartLds<kPacked> &p, uint32_t u, uint32_t mode)
+{
+    if ((p.claimed[u >> 5] >> (u & 31)) & 1u) return __uint_as_float(p.word[u]);
+    if (mode == TAGC_DECODE_PEEL) return 0.0f;
+    const Cells cl = p.of_unknown(u);
+    float r[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const float cv = __uint_as_float(uint32_t(p.cell[cl.c[j]]));
+        r[j] = ((cl.neg >> j) & 1u) ? -cv : cv;
+    }
+    return fmaxf(fminf(r[0], r[1]), fminf(fmaxf(r[0], r[1]), r[2]));
+}
+
+__device__ inline void report_unresolved(uint32_t n, uint32_t mode, uint32_t *status)
+{
+    if (!n) return;
+    atomicAdd(&status[TAGC_ST_UNRESOLVED], n);
+    if (mode != TAGC_DECODE_PEEL) atomicAdd(&status[TAGC_ST_ESTIMATED], n);
 }
 
 // Peels sketch partitions: unknowns rho0 .. rho0+Pa-1 of idx_out, cells a*3*m_sub ...
-// An LDS cell is 64 bits: value bits in the low half, meta word (rank-sum << 15 | degree)
-// in the high half, so one compare-and-swap subtracts a value and removes an unknown.
 //
 // The LDS a partition needs leaves room for one workgroup per CU, and the rounds are bound
 // by LDS latency, not by memory.  So the grid is one workgroup per CU, each taking
 // partitions b, b+G, ...; while one partition is being peeled the cells and c-indices of
 // the workgroup's next one are already on their way into registers, and staging it costs
 // LDS stores only.
-// kCellPre / kIdxPre: cells / unknowns per thread the instantiation can hold (a partition has
-// at most kCellPre * kDecodeThreads cells, so a round's queue needs kCellPre sweeps at most).
-template <uint32_t kCellPre, uint32_t kIdxPre>
+// kCellPre / kIdxPre: cells / unknowns per thread the instantiation can hold.
+template <uint32_t kCellPre, uint32_t kIdxPre, bool kPacked>
 __global__ void __launch_bounds__(kDecodeThreads)
 peel_kernel(const float *__restrict__ sketch, const uint32_t *__restrict__ header,
             const uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
@@ -208,22 +381,13 @@ peel_kernel(const float *__restrict__ sketch, const uint32_t *__restrict__ heade
             uint32_t P_cap, uint32_t mode)
 {
     extern __shared__ uint64_t lds64[];
-    unsigned long long *cell = reinterpret_cast<unsigned long long *>(lds64);  // [T_cap]
-    uint32_t *idx = reinterpret_cast<uint32_t *>(cell + T_cap);      // [P_cap] c-indices
-    uint32_t *claimed = idx + P_cap;                 // [P_cap/32 + 1] resolved unknowns
-    uint32_t *scratch = claimed + (P_cap / 32 + 1);  // [32]
-    uint16_t *queue = reinterpret_cast<uint16_t *>(scratch + 32);  // [T_cap] cells of degree 1
-    // Per round: the number of cells the round queued for the next one, and whether it
-    // resolved anything.  Three of each, used in turn: round r reads what round r-1 left
-    // in slot r%3 (n) resp. (r-1)%3 (any) and writes slot (r+1)%3 resp. r%3, so a wave that
-    // is late into round r never sees what faster waves of the same round already write;
-    // the slot nobody touches in round r is cleared by thread 0 for its next use.
-    __shared__ uint32_t s_n[3], s_any[3];
+    PartLds<kPacked> part(lds64, T_cap, P_cap);
+    __shared__ uint32_t s_n[3];  // see peel_rounds
     const uint32_t tid = threadIdx.x;
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
-    const uint32_t *meta_hi = reinterpret_cast<const uint32_t *>(cell) + 1;  // meta of cell c: [2c]
     const uint32_t cells = 3 * m_sub;
+    part.m_sub = m_sub;
 
     // the cells and c-indices of partition `p` into registers (zeros beyond their ends)
     float pre_cell[kCellPre];
@@ -252,17 +416,18 @@ peel_kernel(const float *__restrict__ sketch, const uint32_t *__restrict__ heade
     const uint32_t Pa = uint32_t(uint64_t(a + 1) * U / A) - rho0;
     // the partition's hash functions: the seed under the salt the encoders used
     const uint32_t sa = salt[a];
-    const uint32_t sw0 = seed_word(seed, 3 * sa), sw1 = seed_word(seed, 3 * sa + 1),
-                   sw2 = seed_word(seed, 3 * sa + 2);
+    part.sw0 = seed_word(seed, 3 * sa);
+    part.sw1 = seed_word(seed, 3 * sa + 1);
+    part.sw2 = seed_word(seed, 3 * sa + 2);
 
     // ---- stage the partition's cells from the registers, clear state
 #pragma unroll
     for (uint32_t q = 0; q < kCellPre; ++q) {
         const uint32_t c = tid + q * kDecodeThreads;
-        if (c < cells) cell[c] = __float_as_uint(pre_cell[q]);
+        if (c < cells) part.cell[c] = __float_as_uint(pre_cell[q]);
     }
-    for (uint32_t c = tid; c < P_cap / 32 + 1; c += kDecodeThreads) claimed[c] = 0;
-    if (tid < 3) s_n[tid] = s_any[tid] = 0;
+    for (uint32_t c = tid; c < P_cap / 32 + 1; c += kDecodeThreads) part.claimed[c] = 0;
+    if (tid < 3) s_n[tid] = 0;
     __syncthreads();
     PHASE_MARK(0);
 
@@ -271,78 +436,27 @@ peel_kernel(const float *__restrict__ sketch, const uint32_t *__restrict__ heade
     for (uint32_t q = 0; q < kIdxPre; ++q) {
         const uint32_t u = tid + q * kDecodeThreads;
         if (u < Pa) {
-            const uint32_t i = pre_idx[q];
-            idx[u] = i;
-            const Cells cl = cells_of(i, m_sub, sw0, sw1, sw2);
-            const unsigned long long inc = (unsigned long long)((u << 15) + 1u) << 32;
+            const Cells cl = part.place(u, pre_idx[q]);
 #pragma unroll
-            for (int j = 0; j < 3; ++j) atomicAdd(&cell[cl.c[j]], inc);
+            for (int j = 0; j < 3; ++j) atomicAdd(part.meta(cl.c[j]), (u << 15) + 1u);
         }
     }
     // the registers are free again: the next partition's data travels during the rounds
     if (a + gridDim.x < A) prefetch(a + gridDim.x);
     __syncthreads();
-    if (mode != TAGC_DECODE_ESTIMATE) {  // estimation alone: the queue stays empty
-        for (uint32_t c0 = 0; c0 < cells; c0 += kDecodeThreads) {
-            const uint32_t c = c0 + tid;
-            queue_push(c < cells && (meta_hi[2 * c] & kDegMask) == 1u, c, &s_n[1], queue);
-        }
-    }
+    if (mode != TAGC_DECODE_ESTIMATE)  // estimation alone: the queue stays empty
+        queue_first<kDecodeThreads, (kCellPre + 2) / 3>(part, tid, &s_n[1], [] { __syncthreads(); });
     PHASE_MARK(1);
 
-    // ---- peel.  One barrier per round: the queue segment [head, tail) holds the cells
-    // that reached degree 1 in the previous round.  A cell of degree 1 is touched by its own
-    // unknown only, so whoever claims that unknown may read its value there at any time;
-    // every other cell is only ever changed by compare-and-swap.  Removals of a round run
-    // concurrently with its claims, which changes neither the set of unknowns the round
-    // resolves (a cell that reaches degree 1 now is queued for the next round) nor, beyond
-    // rounding order, their values.
-    uint32_t rounds = 0, head = 0;
-    for (uint32_t r = 1;; ++r) {
-        __syncthreads();  // queue, counts and cells of the previous round are complete
-        const uint32_t cur = r % 3, nxt = (r + 1) % 3, idle = (r + 2) % 3;
-        if (s_any[idle]) ++rounds;  // slot (r-1)%3: did round r-1 resolve anything
-        const uint32_t tail = head + s_n[cur];
-        if (tail == head) break;
-        if (tid == 0) {
-            s_n[idle] = 0;     // read in round r-1, added to again in round r+1
-            s_any[nxt] = 0;    // read in round r-1 (as its idle slot), set again in round r+1
-        }
-        for (uint32_t e = head + tid; e < tail; e += kDecodeThreads)
-            resolve_entry(queue[e], cell, claimed, idx, &s_any[cur], &s_n[nxt], queue + tail,
-                          m_sub, sw0, sw1, sw2);
-        head = tail;
-    }
+    const uint32_t resolved =
+        peel_rounds<kDecodeThreads>(part, tid, s_n, max_rounds, [] { __syncthreads(); });
     PHASE_MARK(2);
 
     // ---- values leave in one contiguous sweep (stored one by one as they were found they
-    // would cost a cache-line access each); unknowns never claimed stay at 0
-    // or, when the plan asks for it, the median of their three signed readings of the
-    // cells as the rounds left them (idx[u] still holds the c-index of such an unknown)
-    for (uint32_t u = tid; u < Pa; u += kDecodeThreads) {
-        float x = 0.0f;
-        if ((claimed[u >> 5] >> (u & 31)) & 1u) {
-            x = __uint_as_float(idx[u]);
-        } else if (mode != TAGC_DECODE_PEEL) {
-            const Cells cl = cells_of(idx[u], m_sub, sw0, sw1, sw2);
-            float r[3];
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const float cv = __uint_as_float(uint32_t(cell[cl.c[j]]));
-                r[j] = ((cl.neg >> j) & 1u) ? -cv : cv;
-            }
-            x = fmaxf(fminf(r[0], r[1]), fminf(fmaxf(r[0], r[1]), r[2]));
-        }
-        val_out[rho0 + u] = x;
-    }
-    uint32_t resolved = 0;
-    for (uint32_t c = tid; c < P_cap / 32 + 1; c += kDecodeThreads) resolved += __popc(claimed[c]);
-    resolved = block_sum<uint32_t, kDecodeThreads / 64>(resolved, scratch);
-    if (tid == 0 && resolved < Pa) {
-        atomicAdd(&status[TAGC_ST_UNRESOLVED], Pa - resolved);
-        if (mode != TAGC_DECODE_PEEL) atomicAdd(&status[TAGC_ST_ESTIMATED], Pa - resolved);
-    }
-    max_rounds = max(max_rounds, rounds);
+    // would cost a cache-line access each)
+    for (uint32_t u = tid; u < Pa; u += kDecodeThreads) val_out[rho0 + u] = unknown_value(part, u, mode);
+    if (tid == 0) report_unresolved(Pa - resolved, mode, status);
+    __syncthreads();  // before the next partition is staged
     PHASE_MARK(3);
     }  // partitions of this workgroup
     if (tid == 0 && max_rounds) atomicMax(&status[TAGC_ST_ROUNDS], max_rounds);
@@ -367,6 +481,7 @@ constexpr uint32_t kLoadThreads = kLoadWaves * 64, kPeelThreads = kPeelWaves * 6
 constexpr uint32_t kLoadCells = (kDefaultPartCells + kLoadThreads - 1) / kLoadThreads;  // per thread
 constexpr uint32_t kUnit = 16;  // cells of one rank a loader thread requests at a time
 static_assert(kLoadCells == 3 * kUnit, "a rank's cells are three units per loader thread");
+constexpr uint32_t kPeelSlots = (kDefaultPartCells / 3 + kPeelThreads - 1) / kPeelThreads;
 constexpr uint32_t kPeelIdx = (kDefaultPartUnknowns + kPeelThreads - 1) / kPeelThreads;
 
 // Barrier among the kPeelWaves peeling waves: every wave adds 1 to an LDS word and goes on
@@ -390,14 +505,9 @@ sum_peel_kernel(const RankPtrs rp, uint32_t n_in, const uint32_t *__restrict__ h
                 uint32_t T_cap, uint32_t P_cap, uint32_t mode)
 {
     extern __shared__ uint64_t lds64[];
-    unsigned long long *cell = reinterpret_cast<unsigned long long *>(lds64);  // [T_cap]
-    uint32_t *idx = reinterpret_cast<uint32_t *>(cell + T_cap);      // [P_cap] c-indices
-    uint32_t *claimed = idx + P_cap;                 // [P_cap/32 + 1] resolved unknowns
-    uint32_t *scratch = claimed + (P_cap / 32 + 1);  // [32]
-    uint16_t *queue = reinterpret_cast<uint16_t *>(scratch + 32);  // [T_cap] cells of degree 1
-    __shared__ uint32_t s_n[3], s_any[3];  // as in peel_kernel
-    __shared__ uint32_t s_bar;             // peel_barrier's word
-    __shared__ uint32_t s_resolved;        // unknowns the current partition resolved
+    PartLds<true> part(lds64, T_cap, P_cap);
+    __shared__ uint32_t s_n[3];  // see peel_rounds
+    __shared__ uint32_t s_bar;   // peel_barrier's word
     const uint32_t tid = threadIdx.x;
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
@@ -471,7 +581,7 @@ sum_peel_kernel(const RankPtrs rp, uint32_t n_in, const uint32_t *__restrict__ h
 #pragma unroll
             for (uint32_t q = 0; q < kLoadCells; ++q) {
                 const uint32_t c = lt + q * kLoadThreads;
-                if (c < cells) cell[c] = __float_as_uint(acc[q]);
+                if (c < cells) part.cell[c] = __float_as_uint(acc[q]);
             }
             __syncthreads();  // the partition is staged
             if (a + gridDim.x < A) sum_partition(a + gridDim.x);
@@ -480,7 +590,6 @@ sum_peel_kernel(const RankPtrs rp, uint32_t n_in, const uint32_t *__restrict__ h
     }
 
     // ---------------------------------------------------------------- the peelers
-    uint32_t *meta_hi = reinterpret_cast<uint32_t *>(cell) + 1;  // meta of cell c: [2c]
     uint32_t pre_idx[kPeelIdx];
     auto prefetch_idx = [&](uint32_t p) {
         const uint32_t r0 = uint32_t(uint64_t(p) * U / A);
@@ -492,25 +601,18 @@ sum_peel_kernel(const RankPtrs rp, uint32_t n_in, const uint32_t *__restrict__ h
         }
     };
     if (blockIdx.x < A) prefetch_idx(blockIdx.x);
-    uint32_t bar_expected = 0, max_rounds = 0, Pa_prev = 0;
+    uint32_t bar_expected = 0, max_rounds = 0;
+    part.m_sub = m_sub;
     for (uint32_t a = blockIdx.x; a < A; a += gridDim.x) {
         const uint32_t rho0 = uint32_t(uint64_t(a) * U / A);
         const uint32_t Pa = uint32_t(uint64_t(a + 1) * U / A) - rho0;
         const uint32_t sa = salt[a];
-        const uint32_t sw0 = seed_word(seed, 3 * sa), sw1 = seed_word(seed, 3 * sa + 1),
-                       sw2 = seed_word(seed, 3 * sa + 2);
+        part.sw0 = seed_word(seed, 3 * sa);
+        part.sw1 = seed_word(seed, 3 * sa + 1);
+        part.sw2 = seed_word(seed, 3 * sa + 2);
         __syncthreads();  // everybody is done with the previous partition
-        if (tid == 0) {
-            // what the previous partition left unresolved
-            if (a != blockIdx.x && s_resolved < Pa_prev) {
-                atomicAdd(&status[TAGC_ST_UNRESOLVED], Pa_prev - s_resolved);
-                if (mode != TAGC_DECODE_PEEL)
-                    atomicAdd(&status[TAGC_ST_ESTIMATED], Pa_prev - s_resolved);
-            }
-            s_resolved = 0;
-        }
-        for (uint32_t c = tid; c < P_cap / 32 + 1; c += kPeelThreads) claimed[c] = 0;
-        if (tid < 3) s_n[tid] = s_any[tid] = 0;
+        for (uint32_t c = tid; c < P_cap / 32 + 1; c += kPeelThreads) part.claimed[c] = 0;
+        if (tid < 3) s_n[tid] = 0;
         __syncthreads();  // the loaders have staged the cells
 
         // ---- every unknown joins its three cells
@@ -518,74 +620,22 @@ sum_peel_kernel(const RankPtrs rp, uint32_t n_in, const uint32_t *__restrict__ h
         for (uint32_t q = 0; q < kPeelIdx; ++q) {
             const uint32_t u = tid + q * kPeelThreads;
             if (u < Pa) {
-                const uint32_t i = pre_idx[q];
-                idx[u] = i;
-                const Cells cl = cells_of(i, m_sub, sw0, sw1, sw2);
-                const unsigned long long inc = (unsigned long long)((u << 15) + 1u) << 32;
+                const Cells cl = part.place(u, pre_idx[q]);
 #pragma unroll
-                for (int j = 0; j < 3; ++j) atomicAdd(&cell[cl.c[j]], inc);
+                for (int j = 0; j < 3; ++j) atomicAdd(part.meta(cl.c[j]), (u << 15) + 1u);
             }
         }
         if (a + gridDim.x < A) prefetch_idx(a + gridDim.x);
         peel_barrier(&s_bar, bar_expected);
-        if (mode != TAGC_DECODE_ESTIMATE) {
-            for (uint32_t c0 = 0; c0 < cells; c0 += kPeelThreads) {
-                const uint32_t c = c0 + tid;
-                queue_push(c < cells && (meta_hi[2 * c] & kDegMask) == 1u, c, &s_n[1], queue);
-            }
-        }
-
-        // ---- the rounds (see peel_kernel)
-        uint32_t rounds = 0, head = 0;
-        for (uint32_t r = 1;; ++r) {
-            peel_barrier(&s_bar, bar_expected);
-            const uint32_t cur = r % 3, nxt = (r + 1) % 3, idle = (r + 2) % 3;
-            if (s_any[idle]) ++rounds;
-            const uint32_t tail = head + s_n[cur];
-            if (tail == head) break;
-            if (tid == 0) {
-                s_n[idle] = 0;
-                s_any[nxt] = 0;
-            }
-            for (uint32_t e = head + tid; e < tail; e += kPeelThreads)
-                resolve_entry(queue[e], cell, claimed, idx, &s_any[cur], &s_n[nxt],
-                              queue + tail, m_sub, sw0, sw1, sw2);
-            head = tail;
-        }
-
-        // ---- output (see peel_kernel)
-        for (uint32_t u = tid; u < Pa; u += kPeelThreads) {
-            float x = 0.0f;
-            if ((claimed[u >> 5] >> (u & 31)) & 1u) {
-                x = __uint_as_float(idx[u]);
-            } else if (mode != TAGC_DECODE_PEEL) {
-                const Cells cl = cells_of(idx[u], m_sub, sw0, sw1, sw2);
-                float rd[3];
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    const float cv = __uint_as_float(uint32_t(cell[cl.c[j]]));
-                    rd[j] = ((cl.neg >> j) & 1u) ? -cv : cv;
-                }
-                x = fmaxf(fminf(rd[0], rd[1]), fminf(fmaxf(rd[0], rd[1]), rd[2]));
-            }
-            val_out[rho0 + u] = x;
-        }
-        uint32_t resolved = 0;
-        for (uint32_t c = tid; c < P_cap / 32 + 1; c += kPeelThreads) resolved += __popc(claimed[c]);
-        resolved = wave_sum(resolved);
-        if (lane_id() == 0 && resolved) atomicAdd(&s_resolved, resolved);
-        max_rounds = max(max_rounds, rounds);
-        Pa_prev = Pa;
+        if (mode != TAGC_DECODE_ESTIMATE)
+            queue_first<kPeelThreads, kPeelSlots>(part, tid, &s_n[1],
+                                                  [&] { peel_barrier(&s_bar, bar_expected); });
+        const uint32_t resolved = peel_rounds<kPeelThreads>(
+            part, tid, s_n, max_rounds, [&] { peel_barrier(&s_bar, bar_expected); });
+        for (uint32_t u = tid; u < Pa; u += kPeelThreads) val_out[rho0 + u] = unknown_value(part, u, mode);
+        if (tid == 0) report_unresolved(Pa - resolved, mode, status);
     }
-    // the last partition's count: every peeling wave has added its share before this barrier
-    peel_barrier(&s_bar, bar_expected);
-    if (tid == 0) {
-        if (blockIdx.x < A && s_resolved < Pa_prev) {
-            atomicAdd(&status[TAGC_ST_UNRESOLVED], Pa_prev - s_resolved);
-            if (mode != TAGC_DECODE_PEEL) atomicAdd(&status[TAGC_ST_ESTIMATED], Pa_prev - s_resolved);
-        }
-        if (max_rounds) atomicMax(&status[TAGC_ST_ROUNDS], max_rounds);
-    }
+    if (tid == 0 && max_rounds) atomicMax(&status[TAGC_ST_ROUNDS], max_rounds);
 }
 
 // Dense output: one workgroup per 1024-word chunk of the Index writes the 32768 floats
@@ -640,9 +690,18 @@ dense_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words,
 
 }  // namespace
 
+// Partitions of the default size at most: sub-tables of 4096 cells, whose slots fit 12 bits.
+static bool packed_slots(uint32_t T_cap, uint32_t P_cap)
+{
+    return T_cap <= kDefaultPartCells && P_cap <= kDefaultPartUnknowns;
+}
+
 size_t decode_lds_bytes(uint32_t T_cap, uint32_t P_cap)
 {
-    return size_t(T_cap) * 8 + (size_t(P_cap) + (P_cap / 32 + 1) + 32) * 4 + size_t(T_cap) * 2 + 16;
+    // PartLds; in the form that is not packed the queue is as long as there are cells, and 32
+    // words are spare
+    const size_t queue = packed_slots(T_cap, P_cap) ? 3 * size_t(P_cap) : 2 * size_t(T_cap) + 128;
+    return size_t(T_cap) * 8 + (size_t(P_cap) + (P_cap / 32 + 1)) * 4 + queue + 16;
 }
 
 int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
@@ -691,8 +750,8 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
         constexpr uint32_t kI0 = (kDefaultPartUnknowns + kDecodeThreads - 1) / kDecodeThreads;
         constexpr uint32_t kC1 = (kMaxPartCells + kDecodeThreads - 1) / kDecodeThreads;
         constexpr uint32_t kI1 = (kMaxPartUnknowns + kDecodeThreads - 1) / kDecodeThreads;
-        const bool small = p->T_cap <= kC0 * kDecodeThreads && p->P_cap <= kI0 * kDecodeThreads;
-        auto kernel = small ? peel_kernel<kC0, kI0> : peel_kernel<kC1, kI1>;
+        const bool small = packed_slots(p->T_cap, p->P_cap);
+        auto kernel = small ? peel_kernel<kC0, kI0, true> : peel_kernel<kC1, kI1, false>;
         static size_t attr_bytes[2] = {0, 0};
         if (lds > attr_bytes[small]) {
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
