@@ -83,140 +83,95 @@ index_merge_kernel(RankPtrs rp, uint32_t n_in, uint32_t *__restrict__ out, uint3
 
 struct LayoutParams {
     uint32_t mode, milli, P_cap, T_cap;
-    uint64_t n_real, U_cap, A_cap, m_cap;
+    uint64_t M_fixed;  // fixed ratio: target cells, ceil(n_real*1000/milli)
+    uint64_t U_cap, A_cap, m_cap;
+};
+struct Layout {
+    uint32_t U, A, m_sub, m, flags;
 };
 
-// Single workgroup: exclusive prefix of the chunk counts (in place, total appended), the
-// sketch layout, and a cleared status block.
+// The sketch layout of a merged Index with U set bits.
 //
 //   target cells  M = ceil(milli*U/1000)  |  ceil(n_real*1000/milli)
 //   partitions    A = max(1, ceil(U/P_cap), ceil(M/(3q))),  q = T_cap/3   (0 if U = 0)
 //   sub-table     m_sub = max(1, ceil(M/(3A)))  |  max(1, floor(M/(3A)))
 //   total         m = 3*A*m_sub
-__global__ void __launch_bounds__(1024)
-header_kernel(uint32_t *chunk, uint32_t n_chunks, LayoutParams lp, uint32_t *header,
-              uint32_t *status)
+//
+// (U <= U_cap makes everything fit 32 bits: the plan refuses a capacity that does not.)
+__device__ inline Layout layout_of(uint32_t U, const LayoutParams &lp)
 {
-    __shared__ uint32_t smem[16];
-    uint32_t running = 0;
-    for (uint32_t base = 0; base < n_chunks; base += 1024) {
-        const uint32_t i = base + threadIdx.x;
-        uint32_t v = i < n_chunks ? chunk[i] : 0u, tot;
-        uint32_t ex = block_excl_scan<uint32_t, 16>(v, &tot, smem);
-        if (i < n_chunks) chunk[i] = running + ex;
-        running += tot;
+    Layout l{};
+    if (U == 0) return l;
+    if (U > lp.U_cap) {  // caller broke the plan's bounds
+        l.flags = TAGC_FLAG_OVERFLOW;
+        return l;
     }
-    if (threadIdx.x != 0) return;
-    chunk[n_chunks] = running;
-    uint64_t U = running, A = 0, m_sub = 0, m = 0;
-    uint32_t flags = 0;
-    if (U > 0) {
-        uint64_t M = lp.mode == TAGC_SIZE_LOAD_FACTOR ? (uint64_t(lp.milli) * U + 999) / 1000
-                                                      : (lp.n_real * 1000 + lp.milli - 1) / lp.milli;
-        uint64_t q = lp.T_cap / 3;
-        A = (U + lp.P_cap - 1) / lp.P_cap;
-        uint64_t A2 = (M + 3 * q - 1) / (3 * q);
-        if (A2 > A) A = A2;
-        if (A < 1) A = 1;
-        m_sub = lp.mode == TAGC_SIZE_LOAD_FACTOR ? (M + 3 * A - 1) / (3 * A) : M / (3 * A);
-        if (m_sub < 1) m_sub = 1;
-        m = 3 * A * m_sub;
-        if (U > lp.U_cap || A > lp.A_cap || m > lp.m_cap) {  // caller broke the plan's bounds
-            flags = TAGC_FLAG_OVERFLOW;
-            U = A = m_sub = m = 0;
-        }
+    const bool load = lp.mode == TAGC_SIZE_LOAD_FACTOR;
+    const uint32_t M = uint32_t(load ? (uint64_t(lp.milli) * U + 999) / 1000 : lp.M_fixed);
+    const uint32_t q = lp.T_cap / 3;
+    uint32_t A = max((U - 1) / lp.P_cap + 1, M ? (M - 1) / (3 * q) + 1 : 1u);
+    uint32_t m_sub = load ? (M ? (M - 1) / (3 * A) + 1 : 0u) : M / (3 * A);
+    m_sub = max(m_sub, 1u);
+    const uint64_t m = 3ull * A * m_sub;
+    if (A > lp.A_cap || m > lp.m_cap) {
+        l.flags = TAGC_FLAG_OVERFLOW;
+        return l;
     }
-    header[TAGC_HDR_U] = uint32_t(U);
-    header[TAGC_HDR_A] = uint32_t(A);
-    header[TAGC_HDR_MSUB] = uint32_t(m_sub);
-    header[TAGC_HDR_M] = uint32_t(m);
-    for (int i = 4; i < TAGC_HDR_WORDS; ++i) header[i] = 0;
-    for (int i = 0; i < TAGC_ST_WORDS; ++i) status[i] = 0;
-    status[TAGC_ST_FLAGS] = flags;
+    l.U = U;
+    l.A = A;
+    l.m_sub = m_sub;
+    l.m = uint32_t(m);
+    return l;
 }
 
-// One wave per partition boundary a: bounds[a] = c-index of the non-zero of rank
-// floor(a*U/A); bounds[A] = n_c.
-__global__ void __launch_bounds__(256)
-bounds_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words, uint32_t n_c,
-              const uint32_t *__restrict__ chunkpre, uint32_t n_chunks,
-              const uint32_t *__restrict__ header, uint32_t *__restrict__ bounds)
-{
-    const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
-    const uint32_t a = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const uint32_t l = lane_id();
-    if (a > A) return;
-    if (a == A) {
-        if (l == 0) bounds[a] = n_c;
-        return;
-    }
-    const uint32_t rho = uint32_t(uint64_t(a) * U / A);
-    uint32_t lo = 0, hi = n_chunks;  // largest chunk with chunkpre <= rho
-    while (hi - lo > 1) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (chunkpre[mid] <= rho) lo = mid; else hi = mid;
-    }
-    const uint32_t local = rho - chunkpre[lo];
-    const uint32_t wbase = lo * kChunkWords + l * 16;
-    uint32_t w[16];
-    if (wbase + 16 <= n_words) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            uint4 v = *reinterpret_cast<const uint4 *>(bitmap + wbase + 4 * i);
-            w[4 * i] = v.x; w[4 * i + 1] = v.y; w[4 * i + 2] = v.z; w[4 * i + 3] = v.w;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) w[i] = (wbase + i < n_words) ? bitmap[wbase + i] : 0u;
-    }
-    uint32_t tot = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) tot += __popc(w[i]);
-    const uint32_t incl = wave_incl_scan<uint32_t>(tot);
-    const uint32_t excl = incl - tot;
-    if (excl <= local && local < incl) {
-        uint32_t r = local - excl;
-        uint32_t found = n_c;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const uint32_t c = __popc(w[i]);
-            if (found == n_c) {
-                if (r < c) {
-                    uint32_t x = w[i];
-                    for (uint32_t s = 0; s < r; ++s) x &= x - 1;
-                    found = (wbase + i) * 32 + __builtin_ctz(x);
-                } else {
-                    r -= c;
-                }
-            }
-        }
-        bounds[a] = found;
-    }
-}
+// What a launch needs to know of a rank to find the partitions in its pair list.
+struct LayoutRank {
+    const uint32_t *idx;
+    uint32_t *cnt;
+};
+struct LayoutBatch {
+    LayoutRank r[kMaxRanksPerPass];
+};
 
-// ranges[a] of rank r = number of the rank's pairs whose c-index lies below bounds[a]: the
-// pairs of partition a are [ranges[a], ranges[a+1]) of its sorted list.  One thread per
-// (rank, boundary); a binary search costs ~20 dependent loads, but all of them run at once
-// and the encoder's workgroups, which used to search as they started, no longer wait.
-__global__ void __launch_bounds__(256)
-ranges_kernel(RankPtrs idx, RankPtrs cnt, uint32_t n_in, const uint32_t *__restrict__ header,
-              const uint32_t *__restrict__ bounds, uint32_t A_cap, uint32_t ranges_off,
-              uint32_t pair_cap)
+// For kN sorted lists at once, by every 16 lanes of a wave for theirs: the first position whose
+// entry is >= key[i].  Each step cuts the range into 16 parts: 5 or 6 dependent loads for a list
+// of millions where a thread's binary search takes over 20 (cut into 64 parts by a whole wave it
+// is 4, of 64 cache lines each: 58 thousand searches of 2 M entries were bound by those).
+template <uint32_t kN>
+__device__ inline void lower_bounds_by_16(const uint32_t *const (&list)[kN], const uint32_t (&n)[kN],
+                                          const uint32_t (&key)[kN], uint32_t (&pos)[kN])
 {
-    const uint32_t A = header[TAGC_HDR_A];
-    const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-    const uint32_t r = t / (A_cap + 1), a = t % (A_cap + 1);
-    if (r >= n_in || a > A) return;
-    uint32_t *c = static_cast<uint32_t *>(const_cast<void *>(cnt.p[r]));
-    const uint32_t *ix = static_cast<const uint32_t *>(idx.p[r]);
-    const uint32_t n = min(c[TAGC_CNT_TOTAL], pair_cap);
-    const uint32_t key = bounds[a];
-    uint32_t lo = 0, hi = n;  // first position whose c-index is >= key
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (ix[mid] < key) lo = mid + 1; else hi = mid;
+    const uint32_t part = lane_id() & 15, shift = lane_id() & 48;
+    uint32_t lo[kN], hi[kN];
+    bool more = false;
+#pragma unroll
+    for (uint32_t i = 0; i < kN; ++i) {
+        lo[i] = 0;
+        hi[i] = n[i];
+        more |= n[i] != 0;
     }
-    c[ranges_off + a] = lo;
+    while (__ballot(more)) {
+        uint32_t step[kN], v[kN];
+#pragma unroll
+        for (uint32_t i = 0; i < kN; ++i) {  // the last entry of the lane's part
+            step[i] = (hi[i] - lo[i] + 15) / 16;
+            const uint64_t first = lo[i] + uint64_t(part) * step[i];
+            v[i] = first < hi[i] ? list[i][min(first + step[i], uint64_t(hi[i])) - 1] : 0xFFFFFFFFu;
+        }
+        more = false;
+#pragma unroll
+        for (uint32_t i = 0; i < kN; ++i) {
+            // parts wholly below the key; then the part after them, whose last entry is not
+            const uint32_t below = uint32_t(__popc(uint32_t(__ballot(v[i] < key[i]) >> shift) & 0xFFFFu));
+            const uint64_t at = min(lo[i] + uint64_t(below) * step[i], uint64_t(hi[i]));
+            const uint64_t end = min(at + step[i], uint64_t(hi[i]));
+            lo[i] = uint32_t(at);
+            hi[i] = uint32_t(end > at ? end - 1 : at);
+            more |= lo[i] < hi[i];
+        }
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kN; ++i) pos[i] = lo[i];
 }
 
 // Per-partition hash salts (the compression is to be lossless, section 2.2 and Table 1).
@@ -235,23 +190,144 @@ ranges_kernel(RankPtrs idx, RankPtrs cnt, uint32_t n_in, const uint32_t *__restr
 // two slots.  LDS per non-zero: a 32-bit tag (slot_1, slot_2) and a 16-bit link; per cell of
 // a sub-table a 32-bit list head -- little enough for two partitions per compute unit, whose
 // phases (hashing on the vector units, list building and walking in LDS) then overlap.
+//
+// The same kernel derives everything else the later stages need from the merged Index, each
+// step a few dependent loads that would be a launch of their own: every workgroup adds up the
+// chunk counts by itself (a few words per thread) and knows the layout; its partitions' bounds
+// are found by a wave each (bounds[a] = c-index of the non-zero of rank floor(a*U/A);
+// bounds[A] = n_c); and so are their ends in the ranks' sorted pair lists (ranges[a] of a
+// rank = number of its pairs whose c-index lies below bounds[a]).  Four launches (header, bounds,
+// salt, ranges) were 31 us on an 8-rank bucket of 25 M entries and 48 on one of 67 M, this one is
+// 21 and 40; with 16 ranks of 202 M, where the salts are most of it, 138 and 149.
 constexpr uint32_t kSaltThreads = 1024;
+constexpr uint32_t kLayoutBatch = kSaltThreads / 128;  // partitions whose bounds are found at once
 constexpr uint32_t kSaltLimit = 16;       // salts tried: 0 .. 15
 constexpr uint32_t kNoLink = 0xFFFFu;
 constexpr uint32_t kSaltPre = 4;          // Index words per thread requested a partition ahead
 
-__global__ void __launch_bounds__(kSaltThreads)
-salt_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words,
-            const uint32_t *__restrict__ header, const uint32_t *__restrict__ bounds,
-            uint32_t *__restrict__ salt_out, uint64_t seed, uint32_t P_cap, uint32_t q_cap)
+// (8 waves per SIMD asked for: two workgroups a compute unit; 106 scalar registers leave room for one)
+__global__ void __launch_bounds__(kSaltThreads) __attribute__((amdgpu_waves_per_eu(8)))
+layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__restrict__ bitmap,
+              uint32_t n_words, uint32_t n_c, const uint32_t *__restrict__ chunkcnt,
+              uint32_t *__restrict__ chunkpre, uint32_t n_chunks, const LayoutParams lp,
+              uint32_t *__restrict__ header, uint32_t *__restrict__ status,
+              uint32_t *__restrict__ bounds, uint32_t ranges_off, uint32_t pair_cap, uint64_t seed)
 {
+    constexpr uint32_t NT = kSaltThreads;
     extern __shared__ uint32_t lds_salt[];
+    const uint32_t P_cap = lp.P_cap, q_cap = lp.T_cap / 3;
     uint32_t *tag = lds_salt;                        // [P_cap] c-index, then slot_1 | slot_2 << 16
     uint32_t *head = tag + P_cap;                                   // [q_cap]
     uint16_t *link = reinterpret_cast<uint16_t *>(head + q_cap);    // [P_cap]
     __shared__ uint32_t s_n, s_dup;
-    const uint32_t A = header[TAGC_HDR_A], m_sub = min(header[TAGC_HDR_MSUB], q_cap);
+    __shared__ uint32_t s_pre[NT];                // set bits before thread t's chunks
+    __shared__ uint32_t s_bound[2 * kLayoutBatch];  // first and last bound of the batch's partitions
+    __shared__ uint32_t smem[NT / 64];
     const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // ---- set bits before every thread's chunks, the layout
+    const uint32_t per = (n_chunks + NT - 1) / NT;
+    const uint32_t first = tid * per, last = min(first + per, n_chunks);
+    uint32_t own = 0, total;
+    for (uint32_t i = first; i < last; ++i) own += chunkcnt[i];
+    const uint32_t before = block_excl_scan<uint32_t, NT / 64>(own, &total, smem);
+    s_pre[tid] = before;
+    // (what every lane holds alike comes from LDS here: said to be uniform, it stays in scalar
+    // registers, and the loops below are scalar)
+    auto uniform = [](uint32_t x) -> uint32_t { return __builtin_amdgcn_readfirstlane(x); };
+    total = uniform(total);
+    const Layout lay = layout_of(total, lp);
+    const uint32_t U = lay.U, A = lay.A, m_sub = min(lay.m_sub, q_cap);
+    if (all && blockIdx.x == 0) {
+        uint32_t run = before;
+        for (uint32_t i = first; i < last; ++i) {
+            chunkpre[i] = run;
+            run += chunkcnt[i];
+        }
+        if (tid == 0) {
+            chunkpre[n_chunks] = total;
+            header[TAGC_HDR_U] = lay.U;
+            header[TAGC_HDR_A] = lay.A;
+            header[TAGC_HDR_MSUB] = lay.m_sub;
+            header[TAGC_HDR_M] = lay.m;
+            for (int i = 4; i < TAGC_HDR_WORDS; ++i) header[i] = 0;
+            for (int i = 0; i < TAGC_ST_WORDS; ++i) status[i] = 0;
+            status[TAGC_ST_FLAGS] = lay.flags;
+        }
+    }
+    __syncthreads();  // s_pre
+
+    // c-index of the set bit of rank rho < U (by a wave, all lanes get it)
+    auto bound_of = [&](uint32_t rho) -> uint32_t {
+        // the last thread whose chunks start at or before it
+        uint32_t t = uint32_t(__popcll(__ballot(s_pre[lane * (NT / 64)] <= rho))) - 1u;
+        const uint32_t v = lane < NT / 64 ? s_pre[t * (NT / 64) + lane] : 0xFFFFFFFFu;
+        t = t * (NT / 64) + uint32_t(__popcll(__ballot(v <= rho))) - 1u;
+        // its chunk
+        uint32_t run = uniform(s_pre[t]), chunk = t * per, local = 0;
+        for (uint32_t j = 0; j < per; j += 64) {
+            const uint32_t c = t * per + j + lane;
+            const uint32_t n = j + lane < per && c < n_chunks ? chunkcnt[c] : 0u;
+            const uint32_t inc = wave_incl_scan<uint32_t>(n);
+            const uint32_t tot = __builtin_amdgcn_readlane(inc, 63);
+            if (rho - run < tot) {
+                const uint32_t k = uint32_t(__popcll(__ballot(run + inc <= rho)));
+                chunk = t * per + j + k;
+                local = rho - run - (k ? __builtin_amdgcn_readlane(inc, k - 1) : 0u);
+                break;
+            }
+            run += tot;
+        }
+        // its bit, the wave looking at 16 words per lane
+        const uint32_t wbase = chunk * kChunkWords + lane * 16;
+        uint32_t w[16], tot = 0;
+        if (wbase + 16 <= n_words) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint4 x = *reinterpret_cast<const uint4 *>(bitmap + wbase + 4 * i);
+                w[4 * i] = x.x; w[4 * i + 1] = x.y; w[4 * i + 2] = x.z; w[4 * i + 3] = x.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) w[i] = (wbase + i < n_words) ? bitmap[wbase + i] : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) tot += __popc(w[i]);
+        const uint32_t incl = wave_incl_scan<uint32_t>(tot);
+        const uint32_t excl = incl - tot;
+        uint32_t found = n_c;
+        const bool mine = excl <= local && local < incl;
+        if (mine) {
+            uint32_t r = local - excl;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const uint32_t c = __popc(w[i]);
+                if (found == n_c) {
+                    if (r < c) {
+                        uint32_t x = w[i];
+                        for (uint32_t s = 0; s < r; ++s) x &= x - 1;
+                        found = (wbase + i) * 32 + __builtin_ctz(x);
+                    } else {
+                        r -= c;
+                    }
+                }
+            }
+        }
+        const uint64_t who = __ballot(mine);
+        return who ? __builtin_amdgcn_readlane(found, __builtin_ctzll(who)) : n_c;
+    };
+    // rank r's words from ranges_off on: positions in its pair list
+    auto rank_row = [&](uint32_t r) { return batch_row<LayoutRank>(r); };
+    auto pairs_of = [&](uint32_t *cnt) { return min(cnt[TAGC_CNT_TOTAL], pair_cap); };
+
+    if (blockIdx.x == 0) {  // the end of the last partition (of none: the only bound)
+        if (tid == 0) bounds[A] = n_c;
+        if (tid < n_in) {
+            uint32_t *cnt = as_global(rank_row(tid)->cnt);
+            cnt[ranges_off + A] = pairs_of(cnt);
+        }
+    }
     // word `w` of partition [lo, hi), bits outside the partition cleared
     auto load_word = [&](uint32_t w, uint32_t lo, uint32_t hi) -> uint32_t {
         if (lo >= hi || w > ((hi - 1) >> 5) || w >= n_words) return 0u;
@@ -260,37 +336,63 @@ salt_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words,
         if (w == ((hi - 1) >> 5) && (hi & 31)) word &= (1u << (hi & 31)) - 1u;
         return word;
     };
-    // Requests run ahead of the work: the bounds of the partition after the next, and the
-    // first Index words of the next one, are on their way while this one is checked.
-    uint32_t pre[kSaltPre], lo = 0, hi = 0, lo2 = 0, hi2 = 0;
+    // The workgroup's partitions are blockIdx.x, + G, + 2 G, ...
     const uint32_t G = gridDim.x;
-    if (blockIdx.x < A) {
-        lo = bounds[blockIdx.x];
-        hi = bounds[blockIdx.x + 1];
+    const uint32_t n_mine = blockIdx.x < A ? (A - 1 - blockIdx.x) / G + 1 : 0u;
+    for (uint32_t b0 = 0; b0 < n_mine; b0 += kLayoutBatch) {
+    const uint32_t nb = min(kLayoutBatch, n_mine - b0);
+    __syncthreads();  // s_bound is free
+    if ((wave >> 1) < nb) {
+        const uint32_t a = blockIdx.x + (b0 + (wave >> 1)) * G + (wave & 1);
+        const uint32_t x = a == A ? n_c : bound_of(uint32_t(uint64_t(a) * U / A));
+        if (lane == 0) {
+            s_bound[wave] = x;
+            if (!(wave & 1)) bounds[a] = x;
+        }
+    }
+    __syncthreads();
+    // Requests run ahead of the work: the first Index words of the first partition are on their
+    // way while the pair lists are searched, those of the next while one is checked.
+    uint32_t lo = uniform(s_bound[0]), hi = uniform(s_bound[1]), pre[kSaltPre];
 #pragma unroll
-        for (uint32_t k = 0; k < kSaltPre; ++k)
-            pre[k] = load_word((lo >> 5) + k * kSaltThreads + tid, lo, hi);
+    for (uint32_t k = 0; k < kSaltPre; ++k)
+        pre[k] = all ? load_word((lo >> 5) + k * NT + tid, lo, hi) : 0u;
+    constexpr uint32_t kLists = 2;
+    for (uint32_t t0 = 0; t0 < nb * n_in; t0 += kLists * (NT / 16)) {
+        const uint32_t *list[kLists];
+        uint32_t *cnt[kLists];
+        uint32_t n[kLists], key[kLists], pos[kLists];
+#pragma unroll
+        for (uint32_t i = 0; i < kLists; ++i) {
+            const uint32_t t = t0 + i * (NT / 16) + tid / 16;
+            const bool ok = t < nb * n_in;
+            const auto *row = rank_row(ok ? t % n_in : 0u);
+            list[i] = as_global(row->idx);
+            cnt[i] = as_global(row->cnt);
+            n[i] = ok ? pairs_of(cnt[i]) : 0u;
+            key[i] = s_bound[ok ? 2 * (t / n_in) : 0u];
+        }
+        lower_bounds_by_16<kLists>(list, n, key, pos);
+#pragma unroll
+        for (uint32_t i = 0; i < kLists; ++i) {
+            const uint32_t t = t0 + i * (NT / 16) + tid / 16;
+            if ((tid & 15) == 0 && t < nb * n_in)
+                cnt[i][ranges_off + blockIdx.x + (b0 + t / n_in) * G] = pos[i];
+        }
     }
-    if (blockIdx.x + G < A) {
-        lo2 = bounds[blockIdx.x + G];
-        hi2 = bounds[blockIdx.x + G + 1];
-    }
-    for (uint32_t a = blockIdx.x; a < A; a += G) {
+    if (!all) continue;
+    for (uint32_t i = 0; i < nb; ++i) {
         const uint32_t w_lo = lo >> 5, w_hi = lo < hi ? (hi - 1) >> 5 : 0;
         const uint32_t cur_lo = lo, cur_hi = hi;
         uint32_t cur[kSaltPre];
 #pragma unroll
         for (uint32_t k = 0; k < kSaltPre; ++k) cur[k] = pre[k];
-        lo = lo2;
-        hi = hi2;
-        if (a + G < A) {
+        if (i + 1 < nb) {
+            lo = uniform(s_bound[2 * i + 2]);
+            hi = uniform(s_bound[2 * i + 3]);
 #pragma unroll
             for (uint32_t k = 0; k < kSaltPre; ++k)
-                pre[k] = load_word((lo >> 5) + k * kSaltThreads + tid, lo, hi);
-        }
-        if (a + 2 * G < A) {
-            lo2 = bounds[a + 2 * G];
-            hi2 = bounds[a + 2 * G + 1];
+                pre[k] = load_word((lo >> 5) + k * NT + tid, lo, hi);
         }
         uint32_t salt = 0;
         if (cur_lo < cur_hi) {
@@ -341,7 +443,9 @@ salt_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words,
             }
             salt = min(salt, kSaltLimit - 1);
         }
-        if (tid == 0) salt_out[a] = salt;
+        // (the salts lie behind the bounds)
+        if (tid == 0) bounds[lp.A_cap + 1 + blockIdx.x + (b0 + i) * G] = salt;
+    }
     }
 }
 
@@ -357,7 +461,10 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
 {
     const uint32_t n_words = uint32_t(p->n_c / 32);
     const uint32_t n_chunks = uint32_t(p->n_chunks);
-    uint32_t *chunk = static_cast<uint32_t *>(sh->workspace);
+    // set bits of every chunk; their prefix sums, what the decoder reads (at the start, where it
+    // looks for them); behind both, the 4-bit running sum (the plan sized all of it)
+    uint32_t *chunkpre = static_cast<uint32_t *>(sh->workspace);
+    uint32_t *chunk = chunkpre + n_chunks + 1;
     if (n_chunks) {
         ProfileScope ps("index_or", s);
         for (uint32_t r0 = 0; r0 < n_ranks; r0 += kMaxRanksPerPass) {
@@ -365,8 +472,7 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
             const uint32_t n_in = std::min(kMaxRanksPerPass, n_ranks - r0);
             for (uint32_t r = 0; r < n_in; ++r) rp.p[r] = ranks[r0 + r].bitmap;
             const bool last = r0 + n_in == n_ranks;
-            // the 4-bit running sum lives behind the chunk prefixes (the plan sized it)
-            uint32_t *sum4 = chunk + ((size_t(n_chunks) + 1 + 3) & ~size_t(3));
+            uint32_t *sum4 = chunkpre + index_words(n_chunks);
             auto kernel = p->cfg.index_mode == TAGC_INDEX_ADD4
                               ? index_merge_kernel<TAGC_INDEX_ADD4>
                               : (p->cfg.index_mode == TAGC_INDEX_ADD1
@@ -376,50 +482,37 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
                                             last ? chunk : nullptr);
         }
     }
-    {
-        ProfileScope ps("header", s);
-        LayoutParams lp{p->cfg.sizing, p->cfg.sizing_milli, p->P_cap, p->T_cap,
-                        p->n_real,     p->U_cap,            p->A_cap, p->m_cap};
-        header_kernel<<<1, 1024, 0, s>>>(chunk, n_chunks, lp, sh->header, sh->status);
+    const LayoutParams lp{p->cfg.sizing,
+                          p->cfg.sizing_milli,
+                          p->P_cap,
+                          p->T_cap,
+                          (p->n_real * 1000 + p->cfg.sizing_milli - 1) / p->cfg.sizing_milli,
+                          p->U_cap,
+                          p->A_cap,
+                          p->m_cap};
+    const size_t lds = salt_lds_bytes(p->T_cap, p->P_cap);
+    static size_t attr_bytes = 0;
+    if (lds > attr_bytes) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(layout_kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                int(lds)) != hipSuccess)
+            return TAGC_EHIP;
+        attr_bytes = lds;
     }
-    if (n_chunks) {
-        ProfileScope ps("bounds", s);
-        const uint32_t grid = uint32_t((p->A_cap + 1 + 3) / 4);
-        bounds_kernel<<<grid, 256, 0, s>>>(sh->bitmap, n_words, uint32_t(p->n_c), chunk, n_chunks,
-                                           sh->header, sh->bounds);
-    }
-    if (n_chunks) {
-        ProfileScope ps("salt", s);
-        const size_t lds = salt_lds_bytes(p->T_cap, p->P_cap);
-        static size_t attr_bytes = 0;
-        if (lds > attr_bytes) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(salt_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    int(lds)) != hipSuccess)
-                return TAGC_EHIP;
-            attr_bytes = lds;
-        }
-        // as many workgroups as fit the device at once, each taking partitions b, b + grid, ...
-        const uint32_t per_cu = uint32_t(std::max<size_t>(1, std::min<size_t>(2, kLdsBytes / (lds + 1024))));
-        const uint32_t grid = uint32_t(std::min<uint64_t>(p->A_cap, uint64_t(device_cu_count()) * per_cu));
-        salt_kernel<<<grid, kSaltThreads, lds, s>>>(sh->bitmap, n_words, sh->header, sh->bounds,
-                                                    sh->bounds + p->A_cap + 1, p->cfg.seed,
-                                                    p->P_cap, p->T_cap / 3);
-    }
-    if (n_chunks) {
-        ProfileScope ps("ranges", s);
-        for (uint32_t r0 = 0; r0 < n_ranks; r0 += kMaxRanksPerPass) {
-            RankPtrs ri{}, rc{};
-            const uint32_t n_in = std::min(kMaxRanksPerPass, n_ranks - r0);
-            for (uint32_t r = 0; r < n_in; ++r) {
-                ri.p[r] = ranks[r0 + r].idx;
-                rc.p[r] = ranks[r0 + r].cnt;
-            }
-            const uint64_t threads = uint64_t(n_in) * (p->A_cap + 1);
-            ranges_kernel<<<uint32_t((threads + 255) / 256), 256, 0, s>>>(
-                ri, rc, n_in, sh->header, sh->bounds, uint32_t(p->A_cap), p->cnt_ranges,
-                uint32_t(p->K));
-        }
+    // as many workgroups as fit the device at once, each taking partitions b, b + grid, ...
+    const size_t lds_all = lds + 6 * 1024;  // with the kernel's own
+    const uint32_t per_cu = uint32_t(std::max<size_t>(1, std::min<size_t>(2, kLdsBytes / lds_all)));
+    const uint32_t grid = uint32_t(std::min<uint64_t>(p->A_cap, uint64_t(device_cu_count()) * per_cu));
+    for (uint32_t r0 = 0; r0 < n_ranks; r0 += kMaxRanksPerPass) {
+        // (ranks beyond the first launch's only need their pair lists searched)
+        ProfileScope ps("layout", s);
+        LayoutBatch lb{};
+        const uint32_t n_in = std::min(kMaxRanksPerPass, n_ranks - r0);
+        for (uint32_t r = 0; r < n_in; ++r)
+            lb.r[r] = LayoutRank{ranks[r0 + r].idx, ranks[r0 + r].cnt};
+        layout_kernel<<<grid, kSaltThreads, lds, s>>>(
+            lb, n_in, r0 == 0, sh->bitmap, n_words, uint32_t(p->n_c), chunk, chunkpre, n_chunks, lp,
+            sh->header, sh->status, sh->bounds, p->cnt_ranges, uint32_t(p->K), p->cfg.seed);
     }
     return hip_ok(hipGetLastError());
 }

@@ -156,6 +156,10 @@ struct tagc_plan_s {
 
 namespace tagc {
 
+// words of the shared workspace before the 4-bit running sum: chunk prefixes (one more than
+// chunks), chunk counts
+inline uint64_t index_words(uint64_t n_chunks) { return (2 * n_chunks + 1 + 3) & ~uint64_t(3); }
+
 // ------------------------------------------------------------------- hash
 
 __host__ __device__ inline uint32_t mix32(uint32_t x)
