@@ -29,7 +29,7 @@ STAGES = {
     "S3a index OR": ["index_or", "layout"],
     "S2' encode": ["encode"],
     "S3b sketch sum": ["sketch_sum"],
-    "S4 decode": ["enumerate", "peel", "dense"],
+    "S4 decode": ["peel", "dense"],
 }
 FUSED_STAGE = "S3b+S4 sketch sum inside decode"
 
@@ -39,7 +39,7 @@ def stages_of(fused):
     if not fused:
         return STAGES
     st = {k: v for k, v in STAGES.items() if k not in ("S3b sketch sum", "S4 decode")}
-    st[FUSED_STAGE] = ["enumerate", "sum_peel", "dense"]
+    st[FUSED_STAGE] = ["sum_peel", "dense"]
     return st
 
 
@@ -229,7 +229,6 @@ def kernel_alg_bytes(b, z, hdr, k_total, dense, ef=False, wire=1, cell=4):
         "widen4": (1 + 4) * N * n_c // 8,
         "encode": 8 * k_total + N * cell * m,
         "sketch_sum": (N * cell + 4) * m,
-        "enumerate": n_c // 8 + 4 * U,
         "peel": 4 * m + 8 * U,
         "sum_peel": N * cell * m + 8 * U,
         "dense": n_c // 8 + 4 * U + 4 * n_c,

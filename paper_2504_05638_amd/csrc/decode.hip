@@ -61,53 +61,6 @@ __device__ inline Cells cells_of(uint32_t i, uint32_t m_sub, uint32_t sw0, uint3
     return r;
 }
 
-// Enumerates the set bits of the merged Index in ascending order into idx_out.  One
-// workgroup per 1024-word chunk; chunkpre[] (written by the Index aggregation) holds the
-// number of set bits before each chunk, so workgroups are independent.  A thread's
-// indices are consecutive in the output but a wave's stores, taken entry by entry, would
-// hit 64 different cache lines each; so the chunk's first kEnumStage indices are gathered
-// in LDS and leave as contiguous stores.
-constexpr uint32_t kEnumStage = 8192;
-
-__global__ void __launch_bounds__(256)
-enumerate_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words,
-                 const uint32_t *__restrict__ chunkpre, const uint32_t *__restrict__ header,
-                 uint32_t *__restrict__ idx_out)
-{
-    __shared__ uint32_t scratch[8];
-    __shared__ uint32_t stage[kEnumStage];
-    const uint32_t U = header[TAGC_HDR_U];
-    const uint32_t w0 = blockIdx.x * kChunkWords + threadIdx.x * 4;
-    uint32_t w[4] = {0, 0, 0, 0};
-    if (w0 + 4 <= n_words) {
-        const uint4 q = *reinterpret_cast<const uint4 *>(bitmap + w0);
-        w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
-    } else {
-#pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) w[i] = w0 + i < n_words ? bitmap[w0 + i] : 0u;
-    }
-    const uint32_t mine = __popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]);
-    uint32_t tot;
-    const uint32_t base = chunkpre[blockIdx.x];
-    uint32_t pl = block_excl_scan<uint32_t, 4>(mine, &tot, scratch);  // position in the chunk
-#pragma unroll
-    for (uint32_t i = 0; i < 4; ++i) {
-        uint32_t word = w[i];
-        while (word) {
-            const uint32_t b = __builtin_ctz(word);
-            word &= word - 1;
-            const uint32_t v = (w0 + i) * 32 + b;
-            if (pl < kEnumStage) stage[pl] = v;
-            else if (base + pl < U) idx_out[base + pl] = v;
-            ++pl;
-        }
-    }
-    __syncthreads();
-    const uint32_t n = min(tot, kEnumStage);
-    for (uint32_t i = threadIdx.x; i < n; i += 256)
-        if (base + i < U) idx_out[base + i] = stage[i];
-}
-
 // A partition in LDS.  A cell is 64 bits: value bits in the low half, meta word in the high one.
 //
 // kPacked: an unknown keeps where its cells are and their signs, in 40 bits (sub-tables of 4096
@@ -365,18 +318,138 @@ __device__ inline void report_unresolved(uint32_t n, uint32_t mode, uint32_t *st
     if (mode != TAGC_DECODE_PEEL) atomicAdd(&status[TAGC_ST_ESTIMATED], n);
 }
 
-// Peels sketch partitions: unknowns rho0 .. rho0+Pa-1 of idx_out, cells a*3*m_sub ...
+// The merged Index, as the Index aggregation left it.
+struct IndexView {
+    const uint32_t *bitmap;
+    const uint32_t *chunkpre;   // set bits before every chunk
+    const uint16_t *grouppre;   // ... and from there before every group of 64 words
+    const uint32_t *bounds;     // first c-index of every partition
+    uint32_t n_words;
+};
+
+// The unknowns of a partition are the set bits of the merged Index from bounds[a] on, numbered as
+// they come.  A wave turns the Index into unknowns by groups of 64 words, one per lane; since the
+// set bits before every group are known, groups are independent of each other.  The kPre groups
+// that a wave has of nearly every partition are requested a partition ahead.  (As a kernel of its
+// own, whose output the decoder read back, this took 5 us on small buckets and 43 to 53 on those of
+// 7 to 38 M unknowns.)
+template <uint32_t NW, uint32_t kPre>
+struct PartIndex {
+    uint32_t lo, hi;        // the partition's c-indices
+    uint32_t word[kPre];    // word `lane` of the wave's groups
+    uint32_t before;        // lane i: set bits of the whole Index before the i-th of them
+
+    static_assert(kPre <= 64, "a lane per group");
+    __device__ __forceinline__ uint32_t load(const IndexView &v, uint32_t g) const
+    {
+        const uint32_t w = g * kGroupWords + lane_id();
+        return g <= (hi - 1) / (32 * kGroupWords) && w < v.n_words ? v.bitmap[w] : 0u;
+    }
+    __device__ __forceinline__ static uint32_t bits_before(const IndexView &v, uint32_t g)
+    {
+        return v.chunkpre[g / 16] + v.grouppre[g];
+    }
+    __device__ __forceinline__ void request(const IndexView &v, uint32_t a, uint32_t wave)
+    {
+        lo = v.bounds[a];
+        hi = v.bounds[a + 1];
+        const uint32_t g0 = lo / (32 * kGroupWords) + wave;
+#pragma unroll
+        for (uint32_t i = 0; i < kPre; ++i) word[i] = load(v, g0 + i * NW);
+        const uint32_t gl = g0 + lane_id() * NW;
+        before = lane_id() < kPre && gl * kGroupWords < v.n_words ? bits_before(v, gl) : 0u;
+    }
+    // word `lane` of group g, with `pre` set bits before the group: its unknowns' c-indices
+    __device__ __forceinline__ void expand(uint32_t *out, uint32_t n, uint32_t rho0, uint32_t g,
+                                           uint32_t w, uint32_t pre) const
+    {
+        const uint32_t inc = wave_incl_scan<uint32_t>(uint32_t(__popc(w)));
+        uint32_t u = pre - rho0 + inc - uint32_t(__popc(w));
+        const uint32_t c0 = (g * kGroupWords + lane_id()) * 32;
+        if (c0 < lo) {  // bits of the partition before
+            const uint32_t low = lo - c0 >= 32 ? w : w & ((1u << (lo - c0)) - 1u);
+            u += __popc(low);
+            w ^= low;
+        }
+        if (hi - c0 < 32) w &= (1u << (hi - c0)) - 1u;  // (c0 >= hi: below)
+        // (nothing lands outside out[0 .. n) whatever the Index holds)
+        if (c0 >= hi || u > n || uint32_t(__popc(w)) > n - u) w = 0;
+        for (out += u; w; w &= w - 1) *out++ = c0 + uint32_t(__builtin_ctz(w));
+    }
+    // the partition's n unknowns, of which rho0 lie in partitions before, into out[]
+    __device__ __forceinline__ void enumerate(const IndexView &v, uint32_t *out, uint32_t n,
+                                              uint32_t rho0, uint32_t wave) const
+    {
+        const uint32_t g0 = lo / (32 * kGroupWords) + wave, g1 = (hi - 1) / (32 * kGroupWords);
+#pragma unroll
+        for (uint32_t i = 0; i < kPre; ++i)
+            if (g0 + i * NW <= g1)
+                expand(out, n, rho0, g0 + i * NW, word[i], __builtin_amdgcn_readlane(before, i));
+        for (uint32_t g = g0 + kPre * NW; g <= g1; g += 4 * NW) {
+            uint32_t w[4], pre[4];
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) {
+                w[i] = load(v, g + i * NW);
+                pre[i] = g + i * NW <= g1 ? bits_before(v, g + i * NW) : 0u;
+            }
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i)
+                if (g + i * NW <= g1) expand(out, n, rho0, g + i * NW, w[i], pre[i]);
+        }
+    }
+};
+
+// Rank r's sketch: read from the kernel argument segment (explicit arguments lie there in
+// declaration order at their natural alignment, the RankPtrs first), because indexing the argument
+// with a run-time r would keep all 32 pointers in registers (a pointer made from an integer has no
+// address space the compiler knows: it is declared global here, or every load through it would be
+// a flat one, which can only be waited for all at once).
+typedef __attribute__((address_space(1))) const float *GlobalCells;
+__device__ __forceinline__ GlobalCells rank_sketch(uint32_t r)
+{
+    typedef __attribute__((address_space(4))) const uint64_t *KernArg;
+    KernArg ka = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
+    return (GlobalCells)ka[r];
+}
+
+// The partition's unknowns, whose c-indices are in part.word, join their cells; all values start
+// at 0.  Writes the c-indices out on the way.
+template <uint32_t NT, uint32_t kIdx, bool kPacked>
+__device__ __forceinline__ void join_cells(const PartLds<kPacked> &part, uint32_t tid, uint32_t n,
+                                           uint32_t *idx_out)
+{
+#pragma unroll
+    for (uint32_t q = 0; q < kIdx; ++q) {
+        const uint32_t u = tid + q * NT;
+        if (u < n) {
+            const uint32_t i = part.word[u];
+            idx_out[u] = i;
+            const Cells cl = part.place(u, i);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) atomicAdd(part.meta(cl.c[j]), (u << 15) + 1u);
+        }
+    }
+}
+
+// Peels sketch partitions: unknowns rho0 .. rho0+Pa-1 in order of c-index, cells a*3*m_sub ...
 //
 // The LDS a partition needs leaves room for one workgroup per CU, and the rounds are bound
 // by LDS latency, not by memory.  So the grid is one workgroup per CU, each taking
-// partitions b, b+G, ...; while one partition is being peeled the cells and c-indices of
+// partitions b, b+G, ...; while one partition is being peeled the cells and Index words of
 // the workgroup's next one are already on their way into registers, and staging it costs
 // LDS stores only.
 // kCellPre / kIdxPre: cells / unknowns per thread the instantiation can hold.
-template <uint32_t kCellPre, uint32_t kIdxPre, bool kPacked>
+// kRanks: the cells are summed over the n_in <= kRanks ranks here, in rank order, the ranks' cells of
+// the next partition staying in the registers they are loaded to until it is staged.
+// kLoop: over any number of ranks, added up as they come.  For grids that have a workgroup for
+// every partition: there is no next partition whose sum could run beside the rounds, as
+// sum_peel_kernel has it (239 partitions of 8 ranks: 48 us, 52 in that kernel).
+constexpr uint32_t kIndexPre = 6;  // groups of Index words a wave requests ahead
+constexpr uint32_t kHeldRanks = 4;  // kRanks of the form for few ranks
+template <uint32_t kCellPre, uint32_t kIdxPre, bool kPacked, uint32_t kRanks, bool kLoop>
 __global__ void __launch_bounds__(kDecodeThreads)
-peel_kernel(const float *__restrict__ sketch, const uint32_t *__restrict__ header,
-            const uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
+peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t *__restrict__ header,
+            uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
             uint32_t *status, uint64_t seed, const uint32_t *__restrict__ salt, uint32_t T_cap,
             uint32_t P_cap, uint32_t mode)
 {
@@ -384,27 +457,48 @@ peel_kernel(const float *__restrict__ sketch, const uint32_t *__restrict__ heade
     PartLds<kPacked> part(lds64, T_cap, P_cap);
     __shared__ uint32_t s_n[3];  // see peel_rounds
     const uint32_t tid = threadIdx.x;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
     const uint32_t cells = 3 * m_sub;
     part.m_sub = m_sub;
 
-    // the cells and c-indices of partition `p` into registers (zeros beyond their ends)
-    float pre_cell[kCellPre];
-    uint32_t pre_idx[kIdxPre];
-    auto prefetch = [&](uint32_t p) {
-        const uint32_t r0 = uint32_t(uint64_t(p) * U / A);
-        const uint32_t n = uint32_t(uint64_t(p + 1) * U / A) - r0;
-        const float *src = sketch + uint64_t(p) * cells;
+    // the cells and Index words of partition `p` into registers (zeros beyond their ends)
+    float pre_cell[kRanks][kCellPre];
+    PartIndex<kDecodeThreads / 64, kIndexPre> pre_index;
+    auto request_cells = [&](float (&v)[kCellPre], uint32_t r, uint64_t tile) {
+        const GlobalCells src = rank_sketch(r) + tile;
 #pragma unroll
         for (uint32_t q = 0; q < kCellPre; ++q) {
             const uint32_t c = tid + q * kDecodeThreads;
-            pre_cell[q] = c < cells ? __builtin_nontemporal_load(src + c) : 0.0f;
+            v[q] = c < cells ? __builtin_nontemporal_load(src + c) : 0.0f;
         }
+    };
+    // adds the ranks held from the first-th on to the first one
+    auto add_cells = [&](uint32_t first, uint32_t n) {
 #pragma unroll
-        for (uint32_t q = 0; q < kIdxPre; ++q) {
-            const uint32_t u = tid + q * kDecodeThreads;
-            pre_idx[q] = u < n ? __builtin_nontemporal_load(idx_out + r0 + u) : 0u;
+        for (uint32_t i = 1; i < kRanks; ++i)
+            if (i >= first && i < n)
+#pragma unroll
+                for (uint32_t q = 0; q < kCellPre; ++q) pre_cell[0][q] += pre_cell[i][q];
+    };
+    auto prefetch = [&](uint32_t p) {
+        pre_index.request(index, p, wave);
+        const uint64_t tile = uint64_t(p) * cells;
+#pragma unroll
+        for (uint32_t i = 0; i < kRanks; ++i)
+            if (i < n_in) request_cells(pre_cell[i], i, tile);
+        if (!kLoop) return;
+        for (uint32_t r = kRanks; r < n_in; r += kRanks - 1) {
+            __builtin_amdgcn_sched_barrier(0);
+            add_cells(1, kRanks);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (uint32_t i = 1; i < kRanks; ++i)
+                if (r + i - 1 < n_in) request_cells(pre_cell[i], r + i - 1, tile);
+                else
+#pragma unroll
+                    for (uint32_t q = 0; q < kCellPre; ++q) pre_cell[i][q] = -0.0f;  // (x + -0 is x)
         }
     };
     if (blockIdx.x < A) prefetch(blockIdx.x);
@@ -420,27 +514,20 @@ peel_kernel(const float *__restrict__ sketch, const uint32_t *__restrict__ heade
     part.sw1 = seed_word(seed, 3 * sa + 1);
     part.sw2 = seed_word(seed, 3 * sa + 2);
 
-    // ---- stage the partition's cells from the registers, clear state
+    // ---- stage the partition's cells and unknowns from the registers, clear state
+    for (uint32_t c = tid; c < P_cap / 32 + 1; c += kDecodeThreads) part.claimed[c] = 0;
+    if (tid < 3) s_n[tid] = 0;
+    pre_index.enumerate(index, part.word, Pa, rho0, wave);
+    add_cells(1, n_in);
 #pragma unroll
     for (uint32_t q = 0; q < kCellPre; ++q) {
         const uint32_t c = tid + q * kDecodeThreads;
-        if (c < cells) part.cell[c] = __float_as_uint(pre_cell[q]);
+        if (c < cells) part.cell[c] = __float_as_uint(pre_cell[0][q]);
     }
-    for (uint32_t c = tid; c < P_cap / 32 + 1; c += kDecodeThreads) part.claimed[c] = 0;
-    if (tid < 3) s_n[tid] = 0;
     __syncthreads();
     PHASE_MARK(0);
 
-    // ---- every unknown joins its three cells; all values start at 0
-#pragma unroll
-    for (uint32_t q = 0; q < kIdxPre; ++q) {
-        const uint32_t u = tid + q * kDecodeThreads;
-        if (u < Pa) {
-            const Cells cl = part.place(u, pre_idx[q]);
-#pragma unroll
-            for (int j = 0; j < 3; ++j) atomicAdd(part.meta(cl.c[j]), (u << 15) + 1u);
-        }
-    }
+    join_cells<kDecodeThreads, kIdxPre>(part, tid, Pa, idx_out + rho0);
     // the registers are free again: the next partition's data travels during the rounds
     if (a + gridDim.x < A) prefetch(a + gridDim.x);
     __syncthreads();
@@ -499,8 +586,9 @@ __device__ inline void peel_barrier(uint32_t *word, uint32_t &expected)
 }
 
 __global__ void __launch_bounds__(kDecodeThreads)
-sum_peel_kernel(const RankPtrs rp, uint32_t n_in, const uint32_t *__restrict__ header,
-                const uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
+sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
+                const uint32_t *__restrict__ header, uint32_t *__restrict__ idx_out,
+                float *__restrict__ val_out,
                 uint32_t *status, uint64_t seed, const uint32_t *__restrict__ salt,
                 uint32_t T_cap, uint32_t P_cap, uint32_t mode)
 {
@@ -518,19 +606,6 @@ sum_peel_kernel(const RankPtrs rp, uint32_t n_in, const uint32_t *__restrict__ h
     if (tid >= kPeelThreads) {
         // ------------------------------------------------------------ the loaders
         const uint32_t lt = tid - kPeelThreads;
-        // rank r's sketch: read from the kernel argument segment (explicit arguments lie
-        // there in declaration order at their natural alignment, `rp` first), because
-        // indexing the argument with a run-time r would keep all 32 pointers in registers
-        // (a pointer made from an integer has no address space the compiler knows: it is
-        // declared global here, or every load through it would be a flat one, which can
-        // only be waited for all at once)
-        typedef __attribute__((address_space(1))) const float *GlobalCells;
-        auto rank_sketch = [&](uint32_t r) -> GlobalCells {
-            typedef __attribute__((address_space(4))) const uint64_t *KernArg;
-            KernArg ka = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
-            (void)rp;
-            return (GlobalCells)ka[r];
-        };
         float acc[kLoadCells];
         float b0[kUnit], b1[kUnit], b2[kUnit];
         // third t (cells [16 t, 16 t + 16) of this thread's 48) of `src`, a rank's partition.
@@ -590,17 +665,9 @@ sum_peel_kernel(const RankPtrs rp, uint32_t n_in, const uint32_t *__restrict__ h
     }
 
     // ---------------------------------------------------------------- the peelers
-    uint32_t pre_idx[kPeelIdx];
-    auto prefetch_idx = [&](uint32_t p) {
-        const uint32_t r0 = uint32_t(uint64_t(p) * U / A);
-        const uint32_t n = uint32_t(uint64_t(p + 1) * U / A) - r0;
-#pragma unroll
-        for (uint32_t q = 0; q < kPeelIdx; ++q) {
-            const uint32_t u = tid + q * kPeelThreads;
-            pre_idx[q] = u < n ? __builtin_nontemporal_load(idx_out + r0 + u) : 0u;
-        }
-    };
-    if (blockIdx.x < A) prefetch_idx(blockIdx.x);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    PartIndex<kPeelWaves, kIndexPre> pre_index;
+    if (blockIdx.x < A) pre_index.request(index, blockIdx.x, wave);
     uint32_t bar_expected = 0, max_rounds = 0;
     part.m_sub = m_sub;
     for (uint32_t a = blockIdx.x; a < A; a += gridDim.x) {
@@ -615,17 +682,11 @@ sum_peel_kernel(const RankPtrs rp, uint32_t n_in, const uint32_t *__restrict__ h
         if (tid < 3) s_n[tid] = 0;
         __syncthreads();  // the loaders have staged the cells
 
-        // ---- every unknown joins its three cells
-#pragma unroll
-        for (uint32_t q = 0; q < kPeelIdx; ++q) {
-            const uint32_t u = tid + q * kPeelThreads;
-            if (u < Pa) {
-                const Cells cl = part.place(u, pre_idx[q]);
-#pragma unroll
-                for (int j = 0; j < 3; ++j) atomicAdd(part.meta(cl.c[j]), (u << 15) + 1u);
-            }
-        }
-        if (a + gridDim.x < A) prefetch_idx(a + gridDim.x);
+        // (here and not before the barriers, where the loaders would wait for it)
+        pre_index.enumerate(index, part.word, Pa, rho0, wave);
+        peel_barrier(&s_bar, bar_expected);
+        join_cells<kPeelThreads, kPeelIdx>(part, tid, Pa, idx_out + rho0);
+        if (a + gridDim.x < A) pre_index.request(index, a + gridDim.x, wave);
         peel_barrier(&s_bar, bar_expected);
         if (mode != TAGC_DECODE_ESTIMATE)
             queue_first<kPeelThreads, kPeelSlots>(part, tid, &s_n[1],
@@ -716,53 +777,49 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     const uint32_t n_words = uint32_t(p->n_c / 32);
     const uint32_t n_chunks = uint32_t(p->n_chunks);
     const uint32_t *chunkpre = static_cast<const uint32_t *>(sh->workspace);
-    if (n_chunks) {
-        ProfileScope ps("enumerate", s);
-        enumerate_kernel<<<n_chunks, 256, 0, s>>>(sh->bitmap, n_words, chunkpre, sh->header,
-                                                  idx_out);
-    }
+    const IndexView index{sh->bitmap, chunkpre, group_prefixes(sh->workspace, n_chunks), sh->bounds,
+                          n_words};
+    const size_t lds = decode_lds_bytes(p->T_cap, p->P_cap);
+    // a workgroup takes partitions b, b + grid, ...: any grid size gives the same result
+    uint32_t grid = uint32_t(std::min<uint64_t>(p->A_cap, uint64_t(device_cu_count())));
+    if (p->cfg.decode_workgroups) grid = std::min(grid, p->cfg.decode_workgroups);
+    RankPtrs rp{};
     if (fused) {
-        ProfileScope ps("sum_peel", s);
-        RankPtrs rp{};
         for (uint32_t r = 0; r < n_ranks; ++r) rp.p[r] = ranks[r].sketch;
-        const size_t lds = decode_lds_bytes(p->T_cap, p->P_cap);
-        uint32_t grid = uint32_t(std::min<uint64_t>(p->A_cap, uint64_t(device_cu_count())));
-        if (p->cfg.decode_workgroups) grid = std::min(grid, p->cfg.decode_workgroups);
-        static size_t attr_bytes = 0;
-        if (lds > attr_bytes) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(sum_peel_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    int(lds)) != hipSuccess)
-                return TAGC_EHIP;
-            attr_bytes = lds;
-        }
-        sum_peel_kernel<<<grid, kDecodeThreads, lds, s>>>(
-            rp, n_ranks, sh->header, idx_out, val_out, sh->status, p->cfg.seed,
-            sh->bounds + p->A_cap + 1, p->T_cap, p->P_cap, p->cfg.decode_mode);
     } else {
-        ProfileScope ps("peel", s);
-        const size_t lds = decode_lds_bytes(p->T_cap, p->P_cap);
-        // a workgroup takes partitions b, b + grid, ...: any grid size gives the same result
-        uint32_t grid = uint32_t(std::min<uint64_t>(p->A_cap, uint64_t(device_cu_count())));
-        if (p->cfg.decode_workgroups) grid = std::min(grid, p->cfg.decode_workgroups);
-        // the default partition size gets an instantiation that holds exactly its data
-        constexpr uint32_t kC0 = (kDefaultPartCells + kDecodeThreads - 1) / kDecodeThreads;
-        constexpr uint32_t kI0 = (kDefaultPartUnknowns + kDecodeThreads - 1) / kDecodeThreads;
-        constexpr uint32_t kC1 = (kMaxPartCells + kDecodeThreads - 1) / kDecodeThreads;
-        constexpr uint32_t kI1 = (kMaxPartUnknowns + kDecodeThreads - 1) / kDecodeThreads;
-        const bool small = packed_slots(p->T_cap, p->P_cap);
-        auto kernel = small ? peel_kernel<kC0, kI0, true> : peel_kernel<kC1, kI1, false>;
-        static size_t attr_bytes[2] = {0, 0};
-        if (lds > attr_bytes[small]) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    int(lds)) != hipSuccess)
-                return TAGC_EHIP;
-            attr_bytes[small] = lds;
-        }
-        kernel<<<grid, kDecodeThreads, lds, s>>>(
-            sh->sketch, sh->header, idx_out, val_out, sh->status, p->cfg.seed,
-            sh->bounds + p->A_cap + 1, p->T_cap, p->P_cap, p->cfg.decode_mode);
+        rp.p[0] = sh->sketch;
+        n_ranks = 1;
+    }
+    // the default partition size gets an instantiation that holds exactly its data
+    constexpr uint32_t kC0 = (kDefaultPartCells + kDecodeThreads - 1) / kDecodeThreads;
+    constexpr uint32_t kI0 = (kDefaultPartUnknowns + kDecodeThreads - 1) / kDecodeThreads;
+    constexpr uint32_t kC1 = (kMaxPartCells + kDecodeThreads - 1) / kDecodeThreads;
+    constexpr uint32_t kI1 = (kMaxPartUnknowns + kDecodeThreads - 1) / kDecodeThreads;
+    // One summed sketch; up to four ranks; any number with a workgroup per partition; any number.
+    // (Two ranks of 202 M entries, a tenth kept: 654 us with sixteen waves peeling, 696 in
+    // sum_peel_kernel, of whose sixteen four sum; four ranks of 9 M, two fifths kept: 135 and 141.
+    // More ranks' cells do not fit the registers beside the rounds.)
+    const uint32_t form = !fused                  ? (packed_slots(p->T_cap, p->P_cap) ? 1u : 0u)
+                          : n_ranks <= kHeldRanks ? 2u
+                          : grid == p->A_cap      ? 3u
+                                                  : 4u;
+    const auto kernel = form == 4   ? sum_peel_kernel
+                        : form == 3 ? peel_kernel<kC0, kI0, true, kHeldRanks, true>
+                        : form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false>
+                        : form == 1 ? peel_kernel<kC0, kI0, true, 1, false>
+                                    : peel_kernel<kC1, kI1, false, 1, false>;
+    static size_t attr_bytes[5] = {0, 0, 0, 0, 0};
+    if (lds > attr_bytes[form]) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
+            return TAGC_EHIP;
+        attr_bytes[form] = lds;
+    }
+    {
+        ProfileScope ps(fused ? "sum_peel" : "peel", s);
+        kernel<<<grid, kDecodeThreads, lds, s>>>(rp, n_ranks, index, sh->header, idx_out, val_out,
+                                                 sh->status, p->cfg.seed, sh->bounds + p->A_cap + 1,
+                                                 p->T_cap, p->P_cap, p->cfg.decode_mode);
     }
     if (dense_out && n_chunks) {
         ProfileScope ps("dense", s);

@@ -21,9 +21,11 @@ template <int MODE>
 __global__ void __launch_bounds__(256)
 index_merge_kernel(RankPtrs rp, uint32_t n_in, uint32_t *__restrict__ out, uint32_t n_words,
                    int accumulate, int last, uint32_t *__restrict__ sum4,
-                   uint32_t *__restrict__ chunkcnt)
+                   uint32_t *__restrict__ chunkcnt, uint16_t *__restrict__ grouppre)
 {
-    __shared__ uint32_t smem[4];
+    static_assert(kChunkWords == 16 * kGroupWords && kGroupWords == 64, "16 groups of a wave's words");
+    __shared__ uint32_t smem[16];
+    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
     const uint32_t w0 = blockIdx.x * kChunkWords + threadIdx.x * 4;
     uint32_t pc = 0;
     if (MODE == TAGC_INDEX_ADD4) {
@@ -32,23 +34,29 @@ index_merge_kernel(RankPtrs rp, uint32_t n_in, uint32_t *__restrict__ out, uint3
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {
             const uint32_t w = blockIdx.x * kChunkWords + k * 256 + threadIdx.x;
-            if (w >= n_words) break;
-            const size_t q = 4 * size_t(w);
-            uint4 acc = accumulate ? *reinterpret_cast<const uint4 *>(sum4 + q)
-                                   : make_uint4(0, 0, 0, 0);
+            uint32_t set = 0;
+            if (w < n_words) {
+                const size_t q = 4 * size_t(w);
+                uint4 acc = accumulate ? *reinterpret_cast<const uint4 *>(sum4 + q)
+                                       : make_uint4(0, 0, 0, 0);
 #pragma unroll 8
-            for (uint32_t r = 0; r < n_in; ++r) {
-                const uint4 v = ld_stream(
-                    reinterpret_cast<const uint4 *>(static_cast<const uint32_t *>(rp.p[r]) + q));
-                acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+                for (uint32_t r = 0; r < n_in; ++r) {
+                    const uint4 v = ld_stream(reinterpret_cast<const uint4 *>(
+                        static_cast<const uint32_t *>(rp.p[r]) + q));
+                    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+                }
+                if (!last) {
+                    *reinterpret_cast<uint4 *>(sum4 + q) = acc;
+                } else {
+                    const uint32_t m = nibbles_set(acc.x) | (nibbles_set(acc.y) << 8) |
+                                       (nibbles_set(acc.z) << 16) | (nibbles_set(acc.w) << 24);
+                    out[w] = m;
+                    set = __popc(m);
+                }
             }
-            if (!last) {
-                *reinterpret_cast<uint4 *>(sum4 + q) = acc;
-            } else {
-                const uint32_t m = nibbles_set(acc.x) | (nibbles_set(acc.y) << 8) |
-                                   (nibbles_set(acc.z) << 16) | (nibbles_set(acc.w) << 24);
-                out[w] = m;
-                pc += __popc(m);
+            if (chunkcnt) {  // the wave's words are one group
+                set = wave_sum(set);
+                if (lane == 0) smem[4 * k + wave] = set;
             }
         }
     } else if (w0 + 4 <= n_words) {
@@ -75,9 +83,18 @@ index_merge_kernel(RankPtrs rp, uint32_t n_in, uint32_t *__restrict__ out, uint3
             pc += __popc(acc);
         }
     }
-    if (chunkcnt) {
-        pc = block_sum<uint32_t, 4>(pc, smem);
-        if (threadIdx.x == 0) chunkcnt[blockIdx.x] = pc;
+    if (!chunkcnt) return;
+    // set bits of every group of 64 words: a row of 16 lanes has its four words each
+    if (MODE != TAGC_INDEX_ADD4) {
+        for (uint32_t d = 1; d < 16; d <<= 1) pc += __shfl_xor(pc, d, 64);
+        if ((lane & 15) == 0) smem[threadIdx.x >> 4] = pc;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const uint32_t n = lane < 16 ? smem[lane] : 0u;
+        const uint32_t inc = wave_incl_scan<uint32_t>(n);
+        if (lane < 16) grouppre[blockIdx.x * 16 + lane] = uint16_t(inc - n);
+        if (lane == 15) chunkcnt[blockIdx.x] = inc;
     }
 }
 
@@ -461,10 +478,11 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
 {
     const uint32_t n_words = uint32_t(p->n_c / 32);
     const uint32_t n_chunks = uint32_t(p->n_chunks);
-    // set bits of every chunk; their prefix sums, what the decoder reads (at the start, where it
-    // looks for them); behind both, the 4-bit running sum (the plan sized all of it)
+    // (see index_words) prefix sums of the chunks' set bits, the chunks' set bits, the groups'
+    // prefix sums inside their chunks, and the 4-bit running sum
     uint32_t *chunkpre = static_cast<uint32_t *>(sh->workspace);
     uint32_t *chunk = chunkpre + n_chunks + 1;
+    uint16_t *grouppre = group_prefixes(chunkpre, n_chunks);
     if (n_chunks) {
         ProfileScope ps("index_or", s);
         for (uint32_t r0 = 0; r0 < n_ranks; r0 += kMaxRanksPerPass) {
@@ -479,7 +497,7 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
                                      ? index_merge_kernel<TAGC_INDEX_ADD1>
                                      : index_merge_kernel<TAGC_INDEX_OR1>);
             kernel<<<n_chunks, 256, 0, s>>>(rp, n_in, sh->bitmap, n_words, r0 != 0, last, sum4,
-                                            last ? chunk : nullptr);
+                                            last ? chunk : nullptr, grouppre);
         }
     }
     const LayoutParams lp{p->cfg.sizing,

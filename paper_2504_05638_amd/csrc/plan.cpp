@@ -240,8 +240,6 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
     z.shared_header_bytes = 4 * TAGC_HDR_WORDS;
     // the partitions' first c-indices (A + 1), then their hash salts (A)
     z.shared_bounds_bytes = round_up(4 * (2 * p->A_cap + 1), 16);
-    // chunk prefixes and counts; behind them, when the 4-bit Index of more ranks than one pass
-    // takes is summed, the running 4-bit sum
     z.shared_workspace_bytes = 4 * index_words(p->n_chunks);
     if (cfg->index_mode == TAGC_INDEX_ADD4 && cfg->n_ranks > kMaxRanksPerPass)
         z.shared_workspace_bytes += round_up(16 * words, 16);

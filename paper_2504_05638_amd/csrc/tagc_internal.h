@@ -32,7 +32,8 @@ constexpr uint32_t kFastMinKeep = 64;
 constexpr uint32_t kWideEmitCap = 192;  // candidate slots per chunk from which count / place give a wave to a super-chunk
 constexpr uint32_t kWideEmitSuperChunks = 2048;  // ... and super-chunks per bucket from which they do so anyway
 constexpr double kFastMaxCandFrac = 0.30;  // expected candidates per element beyond which the dense path is planned
-constexpr uint32_t kChunkWords = 1024;  // Index words per popcount chunk
+constexpr uint32_t kChunkWords = 1024;  // Index words per popcount chunk, ...
+constexpr uint32_t kGroupWords = 64;    // ... and per group of it
 constexpr uint32_t kTileGroup = 64;     // dense-route tiles whose counts are also kept as one sum
 // A partition keeps, in LDS, 10 bytes per cell (value, meta word, queue slot) and 4 per
 // unknown (its c-index): 12288 cells and 8192 unknowns fill the 160 KiB.
@@ -156,9 +157,14 @@ struct tagc_plan_s {
 
 namespace tagc {
 
-// words of the shared workspace before the 4-bit running sum: chunk prefixes (one more than
-// chunks), chunk counts
-inline uint64_t index_words(uint64_t n_chunks) { return (2 * n_chunks + 1 + 3) & ~uint64_t(3); }
+// The shared workspace: set bits before every chunk of the merged Index (and in all), set bits of
+// every chunk, set bits of a chunk before each of its 16 groups of 64 words (16 bits each); then,
+// when the 4-bit Index of more ranks than one pass takes is summed, the running sum.
+inline uint16_t *group_prefixes(void *workspace, uint64_t n_chunks)
+{
+    return static_cast<uint16_t *>(workspace) + 2 * (2 * n_chunks + 1);
+}
+inline uint64_t index_words(uint64_t n_chunks) { return (2 * n_chunks + 1 + 8 * n_chunks + 3) & ~uint64_t(3); }
 
 // ------------------------------------------------------------------- hash
 
