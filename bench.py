@@ -25,7 +25,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X published HBM3E bandwidth
 # Kernels of the library grouped into the stages of the path.
 STAGES = {
     "S1+S2 sparsify+index": ["fill_zero", "accumulate", "prepare", "scan_spill", "hist1",
-                             "hist2c", "hist2", "select2", "count", "place", "widen4"],
+                             "refine", "count", "place", "widen4"],
     "S3a index OR": ["index_or", "layout"],
     "S2' encode": ["encode"],
     "S3b sketch sum": ["sketch_sum"],
@@ -219,7 +219,6 @@ def kernel_alg_bytes(b, z, hdr, k_total, dense, ef=False, wire=1, cell=4):
     return {
         "scan_spill": (3 if ef else 1) * N * z.n_real * e,
         "hist1": N * z.n_real * e,
-        "hist2": N * z.n_real * e,
         # place = the candidate route's last pass + the dense route's (which reads the gradient
         # again); priced as the former, which is all it is for a bucket without dense-route
         # segments; count reads the candidate slots (about 1.3 x 4 bytes per pair)

@@ -22,7 +22,7 @@
 //                 workgroup that finishes a segment last selects its exact threshold from
 //                 the candidate histogram; if the candidates do not contain k entries (the
 //                 pre-threshold misled) the segment is re-routed
-//    hist2c/select2  fp32 only: low 16 key bits inside the threshold bin
+//    refine       fp32 only: low 16 key bits inside the threshold bin
 //    count        survivors of every super-chunk of candidates (32 chunks)
 //    place        ordered pass over the candidates only: pairs + every Index word
 //
@@ -30,7 +30,7 @@
 //  pre-threshold yet, or were re-routed; three reads)
 //    hist1        exact histogram of the top 15 key bits of every entry, in LDS windows; the
 //                 workgroup that completes a segment's histogram selects its threshold
-//    hist2/select2 fp32 only, as above
+//    refine       fp32 only, as above
 //    count        survivors of every tile of the gradient
 //    place        ordered pass over the gradient: pairs + Index words
 //
@@ -1266,129 +1266,6 @@ hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t n
     }
 }
 
-// fp32, dense route: histogram of the low 16 key bits of the entries in the threshold bin.
-__global__ void __launch_bounds__(256)
-hist2_kernel(const SparsifyBatch, const uint32_t *__restrict__ table, const WsLayout wl)
-{
-    const RankView rv = rank_view();
-    const char *grad = rv.src();
-    const SelDev *sel = rv.at<SelDev>(wl.sel);
-    uint32_t *hist2 = rv.at<uint32_t>(wl.hist2);
-    const uint32_t L = table[0];
-    const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
-    if (!any_dense_route(segs, sel, L)) return;
-    const uint32_t tid = threadIdx.x;
-    for (uint32_t l = 0; l < L; ++l) {
-        const SegDev sd = segs[l];
-        if (!on_dense_route(sd, sel, l) || !sel[l].need2) continue;
-        const uint32_t bin1 = sel[l].bin1;
-        uint32_t *gh = hist2 + uint64_t(l) * kBins2;
-        const char *base = grad + sd.offset * 4;
-        if (sd.flags & kSegAligned) {
-            const uint4 *vp = reinterpret_cast<const uint4 *>(base);
-            const uint64_t nvec = sd.n / 4;
-            for (uint64_t v = blockIdx.x * 256ull + tid; v < nvec; v += gridDim.x * 256ull) {
-                uint4 q = vp[v];
-                uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    uint32_t key = w[e] & 0x7FFFFFFFu;
-                    if (key && (key >> 16) == bin1) atomicAdd(&gh[key & 0xFFFFu], 1u);
-                }
-            }
-            if (blockIdx.x == 0) {
-                uint64_t i = nvec * 4 + tid;
-                if (i < sd.n) {
-                    uint32_t key = reinterpret_cast<const uint32_t *>(base)[i] & 0x7FFFFFFFu;
-                    if (key && (key >> 16) == bin1) atomicAdd(&gh[key & 0xFFFFu], 1u);
-                }
-            }
-        } else {
-            for (uint64_t i = blockIdx.x * 256ull + tid; i < sd.n; i += gridDim.x * 256ull) {
-                uint32_t key = reinterpret_cast<const uint32_t *>(base)[i] & 0x7FFFFFFFu;
-                if (key && (key >> 16) == bin1) atomicAdd(&gh[key & 0xFFFFu], 1u);
-            }
-        }
-    }
-}
-
-// fp32, candidate route: the same histogram from the spilled candidates.
-__global__ void __launch_bounds__(256)
-hist2c_kernel(const SparsifyBatch, const uint32_t *__restrict__ table, const WsLayout wl,
-              uint32_t CAP)
-{
-    const RankView rv = rank_view();
-    const SelDev *sel = rv.at<SelDev>(wl.sel);
-    const uint32_t *cand = rv.at<uint32_t>(wl.cand);
-    const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
-    const uint32_t n_slots_total = uint32_t(wl.n_slots);
-    uint32_t *hist2 = rv.at<uint32_t>(wl.hist2);
-    constexpr uint32_t CHUNK = 64 * 4 * kCandRows;
-    const uint32_t L = table[0];
-    const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
-    const uint32_t lane = threadIdx.x & 63;
-    const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6), n_waves = gridDim.x * 4;
-    for (uint32_t l = 0; l < L; ++l) {
-        const SegDev sd = segs[l];
-        if (sd.k == 0 || sd.n == 0 || on_dense_route(sd, sel, l) || !sel[l].need2) continue;
-        const uint32_t bin1 = sel[l].bin1;
-        uint32_t *gh = hist2 + uint64_t(l) * kBins2;
-        const uint32_t n_chunks = (sd.n + CHUNK - 1) / CHUNK;
-        for (uint32_t ch = wave; ch < n_chunks; ch += n_waves) {
-            const uint32_t g = sd.sc_start * kCandChunksPerSuper + ch;
-            const uint2 info = chunk_info[g];  // count, first slot
-            const uint32_t c = min(info.x, CAP);
-            const uint32_t first = min(info.y, n_slots_total - CAP);
-            for (uint32_t i = lane; i < c; i += 64) {
-                const uint32_t key = cand[first + i] & 0x7FFFFFFFu;
-                if ((key >> 16) == bin1) atomicAdd(&gh[key & 0xFFFFu], 1u);
-            }
-        }
-    }
-}
-
-__global__ void __launch_bounds__(kHistThreads)
-select2_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
-{
-    const RankView rv = rank_view();
-    SelDev *sel = rv.at<SelDev>(wl.sel);
-    const uint32_t *hist2 = rv.at<uint32_t>(wl.hist2);
-    __shared__ uint32_t smem[32];
-    const uint32_t l = blockIdx.x;
-    const SegDev sd = reinterpret_cast<const SegDev *>(table + 8)[l];
-    if (sd.k == 0 || sd.n == 0) return;
-    SelDev r = sel[l];
-    if (!r.need2) return;
-    const uint32_t *h = hist2 + uint64_t(l) * kBins2;
-    constexpr uint32_t BPT = kBins2 / kHistThreads;
-    uint32_t total;
-    BinFound f[2];
-    select_top<kHistThreads, BPT>([&](uint32_t b) { return h[b]; }, own_bins<BPT>(h),
-                                  {sd.k - r.G1, 0u}, f, &total, smem);
-    if (threadIdx.x != 0) return;
-    uint32_t bin = f[0].bin, above = f[0].above;
-    if (bin == kNoBin) {  // cannot happen when both histograms saw the same data
-        bin = 0;
-        above = total;
-        atomicOr(&table_state(table, table[0], rv.slot).glob[0], TAGC_FLAG_OVERFLOW);
-    }
-    r.T = (r.bin1 << 16) | bin;
-    r.G = r.G1 + above;
-    r.quota = sd.k - r.G;
-    r.cnt = sd.k;
-    r.need2 = 0;
-    sel[l] = r;
-}
-
-// ---------------------------------------------------------- ordered output
-
-// Ordered output (the candidate route's super-chunks, the dense route's tiles) takes two
-// launches and no waiting.  `count` leaves, per item, count(key > T) << 31 | count(key == T);
-// `place` starts when all of them are there: every item adds up the counts of the earlier
-// items of its segment by itself (a few hundred to a few thousand words from the L2) and puts
-// its survivors where they belong.  No workgroup ever depends on another one's progress, so
-// neither the order in which the device starts them nor other kernels in flight matter.
-
 // last l with start(l) <= t, start() read through `field` (tile_start or sc_start)
 template <typename F>
 __device__ inline uint32_t segment_of(uint32_t L, uint32_t t, F start)
@@ -1400,6 +1277,197 @@ __device__ inline uint32_t segment_of(uint32_t L, uint32_t t, F start)
     }
     return lo;
 }
+
+// fp32: the low 16 key bits of the thresholds, for the segments whose level-1 bin is known.  The
+// keys of that bin are counted twice, by all 16 bits (memory) and by the upper 8 of them (LDS, then
+// the segment's candidate histogram in the table, which is idle from its selection on: key by
+// key, its few cache lines would be the bottleneck); the workgroup
+// that is done with a segment last looks at 256 counts of each.  Candidate route: the keys come
+// from the spilled slots; the super-chunks of all segments form one list, a workgroup takes one
+// contiguous span of it and a wave a super-chunk at a time, whose chunks' slots are requested
+// kRefineBatch at a time (one chunk after the other, each a chain of two loads, this took 16 us on
+// 8 ranks of 7 M entries, and the two launches that followed 5 and 10; all of it now 14).
+// Dense route: from the gradient, by all workgroups.
+constexpr uint32_t kRefineBatch = 16;
+
+// By a wave, of 256 counts: the largest b with sum_{x >= b} bins[x] >= want and the entries in
+// higher ones; kNoBin if all together hold fewer.
+__device__ inline uint32_t top_of_256(const uint32_t *bins, uint32_t want, uint32_t *above)
+{
+    const uint32_t lane = lane_id();
+    const uint4 v = reinterpret_cast<const uint4 *>(bins)[lane];
+    const uint32_t c[4] = {v.x, v.y, v.z, v.w};
+    const uint32_t own = c[0] + c[1] + c[2] + c[3];
+    const uint32_t inc = wave_incl_scan<uint32_t>(own);
+    const uint32_t total = __builtin_amdgcn_readlane(inc, 63);
+    uint32_t acc = total - inc, bin = kNoBin, at = total;  // acc: in the lanes above
+#pragma unroll
+    for (int i = 3; i >= 0; --i) {
+        if (acc < want && acc + c[i] >= want) {
+            bin = 4 * lane + uint32_t(i);
+            at = acc;
+        }
+        acc += c[i];
+    }
+    const uint64_t who = __ballot(bin != kNoBin);
+    const uint32_t l = who ? uint32_t(__builtin_ctzll(who)) : 0u;
+    *above = __builtin_amdgcn_readlane(at, l);
+    return __builtin_amdgcn_readlane(bin, l);
+}
+
+__global__ void __launch_bounds__(256)
+refine_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t CAP)
+{
+    constexpr uint32_t CHUNK = 64 * 4 * kCandRows, NCH = kCandChunksPerSuper, NWV = 4;
+    __shared__ uint32_t s_last, s_coarse[256];
+    const RankView rv = rank_view();
+    SelDev *sel = rv.at<SelDev>(wl.sel);
+    const uint32_t *cand = rv.at<uint32_t>(wl.cand);
+    const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
+    const uint32_t n_slots_total = uint32_t(wl.n_slots);
+    const uint32_t L = table[0], total_sc = table[4];
+    const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
+    const TableState ts = table_state(table, L, rv.slot);
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    s_coarse[tid] = 0;
+    __syncthreads();
+
+    auto add_key = [&](uint32_t l, uint32_t bin1, uint32_t key) {
+        const bool hit = key && (key >> 16) == bin1;
+        const uint64_t hits = __ballot(hit);
+        if (!hits) return;
+        const uint32_t leader = uint32_t(__builtin_ctzll(hits));
+        uint32_t n = 1;
+        bool adds = hit;
+        // many keys and all the same (quantised values): one add for the wave
+        if (__popcll(hits) > 8 && !__ballot(hit && key != __builtin_amdgcn_readlane(key, leader))) {
+            n = uint32_t(__popcll(hits));
+            adds = lane == leader;
+        }
+        if (adds) {
+            atomicAdd(&rv.at<uint32_t>(wl.hist2)[uint64_t(l) * kBins2 + (key & 0xFFFFu)], n);
+            atomicAdd(&s_coarse[(key >> 8) & 0xFFu], n);
+        }
+    };
+    // the workgroup is done with its part of segment l; the last of `expected` selects
+    auto finish = [&](uint32_t l, uint32_t k, SelDev r, uint32_t expected) {
+        __syncthreads();  // s_coarse is complete
+        const uint32_t c = s_coarse[tid];
+        s_coarse[tid] = 0;
+        if (c) atomicAdd(&ts.win[size_t(l) * kWinWords + tid], c);
+        wait_own_memory_ops();
+        __syncthreads();
+        if (tid == 0) s_last = atomicAdd(&ts.arrive[l], 1u) == expected - 1u;
+        __syncthreads();
+        if (s_last && wave == 0) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            uint32_t *coarse = ts.win + size_t(l) * kWinWords;
+            const uint32_t want = k - r.G1;
+            uint32_t hi_above, lo_above = 0, bin = 0;
+            const uint32_t hi = top_of_256(coarse, want, &hi_above);
+            reinterpret_cast<uint4 *>(coarse)[lane] = make_uint4(0, 0, 0, 0);
+            if (hi != kNoBin)
+                bin = hi << 8 | top_of_256(rv.at<uint32_t>(wl.hist2) + uint64_t(l) * kBins2 + hi * 256,
+                                           want - hi_above, &lo_above);
+            else if (lane == 0)  // cannot happen when both histograms saw the same data
+                atomicOr(&ts.glob[0], TAGC_FLAG_OVERFLOW);
+            if (lane == 0) {
+                r.T = (r.bin1 << 16) | bin;
+                r.G = r.G1 + hi_above + lo_above;
+                r.quota = k - r.G;
+                r.cnt = k;
+                r.need2 = 0;
+                sel[l] = r;
+                ts.arrive[l] = 0;
+            }
+        }
+        __syncthreads();  // s_last
+    };
+
+    // ---- candidate route: super-chunks [s0, s1) of the list
+    const uint32_t span = (total_sc + gridDim.x - 1) / gridDim.x;
+    const uint32_t s0 = min(blockIdx.x * span, total_sc), s1 = min(s0 + span, total_sc);
+    // (requested before anything is known of the segments: every link of the chain counts)
+    auto info_of = [&](uint32_t sc) {
+        return lane < NCH && sc < s1 ? chunk_info[sc * NCH + lane] : make_uint2(0, 0);
+    };
+    const uint2 info0 = info_of(s0 + wave);
+    uint32_t l0 = L;  // the last segment that starts at s0 or before
+    if (s0 < s1) {
+        if (L <= 64)
+            l0 = uint32_t(__popcll(__ballot(lane < L && segs[lane < L ? lane : 0].sc_start <= s0))) - 1u;
+        else
+            l0 = segment_of(L, s0, [&](uint32_t i) { return segs[i].sc_start; });
+    }
+    for (uint32_t l = l0; l < L; ++l) {
+        const SegDev sd = segs[l];
+        const SelDev se = sel[l];
+        if (sd.sc_start >= s1) break;
+        if (sd.k == 0 || sd.n == 0 || !(sd.flags & kSegFast) || se.route || !se.need2) continue;
+        const uint32_t bin1 = se.bin1;
+        const uint32_t n_sc = (sd.n + CHUNK * NCH - 1) / (CHUNK * NCH);
+        const uint32_t lo = max(s0, sd.sc_start), hi = min(s1, sd.sc_start + n_sc);
+        if (lo >= hi) continue;
+        for (uint32_t sc = lo + wave; sc < hi; sc += NWV) {
+            uint32_t cnt_l = 0, first_l = 0;  // of chunk `lane`
+            if (lane < NCH && ((sc - sd.sc_start) * NCH + lane) * CHUNK < sd.n) {
+                const uint2 info = sc == s0 + wave ? info0 : info_of(sc);
+                cnt_l = min(info.x, CAP);
+                first_l = min(info.y, n_slots_total - CAP);
+            }
+#pragma unroll
+            for (uint32_t b0 = 0; b0 < NCH; b0 += kRefineBatch) {
+                uint32_t v[kRefineBatch];
+#pragma unroll
+                for (uint32_t j = 0; j < kRefineBatch; ++j) {
+                    const uint32_t c = __builtin_amdgcn_readlane(cnt_l, b0 + j);
+                    const uint32_t first = __builtin_amdgcn_readlane(first_l, b0 + j);
+                    v[j] = lane < c ? cand[first + lane] : 0u;
+                }
+#pragma unroll
+                for (uint32_t j = 0; j < kRefineBatch; ++j) add_key(l, bin1, v[j] & 0x7FFFFFFFu);
+            }
+            for (uint64_t more = __ballot(cnt_l > 64); more; more &= more - 1) {
+                const uint32_t ch = uint32_t(__builtin_ctzll(more));
+                const uint32_t c = __builtin_amdgcn_readlane(cnt_l, ch);
+                const uint32_t first = __builtin_amdgcn_readlane(first_l, ch);
+                for (uint32_t i = 64 + lane; i < c; i += 64)
+                    add_key(l, bin1, cand[first + i] & 0x7FFFFFFFu);
+            }
+        }
+        finish(l, sd.k, se, (sd.sc_start + n_sc - 1) / span - sd.sc_start / span + 1);
+    }
+
+    // ---- dense route
+    if (!any_dense_route(segs, sel, L)) return;
+    for (uint32_t l = 0; l < L; ++l) {
+        const SegDev sd = segs[l];
+        if (!on_dense_route(sd, sel, l)) continue;
+        const SelDev se = sel[l];
+        if (!se.need2) continue;
+        const uint32_t bin1 = se.bin1;
+        const char *base = rv.src() + sd.offset * 4;
+        const uint32_t nvec = (sd.n + 3) / 4;
+        for (uint32_t v = blockIdx.x * 256 + tid; v < nvec; v += gridDim.x * 256) {
+            const uint4 q = load_vec<kF32>(base, 4 * v, sd.n);
+            add_key(l, bin1, q.x & 0x7FFFFFFFu);
+            add_key(l, bin1, q.y & 0x7FFFFFFFu);
+            add_key(l, bin1, q.z & 0x7FFFFFFFu);
+            add_key(l, bin1, q.w & 0x7FFFFFFFu);
+        }
+        finish(l, sd.k, se, gridDim.x);
+    }
+}
+
+// ---------------------------------------------------------- ordered output
+
+// Ordered output (the candidate route's super-chunks, the dense route's tiles) takes two
+// launches and no waiting.  `count` leaves, per item, count(key > T) << 31 | count(key == T);
+// `place` starts when all of them are there: every item adds up the counts of the earlier
+// items of its segment by itself (a few hundred to a few thousand words from the L2) and puts
+// its survivors where they belong.  No workgroup ever depends on another one's progress, so
+// neither the order in which the device starts them nor other kernels in flight matter.
 
 // pairs segment i emits, as the selection left it (segments that keep nothing have none)
 __device__ inline uint32_t segment_count(const SegDev &sd, const SelDev *sel, uint32_t i)
@@ -2368,18 +2436,10 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
     static int occ_place[2][2] = {{0, 0}, {0, 0}};
     auto per_rank = [&](uint32_t total) { return std::max(1u, total / n); };
     if (DTYPE == kF32 && (p->any_fast || p->span_dense)) {
-        {
-            ProfileScope ps("hist2c", s);
-            hist2c_kernel<<<dim3(per_rank(cus * 4), n), 256, 0, s>>>(sb, table, wl, p->cand_cap);
-        }
-        {
-            ProfileScope ps("hist2", s);
-            hist2_kernel<<<dim3(per_rank(cus * 8), n), 256, 0, s>>>(sb, table, wl);
-        }
-        {
-            ProfileScope ps("select2", s);
-            select2_kernel<<<dim3(L, n), kHistThreads, 0, s>>>(sb, table, wl);
-        }
+        // four super-chunks (a wave each) to a workgroup, no more of them than fit the device
+        ProfileScope ps("refine", s);
+        const uint32_t grid = std::min(per_rank(cus * 8), std::max(1u, (p->total_sc + 3) / 4));
+        refine_kernel<<<dim3(grid, n), 256, 0, s>>>(sb, table, wl, p->cand_cap);
     }
     {
         // the plan fixed the compaction tile's height, and with it which kernels these are
