@@ -1807,6 +1807,9 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
     if (PLACE && lane < CH_WORDS) wbits[wave][lane] = 0;  // (no other wave touches this row)
 
     for (uint32_t sc = bid * NWV + wave; sc < total_sc; sc += nb * NWV) {  // wave-uniform
+        // count and first slot of chunk `lane` (only meaningful for a chunk the scan has seen),
+        // requested together with the tables above
+        const uint2 info = lane < NCH ? chunk_info[sc * NCH + lane] : make_uint2(0, 0);
         // ---- segment, threshold, pair offset of the segment
         uint32_t l, c_off, n_seg, sc_first, T, quota, seg_base, se_cnt, se_route;
         if (L <= 64) {
@@ -1841,7 +1844,6 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
         if (lane < NCH) {
             inseg_l = live && sc_rel0 + lane * CHUNK < n_seg;
             if (inseg_l && se_cnt != 0) {
-                const uint2 info = chunk_info[sc * NCH + lane];
                 cnt_l = min(info.x, CAP);
                 first_l = min(info.y, uint32_t(n_slots_total) - CAP);
             }
@@ -1887,9 +1889,16 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
         uint32_t gb = 0, eb = 0;  // entries above / at the threshold before the current slot
         if (PLACE) {
             // prefix over the segment's earlier super-chunks, whose counts are all there
+            // (eight requests at a time; a tenth kept on 202 M entries, 2 ranks: 163 -> 141 us)
             uint64_t sum = 0;
             if (live)
-                for (uint32_t j = sc_first + lane; j < sc; j += 64) sum += sc_cnt[j];
+                for (uint32_t j = sc_first + lane; j < sc; j += 8 * 64) {
+                    uint64_t c[8];
+#pragma unroll
+                    for (uint32_t i = 0; i < 8; ++i) c[i] = j + 64 * i < sc ? sc_cnt[j + 64 * i] : 0ull;
+#pragma unroll
+                    for (uint32_t i = 0; i < 8; ++i) sum += c[i];
+                }
             sum = wave_sum<uint64_t>(sum);
             gb = uint32_t(sum >> 31);
             eb = uint32_t(sum & 0x7FFFFFFFu);
