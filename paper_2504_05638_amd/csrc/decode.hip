@@ -336,6 +336,7 @@ struct IndexView {
 template <uint32_t NW, uint32_t kPre>
 struct PartIndex {
     uint32_t lo, hi;        // the partition's c-indices
+    uint32_t g_end;         // behind its last group; 0 if it has no unknowns, and so no groups
     uint32_t word[kPre];    // word `lane` of the wave's groups
     uint32_t before;        // lane i: set bits of the whole Index before the i-th of them
 
@@ -343,7 +344,7 @@ struct PartIndex {
     __device__ __forceinline__ uint32_t load(const IndexView &v, uint32_t g) const
     {
         const uint32_t w = g * kGroupWords + lane_id();
-        return g <= (hi - 1) / (32 * kGroupWords) && w < v.n_words ? v.bitmap[w] : 0u;
+        return g < g_end && w < v.n_words ? v.bitmap[w] : 0u;
     }
     __device__ __forceinline__ static uint32_t bits_before(const IndexView &v, uint32_t g)
     {
@@ -353,11 +354,15 @@ struct PartIndex {
     {
         lo = v.bounds[a];
         hi = v.bounds[a + 1];
+        // (lo == hi where partitions outnumber the non-zeros, and both are 0 if c-index 0 is one;
+        // no group lies behind the Index whatever the bounds hold)
+        g_end = lo < hi ? min((hi - 1) / (32 * kGroupWords) + 1, (v.n_words + kGroupWords - 1) / kGroupWords)
+                        : 0u;
         const uint32_t g0 = lo / (32 * kGroupWords) + wave;
 #pragma unroll
         for (uint32_t i = 0; i < kPre; ++i) word[i] = load(v, g0 + i * NW);
         const uint32_t gl = g0 + lane_id() * NW;
-        before = lane_id() < kPre && gl * kGroupWords < v.n_words ? bits_before(v, gl) : 0u;
+        before = lane_id() < kPre && gl < g_end ? bits_before(v, gl) : 0u;
     }
     // word `lane` of group g, with `pre` set bits before the group: its unknowns' c-indices
     __device__ __forceinline__ void expand(uint32_t *out, uint32_t n, uint32_t rho0, uint32_t g,
@@ -380,21 +385,21 @@ struct PartIndex {
     __device__ __forceinline__ void enumerate(const IndexView &v, uint32_t *out, uint32_t n,
                                               uint32_t rho0, uint32_t wave) const
     {
-        const uint32_t g0 = lo / (32 * kGroupWords) + wave, g1 = (hi - 1) / (32 * kGroupWords);
+        const uint32_t g0 = lo / (32 * kGroupWords) + wave;
 #pragma unroll
         for (uint32_t i = 0; i < kPre; ++i)
-            if (g0 + i * NW <= g1)
+            if (g0 + i * NW < g_end)
                 expand(out, n, rho0, g0 + i * NW, word[i], __builtin_amdgcn_readlane(before, i));
-        for (uint32_t g = g0 + kPre * NW; g <= g1; g += 4 * NW) {
+        for (uint32_t g = g0 + kPre * NW; g < g_end; g += 4 * NW) {
             uint32_t w[4], pre[4];
 #pragma unroll
             for (uint32_t i = 0; i < 4; ++i) {
                 w[i] = load(v, g + i * NW);
-                pre[i] = g + i * NW <= g1 ? bits_before(v, g + i * NW) : 0u;
+                pre[i] = g + i * NW < g_end ? bits_before(v, g + i * NW) : 0u;
             }
 #pragma unroll
             for (uint32_t i = 0; i < 4; ++i)
-                if (g + i * NW <= g1) expand(out, n, rho0, g + i * NW, w[i], pre[i]);
+                if (g + i * NW < g_end) expand(out, n, rho0, g + i * NW, w[i], pre[i]);
         }
     }
 };
