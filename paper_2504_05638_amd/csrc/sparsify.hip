@@ -1890,15 +1890,19 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
         uint32_t gb = 0, eb = 0;  // entries above / at the threshold before the current slot
         if (PLACE) {
             // prefix over the segment's earlier super-chunks, whose counts are all there
-            // (eight requests at a time; a tenth kept on 202 M entries, 2 ranks: 163 -> 141 us)
+            // (eight requests at a time; a tenth kept on 202 M entries, 2 ranks: 163 -> 141 us.
+            // fp32 slots are two words each, and beside those in flight there is room for two
+            // requests: with eight, 24 registers went to scratch memory.  2 ranks, a tenth of 67 M
+            // kept, then a hundredth of 202 M: 103 -> 87 us, 66 -> 56)
+            constexpr uint32_t PRE = DTYPE == kBF16 ? 8 : 2;
             uint64_t sum = 0;
             if (live)
-                for (uint32_t j = sc_first + lane; j < sc; j += 8 * 64) {
-                    uint64_t c[8];
+                for (uint32_t j = sc_first + lane; j < sc; j += PRE * 64) {
+                    uint64_t c[PRE];
 #pragma unroll
-                    for (uint32_t i = 0; i < 8; ++i) c[i] = j + 64 * i < sc ? sc_cnt[j + 64 * i] : 0ull;
+                    for (uint32_t i = 0; i < PRE; ++i) c[i] = j + 64 * i < sc ? sc_cnt[j + 64 * i] : 0ull;
 #pragma unroll
-                    for (uint32_t i = 0; i < 8; ++i) sum += c[i];
+                    for (uint32_t i = 0; i < PRE; ++i) sum += c[i];
                 }
             sum = wave_sum<uint64_t>(sum);
             gb = uint32_t(sum >> 31);
