@@ -29,7 +29,7 @@ STAGES = {
     "S3a index OR": ["index_or", "layout"],
     "S2' encode": ["encode"],
     "S3b sketch sum": ["sketch_sum"],
-    "S4 decode": ["peel", "dense"],
+    "S4 decode": ["enumerate", "peel", "dense"],
 }
 FUSED_STAGE = "S3b+S4 sketch sum inside decode"
 
@@ -39,7 +39,7 @@ def stages_of(fused):
     if not fused:
         return STAGES
     st = {k: v for k, v in STAGES.items() if k not in ("S3b sketch sum", "S4 decode")}
-    st[FUSED_STAGE] = ["sum_peel", "dense"]
+    st[FUSED_STAGE] = ["enumerate", "sum_peel", "dense"]
     return st
 
 

@@ -324,15 +324,59 @@ struct IndexView {
     const uint32_t *chunkpre;   // set bits before every chunk
     const uint16_t *grouppre;   // ... and from there before every group of 64 words
     const uint32_t *bounds;     // first c-index of every partition
-    uint32_t n_words;
+    uint32_t n_words, n_chunks;
+    const uint32_t *list;       // kListed: its set bits, ascending (the caller's idx_out)
 };
+
+// Enumerates the set bits of the merged Index in ascending order into idx_out, for the kListed
+// forms of the decoder.  One workgroup per 1024-word chunk; chunkpre[] (written by the Index
+// aggregation) holds the number of set bits before each chunk, so workgroups are independent.  A
+// thread's indices are consecutive in the output but a wave's stores, taken entry by entry, would
+// hit 64 different cache lines each; so the chunk's first kEnumStage indices are gathered
+// in LDS and leave as contiguous stores.
+constexpr uint32_t kEnumStage = 8192;
+
+__global__ void __launch_bounds__(256)
+enumerate_kernel(const IndexView index, const uint32_t *__restrict__ header,
+                 uint32_t *__restrict__ idx_out)
+{
+    __shared__ uint32_t scratch[8];
+    __shared__ uint32_t stage[kEnumStage];
+    const uint32_t U = header[TAGC_HDR_U];
+    const uint32_t w0 = blockIdx.x * kChunkWords + threadIdx.x * 4;
+    uint32_t w[4] = {0, 0, 0, 0};
+    if (w0 + 4 <= index.n_words) {
+        const uint4 q = *reinterpret_cast<const uint4 *>(index.bitmap + w0);
+        w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
+    } else {
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) w[i] = w0 + i < index.n_words ? index.bitmap[w0 + i] : 0u;
+    }
+    const uint32_t mine = __popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]);
+    uint32_t tot;
+    const uint32_t base = index.chunkpre[blockIdx.x];
+    uint32_t pl = block_excl_scan<uint32_t, 4>(mine, &tot, scratch);  // position in the chunk
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+        for (uint32_t word = w[i]; word; word &= word - 1) {
+            const uint32_t v = (w0 + i) * 32 + uint32_t(__builtin_ctz(word));
+            if (pl < kEnumStage) stage[pl] = v;
+            else if (base + pl < U) idx_out[base + pl] = v;
+            ++pl;
+        }
+    }
+    __syncthreads();
+    const uint32_t n = min(tot, kEnumStage);
+    for (uint32_t i = threadIdx.x; i < n; i += 256)
+        if (base + i < U) idx_out[base + i] = stage[i];
+}
 
 // The unknowns of a partition are the set bits of the merged Index from bounds[a] on, numbered as
 // they come.  A wave turns the Index into unknowns by groups of 64 words, one per lane; since the
 // set bits before every group are known, groups are independent of each other.  The kPre groups
 // that a wave has of nearly every partition are requested a partition ahead.  (As a kernel of its
-// own, whose output the decoder read back, this took 5 us on small buckets and 43 to 53 on those of
-// 7 to 38 M unknowns.)
+// own, whose output the decoder reads back, this takes 5 us on small buckets and 43 to 53 on those of
+// 7 to 38 M unknowns; it is left to one where little is set, see launch_decode.)
 template <uint32_t NW, uint32_t kPre>
 struct PartIndex {
     uint32_t lo, hi;        // the partition's c-indices
@@ -340,6 +384,7 @@ struct PartIndex {
     uint32_t word[kPre];    // word `lane` of the wave's groups
     uint32_t before;        // lane i: set bits of the whole Index before the i-th of them
 
+    static constexpr uint32_t kTail = 8;
     static_assert(kPre <= 64, "a lane per group");
     __device__ __forceinline__ uint32_t load(const IndexView &v, uint32_t g) const
     {
@@ -348,7 +393,7 @@ struct PartIndex {
     }
     __device__ __forceinline__ static uint32_t bits_before(const IndexView &v, uint32_t g)
     {
-        return v.chunkpre[g / 16] + v.grouppre[g];
+        return v.chunkpre[g / 16] + (g < v.n_chunks * 16 ? v.grouppre[g] : 0u);
     }
     __device__ __forceinline__ void request(const IndexView &v, uint32_t a, uint32_t wave)
     {
@@ -390,16 +435,51 @@ struct PartIndex {
         for (uint32_t i = 0; i < kPre; ++i)
             if (g0 + i * NW < g_end)
                 expand(out, n, rho0, g0 + i * NW, word[i], __builtin_amdgcn_readlane(before, i));
-        for (uint32_t g = g0 + kPre * NW; g < g_end; g += 4 * NW) {
-            uint32_t w[4], pre[4];
+        // The rest (partitions of far fewer unknowns than the plan has room for), 64 of the wave's
+        // groups at a time, a lane finding out what lies before each and whether it holds anything:
+        // kTail of those that do are on their way together.  (Four at a time, holding anything or
+        // not: 10 partitions of 20 M positions 329 us, 189 in this form; 16 at a time 190.)
+        for (uint32_t gb = g0 + kPre * NW; gb < g_end; gb += 64 * NW) {
+            const uint32_t gl = gb + lane_id() * NW;
+            const uint32_t at = gl < g_end ? bits_before(v, gl) : 0u;
+            const uint32_t behind = gl < g_end ? bits_before(v, gl + 1) : 0u;
+            for (uint64_t some = __ballot(behind != at); some;) {
+                uint32_t w[kTail], i[kTail];
 #pragma unroll
-            for (uint32_t i = 0; i < 4; ++i) {
-                w[i] = load(v, g + i * NW);
-                pre[i] = g + i * NW < g_end ? bits_before(v, g + i * NW) : 0u;
+                for (uint32_t k = 0; k < kTail; ++k) {
+                    i[k] = some ? uint32_t(__builtin_ctzll(some)) : 64u;
+                    some &= some - 1;
+                    w[k] = i[k] < 64 ? load(v, gb + i[k] * NW) : 0u;
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < kTail; ++k)
+                    if (i[k] < 64)
+                        expand(out, n, rho0, gb + i[k] * NW, w[k], __builtin_amdgcn_readlane(at, i[k]));
             }
+        }
+    }
+};
+
+// A partition's unknowns where they have been listed: requested a partition ahead as well.
+template <uint32_t NT, uint32_t kIdx>
+struct PartList {
+    uint32_t idx[kIdx];
+
+    // n c-indices from `list` on
+    __device__ __forceinline__ void request(const uint32_t *list, uint32_t n, uint32_t tid)
+    {
 #pragma unroll
-            for (uint32_t i = 0; i < 4; ++i)
-                if (g + i * NW < g_end) expand(out, n, rho0, g + i * NW, w[i], pre[i]);
+        for (uint32_t q = 0; q < kIdx; ++q) {
+            const uint32_t u = tid + q * NT;
+            idx[q] = u < n ? __builtin_nontemporal_load(list + u) : 0u;
+        }
+    }
+    __device__ __forceinline__ void put(uint32_t *out, uint32_t n, uint32_t tid) const
+    {
+#pragma unroll
+        for (uint32_t q = 0; q < kIdx; ++q) {
+            const uint32_t u = tid + q * NT;
+            if (u < n) out[u] = idx[q];
         }
     }
 };
@@ -418,8 +498,8 @@ __device__ __forceinline__ GlobalCells rank_sketch(uint32_t r)
 }
 
 // The partition's unknowns, whose c-indices are in part.word, join their cells; all values start
-// at 0.  Writes the c-indices out on the way.
-template <uint32_t NT, uint32_t kIdx, bool kPacked>
+// at 0.  Writes the c-indices out on the way, unless kListed (they are there already).
+template <uint32_t NT, uint32_t kIdx, bool kListed, bool kPacked>
 __device__ __forceinline__ void join_cells(const PartLds<kPacked> &part, uint32_t tid, uint32_t n,
                                            uint32_t *idx_out)
 {
@@ -428,7 +508,7 @@ __device__ __forceinline__ void join_cells(const PartLds<kPacked> &part, uint32_
         const uint32_t u = tid + q * NT;
         if (u < n) {
             const uint32_t i = part.word[u];
-            idx_out[u] = i;
+            if (!kListed) idx_out[u] = i;
             const Cells cl = part.place(u, i);
 #pragma unroll
             for (int j = 0; j < 3; ++j) atomicAdd(part.meta(cl.c[j]), (u << 15) + 1u);
@@ -451,7 +531,9 @@ __device__ __forceinline__ void join_cells(const PartLds<kPacked> &part, uint32_
 // sum_peel_kernel has it (239 partitions of 8 ranks: 48 us, 52 in that kernel).
 constexpr uint32_t kIndexPre = 6;  // groups of Index words a wave requests ahead
 constexpr uint32_t kHeldRanks = 4;  // kRanks of the form for few ranks
-template <uint32_t kCellPre, uint32_t kIdxPre, bool kPacked, uint32_t kRanks, bool kLoop>
+constexpr uint32_t kListGroups = 256;  // groups of Index words per partition beyond which its unknowns are listed first
+// kListed: the unknowns are in index.list.
+template <uint32_t kCellPre, uint32_t kIdxPre, bool kPacked, uint32_t kRanks, bool kLoop, bool kListed>
 __global__ void __launch_bounds__(kDecodeThreads)
 peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t *__restrict__ header,
             uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
@@ -468,9 +550,11 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     const uint32_t cells = 3 * m_sub;
     part.m_sub = m_sub;
 
-    // the cells and Index words of partition `p` into registers (zeros beyond their ends)
+    // the cells and Index words (or unknowns) of partition `p` into registers (zeros beyond their
+    // ends)
     float pre_cell[kRanks][kCellPre];
     PartIndex<kDecodeThreads / 64, kIndexPre> pre_index;
+    PartList<kDecodeThreads, kIdxPre> pre_list;
     auto request_cells = [&](float (&v)[kCellPre], uint32_t r, uint64_t tile) {
         const GlobalCells src = rank_sketch(r) + tile;
 #pragma unroll
@@ -488,7 +572,12 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
                 for (uint32_t q = 0; q < kCellPre; ++q) pre_cell[0][q] += pre_cell[i][q];
     };
     auto prefetch = [&](uint32_t p) {
-        pre_index.request(index, p, wave);
+        if (kListed) {
+            const uint32_t r0 = uint32_t(uint64_t(p) * U / A);
+            pre_list.request(index.list + r0, uint32_t(uint64_t(p + 1) * U / A) - r0, tid);
+        } else {
+            pre_index.request(index, p, wave);
+        }
         const uint64_t tile = uint64_t(p) * cells;
 #pragma unroll
         for (uint32_t i = 0; i < kRanks; ++i)
@@ -522,7 +611,8 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     // ---- stage the partition's cells and unknowns from the registers, clear state
     for (uint32_t c = tid; c < P_cap / 32 + 1; c += kDecodeThreads) part.claimed[c] = 0;
     if (tid < 3) s_n[tid] = 0;
-    pre_index.enumerate(index, part.word, Pa, rho0, wave);
+    if (kListed) pre_list.put(part.word, Pa, tid);
+    else pre_index.enumerate(index, part.word, Pa, rho0, wave);
     add_cells(1, n_in);
 #pragma unroll
     for (uint32_t q = 0; q < kCellPre; ++q) {
@@ -532,7 +622,7 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     __syncthreads();
     PHASE_MARK(0);
 
-    join_cells<kDecodeThreads, kIdxPre>(part, tid, Pa, idx_out + rho0);
+    join_cells<kDecodeThreads, kIdxPre, kListed>(part, tid, Pa, idx_out + rho0);
     // the registers are free again: the next partition's data travels during the rounds
     if (a + gridDim.x < A) prefetch(a + gridDim.x);
     __syncthreads();
@@ -590,6 +680,7 @@ __device__ inline void peel_barrier(uint32_t *word, uint32_t &expected)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+template <bool kListed>
 __global__ void __launch_bounds__(kDecodeThreads)
 sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
                 const uint32_t *__restrict__ header, uint32_t *__restrict__ idx_out,
@@ -672,7 +763,16 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
     // ---------------------------------------------------------------- the peelers
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     PartIndex<kPeelWaves, kIndexPre> pre_index;
-    if (blockIdx.x < A) pre_index.request(index, blockIdx.x, wave);
+    PartList<kPeelThreads, kPeelIdx> pre_list;
+    auto prefetch = [&](uint32_t p) {
+        if (kListed) {
+            const uint32_t r0 = uint32_t(uint64_t(p) * U / A);
+            pre_list.request(index.list + r0, uint32_t(uint64_t(p + 1) * U / A) - r0, tid);
+        } else {
+            pre_index.request(index, p, wave);
+        }
+    };
+    if (blockIdx.x < A) prefetch(blockIdx.x);
     uint32_t bar_expected = 0, max_rounds = 0;
     part.m_sub = m_sub;
     for (uint32_t a = blockIdx.x; a < A; a += gridDim.x) {
@@ -688,10 +788,11 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
         __syncthreads();  // the loaders have staged the cells
 
         // (here and not before the barriers, where the loaders would wait for it)
-        pre_index.enumerate(index, part.word, Pa, rho0, wave);
+        if (kListed) pre_list.put(part.word, Pa, tid);
+        else pre_index.enumerate(index, part.word, Pa, rho0, wave);
         peel_barrier(&s_bar, bar_expected);
-        join_cells<kPeelThreads, kPeelIdx>(part, tid, Pa, idx_out + rho0);
-        if (a + gridDim.x < A) pre_index.request(index, a + gridDim.x, wave);
+        join_cells<kPeelThreads, kPeelIdx, kListed>(part, tid, Pa, idx_out + rho0);
+        if (a + gridDim.x < A) prefetch(a + gridDim.x);
         peel_barrier(&s_bar, bar_expected);
         if (mode != TAGC_DECODE_ESTIMATE)
             queue_first<kPeelThreads, kPeelSlots>(part, tid, &s_n[1],
@@ -783,7 +884,7 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     const uint32_t n_chunks = uint32_t(p->n_chunks);
     const uint32_t *chunkpre = static_cast<const uint32_t *>(sh->workspace);
     const IndexView index{sh->bitmap, chunkpre, group_prefixes(sh->workspace, n_chunks), sh->bounds,
-                          n_words};
+                          n_words, n_chunks, idx_out};
     const size_t lds = decode_lds_bytes(p->T_cap, p->P_cap);
     // a workgroup takes partitions b, b + grid, ...: any grid size gives the same result
     uint32_t grid = uint32_t(std::min<uint64_t>(p->A_cap, uint64_t(device_cu_count())));
@@ -800,25 +901,40 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     constexpr uint32_t kI0 = (kDefaultPartUnknowns + kDecodeThreads - 1) / kDecodeThreads;
     constexpr uint32_t kC1 = (kMaxPartCells + kDecodeThreads - 1) / kDecodeThreads;
     constexpr uint32_t kI1 = (kMaxPartUnknowns + kDecodeThreads - 1) / kDecodeThreads;
+    // Partitions that span much of the Index, because little of it can be set: the one workgroup
+    // of a partition would go through all of that, most of the device having nothing to do, so a
+    // kernel over the whole Index lists the unknowns first.  Decoder alone, us, walking / listing
+    // (enumerate and peel): 202 M entries, 80 thousand unknowns in 10 partitions 189 / 44; 67 M in
+    // 110 partitions, 300 groups each, 42 / 41 (a pass 164 / 160); in 164, 200 groups, 40 / 44
+    // (162 / 163); 7 M in 99 partitions, 35 groups, 45 / 53.
+    const bool listed = 16ull * n_chunks > kListGroups * p->A_cap;
     // One summed sketch; up to four ranks; any number with a workgroup per partition; any number.
     // (Two ranks of 202 M entries, a tenth kept: 654 us with sixteen waves peeling, 696 in
     // sum_peel_kernel, of whose sixteen four sum; four ranks of 9 M, two fifths kept: 135 and 141.
     // More ranks' cells do not fit the registers beside the rounds.)
     const uint32_t form = !fused                  ? (packed_slots(p->T_cap, p->P_cap) ? 1u : 0u)
                           : n_ranks <= kHeldRanks ? 2u
-                          : grid == p->A_cap      ? 3u
+                          : grid == p->A_cap && !listed ? 3u
                                                   : 4u;
-    const auto kernel = form == 4   ? sum_peel_kernel
-                        : form == 3 ? peel_kernel<kC0, kI0, true, kHeldRanks, true>
-                        : form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false>
-                        : form == 1 ? peel_kernel<kC0, kI0, true, 1, false>
-                                    : peel_kernel<kC1, kI1, false, 1, false>;
-    static size_t attr_bytes[5] = {0, 0, 0, 0, 0};
-    if (lds > attr_bytes[form]) {
+    auto pick = [&](auto list) {
+        constexpr bool kList = decltype(list)::value;
+        return form == 4   ? sum_peel_kernel<kList>
+               : form == 3 ? peel_kernel<kC0, kI0, true, kHeldRanks, true, false>
+               : form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false, kList>
+               : form == 1 ? peel_kernel<kC0, kI0, true, 1, false, kList>
+                           : peel_kernel<kC1, kI1, false, 1, false, kList>;
+    };
+    const auto kernel = listed ? pick(std::true_type{}) : pick(std::false_type{});
+    static size_t attr_bytes[2][5] = {};
+    if (lds > attr_bytes[listed][form]) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
             return TAGC_EHIP;
-        attr_bytes[form] = lds;
+        attr_bytes[listed][form] = lds;
+    }
+    if (listed) {
+        ProfileScope ps("enumerate", s);
+        enumerate_kernel<<<n_chunks, 256, 0, s>>>(index, sh->header, idx_out);
     }
     {
         ProfileScope ps(fused ? "sum_peel" : "peel", s);

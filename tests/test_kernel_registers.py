@@ -12,7 +12,7 @@ from paper_2504_05638_amd import build
 
 _TOOLS = "/opt/rocm/llvm/bin"
 # the form of the decoder that sums any number of ranks as they come, outside its rounds
-_ALLOWED = {r"11peel_kernelILj12ELj8ELb1ELj4ELb1EE": 2}
+_ALLOWED = {r"11peel_kernelILj12ELj8ELb1ELj4ELb1ELb0EE": 2}
 
 
 def test_no_vector_register_spills(tmp_path):
