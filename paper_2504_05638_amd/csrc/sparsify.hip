@@ -1287,9 +1287,15 @@ __device__ inline uint32_t segment_of(uint32_t L, uint32_t t, F start)
 // from the spilled slots; the super-chunks of all segments form one list, a workgroup takes one
 // contiguous span of it and a wave a super-chunk at a time, whose chunks' slots are requested
 // kRefineBatch at a time (one chunk after the other, each a chain of two loads, this took 16 us on
-// 8 ranks of 7 M entries, and the two launches that followed 5 and 10; all of it now 14).
-// Dense route: from the gradient, by all workgroups.
+// 8 ranks of 7 M entries, and the two launches that followed 5 and 10; all of it now 14).  That list
+// is the first n_cand workgroups' work.
+// Dense route: from the gradient, by the first n_dense workgroups, kRefineRows vectors per thread at
+// a time.  Four workgroups per compute unit at most: each ends in up to 256 atomics on the same few
+// lines and an arrival.  (With as many workgroups as the candidate list asked for, and a vector at a
+// time, 2 ranks of 1 M entries took 82 us, 11 now; 4 ranks of 9 M 105, 44 now, with eight per
+// compute unit 61; one rank of 60 M 104, 63 now.)
 constexpr uint32_t kRefineBatch = 16;
+constexpr uint32_t kRefineRows = 4;
 
 // By a wave, of 256 counts: the largest b with sum_{x >= b} bins[x] >= want and the entries in
 // higher ones; kNoBin if all together hold fewer.
@@ -1317,7 +1323,8 @@ __device__ inline uint32_t top_of_256(const uint32_t *bins, uint32_t want, uint3
 }
 
 __global__ void __launch_bounds__(256)
-refine_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t CAP)
+refine_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t CAP, uint32_t n_cand,
+              uint32_t n_dense)
 {
     constexpr uint32_t CHUNK = 64 * 4 * kCandRows, NCH = kCandChunksPerSuper, NWV = 4;
     __shared__ uint32_t s_last, s_coarse[256];
@@ -1387,8 +1394,9 @@ refine_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t 
     };
 
     // ---- candidate route: super-chunks [s0, s1) of the list
-    const uint32_t span = (total_sc + gridDim.x - 1) / gridDim.x;
-    const uint32_t s0 = min(blockIdx.x * span, total_sc), s1 = min(s0 + span, total_sc);
+    const uint32_t span = (total_sc + n_cand - 1) / n_cand;
+    const uint32_t s0 = blockIdx.x < n_cand ? min(blockIdx.x * span, total_sc) : total_sc,
+                   s1 = min(s0 + span, total_sc);
     // (requested before anything is known of the segments: every link of the chain counts)
     auto info_of = [&](uint32_t sc) {
         return lane < NCH && sc < s1 ? chunk_info[sc * NCH + lane] : make_uint2(0, 0);
@@ -1441,7 +1449,7 @@ refine_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t 
     }
 
     // ---- dense route
-    if (!any_dense_route(segs, sel, L)) return;
+    if (blockIdx.x >= n_dense || !any_dense_route(segs, sel, L)) return;
     for (uint32_t l = 0; l < L; ++l) {
         const SegDev sd = segs[l];
         if (!on_dense_route(sd, sel, l)) continue;
@@ -1450,14 +1458,21 @@ refine_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t 
         const uint32_t bin1 = se.bin1;
         const char *base = rv.src() + sd.offset * 4;
         const uint32_t nvec = (sd.n + 3) / 4;
-        for (uint32_t v = blockIdx.x * 256 + tid; v < nvec; v += gridDim.x * 256) {
-            const uint4 q = load_vec<kF32>(base, 4 * v, sd.n);
-            add_key(l, bin1, q.x & 0x7FFFFFFFu);
-            add_key(l, bin1, q.y & 0x7FFFFFFFu);
-            add_key(l, bin1, q.z & 0x7FFFFFFFu);
-            add_key(l, bin1, q.w & 0x7FFFFFFFu);
+        const uint32_t stride = n_dense * 256;
+        for (uint32_t v = blockIdx.x * 256 + tid; v < nvec; v += kRefineRows * stride) {
+            uint4 q[kRefineRows];
+#pragma unroll
+            for (uint32_t r = 0; r < kRefineRows; ++r)
+                q[r] = load_vec<kF32>(base, 4 * min(v + r * stride, nvec), sd.n);
+#pragma unroll
+            for (uint32_t r = 0; r < kRefineRows; ++r) {
+                add_key(l, bin1, q[r].x & 0x7FFFFFFFu);
+                add_key(l, bin1, q[r].y & 0x7FFFFFFFu);
+                add_key(l, bin1, q[r].z & 0x7FFFFFFFu);
+                add_key(l, bin1, q[r].w & 0x7FFFFFFFu);
+            }
         }
-        finish(l, sd.k, se, gridDim.x);
+        finish(l, sd.k, se, n_dense);
     }
 }
 
@@ -2457,10 +2472,19 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
     static int occ_place[2][2] = {{0, 0}, {0, 0}};
     auto per_rank = [&](uint32_t total) { return std::max(1u, total / n); };
     if (DTYPE == kF32 && (p->any_fast || p->span_dense)) {
-        // four super-chunks (a wave each) to a workgroup, no more of them than fit the device
+        // candidate list: four super-chunks (a wave each) to a workgroup, no more of them than fit
+        // the device; dense route: a workgroup per kRefineRows vectors of its threads where the work
+        // is certain, a sixteenth of that for what may be re-routed (idle workgroups, which a
+        // bucket of 7 M entries on 8 ranks notices: with a quarter of it 3 us)
         ProfileScope ps("refine", s);
-        const uint32_t grid = std::min(per_rank(cus * 8), std::max(1u, (p->total_sc + 3) / 4));
-        refine_kernel<<<dim3(grid, n), 256, 0, s>>>(sb, table, wl, p->cand_cap);
+        const uint32_t n_cand = std::min(per_rank(cus * 8), std::max(1u, (p->total_sc + 3) / 4));
+        const uint64_t turn = 256 * 4 * kRefineRows;  // entries
+        const uint64_t dense = std::max((p->span_dense + turn - 1) / turn,
+                                        p->any_fast ? p->n_real / (16 * turn) : uint64_t(0));
+        const uint32_t n_dense = uint32_t(
+            std::min<uint64_t>(per_rank(cus * 4), std::max<uint64_t>(1, dense)));
+        const uint32_t grid = std::max(n_cand, n_dense);
+        refine_kernel<<<dim3(grid, n), 256, 0, s>>>(sb, table, wl, p->cand_cap, n_cand, n_dense);
     }
     {
         // the plan fixed the compaction tile's height, and with it which kernels these are
