@@ -74,7 +74,7 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
     // kernel it shares with the candidate route's last pass then needs few enough
     // registers for one more workgroup per CU.
     p->any_fast = p->small_dense = false;
-    p->span_dense = 0;
+    p->span_dense = p->dense_pairs = 0;
     for (uint32_t l = 0; l < n_seg; ++l) {
         const tagc_segment &s = segs[l];
         if (!(s.flags & TAGC_SEG_COMPRESS) || s.keep_ppm > 1000000u || s.length == 0) continue;
@@ -117,6 +117,7 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
             }
             if (d.n && !(d.flags & kSegFast)) p->any_nonfast = true;
             if (d.k && !(d.flags & kSegFast) && small(d.n)) d.flags |= kSegSmall;
+            if (!(d.flags & kSegFast)) p->dense_pairs += d.k;
             d.sc_start = uint32_t(scs);
             scs += ceil_div(s.length, uint64_t(p->chunk_elems) * kCandChunksPerSuper);
             p->table.push_back(d);

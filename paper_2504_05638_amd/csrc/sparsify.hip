@@ -1989,7 +1989,7 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
 // segments that keep nothing.  The segments the scan never reads have the first `plan_tiles`
 // tiles, one workgroup each; the workgroups behind take those of re-routed segments in turns.
 //
-// STAGED (a plan with dense-route segments): a tile's survivors are gathered in LDS and leave as
+// STAGED (a plan whose pairs come mostly from here): a tile's survivors are gathered in LDS and leave as
 // contiguous stores; entry by entry each store instruction would touch every cache line a
 // wave's part of the output covers (8.7 M entries of which two fifths are kept, 4 ranks: place
 // 78 us that way, 54 in this).
@@ -2253,13 +2253,12 @@ count_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles,
             rv.at<uint64_t>(wl.tile_cnt), rv.at<uint64_t>(wl.group_cnt), nullptr, nullptr, nullptr);
 }
 
-template <int DTYPE, uint32_t COMPACT_ROWS, bool WIDE>
+template <int DTYPE, uint32_t COMPACT_ROWS, bool WIDE, bool STAGED>
 __global__ void __launch_bounds__(kEmitThreads)
-    __attribute__((amdgpu_waves_per_eu(COMPACT_ROWS == 2 ? 7 : 6, 8)))
+    __attribute__((amdgpu_waves_per_eu(COMPACT_ROWS == 2 ? 7 : STAGED && DTYPE == kBF16 ? 4 : 6, 8)))
 place_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles, uint32_t *table,
              const WsLayout wl, uint32_t CAP)
 {
-    constexpr bool STAGED = COMPACT_ROWS == 4;
     union Lds {
         EmitLds<DTYPE> emit;
         CompactLds<DTYPE, STAGED> compact;
@@ -2469,7 +2468,7 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
     const WsLayout wl = ws_layout(p);
     const uint32_t L = uint32_t(p->table.size());
     const int cus = device_cu_count();
-    static int occ_place[2][2] = {{0, 0}, {0, 0}};
+    static int occ_place[2][3] = {};
     auto per_rank = [&](uint32_t total) { return std::max(1u, total / n); };
     if (DTYPE == kF32 && (p->any_fast || p->span_dense)) {
         // candidate list: four super-chunks (a wave each) to a workgroup, no more of them than fit
@@ -2492,9 +2491,19 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
         const bool rows4 = p->compact_rows == 4, wd = p->emit_wide;
         auto count = wd ? (rows4 ? count_kernel<DTYPE, 4, true> : count_kernel<DTYPE, 2, true>)
                         : (rows4 ? count_kernel<DTYPE, 4, false> : count_kernel<DTYPE, 2, false>);
-        auto place = wd ? (rows4 ? place_kernel<DTYPE, 4, true> : place_kernel<DTYPE, 2, true>)
-                        : (rows4 ? place_kernel<DTYPE, 4, false> : place_kernel<DTYPE, 2, false>);
-        const int occ = resident_blocks_per_cu(place, kEmitThreads, 0, &occ_place[wd][rows4]);
+        // place stages the dense route's tiles where most pairs can come from them.  Beside large
+        // candidate-route segments a short one of the dense route would have every workgroup hold
+        // 33 KiB of LDS and 108 registers for it instead of 1 KiB and 76 (4 ranks of 202 M entries
+        // and 5 thousand: place 62 us staged, 55 not; 25 M and 9 M of which two fifths are kept:
+        // 71 and 92; 25 M and 1 M: 26 and 25).
+        const bool staged = rows4 && 2 * p->dense_pairs > p->K;
+        auto place = wd ? (staged  ? place_kernel<DTYPE, 4, true, true>
+                           : rows4 ? place_kernel<DTYPE, 4, true, false>
+                                   : place_kernel<DTYPE, 2, true, false>)
+                        : (staged  ? place_kernel<DTYPE, 4, false, true>
+                           : rows4 ? place_kernel<DTYPE, 4, false, false>
+                                   : place_kernel<DTYPE, 2, false, false>);
+        const int occ = resident_blocks_per_cu(place, kEmitThreads, 0, &occ_place[wd][rows4 + staged]);
         if (occ <= 0) return TAGC_EHIP;
         // emit_body: kEmitItems super-chunks per workgroup; emit_wide_body: one per wave
         const uint32_t per_wg = wd ? kEmitThreads / 64 : uint32_t(kEmitItems);

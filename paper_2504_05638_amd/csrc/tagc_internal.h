@@ -143,6 +143,7 @@ struct tagc_plan_s {
     bool any_fast;                            // some segment takes it
     bool small_dense;                         // some dense-route segment is kSegSmall
     uint64_t span_dense;                      // entries of the dense-route segments that are not
+    uint64_t dense_pairs;                     // pairs the dense-route segments emit at most
     bool emit_wide;                           // chunks hold hundreds of candidates: a wave per super-chunk in count / place
     uint64_t n_real, n_c, K, U_cap, A_cap, m_cap;
     uint32_t P_cap, T_cap;
