@@ -23,16 +23,19 @@ def _bytes(n, device):
 
 
 class TagcBucket:
-    """One gradient bucket: plan + device buffers for `n_ranks` simulated ranks."""
+    """One gradient bucket: plan + device buffers for `n_ranks` simulated ranks.
 
-    _WORKSPACES_BYTES = 4 << 30
+    Ranks with workspaces of their own share the sparsifier's launches.  `ranks_together`: how
+    many have one (each is rank_workspace_bytes of device memory); 0 = as many as fit a GiB."""
+
+    _WORKSPACES_BYTES = 1 << 30
 
     def __init__(self, segments, dtype, n_ranks, sizing_milli=3000,
                  sizing=B.TAGC_SIZE_LOAD_FACTOR, seed=0, part_unknowns=0,
                  part_cells=0, device="cuda", dense=False, share=None, min_bytes=None,
                  error_feedback=False, decode_mode=B.TAGC_DECODE_PEEL,
                  index_mode=B.TAGC_INDEX_OR1, cell_type=B.TAGC_CELL_F32,
-                 decode_workgroups=0):
+                 decode_workgroups=0, ranks_together=0):
         if not torch.cuda.is_available():
             raise RuntimeError("libtagc needs a GPU: no CPU path exists")
         self.device = torch.device(device)
@@ -72,10 +75,11 @@ class TagcBucket:
             self.sh_sketch.data_ptr(), self.sh_header.data_ptr(),
             self.sh_bounds.data_ptr(), self.sh_ws.data_ptr(),
             self.sh_status.data_ptr())
-        # a workspace per rank, so that the ranks' sparsifiers share their launches; large buckets
-        # fill the device with fewer ranks at a time, and get no more than a few GiB of them
-        # (ranks that share one are sparsified one after the other)
-        n_ws = max(1, min(n_ranks, 32, self._WORKSPACES_BYTES // max(int(z.rank_workspace_bytes), 1)))
+        # (ranks that share one are sparsified one after the other; a large bucket fills the device
+        # with few of them anyway: 16 ranks of 202 M entries, 40 MB each, 3186 us with one each
+        # and 3415 with one for all)
+        n_ws = self._workspaces(n_ranks, max(int(z.rank_workspace_bytes),
+                                             int(self._min_bytes.get("rank_ws", 0))), ranks_together)
         self.rank_ws = [al("rank_ws%d" % i, z.rank_workspace_bytes) for i in range(n_ws)]
         self.rk = (B.tagc_rank_buffers * n_ranks)()
         self._rk_tensors = []
@@ -103,6 +107,14 @@ class TagcBucket:
         self.out_dense = al("out_dense", z.out_dense_bytes) if dense else None
         B.tagc_plan_upload(self.plan, self.table.data_ptr(), _stream_ptr())
         torch.cuda.current_stream().synchronize()
+
+    @classmethod
+    def _workspaces(cls, n_ranks, nbytes, ranks_together):
+        """How many workspaces of `nbytes` the bucket has."""
+        if ranks_together < 0:
+            raise ValueError("ranks_together is a number of ranks, or 0")
+        most = min(n_ranks, 32)
+        return min(most, ranks_together) or max(1, min(most, cls._WORKSPACES_BYTES // max(nbytes, 1)))
 
     def _alloc(self, name, nbytes):
         """A device buffer of at least nbytes; taken from `share` (another bucket that
