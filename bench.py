@@ -89,6 +89,10 @@ def parse_args():
     ap.add_argument("--dense", type=int, default=1, help="also write the dense summed gradient")
     ap.add_argument("--buckets", type=int, default=0,
                     help="only the first B buckets of the workload (0 = all; for experiments)")
+    ap.add_argument("--ranks-together", type=int, default=-1,
+                    help="ranks whose sparsifier work shares launches (0: as many as fit TagcBucket's "
+                         "limit; default: 1 with several buckets in flight of which a rank's part "
+                         "alone fills the device, else 0)")
     ap.add_argument("--lanes", type=int, default=12,
                     help="buckets in flight at once: bucket i runs on HIP stream i %% lanes with "
                          "that lane's own buffers (buckets are independent of each other)")
@@ -334,6 +338,7 @@ def main():
               "sketch": "rank_sketch_bytes", "out_idx": "out_idx_bytes",
               "out_val": "out_val_bytes", "out_dense": "out_dense_bytes"}
     need = {k: 0 for k in fields}
+    plan_bytes = []  # of the compressed segments, per rank
     sizing = B.TAGC_SIZE_FIXED_RATIO if args.ratio else B.TAGC_SIZE_LOAD_FACTOR
     for b in buckets:
         cfg = B.tagc_config(dtype=b.dtype, n_ranks=N, n_hash=3, sizing=sizing,
@@ -343,6 +348,7 @@ def main():
                             cell_type=int(args.cell_bits == 16))
         plan = B.tagc_plan(cfg, [tuple(s[:4]) for s in b.segments])
         z = B.tagc_plan_sizes(plan)
+        plan_bytes.append(z.n_real * b.elem_bytes)
         for k, f in fields.items():
             need[k] = max(need[k], getattr(z, f))
         B.tagc_plan_destroy(plan)
@@ -352,6 +358,13 @@ def main():
     if args.decode_workgroups < 0:
         args.decode_workgroups = 96 if fused else 64
     peel_wgs = args.decode_workgroups if lanes > 1 else 0
+    if args.ranks_together < 0:
+        # One rank of a 7B block (405 MB) is 80 us of streaming; its launches overlap better with
+        # other buckets' when they are its own: 2327 to 2341 GB/s, 2260 to 2295 with 16 ranks to a
+        # launch.  Not of smaller buckets: GPT-2 blocks (28 MB a rank) 1053 with launches of their
+        # own, 1877 with shared ones, shards of 7B blocks (51 MB) 1737 and 2189.
+        big = min(plan_bytes) >= 256 << 20
+        args.ranks_together = 1 if lanes > 1 and big else 0
     tbs = []
     for i, b in enumerate(buckets):
         first = i < lanes  # a lane's first bucket owns the buffers the lane's others reuse
@@ -362,6 +375,7 @@ def main():
                               decode_mode=args.decode_mode, index_mode=args.index_mode,
                               sizing=sizing, cell_type=int(args.cell_bits == 16),
                               decode_workgroups=peel_wgs,
+                              ranks_together=args.ranks_together,
                               share=None if first else tbs[i % lanes],
                               min_bytes=need if first else None))
     stream = torch.cuda.current_stream()
@@ -608,6 +622,7 @@ def main():
                                   "sparse+dense output" if args.dense else "sparse output"),
                    "input_bytes_per_step": input_bytes, "distinct_bucket_data_sets": pool,
                    "buckets_in_flight": lanes, "decode_workgroups": peel_wgs,
+                   "ranks_together": args.ranks_together,
                    "host_issue_ms_per_step": round(1e3 * t_issue_step, 3),
                    "host_issue_total_ms_per_step": round(1e3 * t_issue / args.steps, 3),
                    "pairs_per_step": k_tot, "union_nonzeros_per_step": U_tot,
