@@ -2532,10 +2532,10 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
     return hip_ok(hipGetLastError());
 }
 
-// PHASE_INDEX of n ranks with workspaces and table slots (slot0 and following) of their own.
+// PHASE_INDEX of n ranks with workspaces and table slots (0 .. n-1) of their own.
 template <int DTYPE>
 int launch_sparsify_t(const tagc_plan_t *p, const void *const *grads, const tagc_rank_buffers *ranks,
-                      uint32_t n, uint32_t slot0, const tagc_shared_buffers *sh, hipStream_t s)
+                      uint32_t n, const tagc_shared_buffers *sh, hipStream_t s)
 {
     const uint32_t L = uint32_t(p->table.size());
     // the table is the plan's device state as well (pre-thresholds, counters): written here
@@ -2566,7 +2566,7 @@ int launch_sparsify_t(const tagc_plan_t *p, const void *const *grads, const tagc
         // A rank whose slot of the table's state has not been used since the upload starts
         // from the pre-thresholds of the rank before it (slot 0: from a sample), so it has
         // to wait for those: one launch of the first kernels each, just this once.
-        const uint32_t slot = (slot0 + r) % p->slots, bit = 1u << slot;
+        const uint32_t slot = r, bit = 1u << slot;
         const bool fresh = !(p->used.fetch_or(bit, std::memory_order_relaxed) & bit);
         if (fresh)
             if (const int rc = select()) return rc;
@@ -2611,8 +2611,8 @@ int launch_sparsify(const tagc_plan_t *p, const void *const *grads, const tagc_r
         };
         while (r0 + n < n_ranks && n < p->slots && joins(r0 + n)) ++n;
         const int rc = p->cfg.dtype == TAGC_BF16
-                           ? launch_sparsify_t<kBF16>(p, grads + r0, ranks + r0, n, r0, sh, s)
-                           : launch_sparsify_t<kF32>(p, grads + r0, ranks + r0, n, r0, sh, s);
+                           ? launch_sparsify_t<kBF16>(p, grads + r0, ranks + r0, n, sh, s)
+                           : launch_sparsify_t<kF32>(p, grads + r0, ranks + r0, n, sh, s);
         if (rc) return rc;
         r0 += n;
     }
