@@ -163,12 +163,14 @@ class TagcBucket:
                         self.shared, _stream_ptr(stream))
 
     def compress_index_all(self, grads, stream=None):
-        """compress_index of ranks 0 .. len(grads)-1, in the same launches."""
-        if not grads:
+        """compress_index of ranks 0 .. len(grads)-1, in the same launches.  `grads`: anything
+        that has a length and gives rank r's buffer for r (a list, a tensor with a row per rank)."""
+        if len(grads) == 0:
             return
         if len(grads) > self.n_ranks:
             raise ValueError("%d gradients, the bucket has buffers for %d ranks"
                              % (len(grads), self.n_ranks))
+        grads = [grads[r] for r in range(len(grads))]
         for g in grads:
             self._check_grad(g)
         B.tagc_compress_ranks(self.plan, B.TAGC_PHASE_INDEX, [g.data_ptr() for g in grads],

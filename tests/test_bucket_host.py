@@ -1,6 +1,10 @@
 """TagcBucket's and the binding's host side, without a device."""
-import pytest
+import types
 
+import pytest
+import torch
+
+from paper_2504_05638_amd import binding as B
 from paper_2504_05638_amd.bucket import TagcBucket
 
 
@@ -34,3 +38,61 @@ def test_ranks_together(together, min_bytes, want):
         tb.run([g.cuda() for g in grads])
         torch.cuda.synchronize()
         compare_all(b, ores, tb)
+
+
+class _Grad:
+    """Stands in for a gradient on the device."""
+    dtype, is_cuda = torch.float32, True
+
+    def __init__(self, at):
+        self.at = at
+
+    def data_ptr(self):
+        return self.at
+
+    def is_contiguous(self):
+        return True
+
+    def numel(self):
+        return 1000
+
+
+class _Stacked:
+    """A tensor with a row per rank, as far as a caller of run() can tell: it has a length and rows,
+    and no truth value."""
+    def __init__(self, rows):
+        self.rows = rows
+
+    def __len__(self):
+        return len(self.rows)
+
+    def __getitem__(self, r):
+        return self.rows[r]
+
+    def __bool__(self):
+        raise RuntimeError("Boolean value of Tensor with more than one value is ambiguous")
+
+
+def _bucket(n_ranks):
+    tb = TagcBucket.__new__(TagcBucket)
+    tb.plan = tb.plan_whole = tb.shared = None
+    tb.cfg, tb.n_ranks = B.tagc_config(dtype=B.TAGC_F32), n_ranks
+    tb.sizes = types.SimpleNamespace(grad_elems=1000)
+    tb.rk = (B.tagc_rank_buffers * n_ranks)()
+    return tb
+
+
+def test_rows_of_one_tensor_as_gradients(monkeypatch):
+    """run() takes whatever has a length and rank r's buffer at [r]."""
+    calls = []
+    monkeypatch.setattr(B, "tagc_compress_ranks",
+                        lambda plan, phase, grads, ranks, shared, stream, n: calls.append((grads, n)))
+    tb, stream = _bucket(3), types.SimpleNamespace(cuda_stream=0)
+    for kind in (list, tuple, _Stacked, lambda rows: dict(enumerate(rows))):
+        calls.clear()
+        tb.compress_index_all(kind([_Grad(256 * (r + 1)) for r in range(3)]), stream)
+        assert calls == [([256, 512, 768], 3)]
+    calls.clear()
+    tb.compress_index_all([], stream)
+    tb.compress_index_all(torch.empty(0, 1000), stream)
+    assert not calls
