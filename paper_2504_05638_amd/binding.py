@@ -205,9 +205,11 @@ def tagc_compress(plan, phase, grad_dev, rank: tagc_rank_buffers,
 def tagc_compress_ranks(plan, phase, grads_dev, ranks, shared: tagc_shared_buffers,
                         stream: int = 0, n_ranks=None):
     """tagc_compress for the first n_ranks (default: all) of `ranks`, in the same launches."""
-    n = len(ranks) if n_ranks is None else n_ranks
+    arr, n = _rank_array(ranks, n_ranks)
+    if grads_dev is not None and len(grads_dev) != n:
+        raise ValueError("%d gradients for %d ranks" % (len(grads_dev), n))
     grads = (C.c_void_p * n)(*grads_dev) if grads_dev is not None else None
-    _check(lib().tagc_compress_ranks(plan, phase, grads, _rank_array(ranks), n,
+    _check(lib().tagc_compress_ranks(plan, phase, grads, arr, n,
                                      C.byref(shared), stream), "tagc_compress_ranks")
 
 
@@ -224,15 +226,19 @@ def tagc_feedback_apply(plan, rank: tagc_rank_buffers, shared: tagc_shared_buffe
            "tagc_feedback_apply")
 
 
-def _rank_array(ranks):
-    """A C array of rank buffers: `ranks` itself if it is one already."""
-    return ranks if isinstance(ranks, C.Array) else (tagc_rank_buffers * len(ranks))(*ranks)
+def _rank_array(ranks, n_ranks):
+    """The first n_ranks (None: all) rank buffers as a C array (`ranks` itself if it is one already)
+    and their number, which the library takes at its word."""
+    n = len(ranks) if n_ranks is None else n_ranks
+    if not 0 <= n <= len(ranks):
+        raise ValueError("%d ranks asked for, %d given" % (n, len(ranks)))
+    return (ranks if isinstance(ranks, C.Array) else (tagc_rank_buffers * len(ranks))(*ranks)), n
 
 
 def tagc_aggregate(plan, phase, ranks, shared: tagc_shared_buffers,
                    stream: int = 0, n_ranks=None):
-    n = len(ranks) if n_ranks is None else n_ranks
-    _check(lib().tagc_aggregate(plan, phase, _rank_array(ranks), n, C.byref(shared),
+    arr, n = _rank_array(ranks, n_ranks)
+    _check(lib().tagc_aggregate(plan, phase, arr, n, C.byref(shared),
                                 stream), "tagc_aggregate")
 
 
@@ -244,8 +250,8 @@ def tagc_decompress(plan, shared: tagc_shared_buffers, idx_out, val_out,
 
 def tagc_reduce_decompress(plan, ranks, shared: tagc_shared_buffers, idx_out, val_out,
                            dense_out=None, stream: int = 0, n_ranks=None):
-    n = len(ranks) if n_ranks is None else n_ranks
-    _check(lib().tagc_reduce_decompress(plan, _rank_array(ranks), n, C.byref(shared), idx_out,
+    arr, n = _rank_array(ranks, n_ranks)
+    _check(lib().tagc_reduce_decompress(plan, arr, n, C.byref(shared), idx_out,
                                         val_out, dense_out, stream), "tagc_reduce_decompress")
 
 

@@ -182,7 +182,8 @@ class TagcBucket:
                               _stream_ptr(stream), self._n(n_ranks))
 
     def _n(self, n_ranks):
-        return min(n_ranks or self.n_ranks, self.n_ranks)
+        """How many ranks rk[:n_ranks] names (None, 0: all)."""
+        return len(range(self.n_ranks)[:n_ranks or self.n_ranks])
 
     def aggregate_index(self, n_ranks=None, stream=None):
         B.tagc_aggregate(self.plan, B.TAGC_PHASE_INDEX, self.rk, self.shared,

@@ -96,3 +96,29 @@ def test_rows_of_one_tensor_as_gradients(monkeypatch):
     tb.compress_index_all([], stream)
     tb.compress_index_all(torch.empty(0, 1000), stream)
     assert not calls
+
+
+def test_no_more_ranks_than_there_are():
+    """A number of ranks beyond the buffers given never reaches the library, which would read
+    past them; a bucket's n_ranks is the end of a slice, as of its list of ranks."""
+    tb = _bucket(4)
+    assert [tb._n(n) for n in (None, 0, 1, 4, 9, -1, -9)] == [4, 4, 1, 4, 4, 3, 0]
+    plan = B.tagc_plan(B.tagc_config(dtype=0, n_ranks=8, n_hash=3, sizing_milli=1500),
+                       [(0, 1000, 10_000, 1)])
+    sh, ranks = B.tagc_shared_buffers(), [B.tagc_rank_buffers()] * 2
+    for arr in (ranks, (B.tagc_rank_buffers * 2)(*ranks)):
+        for n in (3, 8, -1):
+            with pytest.raises(ValueError):
+                B.tagc_compress_ranks(plan, B.TAGC_PHASE_INDEX, [256] * max(n, 0), arr, sh, 0, n)
+            with pytest.raises(ValueError):
+                B.tagc_aggregate(plan, B.TAGC_PHASE_INDEX, arr, sh, 0, n)
+            with pytest.raises(ValueError):
+                B.tagc_reduce_decompress(plan, arr, sh, 256, 256, None, 0, n)
+        for grads in ([256], [256] * 3):
+            with pytest.raises(ValueError):
+                B.tagc_compress_ranks(plan, B.TAGC_PHASE_INDEX, grads, arr, sh)
+        with pytest.raises(B.TagcError):     # (null buffers: the library's own refusal)
+            B.tagc_aggregate(plan, B.TAGC_PHASE_INDEX, arr, sh, 0, 2)
+        with pytest.raises(B.TagcError):
+            B.tagc_aggregate(plan, B.TAGC_PHASE_INDEX, arr, sh, 0, 0)
+    B.tagc_plan_destroy(plan)
