@@ -315,9 +315,10 @@ int tagc_compress(const tagc_plan_t *plan, uint32_t phase, const void *grad_dev,
  *   for r in 0 .. n_ranks-1: tagc_compress(plan, phase, grads[r], &ranks[r], shared, stream)
  * with the ranks' work in the same launches.  A launch's ramp-up, tail and turn-around
  * (about 5 us) are then paid once and not once per rank.  In PHASE_INDEX neighbouring ranks
- * go together as far as their workspaces differ (ranks that share one take turns); each of those
- * carries pre-thresholds of its own, ranks that take turns hand them on, and in the first call
- * after an upload all take turns.  grads: host array of n_ranks device pointers
+ * go together as far as their workspaces, and whatever else they write, differ; ranks that
+ * share a buffer take turns, as ranks with the same sketch do in PHASE_SKETCH.  Ranks that go
+ * together carry pre-thresholds of their own, ranks that take turns hand them on, and in the
+ * first call after an upload all take turns.  grads: host array of n_ranks device pointers
  * (not read, may be NULL, in PHASE_SKETCH); ranks: host array.
  */
 int tagc_compress_ranks(const tagc_plan_t *plan, uint32_t phase, const void *const *grads,

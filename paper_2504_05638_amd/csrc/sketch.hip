@@ -239,12 +239,15 @@ int launch_encode(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32_t
             return TAGC_EHIP;
         attr_bytes = lds;
     }
-    for (uint32_t r0 = 0; r0 < n_ranks; r0 += kMaxRanksPerPass) {
-        const uint32_t n_in = std::min(kMaxRanksPerPass, n_ranks - r0);
+    for (uint32_t r0 = 0, n_in; r0 < n_ranks; r0 += n_in) {
+        // (ranks that write to the same sketch take turns)
         EncodeBatch eb{};
-        for (uint32_t r = 0; r < n_in; ++r) {
-            const tagc_rank_buffers &rk = ranks[r0 + r];
-            eb.r[r] = EncodeRank{rk.idx, rk.val, rk.cnt, rk.sketch};
+        for (n_in = 0; n_in < std::min(kMaxRanksPerPass, n_ranks - r0); ++n_in) {
+            const tagc_rank_buffers &rk = ranks[r0 + n_in];
+            bool own = true;
+            for (uint32_t q = 0; q < n_in; ++q) own &= eb.r[q].sketch != rk.sketch;
+            if (!own) break;
+            eb.r[n_in] = EncodeRank{rk.idx, rk.val, rk.cnt, rk.sketch};
         }
         ProfileScope ps("encode", s);
         encode_kernel<<<dim3(uint32_t(p->A_cap), n_in), kEncodeThreads, lds, s>>>(

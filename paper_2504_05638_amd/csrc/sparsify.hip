@@ -2599,14 +2599,19 @@ int launch_sparsify(const tagc_plan_t *p, const void *const *grads, const tagc_r
                     uint32_t n_ranks, const tagc_shared_buffers *sh, hipStream_t s)
 {
     for (uint32_t r0 = 0; r0 < n_ranks;) {
-        // The longest run of ranks that can go together: workspaces of their own (ranks that
-        // share one have to take turns), a slot of the table's state each, and all with an
-        // accumulator or none with one.
+        // The longest run of ranks that can go together: buffers of their own (ranks that share a
+        // workspace or anything else they write have to take turns), a slot of the table's state
+        // each, and all with an accumulator or none with one.
         uint32_t n = 1;
         auto joins = [&](uint32_t r) {
-            if ((ranks[r].acc != nullptr) != (ranks[r0].acc != nullptr)) return false;
-            for (uint32_t q = r0; q < r; ++q)
-                if (ranks[q].workspace == ranks[r].workspace) return false;
+            const tagc_rank_buffers &b = ranks[r];
+            if ((b.acc != nullptr) != (ranks[r0].acc != nullptr)) return false;
+            for (uint32_t q = r0; q < r; ++q) {
+                const tagc_rank_buffers &a = ranks[q];
+                if (a.workspace == b.workspace || a.idx == b.idx || a.val == b.val ||
+                    a.cnt == b.cnt || a.bitmap == b.bitmap || (a.acc && a.acc == b.acc))
+                    return false;
+            }
             return true;
         };
         while (r0 + n < n_ranks && n < p->slots && joins(r0 + n)) ++n;
