@@ -232,8 +232,10 @@ def kernel_alg_bytes(b, z, hdr, k_total, dense, ef=False, wire=1, cell=4):
         "widen4": (1 + 4) * N * n_c // 8,
         "encode": 8 * k_total + N * cell * m,
         "sketch_sum": (N * cell + 4) * m,
-        "peel": 4 * m + 8 * U,
-        "sum_peel": N * cell * m + 8 * U,
+        # (the decoder reads the Index, or the list that enumerate made of it)
+        "enumerate": n_c // 8 + 4 * U,
+        "peel": 4 * m + n_c // 8 + 8 * U,
+        "sum_peel": N * cell * m + n_c // 8 + 8 * U,
         "dense": n_c // 8 + 4 * U + 4 * n_c,
     }
 
