@@ -4,17 +4,19 @@
 // merged Index in [bounds[a], bounds[a+1]); its 3*m_sub cells live in LDS for the whole
 // peel, so the rounds cost no HBM traffic and no kernel launches.
 //
-// Peeling is round-synchronous: in a round every unresolved unknown that touches a cell
-// of degree 1 takes its value from the smallest such hash function, reading the sketch
-// as it stood when the round began; then all unknowns taken in the round subtract
-// themselves from their three cells.  The first round that takes nothing ends the peel.
-// Unknowns left over are reported with value 0 and counted.
+// Peeling is round-synchronous: the unknowns that were alone in a cell when a round began take their
+// values from that cell and subtract themselves from their two others; a round that finds none
+// ends the peel.  Unknowns left over are reported with value 0 and counted.
 //
 // The rounds are driven by cells, not by polling unknowns.  Besides its value every cell
 // keeps one 32-bit word: (sum of the local ranks of its unresolved unknowns) << 15 | degree.
 // When the degree is 1 the upper field *is* the remaining unknown, so a queue of the unknowns
-// that have just become the last of a cell is all a round needs; one compare-and-swap removes
-// an unknown from a cell and tells, by the old degree, whether another one joins the queue.
+// that have just become the last of a cell is all a round needs.  An unknown leaves a cell by an
+// atomic subtraction from that word, whose old degree tells whether another one joins the queue,
+// and by a compare-and-swap of the value.  It is queued once, with the cell it is to be read from:
+// for the first round that is its first cell of degree 1, later the one whose wave came first.
+// (Float32 cells of an unknown that is alone in several agree up to rounding; cells that were
+// rounded to 16 bits on the wire differ by that rounding, and a value with them.)
 // Total work is proportional to the unknowns, not to unknowns x rounds.
 #include <type_traits>
 

@@ -182,13 +182,4 @@ __device__ inline T *as_global(T *p)
     return (T *)(__attribute__((address_space(1))) T *)p;
 }
 
-__device__ inline uint64_t ld_agent(const uint64_t *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline void st_agent(uint64_t *p, uint64_t v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 }  // namespace tagc

@@ -26,11 +26,12 @@
 //    count        survivors of every super-chunk of candidates (32 chunks)
 //    place        ordered pass over the candidates only: pairs + every Index word
 //
-//  dense route (segments that are short, unaligned, keep more than ~3 %, have no
+//  dense route (segments that are short, unaligned, keep more than ~23 %, have no
 //  pre-threshold yet, or were re-routed; three reads)
 //    hist1        exact histogram of the top 15 key bits of every entry, in LDS windows; the
-//                 workgroup that completes a segment's histogram selects its threshold
-//    refine       fp32 only, as above
+//                 workgroup that completes a segment's histogram selects its threshold.  A
+//                 segment that one workgroup's registers hold is selected by one, fp32 included
+//    refine       fp32 only, as above, from the gradient
 //    count        survivors of every tile of the gradient
 //    place        ordered pass over the gradient: pairs + Index words
 //
@@ -257,13 +258,13 @@ accumulate_kernel(const SparsifyBatch, const uint32_t *__restrict__ table, uint3
 // ----------------------------------------------------------------- select
 
 // For each of two counts `want` (0 = not asked): the largest bin b with
-// sum_{x >= b} get(x) >= want, the entries in higher bins and those in b; bin = kNoBin if all
+// sum_{x >= b} get(x) >= want and the entries in higher bins; bin = kNoBin if all
 // bins together hold fewer.  By a workgroup of NT threads, thread t owning the BPT consecutive
 // bins from t * BPT, whose sum it passes as `own`; the thread whose bins hold the answer leaves
 // its number, and one wave reads those bins side by side.
 constexpr uint32_t kNoBin = 0xFFFFFFFFu;
 struct BinFound {
-    uint32_t bin, above, at;
+    uint32_t bin, above;
 };
 template <uint32_t NT, uint32_t BPT, typename Get>
 __device__ inline void select_top(Get &&get, uint32_t own, const uint32_t (&want)[2],
@@ -303,7 +304,6 @@ __device__ inline void select_top(Get &&get, uint32_t own, const uint32_t (&want
             if (above < need && above + c >= need) {
                 smem[16 + 4 * wave] = owner * BPT + b;
                 smem[17 + 4 * wave] = above;
-                smem[18 + 4 * wave] = c;
             }
             acc += tot;
         }
@@ -313,7 +313,7 @@ __device__ inline void select_top(Get &&get, uint32_t own, const uint32_t (&want
     __syncthreads();
 #pragma unroll
     for (uint32_t i = 0; i < 2; ++i)
-        found[i] = BinFound{smem[16 + 4 * i], smem[17 + 4 * i], smem[18 + 4 * i]};
+        found[i] = BinFound{smem[16 + 4 * i], smem[17 + 4 * i]};
     *total_out = total;
     __syncthreads();
 }
@@ -1169,7 +1169,7 @@ hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t n
         if ((sd.flags & kSegSmall) || !on_dense_route(sd, sel, l)) return 0u;
         return (sd.n + TILE - 1) / TILE;
     };
-    uint32_t all = 0;  // (every wave adds them up for itself; < 2^22 segments of < 2^19 tiles)
+    uint32_t all = 0;  // (every wave adds them up for itself; all entries are < 2^32, a tile holds 4096 or more)
     for (uint32_t l = lane; l < (L + 63) / 64 * 64; l += 64) all += tiles_of(l);
     all = wave_sum(all);
     if (all == 0) return;
@@ -2466,7 +2466,6 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
                   hipStream_t s)
 {
     const WsLayout wl = ws_layout(p);
-    const uint32_t L = uint32_t(p->table.size());
     const int cus = device_cu_count();
     static int occ_place[2][3] = {};
     auto per_rank = [&](uint32_t total) { return std::max(1u, total / n); };

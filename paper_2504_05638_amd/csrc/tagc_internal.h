@@ -35,8 +35,9 @@ constexpr double kFastMaxCandFrac = 0.30;  // expected candidates per element be
 constexpr uint32_t kChunkWords = 1024;  // Index words per popcount chunk, ...
 constexpr uint32_t kGroupWords = 64;    // ... and per group of it
 constexpr uint32_t kTileGroup = 64;     // dense-route tiles whose counts are also kept as one sum
-// A partition keeps, in LDS, 10 bytes per cell (value, meta word, queue slot) and 4 per
-// unknown (its c-index): 12288 cells and 8192 unknowns fill the 160 KiB.
+// A partition keeps, in LDS, 8 bytes per cell (value, meta word) and 7 and a bit per unknown (its
+// packed slots, then its value; a queue entry; claimed or not): 12288 cells and 8192 unknowns
+// take 153 of the 160 KiB.  (Larger ones: 10 per cell and 4 and a bit per unknown.)
 constexpr uint32_t kDefaultPartCells = 12288;
 constexpr uint32_t kDefaultPartUnknowns = 8192;
 constexpr uint32_t kMaxPartCells = 16383;      // 16 queue sweeps of 1024 threads at most
