@@ -90,7 +90,7 @@ def parse_args():
     ap.add_argument("--buckets", type=int, default=0,
                     help="only the first B buckets of the workload (0 = all; for experiments)")
     ap.add_argument("--ranks-together", type=int, default=-1,
-                    help="ranks whose sparsifier work shares launches (0: as many as fit TagcBucket's "
+                    help="ranks whose work shares launches (0: as many as fit TagcBucket's "
                          "limit; default: 1 with several buckets in flight of which a rank's part "
                          "alone fills the device, else 0)")
     ap.add_argument("--lanes", type=int, default=12,
@@ -362,7 +362,7 @@ def main():
     peel_wgs = args.decode_workgroups if lanes > 1 else 0
     if args.ranks_together < 0:
         # One rank of a 7B block (405 MB) is 80 us of streaming; its launches overlap better with
-        # other buckets' when they are its own: 2327 to 2341 GB/s, 2260 to 2295 with 16 ranks to a
+        # other buckets' when they are its own: 2315 to 2332 GB/s, 2255 to 2295 with 16 ranks to a
         # launch.  Not of smaller buckets: GPT-2 blocks (28 MB a rank) 1053 with launches of their
         # own, 1877 with shared ones, shards of 7B blocks (51 MB) 1737 and 2189.
         big = min(plan_bytes) >= 256 << 20

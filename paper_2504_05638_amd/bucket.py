@@ -25,8 +25,10 @@ def _bytes(n, device):
 class TagcBucket:
     """One gradient bucket: plan + device buffers for `n_ranks` simulated ranks.
 
-    Ranks with workspaces of their own share the sparsifier's launches.  `ranks_together`: how
-    many have one (each is rank_workspace_bytes of device memory); 0 = as many as fit a GiB."""
+    `ranks_together`: how many ranks' work goes into the same launches; 0 = all of it, in the
+    sparsifier that of as many ranks as a GiB holds workspaces for (each needs its own, of
+    rank_workspace_bytes).  One bucket at a time that is fastest; with several large buckets in
+    flight on streams of their own, launches of one rank each overlap better."""
 
     _WORKSPACES_BYTES = 1 << 30
 
@@ -58,6 +60,7 @@ class TagcBucket:
             self.plan_whole = B.tagc_plan(cfg0, self.segments)
         self.sizes = B.tagc_plan_sizes(self.plan)
         self.n_ranks = n_ranks
+        self._ranks_together = ranks_together
         z, dev = self.sizes, self.device
         self._share = share
         self._min_bytes = min_bytes or {}
@@ -177,9 +180,18 @@ class TagcBucket:
                               self.rk, self.shared, _stream_ptr(stream), len(grads))
 
     def compress_sketch_all(self, n_ranks=None, stream=None):
-        """compress_sketch of the first n_ranks ranks, in the same launches."""
-        B.tagc_compress_ranks(self.plan, B.TAGC_PHASE_SKETCH, None, self.rk, self.shared,
-                              _stream_ptr(stream), self._n(n_ranks))
+        """compress_sketch of the first n_ranks ranks, `ranks_together` of them to a launch (all of
+        them if that was left alone)."""
+        n = self._n(n_ranks)
+        step = self._ranks_together or n
+        for r in range(0, n, step):
+            B.tagc_compress_ranks(self.plan, B.TAGC_PHASE_SKETCH, None, self._rk_from(r), self.shared,
+                                  _stream_ptr(stream), min(step, n - r))
+
+    def _rk_from(self, r):
+        """The ranks' buffers from rank r on, as an array of the library's."""
+        left = self.n_ranks - r
+        return (B.tagc_rank_buffers * left).from_buffer(self.rk, r * B.C.sizeof(B.tagc_rank_buffers))
 
     def _n(self, n_ranks):
         """How many ranks rk[:n_ranks] names (None, 0: all)."""

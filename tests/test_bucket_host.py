@@ -76,7 +76,7 @@ class _Stacked:
 def _bucket(n_ranks):
     tb = TagcBucket.__new__(TagcBucket)
     tb.plan = tb.plan_whole = tb.shared = None
-    tb.cfg, tb.n_ranks = B.tagc_config(dtype=B.TAGC_F32), n_ranks
+    tb.cfg, tb.n_ranks, tb._ranks_together = B.tagc_config(dtype=B.TAGC_F32), n_ranks, 0
     tb.sizes = types.SimpleNamespace(grad_elems=1000)
     tb.rk = (B.tagc_rank_buffers * n_ranks)()
     return tb
@@ -122,3 +122,22 @@ def test_no_more_ranks_than_there_are():
         with pytest.raises(B.TagcError):
             B.tagc_aggregate(plan, B.TAGC_PHASE_INDEX, arr, sh, 0, 0)
     B.tagc_plan_destroy(plan)
+
+
+def test_ranks_together_holds_for_the_sketches(monkeypatch):
+    """Every rank once, in order, as many to a call as the bucket was asked for."""
+    calls = []
+    monkeypatch.setattr(B, "tagc_compress_ranks",
+                        lambda plan, phase, grads, ranks, shared, stream, n:
+                        calls.append([ranks[r].idx for r in range(n)]))
+    tb, stream = _bucket(5), types.SimpleNamespace(cuda_stream=0)
+    for r in range(5):
+        tb.rk[r].idx = 4096 + 16 * r
+    every = [4096 + 16 * r for r in range(5)]
+    for together, n, want in ((0, None, [every]), (1, None, [[i] for i in every]),
+                              (2, None, [every[:2], every[2:4], every[4:]]), (8, None, [every]),
+                              (2, 3, [every[:2], every[2:3]])):
+        calls.clear()
+        tb._ranks_together = together
+        tb.compress_sketch_all(n, stream)
+        assert calls == want
