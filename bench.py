@@ -26,7 +26,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X published HBM3E bandwidth
 STAGES = {
     "S1+S2 sparsify+index": ["fill_zero", "accumulate", "prepare", "scan_spill", "hist1",
                              "refine", "count", "place", "widen4"],
-    "S3a index OR": ["index_or", "layout"],
+    "S3a index OR": ["index_or", "layout", "ranges", "salt"],
     "S2' encode": ["encode"],
     "S3b sketch sum": ["sketch_sum"],
     "S4 decode": ["enumerate", "peel", "dense"],

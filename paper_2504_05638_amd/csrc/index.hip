@@ -218,11 +218,13 @@ __device__ inline void lower_bounds_by_16(const uint32_t *const (&list)[kN], con
 // 21 and 40; with 16 ranks of 202 M, where the salts are most of it, 138 and 149.
 constexpr uint32_t kSaltThreads = 1024;
 constexpr uint32_t kLayoutBatch = kSaltThreads / 128;  // partitions whose bounds are found at once
+constexpr uint64_t kSplitSearches = 32768;  // (partition, rank) pairs
 constexpr uint32_t kSaltLimit = 16;       // salts tried: 0 .. 15
 constexpr uint32_t kNoLink = 0xFFFFu;
 constexpr uint32_t kSaltPre = 4;          // Index words per thread requested a partition ahead
 
 // (8 waves per SIMD asked for: two workgroups a compute unit; 106 scalar registers leave room for one)
+template <bool kBounds, bool kSearch, bool kSalts>
 __global__ void __launch_bounds__(kSaltThreads) __attribute__((amdgpu_waves_per_eu(8)))
 layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__restrict__ bitmap,
               uint32_t n_words, uint32_t n_c, const uint32_t *__restrict__ chunkcnt,
@@ -237,43 +239,49 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     uint32_t *head = tag + P_cap;                                   // [q_cap]
     uint16_t *link = reinterpret_cast<uint16_t *>(head + q_cap);    // [P_cap]
     __shared__ uint32_t s_n, s_dup;
-    __shared__ uint32_t s_pre[NT];                // set bits before thread t's chunks
+    __shared__ uint32_t s_pre[kBounds ? NT : 1];  // set bits before thread t's chunks
     __shared__ uint32_t s_bound[2 * kLayoutBatch];  // first and last bound of the batch's partitions
     __shared__ uint32_t smem[NT / 64];
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // ---- set bits before every thread's chunks, the layout
-    const uint32_t per = (n_chunks + NT - 1) / NT;
-    const uint32_t first = tid * per, last = min(first + per, n_chunks);
-    uint32_t own = 0, total;
-    for (uint32_t i = first; i < last; ++i) own += chunkcnt[i];
-    const uint32_t before = block_excl_scan<uint32_t, NT / 64>(own, &total, smem);
-    s_pre[tid] = before;
     // (what every lane holds alike comes from LDS here: said to be uniform, it stays in scalar
     // registers, and the loops below are scalar)
     auto uniform = [](uint32_t x) -> uint32_t { return __builtin_amdgcn_readfirstlane(x); };
-    total = uniform(total);
-    const Layout lay = layout_of(total, lp);
-    const uint32_t U = lay.U, A = lay.A, m_sub = min(lay.m_sub, q_cap);
-    if (all && blockIdx.x == 0) {
-        uint32_t run = before;
-        for (uint32_t i = first; i < last; ++i) {
-            chunkpre[i] = run;
-            run += chunkcnt[i];
+    // ---- set bits before every thread's chunks, the layout
+    const uint32_t per = (n_chunks + NT - 1) / NT;
+    Layout lay{};
+    if (kBounds) {
+        const uint32_t first = tid * per, last = min(first + per, n_chunks);
+        uint32_t own = 0, total;
+        for (uint32_t i = first; i < last; ++i) own += chunkcnt[i];
+        const uint32_t before = block_excl_scan<uint32_t, NT / 64>(own, &total, smem);
+        s_pre[tid] = before;
+        total = uniform(total);
+        lay = layout_of(total, lp);
+        if (all && blockIdx.x == 0) {
+            uint32_t run = before;
+            for (uint32_t i = first; i < last; ++i) {
+                chunkpre[i] = run;
+                run += chunkcnt[i];
+            }
+            if (tid == 0) {
+                chunkpre[n_chunks] = total;
+                header[TAGC_HDR_U] = lay.U;
+                header[TAGC_HDR_A] = lay.A;
+                header[TAGC_HDR_MSUB] = lay.m_sub;
+                header[TAGC_HDR_M] = lay.m;
+                for (int i = 4; i < TAGC_HDR_WORDS; ++i) header[i] = 0;
+                for (int i = 0; i < TAGC_ST_WORDS; ++i) status[i] = 0;
+                status[TAGC_ST_FLAGS] = lay.flags;
+            }
         }
-        if (tid == 0) {
-            chunkpre[n_chunks] = total;
-            header[TAGC_HDR_U] = lay.U;
-            header[TAGC_HDR_A] = lay.A;
-            header[TAGC_HDR_MSUB] = lay.m_sub;
-            header[TAGC_HDR_M] = lay.m;
-            for (int i = 4; i < TAGC_HDR_WORDS; ++i) header[i] = 0;
-            for (int i = 0; i < TAGC_ST_WORDS; ++i) status[i] = 0;
-            status[TAGC_ST_FLAGS] = lay.flags;
-        }
+        __syncthreads();  // s_pre
+    } else {
+        lay.A = header[TAGC_HDR_A];
+        lay.m_sub = header[TAGC_HDR_MSUB];
     }
-    __syncthreads();  // s_pre
+    const uint32_t U = lay.U, A = lay.A, m_sub = min(lay.m_sub, q_cap);
 
     // c-index of the set bit of rank rho < U (by a wave, all lanes get it)
     auto bound_of = [&](uint32_t rho) -> uint32_t {
@@ -338,9 +346,9 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     auto rank_row = [&](uint32_t r) { return batch_row<LayoutRank>(r); };
     auto pairs_of = [&](uint32_t *cnt) { return min(cnt[TAGC_CNT_TOTAL], pair_cap); };
 
-    if (blockIdx.x == 0) {  // the end of the last partition (of none: the only bound)
+    if (kBounds && blockIdx.x == 0) {  // the end of the last partition (of none: the only bound)
         if (tid == 0) bounds[A] = n_c;
-        if (tid < n_in) {
+        if (kSearch && tid < n_in) {
             uint32_t *cnt = as_global(rank_row(tid)->cnt);
             cnt[ranges_off + A] = pairs_of(cnt);
         }
@@ -359,7 +367,9 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     for (uint32_t b0 = 0; b0 < n_mine; b0 += kLayoutBatch) {
     const uint32_t nb = min(kLayoutBatch, n_mine - b0);
     __syncthreads();  // s_bound is free
-    if ((wave >> 1) < nb) {
+    if (!kBounds) {
+        if (tid < 2 * nb) s_bound[tid] = bounds[blockIdx.x + (b0 + (tid >> 1)) * G + (tid & 1)];
+    } else if ((wave >> 1) < nb) {
         const uint32_t a = blockIdx.x + (b0 + (wave >> 1)) * G + (wave & 1);
         const uint32_t x = a == A ? n_c : bound_of(uint32_t(uint64_t(a) * U / A));
         if (lane == 0) {
@@ -373,9 +383,9 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     uint32_t lo = uniform(s_bound[0]), hi = uniform(s_bound[1]), pre[kSaltPre];
 #pragma unroll
     for (uint32_t k = 0; k < kSaltPre; ++k)
-        pre[k] = all ? load_word((lo >> 5) + k * NT + tid, lo, hi) : 0u;
+        pre[k] = kSalts ? load_word((lo >> 5) + k * NT + tid, lo, hi) : 0u;
     constexpr uint32_t kLists = 2;
-    for (uint32_t t0 = 0; t0 < nb * n_in; t0 += kLists * (NT / 16)) {
+    for (uint32_t t0 = 0; kSearch && t0 < nb * n_in; t0 += kLists * (NT / 16)) {
         const uint32_t *list[kLists];
         uint32_t *cnt[kLists];
         uint32_t n[kLists], key[kLists], pos[kLists];
@@ -397,7 +407,7 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
                 cnt[i][ranges_off + blockIdx.x + (b0 + t / n_in) * G] = pos[i];
         }
     }
-    if (!all) continue;
+    if (!kSalts) continue;
     for (uint32_t i = 0; i < nb; ++i) {
         const uint32_t w_lo = lo >> 5, w_hi = lo < hi ? (hi - 1) >> 5 : 0;
         const uint32_t cur_lo = lo, cur_hi = hi;
@@ -466,6 +476,26 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     }
 }
 
+// The ends of the partitions in the ranks' pair lists as a launch of its own: a thread per (rank,
+// partition), whose binary search is 20 dependent loads, but all of them run at once.
+__global__ void __launch_bounds__(256)
+ranges_kernel(const LayoutBatch, const uint32_t *__restrict__ header,
+              const uint32_t *__restrict__ bounds, uint32_t ranges_off, uint32_t pair_cap)
+{
+    const uint32_t a = blockIdx.x * 256 + threadIdx.x;
+    if (a > header[TAGC_HDR_A]) return;  // (bounds[A] = n_c: all of the list)
+    const auto *row = batch_row<LayoutRank>(blockIdx.y);
+    const uint32_t *list = as_global(row->idx);
+    uint32_t *cnt = as_global(row->cnt);
+    const uint32_t key = bounds[a];
+    uint32_t lo = 0, hi = min(cnt[TAGC_CNT_TOTAL], pair_cap);
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (list[mid] < key) lo = mid + 1; else hi = mid;
+    }
+    cnt[ranges_off + a] = lo;
+}
+
 }  // namespace
 
 size_t salt_lds_bytes(uint32_t T_cap, uint32_t P_cap)
@@ -509,28 +539,56 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
                           p->A_cap,
                           p->m_cap};
     const size_t lds = salt_lds_bytes(p->T_cap, p->P_cap);
-    static size_t attr_bytes = 0;
-    if (lds > attr_bytes) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(layout_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                int(lds)) != hipSuccess)
-            return TAGC_EHIP;
-        attr_bytes = lds;
-    }
     // as many workgroups as fit the device at once, each taking partitions b, b + grid, ...
     const size_t lds_all = lds + 6 * 1024;  // with the kernel's own
     const uint32_t per_cu = uint32_t(std::max<size_t>(1, std::min<size_t>(2, kLdsBytes / lds_all)));
     const uint32_t grid = uint32_t(std::min<uint64_t>(p->A_cap, uint64_t(device_cu_count()) * per_cu));
+    // Many searches in a plan that says, by a limit on the decoder's workgroups, that other buckets
+    // are in flight: three launches.  In the one launch the workgroups that wait for the searches'
+    // loads hold a compute unit's local memory, and no other bucket's salts run meanwhile; and 16
+    // lanes to a search read more than a thread's binary search does.  16 ranks of 202 M entries,
+    // 58 thousand searches: 12 buckets in flight 210 us each in one launch (with the merge), 177 in
+    // three.  Alone, one launch is the better for what follows: 222 and 210 us, but it leaves the
+    // pair lists in the cache for the encoder (593 us, 622 after three launches).
+    const bool split = p->cfg.decode_workgroups && p->A_cap * n_ranks > kSplitSearches;
+    const uint32_t wgs = uint32_t(std::min<uint64_t>((p->A_cap + kLayoutBatch - 1) / kLayoutBatch,
+                                                     uint64_t(device_cu_count()) * 2));
+    const auto layout = layout_kernel<true, true, true>, salts = layout_kernel<false, false, true>;
+    static size_t attr_bytes[2] = {0, 0};
+    if (lds > attr_bytes[split]) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(split ? salts : layout),
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                int(lds)) != hipSuccess)
+            return TAGC_EHIP;
+        attr_bytes[split] = lds;
+    }
+    auto launch = [&](auto kernel, uint32_t n_wgs, size_t lds_bytes, const LayoutBatch &lb,
+                      uint32_t n_in, bool all) {
+        kernel<<<n_wgs, kSaltThreads, lds_bytes, s>>>(
+            lb, n_in, all, sh->bitmap, n_words, uint32_t(p->n_c), chunk, chunkpre, n_chunks, lp,
+            sh->header, sh->status, sh->bounds, p->cnt_ranges, uint32_t(p->K), p->cfg.seed);
+    };
     for (uint32_t r0 = 0; r0 < n_ranks; r0 += kMaxRanksPerPass) {
         // (ranks beyond the first launch's only need their pair lists searched)
-        ProfileScope ps("layout", s);
         LayoutBatch lb{};
         const uint32_t n_in = std::min(kMaxRanksPerPass, n_ranks - r0);
         for (uint32_t r = 0; r < n_in; ++r)
             lb.r[r] = LayoutRank{ranks[r0 + r].idx, ranks[r0 + r].cnt};
-        layout_kernel<<<grid, kSaltThreads, lds, s>>>(
-            lb, n_in, r0 == 0, sh->bitmap, n_words, uint32_t(p->n_c), chunk, chunkpre, n_chunks, lp,
-            sh->header, sh->status, sh->bounds, p->cnt_ranges, uint32_t(p->K), p->cfg.seed);
+        if (r0 == 0 || !split) {
+            ProfileScope ps("layout", s);
+            if (split) launch(layout_kernel<true, false, false>, wgs, 0, lb, n_in, true);
+            else if (r0 == 0) launch(layout, grid, lds, lb, n_in, true);
+            else launch(layout_kernel<true, true, false>, wgs, 0, lb, n_in, false);
+        }
+        if (split) {
+            ProfileScope ps("ranges", s);
+            ranges_kernel<<<dim3(uint32_t((p->A_cap + 1 + 255) / 256), n_in), 256, 0, s>>>(
+                lb, sh->header, sh->bounds, p->cnt_ranges, uint32_t(p->K));
+        }
+    }
+    if (split) {
+        ProfileScope ps("salt", s);
+        launch(salts, grid, lds, LayoutBatch{}, 0, true);
     }
     return hip_ok(hipGetLastError());
 }
