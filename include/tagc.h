@@ -95,7 +95,9 @@ typedef struct tagc_config {
                                whole local memory, so a caller that keeps other
                                buckets' work in flight on other streams leaves
                                the rest of the device to them with a value
-                               like a quarter of the compute units.  Results
+                               like a quarter of the compute units (and
+                               tagc_aggregate(PHASE_INDEX) then takes the form
+                               that holds least while it waits).  Results
                                and buffer sizes do not depend on it: plans that
                                differ in nothing else work on the same buffers  */
     uint32_t reserved;      /* must be 0                                        */

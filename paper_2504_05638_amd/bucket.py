@@ -50,7 +50,7 @@ class TagcBucket:
                                  decode_workgroups=decode_workgroups)
         self.segments = [tuple(s[:4]) for s in segments]
         self.plan = B.tagc_plan(self.cfg, self.segments)
-        # decode_workgroups only shapes tagc_decompress's launch: a plan that differs in
+        # decode_workgroups only shapes launches (tagc_decompress's above all): a plan that differs in
         # nothing else works on the same buffers (for a caller that sometimes decodes with
         # the device to itself)
         self.plan_whole = None
