@@ -190,6 +190,8 @@ class TagcBucket:
 
     def _rk_from(self, r):
         """The ranks' buffers from rank r on, as an array of the library's."""
+        if r == 0:
+            return self.rk
         left = self.n_ranks - r
         return (B.tagc_rank_buffers * left).from_buffer(self.rk, r * B.C.sizeof(B.tagc_rank_buffers))
 
