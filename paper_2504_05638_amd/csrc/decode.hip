@@ -9,7 +9,7 @@
 // ends the peel.  Unknowns left over are reported with value 0 and counted.
 //
 // The rounds are driven by cells, not by polling unknowns.  Besides its value every cell
-// keeps one 32-bit word: (sum of the local ranks of its unresolved unknowns) << 15 | degree.
+// keeps one 32-bit word: (sum of the local ranks of its unresolved unknowns) << 16 | degree.
 // When the degree is 1 the upper field *is* the remaining unknown, so a queue of the unknowns
 // that have just become the last of a cell is all a round needs.  An unknown leaves a cell by an
 // atomic subtraction from that word, whose old degree tells whether another one joins the queue,
@@ -44,26 +44,30 @@ namespace {
 #define PHASE_INIT() do { } while (0)
 #endif
 
-constexpr uint32_t kDegMask = 0x7FFFu;  // low 15 bits of a cell's meta word
+constexpr uint32_t kDegBits = 16;  // of a cell's meta word: the degree
 
+// An unknown's three cells, as byte offsets into the arrays of values and of meta words.
 struct Cells {
-    uint32_t c[3];
-    uint32_t neg;  // bit j: sign of hash function j is -1
+    uint32_t at[3];
+    uint32_t neg;  // bit 4 + j: sign of hash function j is -1
 };
 
-__device__ inline Cells cells_of(uint32_t i, uint32_t m_sub, uint32_t sw0, uint32_t sw1,
-                                 uint32_t sw2)
+// (fsw: the folded seed words)
+__device__ inline Cells cells_of(uint32_t i, uint32_t m_sub, uint32_t fsw0, uint32_t fsw1,
+                                 uint32_t fsw2)
 {
     Cells r;
     uint32_t n0, n1, n2;
-    r.c[0] = hash_slot(i, sw0, m_sub, &n0);
-    r.c[1] = m_sub + hash_slot(i, sw1, m_sub, &n1);
-    r.c[2] = 2 * m_sub + hash_slot(i, sw2, m_sub, &n2);
-    r.neg = n0 | (n1 << 1) | (n2 << 2);
+    const uint32_t fi = fold16(i);
+    r.at[0] = 4 * hash_slot_folded(fi, fsw0, m_sub, &n0);
+    r.at[1] = 4 * (m_sub + hash_slot_folded(fi, fsw1, m_sub, &n1));
+    r.at[2] = 4 * (2 * m_sub + hash_slot_folded(fi, fsw2, m_sub, &n2));
+    r.neg = (n0 << 4) | (n1 << 5) | (n2 << 6);
     return r;
 }
 
-// A partition in LDS.  A cell is 64 bits: value bits in the low half, meta word in the high one.
+// A partition in LDS.  The cells' values and their meta words are two arrays: a wave's accesses are to
+// one or the other at random cells, and interleaved they would all meet in half of the banks.
 //
 // kPacked: an unknown keeps where its cells are and their signs, in 40 bits (sub-tables of 4096
 // cells at most); else its c-index, from which they are hashed anew.  Once resolved, its word
@@ -71,39 +75,78 @@ __device__ inline Cells cells_of(uint32_t i, uint32_t m_sub, uint32_t sw0, uint3
 // rounds (three 32-bit multiplies per hash, at quarter rate).
 //
 // A queue entry is an unknown and which of its three cells it is alone in.
+//
+// The packed form's arrays lie where the default partition size has them, whatever the size: the offsets
+// of the first four are constants of the LDS instructions then (16 bits), and a cell's value and meta
+// word share an address register.
 template <bool kPacked>
 struct PartLds {
-    unsigned long long *cell;  // [T_cap]
+    uint32_t *cell_value;      // [T_cap]
+    uint32_t *cell_meta;       // [T_cap]
     uint32_t *word;            // [P_cap] packed slots or c-index, then the value
     uint32_t *claimed;         // [P_cap/32 + 1] unknowns that are, or were, in the queue
     uint16_t *queue;           // unknown | sub-table of the cell << kUnknownBits, each unknown once
     uint8_t *rest;             // [P_cap] packed: slot_2 >> 8, and the signs in bits 4 .. 6
-    uint32_t m_sub, sw0, sw1, sw2;
+    uint32_t *n_queued;        // [3] see peel_rounds
+    uint32_t *bar;             // [1] see peel_barrier
+    uint32_t m_sub, fsw0, fsw1, fsw2;
     static constexpr uint32_t kUnknownBits = kPacked ? 13 : 14;
     static_assert(kDefaultPartUnknowns <= 1u << 13 && kMaxPartUnknowns <= 1u << 14, "queue entry");
     static_assert(kDefaultPartCells <= 3u << 12, "packed slots are 12 bits");
+    static constexpr uint32_t kClaimWords = (kDefaultPartUnknowns / 32 + 1 + 3) & ~3u;
+    static constexpr size_t kPackedBytes = kDefaultPartCells * 8 + kClaimWords * 4 +
+                                           kDefaultPartUnknowns * 7 + 16;
 
     __device__ __forceinline__ PartLds(void *lds, uint32_t T_cap, uint32_t P_cap)
     {
-        cell = static_cast<unsigned long long *>(lds);
-        word = reinterpret_cast<uint32_t *>(cell + T_cap);
-        claimed = word + P_cap;
-        queue = reinterpret_cast<uint16_t *>(claimed + P_cap / 32 + 1);
-        rest = reinterpret_cast<uint8_t *>(queue + P_cap);
+        n_queued = static_cast<uint32_t *>(lds);
+        bar = n_queued + 3;
+        cell_value = n_queued + 4;
+        if (kPacked) {
+            claimed = cell_value + kDefaultPartCells;
+            rest = reinterpret_cast<uint8_t *>(claimed + kClaimWords);
+            cell_meta = reinterpret_cast<uint32_t *>(rest + kDefaultPartUnknowns);
+            word = cell_meta + kDefaultPartCells;
+            queue = reinterpret_cast<uint16_t *>(word + kDefaultPartUnknowns);
+        } else {
+            cell_meta = cell_value + T_cap;
+            word = cell_meta + T_cap;
+            claimed = word + P_cap;
+            queue = reinterpret_cast<uint16_t *>(claimed + P_cap / 32 + 1);
+            rest = nullptr;
+        }
     }
-    __device__ __forceinline__ uint32_t *value(uint32_t c) const
+    // of the cell at a byte offset
+    __device__ __forceinline__ uint32_t *value(uint32_t at) const
     {
-        return reinterpret_cast<uint32_t *>(cell + c);
+        return reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(cell_value) + at);
     }
-    __device__ __forceinline__ uint32_t *meta(uint32_t c) const { return value(c) + 1; }
+    __device__ __forceinline__ uint32_t *meta(uint32_t at) const
+    {
+        return reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(cell_meta) + at);
+    }
+    // nobody in the first `cells` cells, no unknown claimed (by NT threads)
+    template <uint32_t NT>
+    __device__ __forceinline__ void clear(uint32_t tid, uint32_t cells, uint32_t P_cap) const
+    {
+        if (kPacked) {
+            uint4 *m = reinterpret_cast<uint4 *>(cell_meta);
+#pragma unroll
+            for (uint32_t i = 0; i < kDefaultPartCells / 4; i += NT)
+                if (4 * (i + tid) < cells) m[i + tid] = make_uint4(0, 0, 0, 0);
+        } else {
+            for (uint32_t c = tid; c < cells; c += NT) cell_meta[c] = 0;
+        }
+        for (uint32_t c = tid; c < P_cap / 32 + 1; c += NT) claimed[c] = 0;
+    }
     // unknown u has c-index i: keeps what of_unknown needs, and returns the cells
     __device__ __forceinline__ Cells place(uint32_t u, uint32_t i) const
     {
-        const Cells cl = cells_of(i, m_sub, sw0, sw1, sw2);
+        const Cells cl = cells_of(i, m_sub, fsw0, fsw1, fsw2);
         if (kPacked) {
-            const uint32_t s1 = cl.c[1] - m_sub, s2 = cl.c[2] - 2 * m_sub;
-            word[u] = cl.c[0] | (s1 << 12) | (s2 << 24);
-            rest[u] = uint8_t((s2 >> 8) | (cl.neg << 4));
+            const uint32_t s1 = cl.at[1] - 4 * m_sub, s2 = cl.at[2] - 8 * m_sub;
+            word[u] = (cl.at[0] >> 2) | (s1 << 10) | (s2 << 22);
+            rest[u] = uint8_t((s2 >> 10) | cl.neg);
         } else {
             word[u] = i;
         }
@@ -113,13 +156,13 @@ struct PartLds {
     __device__ __forceinline__ Cells of_unknown(uint32_t u) const
     {
         const uint32_t w = word[u];
-        if (!kPacked) return cells_of(w, m_sub, sw0, sw1, sw2);
+        if (!kPacked) return cells_of(w, m_sub, fsw0, fsw1, fsw2);
         const uint32_t b = rest[u];
         Cells r;
-        r.c[0] = w & 0xFFFu;
-        r.c[1] = m_sub + ((w >> 12) & 0xFFFu);
-        r.c[2] = 2 * m_sub + ((w >> 24) | ((b & 0xFu) << 8));
-        r.neg = b >> 4;
+        r.at[0] = (w & 0xFFFu) * 4;
+        r.at[1] = ((w >> 12) & 0xFFFu) * 4 + 4 * m_sub;
+        r.at[2] = (__builtin_amdgcn_alignbit(b, w, 24) & 0xFFFu) * 4 + 8 * m_sub;
+        r.neg = b;
         return r;
     }
 };
@@ -149,8 +192,7 @@ __device__ __forceinline__ uint32_t take_slots(uint32_t *count, uint32_t n)
 // queues it; the sub-tables take turns, so that which of its cells an unknown is read from does
 // not depend on the order of the waves (cells that were rounded on the wire differ).
 template <uint32_t NT, uint32_t kSlots, bool kPacked, typename Barrier>
-__device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t tid,
-                                            uint32_t *count, Barrier &&barrier)
+__device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t tid, Barrier &&barrier)
 {
     uint32_t u[3][kSlots], mine = 0, n = 0;
     static_assert(3 * kSlots <= 32, "a bit per cell");
@@ -159,7 +201,7 @@ __device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t 
 #pragma unroll
         for (uint32_t q = 0; q < kSlots; ++q) {
             const uint32_t c = tid + q * NT;
-            u[j][q] = c < p.m_sub ? *p.meta(j * p.m_sub + c) : 0u;
+            u[j][q] = c < p.m_sub ? p.cell_meta[j * p.m_sub + c] : 0u;
         }
 #pragma unroll
     for (uint32_t j = 0; j < 3; ++j) {
@@ -168,8 +210,8 @@ __device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t 
 #pragma unroll
         for (uint32_t q = 0; q < kSlots; ++q) {
             had[q] = 0xFFFFFFFFu;
-            const bool one = (u[j][q] & kDegMask) == 1u;
-            u[j][q] >>= 15;
+            const bool one = uint16_t(u[j][q]) == 1u;
+            u[j][q] >>= kDegBits;
             if (one) had[q] = atomicOr(&p.claimed[u[j][q] >> 5], 1u << (u[j][q] & 31));
         }
 #pragma unroll
@@ -180,7 +222,7 @@ __device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t 
         }
     }
     if (n == 0) return;
-    uint32_t at = take_slots(count, n);
+    uint32_t at = take_slots(&p.n_queued[1], n);
 #pragma unroll
     for (uint32_t j = 0; j < 3; ++j)
 #pragma unroll
@@ -198,101 +240,107 @@ __device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t 
 //
 // A round is a chain of dependent LDS accesses: entry -> slots -> own value, the other cells' values
 // and their degrees (counted down on the way) -> the new values, and claims for the next queue ->
-// queue.  Every link goes out for all cells together, and the values are swapped right behind
-// their reading: cells are shared by unknowns that leave in the same round, and a swap that finds
-// another value has to be made again.  With value and degree in one 64-bit swap, whose reading
-// lay a few dozen instructions back, most waves had several of those in a row.  Rounds of a
-// partition, clocks, before and after: 8192 unknowns in 12288 cells (11 rounds) 47.6 K -> 38.3 K;
-// in 10776 cells (21 rounds) 61.9 K -> 50.0 K; one-bucket decodes of the latter 767 -> 656 us.
+// queue.  Every link goes out for all cells together.  The values are swapped right behind
+// their reading: cells are shared by unknowns that leave in the same round (in nearly every round of a
+// wave), and a swap that finds another value has to be made again, that one alone: made again together
+// with one that had succeeded it took three tries, at some 200 clocks each.  A wave with a handful of
+// entries takes 700 clocks for them, 16 full ones 2100: some 110 vector instructions each, 4 clocks
+// apiece on their SIMD.  Rounds of a partition, clocks, before and after, the arrays of PartLds
+// included: 8192 unknowns in 12288 cells (11 rounds) 38.8 K -> 32.0 K; in 10776 cells (21 rounds) 51.1 K ->
+// 43.3 K; decoders of the latter, 2 ranks of 202 M entries, 647 -> 586 us.  (A queue for every wave,
+// without a shared count: 826 us, every wave then has a few entries of every small round.)
 template <bool kPacked>
 __device__ __forceinline__ void resolve_unknown(const PartLds<kPacked> &p, uint32_t entry,
                                                 uint32_t *n_next, uint16_t *next_queue)
 {
     constexpr int kScope = __HIP_MEMORY_SCOPE_WORKGROUP;
-    const uint32_t u = entry & ((1u << p.kUnknownBits) - 1u), j = entry >> p.kUnknownBits;
+    constexpr uint32_t kSign = 0x80000000u, kOne = 1u << PartLds<kPacked>::kUnknownBits;
+    const uint32_t u = entry & (kOne - 1u);
+    const bool j0 = entry < kOne, j2 = entry >= 2 * kOne;  // the sub-table of its own cell is 0; is 2
     const Cells cl = p.of_unknown(u);
-    const uint32_t k[2] = {j == 0 ? 1u : 0u, j == 2 ? 1u : 2u};  // the sub-tables of the others
-    const uint32_t own = j == 0 ? cl.c[0] : (j == 1 ? cl.c[1] : cl.c[2]);
-    const uint32_t c[2] = {j == 0 ? cl.c[1] : cl.c[0], j == 2 ? cl.c[1] : cl.c[2]};
-    const uint32_t dec = (u << 15) + 1u;
-    uint32_t was[2], v[2], r[2], t[2];
+    // its cell in the first and in the second of the other sub-tables
+    const uint32_t own = j0 ? cl.at[0] : (j2 ? cl.at[2] : cl.at[1]);
+    const uint32_t c[2] = {j0 ? cl.at[1] : cl.at[0], j2 ? cl.at[1] : cl.at[2]};
+    const uint32_t dec = (u << kDegBits) + 1u;
+    uint32_t now[2], v[2], r[2], t[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-        was[i] = __hip_atomic_fetch_sub(p.meta(c[i]), dec, __ATOMIC_RELAXED, kScope);
-    const uint32_t x = __hip_atomic_load(p.value(own), __ATOMIC_RELAXED, kScope) ^
-                       ((cl.neg >> j) << 31);
+        now[i] = __hip_atomic_fetch_sub(p.meta(c[i]), dec, __ATOMIC_RELAXED, kScope) - dec;
+    uint32_t x = __hip_atomic_load(p.value(own), __ATOMIC_RELAXED, kScope);
 #pragma unroll
     for (int i = 0; i < 2; ++i) v[i] = __hip_atomic_load(p.value(c[i]), __ATOMIC_RELAXED, kScope);
-    p.word[u] = x;
+    __builtin_amdgcn_sched_barrier(0);  // (all five on their way before anything waits for one)
+    const uint32_t n0 = cl.neg << 27, n1 = cl.neg << 26, n2 = cl.neg << 25;  // the signs in bit 31
+    x ^= (j0 ? n0 : (j2 ? n2 : n1)) & kSign;
+    t[0] = x ^ ((j0 ? n1 : n0) & kSign);
+    t[1] = x ^ ((j2 ? n1 : n2) & kSign);
     auto minus = [&](int i) { return __float_as_uint(__uint_as_float(v[i]) - __uint_as_float(t[i])); };
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        t[i] = x ^ ((cl.neg >> k[i]) << 31);
-        r[i] = atomicCAS(p.value(c[i]), v[i], minus(i));
-    }
-    // Cells that came down to one unknown: was - dec is (that unknown << 15) | 1.  It is claimed
+    for (int i = 0; i < 2; ++i) r[i] = atomicCAS(p.value(c[i]), v[i], minus(i));
+    p.word[u] = x;
+    // Cells that came down to one unknown: its number is what is left of their sum.  It is claimed
     // in the order of the sub-tables: of two cells that it is left alone in now, it is read from
     // the first (which a wave's lanes settle by this order, and waves by who is first).
-    uint32_t had[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, left[2];
-    bool two[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        two[i] = (was[i] & kDegMask) == 2u;
-        left[i] = (was[i] - dec) >> 15;
-    }
+    const uint32_t left[2] = {now[0] >> kDegBits, now[1] >> kDegBits};
+    const bool one[2] = {uint16_t(now[0]) == 1u, uint16_t(now[1]) == 1u};
+    uint32_t had[2] = {0xFFFFFFFFu, 0xFFFFFFFFu}, mid = 0xFFFFFFFFu;
     auto claim = [&](uint32_t w) { return atomicOr(&p.claimed[w >> 5], 1u << (w & 31)); };
-    if (two[0] & (j != 0)) had[0] = claim(left[0]);
-    const uint32_t mid = j == 0 ? left[0] : left[1];
-    if ((j == 0 ? two[0] : two[1]) & (j != 1)) had[1] = claim(mid);
-    if (two[1] & (j != 2)) had[2] = claim(left[1]);
-    while ((r[0] != v[0]) | (r[1] != v[1])) {
-        // again, both together (one that was made already puts what it finds back)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const bool made = r[i] == v[i];
-            if (made) t[i] = 0u;
-            v[i] = r[i];
-            r[i] = atomicCAS(p.value(c[i]), v[i], made ? v[i] : minus(i));
-        }
-    }
-    const bool push[2] = {!(((j == 0 ? had[1] : had[0]) >> (left[0] & 31)) & 1u),
-                          !(((j == 2 ? had[1] : had[2]) >> (left[1] & 31)) & 1u)};
+    if (one[0] & !j0) had[0] = claim(left[0]);
+    if ((j0 & one[0]) | (j2 & one[1])) mid = claim(j0 ? left[0] : left[1]);
+    if (one[1] & !j2) had[1] = claim(left[1]);
+    if (j0) had[0] = mid;
+    if (j2) had[1] = mid;
+    const bool push[2] = {!((had[0] >> (left[0] & 31)) & 1u), !((had[1] >> (left[1] & 31)) & 1u)};
     const uint64_t b0 = __ballot(push[0]), b1 = __ballot(push[1]);
-    const uint32_t n0 = __popcll(b0), n1 = __popcll(b1);
-    if (n0 + n1 == 0) return;
-    const uint32_t at = take_slots(n_next, n0 + n1);
-    if (push[0]) next_queue[at + lanes_below(b0)] = uint16_t(left[0] | (k[0] << p.kUnknownBits));
-    if (push[1]) next_queue[at + n0 + lanes_below(b1)] = uint16_t(left[1] | (k[1] << p.kUnknownBits));
+    const uint32_t q0 = __popcll(b0), q1 = __popcll(b1);
+    if (q0 + q1) {
+        const uint32_t at = take_slots(n_next, q0 + q1);
+        if (push[0]) next_queue[at + lanes_below(b0)] = uint16_t(left[0] | (j0 ? kOne : 0u));
+        if (push[1]) next_queue[at + q0 + lanes_below(b1)] = uint16_t(left[1] | (j2 ? kOne : 2 * kOne));
+    }
+    // swaps that found another value are made again, both cells' together
+    while ((r[0] != v[0]) | (r[1] != v[1])) {
+        const bool again[2] = {r[0] != v[0], r[1] != v[1]};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (again[i]) {
+                v[i] = r[i];
+                r[i] = atomicCAS(p.value(c[i]), v[i], minus(i));
+            }
+    }
 }
 
-// The rounds of a partition whose first queue has s_n[1] entries, by NT threads that meet at
+// The rounds of a partition whose first queue has n_queued[1] entries, by NT threads that meet at
 // `barrier`: one barrier per round.  The queue's [head, tail) holds the unknowns that the round
 // before left alone in a cell.  A cell of degree 1 is touched by its own unknown only, so that
 // one may read its value there at any time; every other cell is only ever changed by atomics.
 // Removals of a round run concurrently with its readings, which changes
 // neither the set of unknowns the round resolves (an unknown left alone in a cell now is queued
 // for the next round) nor, beyond rounding order, their values.
-// s_n: per round the number of unknowns it queued for the next one, three slots used in turn:
+// n_queued: per round the number of unknowns it queued for the next one, three slots used in turn:
 // round r reads what round r-1 left in slot r%3 and adds to slot (r+1)%3, so a wave that is late
 // into round r never sees what faster waves of the same round already write; the slot nobody
 // touches in round r is cleared by thread 0 for its next use.  Returns the unknowns resolved.
 template <uint32_t NT, bool kPacked, typename Barrier>
 __device__ __forceinline__ uint32_t peel_rounds(const PartLds<kPacked> &p, uint32_t tid,
-                                                uint32_t (&s_n)[3], uint32_t &max_rounds,
-                                                Barrier &&barrier)
+                                            uint32_t &max_rounds, Barrier &&barrier)
 {
-    uint32_t head = 0;
-    for (uint32_t r = 1;; ++r) {
+    uint32_t head = 0, now = 1, next = 2, spare = 0;
+    for (uint32_t r = 0;; ++r) {
         barrier();  // queue, counts and cells of the previous round are complete
-        const uint32_t tail = head + s_n[r % 3];
+        const uint32_t tail = head + __builtin_amdgcn_readfirstlane(p.n_queued[now]);
         if (tail == head) {
-            max_rounds = max(max_rounds, r - 1);
+            max_rounds = max(max_rounds, r);
             return head;
         }
-        if (tid == 0) s_n[(r + 2) % 3] = 0;  // read in round r-1, added to again in round r+1
+        if (tid == 0) p.n_queued[spare] = 0;  // read in the round before, added to again in the next
         for (uint32_t e = head + tid; e < tail; e += NT)
-            resolve_unknown(p, p.queue[e], &s_n[(r + 1) % 3], p.queue + tail);
+            resolve_unknown(p, p.queue[e], &p.n_queued[next], p.queue + tail);
         head = tail;
+        const uint32_t was = now;
+        now = next;
+        next = spare;
+        spare = was;
     }
 }
 
@@ -307,8 +355,8 @@ __device__ __forceinline__ float unknown_value(const PartLds<kPacked> &p, uint32
     float r[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        const float cv = __uint_as_float(uint32_t(p.cell[cl.c[j]]));
-        r[j] = ((cl.neg >> j) & 1u) ? -cv : cv;
+        const float cv = __uint_as_float(*p.value(cl.at[j]));
+        r[j] = ((cl.neg >> (4 + j)) & 1u) ? -cv : cv;
     }
     return fmaxf(fminf(r[0], r[1]), fminf(fmaxf(r[0], r[1]), r[2]));
 }
@@ -513,7 +561,7 @@ __device__ __forceinline__ void join_cells(const PartLds<kPacked> &part, uint32_
             if (!kListed) idx_out[u] = i;
             const Cells cl = part.place(u, i);
 #pragma unroll
-            for (int j = 0; j < 3; ++j) atomicAdd(part.meta(cl.c[j]), (u << 15) + 1u);
+            for (int j = 0; j < 3; ++j) atomicAdd(part.meta(cl.at[j]), (u << kDegBits) + 1u);
         }
     }
 }
@@ -542,9 +590,8 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
             uint32_t *status, uint64_t seed, const uint32_t *__restrict__ salt, uint32_t T_cap,
             uint32_t P_cap, uint32_t mode)
 {
-    extern __shared__ uint64_t lds64[];
+    extern __shared__ __align__(16) uint64_t lds64[];
     PartLds<kPacked> part(lds64, T_cap, P_cap);
-    __shared__ uint32_t s_n[3];  // see peel_rounds
     const uint32_t tid = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
@@ -606,20 +653,25 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     const uint32_t Pa = uint32_t(uint64_t(a + 1) * U / A) - rho0;
     // the partition's hash functions: the seed under the salt the encoders used
     const uint32_t sa = salt[a];
-    part.sw0 = seed_word(seed, 3 * sa);
-    part.sw1 = seed_word(seed, 3 * sa + 1);
-    part.sw2 = seed_word(seed, 3 * sa + 2);
+    part.fsw0 = fold16(seed_word(seed, 3 * sa));
+    part.fsw1 = fold16(seed_word(seed, 3 * sa + 1));
+    part.fsw2 = fold16(seed_word(seed, 3 * sa + 2));
+
+    // (addresses that follow from the thread's number are made anew for every partition: kept from one
+    // to the next they take the registers that the prefetch needs)
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
 
     // ---- stage the partition's cells and unknowns from the registers, clear state
-    for (uint32_t c = tid; c < P_cap / 32 + 1; c += kDecodeThreads) part.claimed[c] = 0;
-    if (tid < 3) s_n[tid] = 0;
+    part.template clear<kDecodeThreads>(tid, cells, P_cap);
+    if (tid < 3) part.n_queued[tid] = 0;
     if (kListed) pre_list.put(part.word, Pa, tid);
     else pre_index.enumerate(index, part.word, Pa, rho0, wave);
     add_cells(1, n_in);
 #pragma unroll
     for (uint32_t q = 0; q < kCellPre; ++q) {
         const uint32_t c = tid + q * kDecodeThreads;
-        if (c < cells) part.cell[c] = __float_as_uint(pre_cell[0][q]);
+        if (c < cells) part.cell_value[c] = __float_as_uint(pre_cell[0][q]);
     }
     __syncthreads();
     PHASE_MARK(0);
@@ -629,11 +681,11 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     if (a + gridDim.x < A) prefetch(a + gridDim.x);
     __syncthreads();
     if (mode != TAGC_DECODE_ESTIMATE)  // estimation alone: the queue stays empty
-        queue_first<kDecodeThreads, (kCellPre + 2) / 3>(part, tid, &s_n[1], [] { __syncthreads(); });
+        queue_first<kDecodeThreads, (kCellPre + 2) / 3>(part, tid, [] { __syncthreads(); });
     PHASE_MARK(1);
 
     const uint32_t resolved =
-        peel_rounds<kDecodeThreads>(part, tid, s_n, max_rounds, [] { __syncthreads(); });
+        peel_rounds<kDecodeThreads>(part, tid, max_rounds, [] { __syncthreads(); });
     PHASE_MARK(2);
 
     // ---- values leave in one contiguous sweep (stored one by one as they were found they
@@ -690,15 +742,13 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
                 uint32_t *status, uint64_t seed, const uint32_t *__restrict__ salt,
                 uint32_t T_cap, uint32_t P_cap, uint32_t mode)
 {
-    extern __shared__ uint64_t lds64[];
+    extern __shared__ __align__(16) uint64_t lds64[];
     PartLds<true> part(lds64, T_cap, P_cap);
-    __shared__ uint32_t s_n[3];  // see peel_rounds
-    __shared__ uint32_t s_bar;   // peel_barrier's word
     const uint32_t tid = threadIdx.x;
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
     const uint32_t cells = 3 * m_sub;
-    if (tid == 0) s_bar = 0;
+    if (tid == 0) *part.bar = 0;
     __syncthreads();
 
     if (tid >= kPeelThreads) {
@@ -754,7 +804,7 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
 #pragma unroll
             for (uint32_t q = 0; q < kLoadCells; ++q) {
                 const uint32_t c = lt + q * kLoadThreads;
-                if (c < cells) part.cell[c] = __float_as_uint(acc[q]);
+                if (c < cells) part.cell_value[c] = __float_as_uint(acc[q]);
             }
             __syncthreads();  // the partition is staged
             if (a + gridDim.x < A) sum_partition(a + gridDim.x);
@@ -778,29 +828,30 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
     uint32_t bar_expected = 0, max_rounds = 0;
     part.m_sub = m_sub;
     for (uint32_t a = blockIdx.x; a < A; a += gridDim.x) {
+        uint32_t tid = threadIdx.x;  // (see peel_kernel)
+        asm volatile("" : "+v"(tid));
         const uint32_t rho0 = uint32_t(uint64_t(a) * U / A);
         const uint32_t Pa = uint32_t(uint64_t(a + 1) * U / A) - rho0;
         const uint32_t sa = salt[a];
-        part.sw0 = seed_word(seed, 3 * sa);
-        part.sw1 = seed_word(seed, 3 * sa + 1);
-        part.sw2 = seed_word(seed, 3 * sa + 2);
+        part.fsw0 = fold16(seed_word(seed, 3 * sa));
+        part.fsw1 = fold16(seed_word(seed, 3 * sa + 1));
+        part.fsw2 = fold16(seed_word(seed, 3 * sa + 2));
         __syncthreads();  // everybody is done with the previous partition
-        for (uint32_t c = tid; c < P_cap / 32 + 1; c += kPeelThreads) part.claimed[c] = 0;
-        if (tid < 3) s_n[tid] = 0;
+        part.clear<kPeelThreads>(tid, cells, P_cap);
+        if (tid < 3) part.n_queued[tid] = 0;
         __syncthreads();  // the loaders have staged the cells
 
         // (here and not before the barriers, where the loaders would wait for it)
         if (kListed) pre_list.put(part.word, Pa, tid);
         else pre_index.enumerate(index, part.word, Pa, rho0, wave);
-        peel_barrier(&s_bar, bar_expected);
+        peel_barrier(part.bar, bar_expected);
         join_cells<kPeelThreads, kPeelIdx, kListed>(part, tid, Pa, idx_out + rho0);
         if (a + gridDim.x < A) prefetch(a + gridDim.x);
-        peel_barrier(&s_bar, bar_expected);
+        peel_barrier(part.bar, bar_expected);
         if (mode != TAGC_DECODE_ESTIMATE)
-            queue_first<kPeelThreads, kPeelSlots>(part, tid, &s_n[1],
-                                                  [&] { peel_barrier(&s_bar, bar_expected); });
-        const uint32_t resolved = peel_rounds<kPeelThreads>(
-            part, tid, s_n, max_rounds, [&] { peel_barrier(&s_bar, bar_expected); });
+            queue_first<kPeelThreads, kPeelSlots>(part, tid, [&] { peel_barrier(part.bar, bar_expected); });
+        const uint32_t resolved =
+            peel_rounds<kPeelThreads>(part, tid, max_rounds, [&] { peel_barrier(part.bar, bar_expected); });
         for (uint32_t u = tid; u < Pa; u += kPeelThreads) val_out[rho0 + u] = unknown_value(part, u, mode);
         if (tid == 0) report_unresolved(Pa - resolved, mode, status);
     }
@@ -869,8 +920,8 @@ size_t decode_lds_bytes(uint32_t T_cap, uint32_t P_cap)
 {
     // PartLds; in the form that is not packed the queue is as long as there are cells, and 32
     // words are spare
-    const size_t queue = packed_slots(T_cap, P_cap) ? 3 * size_t(P_cap) : 2 * size_t(T_cap) + 128;
-    return size_t(T_cap) * 8 + (size_t(P_cap) + (P_cap / 32 + 1)) * 4 + queue + 16;
+    if (packed_slots(T_cap, P_cap)) return PartLds<true>::kPackedBytes;
+    return size_t(T_cap) * 10 + (size_t(P_cap) + (P_cap / 32 + 1)) * 4 + 144;
 }
 
 int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,

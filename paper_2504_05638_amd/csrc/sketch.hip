@@ -50,8 +50,8 @@ encode_kernel(const EncodeBatch, const uint32_t *__restrict__ header, uint64_t s
     const uint32_t cells = 3 * m_sub;
     // the partition's hash functions: the seed under the salt the Index aggregation chose
     const uint32_t sa = salt[a];
-    const uint32_t sw0 = seed_word(seed, 3 * sa), sw1 = seed_word(seed, 3 * sa + 1),
-                   sw2 = seed_word(seed, 3 * sa + 2);
+    const uint32_t fsw0 = fold16(seed_word(seed, 3 * sa)), fsw1 = fold16(seed_word(seed, 3 * sa + 1)),
+                   fsw2 = fold16(seed_word(seed, 3 * sa + 2));
     // the partition's run of the sorted pair list, found when the Index was aggregated
     const uint32_t lo = min(cnt[ranges_off + a], pair_cap);
     const uint32_t hi = min(cnt[ranges_off + a + 1], pair_cap);
@@ -60,11 +60,12 @@ encode_kernel(const EncodeBatch, const uint32_t *__restrict__ header, uint64_t s
     auto named = [&](uint32_t i) { return !mask || ((mask[i >> 5] >> (i & 31)) & 1u); };
     auto add = [&](uint32_t i, float v) {
         uint32_t neg;
-        uint32_t slot = hash_slot(i, sw0, m_sub, &neg);
+        const uint32_t fi = fold16(i);
+        uint32_t slot = hash_slot_folded(fi, fsw0, m_sub, &neg);
         lds_add_f32(&tile[slot], neg ? -v : v);
-        slot = hash_slot(i, sw1, m_sub, &neg);
+        slot = hash_slot_folded(fi, fsw1, m_sub, &neg);
         lds_add_f32(&tile[m_sub + slot], neg ? -v : v);
-        slot = hash_slot(i, sw2, m_sub, &neg);
+        slot = hash_slot_folded(fi, fsw2, m_sub, &neg);
         lds_add_f32(&tile[2 * m_sub + slot], neg ? -v : v);
     };
     // a thread's first pairs (all of them for a partition of up to 1024 pairs of this rank)

@@ -170,15 +170,19 @@ inline uint64_t index_words(uint64_t n_chunks) { return (2 * n_chunks + 1 + 8 * 
 
 // ------------------------------------------------------------------- hash
 
-__host__ __device__ inline uint32_t mix32(uint32_t x)
+__host__ __device__ inline uint32_t fold16(uint32_t x) { return x ^ (x >> 16); }
+
+// mix32 behind its first step
+__host__ __device__ inline uint32_t mix32_folded(uint32_t x)
 {
-    x ^= x >> 16;
     x *= 0x6A09E667u;
     x ^= x >> 15;
     x *= 0xBB67AE85u;
     x ^= x >> 16;
     return x;
 }
+
+__host__ __device__ inline uint32_t mix32(uint32_t x) { return mix32_folded(fold16(x)); }
 
 __host__ __device__ inline uint32_t seed_word(uint64_t seed, uint32_t j)
 {
@@ -187,16 +191,24 @@ __host__ __device__ inline uint32_t seed_word(uint64_t seed, uint32_t j)
 
 // slot in [0, m_sub) in the upper bits, sign flag (1 = negative) in bit 31... returned
 // separately: slot via multiply-shift range reduction, sign from the low hash bit.
-__host__ __device__ inline uint32_t hash_slot(uint32_t i, uint32_t sw, uint32_t m_sub,
-                                              uint32_t *neg)
+// The first step of mix32 is linear: fold16(i ^ sw) = fold16(i) ^ fold16(sw), so a kernel that takes
+// several hash functions of an index folds the index once and the seed words once per partition
+// (hash_slot_folded: two instructions less per hash function).
+__host__ __device__ inline uint32_t hash_slot_folded(uint32_t fi, uint32_t fsw, uint32_t m_sub,
+                                                     uint32_t *neg)
 {
-    uint32_t h = mix32(i ^ sw);
+    const uint32_t h = mix32_folded(fi ^ fsw);
     *neg = h & 1u;
 #if defined(__HIP_DEVICE_COMPILE__)
     return __umulhi(h, m_sub);
 #else
     return uint32_t((uint64_t(h) * m_sub) >> 32);
 #endif
+}
+
+__host__ __device__ inline uint32_t hash_slot(uint32_t i, uint32_t sw, uint32_t m_sub, uint32_t *neg)
+{
+    return hash_slot_folded(fold16(i), fold16(sw), m_sub, neg);
 }
 
 // ---------------------------------------------------------------- profile
