@@ -14,7 +14,8 @@
 // that have just become the last of a cell is all a round needs.  An unknown leaves a cell by an
 // atomic subtraction from that word, whose old degree tells whether another one joins the queue,
 // and by a compare-and-swap of the value.  It is queued once, with the cell it is to be read from:
-// for the first round that is its first cell of degree 1, later the one whose wave came first.
+// for the first round that is its first cell of degree 1 (every unknown looks at its three), later
+// the one whose wave came first.
 // (Float32 cells of an unknown that is alone in several agree up to rounding; cells that were
 // rounded to 16 bits on the wire differ by that rounding, and a value with them.)
 // Total work is proportional to the unknowns, not to unknowns x rounds.
@@ -46,25 +47,25 @@ namespace {
 
 constexpr uint32_t kDegBits = 16;  // of a cell's meta word: the degree
 
-// An unknown's three cells, as byte offsets into the arrays of values and of meta words.
+// LDS by address: a base in a scalar register and a constant of the instruction, which the compiler does
+// not see in a pointer to dynamic LDS (it adds the base, 0, to every address).
+template <typename T>
+__device__ __forceinline__ T *lds_at(uint32_t address)
+{
+    return (T *)(__attribute__((address_space(3))) T *)address;
+}
+__device__ __forceinline__ uint32_t lds_address(void *p)
+{
+    uint32_t a = uint32_t((uintptr_t)(__attribute__((address_space(3))) char *)p);
+    asm("" : "+s"(a));
+    return a;
+}
+
+// An unknown's three cells: see PartLds::value and meta.
 struct Cells {
     uint32_t at[3];
     uint32_t neg;  // bit 4 + j: sign of hash function j is -1
 };
-
-// (fsw: the folded seed words)
-__device__ inline Cells cells_of(uint32_t i, uint32_t m_sub, uint32_t fsw0, uint32_t fsw1,
-                                 uint32_t fsw2)
-{
-    Cells r;
-    uint32_t n0, n1, n2;
-    const uint32_t fi = fold16(i);
-    r.at[0] = 4 * hash_slot_folded(fi, fsw0, m_sub, &n0);
-    r.at[1] = 4 * (m_sub + hash_slot_folded(fi, fsw1, m_sub, &n1));
-    r.at[2] = 4 * (2 * m_sub + hash_slot_folded(fi, fsw2, m_sub, &n2));
-    r.neg = (n0 << 4) | (n1 << 5) | (n2 << 6);
-    return r;
-}
 
 // A partition in LDS.  The cells' values and their meta words are two arrays: a wave's accesses are to
 // one or the other at random cells, and interleaved they would all meet in half of the banks.
@@ -77,92 +78,124 @@ __device__ inline Cells cells_of(uint32_t i, uint32_t m_sub, uint32_t fsw0, uint
 // A queue entry is an unknown and which of its three cells it is alone in.
 //
 // The packed form's arrays lie where the default partition size has them, whatever the size: the offsets
-// of the first four are constants of the LDS instructions then (16 bits), and a cell's value and meta
+// of the first ones are constants of the LDS instructions then (16 bits), and a cell's value and meta
 // word share an address register.
 template <bool kPacked>
 struct PartLds {
-    uint32_t *cell_value;      // [T_cap]
-    uint32_t *cell_meta;       // [T_cap]
-    uint32_t *word;            // [P_cap] packed slots or c-index, then the value
-    uint32_t *claimed;         // [P_cap/32 + 1] unknowns that are, or were, in the queue
-    uint16_t *queue;           // unknown | sub-table of the cell << kUnknownBits, each unknown once
-    uint8_t *rest;             // [P_cap] packed: slot_2 >> 8, and the signs in bits 4 .. 6
-    uint32_t *n_queued;        // [3] see peel_rounds
-    uint32_t *bar;             // [1] see peel_barrier
-    uint32_t m_sub, fsw0, fsw1, fsw2;
-    static constexpr uint32_t kUnknownBits = kPacked ? 13 : 14;
+    static constexpr uint32_t kUnknownBits = kPacked ? 13 : 14, kOne = 1u << kUnknownBits;
     static_assert(kDefaultPartUnknowns <= 1u << 13 && kMaxPartUnknowns <= 1u << 14, "queue entry");
     static_assert(kDefaultPartCells <= 3u << 12, "packed slots are 12 bits");
-    static constexpr uint32_t kClaimWords = (kDefaultPartUnknowns / 32 + 1 + 3) & ~3u;
-    static constexpr size_t kPackedBytes = kDefaultPartCells * 8 + kClaimWords * 4 +
-                                           kDefaultPartUnknowns * 7 + 16;
+    // behind n_queued [3] and handed [4] (see peel_rounds), bar (see peel_barrier)
+    static constexpr uint32_t kValue = 32;
+    static constexpr uint32_t kClaimed = kValue + 4 * kDefaultPartCells;
+    static constexpr uint32_t kRest = kClaimed + 4 * ((kDefaultPartUnknowns / 32 + 1 + 3) & ~3u);
+    static constexpr uint32_t kMeta = kRest + kDefaultPartUnknowns;
+    static constexpr uint32_t kWord = kMeta + 4 * kDefaultPartCells;
+    static constexpr uint32_t kQueue = kWord + 4 * kDefaultPartUnknowns;
+    static constexpr uint32_t kPackedBytes = kQueue + 2 * kDefaultPartUnknowns;
+    static_assert(kMeta <= 0xFFFF && kMeta % 16 == 0, "offset of an LDS instruction, 16-byte stores");
 
-    __device__ __forceinline__ PartLds(void *lds, uint32_t T_cap, uint32_t P_cap)
+    uint32_t base;     // of all of it
+    uint32_t meta0;    // [T_cap] meta words
+    uint32_t word0;    // [P_cap] packed slots or c-index, then the value
+    uint32_t claim0;   // [P_cap/32 + 1] unknowns that are, or were, in the queue
+    uint32_t queue0;   // unknown | sub-table of the cell << kUnknownBits, each unknown once
+    uint32_t rest0;    // [P_cap] bytes, packed: slot_2 >> 8, and the signs in bits 4 .. 6
+    uint32_t cell[3];  // address of sub-table j, less kValue
+    uint32_t m_sub, fsw[3];  // folded seed words
+
+    __device__ __forceinline__ PartLds(void *lds, uint32_t T_cap, uint32_t P_cap, uint32_t m)
     {
-        n_queued = static_cast<uint32_t *>(lds);
-        bar = n_queued + 3;
-        cell_value = n_queued + 4;
+        base = lds_address(lds);
         if (kPacked) {
-            claimed = cell_value + kDefaultPartCells;
-            rest = reinterpret_cast<uint8_t *>(claimed + kClaimWords);
-            cell_meta = reinterpret_cast<uint32_t *>(rest + kDefaultPartUnknowns);
-            word = cell_meta + kDefaultPartCells;
-            queue = reinterpret_cast<uint16_t *>(word + kDefaultPartUnknowns);
+            meta0 = base + kMeta;
+            word0 = base + kWord;
+            claim0 = base + kClaimed;
+            queue0 = base + kQueue;
+            rest0 = base + kRest;
         } else {
-            cell_meta = cell_value + T_cap;
-            word = cell_meta + T_cap;
-            claimed = word + P_cap;
-            queue = reinterpret_cast<uint16_t *>(claimed + P_cap / 32 + 1);
-            rest = nullptr;
+            meta0 = base + kValue + 4 * T_cap;
+            word0 = meta0 + 4 * T_cap;
+            claim0 = word0 + 4 * P_cap;
+            queue0 = claim0 + 4 * (P_cap / 32 + 1);
+            rest0 = 0;
         }
+        m_sub = m;
+        for (uint32_t j = 0; j < 3; ++j) cell[j] = base + 4 * j * m;
     }
-    // of the cell at a byte offset
-    __device__ __forceinline__ uint32_t *value(uint32_t at) const
-    {
-        return reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(cell_value) + at);
-    }
+    __device__ __forceinline__ uint32_t *value(uint32_t at) const { return lds_at<uint32_t>(at + kValue); }
     __device__ __forceinline__ uint32_t *meta(uint32_t at) const
     {
-        return reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(cell_meta) + at);
+        return lds_at<uint32_t>(kPacked ? at + kMeta : at + (meta0 - base));
     }
-    // nobody in the first `cells` cells, no unknown claimed (by NT threads)
+    __device__ __forceinline__ uint32_t *word(uint32_t u) const { return lds_at<uint32_t>(word0 + 4 * u); }
+    __device__ __forceinline__ uint8_t *rest(uint32_t u) const
+    {
+        return lds_at<uint8_t>(kPacked ? base + u + kRest : rest0 + u);
+    }
+    // the claims of the 32 unknowns that w / 32 names
+    __device__ __forceinline__ uint32_t *claims(uint32_t w) const
+    {
+        return lds_at<uint32_t>(kPacked ? base + 4 * (w >> 5) + kClaimed : claim0 + 4 * (w >> 5));
+    }
+    __device__ __forceinline__ uint16_t *queue(uint32_t e) const { return lds_at<uint16_t>(queue0 + 2 * e); }
+    __device__ __forceinline__ uint32_t *n_queued(uint32_t i) const { return lds_at<uint32_t>(base + 4 * i); }
+    __device__ __forceinline__ uint32_t *bar() const { return lds_at<uint32_t>(base + 12); }
+    __device__ __forceinline__ uint4 *handed() const { return lds_at<uint4>(base + 16); }
+    // nobody in the first `cells` cells, nothing queued (by NT threads)
     template <uint32_t NT>
-    __device__ __forceinline__ void clear(uint32_t tid, uint32_t cells, uint32_t P_cap) const
+    __device__ __forceinline__ void clear(uint32_t tid, uint32_t cells) const
     {
         if (kPacked) {
-            uint4 *m = reinterpret_cast<uint4 *>(cell_meta);
 #pragma unroll
             for (uint32_t i = 0; i < kDefaultPartCells / 4; i += NT)
-                if (4 * (i + tid) < cells) m[i + tid] = make_uint4(0, 0, 0, 0);
+                if (4 * (i + tid) < cells) *lds_at<uint4>(meta0 + 16 * (i + tid)) = make_uint4(0, 0, 0, 0);
         } else {
-            for (uint32_t c = tid; c < cells; c += NT) cell_meta[c] = 0;
+            for (uint32_t c = tid; c < cells; c += NT) *lds_at<uint32_t>(meta0 + 4 * c) = 0;
         }
-        for (uint32_t c = tid; c < P_cap / 32 + 1; c += NT) claimed[c] = 0;
+        if (tid < 3) *n_queued(tid) = 0;
+    }
+    __device__ __forceinline__ void seed(uint64_t s, uint32_t salt)
+    {
+        for (uint32_t j = 0; j < 3; ++j) fsw[j] = fold16(seed_word(s, 3 * salt + j));
     }
     // unknown u has c-index i: keeps what of_unknown needs, and returns the cells
     __device__ __forceinline__ Cells place(uint32_t u, uint32_t i) const
     {
-        const Cells cl = cells_of(i, m_sub, fsw0, fsw1, fsw2);
+        uint32_t slot[3], neg[3];
+        const uint32_t fi = fold16(i);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) slot[j] = hash_slot_folded(fi, fsw[j], m_sub, &neg[j]);
+        Cells r;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) r.at[j] = cell[j] + 4 * slot[j];
+        r.neg = (neg[0] << 4) | (neg[1] << 5) | (neg[2] << 6);
         if (kPacked) {
-            const uint32_t s1 = cl.at[1] - 4 * m_sub, s2 = cl.at[2] - 8 * m_sub;
-            word[u] = (cl.at[0] >> 2) | (s1 << 10) | (s2 << 22);
-            rest[u] = uint8_t((s2 >> 10) | cl.neg);
+            *word(u) = slot[0] | (slot[1] << 12) | (slot[2] << 24);
+            *rest(u) = uint8_t((slot[2] >> 8) | r.neg);
         } else {
-            word[u] = i;
+            *word(u) = i;
         }
-        return cl;
+        return r;
     }
     // an unresolved unknown's cells
     __device__ __forceinline__ Cells of_unknown(uint32_t u) const
     {
-        const uint32_t w = word[u];
-        if (!kPacked) return cells_of(w, m_sub, fsw0, fsw1, fsw2);
-        const uint32_t b = rest[u];
         Cells r;
-        r.at[0] = (w & 0xFFFu) * 4;
-        r.at[1] = ((w >> 12) & 0xFFFu) * 4 + 4 * m_sub;
-        r.at[2] = (__builtin_amdgcn_alignbit(b, w, 24) & 0xFFFu) * 4 + 8 * m_sub;
-        r.neg = b;
+        const uint32_t w = *word(u);
+        if (kPacked) {
+            const uint32_t b = *rest(u);
+            r.at[0] = cell[0] + 4 * (w & 0xFFFu);
+            r.at[1] = cell[1] + 4 * ((w >> 12) & 0xFFFu);
+            r.at[2] = cell[2] + 4 * (__builtin_amdgcn_alignbit(b, w, 24) & 0xFFFu);
+            r.neg = b;
+            return r;
+        }
+        uint32_t neg[3];
+        const uint32_t fi = fold16(w);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) r.at[j] = cell[j] + 4 * hash_slot_folded(fi, fsw[j], m_sub, &neg[j]);
+        r.neg = (neg[0] << 4) | (neg[1] << 5) | (neg[2] << 6);
         return r;
     }
 };
@@ -186,128 +219,148 @@ __device__ __forceinline__ uint32_t take_slots(uint32_t *count, uint32_t n)
     return __builtin_amdgcn_readlane(at, leader);
 }
 
-// The first round's queue: the unknowns alone in a cell from the start, each with the first
-// sub-table where it is.  Thread t looks at the cells t, t + NT, ... of every sub-table, kSlots of
-// them at most, all at once; one LDS atomic per wave.  Whoever sets an unknown's bit in `claimed`
-// queues it; the sub-tables take turns, so that which of its cells an unknown is read from does
-// not depend on the order of the waves (cells that were rounded on the wire differ).
-template <uint32_t NT, uint32_t kSlots, bool kPacked, typename Barrier>
-__device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t tid, Barrier &&barrier)
+// The partition's n unknowns, whose c-indices are in their words, join their cells: thread t has the
+// unknowns t, t + NT, ..., kIdx of them at most.  Writes the c-indices out on the way, unless kListed
+// (they are there already).
+template <uint32_t NT, uint32_t kIdx, bool kListed, bool kPacked>
+__device__ __forceinline__ void join_cells(const PartLds<kPacked> &p, uint32_t tid, uint32_t n,
+                                           uint32_t *idx_out, uint32_t (&at)[kIdx][3])
 {
-    uint32_t u[3][kSlots], mine = 0, n = 0;
-    static_assert(3 * kSlots <= 32, "a bit per cell");
 #pragma unroll
-    for (uint32_t j = 0; j < 3; ++j)
+    for (uint32_t q = 0; q < kIdx; ++q) {
+        const uint32_t u = tid + q * NT;
 #pragma unroll
-        for (uint32_t q = 0; q < kSlots; ++q) {
-            const uint32_t c = tid + q * NT;
-            u[j][q] = c < p.m_sub ? p.cell_meta[j * p.m_sub + c] : 0u;
-        }
+        for (int j = 0; j < 3; ++j) at[q][j] = p.cell[j];
+        if (u < n) {
+            const uint32_t i = *p.word(u);
+            if (!kListed) idx_out[u] = i;
+            const Cells cl = p.place(u, i);
 #pragma unroll
-    for (uint32_t j = 0; j < 3; ++j) {
-        uint32_t had[kSlots];
-        if (j) barrier();
-#pragma unroll
-        for (uint32_t q = 0; q < kSlots; ++q) {
-            had[q] = 0xFFFFFFFFu;
-            const bool one = uint16_t(u[j][q]) == 1u;
-            u[j][q] >>= kDegBits;
-            if (one) had[q] = atomicOr(&p.claimed[u[j][q] >> 5], 1u << (u[j][q] & 31));
-        }
-#pragma unroll
-        for (uint32_t q = 0; q < kSlots; ++q) {
-            const bool queued = !((had[q] >> (u[j][q] & 31)) & 1u);
-            mine |= uint32_t(queued) << (j * kSlots + q);
-            n += __popcll(__ballot(queued));
+            for (int j = 0; j < 3; ++j) {
+                at[q][j] = cl.at[j];
+                atomicAdd(p.meta(cl.at[j]), (u << kDegBits) + 1u);
+            }
         }
     }
-    if (n == 0) return;
-    uint32_t at = take_slots(&p.n_queued[1], n);
+}
+
+// The first round's queue: the unknowns alone in a cell once all have joined (with the first sub-table
+// where it is), which every unknown's own thread finds out from its three cells, so nothing has to
+// be claimed and the claims are written whole.  `any`: not if only estimates are wanted.  (Cell by
+// cell, with claims in the order of the sub-tables and two barriers for that: three times the
+// instructions.  This, the requests in PartAhead and the stores waited for in wait_loads: everything but the
+// rounds 23.9 K -> 18.5 K clocks a partition; decoders of 2 ranks of 202 M entries 586 -> 553 us.)
+template <uint32_t NT, uint32_t kIdx, bool kPacked>
+__device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t tid, uint32_t n, bool any,
+                                            const uint32_t (&at)[kIdx][3])
+{
+    constexpr uint32_t kOne = PartLds<kPacked>::kOne;
+    const uint32_t lane = lane_id();
+    constexpr uint32_t kBatch = kIdx > 12 ? 2 : 4;  // whose cells are requested together
+    uint32_t entry[kIdx], total = 0;
+    uint64_t alone[kIdx];
 #pragma unroll
-    for (uint32_t j = 0; j < 3; ++j)
+    for (uint32_t q0 = 0; q0 < kIdx; q0 += kBatch) {
+        uint32_t deg[kBatch][3];
 #pragma unroll
-        for (uint32_t q = 0; q < kSlots; ++q) {
-            const bool queued = (mine >> (j * kSlots + q)) & 1u;
-            const uint64_t bal = __ballot(queued);
-            if (queued) p.queue[at + lanes_below(bal)] = uint16_t(u[j][q] | (j << p.kUnknownBits));
-            at += uint32_t(__popcll(bal));
+        for (uint32_t q = q0; q < kIdx && q < q0 + kBatch; ++q)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) deg[q - q0][j] = *p.meta(at[q][j]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (uint32_t q = q0; q < kIdx && q < q0 + kBatch; ++q) {
+            const uint32_t u = tid + q * NT, *d = deg[q - q0];
+            const bool one[3] = {uint16_t(d[0]) == 1u, uint16_t(d[1]) == 1u, uint16_t(d[2]) == 1u};
+            entry[q] = u | (one[0] ? 0u : (one[1] ? kOne : 2 * kOne));
+            alone[q] = __ballot((one[0] | one[1] | one[2]) & (u < n) & any);
+            total += uint32_t(__popcll(alone[q]));
+            // (lanes 0 and 1 have a word of the wave's 64 claims each)
+            const uint32_t w = u - lane + 32 * lane;
+            if (lane < 2 && w < n) *p.claims(w) = uint32_t(alone[q] >> (32 * lane));
         }
+    }
+    if (total == 0) return;
+    uint32_t to = take_slots(p.n_queued(1), total);
+#pragma unroll
+    for (uint32_t q = 0; q < kIdx; ++q) {
+        if ((alone[q] >> lane) & 1u) *p.queue(to + lanes_below(alone[q])) = uint16_t(entry[q]);
+        to += uint32_t(__popcll(alone[q]));
+    }
 }
 
 // One queue entry: an unknown that is alone in its cell `own`.  Its value is read there (nobody
 // else touches a cell of degree 1) and taken out of its two other cells; an unknown that is
-// thereby left alone in one is queued for the next round.  Called by any subset of a wave's lanes.
+// thereby left alone in one is queued for the next round, from the place on that `room` has for a number
+// of them.  Called by any subset of a wave's lanes; returns how many they queued.
 //
 // A round is a chain of dependent LDS accesses: entry -> slots -> own value, the other cells' values
 // and their degrees (counted down on the way) -> the new values, and claims for the next queue ->
 // queue.  Every link goes out for all cells together.  The values are swapped right behind
 // their reading: cells are shared by unknowns that leave in the same round (in nearly every round of a
 // wave), and a swap that finds another value has to be made again, that one alone: made again together
-// with one that had succeeded it took three tries, at some 200 clocks each.  A wave with a handful of
-// entries takes 700 clocks for them, 16 full ones 2100: some 110 vector instructions each, 4 clocks
-// apiece on their SIMD.  Rounds of a partition, clocks, before and after, the arrays of PartLds
-// included: 8192 unknowns in 12288 cells (11 rounds) 38.8 K -> 32.0 K; in 10776 cells (21 rounds) 51.1 K ->
-// 43.3 K; decoders of the latter, 2 ranks of 202 M entries, 647 -> 586 us.  (A queue for every wave,
-// without a shared count: 826 us, every wave then has a few entries of every small round.)
-template <bool kPacked>
-__device__ __forceinline__ void resolve_unknown(const PartLds<kPacked> &p, uint32_t entry,
-                                                uint32_t *n_next, uint16_t *next_queue)
+// with one that had succeeded it took three tries, at some 200 clocks each.  A wave with one entry
+// takes 1100 clocks for it, one with 64 1700 (two more tries), 16 full ones 2100 and a barrier 400: latency and the
+// wave's own 130 instructions (fewer vector instructions, 87 for 110, changed nothing).  Rounds of a
+// partition, clocks, before the arrays were as in PartLds and failed swaps repeated alone, and after: 8192
+// unknowns in 12288 cells (11 rounds) 38.8 K -> 32.0 K; in 10776 cells (21 rounds) 51.1 K -> 43.3 K; decoders of
+// the latter, 2 ranks of 202 M entries, 647 -> 586 us.  (A queue for every wave, without a shared count:
+// 826 us, every wave then has a few entries of every small round.)
+template <bool kPacked, typename Room>
+__device__ __forceinline__ uint32_t resolve_unknown(const PartLds<kPacked> &p, uint32_t entry, Room &&room)
 {
     constexpr int kScope = __HIP_MEMORY_SCOPE_WORKGROUP;
-    constexpr uint32_t kSign = 0x80000000u, kOne = 1u << PartLds<kPacked>::kUnknownBits;
+    constexpr uint32_t kSign = 0x80000000u, kOne = PartLds<kPacked>::kOne;
     const uint32_t u = entry & (kOne - 1u);
     const bool j0 = entry < kOne, j2 = entry >= 2 * kOne;  // the sub-table of its own cell is 0; is 2
     const Cells cl = p.of_unknown(u);
     // its cell in the first and in the second of the other sub-tables
     const uint32_t own = j0 ? cl.at[0] : (j2 ? cl.at[2] : cl.at[1]);
-    const uint32_t c[2] = {j0 ? cl.at[1] : cl.at[0], j2 ? cl.at[1] : cl.at[2]};
+    const uint32_t c0 = j0 ? cl.at[1] : cl.at[0], c1 = j2 ? cl.at[1] : cl.at[2];
     const uint32_t dec = (u << kDegBits) + 1u;
-    uint32_t now[2], v[2], r[2], t[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-        now[i] = __hip_atomic_fetch_sub(p.meta(c[i]), dec, __ATOMIC_RELAXED, kScope) - dec;
+    const uint32_t now0 = __hip_atomic_fetch_sub(p.meta(c0), dec, __ATOMIC_RELAXED, kScope) - dec;
+    const uint32_t now1 = __hip_atomic_fetch_sub(p.meta(c1), dec, __ATOMIC_RELAXED, kScope) - dec;
     uint32_t x = __hip_atomic_load(p.value(own), __ATOMIC_RELAXED, kScope);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) v[i] = __hip_atomic_load(p.value(c[i]), __ATOMIC_RELAXED, kScope);
+    uint32_t v0 = __hip_atomic_load(p.value(c0), __ATOMIC_RELAXED, kScope);
+    uint32_t v1 = __hip_atomic_load(p.value(c1), __ATOMIC_RELAXED, kScope);
     __builtin_amdgcn_sched_barrier(0);  // (all five on their way before anything waits for one)
     const uint32_t n0 = cl.neg << 27, n1 = cl.neg << 26, n2 = cl.neg << 25;  // the signs in bit 31
     x ^= (j0 ? n0 : (j2 ? n2 : n1)) & kSign;
-    t[0] = x ^ ((j0 ? n1 : n0) & kSign);
-    t[1] = x ^ ((j2 ? n1 : n2) & kSign);
-    auto minus = [&](int i) { return __float_as_uint(__uint_as_float(v[i]) - __uint_as_float(t[i])); };
-#pragma unroll
-    for (int i = 0; i < 2; ++i) r[i] = atomicCAS(p.value(c[i]), v[i], minus(i));
-    p.word[u] = x;
+    const uint32_t t0 = x ^ ((j0 ? n1 : n0) & kSign), t1 = x ^ ((j2 ? n1 : n2) & kSign);
+    auto minus = [](uint32_t v, uint32_t t) { return __float_as_uint(__uint_as_float(v) - __uint_as_float(t)); };
+    uint32_t r0 = atomicCAS(p.value(c0), v0, minus(v0, t0));
+    uint32_t r1 = atomicCAS(p.value(c1), v1, minus(v1, t1));
+    *p.word(u) = x;
     // Cells that came down to one unknown: its number is what is left of their sum.  It is claimed
     // in the order of the sub-tables: of two cells that it is left alone in now, it is read from
     // the first (which a wave's lanes settle by this order, and waves by who is first).
-    const uint32_t left[2] = {now[0] >> kDegBits, now[1] >> kDegBits};
-    const bool one[2] = {uint16_t(now[0]) == 1u, uint16_t(now[1]) == 1u};
-    uint32_t had[2] = {0xFFFFFFFFu, 0xFFFFFFFFu}, mid = 0xFFFFFFFFu;
-    auto claim = [&](uint32_t w) { return atomicOr(&p.claimed[w >> 5], 1u << (w & 31)); };
-    if (one[0] & !j0) had[0] = claim(left[0]);
-    if ((j0 & one[0]) | (j2 & one[1])) mid = claim(j0 ? left[0] : left[1]);
-    if (one[1] & !j2) had[1] = claim(left[1]);
-    if (j0) had[0] = mid;
-    if (j2) had[1] = mid;
-    const bool push[2] = {!((had[0] >> (left[0] & 31)) & 1u), !((had[1] >> (left[1] & 31)) & 1u)};
-    const uint64_t b0 = __ballot(push[0]), b1 = __ballot(push[1]);
+    const uint32_t left0 = now0 >> kDegBits, left1 = now1 >> kDegBits;
+    const bool one0 = uint16_t(now0) == 1u, one1 = uint16_t(now1) == 1u;
+    uint32_t had0 = 0xFFFFFFFFu, mid = 0xFFFFFFFFu, had1 = 0xFFFFFFFFu;
+    auto claim = [&](uint32_t w) { return atomicOr(p.claims(w), 1u << (w & 31)); };
+    if (one0 & !j0) had0 = claim(left0);
+    if ((j0 & one0) | (j2 & one1)) mid = claim(j0 ? left0 : left1);
+    if (one1 & !j2) had1 = claim(left1);
+    if (j0) had0 = mid;
+    if (j2) had1 = mid;
+    const bool push0 = !((had0 >> (left0 & 31)) & 1u), push1 = !((had1 >> (left1 & 31)) & 1u);
+    const uint64_t b0 = __ballot(push0), b1 = __ballot(push1);
     const uint32_t q0 = __popcll(b0), q1 = __popcll(b1);
     if (q0 + q1) {
-        const uint32_t at = take_slots(n_next, q0 + q1);
-        if (push[0]) next_queue[at + lanes_below(b0)] = uint16_t(left[0] | (j0 ? kOne : 0u));
-        if (push[1]) next_queue[at + q0 + lanes_below(b1)] = uint16_t(left[1] | (j2 ? kOne : 2 * kOne));
+        const uint32_t to = room(q0 + q1);
+        if (push0) *p.queue(to + lanes_below(b0)) = uint16_t(left0 | (j0 ? kOne : 0u));
+        if (push1) *p.queue(to + q0 + lanes_below(b1)) = uint16_t(left1 | (j2 ? kOne : 2 * kOne));
     }
-    // swaps that found another value are made again, both cells' together
-    while ((r[0] != v[0]) | (r[1] != v[1])) {
-        const bool again[2] = {r[0] != v[0], r[1] != v[1]};
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            if (again[i]) {
-                v[i] = r[i];
-                r[i] = atomicCAS(p.value(c[i]), v[i], minus(i));
-            }
+    // Swaps that found another value are made again, one a time: a lane rarely has two.
+    while ((r0 != v0) | (r1 != v1)) {
+        const bool first = r0 != v0;
+        const uint32_t v = first ? r0 : r1;
+        const uint32_t r = atomicCAS(p.value(first ? c0 : c1), v, minus(v, first ? t0 : t1));
+        v0 = first ? v : v0;
+        r0 = first ? r : r0;
+        v1 = first ? v1 : v;
+        r1 = first ? r1 : r;
     }
+    return q0 + q1;
 }
 
 // The rounds of a partition whose first queue has n_queued[1] entries, by NT threads that meet at
@@ -321,21 +374,49 @@ __device__ __forceinline__ void resolve_unknown(const PartLds<kPacked> &p, uint3
 // round r reads what round r-1 left in slot r%3 and adds to slot (r+1)%3, so a wave that is late
 // into round r never sees what faster waves of the same round already write; the slot nobody
 // touches in round r is cleared by thread 0 for its next use.  Returns the unknowns resolved.
+//
+// Rounds of up to 64 entries, of which most peels have a few and one that gets stuck has dozens, are left to
+// one wave: it goes on without barriers and without a shared count until the queue is empty or longer.
+// (119 partitions of 8166 unknowns in 9393 cells, stuck after 40 rounds: rounds 33.4 K -> 29.0 K clocks, decoder
+// 45 -> 39 us.)
 template <uint32_t NT, bool kPacked, typename Barrier>
 __device__ __forceinline__ uint32_t peel_rounds(const PartLds<kPacked> &p, uint32_t tid,
-                                            uint32_t &max_rounds, Barrier &&barrier)
+                                                uint32_t &max_rounds, Barrier &&barrier)
 {
+    const uint32_t lane = lane_id();
+    auto uniform = [](uint32_t x) -> uint32_t { return __builtin_amdgcn_readfirstlane(x); };
     uint32_t head = 0, now = 1, next = 2, spare = 0;
     for (uint32_t r = 0;; ++r) {
         barrier();  // queue, counts and cells of the previous round are complete
-        const uint32_t tail = head + __builtin_amdgcn_readfirstlane(p.n_queued[now]);
-        if (tail == head) {
+        uint32_t n = uniform(*p.n_queued(now));
+        if (n - 1 < 64) {
+            if (uniform(tid >> 6) == 0) {
+                uint32_t h = head, rounds = r;
+                do {
+                    uint32_t queued = 0;
+                    if (lane < n)
+                        queued = resolve_unknown(p, *p.queue(h + lane), [&](uint32_t) { return h + n; });
+                    h += n;
+                    n = uniform(queued);  // (lane 0 had an entry)
+                    ++rounds;
+                } while (n - 1 < 64);
+                if (lane == 0) *p.handed() = make_uint4(h, n, rounds, 0);
+            }
+            barrier();
+            const uint4 left = *p.handed();
+            head = uniform(left.x);
+            n = uniform(left.y);
+            r = uniform(left.z);
+        }
+        if (n == 0) {
             max_rounds = max(max_rounds, r);
             return head;
         }
-        if (tid == 0) p.n_queued[spare] = 0;  // read in the round before, added to again in the next
+        if (tid == 0) *p.n_queued(spare) = 0;  // read in the round before, added to again in the next
+        const uint32_t tail = head + n;
         for (uint32_t e = head + tid; e < tail; e += NT)
-            resolve_unknown(p, p.queue[e], &p.n_queued[next], p.queue + tail);
+            resolve_unknown(p, *p.queue(e),
+                            [&](uint32_t more) { return tail + take_slots(p.n_queued(next), more); });
         head = tail;
         const uint32_t was = now;
         now = next;
@@ -349,7 +430,7 @@ __device__ __forceinline__ uint32_t peel_rounds(const PartLds<kPacked> &p, uint3
 template <bool kPacked>
 __device__ __forceinline__ float unknown_value(const PartLds<kPacked> &p, uint32_t u, uint32_t mode)
 {
-    if ((p.claimed[u >> 5] >> (u & 31)) & 1u) return __uint_as_float(p.word[u]);
+    if ((*p.claims(u) >> (u & 31)) & 1u) return __uint_as_float(*p.word(u));
     if (mode == TAGC_DECODE_PEEL) return 0.0f;
     const Cells cl = p.of_unknown(u);
     float r[3];
@@ -432,7 +513,7 @@ struct PartIndex {
     uint32_t lo, hi;        // the partition's c-indices
     uint32_t g_end;         // behind its last group; 0 if it has no unknowns, and so no groups
     uint32_t word[kPre];    // word `lane` of the wave's groups
-    uint32_t before;        // lane i: set bits of the whole Index before the i-th of them
+    uint32_t before[2];     // lane i: set bits of the whole Index before the i-th of them, to be added up
 
     static constexpr uint32_t kTail = 8;
     static_assert(kPre <= 64, "a lane per group");
@@ -445,10 +526,10 @@ struct PartIndex {
     {
         return v.chunkpre[g / 16] + (g < v.n_chunks * 16 ? v.grouppre[g] : 0u);
     }
-    __device__ __forceinline__ void request(const IndexView &v, uint32_t a, uint32_t wave)
+    __device__ __forceinline__ void request(const IndexView &v, uint32_t from, uint32_t to, uint32_t wave)
     {
-        lo = v.bounds[a];
-        hi = v.bounds[a + 1];
+        lo = from;
+        hi = to;
         // (lo == hi where partitions outnumber the non-zeros, and both are 0 if c-index 0 is one;
         // no group lies behind the Index whatever the bounds hold)
         g_end = lo < hi ? min((hi - 1) / (32 * kGroupWords) + 1, (v.n_words + kGroupWords - 1) / kGroupWords)
@@ -457,7 +538,10 @@ struct PartIndex {
 #pragma unroll
         for (uint32_t i = 0; i < kPre; ++i) word[i] = load(v, g0 + i * NW);
         const uint32_t gl = g0 + lane_id() * NW;
-        before = lane_id() < kPre && gl < g_end ? bits_before(v, gl) : 0u;
+        // (added up where they are needed: nothing here waits for a load)
+        const bool ok = lane_id() < kPre && gl < g_end;
+        before[0] = ok ? v.chunkpre[gl / 16] : 0u;
+        before[1] = ok && gl < v.n_chunks * 16 ? v.grouppre[gl] : 0u;
     }
     // word `lane` of group g, with `pre` set bits before the group: its unknowns' c-indices
     __device__ __forceinline__ void expand(uint32_t *out, uint32_t n, uint32_t rho0, uint32_t g,
@@ -480,11 +564,11 @@ struct PartIndex {
     __device__ __forceinline__ void enumerate(const IndexView &v, uint32_t *out, uint32_t n,
                                               uint32_t rho0, uint32_t wave) const
     {
-        const uint32_t g0 = lo / (32 * kGroupWords) + wave;
+        const uint32_t g0 = lo / (32 * kGroupWords) + wave, pre = before[0] + before[1];
 #pragma unroll
         for (uint32_t i = 0; i < kPre; ++i)
             if (g0 + i * NW < g_end)
-                expand(out, n, rho0, g0 + i * NW, word[i], __builtin_amdgcn_readlane(before, i));
+                expand(out, n, rho0, g0 + i * NW, word[i], __builtin_amdgcn_readlane(pre, i));
         // The rest (partitions of far fewer unknowns than the plan has room for), 64 of the wave's
         // groups at a time, a lane finding out what lies before each and whether it holds anything:
         // kTail of those that do are on their way together.  (Four at a time, holding anything or
@@ -547,26 +631,59 @@ __device__ __forceinline__ GlobalCells rank_sketch(uint32_t r)
     return (GlobalCells)ka[r];
 }
 
-// The partition's unknowns, whose c-indices are in part.word, join their cells; all values start
-// at 0.  Writes the c-indices out on the way, unless kListed (they are there already).
-template <uint32_t NT, uint32_t kIdx, bool kListed, bool kPacked>
-__device__ __forceinline__ void join_cells(const PartLds<kPacked> &part, uint32_t tid, uint32_t n,
-                                           uint32_t *idx_out)
-{
-#pragma unroll
-    for (uint32_t q = 0; q < kIdx; ++q) {
-        const uint32_t u = tid + q * NT;
-        if (u < n) {
-            const uint32_t i = part.word[u];
-            if (!kListed) idx_out[u] = i;
-            const Cells cl = part.place(u, i);
-#pragma unroll
-            for (int j = 0; j < 3; ++j) atomicAdd(part.meta(cl.at[j]), (u << kDegBits) + 1u);
-        }
-    }
-}
+// A workgroup's partitions a, a + step, ...: partition a has the unknowns [aU/A, (a+1)U/A).  (Divided once
+// and counted on: a 64-bit division is some hundred scalar instructions, for every wave.)
+struct Partitions {
+    uint32_t A, a, step;
+    uint32_t rho, rem;            // aU/A, and what is left of it
+    uint32_t rho_step, rem_step;  // of step * U
+    uint32_t rho_one, rem_one;    // of U
 
-// Peels sketch partitions: unknowns rho0 .. rho0+Pa-1 in order of c-index, cells a*3*m_sub ...
+    __device__ __forceinline__ Partitions(uint32_t U, uint32_t n, uint32_t first, uint32_t by)
+        : A(n), a(first), step(by)
+    {
+        rho = uint32_t(uint64_t(a) * U / A);
+        rem = uint32_t(uint64_t(a) * U - uint64_t(rho) * A);
+        rho_step = uint32_t(uint64_t(step) * U / A);
+        rem_step = uint32_t(uint64_t(step) * U - uint64_t(rho_step) * A);
+        rho_one = U / A;
+        rem_one = U % A;
+    }
+    __device__ __forceinline__ uint32_t unknowns() const { return rho_one + (rem >= A - rem_one); }
+    __device__ __forceinline__ void next()
+    {
+        const uint32_t carry = rem >= A - rem_step;
+        rho += rho_step + carry;
+        rem = carry ? rem - (A - rem_step) : rem + rem_step;
+        a += step;
+    }
+};
+
+// Bounds and salt of a partition, requested a partition before they say what else to request.  They were
+// written by the kernel before on some other compute die, so they take a microsecond or two: waited for
+// where they were needed, they and what waited behind them were 5 K of a partition's 67 K clocks.
+struct PartAhead {
+    uint32_t v;  // lanes 0 and 1: the bounds, lane 2: the salt
+    __device__ __forceinline__ void request(const IndexView &index, const uint32_t *salt, uint32_t a,
+                                            uint32_t A)
+    {
+        v = 0;
+        if (a < A) first(index, salt, a);
+    }
+    // (the grid has no workgroups beyond the room for partitions; the salts lie behind the bounds)
+    __device__ __forceinline__ void first(const IndexView &index, const uint32_t *salt, uint32_t a)
+    {
+        const uint32_t lane = lane_id();
+        v = index.bounds[a + (lane == 2 ? uint32_t(salt - index.bounds) : uint32_t(lane == 1))];
+    }
+    __device__ __forceinline__ uint32_t get(uint32_t i) const { return __builtin_amdgcn_readlane(v, i); }
+};
+
+// Everything requested so far is there.  Placed where it is so anyway, in front of stores: without it
+// the first use behind them would wait for them as well.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
+
+// Peels sketch partitions: unknowns rho .. rho+Pa-1 in order of c-index, cells a*3*m_sub ...
 //
 // The LDS a partition needs leaves room for one workgroup per CU, and the rounds are bound
 // by LDS latency, not by memory.  So the grid is one workgroup per CU, each taking
@@ -591,13 +708,15 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
             uint32_t P_cap, uint32_t mode)
 {
     extern __shared__ __align__(16) uint64_t lds64[];
-    PartLds<kPacked> part(lds64, T_cap, P_cap);
     const uint32_t tid = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    PartAhead ahead;
+    ahead.first(index, salt, blockIdx.x);
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
     const uint32_t cells = 3 * m_sub;
-    part.m_sub = m_sub;
+    if (blockIdx.x >= A) return;
+    PartLds<kPacked> part(lds64, T_cap, P_cap, m_sub);
 
     // the cells and Index words (or unknowns) of partition `p` into registers (zeros beyond their
     // ends)
@@ -620,17 +739,16 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
 #pragma unroll
                 for (uint32_t q = 0; q < kCellPre; ++q) pre_cell[0][q] += pre_cell[i][q];
     };
-    auto prefetch = [&](uint32_t p) {
-        if (kListed) {
-            const uint32_t r0 = uint32_t(uint64_t(p) * U / A);
-            pre_list.request(index.list + r0, uint32_t(uint64_t(p + 1) * U / A) - r0, tid);
-        } else {
-            pre_index.request(index, p, wave);
-        }
-        const uint64_t tile = uint64_t(p) * cells;
+    auto request_unknowns = [&](const Partitions &at) {
+        if (kListed) pre_list.request(index.list + at.rho, at.unknowns(), tid);
+        else pre_index.request(index, ahead.get(0), ahead.get(1), wave);
+    };
+    auto request_first = [&](uint64_t tile) {
 #pragma unroll
         for (uint32_t i = 0; i < kRanks; ++i)
             if (i < n_in) request_cells(pre_cell[i], i, tile);
+    };
+    auto request_rest = [&](uint64_t tile) {
         if (!kLoop) return;
         for (uint32_t r = kRanks; r < n_in; r += kRanks - 1) {
             __builtin_amdgcn_sched_barrier(0);
@@ -644,18 +762,27 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
                     for (uint32_t q = 0; q < kCellPre; ++q) pre_cell[i][q] = -0.0f;  // (x + -0 is x)
         }
     };
-    if (blockIdx.x < A) prefetch(blockIdx.x);
+    Partitions at(U, A, blockIdx.x, gridDim.x);
+    uint32_t sa = 0;
+    // the partition `at` is at; `ahead` holds what is needed for it, and then that of the one after it
+    auto prefetch = [&](bool first) {
+        const uint64_t tile = uint64_t(at.a) * cells;
+        if (first) request_first(tile);  // (these do not need the bounds)
+        sa = ahead.get(2);
+        request_unknowns(at);
+        if (!first) request_first(tile);
+        request_rest(tile);
+        ahead.request(index, salt, at.a + at.step, A);
+    };
+    prefetch(true);
+    wait_loads();
 
     uint32_t max_rounds = 0;
-    for (uint32_t a = blockIdx.x; a < A; a += gridDim.x) {
+    while (at.a < A) {
     PHASE_INIT();
-    const uint32_t rho0 = uint32_t(uint64_t(a) * U / A);
-    const uint32_t Pa = uint32_t(uint64_t(a + 1) * U / A) - rho0;
+    const uint32_t rho0 = at.rho, Pa = at.unknowns();
     // the partition's hash functions: the seed under the salt the encoders used
-    const uint32_t sa = salt[a];
-    part.fsw0 = fold16(seed_word(seed, 3 * sa));
-    part.fsw1 = fold16(seed_word(seed, 3 * sa + 1));
-    part.fsw2 = fold16(seed_word(seed, 3 * sa + 2));
+    part.seed(seed, sa);
 
     // (addresses that follow from the thread's number are made anew for every partition: kept from one
     // to the next they take the registers that the prefetch needs)
@@ -663,25 +790,24 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     asm volatile("" : "+v"(tid));
 
     // ---- stage the partition's cells and unknowns from the registers, clear state
-    part.template clear<kDecodeThreads>(tid, cells, P_cap);
-    if (tid < 3) part.n_queued[tid] = 0;
-    if (kListed) pre_list.put(part.word, Pa, tid);
-    else pre_index.enumerate(index, part.word, Pa, rho0, wave);
+    part.template clear<kDecodeThreads>(tid, cells);
+    if (kListed) pre_list.put(part.word(0), Pa, tid);
+    else pre_index.enumerate(index, part.word(0), Pa, rho0, wave);
     add_cells(1, n_in);
+    uint32_t *to = part.value(part.base + 4 * tid);
 #pragma unroll
-    for (uint32_t q = 0; q < kCellPre; ++q) {
-        const uint32_t c = tid + q * kDecodeThreads;
-        if (c < cells) part.cell_value[c] = __float_as_uint(pre_cell[0][q]);
-    }
+    for (uint32_t q = 0; q < kCellPre; ++q)
+        if (tid + q * kDecodeThreads < cells) to[q * kDecodeThreads] = __float_as_uint(pre_cell[0][q]);
     __syncthreads();
     PHASE_MARK(0);
 
-    join_cells<kDecodeThreads, kIdxPre, kListed>(part, tid, Pa, idx_out + rho0);
-    // the registers are free again: the next partition's data travels during the rounds
-    if (a + gridDim.x < A) prefetch(a + gridDim.x);
+    uint32_t cell[kIdxPre][3];
+    join_cells<kDecodeThreads, kIdxPre, kListed>(part, tid, Pa, idx_out + rho0, cell);
     __syncthreads();
-    if (mode != TAGC_DECODE_ESTIMATE)  // estimation alone: the queue stays empty
-        queue_first<kDecodeThreads, (kCellPre + 2) / 3>(part, tid, [] { __syncthreads(); });
+    queue_first<kDecodeThreads, kIdxPre>(part, tid, Pa, mode != TAGC_DECODE_ESTIMATE, cell);
+    // the registers are free again: the next partition's data travels during the rounds
+    at.next();
+    if (!kLoop && at.a < A) prefetch(false);
     PHASE_MARK(1);
 
     const uint32_t resolved =
@@ -690,10 +816,12 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
 
     // ---- values leave in one contiguous sweep (stored one by one as they were found they
     // would cost a cache-line access each)
+    wait_loads();
     for (uint32_t u = tid; u < Pa; u += kDecodeThreads) val_out[rho0 + u] = unknown_value(part, u, mode);
     if (tid == 0) report_unresolved(Pa - resolved, mode, status);
-    __syncthreads();  // before the next partition is staged
     PHASE_MARK(3);
+    if (kLoop) break;
+    __syncthreads();  // before the next partition is staged
     }  // partitions of this workgroup
     if (tid == 0 && max_rounds) atomicMax(&status[TAGC_ST_ROUNDS], max_rounds);
 }
@@ -717,7 +845,6 @@ constexpr uint32_t kLoadThreads = kLoadWaves * 64, kPeelThreads = kPeelWaves * 6
 constexpr uint32_t kLoadCells = (kDefaultPartCells + kLoadThreads - 1) / kLoadThreads;  // per thread
 constexpr uint32_t kUnit = 16;  // cells of one rank a loader thread requests at a time
 static_assert(kLoadCells == 3 * kUnit, "a rank's cells are three units per loader thread");
-constexpr uint32_t kPeelSlots = (kDefaultPartCells / 3 + kPeelThreads - 1) / kPeelThreads;
 constexpr uint32_t kPeelIdx = (kDefaultPartUnknowns + kPeelThreads - 1) / kPeelThreads;
 
 // Barrier among the kPeelWaves peeling waves: every wave adds 1 to an LDS word and goes on
@@ -743,12 +870,15 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
                 uint32_t T_cap, uint32_t P_cap, uint32_t mode)
 {
     extern __shared__ __align__(16) uint64_t lds64[];
-    PartLds<true> part(lds64, T_cap, P_cap);
     const uint32_t tid = threadIdx.x;
+    PartAhead ahead;  // (the peelers')
+    ahead.first(index, salt, blockIdx.x);
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
     const uint32_t cells = 3 * m_sub;
-    if (tid == 0) *part.bar = 0;
+    PartLds<true> part(lds64, T_cap, P_cap, m_sub);
+    if (blockIdx.x >= A) return;
+    if (tid == 0) *part.bar() = 0;
     __syncthreads();
 
     if (tid >= kPeelThreads) {
@@ -798,14 +928,15 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
             add_unit(b1, T1);
             add_unit(b2, T2);
         };
-        if (blockIdx.x < A) sum_partition(blockIdx.x);
+        sum_partition(blockIdx.x);
         for (uint32_t a = blockIdx.x; a < A; a += gridDim.x) {
             __syncthreads();  // the peelers are done with the LDS
+            uint32_t c0 = lt;  // (see peel_kernel's tid)
+            asm volatile("" : "+v"(c0));
+            uint32_t *to = part.value(part.base + 4 * c0);
 #pragma unroll
-            for (uint32_t q = 0; q < kLoadCells; ++q) {
-                const uint32_t c = lt + q * kLoadThreads;
-                if (c < cells) part.cell_value[c] = __float_as_uint(acc[q]);
-            }
+            for (uint32_t q = 0; q < kLoadCells; ++q)
+                if (c0 + q * kLoadThreads < cells) to[q * kLoadThreads] = __float_as_uint(acc[q]);
             __syncthreads();  // the partition is staged
             if (a + gridDim.x < A) sum_partition(a + gridDim.x);
         }
@@ -816,42 +947,39 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     PartIndex<kPeelWaves, kIndexPre> pre_index;
     PartList<kPeelThreads, kPeelIdx> pre_list;
-    auto prefetch = [&](uint32_t p) {
-        if (kListed) {
-            const uint32_t r0 = uint32_t(uint64_t(p) * U / A);
-            pre_list.request(index.list + r0, uint32_t(uint64_t(p + 1) * U / A) - r0, tid);
-        } else {
-            pre_index.request(index, p, wave);
-        }
+    Partitions at(U, A, blockIdx.x, gridDim.x);
+    uint32_t sa = 0;
+    auto prefetch = [&] {  // (see peel_kernel)
+        sa = ahead.get(2);
+        if (kListed) pre_list.request(index.list + at.rho, at.unknowns(), tid);
+        else pre_index.request(index, ahead.get(0), ahead.get(1), wave);
+        ahead.request(index, salt, at.a + at.step, A);
     };
-    if (blockIdx.x < A) prefetch(blockIdx.x);
+    prefetch();
+    wait_loads();
     uint32_t bar_expected = 0, max_rounds = 0;
-    part.m_sub = m_sub;
-    for (uint32_t a = blockIdx.x; a < A; a += gridDim.x) {
-        uint32_t tid = threadIdx.x;  // (see peel_kernel)
+    while (at.a < A) {
+        uint32_t tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
-        const uint32_t rho0 = uint32_t(uint64_t(a) * U / A);
-        const uint32_t Pa = uint32_t(uint64_t(a + 1) * U / A) - rho0;
-        const uint32_t sa = salt[a];
-        part.fsw0 = fold16(seed_word(seed, 3 * sa));
-        part.fsw1 = fold16(seed_word(seed, 3 * sa + 1));
-        part.fsw2 = fold16(seed_word(seed, 3 * sa + 2));
+        const uint32_t rho0 = at.rho, Pa = at.unknowns();
+        part.seed(seed, sa);
         __syncthreads();  // everybody is done with the previous partition
-        part.clear<kPeelThreads>(tid, cells, P_cap);
-        if (tid < 3) part.n_queued[tid] = 0;
+        part.clear<kPeelThreads>(tid, cells);
         __syncthreads();  // the loaders have staged the cells
 
         // (here and not before the barriers, where the loaders would wait for it)
-        if (kListed) pre_list.put(part.word, Pa, tid);
-        else pre_index.enumerate(index, part.word, Pa, rho0, wave);
-        peel_barrier(part.bar, bar_expected);
-        join_cells<kPeelThreads, kPeelIdx, kListed>(part, tid, Pa, idx_out + rho0);
-        if (a + gridDim.x < A) prefetch(a + gridDim.x);
-        peel_barrier(part.bar, bar_expected);
-        if (mode != TAGC_DECODE_ESTIMATE)
-            queue_first<kPeelThreads, kPeelSlots>(part, tid, [&] { peel_barrier(part.bar, bar_expected); });
-        const uint32_t resolved =
-            peel_rounds<kPeelThreads>(part, tid, max_rounds, [&] { peel_barrier(part.bar, bar_expected); });
+        if (kListed) pre_list.put(part.word(0), Pa, tid);
+        else pre_index.enumerate(index, part.word(0), Pa, rho0, wave);
+        peel_barrier(part.bar(), bar_expected);
+        uint32_t cell[kPeelIdx][3];
+        join_cells<kPeelThreads, kPeelIdx, kListed>(part, tid, Pa, idx_out + rho0, cell);
+        peel_barrier(part.bar(), bar_expected);
+        queue_first<kPeelThreads, kPeelIdx>(part, tid, Pa, mode != TAGC_DECODE_ESTIMATE, cell);
+        at.next();
+        if (at.a < A) prefetch();
+        const uint32_t resolved = peel_rounds<kPeelThreads>(
+            part, tid, max_rounds, [&] { peel_barrier(part.bar(), bar_expected); });
+        wait_loads();
         for (uint32_t u = tid; u < Pa; u += kPeelThreads) val_out[rho0 + u] = unknown_value(part, u, mode);
         if (tid == 0) report_unresolved(Pa - resolved, mode, status);
     }
