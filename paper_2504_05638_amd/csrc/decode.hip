@@ -210,12 +210,7 @@ __device__ __forceinline__ uint32_t take_slots(uint32_t *count, uint32_t n)
 {
     const uint32_t leader = __builtin_ctzll(__ballot(true));
     uint32_t at = 0;
-    // (an address the compiler cannot tell to be uniform: it would wrap the one lane's add in
-    // the dozen instructions that combine a whole wave's)
-    __attribute__((address_space(3))) uint32_t *lds = (__attribute__((address_space(3))) uint32_t *)count;
-    asm("" : "+v"(lds));
-    if (lane_id() == leader)
-        at = __hip_atomic_fetch_add((uint32_t *)lds, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (lane_id() == leader) at = add_by_lane(count, n);
     return __builtin_amdgcn_readlane(at, leader);
 }
 

@@ -102,6 +102,16 @@ __device__ inline void lds_add_f32(float *p, float v)
     } while (old != assumed);
 }
 
+// LDS add by every active lane for itself, returning what was there.  (An address the compiler cannot
+// tell to be uniform: it would wrap the adds of the few lanes that get here in the dozen instructions
+// that combine a whole wave's.)
+__device__ inline uint32_t add_by_lane(uint32_t *count, uint32_t n)
+{
+    __attribute__((address_space(3))) uint32_t *lds = (__attribute__((address_space(3))) uint32_t *)count;
+    asm("" : "+v"(lds));
+    return __hip_atomic_fetch_add((uint32_t *)lds, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Streaming accesses: data that is read or written once and not touched again by the same
 // kernel.  The non-temporal hint keeps such lines from displacing what the caches are for
 // (measured on a 17-stream sum: 5.3 -> 5.9 TB/s, the rate of a pure read).

@@ -201,27 +201,48 @@ __device__ inline void lower_bounds_by_16(const uint32_t *const (&list)[kN], con
 //
 // One workgroup per partition at a time, two workgroups per compute unit.  The partition's
 // non-zeros are the set bits of the merged Index in [bounds[a], bounds[a+1]).  Each gets a
-// number t (any order; a wave takes a run of numbers with one LDS add), its three slots under
-// the salt being tried, and is pushed on the list of its slot_0 (an LDS exchange of the
-// list's head); afterwards it walks what was on that list before it and compares the other
-// two slots.  LDS per non-zero: a 32-bit tag (slot_1, slot_2) and a 16-bit link; per cell of
-// a sub-table a 32-bit list head -- little enough for two partitions per compute unit, whose
-// phases (hashing on the vector units, list building and walking in LDS) then overlap.
-//
+// number t (any order; a wave takes a run of numbers with one LDS add).  Bound by hashing (three 32-bit
+// multiplies per slot, at quarter rate), so nearly all of them are let off with two of their slots: slot_0
+// and six bits of slot_1 name a bit of a filter, 64 bits per cell of a sub-table, and whoever finds its bit
+// set (one in 64 of 8192) sets one in a second filter, by which all that have the same bits then know
+// themselves (one in 30).  Those are listed and compared with all three slots: pushed on the list of their
+// slot_0 (an LDS exchange of the list's head), after which each walks what was on that list before it.  A
+// partition with more of them than the listing has room for (sub-tables of a few cells) is compared
+// that way as a whole.  All of it that way, with a 32-bit tag, a link and a walk for each and all three slots
+// hashed, took, us, and takes now: 16 ranks of 202 M entries 149, 125; 2 ranks with a tenth kept 160, 124;
+// 8 ranks of 67 M 39, 31, of 25 M 22.4, 20.5; a launch with one partition 0.5 more (two barriers more).
 // The same kernel derives everything else the later stages need from the merged Index, each
 // step a few dependent loads that would be a launch of their own: every workgroup adds up the
 // chunk counts by itself (a few words per thread) and knows the layout; its partitions' bounds
 // are found by a wave each (bounds[a] = c-index of the non-zero of rank floor(a*U/A);
 // bounds[A] = n_c); and so are their ends in the ranks' sorted pair lists (ranges[a] of a
 // rank = number of its pairs whose c-index lies below bounds[a]).  Four launches (header, bounds,
-// salt, ranges) were 31 us on an 8-rank bucket of 25 M entries and 48 on one of 67 M, this one is
-// 21 and 40; with 16 ranks of 202 M, where the salts are most of it, 138 and 149.
+// salt, ranges) were 31 us on an 8-rank bucket of 25 M entries and 48 on one of 67 M, in one launch they
+// were 21 and 40 with the same comparison.  A workgroup's first partition waits 20 K clocks for memory, in
+// order: chunk counts, Index words of the bounds, four to six steps of the searches.  (Tried: the
+// chunk counts kept in LDS for the bounds, nothing; 256 parts a step and half the steps in small
+// launches, 3 us slower, bound by the lines; words beyond the first four requested ahead, 0 to 6 % slower.)
 constexpr uint32_t kSaltThreads = 1024;
 constexpr uint32_t kLayoutBatch = kSaltThreads / 128;  // partitions whose bounds are found at once
 constexpr uint64_t kSplitSearches = 32768;  // (partition, rank) pairs
 constexpr uint32_t kSaltLimit = 16;       // salts tried: 0 .. 15
 constexpr uint32_t kNoLink = 0xFFFFu;
+constexpr uint32_t kFilterBits = 64;      // per cell of a sub-table
+constexpr uint32_t kSecondWords = 1024;   // second filter
+constexpr uint32_t kSaltPer = kDefaultPartUnknowns / kSaltThreads;  // non-zeros per thread of a partition of the default size
 constexpr uint32_t kSaltPre = 4;          // Index words per thread requested a partition ahead
+
+// The room for the first filter, which is also that for list heads and a 16-bit link per non-zero; and how many
+// non-zeros (number, tag, link) can be listed behind the heads.
+__host__ __device__ inline uint32_t salt_filter_bytes(uint32_t T_cap, uint32_t P_cap)
+{
+    const uint32_t q = T_cap / 3, filter = q * (kFilterBits / 8), whole = 4 * q + 2 * P_cap;
+    return ((filter > whole ? filter : whole) + 15) & ~15u;
+}
+__host__ __device__ inline uint32_t salt_listed(uint32_t T_cap, uint32_t P_cap)
+{
+    return (salt_filter_bytes(T_cap, P_cap) - 4 * (T_cap / 3)) / 8;
+}
 
 // (8 waves per SIMD asked for: two workgroups a compute unit; 106 scalar registers leave room for one)
 template <bool kBounds, bool kSearch, bool kSalts>
@@ -235,10 +256,17 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     constexpr uint32_t NT = kSaltThreads;
     extern __shared__ uint32_t lds_salt[];
     const uint32_t P_cap = lp.P_cap, q_cap = lp.T_cap / 3;
-    uint32_t *tag = lds_salt;                        // [P_cap] c-index, then slot_1 | slot_2 << 16
-    uint32_t *head = tag + P_cap;                                   // [q_cap]
-    uint16_t *link = reinterpret_cast<uint16_t *>(head + q_cap);    // [P_cap]
-    __shared__ uint32_t s_n, s_dup;
+    uint32_t *second = lds_salt;            // [kSecondWords]
+    uint32_t *tag = second + kSecondWords;  // [P_cap] c-index; compared as a whole: slot_1 | slot_2 << 16
+    // the first filter; behind it in time, list heads and what is compared (see salt_lds_bytes)
+    uint32_t *filter = tag + P_cap;         // [2 * q_cap]
+    uint32_t *head = filter;                // [q_cap]
+    const uint32_t n_listed = salt_listed(lp.T_cap, P_cap);
+    uint32_t *some_tag = head + q_cap;                                      // [n_listed]
+    uint16_t *some = reinterpret_cast<uint16_t *>(some_tag + n_listed);     // [n_listed] their numbers
+    uint16_t *some_link = some + n_listed;                                  // [n_listed]
+    uint16_t *link = reinterpret_cast<uint16_t *>(head + q_cap);            // [P_cap], as a whole
+    __shared__ uint32_t s_n, s_dup, s_some;
     __shared__ uint32_t s_pre[kBounds ? NT : 1];  // set bits before thread t's chunks
     __shared__ uint32_t s_bound[2 * kLayoutBatch];  // first and last bound of the batch's partitions
     __shared__ uint32_t smem[NT / 64];
@@ -423,12 +451,8 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
         }
         uint32_t salt = 0;
         if (cur_lo < cur_hi) {
-            for (salt = 0; salt < kSaltLimit; ++salt) {
-                const uint32_t sw0 = seed_word(seed, 3 * salt), sw1 = seed_word(seed, 3 * salt + 1),
-                               sw2 = seed_word(seed, 3 * salt + 2);
-                for (uint32_t c = tid; c < m_sub; c += kSaltThreads) head[c] = kNoLink;
-                if (tid == 0) s_n = s_dup = 0;
-                __syncthreads();
+            // the non-zeros' c-indices into tag[]
+            auto enumerate = [&] {
                 uint32_t k = 0;
                 for (uint32_t base = w_lo + (tid - lane); base <= w_hi; base += kSaltThreads, ++k) {
                     // (wave-uniform loop: the numbering below is a wave-wide scan)
@@ -445,22 +469,85 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
                     for (; word; word &= word - 1, ++t)  // (a partition holds <= P_cap)
                         if (t < P_cap) tag[t] = (base + lane) * 32 + uint32_t(__builtin_ctz(word));
                 }
-                __syncthreads();
-                // every lane busy: the numbered non-zeros are hashed in number order (a
-                // lane's own Index word holds anything from none to a dozen of them)
-                for (uint32_t t = tid; t < min(s_n, P_cap); t += kSaltThreads) {
-                    const uint32_t i = tag[t];
-                    uint32_t neg;
-                    const uint32_t c0 = hash_slot(i, sw0, m_sub, &neg);
-                    tag[t] = hash_slot(i, sw1, m_sub, &neg) | (hash_slot(i, sw2, m_sub, &neg) << 16);
-                    link[t] = uint16_t(atomicExch(&head[c0], t));
+            };
+            // pushes entry t of a list under its slots, then looks for another one with the same
+            auto push = [&](uint32_t i, uint32_t t, uint32_t *tags, uint16_t *links, const uint32_t (&fsw)[3]) {
+                uint32_t neg;
+                const uint32_t fi = fold16(i), c0 = hash_slot_folded(fi, fsw[0], m_sub, &neg);
+                tags[t] = hash_slot_folded(fi, fsw[1], m_sub, &neg) |
+                          (hash_slot_folded(fi, fsw[2], m_sub, &neg) << 16);
+                links[t] = uint16_t(atomicExch(&head[c0], t));
+            };
+            auto twice = [&](uint32_t t, const uint32_t *tags, const uint16_t *links) {
+                const uint32_t mine = tags[t];
+                bool dup = false;
+                for (uint32_t p = links[t]; p != kNoLink; p = links[p]) dup |= tags[p] == mine;
+                return dup;
+            };
+            // (not kept from one partition to the next in registers that are needed)
+            uint32_t tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));
+            bool listed = false;  // tag[] holds the c-indices
+            for (salt = 0; salt < kSaltLimit; ++salt) {
+                uint32_t fsw[3];
+                for (uint32_t j = 0; j < 3; ++j) fsw[j] = fold16(seed_word(seed, 3 * salt + j));
+                for (uint32_t c = tid; c < 2 * m_sub; c += kSaltThreads) filter[c] = 0;
+                second[tid] = 0;
+                if (tid == 0) {
+                    s_dup = s_some = 0;
+                    if (!listed) s_n = 0;
                 }
                 __syncthreads();
+                if (!listed) {
+                    enumerate();
+                    __syncthreads();
+                }
+                listed = true;
                 const uint32_t n = min(s_n, P_cap);
+                // every lane busy: the non-zeros are hashed in number order (a lane's own Index word
+                // holds anything from none to a dozen of them)
+                auto filter_bit = [&](uint32_t t) -> uint32_t {
+                    uint32_t neg;
+                    const uint32_t fi = fold16(tag[t]), c0 = hash_slot_folded(fi, fsw[0], m_sub, &neg);
+                    return c0 * kFilterBits + hash_slot_folded(fi, fsw[1], m_sub, &neg) % kFilterBits;
+                };
+                auto mark = [&](uint32_t b) {
+                    const uint32_t one = 1u << (b & 31);
+                    if (atomicOr(&filter[b >> 5], one) & one) atomicOr(&second[(b >> 5) % kSecondWords], one);
+                };
+                auto list = [&](uint32_t t, uint32_t b) {
+                    if (!((second[(b >> 5) % kSecondWords] >> (b & 31)) & 1u)) return;
+                    const uint32_t at = add_by_lane(&s_some, 1u);
+                    if (at < n_listed) some[at] = uint16_t(t);
+                };
+                uint32_t bit[kSaltPer];  // (larger partitions: found out twice)
+#pragma unroll
+                for (uint32_t q = 0; q < kSaltPer; ++q) {
+                    const uint32_t t = tid + q * kSaltThreads;
+                    if (t < n) mark(bit[q] = filter_bit(t));
+                }
+                for (uint32_t t = tid + kSaltPer * kSaltThreads; t < n; t += kSaltThreads) mark(filter_bit(t));
+                __syncthreads();
+                for (uint32_t c = tid; c < m_sub; c += kSaltThreads) head[c] = kNoLink;
+#pragma unroll
+                for (uint32_t q = 0; q < kSaltPer; ++q) {
+                    const uint32_t t = tid + q * kSaltThreads;
+                    if (t < n) list(t, bit[q]);
+                }
+                for (uint32_t t = tid + kSaltPer * kSaltThreads; t < n; t += kSaltThreads) list(t, filter_bit(t));
+                __syncthreads();
+                const uint32_t n_some = s_some;
                 bool dup = false;
-                for (uint32_t t = tid; t < n; t += kSaltThreads) {
-                    const uint32_t mine = tag[t];
-                    for (uint32_t p = link[t]; p != kNoLink; p = link[p]) dup |= tag[p] == mine;
+                if (n_some <= n_listed) {
+                    for (uint32_t t = tid; t < n_some; t += kSaltThreads)
+                        push(tag[some[t]], t, some_tag, some_link, fsw);
+                    __syncthreads();
+                    for (uint32_t t = tid; t < n_some; t += kSaltThreads) dup |= twice(t, some_tag, some_link);
+                } else {
+                    for (uint32_t t = tid; t < n; t += kSaltThreads) push(tag[t], t, tag, link, fsw);
+                    listed = false;
+                    __syncthreads();
+                    for (uint32_t t = tid; t < n; t += kSaltThreads) dup |= twice(t, tag, link);
                 }
                 if (dup) s_dup = 1;
                 __syncthreads();
@@ -500,7 +587,7 @@ ranges_kernel(const LayoutBatch, const uint32_t *__restrict__ header,
 
 size_t salt_lds_bytes(uint32_t T_cap, uint32_t P_cap)
 {
-    return size_t(P_cap) * 4 + size_t(T_cap / 3) * 4 + size_t(P_cap) * 2 + 16;
+    return (kSecondWords + size_t(P_cap)) * 4 + salt_filter_bytes(T_cap, P_cap);
 }
 
 int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32_t n_ranks,
