@@ -82,9 +82,12 @@ struct SparsifyBatch {
 };
 static_assert(sizeof(SparsifyBatch) <= 3072, "kernel arguments are limited to 4 KiB");
 
-// Where things are in a rank's workspace, and how many candidate slots it has.
+// Where things are in a rank's workspace, and how many candidate slots it has; and what the table's
+// first words say as well (segments, tiles, super-chunks).  Everything in these kernels waits for that:
+// read from the table it is a trip to memory in front of each of them.
 struct WsLayout {
     uint64_t hist1d, hist2, group_cnt, sel, tile_cnt, sc_cnt, chunk_info, cand, n_slots;
+    uint32_t L, total_tiles, total_sc;
 };
 
 // The row of the rank a workgroup works for, its pointers known to be global memory.
@@ -438,8 +441,16 @@ constexpr uint32_t kSpillThreads = 512;
 #endif
 constexpr uint32_t kSpillWgsPerCU = TAGC_SPILL_WGS;  // workgroups launched per compute unit
 constexpr uint32_t kSpillSpan = 128;   // chunks a workgroup's span has at least in launches of several rounds
-constexpr uint32_t kSpillStage = 512;  // staged slots per wave
-constexpr uint32_t kSpillList = 16;    // staged chunks per wave
+// Slots and chunks a wave stages before they leave.  Stores among the loads cost the scan more than
+// their bytes (16 ranks of 202 M bf16 entries: 235 MB of 6.7 GB, a tenth of the time; without its
+// stores it would run at 6.2 TB/s), so they leave in runs as long as the LDS of two workgroups per
+// compute unit has room for.  bf16, 512 slots and 16 chunks / 1024 and 32, us: one rank 82 / 77,
+// 8 ranks of 67 M 201 / 198, with an accumulator 276 / 270, a tenth kept 225 / 220; fp32, which
+// needs two words a slot, 58 / 65 (one workgroup per compute unit).
+template <int DTYPE>
+constexpr uint32_t kSpillStage = DTYPE == kBF16 ? 1024 : 512;
+template <int DTYPE>
+constexpr uint32_t kSpillList = DTYPE == kBF16 ? 32 : 16;
 constexpr uint32_t kWatchCalls = 8;    // calls that extrapolate a falling pre-threshold after a miss
 constexpr uint32_t kSpillRaise = 6;    // bins (1/128 octave each) a wave's pre-threshold goes up per try
 
@@ -571,17 +582,18 @@ scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint3
     constexpr uint32_t ROW_ELEMS = 64 * VEC;
     constexpr uint32_t CHUNK = ROW_ELEMS * ROWS;
     constexpr uint32_t NW = kSpillThreads / 64;
-    constexpr uint32_t STAGE_WORDS = kSpillStage * (DTYPE == kBF16 ? 1 : 2);
+    constexpr uint32_t STAGE = kSpillStage<DTYPE>, LIST = kSpillList<DTYPE>;
+    constexpr uint32_t STAGE_WORDS = STAGE * (DTYPE == kBF16 ? 1 : 2);
     static_assert(ROWS == 4 && ROWS * VEC <= 32, "packed masks and row counts below");
     __shared__ uint32_t h[kWinWords];
     __shared__ uint32_t s_sel[32];
     __shared__ uint32_t s_last;
     __shared__ uint32_t s_region;  // slots of the workgroup's part of `cand` handed out so far
     __shared__ uint32_t stage[NW][STAGE_WORDS];
-    __shared__ uint32_t list[NW][3][kSpillList];  // chunk number, staging offset, count
+    __shared__ uint32_t list[NW][3][LIST];  // chunk number, staging offset, count
     __shared__ uint4 data[NW][ROWS * 64];         // each wave's current chunk
-    const uint32_t L = table[0];
-    const uint32_t total_chunks = table[4] * kCandChunksPerSuper;
+    const uint32_t L = wl.L;
+    const uint32_t total_chunks = wl.total_sc * kCandChunksPerSuper;
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     const TableState ts = table_state(table, L, rv.slot), from = table_state(table, L, rv.from);
     const uint32_t tid = threadIdx.x, lane = tid & 63;
@@ -601,12 +613,26 @@ scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint3
     for (uint32_t i = tid; i < kWinWords; i += kSpillThreads) h[i] = 0;
     if (tid == 0) s_region = 0;
     // last segment whose first chunk is not beyond the span's start.  Up to 64 segments: lane
-    // i looks at segment i, all at once (a search would be several dependent loads, which is
-    // time the workgroup's first chunk waits for)
+    // i holds segment i's row and pre-threshold, all requested at once (a search, the row, the
+    // pre-threshold would be several dependent loads, which is time the workgroup's first
+    // chunk waits for)
+    uint4 row_a = make_uint4(0, 0, 0, 0), row_b = row_a;
+    uint32_t row_hint = 0;
+    if (L <= 64 && lane < L) {
+        const uint4 *row = reinterpret_cast<const uint4 *>(segs + lane);
+        row_a = row[0];
+        row_b = row[1];
+        row_hint = from.hint[lane];
+    }
+    auto segment = [&](uint32_t l) {
+        if (L > 64) return segs[l];
+        auto get = [&](uint32_t v) { return uint32_t(__builtin_amdgcn_readlane(v, l)); };
+        return SegDev{uint64_t(get(row_a.y)) << 32 | get(row_a.x), get(row_a.z), get(row_a.w),
+                      get(row_b.x), get(row_b.y), get(row_b.z), get(row_b.w)};
+    };
     uint32_t l0 = 0;
     if (L <= 64) {
-        const uint64_t first = lane < L ? uint64_t(segs[lane].sc_start) * kCandChunksPerSuper
-                                        : ~0ull;
+        const uint64_t first = lane < L ? uint64_t(row_b.w) * kCandChunksPerSuper : ~0ull;
         l0 = uint32_t(__popcll(__ballot(first <= g0))) - 1u;  // segment 0 starts at chunk 0
     } else {
         for (uint32_t hi = L; hi - l0 > 1;) {
@@ -619,7 +645,7 @@ scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint3
     uint32_t *st = stage[wib];
     uint32_t *lst_chunk = list[wib][0], *lst_off = list[wib][1], *lst_cnt = list[wib][2];
     uint4 *dw = data[wib];
-    const bool staged = CAP <= kSpillStage;
+    const bool staged = CAP <= STAGE;
     uint32_t n_list = 0, fill = 0;  // wave-uniform
 
     // The staged chunks' slots and counts go out; only this wave touched what it reads.
@@ -643,7 +669,7 @@ scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint3
         // the padding words are stale staging content, which no reader looks at
         for (uint32_t i = lane; i < n_out; i += 64) {
             slots[i] = st[i];
-            if (DTYPE != kBF16) slots[n_slots_total + i] = st[kSpillStage + i];
+            if (DTYPE != kBF16) slots[n_slots_total + i] = st[STAGE + i];
         }
         if (lane < n_list)
             chunk_info[lst_chunk[lane]] = make_uint2(lst_cnt[lane], first + lst_off[lane]);
@@ -654,7 +680,7 @@ scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint3
     };
 
     for (uint32_t l = l0; l < L; ++l) {
-        const SegDev sd = segs[l];
+        const SegDev sd = segment(l);
         const uint64_t s0 = uint64_t(sd.sc_start) * kCandChunksPerSuper;
         if (s0 >= g1) break;
         if (sd.k == 0 || sd.n == 0 || !(sd.flags & kSegFast)) continue;
@@ -667,7 +693,7 @@ scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint3
         // With an accumulator (error feedback) the segment is streamed all the same: this
         // pass is also the one that turns acc into grad + acc, which the dense route then
         // reads instead of the gradient.  Its candidates are then never used.
-        const uint32_t hint = from.hint[l];
+        const uint32_t hint = L <= 64 ? uint32_t(__builtin_amdgcn_readlane(row_hint, l)) : from.hint[l];
         const uint32_t blo = hint ? hint : 0x7F7Fu;  // 1 <= blo <= 0x7FFF
         if (hint || ACC) {
             const char *base = grad + sd.offset * EB;
@@ -851,7 +877,7 @@ scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint3
                 const uint32_t chunk_id = uint32_t(s0) + ch;
                 // (a chunk's slots start on a 16-byte boundary: they are read in such groups)
                 const uint32_t need = min((total + 3u) & ~3u, CAP);
-                if (staged && (n_list == kSpillList || fill + need > kSpillStage)) flush();
+                if (staged && (n_list == LIST || fill + need > STAGE)) flush();
                 uint32_t *slots = cand + uint64_t(chunk_id) * CAP;
                 uint32_t *slots_pos = slots + n_slots_total;  // fp32 only
                 uint32_t *stc = st + fill;
@@ -880,7 +906,7 @@ scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint3
                         } else {
                             if (staged) {
                                 stc[ps] = bits;
-                                stc[kSpillStage + ps] = rel;
+                                stc[STAGE + ps] = rel;
                             } else {
                                 slots[ps] = bits;
                                 slots_pos[ps] = rel;
@@ -940,8 +966,11 @@ scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint3
 // denser than its slots).  sel[l] of a candidate-route segment has been written by the scan.
 __device__ inline bool on_dense_route(const SegDev &sd, const SelDev *sel, uint32_t l)
 {
-    if (sd.k == 0 || sd.n == 0) return false;
-    return !(sd.flags & kSegFast) || sel[l].route != 0;
+    // (looked up whatever the row says, so that row and route are on their way together; a segment
+    // that keeps nothing has no selection, and what lies in its place does not count)
+    const uint32_t route = sel[l].route;
+    return bool(uint32_t(sd.k != 0) & uint32_t(sd.n != 0) &
+                (uint32_t(!(sd.flags & kSegFast)) | uint32_t(route != 0)));
 }
 
 // true iff some segment is on the dense route: lane i looks at segments i, i + 64, ...
@@ -1146,14 +1175,14 @@ hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t n
     const RankView rv = rank_view();
     const char *grad = rv.src();
     SelDev *sel = rv.at<SelDev>(wl.sel);
-    const uint32_t L = table[0];
+    const uint32_t L = wl.L;
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     const TableState ts = table_state(table, L, rv.slot);
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t n_small = gridDim.x - n_span;
     if (blockIdx.x == 0) {  // the tile groups' counts are added to by the next kernel
         uint64_t *gc = rv.at<uint64_t>(wl.group_cnt);
-        for (uint32_t i = tid; i <= table[1] / kTileGroup; i += NT) gc[i] = 0;
+        for (uint32_t i = tid; i <= wl.total_tiles / kTileGroup; i += NT) gc[i] = 0;
     }
     if (SMALL && blockIdx.x < n_small) {
         const uint32_t l = blockIdx.x;
@@ -1333,7 +1362,7 @@ refine_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t 
     const uint32_t *cand = rv.at<uint32_t>(wl.cand);
     const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
     const uint32_t n_slots_total = uint32_t(wl.n_slots);
-    const uint32_t L = table[0], total_sc = table[4];
+    const uint32_t L = wl.L, total_sc = wl.total_sc;
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     const TableState ts = table_state(table, L, rv.slot);
     const uint32_t tid = threadIdx.x, lane = tid & 63;
@@ -1493,10 +1522,9 @@ __device__ inline uint32_t segment_count(const SegDev &sd, const SelDev *sel, ui
 
 // The rank's count words, from the selections and what the call's kernels accumulated in
 // the table (which goes back to zero); by one workgroup of the last kernel.
-__device__ inline void write_rank_counts(uint32_t *table, uint32_t slot, const SelDev *sel,
+__device__ inline void write_rank_counts(uint32_t *table, uint32_t L, uint32_t slot, const SelDev *sel,
                                          uint32_t *cnt, uint32_t *smem /* >= 8 */)
 {
-    const uint32_t L = table[0];
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     uint32_t total = 0;
     for (uint32_t l = threadIdx.x; l < L; l += kEmitThreads) {
@@ -1554,10 +1582,10 @@ struct EmitLds {
 
 template <int DTYPE, bool PLACE>
 __device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid, uint32_t nb,
-                                 const uint32_t *__restrict__ table,
+                                 const uint32_t *__restrict__ table, const WsLayout &wl,
                                  const SelDev *__restrict__ sel,
             const uint32_t *__restrict__ cand, const uint2 *__restrict__ chunk_info,
-            uint64_t n_slots_total, uint32_t CAP, uint64_t *sc_cnt,
+            uint32_t CAP, uint64_t *sc_cnt,
             uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
             uint32_t *__restrict__ bitmap)
 {
@@ -1572,7 +1600,8 @@ __device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid, uin
     static_assert(SC_ELEMS <= 65536, "a position in the super-chunk fits 16 bits");
     __shared__ uint32_t s_gt[2 * NI], s_eq[2 * NI];
     __shared__ uint64_t s_sum[2 * NI];
-    const uint32_t L = table[0], total_sc = table[4];
+    const uint32_t L = wl.L, total_sc = wl.total_sc;
+    const uint64_t n_slots_total = wl.n_slots;
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1787,10 +1816,10 @@ __device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid, uin
 // super-chunk as emit_body.
 template <int DTYPE, bool PLACE, uint32_t BATCH>
 __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
-                                 const uint32_t *__restrict__ table,
+                                 const uint32_t *__restrict__ table, const WsLayout &wl,
                                  const SelDev *__restrict__ sel,
             const uint32_t *__restrict__ cand, const uint2 *__restrict__ chunk_info,
-            uint64_t n_slots_total, uint32_t CAP, uint64_t *sc_cnt,
+            uint32_t CAP, uint64_t *sc_cnt,
             uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
             uint32_t *__restrict__ bitmap)
 {
@@ -1802,7 +1831,8 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
     constexpr uint32_t NWV = kEmitThreads / 64;
     static_assert(NCH <= 64 && CH_WORDS <= 64, "a lane per chunk, a lane per Index word of a chunk");
     __shared__ uint32_t wbits[PLACE ? NWV : 1][PLACE ? CH_WORDS : 1];  // a wave's current chunk
-    const uint32_t L = table[0], total_sc = table[4];
+    const uint32_t L = wl.L, total_sc = wl.total_sc;
+    const uint64_t n_slots_total = wl.n_slots;
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -2002,7 +2032,7 @@ struct CompactLds {
 
 template <int DTYPE, uint32_t ROWS, bool PLACE, bool STAGED>
 __device__ __forceinline__ void compact_body(CompactLds<DTYPE, STAGED> *lds, uint32_t bid, uint32_t nb, uint32_t plan_tiles,
-                                             const char *grad, const uint32_t *__restrict__ table,
+                                             const char *grad, const uint32_t *__restrict__ table, const WsLayout &wl,
                                              const SelDev *__restrict__ sel, uint64_t *tile_cnt,
                                              uint64_t *group_cnt, uint32_t *__restrict__ idx_out,
                                              float *__restrict__ val_out,
@@ -2020,7 +2050,7 @@ __device__ __forceinline__ void compact_body(CompactLds<DTYPE, STAGED> *lds, uin
     __shared__ uint32_t s_wave[NWV][4];
     __shared__ uint64_t s_sum[NWV];
 
-    const uint32_t L = table[0], total_tiles = table[1];
+    const uint32_t L = wl.L, total_tiles = wl.total_tiles;
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2242,14 +2272,14 @@ count_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles,
         const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
         uint64_t *sc_cnt = rv.at<uint64_t>(wl.sc_cnt);
         if (WIDE)
-            emit_wide_body<DTYPE, false, 32>(blockIdx.x, n_emit, table, sel, cand, chunk_info,
-                                             wl.n_slots, CAP, sc_cnt, nullptr, nullptr, nullptr);
+            emit_wide_body<DTYPE, false, 32>(blockIdx.x, n_emit, table, wl, sel, cand, chunk_info,
+                                             CAP, sc_cnt, nullptr, nullptr, nullptr);
         else
-            emit_body<DTYPE, false>(nullptr, blockIdx.x, n_emit, table, sel, cand, chunk_info, wl.n_slots,
+            emit_body<DTYPE, false>(nullptr, blockIdx.x, n_emit, table, wl, sel, cand, chunk_info,
                                     CAP, sc_cnt, nullptr, nullptr, nullptr);
     } else
         compact_body<DTYPE, COMPACT_ROWS, false, false>(
-            nullptr, blockIdx.x - n_emit, gridDim.x - n_emit, plan_tiles, rv.src(), table, sel,
+            nullptr, blockIdx.x - n_emit, gridDim.x - n_emit, plan_tiles, rv.src(), table, wl, sel,
             rv.at<uint64_t>(wl.tile_cnt), rv.at<uint64_t>(wl.group_cnt), nullptr, nullptr, nullptr);
 }
 
@@ -2272,21 +2302,21 @@ place_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles, uint32_t
     const SelDev *sel = rv.at<SelDev>(wl.sel);
     if (blockIdx.x == gridDim.x - 1) {  // (any one workgroup: the last has the least to do)
         __shared__ uint32_t s_cnt[8];
-        write_rank_counts(table, rv.slot, sel, rv.cnt, s_cnt);
+        write_rank_counts(table, wl.L, rv.slot, sel, rv.cnt, s_cnt);
     }
     if (blockIdx.x < n_emit) {
         const uint32_t *cand = rv.at<uint32_t>(wl.cand);
         const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
         uint64_t *sc_cnt = rv.at<uint64_t>(wl.sc_cnt);
         if constexpr (WIDE)
-            emit_wide_body<DTYPE, true, 16>(blockIdx.x, n_emit, table, sel, cand, chunk_info,
-                                            wl.n_slots, CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
+            emit_wide_body<DTYPE, true, 16>(blockIdx.x, n_emit, table, wl, sel, cand, chunk_info,
+                                            CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
         else
-            emit_body<DTYPE, true>(&lds.emit, blockIdx.x, n_emit, table, sel, cand, chunk_info, wl.n_slots,
+            emit_body<DTYPE, true>(&lds.emit, blockIdx.x, n_emit, table, wl, sel, cand, chunk_info,
                                    CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
     } else
         compact_body<DTYPE, COMPACT_ROWS, true, STAGED>(
-            &lds.compact, blockIdx.x - n_emit, gridDim.x - n_emit, plan_tiles, rv.src(), table, sel,
+            &lds.compact, blockIdx.x - n_emit, gridDim.x - n_emit, plan_tiles, rv.src(), table, wl, sel,
             rv.at<uint64_t>(wl.tile_cnt), rv.at<uint64_t>(wl.group_cnt), rv.idx, rv.val, rv.bitmap);
 }
 
@@ -2376,7 +2406,8 @@ WsLayout ws_layout(const tagc_plan_t *p)
 {
     return WsLayout{p->ws.hist1d,   p->ws.hist2,  p->ws.group_cnt,  p->ws.sel,
                     p->ws.tile_cnt, p->ws.sc_cnt, p->ws.chunk_info, p->ws.cand,
-                    uint64_t(p->total_sc) * kCandChunksPerSuper * p->cand_cap};
+                    uint64_t(p->total_sc) * kCandChunksPerSuper * p->cand_cap,
+                    uint32_t(p->table.size()), p->total_tiles, p->total_sc};
 }
 
 SparsifyRank sparsify_rank(const tagc_plan_t *p, const void *grad, const tagc_rank_buffers &rk,
