@@ -678,6 +678,51 @@ struct PartAhead {
 // the first use behind them would wait for them as well.
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
 
+// The dense output of a partition's range [lo, hi) of c-indices, by a workgroup whose thread t has the
+// unknowns t, t + NT, ...: put together in the LDS of the partition, which nobody needs any more, 36864
+// floats at a time -- zeros, the unknowns' values among them, out in 16-byte stores that travel while the
+// next partition is peeled.  Bound by the LDS (written, written to, read: 43 thousand floats a partition
+// take 14 K clocks on top of the peel's 70 K), against 170 us of dense_kernel for 202 M entries, which
+// is bound by the stores.
+template <uint32_t NT, uint32_t kIdx>
+__device__ __forceinline__ void write_dense(const PartLds<true> &p, uint32_t tid, const uint32_t (&idx)[kIdx],
+                                            const float (&val)[kIdx], uint32_t lo, uint32_t hi,
+                                            float *__restrict__ out)
+{
+    constexpr uint32_t kTurns = 9, kPiece = 4 * kTurns * NT;  // floats
+    static_assert(PartLds<true>::kValue % 16 == 0 &&
+                      PartLds<true>::kValue + 4 * kPiece <= PartLds<true>::kPackedBytes,
+                  "a piece lies inside the partition's LDS");
+    const uint32_t area = p.base + PartLds<true>::kValue;
+    for (uint32_t p0 = lo & ~3u; p0 < hi; p0 += kPiece) {
+        const uint32_t n = min(kPiece, (hi - p0 + 3u) & ~3u);
+#pragma unroll 3
+        for (uint32_t i = 0; i < kTurns; ++i) {
+            const uint32_t at = 4 * (tid + i * NT);
+            if (at < n) *lds_at<float4>(area + 4 * at) = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < kIdx; ++q)
+            if (idx[q] - p0 < n) *lds_at<float>(area + 4 * (idx[q] - p0)) = val[q];
+        __syncthreads();
+#pragma unroll 3
+        for (uint32_t i = 0; i < kTurns; ++i) {
+            const uint32_t at = 4 * (tid + i * NT), c = p0 + at;
+            if (at >= n) continue;
+            const float4 v = *lds_at<float4>(area + 4 * at);
+            if (c >= lo && c + 4 <= hi) {
+                st_stream(reinterpret_cast<float4 *>(out + c), v);
+            } else {  // the neighbours' entries are not this partition's to write
+                const float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e)
+                    if (c + e >= lo && c + e < hi) out[c + e] = x[e];
+            }
+        }
+    }
+}
+
 // Peels sketch partitions: unknowns rho .. rho+Pa-1 in order of c-index, cells a*3*m_sub ...
 //
 // The LDS a partition needs leaves room for one workgroup per CU, and the rounds are bound
@@ -695,7 +740,13 @@ constexpr uint32_t kIndexPre = 6;  // groups of Index words a wave requests ahea
 constexpr uint32_t kHeldRanks = 4;  // kRanks of the form for few ranks
 constexpr uint32_t kListGroups = 256;  // groups of Index words per partition beyond which its unknowns are listed first
 // kListed: the unknowns are in index.list.
-template <uint32_t kCellPre, uint32_t kIdxPre, bool kPacked, uint32_t kRanks, bool kLoop, bool kListed>
+// kDense: writes the partitions' part of the dense output as well (dense_kernel has nothing to do).  Where
+// that is stands behind the ranks' sketches: an argument of its own is two scalar registers too many.
+constexpr uint32_t kDenseRow = kMaxRanksPerPass - 1;
+static_assert(kDenseRow >= kHeldRanks, "the forms that write it have few ranks");
+__device__ __forceinline__ float *dense_row() { return (float *)(rank_sketch(kDenseRow)); }
+template <uint32_t kCellPre, uint32_t kIdxPre, bool kPacked, uint32_t kRanks, bool kLoop, bool kListed,
+          bool kDense>
 __global__ void __launch_bounds__(kDecodeThreads)
 peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t *__restrict__ header,
             uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
@@ -710,6 +761,12 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
     const uint32_t cells = 3 * m_sub;
+    if (kDense && A == 0) {  // no partition to write the zeros
+        const uint64_t n4 = uint64_t(index.n_words) * 8;
+        for (uint64_t i = uint64_t(blockIdx.x) * kDecodeThreads + tid; i < n4;
+             i += uint64_t(gridDim.x) * kDecodeThreads)
+            st_stream(reinterpret_cast<float4 *>(dense_row()) + i, make_float4(0.f, 0.f, 0.f, 0.f));
+    }
     if (blockIdx.x >= A) return;
     PartLds<kPacked> part(lds64, T_cap, P_cap, m_sub);
 
@@ -803,6 +860,14 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     // the registers are free again: the next partition's data travels during the rounds
     at.next();
     if (!kLoop && at.a < A) prefetch(false);
+    uint32_t idx[kDense ? kIdxPre : 1];
+    if constexpr (kDense) {  // (this thread wrote them in join_cells; back long before the rounds are over)
+#pragma unroll
+        for (uint32_t q = 0; q < kIdxPre; ++q) {
+            const uint32_t u = tid + q * kDecodeThreads;
+            idx[q] = u < Pa ? idx_out[rho0 + u] : 0xFFFFFFFFu;
+        }
+    }
     PHASE_MARK(1);
 
     const uint32_t resolved =
@@ -812,7 +877,25 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     // ---- values leave in one contiguous sweep (stored one by one as they were found they
     // would cost a cache-line access each)
     wait_loads();
-    for (uint32_t u = tid; u < Pa; u += kDecodeThreads) val_out[rho0 + u] = unknown_value(part, u, mode);
+    if constexpr (kDense) {
+        asm volatile("" : "+v"(tid));  // (as above)
+        // all c-indices lie in a partition's range, those before the first unknown in the first one's
+        // (read again: kept, the bounds take a vector register to spill)
+        const uint32_t a = at.a - at.step;
+        const uint32_t lo = a ? index.bounds[a] : 0u, hi = min(index.bounds[a + 1], 32 * index.n_words);
+        float val[kIdxPre];
+#pragma unroll
+        for (uint32_t q = 0; q < kIdxPre; ++q) {
+            const uint32_t u = tid + q * kDecodeThreads;
+            val[q] = u < Pa ? unknown_value(part, u, mode) : 0.0f;
+            if (u < Pa) val_out[rho0 + u] = val[q];
+        }
+        __syncthreads();
+        write_dense<kDecodeThreads, kIdxPre>(part, tid, idx, val, lo, hi, dense_row());
+    } else {
+        for (uint32_t u = tid; u < Pa; u += kDecodeThreads)
+            val_out[rho0 + u] = unknown_value(part, u, mode);
+    }
     if (tid == 0) report_unresolved(Pa - resolved, mode, status);
     PHASE_MARK(3);
     if (kLoop) break;
@@ -1095,19 +1178,31 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     auto pick = [&](auto list) {
         constexpr bool kList = decltype(list)::value;
         return form == 4   ? sum_peel_kernel<kList>
-               : form == 3 ? peel_kernel<kC0, kI0, true, kHeldRanks, true, false>
-               : form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false, kList>
-               : form == 1 ? peel_kernel<kC0, kI0, true, 1, false, kList>
-                           : peel_kernel<kC1, kI1, false, 1, false, kList>;
+               : form == 3 ? peel_kernel<kC0, kI0, true, kHeldRanks, true, false, false>
+               : form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false, kList, false>
+               : form == 1 ? peel_kernel<kC0, kI0, true, 1, false, kList, false>
+                           : peel_kernel<kC1, kI1, false, 1, false, kList, false>;
     };
-    const auto kernel = listed ? pick(std::true_type{}) : pick(std::false_type{});
-    static size_t attr_bytes[2][5] = {};
-    if (lds > attr_bytes[listed][form]) {
+    // The dense output by the decoder itself, whose rounds leave the memory system idle (sum_peel_kernel's
+    // do not), where there are three turns of partitions to hide all but the last turn's behind, and, since
+    // the union holds at least one rank's pairs, every compute unit has a partition whatever the ranks
+    // share.  A pass, us, dense_kernel / by the decoder: 2 ranks of 202 M entries with a tenth kept 1498 /
+    // 1443, with a fifth 2390 / 2280, of 200 M with 2.5 % 649 / 635, of 40 M with a tenth (929 partitions)
+    // 371 / 364, 4 ranks of 9 M with two fifths (917) 363 / 354; one rank of 42 M (519) 298 / 303.
+    const bool with_dense = dense_out && !listed && (form == 1 || form == 2) && !p->cfg.decode_workgroups &&
+                            p->A_cap >= 3ull * grid && p->K >= uint64_t(grid) * p->P_cap;
+    const auto kernel = with_dense ? (form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false, false, true>
+                                                : peel_kernel<kC0, kI0, true, 1, false, false, true>)
+                        : listed   ? pick(std::true_type{})
+                                   : pick(std::false_type{});
+    static size_t attr_bytes[3][5] = {};
+    if (lds > attr_bytes[with_dense ? 2 : listed][form]) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
             return TAGC_EHIP;
-        attr_bytes[listed][form] = lds;
+        attr_bytes[with_dense ? 2 : listed][form] = lds;
     }
+    if (with_dense) rp.p[kDenseRow] = dense_out;
     if (listed) {
         ProfileScope ps("enumerate", s);
         enumerate_kernel<<<n_chunks, 256, 0, s>>>(index, sh->header, idx_out);
@@ -1118,7 +1213,7 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
                                                  sh->status, p->cfg.seed, sh->bounds + p->A_cap + 1,
                                                  p->T_cap, p->P_cap, p->cfg.decode_mode);
     }
-    if (dense_out && n_chunks) {
+    if (dense_out && n_chunks && !with_dense) {
         ProfileScope ps("dense", s);
         dense_kernel<<<n_chunks, kChunkWords, 0, s>>>(sh->bitmap, n_words, chunkpre, sh->header, val_out,
                                               dense_out);

@@ -1,0 +1,60 @@
+"""The dense output written by the decoder's workgroups, partition by partition (there are three
+turns of partitions or more), against the oracle: ranges that start and end anywhere, ranges longer than what
+is put together at once, partitions without an unknown, nothing kept at all.  Small integers, so values
+must agree bit for bit.  The output is filled with something else before the call that is looked at."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tagc_oracle as O
+from synth import gradients as G
+from tests.helpers import run_both, compare_all
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(b, grads, **kw):
+    fused = kw.get("fused", False)
+    ores, tb = run_both(b, grads, seed=5, **kw)
+    tb.out_dense.fill_(0x55)
+    tb.run([g.cuda() for g in grads], fused=fused)
+    torch.cuda.synchronize()
+    compare_all(b, ores, tb, exact_values=True)
+    return ores
+
+
+@pytest.mark.parametrize("P,T", [(32, 48), (33, 48), (24, 39)])
+@pytest.mark.parametrize("ranks,fused", [(1, False), (2, True), (4, True), (3, False)])
+@pytest.mark.parametrize("milli,mode", [(1500, O.DECODE_PEEL), (1150, O.DECODE_PEEL_ESTIMATE)])
+def test_ranges_of_any_length(P, T, ranks, fused, milli, mode):
+    print("\n[case] dense in decoder P=%d ranks=%d fused=%d milli=%d" % (P, ranks, fused, milli), flush=True)
+    # a quarter kept; one entry in ten thousand over four pieces' length; two fifths kept
+    segs = [G.Seg(0, 100_003, 250_000, 1, "a"), G.Seg(100_008, 149_997, 100, 1, "b"),
+            G.Seg(250_008, 3001, 400_000, 1, "c")]
+    n = 253_009
+    b = G.Bucket("dense_in_decoder", G.F32, ranks, segs, n, milli)
+    rng = np.random.default_rng(ranks)
+    grads = [torch.from_numpy(rng.integers(-1000, 1001, n).astype(np.float32)) for _ in range(ranks)]
+    ores = _check(b, grads, P=P, T=T, fused=fused, decode_mode=mode)
+    assert sum(s.length * s.keep_ppm // 1_000_000 for s in segs) >= 3 * 256 * P
+    assert np.diff(ores.bnd.astype(np.int64)).max() > 2 * 36864
+
+
+@pytest.mark.parametrize("kept", [0, 1, 3])
+@pytest.mark.parametrize("fused", [False, True])
+def test_hardly_anything_kept(kept, fused):
+    print("\n[case] dense in decoder kept=%d fused=%d" % (kept, fused), flush=True)
+    n = 200_001
+    b = G.Bucket("dense_in_decoder", G.F32, 2, [G.Seg(0, n, 250_000, 1, "w")], n, 4000)
+    grads = [torch.zeros(n) for _ in range(2)]
+    for r, g in enumerate(grads):
+        g[[0, 77, n - 1][:kept]] = float(r + 1)
+    _check(b, grads, P=32, T=48, sizing=O.SIZE_FIXED_RATIO, fused=fused)
+
+
+def test_default_partitions():
+    print("\n[case] dense in decoder, default partitions", flush=True)
+    n = 7_200_001
+    b = G.Bucket("dense_in_decoder", G.BF16, 1, [G.Seg(0, n, 900_000, 1, "w")], n, 1500)
+    g = torch.randint(-200, 201, (n,), generator=torch.Generator().manual_seed(3)).to(torch.bfloat16)
+    _check(b, [g], fused=True)
