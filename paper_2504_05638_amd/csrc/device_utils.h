@@ -92,14 +92,25 @@ __device__ inline T block_sum(T v, T *smem)
 // clocks on this hardware (measured: 192 clocks per wave instruction against 6 for the
 // integer ones), so the add is done with an integer compare-and-swap instead; collisions
 // are rare in every use here, so the loop almost always runs once.
-__device__ inline void lds_add_f32(float *p, float v)
+// Three adds to three different words: read together, swapped together, what found another value swapped
+// again alone.
+__device__ inline void lds_add_f32(float *const (&p)[3], const float (&v)[3])
 {
-    uint32_t *w = reinterpret_cast<uint32_t *>(p);
-    uint32_t old = *w, assumed;
-    do {
-        assumed = old;
-        old = atomicCAS(w, assumed, __float_as_uint(__uint_as_float(assumed) + v));
-    } while (old != assumed);
+    uint32_t *w[3], was[3], got[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        w[j] = reinterpret_cast<uint32_t *>(p[j]);
+        was[j] = *w[j];
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        got[j] = atomicCAS(w[j], was[j], __float_as_uint(__uint_as_float(was[j]) + v[j]));
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        while (got[j] != was[j]) {
+            was[j] = got[j];
+            got[j] = atomicCAS(w[j], was[j], __float_as_uint(__uint_as_float(was[j]) + v[j]));
+        }
 }
 
 // LDS add by every active lane for itself, returning what was there.  (An address the compiler cannot
