@@ -45,16 +45,18 @@ encode_kernel(const EncodeBatch, const uint32_t *__restrict__ header, uint64_t s
     constexpr uint32_t NT = kEncodeThreads;
     extern __shared__ float tile[];  // the partition's three sub-tables, as in the sketch
     const uint32_t A = header[TAGC_HDR_A], m_sub = header[TAGC_HDR_MSUB];
-    const uint32_t a = blockIdx.x;
+    const uint32_t a = blockIdx.x;  // (the grid ends where the room for salts and ranges does)
+    // the partition's salt and the ends of its run of the sorted pair list, found when the Index was
+    // aggregated: requested with the header and not behind it
+    uint32_t sa = salt[a], lo = cnt[ranges_off + a], hi = cnt[ranges_off + a + 1];
+    asm volatile("" : "+s"(sa), "+s"(lo), "+s"(hi));
     if (a >= A) return;
     const uint32_t cells = 3 * m_sub;
     // the partition's hash functions: the seed under the salt the Index aggregation chose
-    const uint32_t sa = salt[a];
     const uint32_t fsw0 = fold16(seed_word(seed, 3 * sa)), fsw1 = fold16(seed_word(seed, 3 * sa + 1)),
                    fsw2 = fold16(seed_word(seed, 3 * sa + 2));
-    // the partition's run of the sorted pair list, found when the Index was aggregated
-    const uint32_t lo = min(cnt[ranges_off + a], pair_cap);
-    const uint32_t hi = min(cnt[ranges_off + a + 1], pair_cap);
+    lo = min(lo, pair_cap);
+    hi = min(hi, pair_cap);
     // after an addition-simulated Index All-Reduce (section 2.2) the merged Index need not
     // hold every pair: only the positions it names are encoded (mask = merged Index then)
     auto named = [&](uint32_t i) { return !mask || ((mask[i >> 5] >> (i & 31)) & 1u); };
