@@ -20,6 +20,14 @@ extern "C" {
 void tagc_hash_host(uint32_t i, uint64_t seed, uint32_t j, uint32_t salt, uint32_t m_sub,
                     uint32_t *slot, int32_t *sign);
 
+/*
+ * The pieces in which a decoder workgroup writes the dense output of the c-indices
+ * [lo, hi), lo < hi: piece i is n[i] floats from c-index at[i] on (floats before lo
+ * or from hi on are not stored).  Returns how many there are; goes no further than
+ * cap + 1, and writes no more than cap.  Host memory only.
+ */
+uint32_t tagc_dense_pieces_host(uint32_t lo, uint32_t hi, uint32_t *at, uint32_t *n, uint32_t cap);
+
 #ifdef __cplusplus
 }
 #endif

@@ -31,7 +31,7 @@ TAGC_STATIC_WORKSPACE_BYTES = 16 << 20
 EXPORTS = ["tagc_plan", "tagc_plan_destroy", "tagc_plan_sizes",
            "tagc_plan_upload", "tagc_compress", "tagc_compress_ranks", "tagc_compress_static", "tagc_feedback_apply", "tagc_aggregate",
            "tagc_decompress", "tagc_reduce_decompress", "tagc_profile_enable", "tagc_profile_read",
-           "tagc_hash_host", "tagc_strerror"]
+           "tagc_hash_host", "tagc_dense_pieces_host", "tagc_strerror"]
 
 
 class tagc_segment(C.Structure):
@@ -152,6 +152,9 @@ def lib():
         L.tagc_hash_host.argtypes = [C.c_uint32, C.c_uint64, C.c_uint32, C.c_uint32,
                                      C.c_uint32, C.POINTER(C.c_uint32),
                                      C.POINTER(C.c_int32)]
+        L.tagc_dense_pieces_host.restype = C.c_uint32
+        L.tagc_dense_pieces_host.argtypes = [C.c_uint32, C.c_uint32, C.POINTER(C.c_uint32),
+                                             C.POINTER(C.c_uint32), C.c_uint32]
         L.tagc_strerror.restype = C.c_char_p
         L.tagc_strerror.argtypes = [C.c_int]
         _lib = L
@@ -274,3 +277,10 @@ def tagc_hash_host(i, seed, j, m_sub, salt=0):
     slot, sign = C.c_uint32(), C.c_int32()
     lib().tagc_hash_host(i, seed, j, salt, m_sub, C.byref(slot), C.byref(sign))
     return int(slot.value), int(sign.value)
+
+
+def tagc_dense_pieces_host(lo, hi, cap=256):
+    """[(first c-index, floats)] of the decoder's dense pieces of [lo, hi); None if more than cap."""
+    at, n = (C.c_uint32 * cap)(), (C.c_uint32 * cap)()
+    k = lib().tagc_dense_pieces_host(lo, hi, at, n, cap)
+    return list(zip(at[:k], n[:k])) if k <= cap else None

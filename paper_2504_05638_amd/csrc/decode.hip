@@ -689,13 +689,15 @@ __device__ __forceinline__ void write_dense(const PartLds<true> &p, uint32_t tid
                                             const float (&val)[kIdx], uint32_t lo, uint32_t hi,
                                             float *__restrict__ out)
 {
-    constexpr uint32_t kTurns = 9, kPiece = 4 * kTurns * NT;  // floats
-    static_assert(PartLds<true>::kValue % 16 == 0 &&
-                      PartLds<true>::kValue + 4 * kPiece <= PartLds<true>::kPackedBytes,
-                  "a piece lies inside the partition's LDS");
+    constexpr uint32_t kTurns = kDensePiece / (4 * NT);
+    static_assert(kDensePiece == 4 * kTurns * NT && PartLds<true>::kValue % 16 == 0 &&
+                      PartLds<true>::kValue + 4 * kDensePiece <= PartLds<true>::kPackedBytes,
+                  "a piece is whole turns and lies inside the partition's LDS");
     const uint32_t area = p.base + PartLds<true>::kValue;
-    for (uint32_t p0 = lo & ~3u; p0 < hi; p0 += kPiece) {
-        const uint32_t n = min(kPiece, (hi - p0 + 3u) & ~3u);
+    if (lo >= hi) return;
+    DensePieces piece(lo, hi);
+    do {
+        const uint32_t p0 = piece.at, n = piece.n;
 #pragma unroll 3
         for (uint32_t i = 0; i < kTurns; ++i) {
             const uint32_t at = 4 * (tid + i * NT);
@@ -720,7 +722,7 @@ __device__ __forceinline__ void write_dense(const PartLds<true> &p, uint32_t tid
                     if (c + e >= lo && c + e < hi) out[c + e] = x[e];
             }
         }
-    }
+    } while (piece.next());
 }
 
 // Peels sketch partitions: unknowns rho .. rho+Pa-1 in order of c-index, cells a*3*m_sub ...

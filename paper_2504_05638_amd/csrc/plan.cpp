@@ -428,6 +428,18 @@ extern "C" void tagc_hash_host(uint32_t i, uint64_t seed, uint32_t j, uint32_t s
     *sign = neg ? -1 : 1;
 }
 
+extern "C" uint32_t tagc_dense_pieces_host(uint32_t lo, uint32_t hi, uint32_t *at, uint32_t *n, uint32_t cap)
+{
+    DensePieces piece(lo, hi);
+    uint32_t k = 0;
+    do {
+        if (k == cap) return cap + 1;
+        at[k] = piece.at;
+        n[k++] = piece.n;
+    } while (piece.next());
+    return k;
+}
+
 extern "C" const char *tagc_strerror(int err)
 {
     switch (err) {

@@ -45,6 +45,25 @@ constexpr uint32_t kMaxPartUnknowns = 16384;   // local ranks fit 14 bits
 constexpr uint32_t kDecodeThreads = 1024;
 constexpr uint32_t kLdsBytes = 160 * 1024;
 constexpr uint32_t kMaxRanksPerPass = 32;
+// A range [lo, hi) of c-indices in the pieces in which the decoder's workgroup puts its dense output
+// together: n floats from c-index `at` (a multiple of 4) on.  lo < hi.
+constexpr uint32_t kDensePiece = 36 * kDecodeThreads;
+struct DensePieces {
+    uint32_t at, n, end;
+    __host__ __device__ DensePieces(uint32_t lo, uint32_t hi) : at(lo & ~3u), n(0), end(hi) { size(); }
+    __host__ __device__ bool next()
+    {
+        if (end - at <= kDensePiece) return false;  // (a step could go past 2^32)
+        at += kDensePiece;
+        size();
+        return true;
+    }
+    __host__ __device__ void size()
+    {
+        const uint32_t left = (end - at + 3u) & ~3u;
+        n = left < kDensePiece ? left : kDensePiece;
+    }
+};
 // Candidate histogram of the single-read route: the bins from a segment's pre-threshold
 // upwards (12 octaves of magnitude: a gradient may grow 4000-fold between two calls before
 // its threshold leaves the window); then one count of everything above them, one of the
