@@ -742,8 +742,9 @@ constexpr uint32_t kIndexPre = 6;  // groups of Index words a wave requests ahea
 constexpr uint32_t kHeldRanks = 4;  // kRanks of the form for few ranks
 constexpr uint32_t kListGroups = 256;  // groups of Index words per partition beyond which its unknowns are listed first
 // kListed: the unknowns are in index.list.
-// kDense: writes the partitions' part of the dense output as well (dense_kernel has nothing to do).  Where
-// that is stands behind the ranks' sketches: an argument of its own is two scalar registers too many.
+// kDense: writes the dense output of the partitions that dense_by_decoder names as well (dense_rest_kernel
+// has the others').  Where that is stands behind the ranks' sketches: an argument of its own is two scalar
+// registers too many.
 constexpr uint32_t kDenseRow = kMaxRanksPerPass - 1;
 static_assert(kDenseRow >= kHeldRanks, "the forms that write it have few ranks");
 __device__ __forceinline__ float *dense_row() { return (float *)(rank_sketch(kDenseRow)); }
@@ -763,12 +764,6 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
     const uint32_t cells = 3 * m_sub;
-    if (kDense && A == 0) {  // no partition to write the zeros
-        const uint64_t n4 = uint64_t(index.n_words) * 8;
-        for (uint64_t i = uint64_t(blockIdx.x) * kDecodeThreads + tid; i < n4;
-             i += uint64_t(gridDim.x) * kDecodeThreads)
-            st_stream(reinterpret_cast<float4 *>(dense_row()) + i, make_float4(0.f, 0.f, 0.f, 0.f));
-    }
     if (blockIdx.x >= A) return;
     PartLds<kPacked> part(lds64, T_cap, P_cap, m_sub);
 
@@ -892,8 +887,10 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
             val[q] = u < Pa ? unknown_value(part, u, mode) : 0.0f;
             if (u < Pa) val_out[rho0 + u] = val[q];
         }
-        __syncthreads();
-        write_dense<kDecodeThreads, kIdxPre>(part, tid, idx, val, lo, hi, dense_row());
+        if (dense_by_decoder(A, gridDim.x, 32 * index.n_words, hi - lo)) {
+            __syncthreads();
+            write_dense<kDecodeThreads, kIdxPre>(part, tid, idx, val, lo, hi, dense_row());
+        }
     } else {
         for (uint32_t u = tid; u < Pa; u += kDecodeThreads)
             val_out[rho0 + u] = unknown_value(part, u, mode);
@@ -1074,20 +1071,18 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
 // count plus a popcount -- so the output goes out in plain contiguous 16-byte stores.
 constexpr uint32_t kDenseStage = 8192;
 
-__global__ void __launch_bounds__(kChunkWords)
-dense_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words,
-             const uint32_t *__restrict__ chunkpre, const uint32_t *__restrict__ header,
-             const float *__restrict__ val_out, float *__restrict__ dense_out)
+__device__ __forceinline__ void write_chunk(uint32_t chunk, const uint32_t *__restrict__ bitmap,
+                                            uint32_t n_words, const uint32_t *__restrict__ chunkpre, uint32_t U,
+                                            const float *__restrict__ val_out, float *__restrict__ dense_out)
 {
     constexpr uint32_t NT = kChunkWords;  // one thread per Index word of the chunk
     __shared__ uint32_t scratch[NT / 64];
     __shared__ uint32_t s_word[kChunkWords], s_pre[kChunkWords];
     __shared__ float vals[kDenseStage];
-    const uint32_t U = header[TAGC_HDR_U];
     const uint32_t tid = threadIdx.x;
-    const uint32_t cw0 = blockIdx.x * kChunkWords;  // first word of the chunk
+    const uint32_t cw0 = chunk * kChunkWords;  // first word of the chunk
     const uint32_t word = cw0 + tid < n_words ? bitmap[cw0 + tid] : 0u;
-    const uint32_t base = chunkpre[blockIdx.x];
+    const uint32_t base = chunkpre[chunk];
     uint32_t tot;
     const uint32_t pre = block_excl_scan<uint32_t, NT / 64>(uint32_t(__popc(word)), &tot, scratch);
     s_word[tid] = word;
@@ -1113,6 +1108,48 @@ dense_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words,
             }
         }
         st_stream(out + c, make_float4(o[0], o[1], o[2], o[3]));
+    }
+}
+
+__global__ void __launch_bounds__(kChunkWords)
+dense_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words,
+             const uint32_t *__restrict__ chunkpre, const uint32_t *__restrict__ header,
+             const float *__restrict__ val_out, float *__restrict__ dense_out)
+{
+    write_chunk(blockIdx.x, bitmap, n_words, chunkpre, header[TAGC_HDR_U], val_out, dense_out);
+}
+
+// What a decoder of peel_grid workgroups that writes the dense output has left of it: the chunks that hold
+// c-indices of a partition that was not its to write (what else they hold is written again, with the same
+// values).  A workgroup has the chunks b, b + grid, ..., marked while all its threads go through the
+// partitions' ends.
+constexpr uint32_t kRestMarks = 128;  // words of marks: chunks of a workgroup / 32
+constexpr uint32_t kRestGrid = (1u << 17) / (32 * kRestMarks);  // fewest workgroups for 2^32 c-indices
+static_assert((uint64_t(kRestGrid) * 32 * kRestMarks) * kChunkWords * 32 >= 1ull << 32, "marks for all chunks");
+__global__ void __launch_bounds__(kChunkWords)
+dense_rest_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words, const uint32_t *__restrict__ chunkpre,
+                  uint32_t n_chunks, const uint32_t *__restrict__ header, const uint32_t *__restrict__ bounds,
+                  uint32_t peel_grid, const float *__restrict__ val_out, float *__restrict__ dense_out)
+{
+    __shared__ uint32_t marks[kRestMarks];
+    const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
+    const uint32_t tid = threadIdx.x, b = blockIdx.x, grid = gridDim.x, n_c = 32 * n_words;
+    const bool all = !dense_by_decoder(A, peel_grid, n_c, 0);
+    if (tid < kRestMarks) marks[tid] = all ? 0xFFFFFFFFu : 0u;
+    __syncthreads();
+    for (uint32_t a = tid; !all && a < A; a += kChunkWords) {
+        const uint32_t lo = a ? bounds[a] : 0u, hi = min(bounds[a + 1], n_c);
+        if (lo >= hi || dense_by_decoder(A, peel_grid, n_c, hi - lo)) continue;
+        // its chunks among b, b + grid, ...
+        const uint32_t first = lo / (32 * kChunkWords), last = (hi - 1) / (32 * kChunkWords);
+        for (uint32_t k = first > b ? (first - b + grid - 1) / grid : 0u; b + k * grid <= last; ++k)
+            atomicOr(&marks[k >> 5], 1u << (k & 31));
+    }
+    __syncthreads();
+    for (uint32_t k = 0; b + k * grid < n_chunks; ++k) {
+        if (!((marks[k >> 5] >> (k & 31)) & 1u)) continue;
+        write_chunk(b + k * grid, bitmap, n_words, chunkpre, U, val_out, dense_out);
+        __syncthreads();
     }
 }
 
@@ -1186,11 +1223,13 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
                            : peel_kernel<kC1, kI1, false, 1, false, kList, false>;
     };
     // The dense output by the decoder itself, whose rounds leave the memory system idle (sum_peel_kernel's
-    // do not), where there are three turns of partitions to hide all but the last turn's behind, and, since
-    // the union holds at least one rank's pairs, every compute unit has a partition whatever the ranks
-    // share.  A pass, us, dense_kernel / by the decoder: 2 ranks of 202 M entries with a tenth kept 1498 /
-    // 1443, with a fifth 2390 / 2280, of 200 M with 2.5 % 649 / 635, of 40 M with a tenth (929 partitions)
-    // 371 / 364, 4 ranks of 9 M with two fifths (917) 363 / 354; one rank of 42 M (519) 298 / 303.
+    // do not), where the plan has room for three turns of partitions to hide all but the last turn's behind, and
+    // one rank's pairs alone give every compute unit a partition.  That is what the plan can know: which
+    // partitions' output it really writes the device decides (dense_by_decoder), and a small launch behind
+    // it, 5 us where nothing is left, writes the rest.  Decoder and dense output, us, dense_kernel / by the
+    // decoder: 2 ranks of 202 M entries with a tenth kept 710 / 684, in four layers with 5 to 20 % 628 / 593, of
+    // 200 M with 2.5 % 296 / 283, of 40 M with a tenth (928 partitions) 165 / 159; one rank of 32 M with a fifth
+    // (782) 132 / 133; 200 M nearly all zeros, two partitions, 338 / 341 (6584 by their two workgroups).
     const bool with_dense = dense_out && !listed && (form == 1 || form == 2) && !p->cfg.decode_workgroups &&
                             p->A_cap >= 3ull * grid && p->K >= uint64_t(grid) * p->P_cap;
     const auto kernel = with_dense ? (form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false, false, true>
@@ -1215,7 +1254,12 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
                                                  sh->status, p->cfg.seed, sh->bounds + p->A_cap + 1,
                                                  p->T_cap, p->P_cap, p->cfg.decode_mode);
     }
-    if (dense_out && n_chunks && !with_dense) {
+    if (with_dense) {
+        ProfileScope ps("dense_rest", s);
+        const uint32_t n = std::min(n_chunks, std::max(2 * uint32_t(device_cu_count()), kRestGrid));
+        dense_rest_kernel<<<n, kChunkWords, 0, s>>>(sh->bitmap, n_words, chunkpre, n_chunks, sh->header, sh->bounds,
+                                                    grid, val_out, dense_out);
+    } else if (dense_out && n_chunks) {
         ProfileScope ps("dense", s);
         dense_kernel<<<n_chunks, kChunkWords, 0, s>>>(sh->bitmap, n_words, chunkpre, sh->header, val_out,
                                               dense_out);

@@ -64,6 +64,18 @@ struct DensePieces {
         n = left < kDensePiece ? left : kDensePiece;
     }
 };
+// Whether a decoder of `grid` workgroups writes the dense output of a partition's `len` c-indices itself, A
+// partitions sharing n_c c-indices: only if there are three turns of partitions to hide it behind, and
+// the partition has no more than kDenseShare times an even share.  Both depend on what the device finds: exact
+// zeros are never kept, so that few partitions may be left of a large plan, and a layer of which little is
+// kept is a few partitions however long it is; one workgroup stores some 30 GB/s.  (A share of 2 / 4 / 8,
+// decoder and dense output, us: 2 ranks of 200 M entries in four layers with 5 to 20 % kept 627 / 593 / 594; 150 M
+// with 1 % beside 50 M with 20 % 432 / 431 / 451.)
+constexpr uint32_t kDenseShare = 4;
+__host__ __device__ inline bool dense_by_decoder(uint32_t A, uint32_t grid, uint32_t n_c, uint32_t len)
+{
+    return A >= 3ull * grid && len / kDenseShare <= n_c / A;
+}
 // Candidate histogram of the single-read route: the bins from a segment's pre-threshold
 // upwards (12 octaves of magnitude: a gradient may grow 4000-fold between two calls before
 // its threshold leaves the window); then one count of everything above them, one of the

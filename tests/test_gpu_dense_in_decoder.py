@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from oracle import tagc_oracle as O
+from paper_2504_05638_amd import binding as B
 from synth import gradients as G
 from tests.helpers import run_both, compare_all
 
@@ -58,3 +59,43 @@ def test_default_partitions():
     b = G.Bucket("dense_in_decoder", G.BF16, 1, [G.Seg(0, n, 900_000, 1, "w")], n, 1500)
     g = torch.randint(-200, 201, (n,), generator=torch.Generator().manual_seed(3)).to(torch.bfloat16)
     _check(b, [g], fused=True)
+
+
+# Ranges far longer than the others', or far fewer partitions than the plan has room for: one workgroup
+# stores some 30 GB/s, which is 2 ms for the 64 MB of such a range.
+@pytest.mark.parametrize("what", ["one segment keeps little", "a plan's few partitions", "mostly zeros, fixed ratio"])
+@pytest.mark.parametrize("ranks,fused", [(1, False), (2, True)])
+def test_long_ranges_go_to_the_whole_device(what, ranks, fused):
+    print("\n[case] dense in decoder, %s, ranks=%d" % (what, ranks), flush=True)
+    n, sizing, milli = 16_000_000, O.SIZE_LOAD_FACTOR, 1500
+    segs = [G.Seg(0, n, 8000, 1, "a")]
+    if what == "one segment keeps little":
+        segs = [G.Seg(0, n, 5, 1, "a"), G.Seg(n, 256_000, 250_000, 1, "b"), G.Seg(n + 256_000, n, 5, 1, "c")]
+        n = 2 * n + 256_000
+    elif what.endswith("ratio"):
+        sizing, milli = O.SIZE_FIXED_RATIO, 100_000
+    b = G.Bucket("dense_in_decoder", G.F32, ranks, segs, n, milli)
+    rng = np.random.default_rng(ranks)
+    grads = []
+    for _ in range(ranks):
+        if len(segs) == 3:
+            g = rng.integers(1, 1001, n).astype(np.float32)
+        else:  # (all within the first thousandth: the last partitions' range is the rest)
+            g = np.zeros(n, np.float32)
+            g[rng.choice(n // 1000, 3000, replace=False)] = rng.integers(1, 1001, 3000)
+        grads.append(torch.from_numpy(g))
+    ores, tb = run_both(b, grads, seed=5, P=32, T=48, sizing=sizing, fused=fused)
+    dev = [g.cuda() for g in grads]
+    tb.out_dense.fill_(0x55)
+    torch.cuda.synchronize()
+    B.tagc_profile_enable(True)
+    tb.run(dev, fused=fused)
+    torch.cuda.synchronize()
+    B.tagc_profile_enable(False)
+    took = B.tagc_profile_read()
+    print(took, flush=True)
+    assert "dense" not in took and took["dense_rest"][1] == 1
+    # (12 us a turn of rounds, 14 turns in the largest case; 30 GB/s for what lies between two ends)
+    longest = 4 * np.diff(ores.bnd.astype(np.int64)).max() / 30e6
+    assert took["sum_peel" if fused else "peel"][0] + took["dense_rest"][0] < 0.5 < longest
+    compare_all(b, ores, tb, exact_values=True)
