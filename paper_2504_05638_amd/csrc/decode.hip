@@ -394,6 +394,10 @@ __device__ __forceinline__ uint32_t peel_rounds(const PartLds<kPacked> &p, uint3
                     h += n;
                     n = uniform(queued);  // (lane 0 had an entry)
                     ++rounds;
+                    // (the next entries, and all that is in the cells, may be other lanes' stores)
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 } while (n - 1 < 64);
                 if (lane == 0) *p.handed() = make_uint4(h, n, rounds, 0);
             }
