@@ -228,7 +228,8 @@ constexpr uint64_t kSplitSearches = 32768;  // (partition, rank) pairs
 constexpr uint32_t kSaltLimit = 16;       // salts tried: 0 .. 15
 constexpr uint32_t kNoLink = 0xFFFFu;
 constexpr uint32_t kFilterBits = 64;      // per cell of a sub-table
-constexpr uint32_t kSecondWords = 1024;   // second filter
+constexpr uint32_t kSecondWords = 1024;   // second filter, cleared a word per thread
+static_assert(kSecondWords == kSaltThreads, "every thread clears its word");
 constexpr uint32_t kSaltPer = kDefaultPartUnknowns / kSaltThreads;  // non-zeros per thread of a partition of the default size
 constexpr uint32_t kSaltPre = 4;          // Index words per thread requested a partition ahead
 
@@ -259,7 +260,7 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     uint32_t *second = lds_salt;            // [kSecondWords]
     uint32_t *tag = second + kSecondWords;  // [P_cap] c-index; compared as a whole: slot_1 | slot_2 << 16
     // the first filter; behind it in time, list heads and what is compared (see salt_lds_bytes)
-    uint32_t *filter = tag + P_cap;         // [2 * q_cap]
+    uint32_t *filter = tag + P_cap;         // [kFilterBits / 32 * q_cap]
     uint32_t *head = filter;                // [q_cap]
     const uint32_t n_listed = salt_listed(lp.T_cap, P_cap);
     uint32_t *some_tag = head + q_cap;                                      // [n_listed]
@@ -491,7 +492,7 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
             for (salt = 0; salt < kSaltLimit; ++salt) {
                 uint32_t fsw[3];
                 for (uint32_t j = 0; j < 3; ++j) fsw[j] = fold16(seed_word(seed, 3 * salt + j));
-                for (uint32_t c = tid; c < 2 * m_sub; c += kSaltThreads) filter[c] = 0;
+                for (uint32_t c = tid; c < kFilterBits / 32 * m_sub; c += kSaltThreads) filter[c] = 0;
                 second[tid] = 0;
                 if (tid == 0) {
                     s_dup = s_some = 0;
