@@ -40,7 +40,7 @@ constexpr uint32_t kTileGroup = 64;     // dense-route tiles whose counts are al
 // take 153 of the 160 KiB.  (Larger ones: 10 per cell and 4 and a bit per unknown.)
 constexpr uint32_t kDefaultPartCells = 12288;
 constexpr uint32_t kDefaultPartUnknowns = 8192;
-constexpr uint32_t kMaxPartCells = 16383;      // 16 queue sweeps of 1024 threads at most
+constexpr uint32_t kMaxPartCells = 16383;      // 16 registers of cells per decoder thread
 constexpr uint32_t kMaxPartUnknowns = 16384;   // local ranks fit 14 bits
 constexpr uint32_t kDecodeThreads = 1024;
 constexpr uint32_t kLdsBytes = 160 * 1024;

@@ -1,7 +1,9 @@
 """The dense output written by the decoder's workgroups, partition by partition (there are three
-turns of partitions or more), against the oracle: ranges that start and end anywhere, ranges longer than what
-is put together at once, partitions without an unknown, nothing kept at all.  Small integers, so values
-must agree bit for bit.  The output is filled with something else before the call that is looked at."""
+turns of partitions or more), and what is left of it for the launch behind: ranges that start and end anywhere,
+ranges longer than what is put together at once, ranges much longer than the others, partitions without an
+unknown, nothing kept at all, against the oracle.  Small integers, so values must agree bit for bit.  The
+output is filled with something else before the call that is looked at, and the call's kernels are those of
+this form."""
 import numpy as np
 import pytest
 import torch
@@ -14,14 +16,30 @@ from tests.helpers import run_both, compare_all
 pytestmark = pytest.mark.gpu
 
 
-def _check(b, grads, **kw):
+def _check(b, grads, by_decoder=True, **kw):
+    """Returns the oracle's result and the kernels of the call: {name: (ms, launches)}."""
     fused = kw.get("fused", False)
     ores, tb = run_both(b, grads, seed=5, **kw)
+    dev = [g.cuda() for g in grads]
     tb.out_dense.fill_(0x55)
-    tb.run([g.cuda() for g in grads], fused=fused)
     torch.cuda.synchronize()
+    B.tagc_profile_enable(True)
+    try:
+        tb.run(dev, fused=fused)
+        torch.cuda.synchronize()
+    finally:
+        B.tagc_profile_enable(False)
+    took = B.tagc_profile_read()
+    assert ("dense_rest" in took, "dense" in took) == (by_decoder, not by_decoder), took
     compare_all(b, ores, tb, exact_values=True)
-    return ores
+    return ores, took
+
+
+# Whose output the decoder writes itself: partitions of at most four even shares, if there are three turns
+# of them on a device of 256 compute units.
+def _own(ores):
+    length = np.diff(np.append(0, ores.bnd[1:]).astype(np.int64))
+    return length[length // 4 <= ores.n_c // ores.A] if ores.A >= 3 * 256 else length[:0]
 
 
 @pytest.mark.parametrize("P,T", [(32, 48), (33, 48), (24, 39)])
@@ -36,9 +54,24 @@ def test_ranges_of_any_length(P, T, ranks, fused, milli, mode):
     b = G.Bucket("dense_in_decoder", G.F32, ranks, segs, n, milli)
     rng = np.random.default_rng(ranks)
     grads = [torch.from_numpy(rng.integers(-1000, 1001, n).astype(np.float32)) for _ in range(ranks)]
-    ores = _check(b, grads, P=P, T=T, fused=fused, decode_mode=mode)
-    assert sum(s.length * s.keep_ppm // 1_000_000 for s in segs) >= 3 * 256 * P
-    assert np.diff(ores.bnd.astype(np.int64)).max() > 2 * 36864
+    ores, _ = _check(b, grads, P=P, T=T, fused=fused, decode_mode=mode)
+    # (the second layer's few partitions are not for the decoder)
+    assert 0.9 * ores.A < _own(ores).size < ores.A
+
+
+# One rank: 91 thousand c-indices a partition in the first layer, 30 thousand in the second (three pieces, and one); two: half of that
+@pytest.mark.parametrize("ranks,fused", [(1, False), (2, True)])
+def test_ranges_of_several_pieces(ranks, fused):
+    print("\n[case] dense in decoder, several pieces, ranks=%d" % ranks, flush=True)
+    n = 40_000_037
+    segs = [G.Seg(0, 20_000_001, 350, 1, "a"), G.Seg(20_000_008, 20_000_029, 1050, 1, "b")]
+    b = G.Bucket("dense_in_decoder", G.F32, ranks, segs, n, 1500)
+    rng = np.random.default_rng(ranks)
+    # (up to 32 values and a second rank's in a partition: sums below 2^24 unless half of them share a cell)
+    grads = [torch.from_numpy(rng.integers(-500_000, 500_001, n).astype(np.float32)) for _ in range(ranks)]
+    ores, _ = _check(b, grads, P=32, T=48, fused=fused)
+    own = _own(ores)
+    assert own.size >= 3 * 256 and own.min() <= 36_864 and own.max() > 36_864 * (3 - ranks)
 
 
 @pytest.mark.parametrize("kept", [0, 1, 3])
@@ -50,7 +83,8 @@ def test_hardly_anything_kept(kept, fused):
     grads = [torch.zeros(n) for _ in range(2)]
     for r, g in enumerate(grads):
         g[[0, 77, n - 1][:kept]] = float(r + 1)
-    _check(b, grads, P=32, T=48, sizing=O.SIZE_FIXED_RATIO, fused=fused)
+    ores, _ = _check(b, grads, P=32, T=48, sizing=O.SIZE_FIXED_RATIO, fused=fused)
+    assert ores.A >= 3 * 256 if kept else ores.A == 0
 
 
 def test_default_partitions():
@@ -58,7 +92,16 @@ def test_default_partitions():
     n = 7_200_001
     b = G.Bucket("dense_in_decoder", G.BF16, 1, [G.Seg(0, n, 900_000, 1, "w")], n, 1500)
     g = torch.randint(-200, 201, (n,), generator=torch.Generator().manual_seed(3)).to(torch.bfloat16)
-    _check(b, [g], fused=True)
+    ores, _ = _check(b, [g], fused=True)
+    assert _own(ores).size == ores.A
+
+
+def test_a_plan_of_one_turn():
+    print("\n[case] dense in decoder, one turn", flush=True)
+    n = 20_001
+    b = G.Bucket("dense_in_decoder", G.F32, 1, [G.Seg(0, n, 250_000, 1, "w")], n, 1500)
+    g = torch.from_numpy(np.random.default_rng(0).integers(-1000, 1001, n).astype(np.float32))
+    _check(b, [g], P=32, T=48, by_decoder=False)
 
 
 # Ranges far longer than the others', or far fewer partitions than the plan has room for: one workgroup
@@ -84,18 +127,7 @@ def test_long_ranges_go_to_the_whole_device(what, ranks, fused):
             g = np.zeros(n, np.float32)
             g[rng.choice(n // 1000, 3000, replace=False)] = rng.integers(1, 1001, 3000)
         grads.append(torch.from_numpy(g))
-    ores, tb = run_both(b, grads, seed=5, P=32, T=48, sizing=sizing, fused=fused)
-    dev = [g.cuda() for g in grads]
-    tb.out_dense.fill_(0x55)
-    torch.cuda.synchronize()
-    B.tagc_profile_enable(True)
-    tb.run(dev, fused=fused)
-    torch.cuda.synchronize()
-    B.tagc_profile_enable(False)
-    took = B.tagc_profile_read()
-    print(took, flush=True)
-    assert "dense" not in took and took["dense_rest"][1] == 1
+    ores, took = _check(b, grads, P=32, T=48, sizing=sizing, fused=fused)
     # (12 us a turn of rounds, 14 turns in the largest case; 30 GB/s for what lies between two ends)
     longest = 4 * np.diff(ores.bnd.astype(np.int64)).max() / 30e6
     assert took["sum_peel" if fused else "peel"][0] + took["dense_rest"][0] < 0.5 < longest
-    compare_all(b, ores, tb, exact_values=True)
