@@ -741,7 +741,8 @@ __device__ __forceinline__ void write_dense(const PartLds<true> &p, uint32_t tid
 // the next partition staying in the registers they are loaded to until it is staged.
 // kLoop: over any number of ranks, added up as they come.  For grids that have a workgroup for
 // every partition: there is no next partition whose sum could run beside the rounds, as
-// sum_peel_kernel has it (239 partitions of 8 ranks: 48 us, 52 in that kernel).
+// sum_peel_kernel has it (236 partitions of 8 ranks: 42 us, 48 in that kernel; 20 of 8: 24, 28; 218 of 16:
+// 56, 60).
 constexpr uint32_t kIndexPre = 6;  // groups of Index words a wave requests ahead
 constexpr uint32_t kHeldRanks = 4;  // kRanks of the form for few ranks
 constexpr uint32_t kListGroups = 256;  // groups of Index words per partition beyond which its unknowns are listed first
@@ -1206,14 +1207,15 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     // Partitions that span much of the Index, because little of it can be set: the one workgroup
     // of a partition would go through all of that, most of the device having nothing to do, so a
     // kernel over the whole Index lists the unknowns first.  Decoder alone, us, walking / listing
-    // (enumerate and peel): 202 M entries, 80 thousand unknowns in 10 partitions 189 / 44; 67 M in
-    // 110 partitions, 300 groups each, 42 / 41 (a pass 164 / 160); in 164, 200 groups, 40 / 44
-    // (162 / 163); 7 M in 99 partitions, 35 groups, 45 / 53.
+    // (enumerate and peel): 2 ranks of 202 M entries, 80 thousand unknowns in 10 partitions 189 / 36; 8 ranks
+    // of 67 M in 112 partitions, 290 groups each, 45 / 47 (from the summed sketch 37 / 33); in 164, 200 groups,
+    // 45 / 50 (35 / 35); of 7 M in 103, 33 groups, 35 / 45 (29 / 33).
     const bool listed = 16ull * n_chunks > kListGroups * p->A_cap;
     // One summed sketch; up to four ranks; any number with a workgroup per partition; any number.
-    // (Two ranks of 202 M entries, a tenth kept: 654 us with sixteen waves peeling, 696 in
-    // sum_peel_kernel, of whose sixteen four sum; four ranks of 9 M, two fifths kept: 135 and 141.
-    // More ranks' cells do not fit the registers beside the rounds.)
+    // (Decoder alone, us, sixteen waves peeling / sum_peel_kernel, of whose sixteen four sum: 202 M entries with a
+    // tenth kept, 2 ranks 464 / 507, 4 ranks 900 / 922; 20 to 40 M, 1 to 4 ranks, 25 to 390 partitions, 3 to 4 us
+    // less; 4 ranks of 40 M with 5 % 122 / 122, of 9 M with two fifths 126 / 123.  More ranks' cells do not fit
+    // the registers beside the rounds.)
     const uint32_t form = !fused                  ? (packed_slots(p->T_cap, p->P_cap) ? 1u : 0u)
                           : n_ranks <= kHeldRanks ? 2u
                           : grid == p->A_cap && !listed ? 3u
