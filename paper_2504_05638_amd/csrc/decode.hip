@@ -1142,13 +1142,19 @@ dense_rest_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words, const u
     const bool all = !dense_by_decoder(A, peel_grid, n_c, 0);
     if (tid < kRestMarks) marks[tid] = all ? 0xFFFFFFFFu : 0u;
     __syncthreads();
-    for (uint32_t a = tid; !all && a < A; a += kChunkWords) {
-        const uint32_t lo = a ? bounds[a] : 0u, hi = min(bounds[a + 1], n_c);
-        if (lo >= hi || dense_by_decoder(A, peel_grid, n_c, hi - lo)) continue;
-        // its chunks among b, b + grid, ...
-        const uint32_t first = lo / (32 * kChunkWords), last = (hi - 1) / (32 * kChunkWords);
-        for (uint32_t k = first > b ? (first - b + grid - 1) / grid : 0u; b + k * grid <= last; ++k)
-            atomicOr(&marks[k >> 5], 1u << (k & 31));
+    // (four partitions a thread; the words behind the last bound are the salts)
+    for (uint32_t a0 = 4 * tid; !all && a0 < A; a0 += 4 * kChunkWords) {
+        const uint4 q = *reinterpret_cast<const uint4 *>(bounds + a0);
+        const uint32_t end[5] = {a0 ? q.x : 0u, q.y, q.z, q.w, bounds[a0 + 4]};
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            const uint32_t lo = end[i], hi = min(end[i + 1], n_c);
+            if (a0 + i >= A || lo >= hi || dense_by_decoder(A, peel_grid, n_c, hi - lo)) continue;
+            // its chunks among b, b + grid, ...
+            const uint32_t first = lo / (32 * kChunkWords), last = (hi - 1) / (32 * kChunkWords);
+            for (uint32_t k = first > b ? (first - b + grid - 1) / grid : 0u; b + k * grid <= last; ++k)
+                atomicOr(&marks[k >> 5], 1u << (k & 31));
+        }
     }
     __syncthreads();
     for (uint32_t k = 0; b + k * grid < n_chunks; ++k) {
