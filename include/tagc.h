@@ -96,8 +96,9 @@ typedef struct tagc_config {
                                buckets' work in flight on other streams leaves
                                the rest of the device to them with a value
                                like a quarter of the compute units (and
-                               tagc_aggregate(PHASE_INDEX) then takes the form
-                               that holds least while it waits).  Results
+                               tagc_aggregate(PHASE_INDEX) and
+                               tagc_compress(PHASE_INDEX) then take the forms
+                               that leave them most local memory).  Results
                                and buffer sizes do not depend on it: plans that
                                differ in nothing else work on the same buffers  */
     uint32_t reserved;      /* must be 0                                        */

@@ -446,11 +446,15 @@ constexpr uint32_t kSpillSpan = 128;   // chunks a workgroup's span has at least
 // stores it would run at 6.2 TB/s), so they leave in runs as long as the LDS of two workgroups per
 // compute unit has room for.  bf16, 512 slots and 16 chunks / 1024 and 32, us: one rank 82 / 77,
 // 8 ranks of 67 M 201 / 198, with an accumulator 276 / 270, a tenth kept 225 / 220; fp32, which
-// needs two words a slot, 58 / 65 (one workgroup per compute unit).
-template <int DTYPE>
-constexpr uint32_t kSpillStage = DTYPE == kBF16 ? 1024 : 512;
-template <int DTYPE>
-constexpr uint32_t kSpillList = DTYPE == kBF16 ? 32 : 16;
+// needs two words a slot, 58 / 65 (one workgroup per compute unit).  Not so beside other buckets: two workgroups
+// with the short stage leave 49 KiB, enough for one of another bucket's encoder (48 KiB and 31 registers), with
+// the long one 10.  Buckets of 202 M entries, 12 in flight, ms a step, short / long: 32 from 16 ranks at load factor
+// 1.5 87.4 / 88.3, at 1.15 88.3 / 90.2; 12 from 2 ranks with 3 and 5 % kept 7.6 / 7.7 and 9.7 / 9.7, with a tenth,
+// where a chunk has hundreds of slots and a run of 512 is a chunk or two, 16.1 / 15.9, with a fifth 26.2 / 25.8.
+template <int DTYPE, bool LONG>
+constexpr uint32_t kSpillStage = DTYPE == kBF16 && LONG ? 1024 : 512;
+template <int DTYPE, bool LONG>
+constexpr uint32_t kSpillList = DTYPE == kBF16 && LONG ? 32 : 16;
 constexpr uint32_t kWatchCalls = 8;    // calls that extrapolate a falling pre-threshold after a miss
 constexpr uint32_t kSpillRaise = 6;    // bins (1/128 octave each) a wave's pre-threshold goes up per try
 
@@ -561,8 +565,8 @@ __device__ inline void select_window(uint32_t l, const SegDev &sd, uint32_t blo,
     sel[l] = r;
 }
 
-// ACC: with a gradient accumulator (all ranks of a launch have one, or none).
-template <int DTYPE, bool ACC>
+// ACC: with a gradient accumulator (all ranks of a launch have one, or none).  LONG: the longer stage.
+template <int DTYPE, bool ACC, bool LONG>
 __global__ void __launch_bounds__(kSpillThreads)
 scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t CAP,
                   uint64_t zero_n16, uint32_t wire4)
@@ -582,7 +586,7 @@ scan_spill_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint3
     constexpr uint32_t ROW_ELEMS = 64 * VEC;
     constexpr uint32_t CHUNK = ROW_ELEMS * ROWS;
     constexpr uint32_t NW = kSpillThreads / 64;
-    constexpr uint32_t STAGE = kSpillStage<DTYPE>, LIST = kSpillList<DTYPE>;
+    constexpr uint32_t STAGE = kSpillStage<DTYPE, LONG>, LIST = kSpillList<DTYPE, LONG>;
     constexpr uint32_t STAGE_WORDS = STAGE * (DTYPE == kBF16 ? 1 : 2);
     static_assert(ROWS == 4 && ROWS * VEC <= 32, "packed masks and row counts below");
     __shared__ uint32_t h[kWinWords];
@@ -2462,7 +2466,12 @@ int launch_select(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, boo
     if (p->any_fast || p->span_dense) {
         // (also clears the histograms in memory; short segments need neither)
         ProfileScope ps("scan_spill", s);
-        auto scan = acc ? scan_spill_kernel<DTYPE, true> : scan_spill_kernel<DTYPE, false>;
+        // (the longer stage unless other buckets are in flight and chunks hold dozens of candidates: see
+        // kSpillStage)
+        constexpr bool kCanLong = DTYPE == kBF16;
+        const bool lng = kCanLong && (!p->cfg.decode_workgroups || p->cand_cap >= kWideEmitCap);
+        auto scan = lng ? (acc ? scan_spill_kernel<DTYPE, true, kCanLong> : scan_spill_kernel<DTYPE, false, kCanLong>)
+                        : (acc ? scan_spill_kernel<DTYPE, true, false> : scan_spill_kernel<DTYPE, false, false>);
         // Workgroups that fit the device at once, or, where their spans stay long enough for what
         // a span costs (its window's atomics, its first loads), up to eight rounds of them:
         // compute units do not stream at one rate, and short spans even that out (16 ranks of
