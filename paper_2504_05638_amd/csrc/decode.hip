@@ -244,7 +244,8 @@ __device__ __forceinline__ void join_cells(const PartLds<kPacked> &p, uint32_t t
 // be claimed and the claims are written whole.  `any`: not if only estimates are wanted.  (Cell by
 // cell, with claims in the order of the sub-tables and two barriers for that: three times the
 // instructions.  This, the requests in PartAhead and the stores waited for in wait_loads: everything but the
-// rounds 23.9 K -> 18.5 K clocks a partition; decoders of 2 ranks of 202 M entries 586 -> 553 us.)
+// rounds 23.9 K -> 18.5 K clocks a partition; decoders of 2 ranks of 202 M entries 586 -> 553 us;
+// with everything since 563.)
 template <uint32_t NT, uint32_t kIdx, bool kPacked>
 __device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t tid, uint32_t n, bool any,
                                             const uint32_t (&at)[kIdx][3])
