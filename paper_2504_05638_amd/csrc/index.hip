@@ -150,45 +150,27 @@ struct LayoutBatch {
     LayoutRank r[kMaxRanksPerPass];
 };
 
-// For kN sorted lists at once, by every 16 lanes of a wave for theirs: the first position whose
-// entry is >= key[i].  Each step cuts the range into 16 parts: 5 or 6 dependent loads for a list
-// of millions where a thread's binary search takes over 20 (cut into 64 parts by a whole wave it
-// is 4, of 64 cache lines each: 58 thousand searches of 2 M entries were bound by those).
-template <uint32_t kN>
-__device__ inline void lower_bounds_by_16(const uint32_t *const (&list)[kN], const uint32_t (&n)[kN],
-                                          const uint32_t (&key)[kN], uint32_t (&pos)[kN])
+// By every 16 lanes of a wave for theirs: the first position in a sorted list whose entry is >= key.  Each step
+// cuts the range into 16 parts: 5 or 6 dependent loads for a list of millions where a thread's binary search
+// takes over 20 (cut into 64 parts by a whole wave it is 4, of 64 cache lines each: 58 thousand searches of
+// 2 M entries were bound by those).
+__device__ inline uint32_t lower_bound_by_16(const uint32_t *list, uint32_t n, uint32_t key)
 {
     const uint32_t part = lane_id() & 15, shift = lane_id() & 48;
-    uint32_t lo[kN], hi[kN];
-    bool more = false;
-#pragma unroll
-    for (uint32_t i = 0; i < kN; ++i) {
-        lo[i] = 0;
-        hi[i] = n[i];
-        more |= n[i] != 0;
+    uint32_t lo = 0, hi = n;
+    while (__ballot(lo < hi)) {
+        const uint32_t step = (hi - lo + 15) / 16;
+        const uint64_t first = lo + uint64_t(part) * step;
+        // the last entry of the lane's part
+        const uint32_t v = first < hi ? list[min(first + step, uint64_t(hi)) - 1] : 0xFFFFFFFFu;
+        // parts wholly below the key; then the part after them, whose last entry is not
+        const uint32_t below = uint32_t(__popc(uint32_t(__ballot(v < key) >> shift) & 0xFFFFu));
+        const uint64_t at = min(lo + uint64_t(below) * step, uint64_t(hi));
+        const uint64_t end = min(at + step, uint64_t(hi));
+        lo = uint32_t(at);
+        hi = uint32_t(end > at ? end - 1 : at);
     }
-    while (__ballot(more)) {
-        uint32_t step[kN], v[kN];
-#pragma unroll
-        for (uint32_t i = 0; i < kN; ++i) {  // the last entry of the lane's part
-            step[i] = (hi[i] - lo[i] + 15) / 16;
-            const uint64_t first = lo[i] + uint64_t(part) * step[i];
-            v[i] = first < hi[i] ? list[i][min(first + step[i], uint64_t(hi[i])) - 1] : 0xFFFFFFFFu;
-        }
-        more = false;
-#pragma unroll
-        for (uint32_t i = 0; i < kN; ++i) {
-            // parts wholly below the key; then the part after them, whose last entry is not
-            const uint32_t below = uint32_t(__popc(uint32_t(__ballot(v[i] < key[i]) >> shift) & 0xFFFFu));
-            const uint64_t at = min(lo[i] + uint64_t(below) * step[i], uint64_t(hi[i]));
-            const uint64_t end = min(at + step[i], uint64_t(hi[i]));
-            lo[i] = uint32_t(at);
-            hi[i] = uint32_t(end > at ? end - 1 : at);
-            more |= lo[i] < hi[i];
-        }
-    }
-#pragma unroll
-    for (uint32_t i = 0; i < kN; ++i) pos[i] = lo[i];
+    return lo;
 }
 
 // Per-partition hash salts (the compression is to be lossless, section 2.2 and Table 1).
@@ -218,10 +200,16 @@ __device__ inline void lower_bounds_by_16(const uint32_t *const (&list)[kN], con
 // bounds[A] = n_c); and so are their ends in the ranks' sorted pair lists (ranges[a] of a
 // rank = number of its pairs whose c-index lies below bounds[a]).  Four launches (header, bounds,
 // salt, ranges) were 31 us on an 8-rank bucket of 25 M entries and 48 on one of 67 M, in one launch they
-// were 21 and 40 with the same comparison.  A workgroup's first partition waits 20 K clocks for memory, in
-// order: chunk counts, Index words of the bounds, four to six steps of the searches.  (Tried: the
-// chunk counts kept in LDS for the bounds, nothing; 256 parts a step and half the steps in small
-// launches, 3 us slower, bound by the lines; words beyond the first four requested ahead, 0 to 6 % slower.)
+// were 21 and 40 with the same comparison.  A workgroup's first partition waits for memory, in order: chunk
+// counts, Index words of the bounds, its own words; then the searches waited 10 to 20 K clocks for four to six
+// steps (83 K with 16 ranks of 202 M entries) in which its compute unit hashed nothing.  So some
+// workgroups of the launch find the ends in the pair lists, beside the others' salts (us a pass, before /
+// after: 16 ranks of 202 M entries 3049 / 3021, one of them with three others' Indexes 196.5 / 191.5, 8 ranks of
+// 7 M 218.8 / 217.0, 4 of 1 M 83.6 / 82.1, 3 of 36 thousand 64.8 / 63.7, 8 of 25 M 241 / 238.5; 2 of 202 M with a
+// tenth kept no difference).  (Tried: a step of the searches between the steps of the salts, whose waits are
+// longer than those steps, half as much or nothing; the chunk counts kept in LDS for the bounds, nothing; 256
+// parts a step and half the steps in small launches, 3 us slower, bound by the lines; words beyond the first
+// four requested ahead, 0 to 6 % slower.)
 constexpr uint32_t kSaltThreads = 1024;
 constexpr uint32_t kLayoutBatch = kSaltThreads / 128;  // partitions whose bounds are found at once
 constexpr uint64_t kSplitSearches = 32768;  // (partition, rank) pairs
@@ -252,7 +240,8 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
               uint32_t n_words, uint32_t n_c, const uint32_t *__restrict__ chunkcnt,
               uint32_t *__restrict__ chunkpre, uint32_t n_chunks, const LayoutParams lp,
               uint32_t *__restrict__ header, uint32_t *__restrict__ status,
-              uint32_t *__restrict__ bounds, uint32_t ranges_off, uint32_t pair_cap, uint64_t seed)
+              uint32_t *__restrict__ bounds, uint32_t ranges_off, uint32_t pair_cap, uint64_t seed,
+              uint32_t n_search, uint32_t search0)
 {
     constexpr uint32_t NT = kSaltThreads;
     extern __shared__ uint32_t lds_salt[];
@@ -270,6 +259,7 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     __shared__ uint32_t s_n, s_dup, s_some;
     __shared__ uint32_t s_pre[kBounds ? NT : 1];  // set bits before thread t's chunks
     __shared__ uint32_t s_bound[2 * kLayoutBatch];  // first and last bound of the batch's partitions
+    __shared__ uint32_t s_pairs[kMaxRanksPerPass];
     __shared__ uint32_t smem[NT / 64];
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -277,6 +267,8 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     // (what every lane holds alike comes from LDS here: said to be uniform, it stays in scalar
     // registers, and the loops below are scalar)
     auto uniform = [](uint32_t x) -> uint32_t { return __builtin_amdgcn_readfirstlane(x); };
+    if (kSearch && tid < n_in)
+        s_pairs[tid] = min(as_global(batch_row<LayoutRank>(tid)->cnt)[TAGC_CNT_TOTAL], pair_cap);
     // ---- set bits before every thread's chunks, the layout
     const uint32_t per = (n_chunks + NT - 1) / NT;
     Layout lay{};
@@ -371,73 +363,59 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
         const uint64_t who = __ballot(mine);
         return who ? __builtin_amdgcn_readlane(found, __builtin_ctzll(who)) : n_c;
     };
-    // rank r's words from ranges_off on: positions in its pair list
-    auto rank_row = [&](uint32_t r) { return batch_row<LayoutRank>(r); };
-    auto pairs_of = [&](uint32_t *cnt) { return min(cnt[TAGC_CNT_TOTAL], pair_cap); };
-
     if (kBounds && blockIdx.x == 0) {  // the end of the last partition (of none: the only bound)
         if (tid == 0) bounds[A] = n_c;
-        if (kSearch && tid < n_in) {
-            uint32_t *cnt = as_global(rank_row(tid)->cnt);
-            cnt[ranges_off + A] = pairs_of(cnt);
-        }
+        // (rank r's words from ranges_off on: positions in its pair list)
+        if (kSearch && tid < n_in) as_global(batch_row<LayoutRank>(tid)->cnt)[ranges_off + A] = s_pairs[tid];
     }
-    // word `w` of partition [lo, hi), bits outside the partition cleared
+    // word `w` of partition [lo, hi); and the same with the bits outside the partition cleared, which is a step
+    // of its own because it waits for the word
     auto load_word = [&](uint32_t w, uint32_t lo, uint32_t hi) -> uint32_t {
-        if (lo >= hi || w > ((hi - 1) >> 5) || w >= n_words) return 0u;
-        uint32_t word = bitmap[w];
+        const uint32_t end = lo < hi ? min(((hi - 1) >> 5) + 1, n_words) : 0u;
+        return w < end ? bitmap[w] : 0u;
+    };
+    auto clip_word = [&](uint32_t word, uint32_t w, uint32_t lo, uint32_t hi) -> uint32_t {
         if (w == (lo >> 5)) word &= 0xFFFFFFFFu << (lo & 31);
         if (w == ((hi - 1) >> 5) && (hi & 31)) word &= (1u << (hi & 31)) - 1u;
         return word;
     };
-    // The workgroup's partitions are blockIdx.x, + G, + 2 G, ...
-    const uint32_t G = gridDim.x;
-    const uint32_t n_mine = blockIdx.x < A ? (A - 1 - blockIdx.x) / G + 1 : 0u;
+    // The workgroup's partitions are me, me + G, me + 2 G, ...
+    // (n_search workgroups from search0 on search, the others are for the salts; 0: all are for both)
+    const bool searcher = kSearch && blockIdx.x - search0 < n_search;
+    const uint32_t me = searcher ? blockIdx.x - search0 : blockIdx.x - (blockIdx.x >= search0 ? n_search : 0u);
+    const uint32_t G = searcher ? n_search : gridDim.x - n_search;
+    const uint32_t n_mine = me < A ? (A - 1 - me) / G + 1 : 0u;
     for (uint32_t b0 = 0; b0 < n_mine; b0 += kLayoutBatch) {
     const uint32_t nb = min(kLayoutBatch, n_mine - b0);
     __syncthreads();  // s_bound is free
     if (!kBounds) {
-        if (tid < 2 * nb) s_bound[tid] = bounds[blockIdx.x + (b0 + (tid >> 1)) * G + (tid & 1)];
+        if (tid < 2 * nb) s_bound[tid] = bounds[me + (b0 + (tid >> 1)) * G + (tid & 1)];
     } else if ((wave >> 1) < nb) {
-        const uint32_t a = blockIdx.x + (b0 + (wave >> 1)) * G + (wave & 1);
+        const uint32_t a = me + (b0 + (wave >> 1)) * G + (wave & 1);
         const uint32_t x = a == A ? n_c : bound_of(uint32_t(uint64_t(a) * U / A));
         if (lane == 0) {
             s_bound[wave] = x;
-            if (!(wave & 1)) bounds[a] = x;
+            if (!(wave & 1) && !(kSalts && searcher)) bounds[a] = x;
         }
     }
     __syncthreads();
+    if (searcher || (kSearch && n_search == 0)) {
+        // a wave has the tasks wave, wave + NT / 64, ..., each a rank's list and four partitions
+        for (uint32_t task = wave; task < n_in * ((nb + 3) / 4); task += NT / 64) {
+            const uint32_t r = task % n_in, i = task / n_in * 4 + lane / 16;
+            const auto *row = batch_row<LayoutRank>(r);
+            const uint32_t at = lower_bound_by_16(as_global(row->idx), i < nb ? s_pairs[r] : 0u, s_bound[2 * min(i, nb - 1)]);
+            if ((lane & 15) == 0 && i < nb) as_global(row->cnt)[ranges_off + me + (b0 + i) * G] = at;
+        }
+    }
+    if (searcher) continue;
     // Requests run ahead of the work: the first Index words of the first partition are on their
     // way while the pair lists are searched, those of the next while one is checked.
     uint32_t lo = uniform(s_bound[0]), hi = uniform(s_bound[1]), pre[kSaltPre];
 #pragma unroll
     for (uint32_t k = 0; k < kSaltPre; ++k)
         pre[k] = kSalts ? load_word((lo >> 5) + k * NT + tid, lo, hi) : 0u;
-    constexpr uint32_t kLists = 2;
-    for (uint32_t t0 = 0; kSearch && t0 < nb * n_in; t0 += kLists * (NT / 16)) {
-        const uint32_t *list[kLists];
-        uint32_t *cnt[kLists];
-        uint32_t n[kLists], key[kLists], pos[kLists];
-#pragma unroll
-        for (uint32_t i = 0; i < kLists; ++i) {
-            const uint32_t t = t0 + i * (NT / 16) + tid / 16;
-            const bool ok = t < nb * n_in;
-            const auto *row = rank_row(ok ? t % n_in : 0u);
-            list[i] = as_global(row->idx);
-            cnt[i] = as_global(row->cnt);
-            n[i] = ok ? pairs_of(cnt[i]) : 0u;
-            key[i] = s_bound[ok ? 2 * (t / n_in) : 0u];
-        }
-        lower_bounds_by_16<kLists>(list, n, key, pos);
-#pragma unroll
-        for (uint32_t i = 0; i < kLists; ++i) {
-            const uint32_t t = t0 + i * (NT / 16) + tid / 16;
-            if ((tid & 15) == 0 && t < nb * n_in)
-                cnt[i][ranges_off + blockIdx.x + (b0 + t / n_in) * G] = pos[i];
-        }
-    }
-    if (!kSalts) continue;
-    for (uint32_t i = 0; i < nb; ++i) {
+    for (uint32_t i = 0; kSalts && i < nb; ++i) {
         const uint32_t w_lo = lo >> 5, w_hi = lo < hi ? (hi - 1) >> 5 : 0;
         const uint32_t cur_lo = lo, cur_hi = hi;
         uint32_t cur[kSaltPre];
@@ -459,6 +437,7 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
                     // (wave-uniform loop: the numbering below is a wave-wide scan)
                     uint32_t word = k < kSaltPre ? cur[k < kSaltPre ? k : 0]
                                                  : load_word(base + lane, cur_lo, cur_hi);
+                    word = clip_word(word, base + lane, cur_lo, cur_hi);
                     const uint32_t pc = __popc(word);
                     const uint32_t inc = wave_incl_scan<uint32_t>(pc);
                     const uint32_t tot = __builtin_amdgcn_readlane(inc, 63);
@@ -559,7 +538,7 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
             salt = min(salt, kSaltLimit - 1);
         }
         // (the salts lie behind the bounds)
-        if (tid == 0) bounds[lp.A_cap + 1 + blockIdx.x + (b0 + i) * G] = salt;
+        if (tid == 0) bounds[lp.A_cap + 1 + me + (b0 + i) * G] = salt;
     }
     }
 }
@@ -627,10 +606,9 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
                           p->A_cap,
                           p->m_cap};
     const size_t lds = salt_lds_bytes(p->T_cap, p->P_cap);
-    // as many workgroups as fit the device at once, each taking partitions b, b + grid, ...
     const size_t lds_all = lds + 6 * 1024;  // with the kernel's own
     const uint32_t per_cu = uint32_t(std::max<size_t>(1, std::min<size_t>(2, kLdsBytes / lds_all)));
-    const uint32_t grid = uint32_t(std::min<uint64_t>(p->A_cap, uint64_t(device_cu_count()) * per_cu));
+    const uint32_t most = uint32_t(device_cu_count()) * per_cu;  // workgroups that fit the device at once
     // Many searches in a plan that says, by a limit on the decoder's workgroups, that other buckets
     // are in flight: three launches.  In the one launch the workgroups that wait for the searches'
     // loads hold a compute unit's local memory, and no other bucket's salts run meanwhile; and 16
@@ -639,8 +617,16 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     // three.  Alone, one launch is the better for what follows: 222 and 210 us, but it leaves the
     // pair lists in the cache for the encoder (593 us, 622 after three launches).
     const bool split = p->cfg.decode_workgroups && p->A_cap * n_ranks > kSplitSearches;
-    const uint32_t wgs = uint32_t(std::min<uint64_t>((p->A_cap + kLayoutBatch - 1) / kLayoutBatch,
-                                                     uint64_t(device_cu_count()) * 2));
+    const uint32_t batches = uint32_t(std::min<uint64_t>((p->A_cap + kLayoutBatch - 1) / kLayoutBatch,
+                                                         uint64_t(device_cu_count()) * 2));
+    // Searching workgroups of the one launch, and those that look for salts, each taking
+    // partitions b, b + grid, ...  64 search fast enough to be done before the salts of the largest buckets
+    // (us of a pass, 16 / 32 / 64 / 128 of them: 16 ranks of 202 M entries 3332 / 3121 / 3021 / 3014, 2 ranks with a
+    // tenth kept 1570 / 1442 / 1421 / 1442, 4 ranks of 9 M with two fifths 371 / 343 / 342 / 344).
+    // Not so where they would make the salts' workgroups one more turn.
+    const bool apart = p->A_cap + std::min(64u, batches) <= most || p->A_cap > most;
+    const uint32_t searching = apart ? std::min(std::min(64u, batches), most / 2) : 0u;
+    const uint32_t salting = uint32_t(std::min<uint64_t>(p->A_cap, most - searching));
     const auto layout = layout_kernel<true, true, true>, salts = layout_kernel<false, false, true>;
     static size_t attr_bytes[2] = {0, 0};
     if (lds > attr_bytes[split]) {
@@ -651,10 +637,14 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
         attr_bytes[split] = lds;
     }
     auto launch = [&](auto kernel, uint32_t n_wgs, size_t lds_bytes, const LayoutBatch &lb,
-                      uint32_t n_in, bool all) {
-        kernel<<<n_wgs, kSaltThreads, lds_bytes, s>>>(
+                      uint32_t n_in, bool all, uint32_t n_search) {
+        // (searching workgroups start first, or, if all fit the device, last: on a device nearly full of
+        // those with a partition each they then share few compute units, 8 ranks of 25 M entries, us a pass,
+        // 239 and 237, with 4-bit counters 281 and 277)
+        const uint32_t search0 = n_wgs + n_search <= most ? n_wgs : 0u;
+        kernel<<<n_wgs + n_search, kSaltThreads, lds_bytes, s>>>(
             lb, n_in, all, sh->bitmap, n_words, uint32_t(p->n_c), chunk, chunkpre, n_chunks, lp,
-            sh->header, sh->status, sh->bounds, p->cnt_ranges, uint32_t(p->K), p->cfg.seed);
+            sh->header, sh->status, sh->bounds, p->cnt_ranges, uint32_t(p->K), p->cfg.seed, n_search, search0);
     };
     for (uint32_t r0 = 0; r0 < n_ranks; r0 += kMaxRanksPerPass) {
         // (ranks beyond the first launch's only need their pair lists searched)
@@ -664,9 +654,9 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
             lb.r[r] = LayoutRank{ranks[r0 + r].idx, ranks[r0 + r].cnt};
         if (r0 == 0 || !split) {
             ProfileScope ps("layout", s);
-            if (split) launch(layout_kernel<true, false, false>, wgs, 0, lb, n_in, true);
-            else if (r0 == 0) launch(layout, grid, lds, lb, n_in, true);
-            else launch(layout_kernel<true, true, false>, wgs, 0, lb, n_in, false);
+            if (split) launch(layout_kernel<true, false, false>, batches, 0, lb, n_in, true, 0);
+            else if (r0 == 0) launch(layout, salting, lds, lb, n_in, true, searching);
+            else launch(layout_kernel<true, true, false>, 0, 0, lb, n_in, false, batches);
         }
         if (split) {
             ProfileScope ps("ranges", s);
@@ -676,7 +666,7 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     }
     if (split) {
         ProfileScope ps("salt", s);
-        launch(salts, grid, lds, LayoutBatch{}, 0, true);
+        launch(salts, uint32_t(std::min<uint64_t>(p->A_cap, most)), lds, LayoutBatch{}, 0, true, 0);
     }
     return hip_ok(hipGetLastError());
 }
