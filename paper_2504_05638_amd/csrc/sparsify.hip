@@ -1550,11 +1550,125 @@ __device__ inline void write_rank_counts(uint32_t *table, uint32_t L, uint32_t s
 
 // ------------------------------------------------------------------- emit
 
-// Candidate route, count and place.  A workgroup handles kEmitItems adjacent super-chunks (32
+// Candidate route, count.  How many of a super-chunk's slots are above and at the exact threshold does not
+// depend on their order, so LPC lanes read 4 LPC slots of a chunk at once, the first of all the wave's chunks are in
+// flight, every lane counts its own, and the wave sums once at the end.  Bound by the reads' latency where
+// chunks hold a few dozen slots (8 lanes to a chunk, two waves to a super-chunk), by their bytes where
+// they hold hundreds (MANY: 16 lanes, one wave).  us a pass, before (slots classified in order, a
+// thread's own run or 64 a step) / after: 2 ranks of 202 M entries with a tenth kept 1420 / 1402, one rank's part of
+// a 202 M bucket 188.9 / 185.6, 8 ranks of 7 M fp32 216.1 / 215.1, 8 of 25 M 236.3 / 235.2, 4 of 1 M 81.2 / 81.5.
+// (Dozens of slots with one wave to a super-chunk: 8 ranks of 7 M 219.3, of 25 M 235.5 where this is 234.)
+constexpr uint32_t count_items(bool many)  // super-chunks of a workgroup
+{
+    return kEmitThreads / (many ? 64 : 128);
+}
+
+template <int DTYPE, bool MANY>
+__device__ __forceinline__ void count_body(uint32_t bid, uint32_t nb, const uint32_t *__restrict__ table,
+                                           const WsLayout &wl, const SelDev *__restrict__ sel,
+                                           const uint32_t *__restrict__ cand,
+                                           const uint2 *__restrict__ chunk_info, uint32_t CAP, uint64_t *sc_cnt)
+{
+    constexpr uint32_t CHUNK = 64 * (DTYPE == kBF16 ? 8 : 4) * kCandRows;
+    constexpr uint32_t LPC = MANY ? 16 : 8, WPS = MANY ? 1 : 2;
+    constexpr uint32_t NCH = kCandChunksPerSuper / WPS;  // chunks of a wave
+    constexpr uint32_t STEPS = NCH * LPC / 64;           // requests that cover them
+    constexpr uint32_t ITEMS = count_items(MANY);
+    static_assert(ITEMS * WPS * 64 == kEmitThreads, "a workgroup's waves");
+    __shared__ uint64_t s_n[kEmitThreads / 64];
+    const uint32_t L = wl.L, total_sc = wl.total_sc;
+    const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+    // segment i's table rows in lane i
+    uint32_t t_start = 0xFFFFFFFFu, t_n = 0, t_T = 0, t_quota = 0, t_cnt = 0, t_route = 0;
+    if (L <= 64 && lane < L) {
+        static_assert(sizeof(SegDev) == 32 && sizeof(SelDev) == 32, "two uint4 per row");
+        const uint4 *s4 = reinterpret_cast<const uint4 *>(segs + lane);
+        const uint4 *e4 = reinterpret_cast<const uint4 *>(sel + lane);
+        const uint4 sa = s4[0], sb = s4[1], ea = e4[0], eb = e4[1];
+        t_n = sa.z; t_start = sb.w;     // n, sc_start
+        if (sb.x != 0 && sa.z != 0) {   // k, n: a segment that keeps nothing has no selection
+            t_T = ea.x; t_quota = ea.y; t_cnt = ea.w; t_route = eb.w;  // T, quota, cnt, route
+        }
+    }
+    for (uint32_t base = bid * ITEMS; base < total_sc; base += nb * ITEMS) {  // uniform
+        const bool item = base + wave / WPS < total_sc;
+        const uint32_t sc = item ? base + wave / WPS : base;
+        const uint32_t ch0 = (wave % WPS) * NCH + lane / LPC;
+        // count and first slot of the lane's chunks (only meaningful for a chunk the scan has seen)
+        uint2 info[STEPS];
+#pragma unroll
+        for (uint32_t j = 0; j < STEPS; ++j) info[j] = chunk_info[sc * kCandChunksPerSuper + ch0 + j * (64 / LPC)];
+        uint32_t n_seg, sc_first, T, quota, se_cnt, se_route;
+        if (L <= 64) {
+            const uint32_t l = uint32_t(__popcll(__ballot(t_start <= sc))) - 1u;  // segment 0 starts at 0
+            n_seg = __builtin_amdgcn_readlane(t_n, l);
+            sc_first = __builtin_amdgcn_readlane(t_start, l);
+            T = __builtin_amdgcn_readlane(t_T, l);
+            quota = __builtin_amdgcn_readlane(t_quota, l);
+            se_cnt = __builtin_amdgcn_readlane(t_cnt, l);
+            se_route = __builtin_amdgcn_readlane(t_route, l);
+        } else {
+            const uint32_t l = segment_of(L, sc, [&](uint32_t i) { return segs[i].sc_start; });
+            const SegDev sd = segs[l];
+            SelDev se{};
+            if (sd.k != 0 && sd.n != 0) se = sel[l];
+            n_seg = sd.n; sc_first = sd.sc_start;
+            T = se.T; quota = se.quota; se_cnt = se.cnt; se_route = se.route;
+        }
+        const uint32_t sc_rel0 = (sc - sc_first) * (CHUNK * kCandChunksPerSuper), own = 4 * (lane % LPC);
+        uint32_t c[STEPS];   // slots of this lane's chunk of the step, from the lane's own first on
+        uint32_t at[STEPS];  // where that lies
+#pragma unroll
+        for (uint32_t j = 0; j < STEPS; ++j) {
+            // (the bounds keep the reads inside `cand` whatever an unseen chunk's record holds)
+            const uint32_t rel0 = sc_rel0 + (ch0 + j * (64 / LPC)) * CHUNK;
+            const uint32_t n = !se_route && se_cnt != 0 && rel0 < n_seg ? min(info[j].x, CAP) : 0u;
+            c[j] = n > own ? n - own : 0u;
+            at[j] = (min(info[j].y, uint32_t(wl.n_slots) - CAP) & ~3u) + own;
+        }
+        uint32_t n_gt = 0, n_eq = 0;
+        bool more = true;
+        while (more) {
+            uint4 q[STEPS];
+#pragma unroll
+            for (uint32_t j = 0; j < STEPS; ++j)  // (a chunk's slots start on, and have room up to, 16 bytes)
+                q[j] = c[j] ? *reinterpret_cast<const uint4 *>(cand + at[j]) : make_uint4(0, 0, 0, 0);
+            uint32_t left = 0;
+#pragma unroll
+            for (uint32_t j = 0; j < STEPS; ++j) {
+                const uint32_t v[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
+#pragma unroll
+                for (uint32_t i = 0; i < 4; ++i) {
+                    const uint32_t key = (DTYPE == kBF16 ? v[i] & 0xFFFF0000u : v[i]) & 0x7FFFFFFFu;
+                    n_gt += i < c[j] && key > T;
+                    n_eq += i < c[j] && key == T;
+                }
+                c[j] = c[j] > 4 * LPC ? c[j] - 4 * LPC : 0u;
+                at[j] += 4 * LPC;
+                left |= c[j];
+            }
+            more = __ballot(left != 0) != 0;
+        }
+        n_gt = __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(n_gt), 63);
+        n_eq = __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(n_eq), 63);
+        uint64_t sum = (uint64_t(n_gt) << 31) | uint64_t(quota ? n_eq : 0u);
+        if (WPS > 1) {
+            if (lane == 0) s_n[wave] = sum;
+            __syncthreads();
+            sum = s_n[wave & ~1u] + s_n[wave | 1u];
+            __syncthreads();  // (the next item's)
+        }
+        if (item && lane == 0 && wave % WPS == 0) sc_cnt[sc] = sum;
+    }
+}
+
+// Candidate route, place.  A workgroup handles kEmitItems adjacent super-chunks (32
 // chunks each), two waves per super-chunk: 4 threads per chunk share the chunk's slots
-// evenly, in order, and classify them against the exact threshold.  `count` (PLACE = false)
-// stops there and stores the item's totals.  `place` classifies again, scans over the item's
-// threads, adds up the earlier super-chunks of the segment and places the survivors in
+// evenly, in order, classify them against the exact threshold, scan over the item's
+// threads, add up the earlier super-chunks of the segment and place the survivors in
 // ascending c-index.  A super-chunk's Index words are assembled in LDS and written whole,
 // zeros included.
 //
@@ -1584,12 +1698,12 @@ struct EmitLds {
     uint16_t st_b[kEmitItems][DTYPE == kF32 ? kEmitStage : 2];
 };
 
-template <int DTYPE, bool PLACE>
+template <int DTYPE>
 __device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid, uint32_t nb,
                                  const uint32_t *__restrict__ table, const WsLayout &wl,
                                  const SelDev *__restrict__ sel,
             const uint32_t *__restrict__ cand, const uint2 *__restrict__ chunk_info,
-            uint32_t CAP, uint64_t *sc_cnt,
+            uint32_t CAP, const uint64_t *sc_cnt,
             uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
             uint32_t *__restrict__ bitmap)
 {
@@ -1598,7 +1712,7 @@ __device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid, uin
     constexpr uint32_t SC_ELEMS = CHUNK * kCandChunksPerSuper;
     constexpr uint32_t SC_WORDS = SC_ELEMS / 32;
     constexpr int NI = kEmitItems;
-    auto *bits = lds->bits;  // (place only, as the rest of *lds)
+    auto *bits = lds->bits;
     auto *st_a = lds->st_a;
     auto *st_b = lds->st_b;
     static_assert(SC_ELEMS <= 65536, "a position in the super-chunk fits 16 bits");
@@ -1637,8 +1751,7 @@ __device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid, uin
                 t_T = ea.x; t_quota = ea.y; t_cnt = ea.w; t_route = eb.w;  // T, quota, cnt, route
             }
         }
-        if (PLACE)
-            for (uint32_t i = tt; i < SC_WORDS; i += 128) bits[k][i] = 0;
+        for (uint32_t i = tt; i < SC_WORDS; i += 128) bits[k][i] = 0;
 
         // ---- segment, threshold, pair offset of the segment (all wave-uniform)
         uint32_t l, c_off, n_seg, sc_first, T, quota, seg_base, se_cnt, se_route;
@@ -1729,11 +1842,6 @@ __device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid, uin
         __syncthreads();
         const uint32_t lo_gt = s_gt[2 * k], lo_eq = s_eq[2 * k];
         const uint32_t it_gt = lo_gt + s_gt[2 * k + 1], it_eq = lo_eq + s_eq[2 * k + 1];
-        if (!PLACE) {
-            if (sc < total_sc && tt == 0) sc_cnt[sc] = (uint64_t(it_gt) << 31) | uint64_t(it_eq);
-            __syncthreads();  // s_gt / s_eq are rewritten by the next iteration
-            continue;
-        }
         uint32_t gb = inc_gt - n_gt + ((wave & 1u) ? lo_gt : 0u);
         uint32_t eb = inc_eq - n_eq + ((wave & 1u) ? lo_eq : 0u);
         // ---- prefix over the segment's earlier super-chunks, whose counts are all there
@@ -1816,14 +1924,13 @@ __device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid, uin
 // and reads its chunks' slots 64 at a time, in position order, BATCH such reads in
 // flight.  The survivors among the 64 slots of one read are neighbours in the output, so
 // they are stored as they are found; the Index words of a chunk are collected in LDS and
-// leave when its last slots are through.  Same inputs, same outputs, same counts per
-// super-chunk as emit_body.
-template <int DTYPE, bool PLACE, uint32_t BATCH>
+// leave when its last slots are through.  Same inputs, same outputs as emit_body.
+template <int DTYPE, uint32_t BATCH>
 __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
                                  const uint32_t *__restrict__ table, const WsLayout &wl,
                                  const SelDev *__restrict__ sel,
             const uint32_t *__restrict__ cand, const uint2 *__restrict__ chunk_info,
-            uint32_t CAP, uint64_t *sc_cnt,
+            uint32_t CAP, const uint64_t *sc_cnt,
             uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
             uint32_t *__restrict__ bitmap)
 {
@@ -1834,7 +1941,7 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
     constexpr uint32_t CH_WORDS = CHUNK / 32;
     constexpr uint32_t NWV = kEmitThreads / 64;
     static_assert(NCH <= 64 && CH_WORDS <= 64, "a lane per chunk, a lane per Index word of a chunk");
-    __shared__ uint32_t wbits[PLACE ? NWV : 1][PLACE ? CH_WORDS : 1];  // a wave's current chunk
+    __shared__ uint32_t wbits[NWV][CH_WORDS];  // a wave's current chunk
     const uint32_t L = wl.L, total_sc = wl.total_sc;
     const uint64_t n_slots_total = wl.n_slots;
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
@@ -1854,7 +1961,7 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
             t_T = ea.x; t_quota = ea.y; t_cnt = ea.w; t_route = eb4.w;  // T, quota, cnt, route
         }
     }
-    if (PLACE && lane < CH_WORDS) wbits[wave][lane] = 0;  // (no other wave touches this row)
+    if (lane < CH_WORDS) wbits[wave][lane] = 0;  // (no other wave touches this row)
 
     for (uint32_t sc = bid * NWV + wave; sc < total_sc; sc += nb * NWV) {  // wave-uniform
         // count and first slot of chunk `lane` (only meaningful for a chunk the scan has seen),
@@ -1937,33 +2044,31 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
         request(0);  // (on their way while the prefix below is added up)
 
         uint32_t gb = 0, eb = 0;  // entries above / at the threshold before the current slot
-        if (PLACE) {
-            // prefix over the segment's earlier super-chunks, whose counts are all there
-            // (eight requests at a time; a tenth kept on 202 M entries, 2 ranks: 163 -> 141 us.
-            // fp32 slots are two words each, and beside those in flight there is room for two
-            // requests: with eight, 24 registers went to scratch memory.  2 ranks, a tenth of 67 M
-            // kept, then a hundredth of 202 M: 103 -> 87 us, 66 -> 56)
-            constexpr uint32_t PRE = DTYPE == kBF16 ? 8 : 2;
-            uint64_t sum = 0;
-            if (live)
-                for (uint32_t j = sc_first + lane; j < sc; j += PRE * 64) {
-                    uint64_t c[PRE];
+        // prefix over the segment's earlier super-chunks, whose counts are all there
+        // (eight requests at a time; a tenth kept on 202 M entries, 2 ranks: 163 -> 141 us.
+        // fp32 slots are two words each, and beside those in flight there is room for two
+        // requests: with eight, 24 registers went to scratch memory.  2 ranks, a tenth of 67 M
+        // kept, then a hundredth of 202 M: 103 -> 87 us, 66 -> 56)
+        constexpr uint32_t PRE = DTYPE == kBF16 ? 8 : 2;
+        uint64_t sum = 0;
+        if (live)
+            for (uint32_t j = sc_first + lane; j < sc; j += PRE * 64) {
+                uint64_t c[PRE];
 #pragma unroll
-                    for (uint32_t i = 0; i < PRE; ++i) c[i] = j + 64 * i < sc ? sc_cnt[j + 64 * i] : 0ull;
+                for (uint32_t i = 0; i < PRE; ++i) c[i] = j + 64 * i < sc ? sc_cnt[j + 64 * i] : 0ull;
 #pragma unroll
-                    for (uint32_t i = 0; i < PRE; ++i) sum += c[i];
-                }
-            sum = wave_sum<uint64_t>(sum);
-            gb = uint32_t(sum >> 31);
-            eb = uint32_t(sum & 0x7FFFFFFFu);
-            // chunks of the segment without a candidate have no group of their own unless
-            // group = chunk: their Index words are zero
-            if (!one_each) {
-                for (uint64_t em = __ballot(inseg_l && cnt_l == 0); em; em &= em - 1) {
-                    const uint32_t ch = uint32_t(__builtin_ctzll(em));
-                    const uint32_t rel0 = sc_rel0 + ch * CHUNK + lane * 32;
-                    if (lane < CH_WORDS && rel0 < n_seg) bitmap[(c_off + rel0) >> 5] = 0;
-                }
+                for (uint32_t i = 0; i < PRE; ++i) sum += c[i];
+            }
+        sum = wave_sum<uint64_t>(sum);
+        gb = uint32_t(sum >> 31);
+        eb = uint32_t(sum & 0x7FFFFFFFu);
+        // chunks of the segment without a candidate have no group of their own unless
+        // group = chunk: their Index words are zero
+        if (!one_each) {
+            for (uint64_t em = __ballot(inseg_l && cnt_l == 0); em; em &= em - 1) {
+                const uint32_t ch = uint32_t(__builtin_ctzll(em));
+                const uint32_t rel0 = sc_rel0 + ch * CHUNK + lane * 32;
+                if (lane < CH_WORDS && rel0 < n_seg) bitmap[(c_off + rel0) >> 5] = 0;
             }
         }
 
@@ -1980,31 +2085,29 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
                 const bool is_gt = valid && key > T;
                 const bool is_eq = valid && key == T && quota != 0;
                 const uint64_t bgt = __ballot(is_gt), beq = __ballot(is_eq);
-                if (PLACE) {
-                    const uint32_t my_gb = gb + uint32_t(__popcll(bgt & lanes_below));
-                    const uint32_t my_eb = eb + uint32_t(__popcll(beq & lanes_below));
-                    // entries above T all survive, ties while the quota lasts
-                    const bool keep = is_gt || (is_eq && my_eb < quota);
-                    if (keep) {
-                        const uint32_t pos = is_gt ? my_gb + min(my_eb, quota) : my_gb + my_eb;
-                        idx_out[seg_base + pos] = c_off + sc_rel0 + ch * CHUNK + rel;
-                        val_out[seg_base + pos] = __uint_as_float(vbits);
-                        atomicOr(&wbits[wave][rel >> 5], 1u << (rel & 31));
+                const uint32_t my_gb = gb + uint32_t(__popcll(bgt & lanes_below));
+                const uint32_t my_eb = eb + uint32_t(__popcll(beq & lanes_below));
+                // entries above T all survive, ties while the quota lasts
+                const bool keep = is_gt || (is_eq && my_eb < quota);
+                if (keep) {
+                    const uint32_t pos = is_gt ? my_gb + min(my_eb, quota) : my_gb + my_eb;
+                    idx_out[seg_base + pos] = c_off + sc_rel0 + ch * CHUNK + rel;
+                    val_out[seg_base + pos] = __uint_as_float(vbits);
+                    atomicOr(&wbits[wave][rel >> 5], 1u << (rel & 31));
+                }
+                // the chunk's last slots: its Index words leave
+                if (s0 + 64 >= c && __builtin_amdgcn_readlane(ins_l, ch)) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    if (lane < CH_WORDS) {
+                        const uint32_t w = wbits[wave][lane];
+                        wbits[wave][lane] = 0;
+                        const uint32_t rel0 = sc_rel0 + ch * CHUNK + lane * 32;
+                        if (rel0 < n_seg) bitmap[(c_off + rel0) >> 5] = w;
                     }
-                    // the chunk's last slots: its Index words leave
-                    if (s0 + 64 >= c && __builtin_amdgcn_readlane(ins_l, ch)) {
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        if (lane < CH_WORDS) {
-                            const uint32_t w = wbits[wave][lane];
-                            wbits[wave][lane] = 0;
-                            const uint32_t rel0 = sc_rel0 + ch * CHUNK + lane * 32;
-                            if (rel0 < n_seg) bitmap[(c_off + rel0) >> 5] = w;
-                        }
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
                 }
                 gb += uint32_t(__popcll(bgt));
                 eb += uint32_t(__popcll(beq));
@@ -2012,7 +2115,6 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
             b0 += BATCH;
             if (b0 < n_groups) request(b0);
         }
-        if (!PLACE && lane == 0) sc_cnt[sc] = (uint64_t(gb) << 31) | uint64_t(eb);
     }
 }
 
@@ -2264,7 +2366,7 @@ __device__ __forceinline__ void compact_body(CompactLds<DTYPE, STAGED> *lds, uin
 // that part costs nothing, not even an empty kernel's turn-around.
 static_assert(kEmitThreads == kCompactThreads, "one launch for both parts");
 
-template <int DTYPE, uint32_t COMPACT_ROWS, bool WIDE>
+template <int DTYPE, uint32_t COMPACT_ROWS, bool MANY>
 __global__ void __launch_bounds__(kEmitThreads)
 count_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles,
              const uint32_t *__restrict__ table, const WsLayout wl, uint32_t CAP)
@@ -2272,15 +2374,8 @@ count_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles,
     const RankView rv = rank_view();
     const SelDev *sel = rv.at<SelDev>(wl.sel);
     if (blockIdx.x < n_emit) {
-        const uint32_t *cand = rv.at<uint32_t>(wl.cand);
-        const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
-        uint64_t *sc_cnt = rv.at<uint64_t>(wl.sc_cnt);
-        if (WIDE)
-            emit_wide_body<DTYPE, false, 32>(blockIdx.x, n_emit, table, wl, sel, cand, chunk_info,
-                                             CAP, sc_cnt, nullptr, nullptr, nullptr);
-        else
-            emit_body<DTYPE, false>(nullptr, blockIdx.x, n_emit, table, wl, sel, cand, chunk_info,
-                                    CAP, sc_cnt, nullptr, nullptr, nullptr);
+        count_body<DTYPE, MANY>(blockIdx.x, n_emit, table, wl, sel, rv.at<uint32_t>(wl.cand),
+                                rv.at<uint2>(wl.chunk_info), CAP, rv.at<uint64_t>(wl.sc_cnt));
     } else
         compact_body<DTYPE, COMPACT_ROWS, false, false>(
             nullptr, blockIdx.x - n_emit, gridDim.x - n_emit, plan_tiles, rv.src(), table, wl, sel,
@@ -2311,12 +2406,11 @@ place_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles, uint32_t
     if (blockIdx.x < n_emit) {
         const uint32_t *cand = rv.at<uint32_t>(wl.cand);
         const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
-        uint64_t *sc_cnt = rv.at<uint64_t>(wl.sc_cnt);
+        const uint64_t *sc_cnt = rv.at<uint64_t>(wl.sc_cnt);
         if constexpr (WIDE)
-            emit_wide_body<DTYPE, true, 16>(blockIdx.x, n_emit, table, wl, sel, cand, chunk_info,
-                                            CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
+            emit_wide_body<DTYPE, 16>(blockIdx.x, n_emit, table, wl, sel, cand, chunk_info, CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
         else
-            emit_body<DTYPE, true>(&lds.emit, blockIdx.x, n_emit, table, wl, sel, cand, chunk_info,
+            emit_body<DTYPE>(&lds.emit, blockIdx.x, n_emit, table, wl, sel, cand, chunk_info,
                                    CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
     } else
         compact_body<DTYPE, COMPACT_ROWS, true, STAGED>(
@@ -2526,10 +2620,11 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
     }
     {
         // the plan fixed the compaction tile's height, and with it which kernels these are
-        // (and whether chunks hold dozens or hundreds of candidates)
+        // (and, for place, whether chunks hold dozens or hundreds of candidates)
         const bool rows4 = p->compact_rows == 4, wd = p->emit_wide;
-        auto count = wd ? (rows4 ? count_kernel<DTYPE, 4, true> : count_kernel<DTYPE, 2, true>)
-                        : (rows4 ? count_kernel<DTYPE, 4, false> : count_kernel<DTYPE, 2, false>);
+        const bool many = p->cand_cap >= kWideEmitCap;
+        auto count = many ? (rows4 ? count_kernel<DTYPE, 4, true> : count_kernel<DTYPE, 2, true>)
+                          : (rows4 ? count_kernel<DTYPE, 4, false> : count_kernel<DTYPE, 2, false>);
         // place stages the dense route's tiles where most pairs can come from them.  Beside large
         // candidate-route segments a short one of the dense route would have every workgroup hold
         // 33 KiB of LDS and 108 registers for it instead of 1 KiB and 76 (4 ranks of 202 M entries
@@ -2545,22 +2640,24 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
         const int occ = resident_blocks_per_cu(place, kEmitThreads, 0, &occ_place[wd][rows4 + staged]);
         if (occ <= 0) return TAGC_EHIP;
         // emit_body: kEmitItems super-chunks per workgroup; emit_wide_body: one per wave
-        const uint32_t per_wg = wd ? kEmitThreads / 64 : uint32_t(kEmitItems);
-        const uint32_t n_emit = p->any_fast ? (p->total_sc + per_wg - 1) / per_wg : 0;
+        auto n_emit = [&](uint32_t per_wg) {
+            return p->any_fast ? (p->total_sc + per_wg - 1) / per_wg : 0u;
+        };
+        const uint32_t n_count = n_emit(count_items(many)), n_place = n_emit(wd ? kEmitThreads / 64 : kEmitItems);
         // Dense route: one tile per workgroup where the work is certain.  The tiles of the
         // candidate route's segments are only a safety net for re-routed ones and the
         // workgroups for them nearly always exit at once: a grid that fits the device takes
         // those tiles in turns.
         const uint32_t n_net = std::min<uint32_t>(p->total_tiles - p->plan_tiles,
                                                   per_rank(uint32_t(cus) * uint32_t(occ)));
-        const dim3 grid(n_emit + p->plan_tiles + n_net, n);
+        auto grid = [&](uint32_t n_cand) { return dim3(n_cand + p->plan_tiles + n_net, n); };
         {
             ProfileScope ps("count", s);
-            count<<<grid, kEmitThreads, 0, s>>>(sb, n_emit, p->plan_tiles, table, wl, p->cand_cap);
+            count<<<grid(n_count), kEmitThreads, 0, s>>>(sb, n_count, p->plan_tiles, table, wl, p->cand_cap);
         }
         {
             ProfileScope ps("place", s);
-            place<<<grid, kEmitThreads, 0, s>>>(sb, n_emit, p->plan_tiles, table, wl, p->cand_cap);
+            place<<<grid(n_place), kEmitThreads, 0, s>>>(sb, n_place, p->plan_tiles, table, wl, p->cand_cap);
         }
     }
     if (p->cfg.index_mode == TAGC_INDEX_ADD4 && p->n_c) {
