@@ -52,9 +52,7 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
     p->any_nonfast = false;
 
     // Candidate route: slots per chunk for 1.3 x the kept fraction plus six standard
-    // deviations.  What follows the scan costs in proportion to the candidates; with the
-    // form of count and place that suits the number of candidates per chunk (emit_body for
-    // dozens, emit_wide_body for hundreds) it beats the dense route's three reads of the
+    // deviations.  What follows the scan costs in proportion to the candidates; it beats the dense route's three reads of the
     // gradient up to Table 1's 2x regime (a fifth kept: 26 % of a chunk expected as
     // candidates; measured on 7B-shaped buckets).  Returns the slots a chunk needs, 0 = dense
     // route.
@@ -145,13 +143,6 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
         delete p;
         return TAGC_ESIZE;
     }
-    // count / place give a wave to every super-chunk where chunks hold hundreds of
-    // candidates, and in large buckets whatever they hold: that form needs next to no LDS, so
-    // its workgroups run beside another bucket's scan, which is what large buckets are timed
-    // with (7B-shaped buckets, 12 in flight: 4 % of a step; one bucket at a time it is 3 us
-    // per rank slower than four threads per chunk, which small buckets, bound by the time
-    // a launch takes, would notice)
-    p->emit_wide = p->cand_cap >= kWideEmitCap || scs >= kWideEmitSuperChunks;
     p->n_real = n_real;
     p->n_c = c;
     p->K = K;

@@ -1557,7 +1557,8 @@ __device__ inline void write_rank_counts(uint32_t *table, uint32_t L, uint32_t s
 // they hold hundreds (MANY: 16 lanes, one wave).  us a pass, before (slots classified in order, a
 // thread's own run or 64 a step) / after: 2 ranks of 202 M entries with a tenth kept 1420 / 1402, one rank's part of
 // a 202 M bucket 188.9 / 185.6, 8 ranks of 7 M fp32 216.1 / 215.1, 8 of 25 M 236.3 / 235.2, 4 of 1 M 81.2 / 81.5.
-// (Dozens of slots with one wave to a super-chunk: 8 ranks of 7 M 219.3, of 25 M 235.5 where this is 234.)
+// (Dozens of slots with one wave to a super-chunk were slower than before: 8 ranks of 7 M 217 and 219, of 25 M 234
+// and 235.5.)
 constexpr uint32_t count_items(bool many)  // super-chunks of a workgroup
 {
     return kEmitThreads / (many ? 64 : 128);
@@ -1665,268 +1666,39 @@ __device__ __forceinline__ void count_body(uint32_t bid, uint32_t nb, const uint
     }
 }
 
-// Candidate route, place.  A workgroup handles kEmitItems adjacent super-chunks (32
-// chunks each), two waves per super-chunk: 4 threads per chunk share the chunk's slots
-// evenly, in order, classify them against the exact threshold, scan over the item's
-// threads, add up the earlier super-chunks of the segment and place the survivors in
-// ascending c-index.  A super-chunk's Index words are assembled in LDS and written whole,
-// zeros included.
+// Candidate route, place.  A wave takes a whole super-chunk, classifies its slots against the exact threshold,
+// adds up the earlier super-chunks of the segment and places the survivors in ascending c-index.  Bound by
+// latency where chunks hold few slots, and by memory where they hold hundreds.  Everything whose address follows
+// from the workgroup number alone is requested at once: the chunk counts, and -- lane i taking segment i -- the
+// whole segment and selection tables, from which the item's segment, its threshold and the pair offset of
+// the segment come by ballot, readlane and a wave sum (tables of more than 64 segments take a slower path).
 //
-// Every step is latency-bound (a dependent memory access costs 1-3 us under load), so the
-// kernels are built to need few of them in a row and to be resident all at once (one item's
-// state per thread keeps the register count low enough for that).  Everything whose
-// address follows from the workgroup number alone is requested at once: the chunk counts,
-// and -- lane i taking segment i -- the whole segment and selection tables, from which the
-// item's segment, its threshold and the pair offset of the segment come by ballot,
-// readlane and a wave sum (tables of more than 64 segments take a slower path).
+// The chunks' slots are numbered through by groups of 16 bytes, a lane a group: a step is 256 slots whatever
+// the chunks hold, and every lane finds the chunk of its group by four steps of a search in the chunks' last
+// group numbers.  BATCH steps are in flight, and the request behind a step goes out before that step's own
+// stores: loads are waited for in issue order, and so are the stores between them.  A step's survivors are
+// neighbours in the output; they are put side by side in LDS and leave as contiguous stores (entry by entry, each
+// store would touch up to 64 cache lines).  The Index words of half a super-chunk are collected in
+// LDS (all of it would leave room for fewer workgroups) and written whole, zeros included.
 //
-// An item's survivors are consecutive in the output.  Stored entry by entry, each wave
-// instruction would touch 64 different cache lines (measured: 60 % of the kernel's time);
-// so the first kEmitStage of them are placed in LDS and leave as contiguous stores, and
-// only what exceeds that (items keeping more than about 2 %) is stored directly.
-constexpr uint32_t kEmitStage = 800;  // survivors of an item that go through LDS
-static_assert(kEmitThreads == 128 * kEmitItems, "two waves per item");
-
+// us a pass, before / after.  Before, chunks of dozens of slots had four threads each and 23 KiB of LDS a
+// workgroup: 8 ranks of 67 M entries 467.4 / 449.7, of 25 M 235.7 / 230.5, of 7 M fp32 214.8 / 211.9, 4 of 1 M fp32
+// 81.5 / 81.7.  Chunks of hundreds, and large buckets, had 64 slots of one chunk to a step, 32 or more
+// steps a super-chunk, and stored survivors as found: 16 ranks of 202 M 3018 / 2970, 2 of them with a tenth kept
+// 1398 / 1382, one rank's part of a 202 M bucket 186.3 / 178.3.
+constexpr uint32_t kEmitWindow = kCandChunksPerSuper / 2;  // chunks whose Index words are collected at a time
 template <int DTYPE>
 struct EmitLds {
-    static constexpr uint32_t kWords = 64 * (DTYPE == kBF16 ? 8 : 4) * kCandRows *
-                                       kCandChunksPerSuper / 32;
-    uint32_t bits[kEmitItems][kWords];
-    // staged survivor: value bits and position in the super-chunk (16 bits); bf16 packs
+    static constexpr uint32_t kWords = 64 * (DTYPE == kBF16 ? 8 : 4) * kCandRows * kEmitWindow / 32;
+    uint32_t bits[kEmitThreads / 64][kWords];
+    // a step's survivors: value bits and position in the super-chunk (16 bits); bf16 packs
     // both in one word, like a candidate slot
-    uint32_t st_a[kEmitItems][kEmitStage];
-    uint16_t st_b[kEmitItems][DTYPE == kF32 ? kEmitStage : 2];
+    uint32_t st_a[kEmitThreads / 64][256];
+    uint16_t st_b[kEmitThreads / 64][DTYPE == kF32 ? 256 : 2];
 };
 
-template <int DTYPE>
-__device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid, uint32_t nb,
-                                 const uint32_t *__restrict__ table, const WsLayout &wl,
-                                 const SelDev *__restrict__ sel,
-            const uint32_t *__restrict__ cand, const uint2 *__restrict__ chunk_info,
-            uint32_t CAP, const uint64_t *sc_cnt,
-            uint32_t *__restrict__ idx_out, float *__restrict__ val_out,
-            uint32_t *__restrict__ bitmap)
-{
-    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4;
-    constexpr uint32_t CHUNK = 64 * VEC * kCandRows;
-    constexpr uint32_t SC_ELEMS = CHUNK * kCandChunksPerSuper;
-    constexpr uint32_t SC_WORDS = SC_ELEMS / 32;
-    constexpr int NI = kEmitItems;
-    auto *bits = lds->bits;
-    auto *st_a = lds->st_a;
-    auto *st_b = lds->st_b;
-    static_assert(SC_ELEMS <= 65536, "a position in the super-chunk fits 16 bits");
-    __shared__ uint32_t s_gt[2 * NI], s_eq[2 * NI];
-    __shared__ uint64_t s_sum[2 * NI];
-    const uint32_t L = wl.L, total_sc = wl.total_sc;
-    const uint64_t n_slots_total = wl.n_slots;
-    const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
-    const uint32_t tid = threadIdx.x, lane = tid & 63;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t k = wave >> 1;  // this wave's item within the workgroup
-    const uint32_t tt = tid & 127;
-    const uint32_t ch_in_sc = tt >> 2, part = tt & 3;
-
-    for (uint32_t base = bid * NI; base < total_sc; base += nb * NI) {
-        // ---- requests that depend on nothing but the item number
-        const uint32_t sc = base + k;
-        bool live = sc < total_sc;
-        const uint32_t scc = live ? sc : 0u;
-        const uint32_t g = scc * kCandChunksPerSuper + ch_in_sc;  // global chunk number
-        // count and first slot (only meaningful for a chunk the scan has seen)
-        const uint2 cinfo = chunk_info[g];
-        const uint32_t craw = cinfo.x;
-        // (the bound keeps the reads inside `cand` whatever an unseen chunk's record holds)
-        const uint32_t *sp = cand + (min(cinfo.y, uint32_t(n_slots_total) - CAP) & ~3u);
-        // segment i's table rows in lane i
-        uint32_t t_start = 0xFFFFFFFFu, t_n = 0, t_coff = 0, t_T = 0, t_quota = 0, t_cnt = 0,
-                 t_route = 0;
-        if (L <= 64 && lane < L) {
-            static_assert(sizeof(SegDev) == 32 && sizeof(SelDev) == 32, "two uint4 per row");
-            const uint4 *s4 = reinterpret_cast<const uint4 *>(segs + lane);
-            const uint4 *e4 = reinterpret_cast<const uint4 *>(sel + lane);
-            const uint4 sa = s4[0], sb = s4[1], ea = e4[0], eb = e4[1];
-            t_n = sa.z; t_coff = sa.w; t_start = sb.w;                 // n, c_off, sc_start
-            if (sb.x != 0 && sa.z != 0) {   // k, n: a segment that keeps nothing has no selection
-                t_T = ea.x; t_quota = ea.y; t_cnt = ea.w; t_route = eb.w;  // T, quota, cnt, route
-            }
-        }
-        for (uint32_t i = tt; i < SC_WORDS; i += 128) bits[k][i] = 0;
-
-        // ---- segment, threshold, pair offset of the segment (all wave-uniform)
-        uint32_t l, c_off, n_seg, sc_first, T, quota, seg_base, se_cnt, se_route;
-        if (L <= 64) {
-            const uint64_t le = __ballot(t_start <= scc);  // a prefix of the lanes
-            l = uint32_t(__popcll(le)) - 1u;               // segment 0 starts at 0
-            n_seg = __builtin_amdgcn_readlane(t_n, l);
-            c_off = __builtin_amdgcn_readlane(t_coff, l);
-            sc_first = __builtin_amdgcn_readlane(t_start, l);
-            T = __builtin_amdgcn_readlane(t_T, l);
-            quota = __builtin_amdgcn_readlane(t_quota, l);
-            se_cnt = __builtin_amdgcn_readlane(t_cnt, l);
-            se_route = __builtin_amdgcn_readlane(t_route, l);
-            seg_base = wave_sum<uint32_t>(lane < l ? t_cnt : 0u);
-        } else {
-            l = segment_of(L, scc, [&](uint32_t i) { return segs[i].sc_start; });
-            const SegDev sd = segs[l];
-            SelDev se{};
-            if (sd.k != 0 && sd.n != 0) se = sel[l];
-            n_seg = sd.n; c_off = sd.c_off; sc_first = sd.sc_start;
-            T = se.T; quota = se.quota; se_cnt = se.cnt; se_route = se.route;
-            uint32_t sum = 0;
-            for (uint32_t i = lane; i < l; i += 64) sum += segment_count(segs[i], sel, i);
-            seg_base = wave_sum<uint32_t>(sum);
-        }
-        live = live && !se_route;  // the dense route writes re-routed segments
-        const uint32_t sc_rel0 = (scc - sc_first) * SC_ELEMS;
-        const bool in_seg = live && se_cnt != 0 && sc_rel0 + ch_in_sc * CHUNK < n_seg;
-        const uint32_t ccnt = in_seg ? min(craw, CAP) : 0u;
-        // the chunk's slots in four equal runs of whole 16-byte groups, one per thread
-        const uint32_t run = ((ccnt + 3) / 4 + 3) & ~3u;
-        const uint32_t s0 = min(part * run, ccnt), s1 = min(s0 + run, ccnt);
-        // The first two 16-byte groups of the run (all of it unless the chunk holds more
-        // than 32 candidates) are requested together and kept for both passes; a longer
-        // run reads the rest group by group.
-        constexpr uint32_t QN = 2;
-        uint4 q[QN], qp[QN];
-#pragma unroll
-        for (uint32_t j = 0; j < QN; ++j) {
-            q[j] = qp[j] = make_uint4(0, 0, 0, 0);
-            if (s0 + 4 * j < s1) {
-                q[j] = *reinterpret_cast<const uint4 *>(sp + s0 + 4 * j);
-                if (DTYPE == kF32)
-                    qp[j] = *reinterpret_cast<const uint4 *>(sp + n_slots_total + s0 + 4 * j);
-            }
-        }
-        // fn(value bits, position in chunk) for every slot of this thread
-        auto for_slots = [&](auto &&fn) {
-#pragma unroll
-            for (uint32_t j = 0; j < QN; ++j) {
-                const uint32_t v[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
-                const uint32_t rp[4] = {qp[j].x, qp[j].y, qp[j].z, qp[j].w};
-#pragma unroll
-                for (uint32_t i = 0; i < 4; ++i) {
-                    if (s0 + 4 * j + i >= s1) continue;
-                    if (DTYPE == kBF16) fn(v[i] & 0xFFFF0000u, v[i] & 0xFFFFu);
-                    else fn(v[i], rp[i]);
-                }
-            }
-            for (uint32_t s4 = s0 + 4 * QN; s4 < s1; s4 += 4) {
-                const uint4 a = *reinterpret_cast<const uint4 *>(sp + s4);
-                uint4 b = make_uint4(0, 0, 0, 0);
-                if (DTYPE == kF32) b = *reinterpret_cast<const uint4 *>(sp + n_slots_total + s4);
-                const uint32_t v[4] = {a.x, a.y, a.z, a.w};
-                const uint32_t rp[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-                for (uint32_t i = 0; i < 4; ++i) {
-                    if (s4 + i >= s1) continue;
-                    if (DTYPE == kBF16) fn(v[i] & 0xFFFF0000u, v[i] & 0xFFFFu);
-                    else fn(v[i], rp[i]);
-                }
-            }
-        };
-        // ---- pass 1: count this thread's slots above / at the threshold
-        uint32_t n_gt = 0, n_eq = 0;
-        for_slots([&](uint32_t vbits, uint32_t) {
-            const uint32_t key = vbits & 0x7FFFFFFFu;
-            n_gt += key > T;
-            n_eq += (key == T) && quota;
-        });
-        // ---- order inside the item (its 128 threads are in position order)
-        const uint32_t inc_gt = wave_incl_scan<uint32_t>(n_gt);
-        const uint32_t inc_eq = wave_incl_scan<uint32_t>(n_eq);
-        if (lane == 63) {
-            s_gt[wave] = inc_gt;
-            s_eq[wave] = inc_eq;
-        }
-        __syncthreads();
-        const uint32_t lo_gt = s_gt[2 * k], lo_eq = s_eq[2 * k];
-        const uint32_t it_gt = lo_gt + s_gt[2 * k + 1], it_eq = lo_eq + s_eq[2 * k + 1];
-        uint32_t gb = inc_gt - n_gt + ((wave & 1u) ? lo_gt : 0u);
-        uint32_t eb = inc_eq - n_eq + ((wave & 1u) ? lo_eq : 0u);
-        // ---- prefix over the segment's earlier super-chunks, whose counts are all there
-        uint64_t sum = 0;
-        if (live)
-            for (uint32_t j = sc_first + tt; j < sc; j += 128) sum += sc_cnt[j];
-        sum = wave_sum<uint64_t>(sum);
-        if (lane == 0) s_sum[wave] = sum;
-        __syncthreads();  // also orders the clearing of `bits` before the ORs below
-        sum = s_sum[2 * k] + s_sum[2 * k + 1];
-        // output position (within the segment) of the item's first survivor, and how many
-        // survivors the item has: entries above T all survive, ties while the quota lasts
-        const uint32_t pre_gt = uint32_t(sum >> 31), pre_eq = uint32_t(sum & 0x7FFFFFFFu);
-        const uint32_t item_pos = pre_gt + min(pre_eq, quota);
-        const uint32_t item_n = pre_gt + it_gt + min(pre_eq + it_eq, quota) - item_pos;
-        gb += pre_gt;
-        eb += pre_eq;
-        // ---- pass 2: place the survivors
-        if (n_gt | n_eq) {
-            for_slots([&](uint32_t vbits, uint32_t rel) {
-                const uint32_t key = vbits & 0x7FFFFFFFu;
-                uint32_t pos;
-                bool keep;
-                if (key > T) {
-                    pos = gb + min(eb, quota);
-                    keep = true;
-                    ++gb;
-                } else if (key == T && quota) {
-                    pos = gb + eb;
-                    keep = eb < quota;
-                    ++eb;
-                } else {
-                    return;
-                }
-                if (keep) {
-                    const uint32_t rel_sc = ch_in_sc * CHUNK + rel;
-                    const uint32_t ci = c_off + sc_rel0 + rel_sc;
-                    const uint32_t p = pos - item_pos;
-                    if (p < kEmitStage) {
-                        if (DTYPE == kBF16) {
-                            st_a[k][p] = vbits | rel_sc;
-                        } else {
-                            st_a[k][p] = vbits;
-                            st_b[k][DTYPE == kF32 ? p : 0] = uint16_t(rel_sc);
-                        }
-                    } else {
-                        idx_out[seg_base + pos] = ci;
-                        val_out[seg_base + pos] = __uint_as_float(vbits);
-                    }
-                    atomicOr(&bits[k][rel_sc >> 5], 1u << (rel_sc & 31));
-                }
-            });
-        }
-        __syncthreads();
-        if (live) {
-            const uint32_t n_st = min(item_n, kEmitStage);
-            for (uint32_t i = tt; i < n_st; i += 128) {
-                const uint32_t a = st_a[k][i];
-                const uint32_t rel_sc = DTYPE == kBF16 ? (a & 0xFFFFu) : st_b[k][DTYPE == kF32 ? i : 0];
-                idx_out[seg_base + item_pos + i] = c_off + sc_rel0 + rel_sc;
-                val_out[seg_base + item_pos + i] =
-                    __uint_as_float(DTYPE == kBF16 ? (a & 0xFFFF0000u) : a);
-            }
-            const uint32_t w0 = (c_off + sc_rel0) >> 5;
-            for (uint32_t i = tt; i < SC_WORDS; i += 128)
-                if (sc_rel0 + i * 32 < n_seg) bitmap[w0 + i] = bits[k][i];
-        }
-        __syncthreads();  // LDS is reused by the next iteration
-    }
-}
-
-// ------------------------------------------------- emit, a wave per super-chunk
-
-// emit_body gives a chunk's slots to four threads, which suits the few dozen candidates a
-// chunk holds when one entry in a hundred is kept, and stages an item's survivors in LDS.
-// Where a tenth or a fifth is kept (the 4x and 2x regimes of Table 1) a chunk holds
-// hundreds; and the LDS (23 KiB per workgroup in place) keeps all but two of its workgroups
-// off a compute unit on which another bucket's scan is running, which is how large buckets
-// are usually processed.  Here a wave takes a whole super-chunk
-// and reads its chunks' slots 64 at a time, in position order, BATCH such reads in
-// flight.  The survivors among the 64 slots of one read are neighbours in the output, so
-// they are stored as they are found; the Index words of a chunk are collected in LDS and
-// leave when its last slots are through.  Same inputs, same outputs as emit_body.
 template <int DTYPE, uint32_t BATCH>
-__device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
+__device__ __forceinline__ void emit_body(EmitLds<DTYPE> *lds, uint32_t bid,
                                  const uint32_t *__restrict__ table, const WsLayout &wl,
                                  const SelDev *__restrict__ sel,
             const uint32_t *__restrict__ cand, const uint2 *__restrict__ chunk_info,
@@ -1938,16 +1710,29 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
     constexpr uint32_t CHUNK = 64 * VEC * kCandRows;
     constexpr uint32_t NCH = kCandChunksPerSuper;
     constexpr uint32_t SC_ELEMS = CHUNK * NCH;
-    constexpr uint32_t CH_WORDS = CHUNK / 32;
+    constexpr uint32_t WORDS = EmitLds<DTYPE>::kWords;
     constexpr uint32_t NWV = kEmitThreads / 64;
-    static_assert(NCH <= 64 && CH_WORDS <= 64, "a lane per chunk, a lane per Index word of a chunk");
-    __shared__ uint32_t wbits[NWV][CH_WORDS];  // a wave's current chunk
+    static_assert(NCH == 32 && kEmitWindow == 16, "a lane per chunk, four steps of the search");
+    static_assert(SC_ELEMS <= 65536, "a position in the super-chunk fits 16 bits");
     const uint32_t L = wl.L, total_sc = wl.total_sc;
     const uint64_t n_slots_total = wl.n_slots;
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t lanes_below = (1ull << lane) - 1ull;
+    const uint32_t sc = bid * NWV + wave;
+    if (sc >= total_sc) return;
+    // (no other wave touches these)
+    uint32_t *bits = lds->bits[wave], *st_a = lds->st_a[wave];
+    uint16_t *st_b = lds->st_b[wave];
+    auto wave_fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+
+    auto total = [](uint32_t x) -> uint32_t {
+        return __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(x), 63);
+    };
 
     // segment i's table rows in lane i
     uint32_t t_start = 0xFFFFFFFFu, t_n = 0, t_coff = 0, t_T = 0, t_quota = 0, t_cnt = 0,
@@ -1961,161 +1746,155 @@ __device__ __forceinline__ void emit_wide_body(uint32_t bid, uint32_t nb,
             t_T = ea.x; t_quota = ea.y; t_cnt = ea.w; t_route = eb4.w;  // T, quota, cnt, route
         }
     }
-    if (lane < CH_WORDS) wbits[wave][lane] = 0;  // (no other wave touches this row)
+    for (uint32_t i = lane; i < WORDS; i += 64) bits[i] = 0;
 
-    for (uint32_t sc = bid * NWV + wave; sc < total_sc; sc += nb * NWV) {  // wave-uniform
-        // count and first slot of chunk `lane` (only meaningful for a chunk the scan has seen),
-        // requested together with the tables above
-        const uint2 info = lane < NCH ? chunk_info[sc * NCH + lane] : make_uint2(0, 0);
-        // ---- segment, threshold, pair offset of the segment
-        uint32_t l, c_off, n_seg, sc_first, T, quota, seg_base, se_cnt, se_route;
-        if (L <= 64) {
-            const uint64_t le = __ballot(t_start <= sc);  // a prefix of the lanes
-            l = uint32_t(__popcll(le)) - 1u;              // segment 0 starts at 0
-            n_seg = __builtin_amdgcn_readlane(t_n, l);
-            c_off = __builtin_amdgcn_readlane(t_coff, l);
-            sc_first = __builtin_amdgcn_readlane(t_start, l);
-            T = __builtin_amdgcn_readlane(t_T, l);
-            quota = __builtin_amdgcn_readlane(t_quota, l);
-            se_cnt = __builtin_amdgcn_readlane(t_cnt, l);
-            se_route = __builtin_amdgcn_readlane(t_route, l);
-            seg_base = wave_sum<uint32_t>(lane < l ? t_cnt : 0u);
-        } else {
-            l = segment_of(L, sc, [&](uint32_t i) { return segs[i].sc_start; });
-            const SegDev sd = segs[l];
-            SelDev se{};
-            if (sd.k != 0 && sd.n != 0) se = sel[l];
-            n_seg = sd.n; c_off = sd.c_off; sc_first = sd.sc_start;
-            T = se.T; quota = se.quota; se_cnt = se.cnt; se_route = se.route;
-            uint32_t sum = 0;
-            for (uint32_t i = lane; i < l; i += 64) sum += segment_count(segs[i], sel, i);
-            seg_base = wave_sum<uint32_t>(sum);
+    // count and first slot of chunk `lane` (only meaningful for a chunk the scan has seen),
+    // requested together with the tables above
+    const uint2 info = lane < NCH ? chunk_info[sc * NCH + lane] : make_uint2(0, 0);
+    // ---- segment, threshold, pair offset of the segment
+    uint32_t l, c_off, n_seg, sc_first, T, quota, seg_base, se_cnt, se_route;
+    if (L <= 64) {
+        const uint64_t le = __ballot(t_start <= sc);  // a prefix of the lanes
+        l = uint32_t(__popcll(le)) - 1u;              // segment 0 starts at 0
+        n_seg = __builtin_amdgcn_readlane(t_n, l);
+        c_off = __builtin_amdgcn_readlane(t_coff, l);
+        sc_first = __builtin_amdgcn_readlane(t_start, l);
+        T = __builtin_amdgcn_readlane(t_T, l);
+        quota = __builtin_amdgcn_readlane(t_quota, l);
+        se_cnt = __builtin_amdgcn_readlane(t_cnt, l);
+        se_route = __builtin_amdgcn_readlane(t_route, l);
+        seg_base = lane < l ? t_cnt : 0u;
+    } else {
+        l = segment_of(L, sc, [&](uint32_t i) { return segs[i].sc_start; });
+        const SegDev sd = segs[l];
+        SelDev se{};
+        if (sd.k != 0 && sd.n != 0) se = sel[l];
+        n_seg = sd.n; c_off = sd.c_off; sc_first = sd.sc_start;
+        T = se.T; quota = se.quota; se_cnt = se.cnt; se_route = se.route;
+        uint32_t sum = 0;
+        for (uint32_t i = lane; i < l; i += 64) sum += segment_count(segs[i], sel, i);
+        seg_base = sum;
+    }
+    seg_base = total(seg_base);
+    if (se_route) return;  // the dense route writes re-routed segments
+    const uint32_t sc_rel0 = (sc - sc_first) * SC_ELEMS;
+
+    // ---- chunk `lane` of the super-chunk: its candidates and where their slots are
+    // (the bounds keep the reads inside `cand` whatever the record holds)
+    uint32_t cnt_l = 0;
+    if (lane < NCH && se_cnt != 0 && sc_rel0 + lane * CHUNK < n_seg) cnt_l = min(info.x, CAP);
+    const uint32_t ngr_l = (cnt_l + 3u) >> 2;
+    const uint32_t gend_l = wave_incl_scan<uint32_t>(ngr_l);  // (lanes from NCH on: the total)
+    // slot and slots left at group g: these + 4 g, - 4 g
+    const uint32_t at_l = (min(info.y, uint32_t(n_slots_total) - CAP) & ~3u) - 4 * (gend_l - ngr_l);
+    const uint32_t left_l = cnt_l + 4 * (gend_l - ngr_l);
+    // steps of the first window and of both
+    const uint32_t G0 = __builtin_amdgcn_readlane(gend_l, kEmitWindow - 1);
+    const uint32_t G1 = __builtin_amdgcn_readlane(gend_l, 63);
+    const uint32_t S0 = (G0 + 63) >> 6, S = S0 + ((G1 - G0 + 63) >> 6);
+    uint4 q[BATCH], qp[BATCH];
+    uint32_t who[BATCH];  // chunk << 8 | slots of the lane's group
+    auto request = [&](uint32_t t, uint32_t j) {
+        const bool second = t >= S0;
+        const uint32_t g = (second ? G0 + (t - S0) * 64 : t * 64) + lane;
+        uint32_t ch = second ? kEmitWindow : 0u;  // first chunk that ends behind g
+#pragma unroll
+        for (uint32_t d = kEmitWindow / 2; d; d >>= 1)
+            ch += uint32_t(__shfl(gend_l, int(ch + d - 1), 64)) <= g ? d : 0u;
+        const uint32_t at = uint32_t(__shfl(at_l, int(ch), 64)) + 4 * g;
+        const uint32_t left = uint32_t(__shfl(left_l, int(ch), 64)) - 4 * g;
+        const uint32_t n = g < (second ? G1 : G0) ? min(left, 4u) : 0u;
+        who[j] = ch << 8 | n;
+        q[j] = qp[j] = make_uint4(0, 0, 0, 0);
+        if (n) {  // (a chunk's slots start on, and have room up to, 16 bytes)
+            q[j] = *reinterpret_cast<const uint4 *>(cand + at);
+            if (DTYPE == kF32) qp[j] = *reinterpret_cast<const uint4 *>(cand + n_slots_total + at);
         }
-        const bool live = !se_route;  // the dense route writes re-routed segments
-        const uint32_t sc_rel0 = (sc - sc_first) * SC_ELEMS;
+    };
+#pragma unroll
+    for (uint32_t j = 0; j < BATCH; ++j)
+        if (j < S) request(j, j);  // (on their way while the prefix below is added up)
 
-        // ---- chunk `lane` of the super-chunk: its candidates and where their slots are
-        // (the bound keeps the reads inside `cand` whatever the record holds)
-        bool inseg_l = false;
-        uint32_t cnt_l = 0, first_l = 0;
-        if (lane < NCH) {
-            inseg_l = live && sc_rel0 + lane * CHUNK < n_seg;
-            if (inseg_l && se_cnt != 0) {
-                cnt_l = min(info.x, CAP);
-                first_l = min(info.y, uint32_t(n_slots_total) - CAP);
-            }
+    // prefix over the segment's earlier super-chunks, whose counts are all there
+    // (eight requests at a time; a tenth kept on 202 M entries, 2 ranks: 163 -> 141 us.
+    // fp32 slots are two words each, and beside those in flight there is room for two
+    // requests: with eight, 24 registers went to scratch memory.  2 ranks, a tenth of 67 M
+    // kept, then a hundredth of 202 M: 103 -> 87 us, 66 -> 56)
+    constexpr uint32_t PRE = DTYPE == kBF16 ? 8 : 2;
+    uint64_t sum = 0;
+    for (uint32_t j = sc_first + lane; j < sc; j += PRE * 64) {
+        uint64_t c[PRE];
+#pragma unroll
+        for (uint32_t i = 0; i < PRE; ++i) c[i] = j + 64 * i < sc ? sc_cnt[j + 64 * i] : 0ull;
+#pragma unroll
+        for (uint32_t i = 0; i < PRE; ++i) sum += c[i];
+    }
+    // entries above / at the threshold before the current step
+    uint32_t gb = total(uint32_t(sum >> 31));
+    uint32_t eb = total(uint32_t(sum & 0x7FFFFFFFu));
+
+    // a window's Index words leave, and read zero again
+    auto flush = [&](uint32_t window) {
+        wave_fence();
+#pragma unroll 8
+        for (uint32_t i = lane; i < WORDS; i += 64) {
+            const uint32_t w = bits[i], rel0 = sc_rel0 + (window * WORDS + i) * 32;
+            bits[i] = 0;
+            if (rel0 < n_seg) bitmap[(c_off + rel0) >> 5] = w;
         }
-        // Reads of 64 slots ("groups"), numbered through the super-chunk.  Where no chunk
-        // needs a second read (a few dozen candidates per chunk) group g is simply chunk g.
-        const uint32_t ngr_l = (cnt_l + 63u) >> 6;
-        const uint32_t gend_l = wave_incl_scan<uint32_t>(ngr_l);  // (lanes from NCH on: the total)
-        const bool one_each = __ballot(ngr_l > 1u) == 0;
-        const uint32_t n_groups = one_each ? NCH : __builtin_amdgcn_readlane(gend_l, 63);
-        const uint32_t ins_l = inseg_l ? 1u : 0u;
-        // where group g lies (all wave-uniform): chunk, first slot, slots of the chunk
-        auto locate = [&](uint32_t g, uint32_t &ch, uint32_t &c, uint32_t &s0, uint32_t &first) {
-            if (one_each) {
-                ch = g;
-                s0 = 0;
-            } else {
-                ch = uint32_t(__popcll(__ballot(gend_l <= g)));  // chunks that end before g
-                const uint32_t gbeg = __builtin_amdgcn_readlane(gend_l, ch) -
-                                      __builtin_amdgcn_readlane(ngr_l, ch);
-                s0 = (g - gbeg) * 64;
-            }
-            c = __builtin_amdgcn_readlane(cnt_l, ch);
-            first = __builtin_amdgcn_readlane(first_l, ch);
-        };
-        uint32_t v[BATCH], vp[BATCH];
-        auto request = [&](uint32_t b0) {
+        wave_fence();
+    };
+    for (uint32_t t0 = 0; t0 < S; t0 += BATCH) {
 #pragma unroll
-            for (uint32_t j = 0; j < BATCH; ++j) {
-                v[j] = vp[j] = 0;
-                if (b0 + j < n_groups) {
-                    uint32_t ch, c, s0, first;
-                    locate(b0 + j, ch, c, s0, first);
-                    if (s0 + lane < c) {
-                        v[j] = cand[first + s0 + lane];
-                        if (DTYPE == kF32) vp[j] = cand[n_slots_total + first + s0 + lane];
-                    }
+        for (uint32_t j = 0; j < BATCH; ++j) {
+            const uint32_t t = t0 + j;
+            if (t >= S) break;  // uniform
+            if (t == S0) flush(0);
+            const uint32_t n = who[j] & 0xFFu, base = (who[j] >> 8) * CHUNK;
+            const uint32_t a[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
+            const uint32_t b[4] = {qp[j].x, qp[j].y, qp[j].z, qp[j].w};
+            constexpr uint32_t KEY = DTYPE == kBF16 ? 0x7FFF0000u : 0x7FFFFFFFu;
+            uint32_t own = 0;  // entries above << 16 | at the threshold
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) {
+                const uint32_t key = a[i] & KEY;
+                own += i < n ? (key > T ? 0x10000u : key == T && quota ? 1u : 0u) : 0u;
+            }
+            if (t + BATCH < S) request(t + BATCH, j);
+            const uint32_t inc = wave_incl_scan<uint32_t>(own);
+            const uint32_t all = __builtin_amdgcn_readlane(inc, 63);
+            // entries above T all survive, ties while the quota lasts
+            const uint32_t pos0 = gb + min(eb, quota);  // the step's first survivor
+            uint32_t my_gb = gb + ((inc - own) >> 16), my_eb = eb + ((inc - own) & 0xFFFFu);
+            gb += all >> 16;
+            eb += all & 0xFFFFu;
+            const uint32_t kept = gb + min(eb, quota) - pos0;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) {
+                const uint32_t key = a[i] & KEY;
+                const bool is_gt = i < n && key > T, is_eq = i < n && key == T && quota;
+                if (is_gt || (is_eq && my_eb < quota)) {
+                    const uint32_t p = my_gb + min(my_eb, quota) - pos0;
+                    const uint32_t rel = base + ((DTYPE == kBF16 ? a[i] : b[i]) & (CHUNK - 1u));
+                    st_a[p] = DTYPE == kBF16 ? (a[i] & 0xFFFF0000u) | rel : a[i];
+                    if (DTYPE == kF32) st_b[p] = uint16_t(rel);
+                    const uint32_t in_window = rel & (WORDS * 32 - 1u);
+                    atomicOr(&bits[in_window >> 5], 1u << (in_window & 31));
                 }
+                my_gb += is_gt;
+                my_eb += is_eq;
             }
-        };
-        request(0);  // (on their way while the prefix below is added up)
-
-        uint32_t gb = 0, eb = 0;  // entries above / at the threshold before the current slot
-        // prefix over the segment's earlier super-chunks, whose counts are all there
-        // (eight requests at a time; a tenth kept on 202 M entries, 2 ranks: 163 -> 141 us.
-        // fp32 slots are two words each, and beside those in flight there is room for two
-        // requests: with eight, 24 registers went to scratch memory.  2 ranks, a tenth of 67 M
-        // kept, then a hundredth of 202 M: 103 -> 87 us, 66 -> 56)
-        constexpr uint32_t PRE = DTYPE == kBF16 ? 8 : 2;
-        uint64_t sum = 0;
-        if (live)
-            for (uint32_t j = sc_first + lane; j < sc; j += PRE * 64) {
-                uint64_t c[PRE];
-#pragma unroll
-                for (uint32_t i = 0; i < PRE; ++i) c[i] = j + 64 * i < sc ? sc_cnt[j + 64 * i] : 0ull;
-#pragma unroll
-                for (uint32_t i = 0; i < PRE; ++i) sum += c[i];
+            wave_fence();
+            for (uint32_t i = lane; i < kept; i += 64) {
+                const uint32_t w = st_a[i], r = DTYPE == kBF16 ? w & 0xFFFFu : uint32_t(st_b[i]);
+                idx_out[seg_base + pos0 + i] = c_off + sc_rel0 + r;
+                val_out[seg_base + pos0 + i] = __uint_as_float(DTYPE == kBF16 ? w & 0xFFFF0000u : w);
             }
-        sum = wave_sum<uint64_t>(sum);
-        gb = uint32_t(sum >> 31);
-        eb = uint32_t(sum & 0x7FFFFFFFu);
-        // chunks of the segment without a candidate have no group of their own unless
-        // group = chunk: their Index words are zero
-        if (!one_each) {
-            for (uint64_t em = __ballot(inseg_l && cnt_l == 0); em; em &= em - 1) {
-                const uint32_t ch = uint32_t(__builtin_ctzll(em));
-                const uint32_t rel0 = sc_rel0 + ch * CHUNK + lane * 32;
-                if (lane < CH_WORDS && rel0 < n_seg) bitmap[(c_off + rel0) >> 5] = 0;
-            }
-        }
-
-        for (uint32_t b0 = 0; b0 < n_groups;) {
-#pragma unroll
-            for (uint32_t j = 0; j < BATCH; ++j) {
-                if (b0 + j >= n_groups) continue;
-                uint32_t ch, c, s0, first;
-                locate(b0 + j, ch, c, s0, first);
-                const bool valid = s0 + lane < c;
-                const uint32_t vbits = DTYPE == kBF16 ? (v[j] & 0xFFFF0000u) : v[j];
-                const uint32_t rel = (DTYPE == kBF16 ? (v[j] & 0xFFFFu) : vp[j]) & (CHUNK - 1u);
-                const uint32_t key = vbits & 0x7FFFFFFFu;
-                const bool is_gt = valid && key > T;
-                const bool is_eq = valid && key == T && quota != 0;
-                const uint64_t bgt = __ballot(is_gt), beq = __ballot(is_eq);
-                const uint32_t my_gb = gb + uint32_t(__popcll(bgt & lanes_below));
-                const uint32_t my_eb = eb + uint32_t(__popcll(beq & lanes_below));
-                // entries above T all survive, ties while the quota lasts
-                const bool keep = is_gt || (is_eq && my_eb < quota);
-                if (keep) {
-                    const uint32_t pos = is_gt ? my_gb + min(my_eb, quota) : my_gb + my_eb;
-                    idx_out[seg_base + pos] = c_off + sc_rel0 + ch * CHUNK + rel;
-                    val_out[seg_base + pos] = __uint_as_float(vbits);
-                    atomicOr(&wbits[wave][rel >> 5], 1u << (rel & 31));
-                }
-                // the chunk's last slots: its Index words leave
-                if (s0 + 64 >= c && __builtin_amdgcn_readlane(ins_l, ch)) {
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    if (lane < CH_WORDS) {
-                        const uint32_t w = wbits[wave][lane];
-                        wbits[wave][lane] = 0;
-                        const uint32_t rel0 = sc_rel0 + ch * CHUNK + lane * 32;
-                        if (rel0 < n_seg) bitmap[(c_off + rel0) >> 5] = w;
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                }
-                gb += uint32_t(__popcll(bgt));
-                eb += uint32_t(__popcll(beq));
-            }
-            b0 += BATCH;
-            if (b0 < n_groups) request(b0);
+            wave_fence();
         }
     }
+    if (S == S0) flush(0);
+    flush(1);
 }
 
 // ---------------------------------------------------------------- compact
@@ -2382,7 +2161,7 @@ count_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles,
             rv.at<uint64_t>(wl.tile_cnt), rv.at<uint64_t>(wl.group_cnt), nullptr, nullptr, nullptr);
 }
 
-template <int DTYPE, uint32_t COMPACT_ROWS, bool WIDE, bool STAGED>
+template <int DTYPE, uint32_t COMPACT_ROWS, bool STAGED>
 __global__ void __launch_bounds__(kEmitThreads)
     __attribute__((amdgpu_waves_per_eu(COMPACT_ROWS == 2 ? 7 : STAGED && DTYPE == kBF16 ? 4 : 6, 8)))
 place_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles, uint32_t *table,
@@ -2392,11 +2171,7 @@ place_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles, uint32_t
         EmitLds<DTYPE> emit;
         CompactLds<DTYPE, STAGED> compact;
     };
-    union LdsWide {
-        uint32_t wide;
-        CompactLds<DTYPE, STAGED> compact;
-    };
-    __shared__ typename std::conditional<WIDE, LdsWide, Lds>::type lds;
+    __shared__ Lds lds;
     const RankView rv = rank_view();
     const SelDev *sel = rv.at<SelDev>(wl.sel);
     if (blockIdx.x == gridDim.x - 1) {  // (any one workgroup: the last has the least to do)
@@ -2407,11 +2182,8 @@ place_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles, uint32_t
         const uint32_t *cand = rv.at<uint32_t>(wl.cand);
         const uint2 *chunk_info = rv.at<uint2>(wl.chunk_info);
         const uint64_t *sc_cnt = rv.at<uint64_t>(wl.sc_cnt);
-        if constexpr (WIDE)
-            emit_wide_body<DTYPE, 16>(blockIdx.x, n_emit, table, wl, sel, cand, chunk_info, CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
-        else
-            emit_body<DTYPE>(&lds.emit, blockIdx.x, n_emit, table, wl, sel, cand, chunk_info,
-                                   CAP, sc_cnt, rv.idx, rv.val, rv.bitmap);
+        emit_body<DTYPE, DTYPE == kBF16 ? 4 : 2>(&lds.emit, blockIdx.x, table, wl, sel, cand, chunk_info, CAP,
+                                                 sc_cnt, rv.idx, rv.val, rv.bitmap);
     } else
         compact_body<DTYPE, COMPACT_ROWS, true, STAGED>(
             &lds.compact, blockIdx.x - n_emit, gridDim.x - n_emit, plan_tiles, rv.src(), table, wl, sel,
@@ -2563,7 +2335,7 @@ int launch_select(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, boo
         // (the longer stage unless other buckets are in flight and chunks hold dozens of candidates: see
         // kSpillStage)
         constexpr bool kCanLong = DTYPE == kBF16;
-        const bool lng = kCanLong && (!p->cfg.decode_workgroups || p->cand_cap >= kWideEmitCap);
+        const bool lng = kCanLong && (!p->cfg.decode_workgroups || p->cand_cap >= kManyCandCap);
         auto scan = lng ? (acc ? scan_spill_kernel<DTYPE, true, kCanLong> : scan_spill_kernel<DTYPE, false, kCanLong>)
                         : (acc ? scan_spill_kernel<DTYPE, true, false> : scan_spill_kernel<DTYPE, false, false>);
         // Workgroups that fit the device at once, or, where their spans stay long enough for what
@@ -2601,7 +2373,7 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
 {
     const WsLayout wl = ws_layout(p);
     const int cus = device_cu_count();
-    static int occ_place[2][3] = {};
+    static int occ_place[3] = {};
     auto per_rank = [&](uint32_t total) { return std::max(1u, total / n); };
     if (DTYPE == kF32 && (p->any_fast || p->span_dense)) {
         // candidate list: four super-chunks (a wave each) to a workgroup, no more of them than fit
@@ -2620,9 +2392,9 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
     }
     {
         // the plan fixed the compaction tile's height, and with it which kernels these are
-        // (and, for place, whether chunks hold dozens or hundreds of candidates)
-        const bool rows4 = p->compact_rows == 4, wd = p->emit_wide;
-        const bool many = p->cand_cap >= kWideEmitCap;
+        // (and, for count, whether chunks hold dozens or hundreds of candidates)
+        const bool rows4 = p->compact_rows == 4;
+        const bool many = p->cand_cap >= kManyCandCap;
         auto count = many ? (rows4 ? count_kernel<DTYPE, 4, true> : count_kernel<DTYPE, 2, true>)
                           : (rows4 ? count_kernel<DTYPE, 4, false> : count_kernel<DTYPE, 2, false>);
         // place stages the dense route's tiles where most pairs can come from them.  Beside large
@@ -2631,19 +2403,14 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
         // and 5 thousand: place 62 us staged, 55 not; 25 M and 9 M of which two fifths are kept:
         // 71 and 92; 25 M and 1 M: 26 and 25).
         const bool staged = rows4 && 2 * p->dense_pairs > p->K;
-        auto place = wd ? (staged  ? place_kernel<DTYPE, 4, true, true>
-                           : rows4 ? place_kernel<DTYPE, 4, true, false>
-                                   : place_kernel<DTYPE, 2, true, false>)
-                        : (staged  ? place_kernel<DTYPE, 4, false, true>
-                           : rows4 ? place_kernel<DTYPE, 4, false, false>
-                                   : place_kernel<DTYPE, 2, false, false>);
-        const int occ = resident_blocks_per_cu(place, kEmitThreads, 0, &occ_place[wd][rows4 + staged]);
+        auto place = staged ? place_kernel<DTYPE, 4, true>
+                     : rows4 ? place_kernel<DTYPE, 4, false> : place_kernel<DTYPE, 2, false>;
+        const int occ = resident_blocks_per_cu(place, kEmitThreads, 0, &occ_place[rows4 + staged]);
         if (occ <= 0) return TAGC_EHIP;
-        // emit_body: kEmitItems super-chunks per workgroup; emit_wide_body: one per wave
         auto n_emit = [&](uint32_t per_wg) {
             return p->any_fast ? (p->total_sc + per_wg - 1) / per_wg : 0u;
         };
-        const uint32_t n_count = n_emit(count_items(many)), n_place = n_emit(wd ? kEmitThreads / 64 : kEmitItems);
+        const uint32_t n_count = n_emit(count_items(many)), n_place = n_emit(kEmitThreads / 64);
         // Dense route: one tile per workgroup where the work is certain.  The tiles of the
         // candidate route's segments are only a safety net for re-routed ones and the
         // workgroups for them nearly always exit at once: a grid that fits the device takes

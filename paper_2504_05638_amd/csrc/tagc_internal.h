@@ -25,12 +25,10 @@ constexpr uint32_t kHistWindow = 4096;
 constexpr uint32_t kCandRows = 4;        // 16-byte vectors per lane per candidate chunk
 constexpr uint32_t kCandChunksPerSuper = 32;  // chunks one emit workgroup handles
 constexpr uint32_t kEmitThreads = 256;
-constexpr int kEmitItems = 2;  // super-chunks per workgroup of the candidate route's last pass
 constexpr uint32_t kSampleVectors = 4096;     // 16-byte vectors sampled per segment
 constexpr uint32_t kFastMinElems = 1u << 17;  // shorter segments take the dense path
 constexpr uint32_t kFastMinKeep = 64;
-constexpr uint32_t kWideEmitCap = 192;  // candidate slots per chunk from which count / place give a wave to a super-chunk
-constexpr uint32_t kWideEmitSuperChunks = 2048;  // ... and super-chunks per bucket from which they do so anyway
+constexpr uint32_t kManyCandCap = 192;  // candidate slots per chunk from which a chunk holds hundreds of them
 constexpr double kFastMaxCandFrac = 0.30;  // expected candidates per element beyond which the dense path is planned
 constexpr uint32_t kChunkWords = 1024;  // Index words per popcount chunk, ...
 constexpr uint32_t kGroupWords = 64;    // ... and per group of it
@@ -176,7 +174,6 @@ struct tagc_plan_s {
     bool small_dense;                         // some dense-route segment is kSegSmall
     uint64_t span_dense;                      // entries of the dense-route segments that are not
     uint64_t dense_pairs;                     // pairs the dense-route segments emit at most
-    bool emit_wide;                           // chunks hold hundreds of candidates: a wave per super-chunk in count / place
     uint64_t n_real, n_c, K, U_cap, A_cap, m_cap;
     uint32_t P_cap, T_cap;
     tagc::Workspace ws;
