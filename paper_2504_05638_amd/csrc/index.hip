@@ -203,13 +203,15 @@ __device__ inline uint32_t lower_bound_by_16(const uint32_t *list, uint32_t n, u
 // were 21 and 40 with the same comparison.  A workgroup's first partition waits for memory, in order: chunk
 // counts, Index words of the bounds, its own words; then the searches waited 10 to 20 K clocks for four to six
 // steps (83 K with 16 ranks of 202 M entries) in which its compute unit hashed nothing.  So some
-// workgroups of the launch find the ends in the pair lists, beside the others' salts (us a pass, before /
-// after: 16 ranks of 202 M entries 3049 / 3021, one of them with three others' Indexes 196.5 / 191.5, 8 ranks of
-// 7 M 218.8 / 217.0, 4 of 1 M 83.6 / 82.1, 3 of 36 thousand 64.8 / 63.7, 8 of 25 M 241 / 238.5; 2 of 202 M with a
-// tenth kept no difference).  (Tried: a step of the searches between the steps of the salts, whose waits are
+// workgroups of the launch find the ends in the pair lists, beside the others' salts (us of this kernel, before /
+// after: 16 ranks of 202 M entries 125 / 105, one of them with three others' Indexes 52 / 47, 8 ranks of 67 M 27 / 24,
+// of 25 M 24.2 / 21.6, of 7 M 20.4 / 18.0, 4 of 1 M 17.0 / 15.0, 3 of 36 thousand 14.3 / 13.0; 2 of 202 M with a
+// tenth kept 124.5 / 122.7).  (Tried: a step of the searches between the steps of the salts, whose waits are
 // longer than those steps, half as much or nothing; the chunk counts kept in LDS for the bounds, nothing; 256
 // parts a step and half the steps in small launches, 3 us slower, bound by the lines; words beyond the first
-// four requested ahead, 0 to 6 % slower.)
+// four requested ahead, 0 to 6 % slower; two searches of a wave at once, 16 ranks of 202 M 141 where one was 135, 8 of
+// 7 M 18.9, 18.0; the last, nearly empty turn of the salts taken by the searchers once they are through, 2 of 202 M
+// with a tenth 133.5, 4 of 202 M 48.3, 47.2, since they are through last.)
 constexpr uint32_t kSaltThreads = 1024;
 constexpr uint32_t kLayoutBatch = kSaltThreads / 128;  // partitions whose bounds are found at once
 constexpr uint64_t kSplitSearches = 32768;  // (partition, rank) pairs
@@ -409,8 +411,8 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
         }
     }
     if (searcher) continue;
-    // Requests run ahead of the work: the first Index words of the first partition are on their
-    // way while the pair lists are searched, those of the next while one is checked.
+    // Requests run ahead of the work: the first Index words of a partition while the one before it is checked.
+    // (Those of the first ahead of the searches too, where a workgroup does both: no difference.)
     uint32_t lo = uniform(s_bound[0]), hi = uniform(s_bound[1]), pre[kSaltPre];
 #pragma unroll
     for (uint32_t k = 0; k < kSaltPre; ++k)
@@ -619,13 +621,18 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     const bool split = p->cfg.decode_workgroups && p->A_cap * n_ranks > kSplitSearches;
     const uint32_t batches = uint32_t(std::min<uint64_t>((p->A_cap + kLayoutBatch - 1) / kLayoutBatch,
                                                          uint64_t(device_cu_count()) * 2));
-    // Searching workgroups of the one launch, and those that look for salts, each taking
-    // partitions b, b + grid, ...  64 search fast enough to be done before the salts of the largest buckets
-    // (us of a pass, 16 / 32 / 64 / 128 of them: 16 ranks of 202 M entries 3332 / 3121 / 3021 / 3014, 2 ranks with a
-    // tenth kept 1570 / 1442 / 1421 / 1442, 4 ranks of 9 M with two fifths 371 / 343 / 342 / 344).
-    // Not so where they would make the salts' workgroups one more turn.
-    const bool apart = p->A_cap + std::min(64u, batches) <= most || p->A_cap > most;
-    const uint32_t searching = apart ? std::min(std::min(64u, batches), most / 2) : 0u;
+    // Searching workgroups of the one launch, and those that look for salts, each taking partitions b, b + grid,
+    // ...  The searches of a partition grow with the ranks, its salt does not: 64 are done before the salts
+    // with up to eight ranks, 96 with more (us of layout, 32 / 64 / 96 / 128 of them: 16 ranks of 202 M entries
+    // 238 / 138 / 106 / 115, where all workgroups did both in 125; 12 ranks 155 / 93 / 86 / 93; 8 ranks 87 / 65 / 65 /
+    // 71; 2 ranks with a tenth kept 159 / 123 / 133 / 143; 4 ranks 48 / 48 / 52 / 51; 16 ranks of 9 M with two fifths
+    // 98 / 64 / 51 / 54).  None where all workgroups have a partition each and the salts' alone would not: all of
+    // them do both then (8 ranks of 49 M entries, 464 partitions, 24.9).  A call may have as few under a plan for more,
+    // when ranks share what they keep: two turns (480 partitions, 29.8; 28.7 if all did both, but for the
+    // kernel to ask how many there are cost all other calls 0.5 to 1).
+    const uint32_t want = std::min(n_ranks > 8 ? 96u : 64u, batches);
+    const bool apart = p->A_cap + want <= most || p->A_cap > most;
+    const uint32_t searching = apart ? std::min(want, most / 2) : 0u;
     const uint32_t salting = uint32_t(std::min<uint64_t>(p->A_cap, most - searching));
     const auto layout = layout_kernel<true, true, true>, salts = layout_kernel<false, false, true>;
     static size_t attr_bytes[2] = {0, 0};

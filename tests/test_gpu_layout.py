@@ -29,11 +29,37 @@ def test_layout_and_ranges(n, keep_ppm, ranks, P, T, least):
     ores, tb = run_both(b, _ints(n, ranks, 7), seed=2, P=P, T=T, dense=False)
     hdr, _ = compare_all(b, ores, tb, exact_values=P != 16)
     assert hdr["A"] >= least
-    # a rank's ranges: where its sorted pairs cross the partition bounds
+    _check_ranges(tb, ranks, hdr["A"])
+
+
+# All workgroups do both, searches and salts: as many partitions as the device holds workgroups, nearly.  Apart: as many
+# under a plan for twice as many, which are two turns of the salts; more than eight ranks, which have more searchers.
+@pytest.mark.parametrize("keep_ppm,ranks,shared,P,T,cap,least", [
+    (15_000, 4, False, 512, 768, (456, 512), 456),
+    (30_000, 4, True, 512, 768, (513, 2000), 449),
+    (4_000, 16, False, 256, 384, (768, 2000), 768),
+])
+def test_who_searches(keep_ppm, ranks, shared, P, T, cap, least):
+    print("\n[case] who searches, ranks=%d P=%d ppm=%d" % (ranks, P, keep_ppm), flush=True)
+    n = 4_000_000
+    b = G.Bucket("layout", G.F32, ranks, [G.Seg(0, n, keep_ppm, 1, "w")], n, 1600)
+    grads = _ints(n, ranks, 11)
+    if shared:
+        grads = grads[:2] * 2
+    ores, tb = run_both(b, grads, seed=2, P=P, T=T, dense=False)
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256  # (two workgroups each)
+    assert cap[0] <= tb.sizes.partition_capacity <= cap[1]
+    hdr, _ = compare_all(b, ores, tb, exact_values=True)
+    assert least <= hdr["A"] and (not shared or hdr["A"] <= 512)
+    _check_ranges(tb, ranks, hdr["A"])
+
+
+def _check_ranges(tb, ranks, A):
+    """A rank's ranges: where its sorted pairs cross the partition bounds."""
     bounds = tb.bounds()
     first = (5 + tb.sizes.n_seg_compressed + 3) // 4 * 4
     for r in range(ranks):
-        got = tb._np(tb._rk_tensors[r]["cnt"], np.uint32)[first:first + hdr["A"] + 1]
+        got = tb._np(tb._rk_tensors[r]["cnt"], np.uint32)[first:first + A + 1]
         idx, _ = tb.rank_pairs(r)
         assert np.array_equal(got, np.searchsorted(idx, bounds))
 
