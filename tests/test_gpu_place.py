@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 _SC = {G.F32: 32 * 1024, G.BF16: 32 * 2048}
 
 
-def _check(what, segs, dtype, values, candidates=True):
+def _check(what, segs, dtype, values):
     print("\n[case] place %s" % (what,), flush=True)
     n = segs[-1].offset + segs[-1].length
     b = G.Bucket("place", dtype, 2, segs, n, 3000)
@@ -25,8 +25,7 @@ def _check(what, segs, dtype, values, candidates=True):
         tb.run(dev)
         torch.cuda.synchronize()
         compare_all(b, ores, tb)
-        if candidates:
-            assert all(tb.rank_counts(r)["dense_segments"] == 0 for r in range(2))
+        assert all(tb.rank_counts(r)["dense_segments"] == 0 for r in range(2))
 
 
 def _normal(r, n):
@@ -54,7 +53,7 @@ def test_windows_without_a_slot(dtype, first):
         empty = (torch.arange(n) // half) % 2 == (0 if first else 1)
         x[empty] *= 1e-3
         return x
-    _check(("windows", dtype, first), [G.Seg(0, n, 4_000, 1, "a")], dtype, values, candidates=False)
+    _check(("windows", dtype, first), [G.Seg(0, n, 4_000, 1, "a")], dtype, values)
 
 
 def test_more_segments_than_lanes():
@@ -63,4 +62,4 @@ def test_more_segments_than_lanes():
         n = 131_080 + 8 * i
         segs.append(G.Seg(off, n, 12_000 + 100 * i, 1, "s%d" % i))
         off += n
-    _check("segments", segs, G.BF16, _normal, candidates=False)
+    _check("segments", segs, G.BF16, _normal)
