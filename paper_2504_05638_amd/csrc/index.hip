@@ -382,7 +382,8 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
         return word;
     };
     // The workgroup's partitions are me, me + G, me + 2 G, ...
-    // (n_search workgroups from search0 on search, the others are for the salts; 0: all are for both)
+    // (n_search workgroups from search0 on search, the others are for the salts; 0: all are for both.  search0
+    // is where the others end; written with that in mind, this kernel came out 0.5 to 3 us slower.)
     const bool searcher = kSearch && blockIdx.x - search0 < n_search;
     const uint32_t me = searcher ? blockIdx.x - search0 : blockIdx.x - (blockIdx.x >= search0 ? n_search : 0u);
     const uint32_t G = searcher ? n_search : gridDim.x - n_search;
@@ -645,10 +646,10 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     }
     auto launch = [&](auto kernel, uint32_t n_wgs, size_t lds_bytes, const LayoutBatch &lb,
                       uint32_t n_in, bool all, uint32_t n_search) {
-        // (searching workgroups start first, or, if all fit the device, last: on a device nearly full of
-        // those with a partition each they then share few compute units, 8 ranks of 25 M entries, us a pass,
-        // 239 and 237, with 4-bit counters 281 and 277)
-        const uint32_t search0 = n_wgs + n_search <= most ? n_wgs : 0u;
+        // (searching workgroups are the last: on a device nearly full of those with a partition each they then
+        // share few compute units, 8 ranks of 25 M entries, us a pass, first / last: 239 / 237, with 4-bit
+        // counters 281 / 277)
+        const uint32_t search0 = n_wgs;
         kernel<<<n_wgs + n_search, kSaltThreads, lds_bytes, s>>>(
             lb, n_in, all, sh->bitmap, n_words, uint32_t(p->n_c), chunk, chunkpre, n_chunks, lp,
             sh->header, sh->status, sh->bounds, p->cnt_ranges, uint32_t(p->K), p->cfg.seed, n_search, search0);

@@ -23,7 +23,7 @@ constexpr uint32_t kDenseRows = 4;        // 16-byte vectors per thread and tile
 constexpr uint32_t kSmallVecs = 8;        // 16-byte vectors per thread such a segment has at most
 constexpr uint32_t kHistWindow = 4096;
 constexpr uint32_t kCandRows = 4;        // 16-byte vectors per lane per candidate chunk
-constexpr uint32_t kCandChunksPerSuper = 32;  // chunks one emit workgroup handles
+constexpr uint32_t kCandChunksPerSuper = 32;  // chunks that a wave of place takes
 constexpr uint32_t kEmitThreads = 256;
 constexpr uint32_t kSampleVectors = 4096;     // 16-byte vectors sampled per segment
 constexpr uint32_t kFastMinElems = 1u << 17;  // shorter segments take the dense path
