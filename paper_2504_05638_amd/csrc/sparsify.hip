@@ -1552,20 +1552,30 @@ __device__ inline void write_rank_counts(uint32_t *table, uint32_t L, uint32_t s
 
 // Candidate route, count.  How many of a super-chunk's slots are above and at the exact threshold does not
 // depend on their order, so LPC lanes read 4 LPC slots of a chunk at once, the first of all the wave's chunks are in
-// flight, every lane counts its own, and the wave sums once at the end.  Bound by the reads' latency where
-// chunks hold a few dozen slots (8 lanes to a chunk, two waves to a super-chunk), by their bytes where
-// they hold hundreds (MANY: 16 lanes, one wave).  us a pass, before (slots classified in order, a
-// thread's own run or 64 a step) / after: 2 ranks of 202 M entries with a tenth kept 1420 / 1402, one rank's part of
-// a 202 M bucket 188.9 / 185.6, 8 ranks of 7 M fp32 216.1 / 215.1, 8 of 25 M 236.3 / 235.2, 4 of 1 M 81.2 / 81.5.
-// (Dozens of slots with one wave to a super-chunk were slower than before: 8 ranks of 7 M 217 and 219, of 25 M 234
-// and 235.5.)
+// flight, every lane counts its own, and the wave sums once at the end.  Bound by the reads' latency (8 lanes to a
+// chunk, two waves to a super-chunk), or by their bytes where the slots lie in memory and not in the last cache
+// (MANY: 16 lanes, one wave; see count_from_memory).  us of the kernel, slots classified in order, a thread's own run
+// or 64 a step / this: 2 ranks of 202 M entries with a tenth kept 84 / 55, 16 of 202 M 74 / 64, one rank's part of
+// those 11.9 / 7.8, 1 rank of 4 M with a fifth 63 / 20.6.
 constexpr uint32_t count_items(bool many)  // super-chunks of a workgroup
 {
     return kEmitThreads / (many ? 64 : 128);
 }
 
+// Whether count reads the slots of n ranks from memory: chunks that hold hundreds, and more of them all than the
+// last cache (256 MiB) keeps from the scan.  us of count, from memory / not: 2 ranks of 200 M entries with 12, 15, 20, 23
+// percent kept (250, 312, 416, 478 MB) 63 / 70, 74 / 79, 115 / 128, 143 / 153; of 100 M with 20, 23 (208, 239 MB)
+// 58 / 42, 80 / 56, 1 of 4 M with 8, 23 percent 18.5 / 11.5, 40 / 23; fp32, two words a slot, 2 of 100 M with 12, 20
+// percent (250, 416 MB) 31.7 / 27.5, 40.4 / 42.5.  (Dozens of slots in 193 MB, 16 of 202 M entries: 75 / 64.)
+inline bool count_from_memory(const tagc_plan_t *p, uint32_t n)
+{
+    // (a chunk's pre-threshold lets 1.3 times the kept entries through)
+    const double bytes = 1.3 * double(p->K - p->dense_pairs) * n * (p->cfg.dtype == kF32 ? 8 : 4);
+    return p->cand_cap >= kManyCandCap && bytes > 244e6;
+}
+
 template <int DTYPE, bool MANY>
-__device__ __forceinline__ void count_body(uint32_t bid, uint32_t nb, const uint32_t *__restrict__ table,
+__device__ __forceinline__ void count_body(uint32_t bid, const uint32_t *__restrict__ table,
                                            const WsLayout &wl, const SelDev *__restrict__ sel,
                                            const uint32_t *__restrict__ cand,
                                            const uint2 *__restrict__ chunk_info, uint32_t CAP, uint64_t *sc_cnt)
@@ -1594,76 +1604,74 @@ __device__ __forceinline__ void count_body(uint32_t bid, uint32_t nb, const uint
             t_T = ea.x; t_quota = ea.y; t_cnt = ea.w; t_route = eb.w;  // T, quota, cnt, route
         }
     }
-    for (uint32_t base = bid * ITEMS; base < total_sc; base += nb * ITEMS) {  // uniform
-        const bool item = base + wave / WPS < total_sc;
-        const uint32_t sc = item ? base + wave / WPS : base;
-        const uint32_t ch0 = (wave % WPS) * NCH + lane / LPC;
-        // count and first slot of the lane's chunks (only meaningful for a chunk the scan has seen)
-        uint2 info[STEPS];
+    const uint32_t base = bid * ITEMS;  // (some of the last workgroup's items may be none)
+    const bool item = base + wave / WPS < total_sc;
+    const uint32_t sc = item ? base + wave / WPS : base;
+    const uint32_t ch0 = (wave % WPS) * NCH + lane / LPC;
+    // count and first slot of the lane's chunks (only meaningful for a chunk the scan has seen)
+    uint2 info[STEPS];
 #pragma unroll
-        for (uint32_t j = 0; j < STEPS; ++j) info[j] = chunk_info[sc * kCandChunksPerSuper + ch0 + j * (64 / LPC)];
-        uint32_t n_seg, sc_first, T, quota, se_cnt, se_route;
-        if (L <= 64) {
-            const uint32_t l = uint32_t(__popcll(__ballot(t_start <= sc))) - 1u;  // segment 0 starts at 0
-            n_seg = __builtin_amdgcn_readlane(t_n, l);
-            sc_first = __builtin_amdgcn_readlane(t_start, l);
-            T = __builtin_amdgcn_readlane(t_T, l);
-            quota = __builtin_amdgcn_readlane(t_quota, l);
-            se_cnt = __builtin_amdgcn_readlane(t_cnt, l);
-            se_route = __builtin_amdgcn_readlane(t_route, l);
-        } else {
-            const uint32_t l = segment_of(L, sc, [&](uint32_t i) { return segs[i].sc_start; });
-            const SegDev sd = segs[l];
-            SelDev se{};
-            if (sd.k != 0 && sd.n != 0) se = sel[l];
-            n_seg = sd.n; sc_first = sd.sc_start;
-            T = se.T; quota = se.quota; se_cnt = se.cnt; se_route = se.route;
-        }
-        const uint32_t sc_rel0 = (sc - sc_first) * (CHUNK * kCandChunksPerSuper), own = 4 * (lane % LPC);
-        uint32_t c[STEPS];   // slots of this lane's chunk of the step, from the lane's own first on
-        uint32_t at[STEPS];  // where that lies
+    for (uint32_t j = 0; j < STEPS; ++j) info[j] = chunk_info[sc * kCandChunksPerSuper + ch0 + j * (64 / LPC)];
+    uint32_t n_seg, sc_first, T, quota, se_cnt, se_route;
+    if (L <= 64) {
+        const uint32_t l = uint32_t(__popcll(__ballot(t_start <= sc))) - 1u;  // segment 0 starts at 0
+        n_seg = __builtin_amdgcn_readlane(t_n, l);
+        sc_first = __builtin_amdgcn_readlane(t_start, l);
+        T = __builtin_amdgcn_readlane(t_T, l);
+        quota = __builtin_amdgcn_readlane(t_quota, l);
+        se_cnt = __builtin_amdgcn_readlane(t_cnt, l);
+        se_route = __builtin_amdgcn_readlane(t_route, l);
+    } else {
+        const uint32_t l = segment_of(L, sc, [&](uint32_t i) { return segs[i].sc_start; });
+        const SegDev sd = segs[l];
+        SelDev se{};
+        if (sd.k != 0 && sd.n != 0) se = sel[l];
+        n_seg = sd.n; sc_first = sd.sc_start;
+        T = se.T; quota = se.quota; se_cnt = se.cnt; se_route = se.route;
+    }
+    const uint32_t sc_rel0 = (sc - sc_first) * (CHUNK * kCandChunksPerSuper), own = 4 * (lane % LPC);
+    uint32_t c[STEPS];   // slots of this lane's chunk of the step, from the lane's own first on
+    uint32_t at[STEPS];  // where that lies
+#pragma unroll
+    for (uint32_t j = 0; j < STEPS; ++j) {
+        // (the bounds keep the reads inside `cand` whatever an unseen chunk's record holds)
+        const uint32_t rel0 = sc_rel0 + (ch0 + j * (64 / LPC)) * CHUNK;
+        const uint32_t n = !se_route && se_cnt != 0 && rel0 < n_seg ? min(info[j].x, CAP) : 0u;
+        c[j] = n > own ? n - own : 0u;
+        at[j] = (min(info[j].y, uint32_t(wl.n_slots) - CAP) & ~3u) + own;
+    }
+    uint32_t n_gt = 0, n_eq = 0;
+    bool more = true;
+    while (more) {
+        uint4 q[STEPS];
+#pragma unroll
+        for (uint32_t j = 0; j < STEPS; ++j)  // (a chunk's slots start on, and have room up to, 16 bytes)
+            q[j] = c[j] ? *reinterpret_cast<const uint4 *>(cand + at[j]) : make_uint4(0, 0, 0, 0);
+        uint32_t left = 0;
 #pragma unroll
         for (uint32_t j = 0; j < STEPS; ++j) {
-            // (the bounds keep the reads inside `cand` whatever an unseen chunk's record holds)
-            const uint32_t rel0 = sc_rel0 + (ch0 + j * (64 / LPC)) * CHUNK;
-            const uint32_t n = !se_route && se_cnt != 0 && rel0 < n_seg ? min(info[j].x, CAP) : 0u;
-            c[j] = n > own ? n - own : 0u;
-            at[j] = (min(info[j].y, uint32_t(wl.n_slots) - CAP) & ~3u) + own;
-        }
-        uint32_t n_gt = 0, n_eq = 0;
-        bool more = true;
-        while (more) {
-            uint4 q[STEPS];
+            const uint32_t v[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
 #pragma unroll
-            for (uint32_t j = 0; j < STEPS; ++j)  // (a chunk's slots start on, and have room up to, 16 bytes)
-                q[j] = c[j] ? *reinterpret_cast<const uint4 *>(cand + at[j]) : make_uint4(0, 0, 0, 0);
-            uint32_t left = 0;
-#pragma unroll
-            for (uint32_t j = 0; j < STEPS; ++j) {
-                const uint32_t v[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
-#pragma unroll
-                for (uint32_t i = 0; i < 4; ++i) {
-                    const uint32_t key = (DTYPE == kBF16 ? v[i] & 0xFFFF0000u : v[i]) & 0x7FFFFFFFu;
-                    n_gt += i < c[j] && key > T;
-                    n_eq += i < c[j] && key == T;
-                }
-                c[j] = c[j] > 4 * LPC ? c[j] - 4 * LPC : 0u;
-                at[j] += 4 * LPC;
-                left |= c[j];
+            for (uint32_t i = 0; i < 4; ++i) {
+                const uint32_t key = (DTYPE == kBF16 ? v[i] & 0xFFFF0000u : v[i]) & 0x7FFFFFFFu;
+                n_gt += i < c[j] && key > T;
+                n_eq += i < c[j] && key == T;
             }
-            more = __ballot(left != 0) != 0;
+            c[j] = c[j] > 4 * LPC ? c[j] - 4 * LPC : 0u;
+            at[j] += 4 * LPC;
+            left |= c[j];
         }
-        n_gt = __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(n_gt), 63);
-        n_eq = __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(n_eq), 63);
-        uint64_t sum = (uint64_t(n_gt) << 31) | uint64_t(quota ? n_eq : 0u);
-        if (WPS > 1) {
-            if (lane == 0) s_n[wave] = sum;
-            __syncthreads();
-            sum = s_n[wave & ~1u] + s_n[wave | 1u];
-            __syncthreads();  // (the next item's)
-        }
-        if (item && lane == 0 && wave % WPS == 0) sc_cnt[sc] = sum;
+        more = __ballot(left != 0) != 0;
     }
+    n_gt = __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(n_gt), 63);
+    n_eq = __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(n_eq), 63);
+    uint64_t sum = (uint64_t(n_gt) << 31) | uint64_t(quota ? n_eq : 0u);
+    if (WPS > 1) {
+        if (lane == 0) s_n[wave] = sum;
+        __syncthreads();
+        sum = s_n[wave & ~1u] + s_n[wave | 1u];
+    }
+    if (item && lane == 0 && wave % WPS == 0) sc_cnt[sc] = sum;
 }
 
 // Candidate route, place.  A wave takes a whole super-chunk, classifies its slots against the exact threshold,
@@ -2154,7 +2162,7 @@ count_kernel(const SparsifyBatch, uint32_t n_emit, uint32_t plan_tiles,
     const RankView rv = rank_view();
     const SelDev *sel = rv.at<SelDev>(wl.sel);
     if (blockIdx.x < n_emit) {
-        count_body<DTYPE, MANY>(blockIdx.x, n_emit, table, wl, sel, rv.at<uint32_t>(wl.cand),
+        count_body<DTYPE, MANY>(blockIdx.x, table, wl, sel, rv.at<uint32_t>(wl.cand),
                                 rv.at<uint2>(wl.chunk_info), CAP, rv.at<uint64_t>(wl.sc_cnt));
     } else
         compact_body<DTYPE, COMPACT_ROWS, false, false>(
@@ -2393,16 +2401,16 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
     }
     {
         // the plan fixed the compaction tile's height, and with it which kernels these are
-        // (and, for count, whether chunks hold dozens or hundreds of candidates)
         const bool rows4 = p->compact_rows == 4;
-        const bool many = p->cand_cap >= kManyCandCap;
+        const bool many = count_from_memory(p, n);
         auto count = many ? (rows4 ? count_kernel<DTYPE, 4, true> : count_kernel<DTYPE, 2, true>)
                           : (rows4 ? count_kernel<DTYPE, 4, false> : count_kernel<DTYPE, 2, false>);
         // place stages the dense route's tiles where most pairs can come from them.  Beside large
         // candidate-route segments a short one of the dense route would have every workgroup hold
-        // 33 KiB of LDS and 108 registers for it instead of 1 KiB and 76 (4 ranks of 202 M entries
-        // and 5 thousand: place 62 us staged, 55 not; 25 M and 9 M of which two fifths are kept:
-        // 71 and 92; 25 M and 1 M: 26 and 25).
+        // 33 KiB of LDS and 107 registers for it instead of 20 KiB and 75 (us of place, staged / not, 4 ranks
+        // of 202 M entries and 5 thousand 49.3 / 44.0; of 25 M and 9 M of which two fifths are kept 58 / 86,
+        // of 25 M and 1 M 18.4 / 22.5, of 100 M and 3 M 43.5 / 52; the line could lie a little lower: of
+        // 100 M and 1 M 32.2 / 34.7; one rank, or fp32: the same way by less).
         const bool staged = rows4 && 2 * p->dense_pairs > p->K;
         auto place = staged ? place_kernel<DTYPE, 4, true>
                      : rows4 ? place_kernel<DTYPE, 4, false> : place_kernel<DTYPE, 2, false>;

@@ -63,3 +63,33 @@ def test_more_segments_than_lanes():
         segs.append(G.Seg(off, n, 12_000 + 100 * i, 1, "s%d" % i))
         off += n
     _check("segments", segs, G.BF16, _normal)
+
+
+@pytest.mark.parametrize("dtype,n", [(G.BF16, 26_000_021), (G.F32, 13_000_013)])
+def test_counts_from_memory(dtype, n):
+    """16 ranks in one launch have more slots than the last cache holds, and count has a form of its own for
+    that; a rank at a time has not.  The same selections, whole and to the bit."""
+    from paper_2504_05638_amd.bucket import TagcBucket
+    ranks, ppm = 16, 150_000
+    print("\n[case] count from memory dtype=%d" % dtype, flush=True)
+    slots = 1.3 * ranks * (n * ppm // 10**6) * (8 if dtype == G.F32 else 4)
+    assert slots > 244e6 > slots / ranks
+    segs = [G.Seg(0, n, ppm, 1, "a")]
+    td = torch.float32 if dtype == G.F32 else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    grads = [torch.randn(n, generator=gen, device="cuda").to(td) for _ in range(ranks)]
+    apart = TagcBucket(segs, dtype, ranks, seed=3, ranks_together=1, dense=False)
+    whole = TagcBucket(segs, dtype, ranks, seed=3, ranks_together=ranks, dense=False)
+    assert len(whole.rank_ws) == ranks
+    for tb in (apart, whole):
+        tb.compress_index_all(grads)
+    torch.cuda.synchronize()
+    for r in range(ranks):
+        a, w = apart.rank_counts(r), whole.rank_counts(r)
+        assert a["dense_segments"] == w["dense_segments"] == 0 and a["total"] == n * ppm // 10**6
+        assert a == w
+        for name in ("idx", "val", "bitmap"):
+            used = 4 * a["total"] if name != "bitmap" else 4 * whole.sizes.bitmap_words
+            assert torch.equal(apart._rk_tensors[r][name][:used], whole._rk_tensors[r][name][:used]), (r, name)
+    apart.close()
+    whole.close()
