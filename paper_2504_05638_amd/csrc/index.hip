@@ -214,6 +214,7 @@ __device__ inline uint32_t lower_bound_by_16(const uint32_t *list, uint32_t n, u
 // with a tenth 133.5, 4 of 202 M 48.3, 47.2, since they are through last.)
 constexpr uint32_t kSaltThreads = 1024;
 constexpr uint32_t kLayoutBatch = kSaltThreads / 128;  // partitions whose bounds are found at once
+constexpr uint64_t kSearchApart = 2048;  // non-zeros of a partition from which on some workgroups only search
 constexpr uint64_t kSplitSearches = 32768;  // (partition, rank) pairs
 constexpr uint32_t kSaltLimit = 16;       // salts tried: 0 .. 15
 constexpr uint32_t kNoLink = 0xFFFFu;
@@ -627,12 +628,15 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     // with up to eight ranks, 96 with more (us of layout, 32 / 64 / 96 / 128 of them: 16 ranks of 202 M entries
     // 238 / 138 / 106 / 115, where all workgroups did both in 125; 12 ranks 155 / 93 / 86 / 93; 8 ranks 87 / 65 / 65 /
     // 71; 2 ranks with a tenth kept 159 / 123 / 133 / 143; 4 ranks 48 / 48 / 52 / 51; 16 ranks of 9 M with two fifths
-    // 98 / 64 / 51 / 54).  None where all workgroups have a partition each and the salts' alone would not: all of
-    // them do both then (8 ranks of 49 M entries, 464 partitions, 24.9).  A call may have as few under a plan for more,
+    // 98 / 64 / 51 / 54).  None, all of them do both, where all workgroups have a partition each and the salts'
+    // alone would not (8 ranks of 49 M entries, 464 partitions, 24.9).  A call may have as few under a plan for more,
     // when ranks share what they keep: two turns (480 partitions, 29.8; 28.7 if all did both, but for the
-    // kernel to ask how many there are cost all other calls 0.5 to 1).
+    // kernel to ask how many there are cost all other calls 0.5 to 1).  Nor where there are more partitions than
+    // workgroups, and small ones: the salts are the lesser part then (50 M entries, all do both / 64, or 96, apart: 4
+    // ranks with partitions of 40 non-zeros 291 / 405, 320 49 / 63, 640 32 / 39, 1280 25.6 / 25.5, 2560 23.3 / 21.6,
+    // 6400 25.9 / 23.8; 8 ranks with 640 56 / 66, 1280 38.8 / 40.5, 2560 30.0 / 27.7; 16 ranks 103 / 125, 69 / 73, 48 / 47).
     const uint32_t want = std::min(n_ranks > 8 ? 96u : 64u, batches);
-    const bool apart = p->A_cap + want <= most || p->A_cap > most;
+    const bool apart = p->A_cap + want <= most || (p->A_cap > most && p->U_cap >= kSearchApart * p->A_cap);
     const uint32_t searching = apart ? std::min(want, most / 2) : 0u;
     const uint32_t salting = uint32_t(std::min<uint64_t>(p->A_cap, most - searching));
     const auto layout = layout_kernel<true, true, true>, salts = layout_kernel<false, false, true>;

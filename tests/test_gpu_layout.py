@@ -32,16 +32,17 @@ def test_layout_and_ranges(n, keep_ppm, ranks, P, T, least):
     _check_ranges(tb, ranks, hdr["A"])
 
 
-# All workgroups do both, searches and salts: as many partitions as the device holds workgroups, nearly.  Apart: as many
-# under a plan for twice as many, which are two turns of the salts; more than eight ranks, which have more searchers.
-@pytest.mark.parametrize("keep_ppm,ranks,shared,P,T,cap,least", [
-    (15_000, 4, False, 512, 768, (456, 512), 456),
-    (30_000, 4, True, 512, 768, (513, 2000), 449),
-    (4_000, 16, False, 256, 384, (768, 2000), 768),
+# All workgroups do both, searches and salts: as many partitions as the device holds workgroups, nearly; many small
+# ones.  Apart: nearly as many as the device holds under a plan for twice as many, which are two turns of the salts; more
+# than eight ranks, which have more searchers.
+@pytest.mark.parametrize("n,keep_ppm,ranks,shared,P,T,cap,least,most", [
+    (4_000_000, 15_000, 4, False, 512, 768, (456, 512), 456, 512),
+    (4_000_000, 4_000, 16, False, 256, 384, (1024, 2000), 1000, 2000),
+    (8_000_000, 77_500, 4, True, 2500, 4002, (513, 2000), 449, 512),
+    (8_000_000, 16_000, 16, False, 2500, 4002, (768, 2000), 700, 2000),
 ])
-def test_who_searches(keep_ppm, ranks, shared, P, T, cap, least):
+def test_who_searches(n, keep_ppm, ranks, shared, P, T, cap, least, most):
     print("\n[case] who searches, ranks=%d P=%d ppm=%d" % (ranks, P, keep_ppm), flush=True)
-    n = 4_000_000
     b = G.Bucket("layout", G.F32, ranks, [G.Seg(0, n, keep_ppm, 1, "w")], n, 1600)
     grads = _ints(n, ranks, 11)
     if shared:
@@ -50,7 +51,8 @@ def test_who_searches(keep_ppm, ranks, shared, P, T, cap, least):
     assert torch.cuda.get_device_properties(0).multi_processor_count == 256  # (two workgroups each)
     assert cap[0] <= tb.sizes.partition_capacity <= cap[1]
     hdr, _ = compare_all(b, ores, tb, exact_values=True)
-    assert least <= hdr["A"] and (not shared or hdr["A"] <= 512)
+    assert least <= hdr["A"] <= most
+    assert (tb.sizes.union_capacity >= 2048 * tb.sizes.partition_capacity) == (P == 2500)  # the line between them
     _check_ranges(tb, ranks, hdr["A"])
 
 
