@@ -617,9 +617,9 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     // are in flight: three launches.  In the one launch the workgroups that wait for the searches'
     // loads hold a compute unit's local memory, and no other bucket's salts run meanwhile; and 16
     // lanes to a search read more than a thread's binary search does.  16 ranks of 202 M entries,
-    // 58 thousand searches: 12 buckets in flight 210 us each in one launch (with the merge), 177 in
-    // three.  Alone, one launch is the better for what follows: 222 and 210 us, but it leaves the
-    // pair lists in the cache for the encoder (593 us, 622 after three launches).
+    // 58 thousand searches: 12 buckets in flight 190 us each in one launch (with the merge), 153 in
+    // three.  Alone one launch is the better, 105 and 113 us (without the merge), and it leaves the
+    // pair lists in the cache for the encoder (570 us, 582 after three launches).
     const bool split = p->cfg.decode_workgroups && p->A_cap * n_ranks > kSplitSearches;
     const uint32_t batches = uint32_t(std::min<uint64_t>((p->A_cap + kLayoutBatch - 1) / kLayoutBatch,
                                                          uint64_t(device_cu_count()) * 2));

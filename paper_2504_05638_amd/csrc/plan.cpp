@@ -52,10 +52,11 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
     p->any_nonfast = false;
 
     // Candidate route: slots per chunk for 1.3 x the kept fraction plus six standard
-    // deviations.  What follows the scan costs in proportion to the candidates; it beats the dense route's three reads of the
-    // gradient up to Table 1's 2x regime (a fifth kept: 26 % of a chunk expected as
-    // candidates; measured on 7B-shaped buckets).  Returns the slots a chunk needs, 0 = dense
-    // route.
+    // deviations.  What follows the scan costs in proportion to the candidates; it beats the dense route's three
+    // reads of the gradient up to a fifth kept or so (a pass in us, dense / candidate: one rank of 50 M bf16 entries
+    // with 15, 20, 23 % kept 330 / 318, 357 / 373, 375 / 409, four ranks with 20, 23, 26 % 880 / 875, 916 / 933,
+    // 945 / 1012; fp32, one rank of 25 M 263 / 234, 279 / 274, 288 / 298, four 649 / 608, 657 / 638, 686 / 711: the
+    // line, at 23 %, is a little high for bf16).  Returns the slots a chunk needs, 0 = dense route.
     auto fast_slots = [&](const tagc_segment &s) -> uint32_t {
         const uint64_t k = uint64_t((unsigned __int128)s.length * s.keep_ppm / 1000000u);
         if (s.offset % p->vec_elems || s.length < kFastMinElems || k < kFastMinKeep) return 0;

@@ -1690,11 +1690,11 @@ __device__ __forceinline__ void count_body(uint32_t bid, const uint32_t *__restr
 // LDS (all of it would leave room for fewer workgroups) and written whole, zeros included.  (Tried: a quarter, 12 KiB
 // a workgroup instead of 20: 2 ranks of 202 M entries with a tenth kept 1382 -> 1399, no less with other buckets in flight.)
 //
-// us a pass, before / after.  Before, chunks of dozens of slots had four threads each and 23 KiB of LDS a
-// workgroup: 8 ranks of 67 M entries 467.4 / 449.7, of 25 M 235.7 / 230.5, of 7 M fp32 214.8 / 211.9, 4 of 1 M fp32
-// 81.5 / 81.7.  Chunks of hundreds, and large buckets, had 64 slots of one chunk to a step, 32 or more
-// steps a super-chunk, and stored survivors as found: 16 ranks of 202 M 3018 / 2970, 2 of them with a tenth kept
-// 1398 / 1382, one rank's part of a 202 M bucket 186.3 / 178.3.
+// us of the kernel, before / after.  Before, chunks of dozens of slots had four threads each and 23 KiB of LDS a
+// workgroup: 8 ranks of 67 M entries 47.8 / 30.4, of 25 M 22.5 / 18.9, of 7 M fp32 22.1 / 18.7, 4 of 1 M fp32
+// 9.6 / 9.9.  Chunks of hundreds, and large buckets, had 64 slots of one chunk to a step, 32 or more
+// steps a super-chunk, and stored survivors as found: 16 ranks of 202 M 227 / 182, 2 of them with a tenth kept
+// 162 / 149, one rank's part of a 202 M bucket 23.4 / 17.8.
 constexpr uint32_t kEmitWindow = kCandChunksPerSuper / 2;  // chunks whose Index words are collected at a time
 template <int DTYPE>
 struct EmitLds {

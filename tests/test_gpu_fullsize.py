@@ -267,8 +267,7 @@ def test_config4_sharded_7b_bucket():
                           (100_000, 3000, 3, True)])
 def test_config3_heavy_tails_shared_supports(keep_ppm, lf, offset, dense_route):
     """64 M Student-t entries per rank, half of every rank's support shared with all others.
-    At 10 % kept a chunk holds hundreds of candidates (count and place with a wave per
-    super-chunk); the same from an offset that is no multiple of a 16-byte vector, which
+    At 10 % kept a chunk holds hundreds of candidates; the same from an offset that is no multiple of a 16-byte vector, which
     the plan sends down the route that reads the gradient three times."""
     print("\n[case] config3 at full size keep=%d lf=%d offset=%d" % (keep_ppm, lf, offset),
           flush=True)

@@ -501,8 +501,7 @@ def test_more_than_64_candidate_route_segments(keep_lo, keep_hi):
     """70 segments that all take the candidate route (the final kernel reads the segment
     tables lane-parallel for up to 64 segments and falls back to a search beyond), with
     ragged lengths so that super-chunks end inside chunks, and varying keep ratios: a few
-    per cent (dozens of candidates per chunk) and Table 1's dense regimes (hundreds: the
-    last two kernels then give a wave to every super-chunk)."""
+    per cent (dozens of candidates per chunk) and Table 1's dense regimes (hundreds)."""
     _announce("70 fast segments, keep %d-%d ppm" % (keep_lo, keep_hi))
     rng = np.random.default_rng(5)
     segs, sigma, off = [], {}, 0
@@ -526,8 +525,7 @@ def test_more_than_64_candidate_route_segments(keep_lo, keep_hi):
 def test_hundreds_of_candidates_per_chunk(dtype, keep_ppm):
     """Table 1's dense regimes on the candidate route: a twentieth, a tenth and a fifth of
     the entries kept, so that a 4 KiB chunk holds hundreds of candidates (slots staged per
-    wave at the lower two ratios, written in place at the highest; count and place with a
-    wave per super-chunk).  Several super-chunks per segment, a ragged tail, one segment
+    wave at the lower two ratios, written in place at the highest).  Several super-chunks per segment, a ragged tail, one segment
     of small integers (a tie class at the threshold that spans chunks and super-chunks, so
     the quota of ties runs out in the middle of a read), two segments that keep one entry
     in a hundred among them (a few dozen candidates per chunk, one read per chunk; one of
