@@ -205,8 +205,7 @@ __device__ inline uint32_t lower_bound_by_16(const uint32_t *list, uint32_t n, u
 // steps (83 K with 16 ranks of 202 M entries) in which its compute unit hashed nothing.  So some
 // workgroups of the launch find the ends in the pair lists, beside the others' salts (us of this kernel, before /
 // after: 16 ranks of 202 M entries 125 / 105, one of them with three others' Indexes 52 / 47, 8 ranks of 67 M 27 / 24,
-// of 25 M 24.2 / 21.6, of 7 M 20.4 / 18.0, 4 of 1 M 17.0 / 15.0, 3 of 36 thousand 14.3 / 13.0; 2 of 202 M with a
-// tenth kept 124.5 / 122.7).  (Tried: a step of the searches between the steps of the salts, whose waits are
+// of 25 M 24.2 / 21.6, of 7 M 20.4 / 18.0, 4 of 1 M 17.0 / 15.0, 3 of 36 thousand 14.3 / 13.0).  (Tried: a step of the searches between the steps of the salts, whose waits are
 // longer than those steps, half as much or nothing; the chunk counts kept in LDS for the bounds, nothing; 256
 // parts a step and half the steps in small launches, 3 us slower, bound by the lines; words beyond the first
 // four requested ahead, 0 to 6 % slower; two searches of a wave at once, 16 ranks of 202 M 141 where one was 135, 8 of
@@ -627,7 +626,7 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     // ...  The searches of a partition grow with the ranks, its salt does not: 64 are done before the salts
     // with up to eight ranks, 96 with more (us of layout, 32 / 64 / 96 / 128 of them: 16 ranks of 202 M entries
     // 238 / 138 / 106 / 115, where all workgroups did both in 125; 12 ranks 155 / 93 / 86 / 93; 8 ranks 87 / 65 / 65 /
-    // 71; 2 ranks with a tenth kept 159 / 123 / 133 / 143; 4 ranks 48 / 48 / 52 / 51; 16 ranks of 9 M with two fifths
+    // 71; 4 ranks 48 / 48 / 52 / 51; 16 ranks of 9 M with two fifths
     // 98 / 64 / 51 / 54).  None, all of them do both, where all workgroups have a partition each and the salts'
     // alone would not (8 ranks of 49 M entries, 464 partitions, 24.9).  A call may have as few under a plan for more,
     // when ranks share what they keep: two turns (480 partitions, 29.8; 28.7 if all did both, but for the
@@ -635,8 +634,15 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     // workgroups, and small ones: the salts are the lesser part then (50 M entries, all do both / 64, or 96, apart: 4
     // ranks with partitions of 40 non-zeros 291 / 405, 320 49 / 63, 640 32 / 39, 1280 25.6 / 25.5, 2560 23.3 / 21.6,
     // 6400 25.9 / 23.8; 8 ranks with 640 56 / 66, 1280 38.8 / 40.5, 2560 30.0 / 27.7; 16 ranks 103 / 125, 69 / 73, 48 / 47).
+    // Nor where there are few ranks and many partitions of the default size, whose searches are little beside the
+    // salts that 64 workgroups less look for (both / apart: 1 rank, 2000, 3000, 4900 partitions 60 / 60, 81 / 85,
+    // 124 / 127; 2 ranks, 2000, 3000, 4640, 8800 60 / 61, 82 / 86, 119 / 124, 198 / 212; 4 ranks, 1900, 2300, 2400, 3200,
+    // 4200, 7200 68.5 / 64, 65 / 68, 58.5 / 55.5, 85 / 87, 102 / 107, 169 / 174; 5 ranks, 3200, 5000 87 / 87, 121 / 121;
+    // 6 ranks, 2900 82 / 75).
     const uint32_t want = std::min(n_ranks > 8 ? 96u : 64u, batches);
-    const bool apart = p->A_cap + want <= most || (p->A_cap > most && p->U_cap >= kSearchApart * p->A_cap);
+    const bool apart = p->A_cap + want <= most ||
+                       (p->A_cap > most && p->U_cap >= kSearchApart * p->A_cap &&
+                        (n_ranks > 4 || p->A_cap <= 5 * uint64_t(most)));
     const uint32_t searching = apart ? std::min(want, most / 2) : 0u;
     const uint32_t salting = uint32_t(std::min<uint64_t>(p->A_cap, most - searching));
     const auto layout = layout_kernel<true, true, true>, salts = layout_kernel<false, false, true>;
