@@ -293,15 +293,17 @@ __device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t 
 // and their degrees (counted down on the way) -> the new values, and claims for the next queue ->
 // queue.  Every link goes out for all cells together.  The values are swapped right behind
 // their reading: cells are shared by unknowns that leave in the same round (in nearly every round of a
-// wave), and a swap that finds another value has to be made again, that one alone: made again together
-// with one that had succeeded it took three tries, at some 200 clocks each.  A wave with one entry
-// takes 1100 clocks for it, one with 64 1700 (two more tries), 16 full ones 2100 and a barrier 400: latency and the
-// wave's own 130 instructions (fewer vector instructions, 87 for 110, changed nothing).  Rounds of a
-// partition, clocks, before the arrays were as in PartLds and failed swaps repeated alone, and after: 8192
-// unknowns in 12288 cells (11 rounds) 38.8 K -> 32.0 K; in 10776 cells (21 rounds) 51.1 K -> 43.3 K; decoders of
-// the latter, 2 ranks of 202 M entries, 647 -> 586 us.  (A queue for every wave, without a shared count:
-// 826 us, every wave then has a few entries of every small round.)
-template <bool kPacked, typename Room>
+// wave), and what a swap found changed is left to the native add: made again, once or twice at some 200 clocks, it held
+// up the whole wave (decoders of 2 ranks of 202 M entries with a tenth kept 647 -> 612 us, of 4 ranks of 9 M with two
+// fifths 108 -> 104.5).  A wave that is alone with a round (kAlone: 64 entries at most) adds natively at once: a
+// partition that gets stuck after 40 rounds, most of them such, 35.7 -> 34.1.  (In all rounds: sixteen waves' adds
+// take 49 clocks each, a swap is not felt.)  A wave with one entry takes 1100 clocks for it, 16 full ones 2100 and a barrier
+// 400, before that change: latency and the wave's own 130 instructions (fewer vector instructions, 87
+// for 110, changed nothing).  Rounds of a partition, clocks, before the arrays were as in PartLds and failed swaps
+// repeated alone, and after: 8192 unknowns in 12288 cells (11 rounds) 38.8 K -> 32.0 K; in 10776 cells (21
+// rounds) 51.1 K -> 43.3 K.  (A queue for every wave, without a shared count: 826 us where 647 were, every wave then
+// has a few entries of every small round.)
+template <bool kAlone, bool kPacked, typename Room>
 __device__ __forceinline__ uint32_t resolve_unknown(const PartLds<kPacked> &p, uint32_t entry, Room &&room)
 {
     constexpr int kScope = __HIP_MEMORY_SCOPE_WORKGROUP;
@@ -316,15 +318,24 @@ __device__ __forceinline__ uint32_t resolve_unknown(const PartLds<kPacked> &p, u
     const uint32_t now0 = __hip_atomic_fetch_sub(p.meta(c0), dec, __ATOMIC_RELAXED, kScope) - dec;
     const uint32_t now1 = __hip_atomic_fetch_sub(p.meta(c1), dec, __ATOMIC_RELAXED, kScope) - dec;
     uint32_t x = __hip_atomic_load(p.value(own), __ATOMIC_RELAXED, kScope);
-    uint32_t v0 = __hip_atomic_load(p.value(c0), __ATOMIC_RELAXED, kScope);
-    uint32_t v1 = __hip_atomic_load(p.value(c1), __ATOMIC_RELAXED, kScope);
+    uint32_t v0 = 0, v1 = 0;
+    if (!kAlone) {
+        v0 = __hip_atomic_load(p.value(c0), __ATOMIC_RELAXED, kScope);
+        v1 = __hip_atomic_load(p.value(c1), __ATOMIC_RELAXED, kScope);
+    }
     __builtin_amdgcn_sched_barrier(0);  // (all five on their way before anything waits for one)
     const uint32_t n0 = cl.neg << 27, n1 = cl.neg << 26, n2 = cl.neg << 25;  // the signs in bit 31
     x ^= (j0 ? n0 : (j2 ? n2 : n1)) & kSign;
     const uint32_t t0 = x ^ ((j0 ? n1 : n0) & kSign), t1 = x ^ ((j2 ? n1 : n2) & kSign);
     auto minus = [](uint32_t v, uint32_t t) { return __float_as_uint(__uint_as_float(v) - __uint_as_float(t)); };
-    uint32_t r0 = atomicCAS(p.value(c0), v0, minus(v0, t0));
-    uint32_t r1 = atomicCAS(p.value(c1), v1, minus(v1, t1));
+    uint32_t r0 = 0, r1 = 0;
+    if (kAlone) {
+        lds_native_add(p.value(c0), t0 ^ kSign);
+        lds_native_add(p.value(c1), t1 ^ kSign);
+    } else {
+        r0 = atomicCAS(p.value(c0), v0, minus(v0, t0));
+        r1 = atomicCAS(p.value(c1), v1, minus(v1, t1));
+    }
     *p.word(u) = x;
     // Cells that came down to one unknown: its number is what is left of their sum.  It is claimed
     // in the order of the sub-tables: of two cells that it is left alone in now, it is read from
@@ -346,16 +357,10 @@ __device__ __forceinline__ uint32_t resolve_unknown(const PartLds<kPacked> &p, u
         if (push0) *p.queue(to + lanes_below(b0)) = uint16_t(left0 | (j0 ? kOne : 0u));
         if (push1) *p.queue(to + q0 + lanes_below(b1)) = uint16_t(left1 | (j2 ? kOne : 2 * kOne));
     }
-    // Swaps that found another value are made again, one a time: a lane rarely has two.
-    while ((r0 != v0) | (r1 != v1)) {
-        const bool first = r0 != v0;
-        const uint32_t v = first ? r0 : r1;
-        const uint32_t r = atomicCAS(p.value(first ? c0 : c1), v, minus(v, first ? t0 : t1));
-        v0 = first ? v : v0;
-        r0 = first ? r : r0;
-        v1 = first ? v1 : v;
-        r1 = first ? r1 : r;
-    }
+    // Where a swap found another value the native add does it, which nobody waits for: it takes three clocks a
+    // lane, but these are few.
+    if (r0 != v0) lds_native_add(p.value(c0), t0 ^ kSign);
+    if (r1 != v1) lds_native_add(p.value(c1), t1 ^ kSign);
     return q0 + q1;
 }
 
@@ -391,7 +396,7 @@ __device__ __forceinline__ uint32_t peel_rounds(const PartLds<kPacked> &p, uint3
                 do {
                     uint32_t queued = 0;
                     if (lane < n)
-                        queued = resolve_unknown(p, *p.queue(h + lane), [&](uint32_t) { return h + n; });
+                        queued = resolve_unknown<true>(p, *p.queue(h + lane), [&](uint32_t) { return h + n; });
                     h += n;
                     n = uniform(queued);  // (lane 0 had an entry)
                     ++rounds;
@@ -415,7 +420,7 @@ __device__ __forceinline__ uint32_t peel_rounds(const PartLds<kPacked> &p, uint3
         if (tid == 0) *p.n_queued(spare) = 0;  // read in the round before, added to again in the next
         const uint32_t tail = head + n;
         for (uint32_t e = head + tid; e < tail; e += NT)
-            resolve_unknown(p, *p.queue(e),
+            resolve_unknown<false>(p, *p.queue(e),
                             [&](uint32_t more) { return tail + take_slots(p.n_queued(next), more); });
         head = tail;
         const uint32_t was = now;
@@ -761,10 +766,13 @@ __device__ __forceinline__ void write_dense(const PartLds<true> &p, uint32_t tid
 // kCellPre / kIdxPre: cells / unknowns per thread the instantiation can hold.
 // kRanks: the cells are summed over the n_in <= kRanks ranks here, in rank order, the ranks' cells of
 // the next partition staying in the registers they are loaded to until it is staged.
-// kLoop: over any number of ranks, added up as they come.  For grids that have a workgroup for
+// kLoop: over any number of ranks, or the summed sketch, added up as they come.  For grids that have a workgroup for
 // every partition: there is no next partition whose sum could run beside the rounds, as
 // sum_peel_kernel has it (236 partitions of 8 ranks: 42 us, 48 in that kernel; 20 of 8: 24, 28; 218 of 16:
-// 56, 60).
+// 56, 60).  Nor is there one before, whose rounds its cells could travel behind: the Index words are requested first
+// and the unknowns enumerated, joined and looked through for the first queue, none of which needs a value, while the
+// cells travel (8 ranks of 25 M entries 40.4 -> 38.0, 3 of 36 thousand, one partition, 18.6 -> 15.9, 4 of 1 M 20.8 ->
+// 17.9, a summed sketch in 236 partitions 32.0 -> 29.4).
 constexpr uint32_t kIndexPre = 6;  // groups of Index words a wave requests ahead
 constexpr uint32_t kHeldRanks = 4;  // kRanks of the form for few ranks
 constexpr uint32_t kListGroups = 256;  // groups of Index words per partition beyond which its unknowns are listed first
@@ -825,20 +833,20 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
         for (uint32_t i = 0; i < kRanks; ++i)
             if (i < n_in) request_cells(pre_cell[i], i, tile);
     };
-    auto request_rest = [&](uint64_t tile) {
-        if (!kLoop) return;
-        for (uint32_t r = kRanks; r < n_in; r += kRanks - 1) {
-            __builtin_amdgcn_sched_barrier(0);
-            add_cells(1, kRanks);
-            __builtin_amdgcn_sched_barrier(0);
+    // (kLoop) adds up the ranks requested, and requests those from r on
+    auto request_more = [&](uint32_t r, uint64_t tile) {
+        __builtin_amdgcn_sched_barrier(0);
+        add_cells(1, kRanks);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (uint32_t i = 1; i < kRanks; ++i)
-                if (r + i - 1 < n_in) request_cells(pre_cell[i], r + i - 1, tile);
-                else
+        for (uint32_t i = 1; i < kRanks; ++i)
+            if (r + i - 1 < n_in) request_cells(pre_cell[i], r + i - 1, tile);
+            else
 #pragma unroll
-                    for (uint32_t q = 0; q < kCellPre; ++q) pre_cell[i][q] = -0.0f;  // (x + -0 is x)
-        }
+                for (uint32_t q = 0; q < kCellPre; ++q) pre_cell[i][q] = -0.0f;  // (x + -0 is x)
+        __builtin_amdgcn_sched_barrier(0);
     };
+    constexpr uint32_t kMore = kRanks - 1;  // ranks of a step of it
     Partitions at(U, A, blockIdx.x, gridDim.x);
     uint32_t sa = 0;
     // the partition `at` is at; `ahead` holds what is needed for it, and then that of the one after it
@@ -847,10 +855,15 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
         request_unknowns(at);
         ahead.request(index, salt, at.a + at.step, A);
     };
-    request_first(uint64_t(at.a) * cells);  // (these do not need the bounds)
-    prefetch();
-    request_rest(uint64_t(at.a) * cells);
-    wait_loads();
+    const uint64_t tile0 = uint64_t(at.a) * cells;
+    if (kLoop) {  // (the Index words first: see below)
+        prefetch();
+        request_first(tile0);
+    } else {
+        request_first(tile0);  // (these do not need the bounds)
+        prefetch();
+        wait_loads();
+    }
 
     uint32_t max_rounds = 0;
     while (at.a < A) {
@@ -868,11 +881,15 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     part.template clear<kDecodeThreads>(tid, cells);
     if (kListed) pre_list.put(part.word(0), Pa, tid);
     else pre_index.enumerate(index, part.word(0), Pa, rho0, wave);
+    auto stage_cells = [&] {
     add_cells(1, n_in);
     const uint32_t to = part.base + PartLds<kPacked>::kValue + 16 * tid;
 #pragma unroll
     for (uint32_t q = 0; q < kCellPre; q += 4)
         stage_four(to + 4 * q * kDecodeThreads, pre_cell[0] + q, 4 * tid + q * kDecodeThreads, cells);
+    };
+    if (!kLoop) stage_cells();
+    else if (n_in > kRanks) request_more(kRanks, tile0);
     __syncthreads();
     PHASE_MARK(0);
 
@@ -890,11 +907,18 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     uint32_t cell[kIdxPre][3];
     join_cells<kDecodeThreads, kIdxPre, kListed>(part, tid, Pa, idx_out + rho0, cell);
     if (kRanks > kBefore) request_next(kBefore);
+    if (kLoop && n_in > kRanks + kMore) request_more(kRanks + kMore, tile0);
     __syncthreads();
     queue_first<kDecodeThreads, kIdxPre>(part, tid, Pa, mode != TAGC_DECODE_ESTIMATE, cell);
     if (kDense && !kLoop && at.a < A) prefetch();
 #pragma unroll
     for (uint32_t r = kBefore + 1; r < kRanks; ++r) request_next(r);
+    // With a workgroup for every partition the ranks' cells travel and are added up beside all that, which needs no
+    // values: those are only wanted now.
+    if (kLoop) {
+        for (uint32_t r = kRanks + 2 * kMore; r < n_in; r += kMore) request_more(r, tile0);
+        stage_cells();
+    }
     uint32_t idx[kDense ? kIdxPre : 1];
     if constexpr (kDense) {  // (this thread wrote them in join_cells; back long before the rounds are over)
 #pragma unroll
@@ -1249,14 +1273,14 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     // of 67 M in 112 partitions, 290 groups each, 45 / 47 (from the summed sketch 37 / 33); in 164, 200 groups,
     // 45 / 50 (35 / 35); of 7 M in 103, 33 groups, 35 / 45 (29 / 33).
     const bool listed = 16ull * n_chunks > kListGroups * p->A_cap;
-    // One summed sketch; up to four ranks; any number with a workgroup per partition; any number.
+    // A workgroup per partition, whatever is summed; else one summed sketch; up to four ranks; any number.
     // (Decoder alone, us, sixteen waves peeling / sum_peel_kernel, of whose sixteen four sum: 202 M entries with a
     // tenth kept, 2 ranks 464 / 507, 4 ranks 900 / 922; 20 to 40 M, 1 to 4 ranks, 25 to 390 partitions, 3 to 4 us
     // less; 4 ranks of 40 M with 5 % 122 / 122, of 9 M with two fifths 126 / 123.  More ranks' cells do not fit
     // the registers beside the rounds.)
-    const uint32_t form = !fused                  ? (packed_slots(p->T_cap, p->P_cap) ? 1u : 0u)
+    const uint32_t form = grid == p->A_cap && !listed && packed_slots(p->T_cap, p->P_cap) ? 3u
+                          : !fused                ? (packed_slots(p->T_cap, p->P_cap) ? 1u : 0u)
                           : n_ranks <= kHeldRanks ? 2u
-                          : grid == p->A_cap && !listed ? 3u
                                                   : 4u;
     auto pick = [&](auto list) {
         constexpr bool kList = decltype(list)::value;

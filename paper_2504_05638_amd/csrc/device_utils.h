@@ -88,12 +88,15 @@ __device__ inline T block_sum(T v, T *smem)
     return tot;
 }
 
-// float add on an LDS word.  The native LDS float atomic runs at about one lane per three
-// clocks on this hardware (measured: 192 clocks per wave instruction against 6 for the
-// integer ones), so the add is done with an integer compare-and-swap instead; collisions
-// are rare in every use here, so the loop almost always runs once.
-// Three adds to three different words: read together, swapped together, what found another value swapped
-// again alone.
+// The native LDS float add runs at about three clocks a lane on this hardware (a wave's 64 lanes 192, where an integer
+// atomic takes 6 to 20), but what issues it waits for nothing.  (Same bits as the vector add, denormals too.)
+__device__ inline void lds_native_add(uint32_t *p, uint32_t v)
+{
+    __hip_atomic_fetch_add(reinterpret_cast<float *>(p), __uint_as_float(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Three float adds to three different LDS words: read together and swapped together, by integer compare-and-swap, and
+// where a swap found another value, which of a wave's 64 lanes one or two do, added natively.
 __device__ inline void lds_add_f32(float *const (&p)[3], const float (&v)[3])
 {
     uint32_t *w[3], was[3], got[3];
@@ -107,10 +110,7 @@ __device__ inline void lds_add_f32(float *const (&p)[3], const float (&v)[3])
         got[j] = atomicCAS(w[j], was[j], __float_as_uint(__uint_as_float(was[j]) + v[j]));
 #pragma unroll
     for (int j = 0; j < 3; ++j)
-        while (got[j] != was[j]) {
-            was[j] = got[j];
-            got[j] = atomicCAS(w[j], was[j], __float_as_uint(__uint_as_float(was[j]) + v[j]));
-        }
+        if (got[j] != was[j]) lds_native_add(w[j], __float_as_uint(v[j]));
 }
 
 // LDS add by every active lane for itself, returning what was there.  (An address the compiler cannot
