@@ -756,6 +756,32 @@ __device__ __forceinline__ void write_dense(const PartLds<true> &p, uint32_t tid
     } while (piece.next());
 }
 
+// The zeros of the dense output, by workgroup `b` of `n` that have no partition: the entries whose Index bit is not
+// set, and no others, so that nobody has to wait for whom writes the others.  A wave takes 16 words at a
+// time, the next of which are on their way.
+constexpr uint32_t kZeroWords = 16;
+constexpr uint32_t kZeroShare = 512 * 1024;  // entries of the output for each such workgroup at most
+__device__ __forceinline__ void write_zeros(const IndexView &index, uint32_t b, uint32_t n, float *__restrict__ out)
+{
+    const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t step = n * (kDecodeThreads / 64) * kZeroWords;
+    auto request = [&](uint32_t w) { return lane < kZeroWords && w + lane < index.n_words ? index.bitmap[w + lane] : 0u; };
+    uint32_t w0 = (b * (kDecodeThreads / 64) + wave) * kZeroWords;
+    uint32_t next = w0 < index.n_words ? request(w0) : 0u;
+    for (; w0 < index.n_words; w0 += step) {
+        const uint32_t word = next;
+        if (w0 + step < index.n_words) next = request(w0 + step);
+        float *to = out + 32 * uint64_t(w0) + lane;
+#pragma unroll
+        for (uint32_t i = 0; i < kZeroWords; i += 2) {
+            if (w0 + i >= index.n_words) break;
+            const uint32_t lo = __builtin_amdgcn_readlane(word, i), hi = __builtin_amdgcn_readlane(word, i + 1);
+            const bool there = lane < 32 || w0 + i + 1 < index.n_words;
+            if (there && !(((lane < 32 ? lo : hi) >> (lane & 31)) & 1u)) to[32 * i] = 0.0f;
+        }
+    }
+}
+
 // Peels sketch partitions: unknowns rho .. rho+Pa-1 in order of c-index, cells a*3*m_sub ...
 //
 // The LDS a partition needs leaves room for one workgroup per CU, and the rounds are bound
@@ -778,7 +804,8 @@ constexpr uint32_t kHeldRanks = 4;  // kRanks of the form for few ranks
 constexpr uint32_t kListGroups = 256;  // groups of Index words per partition beyond which its unknowns are listed first
 // kListed: the unknowns are in index.list.
 // kDense: writes the dense output of the partitions that dense_by_decoder names as well (dense_rest_kernel
-// has the others').  Where that is stands behind the ranks' sketches: an argument of its own is two scalar
+// has the others'); with kLoop all of it, its partitions' values where they belong, and the workgroups that have no
+// partition the zeros (write_zeros).  Where that is stands behind the ranks' sketches: an argument of its own is two scalar
 // registers too many.
 constexpr uint32_t kDenseRow = kMaxRanksPerPass - 1;
 static_assert(kDenseRow >= kHeldRanks, "the forms that write it have few ranks");
@@ -799,7 +826,10 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
     const uint32_t cells = 3 * m_sub;
-    if (blockIdx.x >= A) return;
+    if (blockIdx.x >= A) {
+        if (kLoop && kDense) write_zeros(index, blockIdx.x - A, gridDim.x - A, dense_row());
+        return;
+    }
     PartLds<kPacked> part(lds64, T_cap, P_cap, m_sub);
 
     // the cells and Index words (or unknowns) of partition `p` into registers (zeros beyond their
@@ -901,7 +931,7 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     auto request_next = [&](uint32_t r) {
         if (!kLoop && at.a < A && r < n_in) request_cells(pre_cell[r < kRanks ? r : 0], r, uint64_t(at.a) * cells);
     };
-    constexpr uint32_t kBefore = kDense ? 0 : 1;  // ranks requested before the join (the dense output is on its way then)
+    constexpr uint32_t kBefore = kDense && !kLoop ? 0 : 1;  // ranks requested before the join (the dense output is on its way then)
     if (!kDense && !kLoop && at.a < A) prefetch();
     if (kBefore) request_next(0);
     uint32_t cell[kIdxPre][3];
@@ -938,18 +968,19 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     wait_loads();
     if constexpr (kDense) {
         asm volatile("" : "+v"(tid));  // (as above)
-        // all c-indices lie in a partition's range, those before the first unknown in the first one's
-        // (read again: kept, the bounds take a vector register to spill)
-        const uint32_t a = at.a - at.step;
-        const uint32_t lo = a ? index.bounds[a] : 0u, hi = min(index.bounds[a + 1], 32 * index.n_words);
         float val[kIdxPre];
 #pragma unroll
         for (uint32_t q = 0; q < kIdxPre; ++q) {
             const uint32_t u = tid + q * kDecodeThreads;
             val[q] = u < Pa ? unknown_value(part, u, mode) : 0.0f;
             if (u < Pa) val_out[rho0 + u] = val[q];
+            if (kLoop && u < Pa) dense_row()[idx[q]] = val[q];
         }
-        if (dense_by_decoder(A, gridDim.x, 32 * index.n_words, hi - lo)) {
+        // all c-indices lie in a partition's range, those before the first unknown in the first one's
+        // (read again: kept, the bounds take a vector register to spill)
+        const uint32_t a = at.a - at.step;
+        const uint32_t lo = !kLoop && a ? index.bounds[a] : 0u, hi = kLoop ? 0u : min(index.bounds[a + 1], 32 * index.n_words);
+        if (!kLoop && dense_by_decoder(A, gridDim.x, 32 * index.n_words, hi - lo)) {
             __syncthreads();
             write_dense<kDecodeThreads, kIdxPre>(part, tid, idx, val, lo, hi, dense_row());
         }
@@ -1300,18 +1331,34 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     // (782) 132 / 133; 200 M nearly all zeros, two partitions, 338 / 341 (6584 by their two workgroups).
     const bool with_dense = dense_out && !listed && (form == 1 || form == 2) && !p->cfg.decode_workgroups &&
                             p->A_cap >= 3ull * grid && p->K >= uint64_t(grid) * p->P_cap;
-    const auto kernel = with_dense ? (form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false, false, true>
+    // Where there are fewer partitions than compute units, workgroups on the others write the dense output's zeros
+    // meanwhile, and the decoder its values among them.  As long as a workgroup has no more to write than about what a
+    // peel and dense_kernel would take it: decoder and dense output of the sum / of one summed sketch, us, dense_kernel
+    // / this way, by partitions and entries per writing workgroup: 2, 1 K 27.8, 27.3 / 23.7, 23.1; 11, 4 K 23.0, 21.8 / 18.6, 17.5;
+    // 80, 47 K 38.1, 34.6 / 38.5, 31.4; 119, 93 K 42.9, 39.1 / 43.6, 33.2; 159, 178 K 48.2, 42.9 / 47.7, 36.0; 82, 188 K
+    // 58.7, 56.1 / 44.2, 38.2; 204, 381 K 51.3, 44.2 / 48.4, 43.3; 66, 344 K 84.1, 81.4 / 83.7, 80.8; 131, 528 K 89.5,
+    // 84.4 / 72.5, 75.1; one rank of 1 M with 5 to 40 % kept 30.3 to 33.6 / 27.3 to 26.1, of 4 M with two fifths in 205
+    // partitions 38.4 / 30.9.  (The sum of eight ranks needs the memory itself.)  Plans with partitions of another size
+    // than the default keep the launch: what is peeled in a few us was not measured, and a test counts on it.
+    const uint32_t cus = uint32_t(device_cu_count());
+    const bool whole = p->P_cap == kDefaultPartUnknowns && p->T_cap == kDefaultPartCells;
+    const uint32_t spare = form == 3 && whole && p->A_cap < cus && !p->cfg.decode_workgroups ? cus - uint32_t(p->A_cap) : 0u;
+    const bool with_zeros = dense_out && n_words && n_ranks <= kDenseRow && p->n_c <= uint64_t(spare) * kZeroShare;
+    if (with_zeros) grid += std::min(spare, (n_words + kZeroWords * (kDecodeThreads / 64) - 1) / (kZeroWords * (kDecodeThreads / 64)));
+    const auto kernel = with_zeros ? peel_kernel<kC0, kI0, true, kHeldRanks, true, false, true>
+                        : with_dense ? (form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false, false, true>
                                                 : peel_kernel<kC0, kI0, true, 1, false, false, true>)
                         : listed   ? pick(std::true_type{})
                                    : pick(std::false_type{});
     static size_t attr_bytes[3][5] = {};
-    if (lds > attr_bytes[with_dense ? 2 : listed][form]) {
+    size_t &attr = attr_bytes[with_dense || with_zeros ? 2 : listed][form];
+    if (lds > attr) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
             return TAGC_EHIP;
-        attr_bytes[with_dense ? 2 : listed][form] = lds;
+        attr = lds;
     }
-    if (with_dense) rp.p[kDenseRow] = dense_out;
+    if (with_dense || with_zeros) rp.p[kDenseRow] = dense_out;
     if (listed) {
         ProfileScope ps("enumerate", s);
         enumerate_kernel<<<n_chunks, 256, 0, s>>>(index, sh->header, idx_out);
@@ -1327,7 +1374,7 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
         const uint32_t n = std::min(n_chunks, std::max(2 * uint32_t(device_cu_count()), kRestGrid));
         dense_rest_kernel<<<n, kChunkWords, 0, s>>>(sh->bitmap, n_words, chunkpre, n_chunks, sh->header, sh->bounds,
                                                     grid, val_out, dense_out);
-    } else if (dense_out && n_chunks) {
+    } else if (dense_out && n_chunks && !with_zeros) {
         ProfileScope ps("dense", s);
         dense_kernel<<<n_chunks, kChunkWords, 0, s>>>(sh->bitmap, n_words, chunkpre, sh->header, val_out,
                                               dense_out);

@@ -1,0 +1,47 @@
+"""The dense output where partitions are fewer than compute units: workgroups without one write the zeros, by the
+merged Index, while the others peel and put their values among them.  Every entry of it is written, whatever was
+there, at sizes around a wave's 16 Index words and a workgroup's, and where nothing is kept."""
+import numpy as np
+import pytest
+import torch
+
+from synth import gradients as G
+from tests.helpers import run_both, compare_all
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 33, 511, 513, 8191, 8193, 100_003])
+@pytest.mark.parametrize("ranks,fused", [(1, False), (3, True), (31, True), (32, True)])
+def test_every_entry_is_written(n, ranks, fused):
+    print("\n[case] dense beside peel n=%d ranks=%d fused=%d" % (n, ranks, fused), flush=True)
+    rng = np.random.default_rng(n)
+    segs = [G.Seg(0, n, 50_000, 1, "a"), G.Seg(n, n, 1_000_000, 1, "b"), G.Seg(2 * n, n, 0, 1, "c")]
+    b = G.Bucket("beside", G.F32, ranks, segs, 3 * n, 1500)
+    grads = [torch.from_numpy(rng.integers(-9, 10, 3 * n).astype(np.float32)) for _ in range(ranks)]
+    for g in grads:  # (of the second segment little is kept all the same: zeros never are)
+        g[n:2 * n][torch.from_numpy(rng.random(n) < 0.9)] = 0
+    ores, tb = run_both(b, grads, seed=5, fused=fused)
+    tb.out_dense.view(torch.int32).fill_(-1)
+    (tb.reduce_decompress if fused else tb.decompress)()
+    torch.cuda.synchronize()
+    tb.status()
+    idx, val = tb.outputs()
+    want = np.zeros(tb.sizes.n_c, np.float32)
+    want[idx] = val
+    assert np.array_equal(tb.dense().view(np.uint32), want.view(np.uint32))
+    tb.run([g.cuda() for g in grads], fused=fused)
+    torch.cuda.synchronize()
+    compare_all(b, ores, tb, exact_values=True)
+    tb.close()
+
+
+def test_nothing_kept():
+    from paper_2504_05638_amd.bucket import TagcBucket
+    print("\n[case] dense beside peel, nothing kept", flush=True)
+    tb = TagcBucket([(0, 300_000, 20_000, 1)], G.F32, 2, dense=True)
+    tb.out_dense.view(torch.int32).fill_(-1)
+    tb.run([torch.zeros(300_000, device="cuda")] * 2, fused=True)
+    torch.cuda.synchronize()
+    assert tb.header()["U"] == 0 and not tb.dense().view(np.uint32).any()
+    tb.close()
