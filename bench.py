@@ -24,7 +24,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X published HBM3E bandwidth
 
 # Kernels of the library grouped into the stages of the path.
 STAGES = {
-    "S1+S2 sparsify+index": ["fill_zero", "accumulate", "prepare", "scan_spill", "hist1",
+    "S1+S2 sparsify+index": ["fill_zero", "accumulate", "prepare", "small", "scan_spill", "hist1",
                              "refine", "count", "place", "widen4"],
     "S3a index OR": ["index_or", "layout", "ranges", "salt"],
     "S2' encode": ["encode"],

@@ -73,10 +73,12 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
     // kernel it shares with the candidate route's last pass then needs few enough
     // registers for one more workgroup per CU.
     p->any_fast = p->small_dense = false;
+    p->all_small = true;
     p->span_dense = p->dense_pairs = 0;
     for (uint32_t l = 0; l < n_seg; ++l) {
         const tagc_segment &s = segs[l];
         if (!(s.flags & TAGC_SEG_COMPRESS) || s.keep_ppm > 1000000u || s.length == 0) continue;
+        if (!small(s.length)) p->all_small = false;
         if (!uint64_t((unsigned __int128)s.length * s.keep_ppm / 1000000u)) continue;
         if (fast_slots(s)) {
             p->any_fast = true;
@@ -140,6 +142,7 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
         delete p;
         return TAGC_ENOMEM;
     }
+    p->all_small &= p->table.size() <= kSmallSegments;
     if (c >= (1ull << 32)) {
         delete p;
         return TAGC_ESIZE;

@@ -1031,13 +1031,14 @@ __device__ inline void for_keys(uint4 v, Fn &&fn)
 
 // What a dense-route segment's level-1 histogram says: writes the selection (fp32: its upper
 // half) and, for a segment that was re-routed, the pre-threshold for the next call, the bin
-// above which about 1.3 k entries lie (what the slots per chunk are sized for).  One thread.
+// above which about 1.3 k entries lie (what the slots per chunk are sized for).  One thread `leaves` what it finds in
+// the table.
 template <int DTYPE>
 __device__ inline SelDev dense_selection(uint32_t l, const SegDev &sd, const BinFound &k_th,
                                          const BinFound &want, uint32_t total, uint32_t nonfinite,
-                                         const TableState ts)
+                                         const TableState ts, bool leaves = true)
 {
-    if (sd.flags & kSegFast) {
+    if (leaves && (sd.flags & kSegFast)) {
         // fewer non-zeros than 1.3 k in the whole segment: everything is a candidate
         const uint32_t b2 = want.bin != kNoBin ? max(want.bin, 1u) : 1u;
         // after a miss (the scale fell below what the carried pre-threshold admits) the next
@@ -1045,8 +1046,8 @@ __device__ inline SelDev dense_selection(uint32_t l, const SegDev &sd, const Bin
         ts.hint[l] = next_hint(b2, ts.prev[l], ts.watch[l]);
         ts.prev[l] = b2;
     }
-    if (nonfinite) atomicAdd(&ts.glob[1], nonfinite);
-    atomicAdd(&ts.glob[2], 1u);
+    if (leaves && nonfinite) atomicAdd(&ts.glob[1], nonfinite);
+    if (leaves) atomicAdd(&ts.glob[2], 1u);
     SelDev r{};
     r.route = 1;
     if (k_th.bin == kNoBin) {  // fewer non-zeros than k: keep every non-zero
@@ -1079,16 +1080,19 @@ __device__ inline uint32_t carried_count(const SegDev &sd)
 // flushes and an arrival count (five segments of 400 to 11,000 fp32 entries, three ranks: 75 us
 // over two launches; 15 in one in this form, a third of it the time a launch takes).
 template <int DTYPE>
-__device__ __forceinline__ void select_small(uint32_t l, const SegDev &sd, const char *base,
-                                             SelDev *sel, const TableState ts, uint32_t *h16,
-                                             uint32_t *smem)
+__device__ __forceinline__ void load_small(uint4 (&v)[kSmallVecs], const SegDev &sd, const char *base)
 {
     constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4;
+#pragma unroll
+    for (uint32_t i = 0; i < kSmallVecs; ++i)
+        v[i] = load_vec<DTYPE>(base, (i * kSmallThreads + threadIdx.x) * VEC, sd.n);
+}
+template <int DTYPE>
+__device__ __forceinline__ SelDev select_small(uint32_t l, const SegDev &sd, const uint4 (&v)[kSmallVecs],
+                                               const TableState ts, uint32_t *h16, uint32_t *smem, bool leaves)
+{
     constexpr uint32_t NT = kSmallThreads;
     const uint32_t tid = threadIdx.x;
-    uint4 v[kSmallVecs];
-#pragma unroll
-    for (uint32_t i = 0; i < kSmallVecs; ++i) v[i] = load_vec<DTYPE>(base, (i * NT + tid) * VEC, sd.n);
     for (uint32_t i = tid; i < kBins1 / 8; i += NT)
         reinterpret_cast<uint4 *>(h16)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
@@ -1112,39 +1116,60 @@ __device__ __forceinline__ void select_small(uint32_t l, const SegDev &sd, const
     BinFound f[2];
     auto get = [&](uint32_t b) { return (h16[b >> 1] >> (16 * (b & 1u))) & 0xFFFFu; };
     select_top<NT, BPT>(get, own, {sd.k, carried_count(sd)}, f, &total, smem);
-    if (DTYPE == kBF16 || f[0].bin == kNoBin) {  // uniform
-        if (tid == 0) sel[l] = dense_selection<DTYPE>(l, sd, f[0], f[1], total, smem[32], ts);
-        return;
-    }
-    // fp32: eight key bits a round
+    SelDev r = dense_selection<DTYPE>(l, sd, f[0], f[1], total, smem[32], ts, leaves && tid == 0);
+    if (DTYPE == kBF16 || f[0].bin == kNoBin) return r;  // uniform
     uint32_t above = f[0].above, prefix = f[0].bin;  // key >> shift of the bin looked into
-#pragma unroll
-    for (uint32_t round = 0; round < 2; ++round) {
-        const uint32_t shift = 16 - 8 * round;
-        if (tid < 256) h16[tid] = 0;
+    const uint32_t in_bin = get(prefix);
+    __syncthreads();  // everybody has read h16
+    if (in_bin <= 64) {
+        // fp32, and no more entries in the threshold's bin than a wave has lanes, as nearly always: every wave compares them
+        // all with each other (the two rounds below are sixteen barriers: small_kernel of 11 thousand entries 16.1 us, 13.5 this way)
+        const uint32_t lane = tid & 63, want = sd.k - above;
+        if (tid == 0) smem[33] = 0;
         __syncthreads();
 #pragma unroll
         for (uint32_t i = 0; i < kSmallVecs; ++i)
-            for_keys<DTYPE>(v[i], [&](uint32_t, uint32_t key) {
-                if ((key >> shift) == prefix) atomicAdd(&h16[(key >> (shift - 8)) & 0xFFu], 1u);
+            for_keys<DTYPE>(v[i], [&](uint32_t bin, uint32_t key) {
+                if (bin == prefix) h16[add_by_lane(&smem[33], 1u)] = key;
             });
         __syncthreads();
-        uint32_t tot2;
-        BinFound g[2];
-        select_top<NT, 1>([&](uint32_t b) { return h16[b]; }, tid < 256 ? h16[tid] : 0u,
-                          {sd.k - above, 0u}, g, &tot2, smem);
-        above += g[0].above;
-        prefix = (prefix << 8) | g[0].bin;
+        const uint32_t mine = lane < in_bin ? h16[lane] : 0u;
+        uint32_t gt = 0, ge = 0;
+        for (uint32_t i = 0; i < in_bin; ++i) {
+            const uint32_t x = __builtin_amdgcn_readlane(mine, i);
+            gt += x > mine;
+            ge += x >= mine;
+        }
+        const uint32_t who = uint32_t(__builtin_ctzll(__ballot(lane < in_bin && gt < want && ge >= want)));
+        prefix = __builtin_amdgcn_readlane(mine, who);
+        above += __builtin_amdgcn_readlane(gt, who);
+    } else {
+        // eight key bits a round
+#pragma unroll
+        for (uint32_t round = 0; round < 2; ++round) {
+            const uint32_t shift = 16 - 8 * round;
+            if (tid < 256) h16[tid] = 0;
+            __syncthreads();
+#pragma unroll
+            for (uint32_t i = 0; i < kSmallVecs; ++i)
+                for_keys<DTYPE>(v[i], [&](uint32_t, uint32_t key) {
+                    if ((key >> shift) == prefix) atomicAdd(&h16[(key >> (shift - 8)) & 0xFFu], 1u);
+                });
+            __syncthreads();
+            uint32_t tot2;
+            BinFound g[2];
+            select_top<NT, 1>([&](uint32_t b) { return h16[b]; }, tid < 256 ? h16[tid] : 0u,
+                              {sd.k - above, 0u}, g, &tot2, smem);
+            above += g[0].above;
+            prefix = (prefix << 8) | g[0].bin;
+        }
     }
-    if (tid == 0) {
-        SelDev r = dense_selection<DTYPE>(l, sd, f[0], f[1], total, smem[32], ts);
-        r.T = prefix;
-        r.G = above;
-        r.quota = sd.k - above;
-        r.cnt = sd.k;
-        r.need2 = 0;
-        sel[l] = r;
-    }
+    r.T = prefix;
+    r.G = above;
+    r.quota = sd.k - above;
+    r.cnt = sd.k;
+    r.need2 = 0;
+    return r;
 }
 
 // Dense route: thresholds of the segments the scan does not select for, by plan or because its
@@ -1191,8 +1216,12 @@ hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t n
     if (SMALL && blockIdx.x < n_small) {
         const uint32_t l = blockIdx.x;
         const SegDev sd = segs[l];
-        if (sd.k != 0 && (sd.flags & kSegSmall))
-            select_small<DTYPE>(l, sd, grad + sd.offset * EB, sel, ts, h, smem);
+        if (sd.k != 0 && (sd.flags & kSegSmall)) {
+            uint4 v[kSmallVecs];
+            load_small<DTYPE>(v, sd, grad + sd.offset * EB);
+            const SelDev r = select_small<DTYPE>(l, sd, v, ts, h, smem, true);
+            if (tid == 0) sel[l] = r;
+        }
         return;
     }
     // tiles of the segment of row l that go through here
@@ -1297,6 +1326,172 @@ hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t n
             if (tid == 0) sel[l] = dense_selection<DTYPE>(l, sd, f[0], f[1], total, smem[32], ts);
         }
         first += __builtin_amdgcn_readlane(inc, 63);
+    }
+}
+
+// ------------------------------------------------------------------ small
+
+// A plan of few segments (kSmallSegments) that are all such that one workgroup's registers hold them takes one launch from
+// the gradient to pairs, Index and counts: a workgroup that has found its segment's threshold has all its entries at hand.
+// What it cannot know is how many pairs the segments before it emit: as many as they are to keep, unless one has
+// fewer non-zeros than that.  So it looks, a wave a segment, at their first entries until it has seen so many
+// non-zeros, which is a few hundred entries and over before its own threshold is found.  Nobody waits for anybody.
+// us: hist1, count and place of five segments of 72 to 11 thousand fp32 entries, three ranks, 23.5; this 13.5.
+// The segment's pairs from position `base` of the rank's list on; and its Index words.
+template <int DTYPE>
+__device__ __forceinline__ void emit_small(const SegDev &sd, const uint4 (&v)[kSmallVecs], const SelDev &se, uint32_t base,
+                                           uint32_t *idx, float *val, uint32_t *bitmap, uint32_t *s_rows /* [kSmallVecs * NT / 64] */)
+{
+    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4, NT = kSmallThreads, NWV = NT / 64, LPW = 32 / VEC;
+    static_assert(kSmallVecs * NWV == 128, "two counts a lane");
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // entries above the threshold, and at it << 16, of a vector (a segment has fewer than 65536)
+    auto marks = [&](const uint4 &q, uint32_t &gt, uint32_t &eq) {
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+        gt = eq = 0;
+#pragma unroll
+        for (uint32_t e = 0; e < VEC; ++e) {
+            const uint32_t key = vec_elem_bits<DTYPE>(w, e) & 0x7FFFFFFFu;
+            gt |= uint32_t(key > se.T) << e;
+            eq |= uint32_t(key == se.T) << e;
+        }
+        if (!se.quota) eq = 0;
+    };
+    uint32_t own[kSmallVecs], inc[kSmallVecs];
+#pragma unroll
+    for (uint32_t i = 0; i < kSmallVecs; ++i) {
+        uint32_t gt, eq;
+        marks(v[i], gt, eq);
+        own[i] = __popc(gt) | (__popc(eq) << 16);
+        inc[i] = wave_incl_scan<uint32_t>(own[i]);
+        if (lane == 63) s_rows[i * NWV + wave] = inc[i];
+    }
+    __syncthreads();
+    if (wave == 0) {  // what lies before each wave's vectors of a row
+        const uint32_t a = s_rows[2 * lane], b = s_rows[2 * lane + 1];
+        const uint32_t before = wave_incl_scan<uint32_t>(a + b) - a - b;
+        s_rows[2 * lane] = before;
+        s_rows[2 * lane + 1] = before + a;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kSmallVecs; ++i) {
+        if (i * NT * VEC >= sd.n) break;  // uniform
+        const uint32_t at = s_rows[i * NWV + wave] + inc[i] - own[i], rel = (i * NT + tid) * VEC;
+        uint32_t gb = at & 0xFFFFu, eb = at >> 16, gt, eq;
+        marks(v[i], gt, eq);
+        const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+        uint32_t kept = gt;
+        for (uint32_t m = gt | eq; m; m &= m - 1) {
+            const uint32_t e = uint32_t(__builtin_ctz(m));
+            const bool above = (gt >> e) & 1u;
+            if (above || eb < se.quota) {
+                const uint32_t pos = base + gb + min(eb, se.quota);
+                // (a register cannot be named by a number that is not known)
+                uint32_t bits = 0;
+#pragma unroll
+                for (uint32_t x = 0; x < VEC; ++x) bits = e == x ? vec_elem_bits<DTYPE>(w, x) : bits;
+                idx[pos] = sd.c_off + rel + e;
+                val[pos] = __uint_as_float(bits);
+                kept |= 1u << e;
+            }
+            gb += above;
+            eb += !above;
+        }
+        uint32_t x = kept << (VEC * (tid & (LPW - 1)));
+#pragma unroll
+        for (uint32_t d = 1; d < LPW; d <<= 1) x |= __shfl_xor(x, d, 64);
+        const uint32_t rel0 = rel - (tid & (LPW - 1)) * VEC;  // first entry of the word
+        if ((tid & (LPW - 1)) == 0 && rel0 < sd.n) bitmap[(sd.c_off + rel0) >> 5] = x;
+    }
+}
+
+// By a wave: the pairs a segment emits, its non-zeros or what it is to keep.
+template <int DTYPE>
+__device__ inline uint32_t emitted_small(const SegDev &sd, const char *base)
+{
+    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4, TURN = 2;
+    uint32_t n = 0;
+    for (uint32_t at = 0; at < sd.n && n < sd.k; at += TURN * 64 * VEC) {
+        uint32_t own = 0;
+        uint4 v[TURN];
+#pragma unroll
+        for (uint32_t i = 0; i < TURN; ++i) v[i] = load_vec<DTYPE>(base, at + (i * 64 + lane_id()) * VEC, sd.n);
+#pragma unroll
+        for (uint32_t i = 0; i < TURN; ++i) for_keys<DTYPE>(v[i], [&](uint32_t, uint32_t) { ++own; });
+        n += __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(own), 63);
+    }
+    return min(n, sd.k);
+}
+
+template <int DTYPE>
+__global__ void __launch_bounds__(kSmallThreads)
+small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
+{
+    constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
+    __shared__ uint32_t h[kBins1 / 2];
+    __shared__ uint32_t smem[40];
+    __shared__ uint32_t s_base;
+    const RankView rv = rank_view();
+    const char *grad = rv.src();
+    const uint32_t L = wl.L, l = blockIdx.x, tid = threadIdx.x;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
+    const TableState ts = table_state(table, L, rv.slot);
+    const SegDev sd = segs[l];
+    uint4 v[kSmallVecs];
+    load_small<DTYPE>(v, sd, grad + sd.offset * EB);
+    if (tid == 0) s_base = 0;
+    uint32_t dense = 0;  // segments that keep something (lane i has looked at segment i: they are 64 at most)
+    if (l == L - 1) {
+        const SegDev row = segs[min(lane_id(), L - 1)];
+        dense = uint32_t(__popcll(__ballot(lane_id() < L && row.k && row.n)));
+    }
+    __syncthreads();
+    for (uint32_t i = wave; i < l; i += kSmallThreads / 64) {
+        const SegDev before = segs[i];
+        const uint32_t n = emitted_small<DTYPE>(before, grad + before.offset * EB);
+        if (n && lane_id() == 0) atomicAdd(&s_base, n);
+    }
+    const bool keeps = sd.k != 0 && sd.n != 0;
+    SelDev r{};  // (no entry is above the largest key)
+    r.T = 0xFFFFFFFFu;
+    if (tid == 0) smem[32] = 0;
+    if (keeps) r = select_small<DTYPE>(l, sd, v, ts, h, smem, false);
+    // The entries that are not finite are counted by the last one to say that it has found its segment's, which
+    // only has to look if somebody had some; the others' counts are the plan's.
+    constexpr uint32_t kSome = 1u << 16;
+    static_assert(kSmallSegments < kSome, "arrivals");
+    uint32_t came = 0, nonfinite = 0;
+    if (tid == 0) {
+        nonfinite = keeps ? smem[32] : 0u;
+        if (nonfinite) {
+            atomicAdd(&ts.glob[1], nonfinite);
+            wait_own_memory_ops();
+        }
+        came = atomicAdd(&ts.arrive[0], nonfinite ? 1u + kSome : 1u);
+    }
+    __syncthreads();  // h, s_base
+    const uint32_t base = s_base;
+    if (sd.n) emit_small<DTYPE>(sd, v, r, base, rv.idx, rv.val, rv.bitmap, h);  // uniform
+    if (tid == 0) {
+        rv.cnt[TAGC_CNT_SEG0 + l] = r.cnt;
+        if (l == L - 1) {
+            rv.cnt[TAGC_CNT_TOTAL] = base + r.cnt;
+            rv.cnt[TAGC_CNT_FLAGS] = 0;
+            rv.cnt[TAGC_CNT_DENSE] = dense;
+            rv.cnt[TAGC_CNT_RESERVED] = 0;
+        }
+        if ((came & (kSome - 1)) == L - 1) {
+            uint32_t all = 0;
+            if (came >= kSome || nonfinite) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                all = ts.glob[1];
+                ts.glob[1] = 0;
+            }
+            rv.cnt[TAGC_CNT_NONFINITE] = all;
+            ts.arrive[0] = 0;
+        }
     }
 }
 
@@ -2333,6 +2528,11 @@ int launch_select(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, boo
         ProfileScope ps("accumulate", s);
         accumulate_kernel<DTYPE><<<dim3(per_rank(cus * 4), n), 256, 0, s>>>(sb, table, wide);
     }
+    if (p->all_small) {
+        ProfileScope ps("small", s);
+        small_kernel<DTYPE><<<dim3(uint32_t(p->table.size()), n), kSmallThreads, 0, s>>>(sb, table, wl);
+        return TAGC_OK;
+    }
     if (sample) {
         ProfileScope ps("prepare", s);
         prepare_kernel<DTYPE><<<dim3(uint32_t(p->table.size()), n), kHistThreads, lds_hist, s>>>(
@@ -2399,7 +2599,7 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
         const uint32_t grid = std::max(n_cand, n_dense);
         refine_kernel<<<dim3(grid, n), 256, 0, s>>>(sb, table, wl, p->cand_cap, n_cand, n_dense);
     }
-    {
+    if (!p->all_small) {
         // the plan fixed the compaction tile's height, and with it which kernels these are
         const bool rows4 = p->compact_rows == 4;
         const bool many = count_from_memory(p, n);

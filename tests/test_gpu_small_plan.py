@@ -1,0 +1,83 @@
+"""Plans whose segments are all held by one workgroup's registers: one launch from the gradient to pairs, Index and
+counts.  Segments that fall short of what they are to keep (fewer non-zeros than that), at the front and in the middle,
+move the pairs of all behind them; the most segments such a plan has, and more; entries that are not finite; ties; segments that keep nothing or are empty; the
+largest such segment and one entry more; odd offsets; repeated calls, the state left behind included; against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from synth import gradients as G
+from tests.helpers import run_both, compare_all
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(segs, n, dtype, zeros, ranks=2, ties=False, error_feedback=False):
+    """`zeros`: segments left with three non-zeros, by rank."""
+    b = G.Bucket("small", dtype, ranks, segs, n, 1500)
+    rng = np.random.default_rng(n)
+    td = torch.float32 if dtype == G.F32 else torch.bfloat16
+    grads = []
+    for r in range(ranks):
+        x = rng.integers(-3, 4, n) if ties else rng.integers(-120, 121, n)
+        for i in zeros[r % len(zeros)]:
+            s = segs[i]
+            x[s.offset + 3:s.offset + s.length] = 0
+        grads.append(torch.from_numpy(x.astype(np.float32)).to(td))
+    ores, tb = run_both(b, grads, seed=6)
+    compare_all(b, ores, tb, exact_values=True)
+    for _ in range(2):  # the counters are back where they were
+        tb.run([g.cuda() for g in grads])
+        torch.cuda.synchronize()
+        compare_all(b, ores, tb, exact_values=True)
+    tb.close()
+
+
+def _segments(lengths, ppm, gap=0):
+    segs, at = [], 0
+    for i, n in enumerate(lengths):
+        segs.append(G.Seg(at, n, ppm[i % len(ppm)], 1, "s%d" % i))
+        at += n + gap
+    return segs, at
+
+
+@pytest.mark.parametrize("dtype", [G.F32, G.BF16])
+@pytest.mark.parametrize("zeros", [((),), ((0,), ()), ((2,), (3,)), ((0, 1, 2, 3, 4),), ((4,),)])
+@pytest.mark.parametrize("ties", [False, True])
+def test_segments_that_fall_short(dtype, zeros, ties):
+    print("\n[case] small plan dtype=%d zeros=%s ties=%d" % (dtype, zeros, ties), flush=True)
+    segs, n = _segments([4097, 1023, 30_001, 8192, 777], [20_000, 300_000, 50_000])
+    _run(segs, n, dtype, zeros, ties=ties)
+
+
+@pytest.mark.parametrize("dtype", [G.F32, G.BF16])
+@pytest.mark.parametrize("count,zeros", [(1, ((0,),)), (64, ((),)), (64, ((3,),)), (64, ((50,), (60, 62))), (65, ((20,),)), (130, ((63, 128), ()))])
+def test_many_segments(dtype, zeros, count):
+    print("\n[case] small plan, %d segments dtype=%d zeros=%s" % (count, dtype, zeros), flush=True)
+    segs, n = _segments([33 + 7 * (i % 5) for i in range(count)], [200_000, 400_000], gap=1)
+    _run(segs, n, dtype, zeros)
+
+
+@pytest.mark.parametrize("dtype,most", [(G.F32, 32768), (G.BF16, 65535)])
+@pytest.mark.parametrize("more", [0, 1])
+def test_the_largest_segment_and_one_more(dtype, most, more):
+    print("\n[case] small plan dtype=%d n=%d" % (dtype, most + more), flush=True)
+    segs = [G.Seg(1, most + more, 30_000, 1, "a"), G.Seg(most + 5, 0, 30_000, 1, "b"), G.Seg(most + 5, 999, 0, 1, "c"),
+            G.Seg(most + 1007, 31, 1_000_000, 1, "d")]
+    _run(segs, most + 1038, dtype, ((0,), ()))
+
+
+@pytest.mark.parametrize("dtype", [G.F32, G.BF16])
+def test_not_finite(dtype):
+    from paper_2504_05638_amd.bucket import TagcBucket
+    print("\n[case] small plan, not finite dtype=%d" % dtype, flush=True)
+    segs, n = _segments([5000, 300, 7000], [50_000])
+    tb = TagcBucket(segs, dtype, 1)
+    for bad in ([], [7, 5100, 11_000, 11_001], []):  # (counted anew in every call)
+        g = torch.randn(n, generator=torch.Generator().manual_seed(1))
+        g[bad] = torch.tensor([float("inf"), float("nan"), -float("inf"), float("inf")])[:len(bad)]
+        tb.run([g.to(torch.float32 if dtype == G.F32 else torch.bfloat16).cuda()])
+        torch.cuda.synchronize()
+        cnt = tb.rank_counts(0)
+        assert cnt["nonfinite"] == len(bad) and cnt["dense_segments"] == 3 and cnt["total"] == sum(cnt["seg"])
+    tb.close()
