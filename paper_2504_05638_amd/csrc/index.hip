@@ -145,10 +145,43 @@ __device__ inline Layout layout_of(uint32_t U, const LayoutParams &lp)
 struct LayoutRank {
     const uint32_t *idx;
     uint32_t *cnt;
+    const uint32_t *wire;  // its Index as it goes on the wire
 };
 struct LayoutBatch {
     LayoutRank r[kMaxRanksPerPass];
 };
+
+// Words 4 w .. 4 w + 3 of the merged Index of the n_in ranks of a launch, as index_merge_kernel has them.
+template <int MODE>
+__device__ __forceinline__ uint4 merge_four(uint32_t n_in, uint32_t w, uint32_t n_words)
+{
+    constexpr uint32_t WIRE = MODE == TAGC_INDEX_ADD4 ? 4 : 1;  // 16-byte vectors on the wire
+    uint4 acc[WIRE];
+#pragma unroll
+    for (uint32_t i = 0; i < WIRE; ++i) acc[i] = make_uint4(0, 0, 0, 0);
+#pragma unroll 4
+    for (uint32_t r = 0; r < n_in; ++r) {
+        const uint4 *wire = reinterpret_cast<const uint4 *>(as_global(batch_row<LayoutRank>(r)->wire)) + WIRE * w;
+#pragma unroll
+        for (uint32_t i = 0; i < WIRE; ++i) {
+            if (WIRE > 1 && WIRE * w + i >= n_words) continue;  // (its words' counters are all there is room for)
+            const uint4 v = wire[i];
+            if (MODE == TAGC_INDEX_OR1) {
+                acc[i].x |= v.x; acc[i].y |= v.y; acc[i].z |= v.z; acc[i].w |= v.w;
+            } else {
+                acc[i].x += v.x; acc[i].y += v.y; acc[i].z += v.z; acc[i].w += v.w;
+            }
+        }
+    }
+    if constexpr (MODE == TAGC_INDEX_ADD4) {
+        auto word = [](const uint4 &a) {
+            return nibbles_set(a.x) | (nibbles_set(a.y) << 8) | (nibbles_set(a.z) << 16) | (nibbles_set(a.w) << 24);
+        };
+        return make_uint4(word(acc[0]), word(acc[1]), word(acc[2]), word(acc[3]));
+    } else {
+        return acc[0];
+    }
+}
 
 // By every 16 lanes of a wave for theirs: the first position in a sorted list whose entry is >= key.  Each step
 // cuts the range into 16 parts: 5 or 6 dependent loads for a list of millions where a thread's binary search
@@ -220,6 +253,14 @@ constexpr uint32_t kNoLink = 0xFFFFu;
 constexpr uint32_t kFilterBits = 64;      // per cell of a sub-table
 constexpr uint32_t kSecondWords = 1024;   // second filter, cleared a word per thread
 static_assert(kSecondWords == kSaltThreads, "every thread clears its word");
+// Index words up to which the layout merges the ranks' Indexes itself: four of each to a thread, kept in LDS, where
+// everything that is looked up in the merged Index then is.  Every workgroup merges them all, so they are few and read
+// little.  us of the Index aggregation, merge and layout / layout alone: 33 thousand entries from 3 ranks 13.4 / 9.8, 66
+// thousand from 1, 8, 16 ranks 13.4, 15.5, 17.1 / 9.7, 11.8, 12.3, 131 thousand from 1, 4, 8 ranks 14.6, 15.3, 16.9 / 11.5, 12.3,
+// 13.4, with 32 partitions 16.7 / 12.6.
+constexpr uint32_t kMergeWords = 4 * kSaltThreads;
+constexpr uint32_t kMergeMost = 64;             // partitions of the plan at most
+constexpr uint32_t kMergeBytes = 128 * 1024;    // of all ranks' Indexes
 constexpr uint32_t kSaltPer = kDefaultPartUnknowns / kSaltThreads;  // non-zeros per thread of a partition of the default size
 constexpr uint32_t kSaltPre = 4;          // Index words per thread requested a partition ahead
 
@@ -236,17 +277,21 @@ __host__ __device__ inline uint32_t salt_listed(uint32_t T_cap, uint32_t P_cap)
 }
 
 // (8 waves per SIMD asked for: two workgroups a compute unit; 106 scalar registers leave room for one)
-template <bool kBounds, bool kSearch, bool kSalts>
+// kMerge: the ranks' Indexes are merged here (MODE says how), and `bitmap`, `chunkcnt` and `grouppre` written.
+constexpr int kNoMerge = -1;
+template <bool kBounds, bool kSearch, bool kSalts, int MODE>
 __global__ void __launch_bounds__(kSaltThreads) __attribute__((amdgpu_waves_per_eu(8)))
-layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__restrict__ bitmap,
-              uint32_t n_words, uint32_t n_c, const uint32_t *__restrict__ chunkcnt,
+layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, uint32_t *__restrict__ bitmap,
+              uint32_t n_words, uint32_t n_c, uint32_t *__restrict__ chunkcnt, uint16_t *__restrict__ grouppre,
               uint32_t *__restrict__ chunkpre, uint32_t n_chunks, const LayoutParams lp,
               uint32_t *__restrict__ header, uint32_t *__restrict__ status,
               uint32_t *__restrict__ bounds, uint32_t ranges_off, uint32_t pair_cap, uint64_t seed,
               uint32_t n_search, uint32_t search0)
 {
     constexpr uint32_t NT = kSaltThreads;
+    constexpr bool kMerge = MODE != kNoMerge;
     extern __shared__ uint32_t lds_salt[];
+    __shared__ __align__(16) uint32_t s_words[kMerge ? kMergeWords : 1];
     const uint32_t P_cap = lp.P_cap, q_cap = lp.T_cap / 3;
     uint32_t *second = lds_salt;            // [kSecondWords]
     uint32_t *tag = second + kSecondWords;  // [P_cap] c-index; compared as a whole: slot_1 | slot_2 << 16
@@ -275,13 +320,35 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     const uint32_t per = (n_chunks + NT - 1) / NT;
     Layout lay{};
     if (kBounds) {
-        const uint32_t first = tid * per, last = min(first + per, n_chunks);
+        const uint32_t first = tid * per, last = kMerge ? first : min(first + per, n_chunks);
         uint32_t own = 0, total;
         for (uint32_t i = first; i < last; ++i) own += chunkcnt[i];
+        uint4 merged = make_uint4(0, 0, 0, 0);
+        if (kMerge) {  // (an Index has room for whole vectors; its padding bits are never set, but not so behind its words)
+            if (4 * tid < n_words) merged = merge_four<kMerge ? MODE : TAGC_INDEX_OR1>(n_in, tid, n_words);
+            if (4 * tid + 1 >= n_words) merged.y = 0;
+            if (4 * tid + 2 >= n_words) merged.z = 0;
+            if (4 * tid + 3 >= n_words) merged.w = 0;
+            reinterpret_cast<uint4 *>(s_words)[tid] = merged;
+            own = __popc(merged.x) + __popc(merged.y) + __popc(merged.z) + __popc(merged.w);
+        }
         const uint32_t before = block_excl_scan<uint32_t, NT / 64>(own, &total, smem);
         s_pre[tid] = before;
         total = uniform(total);
         lay = layout_of(total, lp);
+        if (kMerge) __syncthreads();
+        if (kMerge && blockIdx.x == 0) {  // what a merge of its own leaves
+            const uint32_t w[4] = {merged.x, merged.y, merged.z, merged.w};
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i)
+                if (4 * tid + i < n_words) bitmap[4 * tid + i] = w[i];
+            constexpr uint32_t PC = kChunkWords / 4, PG = kGroupWords / 4;  // threads of a chunk, of a group
+            if (tid % PC == 0 && tid / PC < n_chunks) {
+                chunkcnt[tid / PC] = (tid + PC < NT ? s_pre[tid + PC] : total) - before;
+                chunkpre[tid / PC] = before;
+            }
+            if (tid % PG == 0 && tid / PC < n_chunks) grouppre[tid / PG] = uint16_t(before - s_pre[tid / PC * PC]);
+        }
         if (all && blockIdx.x == 0) {
             uint32_t run = before;
             for (uint32_t i = first; i < last; ++i) {
@@ -312,6 +379,18 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
         uint32_t t = uint32_t(__popcll(__ballot(s_pre[lane * (NT / 64)] <= rho))) - 1u;
         const uint32_t v = lane < NT / 64 ? s_pre[t * (NT / 64) + lane] : 0xFFFFFFFFu;
         t = t * (NT / 64) + uint32_t(__popcll(__ballot(v <= rho))) - 1u;
+        if constexpr (kMerge) {  // its word, then its bit
+            uint32_t r = rho - uniform(s_pre[t]), word = 0, i = 0;
+            for (; i < 4; ++i) {
+                word = uniform(s_words[4 * t + i]);
+                const uint32_t c = __popc(word);
+                if (r < c) break;
+                r -= c;
+            }
+            const uint64_t hit = __ballot(lane < 32 && ((word >> (lane & 31)) & 1u) &&
+                                          uint32_t(__popc(word & ((1u << (lane & 31)) - 1u))) == r);
+            return hit ? (4 * t + i) * 32 + uint32_t(__builtin_ctzll(hit)) : n_c;
+        }
         // its chunk
         uint32_t run = uniform(s_pre[t]), chunk = t * per, local = 0;
         for (uint32_t j = 0; j < per; j += 64) {
@@ -374,7 +453,7 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
     // of its own because it waits for the word
     auto load_word = [&](uint32_t w, uint32_t lo, uint32_t hi) -> uint32_t {
         const uint32_t end = lo < hi ? min(((hi - 1) >> 5) + 1, n_words) : 0u;
-        return w < end ? bitmap[w] : 0u;
+        return w < end ? (kMerge ? s_words[w] : bitmap[w]) : 0u;
     };
     auto clip_word = [&](uint32_t word, uint32_t w, uint32_t lo, uint32_t hi) -> uint32_t {
         if (w == (lo >> 5)) word &= 0xFFFFFFFFu << (lo & 31);
@@ -395,7 +474,9 @@ layout_kernel(const LayoutBatch, uint32_t n_in, uint32_t all, const uint32_t *__
         if (tid < 2 * nb) s_bound[tid] = bounds[me + (b0 + (tid >> 1)) * G + (tid & 1)];
     } else if ((wave >> 1) < nb) {
         const uint32_t a = me + (b0 + (wave >> 1)) * G + (wave & 1);
-        const uint32_t x = a == A ? n_c : bound_of(uint32_t(uint64_t(a) * U / A));
+        // (floor(a U / A): 32-bit divisions where they are enough, a 64-bit one is several times the instructions)
+        const uint32_t rho = A < 65536 ? a * (U / A) + a * (U % A) / A : uint32_t(uint64_t(a) * U / A);
+        const uint32_t x = a == A ? n_c : bound_of(rho);
         if (lane == 0) {
             s_bound[wave] = x;
             if (!(wave & 1) && !(kSalts && searcher)) bounds[a] = x;
@@ -583,7 +664,10 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     uint32_t *chunkpre = static_cast<uint32_t *>(sh->workspace);
     uint32_t *chunk = chunkpre + n_chunks + 1;
     uint16_t *grouppre = group_prefixes(chunkpre, n_chunks);
-    if (n_chunks) {
+    // Small Indexes are merged by the layout, whose workgroups are few then.
+    const bool merges = n_chunks && n_words <= kMergeWords && p->A_cap <= kMergeMost && n_ranks <= kMaxRanksPerPass &&
+                        uint64_t(n_ranks) * n_words * (p->cfg.index_mode == TAGC_INDEX_ADD4 ? 16 : 4) <= kMergeBytes;
+    if (n_chunks && !merges) {
         ProfileScope ps("index_or", s);
         for (uint32_t r0 = 0; r0 < n_ranks; r0 += kMaxRanksPerPass) {
             RankPtrs rp{};
@@ -609,7 +693,7 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
                           p->A_cap,
                           p->m_cap};
     const size_t lds = salt_lds_bytes(p->T_cap, p->P_cap);
-    const size_t lds_all = lds + 6 * 1024;  // with the kernel's own
+    const size_t lds_all = lds + 6 * 1024 + (merges ? 4 * kMergeWords : 0);  // with the kernel's own
     const uint32_t per_cu = uint32_t(std::max<size_t>(1, std::min<size_t>(2, kLdsBytes / lds_all)));
     const uint32_t most = uint32_t(device_cu_count()) * per_cu;  // workgroups that fit the device at once
     // Many searches in a plan that says, by a limit on the decoder's workgroups, that other buckets
@@ -645,14 +729,19 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
                         (n_ranks > 4 || p->A_cap <= 5 * uint64_t(most)));
     const uint32_t searching = apart ? std::min(want, most / 2) : 0u;
     const uint32_t salting = uint32_t(std::min<uint64_t>(p->A_cap, most - searching));
-    const auto layout = layout_kernel<true, true, true>, salts = layout_kernel<false, false, true>;
-    static size_t attr_bytes[2] = {0, 0};
-    if (lds > attr_bytes[split]) {
+    const auto layout = !merges ? layout_kernel<true, true, true, kNoMerge>
+                        : p->cfg.index_mode == TAGC_INDEX_ADD4 ? layout_kernel<true, true, true, TAGC_INDEX_ADD4>
+                        : p->cfg.index_mode == TAGC_INDEX_ADD1 ? layout_kernel<true, true, true, TAGC_INDEX_ADD1>
+                                                               : layout_kernel<true, true, true, TAGC_INDEX_OR1>;
+    const auto salts = layout_kernel<false, false, true, kNoMerge>;
+    static size_t attr_bytes[5] = {};
+    size_t &attr = attr_bytes[merges ? 2 + p->cfg.index_mode : split ? 1 : 0];
+    if (lds > attr) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(split ? salts : layout),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
                                 int(lds)) != hipSuccess)
             return TAGC_EHIP;
-        attr_bytes[split] = lds;
+        attr = lds;
     }
     auto launch = [&](auto kernel, uint32_t n_wgs, size_t lds_bytes, const LayoutBatch &lb,
                       uint32_t n_in, bool all, uint32_t n_search) {
@@ -661,7 +750,7 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
         // counters 281 / 277)
         const uint32_t search0 = n_wgs;
         kernel<<<n_wgs + n_search, kSaltThreads, lds_bytes, s>>>(
-            lb, n_in, all, sh->bitmap, n_words, uint32_t(p->n_c), chunk, chunkpre, n_chunks, lp,
+            lb, n_in, all, sh->bitmap, n_words, uint32_t(p->n_c), chunk, grouppre, chunkpre, n_chunks, lp,
             sh->header, sh->status, sh->bounds, p->cnt_ranges, uint32_t(p->K), p->cfg.seed, n_search, search0);
     };
     for (uint32_t r0 = 0; r0 < n_ranks; r0 += kMaxRanksPerPass) {
@@ -669,12 +758,12 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
         LayoutBatch lb{};
         const uint32_t n_in = std::min(kMaxRanksPerPass, n_ranks - r0);
         for (uint32_t r = 0; r < n_in; ++r)
-            lb.r[r] = LayoutRank{ranks[r0 + r].idx, ranks[r0 + r].cnt};
+            lb.r[r] = LayoutRank{ranks[r0 + r].idx, ranks[r0 + r].cnt, ranks[r0 + r].bitmap};
         if (r0 == 0 || !split) {
             ProfileScope ps("layout", s);
-            if (split) launch(layout_kernel<true, false, false>, batches, 0, lb, n_in, true, 0);
+            if (split) launch(layout_kernel<true, false, false, kNoMerge>, batches, 0, lb, n_in, true, 0);
             else if (r0 == 0) launch(layout, salting, lds, lb, n_in, true, searching);
-            else launch(layout_kernel<true, true, false>, 0, 0, lb, n_in, false, batches);
+            else launch(layout_kernel<true, true, false, kNoMerge>, 0, 0, lb, n_in, false, batches);
         }
         if (split) {
             ProfileScope ps("ranges", s);

@@ -1,0 +1,35 @@
+"""Indexes of up to 4096 words that the layout merges itself: sizes around a vector, a group of 64 words, a chunk of 1024
+and the limit, in the three ways of merging, against the oracle; one word more takes a merge of its own, which the
+profile shows."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_05638_amd import binding as B
+from synth import gradients as G
+from oracle import tagc_oracle as O
+from tests.helpers import run_both, compare_all
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("words", [1, 3, 5, 64, 65, 1023, 1025, 2048, 4095, 4096, 4097])
+@pytest.mark.parametrize("ranks,mode", [(1, O.INDEX_OR1), (3, O.INDEX_OR1), (5, O.INDEX_ADD1), (2, O.INDEX_ADD4), (9, O.INDEX_OR1)])
+def test_merged_by_the_layout(words, ranks, mode):
+    print("\n[case] small index words=%d ranks=%d mode=%d" % (words, ranks, mode), flush=True)
+    n = 32 * words - 5  # (padding bits at the end)
+    b = G.Bucket("small_index", G.F32, ranks, [G.Seg(0, n, 60_000, 1, "a")], n, 1500)
+    rng = np.random.default_rng(words)
+    grads = [torch.from_numpy(rng.integers(-200, 201, n).astype(np.float32)) for _ in range(ranks)]
+    ores, tb = run_both(b, grads, seed=4, index_mode=mode)
+    compare_all(b, ores, tb, exact_values=True)
+    B.tagc_profile_enable(True)
+    try:
+        tb.run([g.cuda() for g in grads])
+        torch.cuda.synchronize()
+    finally:
+        B.tagc_profile_enable(False)
+    bytes_ = ranks * words * (16 if mode == O.INDEX_ADD4 else 4)
+    assert ("index_or" in B.tagc_profile_read()) == (words > 4096 or bytes_ > 128 * 1024)
+    compare_all(b, ores, tb, exact_values=True)
+    tb.close()
