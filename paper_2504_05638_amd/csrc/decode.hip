@@ -93,6 +93,8 @@ struct PartLds {
     static constexpr uint32_t kWord = kMeta + 4 * kDefaultPartCells;
     static constexpr uint32_t kQueue = kWord + 4 * kDefaultPartUnknowns;
     static constexpr uint32_t kPackedBytes = kQueue + 2 * kDefaultPartUnknowns;
+    static constexpr uint32_t kStaged = kRest - 4;  // (behind the claims: see sum_peel_kernel)
+    static_assert(kStaged >= kClaimed + 4 * (kDefaultPartUnknowns / 32 + 1), "a word to spare");
     static_assert(kMeta <= 0xFFFF && kMeta % 16 == 0, "offset of an LDS instruction, 16-byte stores");
 
     uint32_t base;     // of all of it
@@ -141,6 +143,7 @@ struct PartLds {
     __device__ __forceinline__ uint16_t *queue(uint32_t e) const { return lds_at<uint16_t>(queue0 + 2 * e); }
     __device__ __forceinline__ uint32_t *n_queued(uint32_t i) const { return lds_at<uint32_t>(base + 4 * i); }
     __device__ __forceinline__ uint32_t *bar() const { return lds_at<uint32_t>(base + 12); }
+    __device__ __forceinline__ uint32_t *staged() const { return lds_at<uint32_t>(base + kStaged); }
     __device__ __forceinline__ uint4 *handed() const { return lds_at<uint4>(base + 16); }
     // nobody in the first `cells` cells, nothing queued (by NT threads)
     template <uint32_t NT>
@@ -1004,9 +1007,12 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
 // everything else idle; run one after the other they cost the sum.  Here a workgroup's 16
 // waves split up: kLoadWaves of them do nothing but add up, in rank order, the cells of the
 // workgroup's *next* partition in their registers (48 cells per thread), while the other
-// kPeelWaves peel the current one in LDS as peel_kernel does.  The two groups meet twice per
-// partition, at hardware barriers: when the peelers are done with the LDS (the loaders then
-// write the summed cells there) and when that is written.  The peelers' own barriers (after
+// kPeelWaves peel the current one in LDS as peel_kernel does.  The two groups meet once per
+// partition, at a hardware barrier: when the peelers are done with the LDS.  The loaders then
+// write the summed cells there, say so in an LDS word, and go on; the peelers enumerate, join and queue the
+// partition's unknowns, none of which needs a value, and look at that word before the rounds.  (With a second barrier
+// there, the peelers of a workgroup's first partition began with the unknowns when its cells had been summed.  us, that
+// way / this: 8 ranks of 7 M entries, 325 partitions, 47.7 / 41.4, of 67 M, 433, 77.1 / 67.5, 16 of 202 M, 3640, 551 / 552.)  The peelers' own barriers (after
 // the unknowns joined their cells, one per round) must not hold up the loaders, which have
 // no part in them and may be waiting for memory: they are counted in an LDS word instead
 // (peel_barrier).
@@ -1048,7 +1054,7 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
     const uint32_t cells = 3 * m_sub;
     PartLds<true> part(lds64, T_cap, P_cap, m_sub);
     if (blockIdx.x >= A) return;
-    if (tid == 0) *part.bar() = 0;
+    if (tid == 0) *part.bar() = *part.staged() = 0;
     __syncthreads();
 
     if (tid >= kPeelThreads) {
@@ -1099,14 +1105,15 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
         };
         sum_partition(blockIdx.x);
         for (uint32_t a = blockIdx.x; a < A; a += gridDim.x) {
-            __syncthreads();  // the peelers are done with the LDS
+            if (a != blockIdx.x) __syncthreads();  // the peelers are done with the LDS
             uint32_t c0 = lt;  // (see peel_kernel's tid)
             asm volatile("" : "+v"(c0));
             const uint32_t to = part.base + PartLds<true>::kValue + 16 * c0;
 #pragma unroll
             for (uint32_t q = 0; q < kLoadCells; q += 4)
                 stage_four(to + 4 * q * kLoadThreads, acc + q, 4 * c0 + q * kLoadThreads, cells);
-            __syncthreads();  // the partition is staged
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // this wave's cells are staged
+            if (lane_id() == 0) atomicAdd(part.staged(), 1u);
             if (a + gridDim.x < A) sum_partition(a + gridDim.x);
         }
         return;
@@ -1126,17 +1133,14 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
     };
     prefetch();
     wait_loads();
-    uint32_t bar_expected = 0, max_rounds = 0;
+    uint32_t bar_expected = 0, max_rounds = 0, staged = 0;
     while (at.a < A) {
         uint32_t tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         const uint32_t rho0 = at.rho, Pa = at.unknowns();
         part.seed(seed, sa);
-        __syncthreads();  // everybody is done with the previous partition
+        if (staged) __syncthreads();  // everybody is done with the previous partition
         part.clear<kPeelThreads>(tid, cells);
-        __syncthreads();  // the loaders have staged the cells
-
-        // (here and not before the barriers, where the loaders would wait for it)
         if (kListed) pre_list.put(part.word(0), Pa, tid);
         else pre_index.enumerate(index, part.word(0), Pa, rho0, wave);
         peel_barrier(part.bar(), bar_expected);
@@ -1146,6 +1150,12 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
         queue_first<kPeelThreads, kPeelIdx>(part, tid, Pa, mode != TAGC_DECODE_ESTIMATE, cell);
         at.next();
         if (at.a < A) prefetch();
+        // the loaders have staged the cells: every loader wave of a workgroup says so once for each of its partitions,
+        // whatever the peelers do, so the wait ends
+        staged += kLoadWaves;
+        while (__hip_atomic_load(part.staged(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < staged)
+            __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         const uint32_t resolved = peel_rounds<kPeelThreads>(
             part, tid, max_rounds, [&] { peel_barrier(part.bar(), bar_expected); });
         wait_loads();
