@@ -1165,45 +1165,51 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
     if (tid == 0 && max_rounds) atomicMax(&status[TAGC_ST_ROUNDS], max_rounds);
 }
 
-// Dense output: one workgroup per 1024-word chunk of the Index writes the 32768 floats
-// it covers, zeros included.  The chunk's Index words, the number of set bits before each
-// word, and the chunk's values (one contiguous run of val_out; its first kDenseStage
-// entries, a denser chunk reads the rest one by one) are put in LDS; after that a thread
+// Dense output: a workgroup writes the 32 NT floats that NT words of the Index cover, zeros
+// included.  The Index words, the number of set bits before each
+// word, and the words' values (one contiguous run of val_out; its first kDenseStage NT / 1024
+// entries, denser words read the rest one by one) are put in LDS; after that a thread
 // builds any four consecutive outputs on its own -- the rank of a set bit is the word's
 // count plus a popcount -- so the output goes out in plain contiguous 16-byte stores.
 constexpr uint32_t kDenseStage = 8192;
+// Words of a workgroup of dense_kernel.  Bound by the stores; whole chunks, two workgroups of 1024 threads to a compute unit,
+// ended in a turn that was half empty (us, 256 / 512 / 1024 words: 7 M entries 8.9 / 9.1 / 9.6, 25 M 20.1 / 20.4 / 22.1,
+// 67 M 50.4 / 50.9 / 51.5, 202 M 151 / 162 / 155).
+constexpr uint32_t kDenseWords = 256;
 
-__device__ __forceinline__ void write_chunk(uint32_t chunk, const uint32_t *__restrict__ bitmap,
-                                            uint32_t n_words, const uint32_t *__restrict__ chunkpre, uint32_t U,
-                                            const float *__restrict__ val_out, float *__restrict__ dense_out)
+template <uint32_t NT>
+__device__ __forceinline__ void write_words(uint32_t piece, const uint32_t *__restrict__ bitmap, uint32_t n_words,
+                                            const uint32_t *__restrict__ chunkpre, const uint16_t *__restrict__ grouppre,
+                                            uint32_t U, const float *__restrict__ val_out, float *__restrict__ dense_out)
 {
-    constexpr uint32_t NT = kChunkWords;  // one thread per Index word of the chunk
+    constexpr uint32_t STAGE = kDenseStage * NT / kChunkWords;  // one thread per word
+    static_assert(kChunkWords % NT == 0 && NT % kGroupWords == 0, "whole groups of one chunk");
     __shared__ uint32_t scratch[NT / 64];
-    __shared__ uint32_t s_word[kChunkWords], s_pre[kChunkWords];
-    __shared__ float vals[kDenseStage];
+    __shared__ uint32_t s_word[NT], s_pre[NT];
+    __shared__ float vals[STAGE];
     const uint32_t tid = threadIdx.x;
-    const uint32_t cw0 = chunk * kChunkWords;  // first word of the chunk
+    const uint32_t cw0 = piece * NT;  // first word
     const uint32_t word = cw0 + tid < n_words ? bitmap[cw0 + tid] : 0u;
-    const uint32_t base = chunkpre[chunk];
+    const uint32_t base = chunkpre[cw0 / kChunkWords] + (NT < kChunkWords ? grouppre[cw0 / kGroupWords] : 0u);
     uint32_t tot;
     const uint32_t pre = block_excl_scan<uint32_t, NT / 64>(uint32_t(__popc(word)), &tot, scratch);
     s_word[tid] = word;
     s_pre[tid] = pre;
-    const uint32_t n_st = min(tot, kDenseStage);
+    const uint32_t n_st = min(tot, STAGE);
     for (uint32_t i = tid; i < n_st; i += NT) vals[i] = base + i < U ? val_out[base + i] : 0.f;
     __syncthreads();
-    const uint32_t n4 = min(kChunkWords, n_words - cw0) * 8;  // float4 groups of this chunk
+    const uint32_t n4 = min(NT, n_words - cw0) * 8;  // float4 groups
     float4 *out = reinterpret_cast<float4 *>(dense_out + uint64_t(cw0) * 32);
     for (uint32_t c = tid; c < n4; c += NT) {
         const uint32_t wd = s_word[c >> 3], sh = (c & 7u) * 4u;
         const uint32_t nib = (wd >> sh) & 0xFu;
         float o[4] = {0.f, 0.f, 0.f, 0.f};
         if (nib) {
-            uint32_t r = s_pre[c >> 3] + __popc(wd & ((1u << sh) - 1u));  // rank in the chunk
+            uint32_t r = s_pre[c >> 3] + __popc(wd & ((1u << sh) - 1u));  // rank among the words'
 #pragma unroll
             for (uint32_t b = 0; b < 4; ++b) {
                 if ((nib >> b) & 1u) {
-                    if (r < kDenseStage) o[b] = vals[r];
+                    if (r < STAGE) o[b] = vals[r];
                     else if (base + r < U) o[b] = val_out[base + r];
                     ++r;
                 }
@@ -1213,12 +1219,12 @@ __device__ __forceinline__ void write_chunk(uint32_t chunk, const uint32_t *__re
     }
 }
 
-__global__ void __launch_bounds__(kChunkWords)
+__global__ void __launch_bounds__(kDenseWords)
 dense_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words,
-             const uint32_t *__restrict__ chunkpre, const uint32_t *__restrict__ header,
+             const uint32_t *__restrict__ chunkpre, const uint16_t *__restrict__ grouppre, const uint32_t *__restrict__ header,
              const float *__restrict__ val_out, float *__restrict__ dense_out)
 {
-    write_chunk(blockIdx.x, bitmap, n_words, chunkpre, header[TAGC_HDR_U], val_out, dense_out);
+    write_words<kDenseWords>(blockIdx.x, bitmap, n_words, chunkpre, grouppre, header[TAGC_HDR_U], val_out, dense_out);
 }
 
 // What a decoder of peel_grid workgroups that writes the dense output has left of it: the chunks that hold
@@ -1256,7 +1262,7 @@ dense_rest_kernel(const uint32_t *__restrict__ bitmap, uint32_t n_words, const u
     __syncthreads();
     for (uint32_t k = 0; b + k * grid < n_chunks; ++k) {
         if (!((marks[k >> 5] >> (k & 31)) & 1u)) continue;
-        write_chunk(b + k * grid, bitmap, n_words, chunkpre, U, val_out, dense_out);
+        write_words<kChunkWords>(b + k * grid, bitmap, n_words, chunkpre, nullptr, U, val_out, dense_out);
         __syncthreads();
     }
 }
@@ -1386,8 +1392,8 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
                                                     grid, val_out, dense_out);
     } else if (dense_out && n_chunks && !with_zeros) {
         ProfileScope ps("dense", s);
-        dense_kernel<<<n_chunks, kChunkWords, 0, s>>>(sh->bitmap, n_words, chunkpre, sh->header, val_out,
-                                              dense_out);
+        dense_kernel<<<(n_words + kDenseWords - 1) / kDenseWords, kDenseWords, 0, s>>>(
+            sh->bitmap, n_words, chunkpre, index.grouppre, sh->header, val_out, dense_out);
     }
     return hip_ok(hipGetLastError());
 }

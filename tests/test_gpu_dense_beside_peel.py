@@ -45,3 +45,20 @@ def test_nothing_kept():
     torch.cuda.synchronize()
     assert tb.header()["U"] == 0 and not tb.dense().view(np.uint32).any()
     tb.close()
+
+
+# The launch that writes all of it (partitions of another size have it): 256 words to a workgroup, of which a quarter's
+# values are staged
+@pytest.mark.parametrize("words", [255, 256, 257, 1023, 1025, 2300])
+@pytest.mark.parametrize("ppm", [100_000, 700_000])
+def test_a_launch_of_its_own(words, ppm):
+    print("\n[case] dense kernel words=%d ppm=%d" % (words, ppm), flush=True)
+    n = 32 * words - 3
+    b = G.Bucket("dense", G.F32, 1, [G.Seg(0, n, ppm, 1, "a")], n, 1500)
+    g = torch.from_numpy(np.random.default_rng(words).integers(1, 100, n).astype(np.float32))
+    ores, tb = run_both(b, [g], seed=5, P=256, T=384)
+    tb.out_dense.view(torch.int32).fill_(-1)
+    tb.run([g.cuda()])
+    torch.cuda.synchronize()
+    compare_all(b, ores, tb, exact_values=True)
+    tb.close()
