@@ -797,8 +797,8 @@ __device__ __forceinline__ void write_zeros(const IndexView &index, uint32_t b, 
 // the next partition staying in the registers they are loaded to until it is staged.
 // kLoop: over any number of ranks, or the summed sketch, added up as they come.  For grids that have a workgroup for
 // every partition: there is no next partition whose sum could run beside the rounds, as
-// sum_peel_kernel has it (236 partitions of 8 ranks: 42 us, 48 in that kernel; 20 of 8: 24, 28; 218 of 16:
-// 56, 60).  Nor is there one before, whose rounds its cells could travel behind: the Index words are requested first
+// sum_peel_kernel has it (40 partitions of 8 ranks: 27.7 us, 28.9 in that kernel; 51 of 5: 27.5, 30.1; 159 of 8: 31.1,
+// 31.3; 239 of 8: 35.6, 34.5; 233 of 12: 39.8, 41.4).  Nor is there one before, whose rounds its cells could travel behind: the Index words are requested first
 // and the unknowns enumerated, joined and looked through for the first queue, none of which needs a value, while the
 // cells travel (8 ranks of 25 M entries 40.4 -> 38.0, 3 of 36 thousand, one partition, 18.6 -> 15.9, 4 of 1 M 20.8 ->
 // 17.9, a summed sketch in 236 partitions 32.0 -> 29.4).
@@ -840,12 +840,15 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     float pre_cell[kRanks][kCellPre];
     PartIndex<kDecodeThreads / 64, kIndexPre> pre_index;
     PartList<kDecodeThreads, kIdxPre> pre_list;
+    // (the form for larger partitions has no runs of four registers to spare)
+    constexpr uint32_t kFour = kPacked ? 4 : 1;
     auto request_cells = [&](float (&v)[kCellPre], uint32_t r, uint64_t tile) {
         const GlobalCells src = rank_sketch(r) + tile;
 #pragma unroll
-        for (uint32_t q = 0; q < kCellPre; q += 4) {
-            const uint32_t c = 4 * tid + q * kDecodeThreads;
-            if (c < cells) request_four(v + q, src + c);  // (a sketch has room for three more cells)
+        for (uint32_t q = 0; q < kCellPre; q += kFour) {
+            const uint32_t c = kFour * tid + q * kDecodeThreads;
+            if (kFour == 1) v[q] = c < cells ? __builtin_nontemporal_load(src + c) : 0.0f;
+            else if (c < cells) request_four(v + q, src + c);  // (a sketch has room for three more cells)
             else v[q] = v[q + 1] = v[q + 2] = v[q + 3] = 0.0f;
         }
     };
@@ -916,10 +919,13 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     else pre_index.enumerate(index, part.word(0), Pa, rho0, wave);
     auto stage_cells = [&] {
     add_cells(1, n_in);
-    const uint32_t to = part.base + PartLds<kPacked>::kValue + 16 * tid;
+    const uint32_t to = part.base + PartLds<kPacked>::kValue + 4 * kFour * tid;
 #pragma unroll
-    for (uint32_t q = 0; q < kCellPre; q += 4)
-        stage_four(to + 4 * q * kDecodeThreads, pre_cell[0] + q, 4 * tid + q * kDecodeThreads, cells);
+    for (uint32_t q = 0; q < kCellPre; q += kFour) {
+        const uint32_t c = kFour * tid + q * kDecodeThreads, at = to + 4 * q * kDecodeThreads;
+        if (kFour == 4) stage_four(at, pre_cell[0] + q, c, cells);
+        else if (c < cells) *lds_at<float>(at) = pre_cell[0][q];
+    }
     };
     if (!kLoop) stage_cells();
     else if (n_in > kRanks) request_more(kRanks, tile0);
@@ -934,18 +940,20 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     auto request_next = [&](uint32_t r) {
         if (!kLoop && at.a < A && r < n_in) request_cells(pre_cell[r < kRanks ? r : 0], r, uint64_t(at.a) * cells);
     };
-    constexpr uint32_t kBefore = kDense && !kLoop ? 0 : 1;  // ranks requested before the join (the dense output is on its way then)
-    if (!kDense && !kLoop && at.a < A) prefetch();
+    // Ranks requested before the join, and by its end: none before it where a dense output is on its way, and none at all
+    // in front of the first queue in the form for larger partitions, which has no registers for that.
+    constexpr uint32_t kBefore = kPacked && !(kDense && !kLoop) ? 1 : 0, kJoined = kPacked ? kBefore + 1 : 0;
+    if (kBefore && !kLoop && at.a < A) prefetch();
     if (kBefore) request_next(0);
     uint32_t cell[kIdxPre][3];
     join_cells<kDecodeThreads, kIdxPre, kListed>(part, tid, Pa, idx_out + rho0, cell);
-    if (kRanks > kBefore) request_next(kBefore);
+    if (kRanks > kBefore && kJoined > kBefore) request_next(kBefore);
     if (kLoop && n_in > kRanks + kMore) request_more(kRanks + kMore, tile0);
     __syncthreads();
     queue_first<kDecodeThreads, kIdxPre>(part, tid, Pa, mode != TAGC_DECODE_ESTIMATE, cell);
-    if (kDense && !kLoop && at.a < A) prefetch();
+    if (!kBefore && !kLoop && at.a < A) prefetch();
 #pragma unroll
-    for (uint32_t r = kBefore + 1; r < kRanks; ++r) request_next(r);
+    for (uint32_t r = kJoined; r < kRanks; ++r) request_next(r);
     // With a workgroup for every partition the ranks' cells travel and are added up beside all that, which needs no
     // values: those are only wanted now.
     if (kLoop) {
