@@ -699,7 +699,7 @@ struct PartAhead {
         v = 0;
         if (a < A) first(index, salt, a);
     }
-    // (the grid has no workgroups beyond the room for partitions; the salts lie behind the bounds)
+    // (a is inside the room for partitions, whose salts lie behind the bounds and one more)
     __device__ __forceinline__ void first(const IndexView &index, const uint32_t *salt, uint32_t a)
     {
         const uint32_t lane = lane_id();
@@ -825,7 +825,8 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     const uint32_t tid = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     PartAhead ahead;
-    ahead.first(index, salt, blockIdx.x);
+    // (workgroups beyond the room for partitions, which only write zeros, ask for what the last of it holds)
+    ahead.first(index, salt, kLoop && kDense ? min(blockIdx.x, uint32_t(salt - index.bounds) - 2u) : blockIdx.x);
     const uint32_t U = header[TAGC_HDR_U], A = header[TAGC_HDR_A];
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
     const uint32_t cells = 3 * m_sub;
