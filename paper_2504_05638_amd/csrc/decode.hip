@@ -986,7 +986,9 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
             const uint32_t u = tid + q * kDecodeThreads;
             val[q] = u < Pa ? unknown_value(part, u, mode) : 0.0f;
             if (u < Pa) val_out[rho0 + u] = val[q];
-            if (kLoop && u < Pa) dense_row()[idx[q]] = val[q];
+            // (a word of the partition that no set bit has filled holds anything, should the Index have changed since it
+            // was merged: nothing lands outside the output)
+            if (kLoop && idx[q] < 32 * index.n_words) dense_row()[idx[q]] = val[q];
         }
         // all c-indices lie in a partition's range, those before the first unknown in the first one's
         // (read again: kept, the bounds take a vector register to spill)

@@ -62,3 +62,30 @@ def test_a_launch_of_its_own(words, ppm):
     torch.cuda.synchronize()
     compare_all(b, ores, tb, exact_values=True)
     tb.close()
+
+
+# The decoder takes what the merged Index holds at the moment, whatever the bounds were made from: with fewer set bits
+# than there were unknowns, the others' c-indices are what the local memory held.
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("n", [100_003, 3_000_000])
+def test_nothing_lands_outside(n, fused):
+    from paper_2504_05638_amd import binding as B
+    from paper_2504_05638_amd.bucket import TagcBucket
+    print("\n[case] dense beside peel, Index cleared, n=%d fused=%d" % (n, fused), flush=True)
+    tb = TagcBucket([(0, n, 50_000, 1)], G.F32, 2)
+    grads = [torch.randn(n, generator=torch.Generator().manual_seed(r)).cuda() for r in range(2)]
+    for _ in range(2):
+        tb.run(grads, fused=fused)
+    room, guard = int(tb.sizes.n_c), 1 << 28
+    out = torch.full((room + 2 * guard,), -1, dtype=torch.int32, device="cuda")
+    at, s = out.data_ptr() + 4 * guard, torch.cuda.current_stream().cuda_stream
+    tb.sh_bitmap.zero_()
+    if fused:
+        B.tagc_reduce_decompress(tb.plan, tb.rk, tb.shared, tb.out_idx.data_ptr(), tb.out_val.data_ptr(), at, s, 2)
+    else:
+        B.tagc_decompress(tb.plan, tb.shared, tb.out_idx.data_ptr(), tb.out_val.data_ptr(), at, s)
+    torch.cuda.synchronize()
+    assert bool((out[:guard] == -1).all()) and bool((out[guard + room:] == -1).all())
+    # (no bit is set: all is zero but for the few entries that such a c-index may name)
+    assert int((out[guard:guard + room] != 0).sum()) <= tb.header()["U"]
+    tb.close()
