@@ -760,11 +760,12 @@ __device__ __forceinline__ void write_dense(const PartLds<true> &p, uint32_t tid
 }
 
 // The zeros of the dense output, by workgroup `b` of `n` that have no partition: the entries whose Index bit is not
-// set, and no others, so that nobody has to wait for whom writes the others.  A wave takes 16 words at a
-// time, the next of which are on their way.
+// set, and no others, so that nobody has to wait for whom writes the others; all of them where there is no partition
+// (after an overflow, when bits are set all the same).  A wave takes 16 words at a time, the next of which are on
+// their way.
 constexpr uint32_t kZeroWords = 16;
 constexpr uint32_t kZeroShare = 512 * 1024;  // entries of the output for each such workgroup at most
-__device__ __forceinline__ void write_zeros(const IndexView &index, uint32_t b, uint32_t n, float *__restrict__ out)
+__device__ __forceinline__ void write_zeros(const IndexView &index, uint32_t b, uint32_t n, bool all, float *__restrict__ out)
 {
     const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t step = n * (kDecodeThreads / 64) * kZeroWords;
@@ -772,7 +773,7 @@ __device__ __forceinline__ void write_zeros(const IndexView &index, uint32_t b, 
     uint32_t w0 = (b * (kDecodeThreads / 64) + wave) * kZeroWords;
     uint32_t next = w0 < index.n_words ? request(w0) : 0u;
     for (; w0 < index.n_words; w0 += step) {
-        const uint32_t word = next;
+        const uint32_t word = all ? 0u : next;
         if (w0 + step < index.n_words) next = request(w0 + step);
         float *to = out + 32 * uint64_t(w0) + lane;
 #pragma unroll
@@ -831,7 +832,7 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     const uint32_t m_sub = header[TAGC_HDR_MSUB];
     const uint32_t cells = 3 * m_sub;
     if (blockIdx.x >= A) {
-        if (kLoop && kDense) write_zeros(index, blockIdx.x - A, gridDim.x - A, dense_row());
+        if (kLoop && kDense) write_zeros(index, blockIdx.x - A, gridDim.x - A, A == 0, dense_row());
         return;
     }
     PartLds<kPacked> part(lds64, T_cap, P_cap, m_sub);

@@ -89,3 +89,21 @@ def test_nothing_lands_outside(n, fused):
     # (no bit is set: all is zero but for the few entries that such a c-index may name)
     assert int((out[guard:guard + room] != 0).sum()) <= tb.header()["U"]
     tb.close()
+
+
+# Three ranks keep the one entry of every segment: their 1-bit Indexes add up to two set bits each, more than the plan
+# has room for.  No partition is decoded then, and the dense output is zeros.
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("segments", [1, 40])
+def test_zeros_after_an_overflow(segments, fused):
+    from paper_2504_05638_amd import binding as B
+    from paper_2504_05638_amd.bucket import TagcBucket
+    print("\n[case] dense beside peel, overflow segments=%d fused=%d" % (segments, fused), flush=True)
+    tb = TagcBucket([(i, 1, 1_000_000, 1) for i in range(segments)], G.F32, 3, index_mode=B.TAGC_INDEX_ADD1, dense=True)
+    tb.out_dense.view(torch.int32).fill_(-1)
+    tb.run([torch.full((segments,), 5.0, device="cuda")] * 3, fused=fused)
+    torch.cuda.synchronize()
+    assert tb.status()["flags"] == B.TAGC_FLAG_OVERFLOW and tb.header()["A"] == 0
+    assert np.array_equal(tb.shared_bitmap(), np.full(segments, 3, np.uint32))
+    assert not tb.dense().view(np.uint32).any()
+    tb.close()
