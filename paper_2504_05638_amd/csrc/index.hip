@@ -664,9 +664,14 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     uint32_t *chunkpre = static_cast<uint32_t *>(sh->workspace);
     uint32_t *chunk = chunkpre + n_chunks + 1;
     uint16_t *grouppre = group_prefixes(chunkpre, n_chunks);
-    // Small Indexes are merged by the layout, whose workgroups are few then.
-    const bool merges = n_chunks && n_words <= kMergeWords && p->A_cap <= kMergeMost && n_ranks <= kMaxRanksPerPass &&
-                        uint64_t(n_ranks) * n_words * (p->cfg.index_mode == TAGC_INDEX_ADD4 ? 16 : 4) <= kMergeBytes;
+    // Small Indexes are merged by the layout, whose workgroups are few then.  Each reads all of the ranks' Indexes and
+    // one writes the merged one meanwhile, so not where that takes a rank's own place (a merge of its own reads
+    // and writes word by word).
+    const uint64_t wire_bytes = uint64_t(n_words) * (p->cfg.index_mode == TAGC_INDEX_ADD4 ? 16 : 4);
+    bool merges = n_chunks && n_words <= kMergeWords && p->A_cap <= kMergeMost && n_ranks <= kMaxRanksPerPass &&
+                  n_ranks * wire_bytes <= kMergeBytes;
+    for (uint32_t r = 0; merges && r < n_ranks; ++r)
+        merges = !overlap(sh->bitmap, 4ull * n_words, ranks[r].bitmap, wire_bytes);
     if (n_chunks && !merges) {
         ProfileScope ps("index_or", s);
         for (uint32_t r0 = 0; r0 < n_ranks; r0 += kMaxRanksPerPass) {

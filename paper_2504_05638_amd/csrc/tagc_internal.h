@@ -277,6 +277,13 @@ size_t salt_lds_bytes(uint32_t T_cap, uint32_t P_cap);
 // (TAGC_STATIC_WORKSPACE_BYTES); looked up on the first call per device, never allocated
 int static_workspace(void **out);
 
+// whether two ranges of device memory share a byte
+inline bool overlap(const void *a, uint64_t bytes_a, const void *b, uint64_t bytes_b)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + bytes_b && y < x + bytes_a;
+}
+
 inline int hip_ok(hipError_t e) { return e == hipSuccess ? TAGC_OK : TAGC_EHIP; }
 
 }  // namespace tagc

@@ -33,3 +33,30 @@ def test_merged_by_the_layout(words, ranks, mode):
     assert ("index_or" in B.tagc_profile_read()) == (words > 4096 or bytes_ > 128 * 1024)
     compare_all(b, ores, tb, exact_values=True)
     tb.close()
+
+
+# The merged Index in the place of a rank's own: merged by a launch of its own, whatever the size
+@pytest.mark.parametrize("words", [1, 65, 4096])
+@pytest.mark.parametrize("rank", [0, 2])
+@pytest.mark.parametrize("mode", [O.INDEX_OR1, O.INDEX_ADD1])
+def test_merged_in_place(words, rank, mode):
+    print("\n[case] small index in place words=%d rank=%d mode=%d" % (words, rank, mode), flush=True)
+    n, ranks = 32 * words - 5, 3
+    b = G.Bucket("small_index", G.F32, ranks, [G.Seg(0, n, 60_000, 1, "a")], n, 1500)
+    rng = np.random.default_rng(words)
+    grads = [torch.from_numpy(rng.integers(-200, 201, n).astype(np.float32)) for _ in range(ranks)]
+    ores, tb = run_both(b, grads, seed=4, index_mode=mode)
+    tb.shared.bitmap = tb.rk[rank].bitmap
+    B.tagc_profile_enable(True)
+    try:
+        tb.run([g.cuda() for g in grads])
+        torch.cuda.synchronize()
+    finally:
+        B.tagc_profile_enable(False)
+    assert "index_or" in B.tagc_profile_read()
+    assert np.array_equal(tb.rank_bitmap(rank), ores.bitmap[:words])
+    tb.sh_bitmap.copy_(tb._rk_tensors[rank]["bitmap"][:tb.sh_bitmap.numel()])
+    local = ores.ranks[rank].bitmap[:words].copy()
+    tb._rk_tensors[rank]["bitmap"][:4 * words].copy_(torch.from_numpy(local.view(np.uint8)))
+    compare_all(b, ores, tb, exact_values=True)
+    tb.close()
