@@ -1349,6 +1349,15 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
                : form == 1 ? peel_kernel<kC0, kI0, true, 1, false, kList, false>
                            : peel_kernel<kC1, kI1, false, 1, false, kList, false>;
     };
+    // A dense output that begins before the last partition is decoded must lie apart from what is still read by then; a
+    // launch behind the decoder may put it in the place of a sketch, say.
+    auto dense_apart = [&] {
+        const uint64_t bytes = 4 * p->n_c;
+        bool apart = !overlap(dense_out, bytes, idx_out, 4 * p->U_cap) && !overlap(dense_out, bytes, sh->bounds, p->sizes.shared_bounds_bytes);
+        for (uint32_t r = 0; r < n_ranks; ++r) apart &= !overlap(dense_out, bytes, rp.p[r], 4 * p->m_cap);
+        return apart;
+    };
+    const bool early = dense_out && !listed && !p->cfg.decode_workgroups && dense_apart();
     // The dense output by the decoder itself, whose rounds leave the memory system idle (sum_peel_kernel's
     // do not), where the plan has room for three turns of partitions to hide all but the last turn's behind, and
     // one rank's pairs alone give every compute unit a partition.  That is what the plan can know: which
@@ -1357,8 +1366,8 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     // decoder: 2 ranks of 202 M entries with a tenth kept 710 / 684, in four layers with 5 to 20 % 628 / 593, of
     // 200 M with 2.5 % 296 / 283, of 40 M with a tenth (928 partitions) 165 / 159; one rank of 32 M with a fifth
     // (782) 132 / 133; 200 M nearly all zeros, two partitions, 338 / 341 (6584 by their two workgroups).
-    const bool with_dense = dense_out && !listed && (form == 1 || form == 2) && !p->cfg.decode_workgroups &&
-                            p->A_cap >= 3ull * grid && p->K >= uint64_t(grid) * p->P_cap;
+    const bool with_dense = early && (form == 1 || form == 2) && p->A_cap >= 3ull * grid &&
+                            p->K >= uint64_t(grid) * p->P_cap;
     // Where there are fewer partitions than compute units, workgroups on the others write the dense output's zeros
     // meanwhile, and the decoder its values among them.  As long as a workgroup has no more to write than about what a
     // peel and dense_kernel would take it: decoder and dense output of the sum / of one summed sketch, us, dense_kernel
@@ -1370,8 +1379,8 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     // than the default keep the launch: what is peeled in a few us was not measured, and a test counts on it.
     const uint32_t cus = uint32_t(device_cu_count());
     const bool whole = p->P_cap == kDefaultPartUnknowns && p->T_cap == kDefaultPartCells;
-    const uint32_t spare = form == 3 && whole && p->A_cap < cus && !p->cfg.decode_workgroups ? cus - uint32_t(p->A_cap) : 0u;
-    const bool with_zeros = dense_out && n_words && n_ranks <= kDenseRow && p->n_c <= uint64_t(spare) * kZeroShare;
+    const uint32_t spare = early && form == 3 && whole && p->A_cap < cus ? cus - uint32_t(p->A_cap) : 0u;
+    const bool with_zeros = n_words && spare && n_ranks <= kDenseRow && p->n_c <= uint64_t(spare) * kZeroShare;
     if (with_zeros) grid += std::min(spare, (n_words + kZeroWords * (kDecodeThreads / 64) - 1) / (kZeroWords * (kDecodeThreads / 64)));
     const auto kernel = with_zeros ? peel_kernel<kC0, kI0, true, kHeldRanks, true, false, true>
                         : with_dense ? (form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false, false, true>

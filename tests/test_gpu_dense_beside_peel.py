@@ -107,3 +107,38 @@ def test_zeros_after_an_overflow(segments, fused):
     assert np.array_equal(tb.shared_bitmap(), np.full(segments, 3, np.uint32))
     assert not tb.dense().view(np.uint32).any()
     tb.close()
+
+
+# A dense output in the place of a sketch, which nobody needs behind the decoder: by the launch behind it
+@pytest.mark.parametrize("fused,where", [(False, "sum"), (True, "sketch0"), (True, "sketch2"), (True, "idx"), (True, "bounds")])
+@pytest.mark.parametrize("n,P,T", [(2_000, 0, 0), (30_000, 32, 48)])
+def test_in_the_place_of_what_was_read(fused, where, n, P, T):
+    from paper_2504_05638_amd import binding as B
+    print("\n[case] dense over %s n=%d" % (where, n), flush=True)
+    b = G.Bucket("beside", G.F32, 3, [G.Seg(0, n, 900_000, 1, "a")], n, 3000)
+    rng = np.random.default_rng(n)
+    grads = [torch.from_numpy(rng.integers(-9, 10, n).astype(np.float32)) for _ in range(3)]
+    ores, tb = run_both(b, grads, seed=5, P=P, T=T, fused=fused)
+    want = tb.dense()
+    out = {"sum": tb.sh_sketch, "idx": tb.out_idx, "bounds": tb.sh_bounds}.get(where)
+    if out is None:
+        out = tb._rk_tensors[int(where[-1])]["sketch"]
+    elif where in ("idx", "bounds"):  # (at the end of a buffer that begins as that one)
+        big = torch.zeros(out.numel() + 4 * n + 4096, dtype=torch.uint8, device="cuda")
+        big[:out.numel()] = out
+        out = big
+        if where == "idx":
+            tb.out_idx = big
+        else:
+            tb.shared.bounds = big.data_ptr()
+    assert out.numel() >= 4 * int(tb.sizes.n_c)
+    tb.out_dense = out
+    B.tagc_profile_enable(True)
+    try:
+        (tb.reduce_decompress if fused else tb.decompress)()
+        torch.cuda.synchronize()
+    finally:
+        B.tagc_profile_enable(False)
+    assert "dense" in B.tagc_profile_read()
+    assert np.array_equal(tb.dense(), want)  # (an entry that cancels may be a zero of either sign)
+    tb.close()
