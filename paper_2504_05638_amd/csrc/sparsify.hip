@@ -1331,12 +1331,14 @@ hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t n
 
 // ------------------------------------------------------------------ small
 
-// A plan of few segments (kSmallSegments) that are all such that one workgroup's registers hold them takes one launch from
+// Few short segments (tagc_plan says which) take one launch from
 // the gradient to pairs, Index and counts: a workgroup that has found its segment's threshold has all its entries at hand.
 // What it cannot know is how many pairs the segments before it emit: as many as they are to keep, unless one has
 // fewer non-zeros than that.  So it looks, a wave a segment, at their first entries until it has seen so many
-// non-zeros, which is a few hundred entries and over before its own threshold is found.  Nobody waits for anybody.
-// us: hist1, count and place of five segments of 72 to 11 thousand fp32 entries, three ranks, 23.5; this 13.5.
+// non-zeros, which is one trip of 512 (bf16: 1024) entries where few are kept, and all of them where nearly all are zeros:
+// what eight trips have not settled is left to all waves, four times as wide (a wave to its end: 36 us where this
+// takes 18 and hist1, count and place 20, two segments of 25 thousand zeros before the last, eight ranks).  Nobody waits
+// for anybody.  us: hist1, count and place of five segments of 72 to 11 thousand fp32 entries, three ranks, 23.5; this 13.5.
 // The segment's pairs from position `base` of the rank's list on; and its Index words.
 template <int DTYPE>
 __device__ __forceinline__ void emit_small(const SegDev &sd, const uint4 (&v)[kSmallVecs], const SelDev &se, uint32_t base,
@@ -1406,23 +1408,22 @@ __device__ __forceinline__ void emit_small(const SegDev &sd, const uint4 (&v)[kS
     }
 }
 
-// By a wave: the pairs a segment emits, its non-zeros or what it is to keep.
-template <int DTYPE>
-__device__ inline uint32_t emitted_small(const SegDev &sd, const char *base)
+// By a wave: the non-zeros among a segment's entries `at` .. and so on, TURN vectors to a lane.
+template <int DTYPE, uint32_t TURN>
+__device__ inline uint32_t nonzeros_small(const SegDev &sd, const char *base, uint32_t at)
 {
-    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4, TURN = 2;
-    uint32_t n = 0;
-    for (uint32_t at = 0; at < sd.n && n < sd.k; at += TURN * 64 * VEC) {
-        uint32_t own = 0;
-        uint4 v[TURN];
+    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4;
+    uint32_t own = 0;
+    uint4 v[TURN];
 #pragma unroll
-        for (uint32_t i = 0; i < TURN; ++i) v[i] = load_vec<DTYPE>(base, at + (i * 64 + lane_id()) * VEC, sd.n);
+    for (uint32_t i = 0; i < TURN; ++i) v[i] = load_vec<DTYPE>(base, at + (i * 64 + lane_id()) * VEC, sd.n);
 #pragma unroll
-        for (uint32_t i = 0; i < TURN; ++i) for_keys<DTYPE>(v[i], [&](uint32_t, uint32_t) { ++own; });
-        n += __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(own), 63);
-    }
-    return min(n, sd.k);
+    for (uint32_t i = 0; i < TURN; ++i) for_keys<DTYPE>(v[i], [&](uint32_t, uint32_t) { ++own; });
+    return __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(own), 63);
 }
+
+constexpr uint32_t kSmallAlone = 8;  // trips of a wave alone, two vectors a lane each
+constexpr uint32_t kSmallTurn = 8;   // vectors a lane of a turn of all waves
 
 template <int DTYPE>
 __global__ void __launch_bounds__(kSmallThreads)
@@ -1431,7 +1432,7 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
     constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
     __shared__ uint32_t h[kBins1 / 2];
     __shared__ uint32_t smem[40];
-    __shared__ uint32_t s_base;
+    __shared__ uint32_t s_base, s_more, s_which[kSmallSegments], s_at[kSmallSegments], s_seen[kSmallSegments];
     const RankView rv = rank_view();
     const char *grad = rv.src();
     const uint32_t L = wl.L, l = blockIdx.x, tid = threadIdx.x;
@@ -1441,17 +1442,33 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
     const SegDev sd = segs[l];
     uint4 v[kSmallVecs];
     load_small<DTYPE>(v, sd, grad + sd.offset * EB);
-    if (tid == 0) s_base = 0;
+    if (tid == 0) s_base = s_more = 0;
     uint32_t dense = 0;  // segments that keep something (lane i has looked at segment i: they are 64 at most)
     if (l == L - 1) {
         const SegDev row = segs[min(lane_id(), L - 1)];
         dense = uint32_t(__popcll(__ballot(lane_id() < L && row.k && row.n)));
     }
     __syncthreads();
-    for (uint32_t i = wave; i < l; i += kSmallThreads / 64) {
+    // ---- the pairs before the segment's own: a wave a segment, until it has seen k non-zeros, or so few that it
+    // would not see them in ALONE entries
+    constexpr uint32_t NWV = kSmallThreads / 64, TRIP = 2 * 64 * 16 / EB, TURN = kSmallTurn * 64 * 16 / EB;
+    constexpr uint32_t ALONE = kSmallAlone * TRIP;
+    for (uint32_t i = wave; i < l; i += NWV) {
         const SegDev before = segs[i];
-        const uint32_t n = emitted_small<DTYPE>(before, grad + before.offset * EB);
-        if (n && lane_id() == 0) atomicAdd(&s_base, n);
+        uint32_t n = 0, at = 0;
+        while (at < before.n && n < before.k) {
+            n += nonzeros_small<DTYPE, 2>(before, grad + before.offset * EB, at);
+            at += TRIP;
+            if (at == ALONE || (before.n > ALONE && n * (ALONE / TRIP) < before.k * (at / TRIP))) break;
+        }
+        if (lane_id() == 0 && at < before.n && n < before.k) {
+            const uint32_t j = atomicAdd(&s_more, 1u);
+            s_which[j] = i;
+            s_at[j] = at;
+            s_seen[j] = n;
+        } else if (lane_id() == 0 && n) {
+            atomicAdd(&s_base, min(n, before.k));
+        }
     }
     const bool keeps = sd.k != 0 && sd.n != 0;
     SelDev r{};  // (no entry is above the largest key)
@@ -1471,7 +1488,25 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
         }
         came = atomicAdd(&ts.arrive[0], nonfinite ? 1u + kSome : 1u);
     }
-    __syncthreads();  // h, s_base
+    __syncthreads();  // h, s_base, s_more
+    // ---- what such waves have left over, by all of them
+    const uint32_t more = __builtin_amdgcn_readfirstlane(s_more);
+    if (more) {
+        for (uint32_t j = 0, turn = wave; j < more; ++j) {
+            const SegDev before = segs[__builtin_amdgcn_readfirstlane(s_which[j])];
+            const uint32_t from = __builtin_amdgcn_readfirstlane(s_at[j]);
+            for (uint32_t at = from + turn % NWV * TURN; at < before.n; at += NWV * TURN) {
+                if (__hip_atomic_load(&s_seen[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= before.k) break;
+                const uint32_t n = nonzeros_small<DTYPE, kSmallTurn>(before, grad + before.offset * EB, at);
+                if (n && lane_id() == 0) atomicAdd(&s_seen[j], n);
+            }
+            // (the next one's first turn is for the wave behind the last turn's)
+            turn += NWV - (before.n - from + TURN - 1) / TURN % NWV;
+        }
+        __syncthreads();
+        if (tid < more) atomicAdd(&s_base, min(s_seen[tid], segs[s_which[tid]].k));
+        __syncthreads();
+    }
     const uint32_t base = s_base;
     if (sd.n) emit_small<DTYPE>(sd, v, r, base, rv.idx, rv.val, rv.bitmap, h);  // uniform
     if (tid == 0) {
@@ -2532,14 +2567,14 @@ SparsifyRank sparsify_rank(const tagc_plan_t *p, const void *grad, const tagc_ra
 
 // The first kernels of PHASE_INDEX, up to every segment's threshold (fp32: its upper half), for
 // n ranks with workspaces and table slots of their own, all with an accumulator (`acc`) or none
-// with one.  `sample`: no pre-threshold is known yet.
+// with one.  `sample`: no pre-threshold is known yet.  `one`: small_kernel does it all, launch_output's part as well.
 //
 // Error feedback: scan_spill (candidate route) and accumulate_kernel (all other segments) turn
 // acc into grad + acc; whoever reads the input after them reads it from acc.  Both read acc
 // through the Index this rank's previous call left in rk->bitmap (what was sent reads as 0)
 // before place / widen4 overwrite that Index with the new one.
 template <int DTYPE>
-int launch_select(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, bool acc, bool sample,
+int launch_select(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, bool acc, bool sample, bool one,
                   uint32_t *table, hipStream_t s)
 {
     const WsLayout wl = ws_layout(p);
@@ -2554,7 +2589,7 @@ int launch_select(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, boo
         ProfileScope ps("accumulate", s);
         accumulate_kernel<DTYPE><<<dim3(per_rank(cus * 4), n), 256, 0, s>>>(sb, table, wide);
     }
-    if (p->all_small) {
+    if (one) {
         ProfileScope ps("small", s);
         small_kernel<DTYPE><<<dim3(uint32_t(p->table.size()), n), kSmallThreads, 0, s>>>(sb, table, wl);
         return TAGC_OK;
@@ -2603,7 +2638,7 @@ int launch_select(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, boo
 
 // The rest of PHASE_INDEX for the same ranks: the thresholds' lower half (fp32), counts, output.
 template <int DTYPE>
-int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uint32_t *table,
+int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, bool one, uint32_t *table,
                   hipStream_t s)
 {
     const WsLayout wl = ws_layout(p);
@@ -2625,7 +2660,7 @@ int launch_output(const tagc_plan_t *p, const SparsifyBatch &sb, uint32_t n, uin
         const uint32_t grid = std::max(n_cand, n_dense);
         refine_kernel<<<dim3(grid, n), 256, 0, s>>>(sb, table, wl, p->cand_cap, n_cand, n_dense);
     }
-    if (!p->all_small) {
+    if (!one) {
         // the plan fixed the compaction tile's height, and with it which kernels these are
         const bool rows4 = p->compact_rows == 4;
         const bool many = count_from_memory(p, n);
@@ -2689,13 +2724,17 @@ int launch_sparsify_t(const tagc_plan_t *p, const void *const *grads, const tagc
         return hip_ok(hipGetLastError());
     }
     const bool acc = ranks[0].acc != nullptr;
+    // (with a compute unit for every workgroup: 32 ranks of 9, 12, 20 segments with a little under 200 KiB each, nearly all
+    // zeros, three launches / one 28.1 / 33.4, 29.4 / 38.2, 31.8 / 43.6 us, of 7 segments 0.9; 32 of 28 short
+    // ones without zeros 40 / 51, 8 of them 0.8)
+    const bool one = p->all_small && uint64_t(L) * n <= uint64_t(device_cu_count());
     SparsifyBatch sb{};
     SparsifyBatch part{};  // the ranks whose thresholds are launched next
     uint32_t n_part = 0;
     bool sample = false;
     auto select = [&]() -> int {
         if (!n_part) return TAGC_OK;
-        const int rc = launch_select<DTYPE>(p, part, n_part, acc, sample, table, s);
+        const int rc = launch_select<DTYPE>(p, part, n_part, acc, sample, one, table, s);
         n_part = 0;
         sample = false;
         return rc;
@@ -2715,7 +2754,7 @@ int launch_sparsify_t(const tagc_plan_t *p, const void *const *grads, const tagc
             if (const int rc = select()) return rc;
     }
     if (const int rc = select()) return rc;
-    return launch_output<DTYPE>(p, sb, n, table, s);
+    return launch_output<DTYPE>(p, sb, n, one, table, s);
 }
 
 }  // namespace

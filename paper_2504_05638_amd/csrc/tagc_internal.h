@@ -21,7 +21,9 @@ constexpr uint32_t kDenseThreads = 256;   // dense route's histogram; ...
 constexpr uint32_t kSmallThreads = 1024;  // ... of a plan with segments one workgroup holds
 constexpr uint32_t kDenseRows = 4;        // 16-byte vectors per thread and tile of it
 constexpr uint32_t kSmallVecs = 8;        // 16-byte vectors per thread such a segment has at most
-constexpr uint32_t kSmallSegments = 64;   // segments up to which a plan of such segments takes one launch
+constexpr uint32_t kSmallSegments = 64;   // segments up to which a plan of such segments takes one launch, ...
+constexpr uint32_t kSmallPairs = 80 * 1024;    // ... entries and four times those kept of each, ...
+constexpr uint32_t kSmallBefore = 192 * 1024;  // ... and bytes before the last (see tagc_plan)
 constexpr uint32_t kHistWindow = 4096;
 constexpr uint32_t kCandRows = 4;        // 16-byte vectors per lane per candidate chunk
 constexpr uint32_t kCandChunksPerSuper = 32;  // chunks that a wave of place takes
@@ -173,7 +175,7 @@ struct tagc_plan_s {
     bool static_dense;                        // some segment with k > 0 never takes the candidate route
     bool any_fast;                            // some segment takes it
     bool small_dense;                         // some dense-route segment is kSegSmall
-    bool all_small;                           // one workgroup's registers hold any of the segments, which are few
+    bool all_small;                           // a workgroup a segment is the faster sparsifier if all run at once
     uint64_t span_dense;                      // entries of the dense-route segments that are not
     uint64_t dense_pairs;                     // pairs the dense-route segments emit at most
     uint64_t n_real, n_c, K, U_cap, A_cap, m_cap;

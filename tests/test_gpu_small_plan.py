@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2504_05638_amd import binding as B
 from synth import gradients as G
 from tests.helpers import run_both, compare_all
 
@@ -81,3 +82,68 @@ def test_not_finite(dtype):
         cnt = tb.rank_counts(0)
         assert cnt["nonfinite"] == len(bad) and cnt["dense_segments"] == 3 and cnt["total"] == sum(cnt["seg"])
     tb.close()
+
+
+def _took(segs, n, dtype, ranks):
+    """The sparsifier's kernels in the second call on a plan."""
+    from paper_2504_05638_amd.bucket import TagcBucket
+    tb = TagcBucket(segs, dtype, ranks)
+    g = [torch.ones(n, device="cuda", dtype=torch.float32 if dtype == G.F32 else torch.bfloat16)] * ranks
+    tb.compress_index_all(g)
+    torch.cuda.synchronize()
+    B.tagc_profile_enable(True)
+    try:
+        tb.compress_index_all(g)
+        torch.cuda.synchronize()
+    finally:
+        B.tagc_profile_enable(False)
+    tb.close()
+    return set(B.tagc_profile_read())
+
+
+# Lengths, kept (ppm), ranks; whether one launch takes them.  What a workgroup would be slower over than the device
+# is left to the device: too many pairs of a segment, too much in front of the last (all of which has to be looked
+# through if it is zeros), more workgroups than compute units; and a plan that keeps nothing.
+@pytest.mark.parametrize("dtype,lengths,ppm,ranks,one", [
+    (G.F32, [32768], 375_000, 1, True), (G.F32, [32768], 376_000, 1, False),
+    (G.BF16, [65535], 62_000, 1, True), (G.BF16, [65535], 63_000, 1, False),
+    (G.BF16, [8192], 1_000_000, 1, True), (G.BF16, [8193], 1_000_000, 1, False), (G.BF16, [8700], 945_000, 1, True),
+    (G.F32, [24576, 24576, 30_000], 20_000, 2, True), (G.F32, [24576, 24577, 300], 20_000, 2, False),
+    (G.BF16, [49152, 49152, 30_000], 20_000, 2, True), (G.BF16, [49152, 49153, 300], 20_000, 2, False),
+    (G.F32, [700] * 8, 20_000, 32, True), (G.F32, [700] * 9, 20_000, 32, False),
+    (G.F32, [700] * 64, 20_000, 4, True), (G.F32, [700] * 65, 20_000, 1, False), (G.BF16, [40] * 7, 20_000, 2, False)])
+def test_which_plans_take_one_launch(dtype, lengths, ppm, ranks, one):
+    print("\n[case] small plan, route dtype=%d lengths=%s ppm=%d ranks=%d" % (dtype, lengths[:3], ppm, ranks), flush=True)
+    segs, n = _segments(lengths, [ppm])
+    took = _took(segs, n, dtype, ranks)
+    assert ("small" in took, "place" in took) == (one, not one), took
+
+
+# What a wave has not settled in eight trips (4096 entries, bf16 8192) all waves look through: non-zeros before and behind
+# that, exactly as many as are kept up to an edge of it and one fewer, several such segments at once
+@pytest.mark.parametrize("dtype,alone", [(G.F32, 4096), (G.BF16, 8192)])
+@pytest.mark.parametrize("at", ["front", "spread", "behind", "end", "none"])
+def test_what_one_wave_leaves(dtype, alone, at):
+    print("\n[case] small plan, left to all waves dtype=%d at=%s" % (dtype, at), flush=True)
+    lengths = [alone, alone + 1, alone + 77, 3 * alone - 5, 5000, 18_003 if dtype == G.F32 else 30_003, 901]
+    for kept in (60, 700):
+        segs, at0 = [], 0
+        for i, n in enumerate(lengths):
+            segs.append(G.Seg(at0, n, 1_000_000 * kept // n + 1, 1, "s%d" % i))
+            at0 += n
+        b = G.Bucket("small", dtype, 3, segs, at0, 1500)
+        rng = np.random.default_rng(kept)
+        grads = []
+        for r in range(3):  # one non-zero fewer than are kept, as many, one more
+            x = np.zeros(at0)
+            for s in segs:
+                k = s.length * s.keep_ppm // 1_000_000
+                n = 0 if at == "none" else k - 1 + r
+                lo, hi = {"front": (0, n), "behind": (alone, s.length), "end": (s.length - n, s.length)}.get(at, (0, s.length))
+                lo = min(lo, s.length - n)
+                x[s.offset + rng.choice(np.arange(lo, max(hi, lo + n)), n, replace=False)] = rng.integers(1, 120, n)
+            grads.append(torch.from_numpy(x.astype(np.float32)).to(torch.float32 if dtype == G.F32 else torch.bfloat16))
+        ores, tb = run_both(b, grads, seed=6)
+        compare_all(b, ores, tb, exact_values=True)
+        tb.close()
+        assert "small" in _took(segs, at0, dtype, 3)
