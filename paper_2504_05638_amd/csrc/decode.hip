@@ -764,7 +764,6 @@ __device__ __forceinline__ void write_dense(const PartLds<true> &p, uint32_t tid
 // (after an overflow, when bits are set all the same).  A wave takes 16 words at a time, the next of which are on
 // their way.
 constexpr uint32_t kZeroWords = 16;
-constexpr uint32_t kZeroShare = 512 * 1024;  // entries of the output for each such workgroup at most
 __device__ __forceinline__ void write_zeros(const IndexView &index, uint32_t b, uint32_t n, bool all, float *__restrict__ out)
 {
     const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1369,18 +1368,24 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     const bool with_dense = early && (form == 1 || form == 2) && p->A_cap >= 3ull * grid &&
                             p->K >= uint64_t(grid) * p->P_cap;
     // Where there are fewer partitions than compute units, workgroups on the others write the dense output's zeros
-    // meanwhile, and the decoder its values among them.  As long as a workgroup has no more to write than about what a
-    // peel and dense_kernel would take it: decoder and dense output of the sum / of one summed sketch, us, dense_kernel
-    // / this way, by partitions and entries per writing workgroup: 2, 1 K 27.8, 27.3 / 23.7, 23.1; 11, 4 K 23.0, 21.8 / 18.6, 17.5;
-    // 80, 47 K 38.1, 34.6 / 38.5, 31.4; 119, 93 K 42.9, 39.1 / 43.6, 33.2; 159, 178 K 48.2, 42.9 / 47.7, 36.0; 82, 188 K
-    // 58.7, 56.1 / 44.2, 38.2; 204, 381 K 51.3, 44.2 / 48.4, 43.3; 66, 344 K 84.1, 81.4 / 83.7, 80.8; 131, 528 K 89.5,
-    // 84.4 / 72.5, 75.1; one rank of 1 M with 5 to 40 % kept 30.3 to 33.6 / 27.3 to 26.1, of 4 M with two fifths in 205
-    // partitions 38.4 / 30.9.  (The sum of eight ranks needs the memory itself.)  Plans with partitions of another size
-    // than the default keep the launch: what is peeled in a few us was not measured, and a test counts on it.
+    // meanwhile, and the decoder its values among them.  Such a workgroup stores 7.7 thousand entries a us, so it may have
+    // as many as that makes of what the peel and dense_kernel would take: 100 Ki, 16 for each unknown of a partition,
+    // and a 180th of the output (1.4 M entries a us).  Decoder and dense output, us, dense_kernel / this way, by the
+    // share of that limit that such a workgroup has, the summed sketch, partitions of 8192: 0.2 32.6 / 28.8 (80
+    // partitions of 3 M entries), 0.5 41.6 / 36.6 (156 of 16 M), 0.7 61.2 / 40.3 (100 of 41 M), 0.8 54.3 / 44.3 (157 of
+    // 32 M), 0.9 83.4 / 74.6 (131 of 67 M), 1.0 45.9 / 46.3 (200 of 19 M), 1.15 46.1 / 50.0 (200 of 21 M), 1.3 60.4 /
+    // 71.3 (187 of 39 M); of 2048 unknowns 0.7 24.8 / 21.4, 1.1 27.9 / 29.8 (200 of 8, 12 M); of 512 0.8 19.9 / 17.2, 1.1
+    // 22.2 / 25.6 (200 of 7, 11 M); of 32 0.8 19.4 / 16.2, 1.1 21.3 / 24.2 (200 of 6, 10 M).
+    // The sum of many ranks needs the memory itself, and where there is some to write, but not so much that the launch behind
+    // it takes long, loses what that would take: 8 ranks, 0.8 M entries 37.7 / 31.1, 3 M 39.1 / 35.2, 6 M 35.1 /
+    // 36.0, 8 M 37.3 / 38.7, 12 M 41.6 / 44.8, 16 M 46.4 / 46.4, 19 M 51.5 / 48.7, 24 M 52.9 / 47.6; 16 ranks, 3 M 41.7 /
+    // 39.6, 6 M 42.7 / 45.0, 10 M 53.9 / 56.4, 16 M 51.1 / 48.2; 4 ranks, 6 M 34.3 / 34.5, 8 M 38.1 / 38.1, 12 M 38.8 / 37.8.
+    // (Plans whose unknowns are listed have no such decoder: it would be one form more.)
     const uint32_t cus = uint32_t(device_cu_count());
-    const bool whole = p->P_cap == kDefaultPartUnknowns && p->T_cap == kDefaultPartCells;
-    const uint32_t spare = early && form == 3 && whole && p->A_cap < cus ? cus - uint32_t(p->A_cap) : 0u;
-    const bool with_zeros = n_words && spare && n_ranks <= kDenseRow && p->n_c <= uint64_t(spare) * kZeroShare;
+    const uint32_t spare = early && form == 3 && p->A_cap < cus ? cus - uint32_t(p->A_cap) : 0u;
+    const uint64_t share = 100 * 1024 + 16ull * p->P_cap + p->n_c / 180;
+    const bool crowded = n_ranks > kHeldRanks && p->n_c >= 4u << 20 && p->n_c < 16u << 20;
+    const bool with_zeros = n_words && n_ranks <= kDenseRow && p->n_c <= spare * share && !crowded;
     if (with_zeros) grid += std::min(spare, (n_words + kZeroWords * (kDecodeThreads / 64) - 1) / (kZeroWords * (kDecodeThreads / 64)));
     const auto kernel = with_zeros ? peel_kernel<kC0, kI0, true, kHeldRanks, true, false, true>
                         : with_dense ? (form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false, false, true>

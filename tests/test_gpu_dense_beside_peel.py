@@ -47,8 +47,8 @@ def test_nothing_kept():
     tb.close()
 
 
-# The launch that writes all of it (partitions of another size have it): 256 words to a workgroup, of which a quarter's
-# values are staged
+# The launch that writes all of it (a plan that limits the decoder's workgroups has it): 256 words to a workgroup, of which
+# a quarter's values are staged
 @pytest.mark.parametrize("words", [255, 256, 257, 1023, 1025, 2300])
 @pytest.mark.parametrize("ppm", [100_000, 700_000])
 def test_a_launch_of_its_own(words, ppm):
@@ -56,7 +56,7 @@ def test_a_launch_of_its_own(words, ppm):
     n = 32 * words - 3
     b = G.Bucket("dense", G.F32, 1, [G.Seg(0, n, ppm, 1, "a")], n, 1500)
     g = torch.from_numpy(np.random.default_rng(words).integers(1, 100, n).astype(np.float32))
-    ores, tb = run_both(b, [g], seed=5, P=256, T=384)
+    ores, tb = run_both(b, [g], seed=5, P=256, T=384, decode_workgroups=200)
     tb.out_dense.view(torch.int32).fill_(-1)
     tb.run([g.cuda()])
     torch.cuda.synchronize()
@@ -141,4 +141,41 @@ def test_in_the_place_of_what_was_read(fused, where, n, P, T):
         B.tagc_profile_enable(False)
     assert "dense" in B.tagc_profile_read()
     assert np.array_equal(tb.dense(), want)  # (an entry that cancels may be a zero of either sign)
+    tb.close()
+
+
+def _took(tb, fused):
+    """The kernels of a decode into a filled output, which is then what the unknowns and their values say."""
+    from paper_2504_05638_amd import binding as B
+    tb.out_dense.view(torch.int32).fill_(-1)
+    torch.cuda.synchronize()
+    B.tagc_profile_enable(True)
+    try:
+        (tb.reduce_decompress if fused else tb.decompress)()
+        torch.cuda.synchronize()
+    finally:
+        B.tagc_profile_enable(False)
+    idx, val = tb.outputs()
+    want = np.zeros(tb.sizes.n_c, np.float32)
+    want[idx] = val
+    assert np.array_equal(tb.dense().view(np.uint32), want.view(np.uint32))
+    return set(B.tagc_profile_read())
+
+
+# Where the lines lie: what a writing workgroup may have (partitions of 32 unknowns, 200 of them, 56 workgroups left, some
+# eighteen turns of 16 words a wave each; 8192 unknowns, 30 partitions), and the sum of more than four ranks into 16 to 64 MB
+@pytest.mark.parametrize("n,ppm,ranks,P,T,fused,beside", [
+    (8_364_000, 765, 1, 32, 48, True, True), (8_367_000, 765, 1, 32, 48, True, False), (8_364_033, 765, 1, 32, 48, False, True),
+    (3_999_969, 15_000, 4, 0, 0, True, True),
+    ((4 << 20) - 32, 9500, 5, 0, 0, True, True), (4 << 20, 9500, 5, 0, 0, True, False), (4 << 20, 9500, 5, 0, 0, False, True),
+    (4 << 20, 9500, 4, 0, 0, True, True), ((16 << 20) - 32, 3500, 5, 0, 0, True, False), (16 << 20, 3500, 5, 0, 0, True, True)])
+def test_who_writes_it(n, ppm, ranks, P, T, fused, beside):
+    from paper_2504_05638_amd.bucket import TagcBucket
+    print("\n[case] dense beside peel or behind n=%d ranks=%d P=%d fused=%d" % (n, ranks, P, fused), flush=True)
+    tb = TagcBucket([(0, n, ppm, 1)], G.F32, ranks, part_unknowns=P, part_cells=T, dense=True,
+                    sizing_milli=1500)
+    assert tb.sizes.partition_capacity == 200 if P else tb.sizes.partition_capacity < 60
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    tb.run([torch.randn(n, device="cuda", generator=gen) for _ in range(ranks)], fused=fused)
+    assert ("dense" in _took(tb, fused)) != beside
     tb.close()
