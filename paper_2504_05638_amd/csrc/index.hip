@@ -255,12 +255,15 @@ constexpr uint32_t kSecondWords = 1024;   // second filter, cleared a word per t
 static_assert(kSecondWords == kSaltThreads, "every thread clears its word");
 // Index words up to which the layout merges the ranks' Indexes itself: four of each to a thread, kept in LDS, where
 // everything that is looked up in the merged Index then is.  Every workgroup merges them all, so they are few and read
-// little.  us of the Index aggregation, merge and layout / layout alone: 33 thousand entries from 3 ranks 13.4 / 9.8, 66
-// thousand from 1, 8, 16 ranks 13.4, 15.5, 17.1 / 9.7, 11.8, 12.3, 131 thousand from 1, 4, 8 ranks 14.6, 15.3, 16.9 / 11.5, 12.3,
-// 13.4, with 32 partitions 16.7 / 12.6.
+// little.  us of the Index aggregation, merge and layout / layout alone: 33 thousand entries from 1, 8, 16 ranks 14.5, 15.7,
+// 17.2 / 11.1, 11.9, 12.4, 66 thousand 16.6, 19.9, 23.4 / 12.3, 13.3, 13.6, 131 thousand from 1, 4, 8 ranks 16.8, 17.1, 17.5 /
+// 13.1, 13.4, 13.9; in 52 partitions 15.9 / 11.8 (4 ranks).  4-bit counters: a thread has four vectors of a rank, and more
+// than eight ranks' go out in too many trips: 8 thousand entries from 8, 16, 32 ranks 15.3, 15.6, 16.6 / 13.7, 16.5, 21.3, 33
+// thousand from 8 18.2 / 15.3.
 constexpr uint32_t kMergeWords = 4 * kSaltThreads;
 constexpr uint32_t kMergeMost = 64;             // partitions of the plan at most
 constexpr uint32_t kMergeBytes = 128 * 1024;    // of all ranks' Indexes
+constexpr uint32_t kMergeRanks4 = 8;            // ranks of 4-bit counters
 constexpr uint32_t kSaltPer = kDefaultPartUnknowns / kSaltThreads;  // non-zeros per thread of a partition of the default size
 constexpr uint32_t kSaltPre = 4;          // Index words per thread requested a partition ahead
 
@@ -667,8 +670,10 @@ int launch_index_or(const tagc_plan_t *p, const tagc_rank_buffers *ranks, uint32
     // Small Indexes are merged by the layout, whose workgroups are few then.  Each reads all of the ranks' Indexes and
     // one writes the merged one meanwhile, so not where that takes a rank's own place (a merge of its own reads
     // and writes word by word).
-    const uint64_t wire_bytes = uint64_t(n_words) * (p->cfg.index_mode == TAGC_INDEX_ADD4 ? 16 : 4);
-    bool merges = n_chunks && n_words <= kMergeWords && p->A_cap <= kMergeMost && n_ranks <= kMaxRanksPerPass &&
+    const bool add4 = p->cfg.index_mode == TAGC_INDEX_ADD4;
+    const uint64_t wire_bytes = uint64_t(n_words) * (add4 ? 16 : 4);
+    bool merges = n_chunks && n_words <= kMergeWords && p->A_cap <= kMergeMost &&
+                  n_ranks <= (add4 ? kMergeRanks4 : kMaxRanksPerPass) &&
                   n_ranks * wire_bytes <= kMergeBytes;
     for (uint32_t r = 0; merges && r < n_ranks; ++r)
         merges = !overlap(sh->bitmap, 4ull * n_words, ranks[r].bitmap, wire_bytes);

@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("words", [1, 3, 5, 64, 65, 1023, 1025, 2048, 4095, 4096, 4097])
-@pytest.mark.parametrize("ranks,mode", [(1, O.INDEX_OR1), (3, O.INDEX_OR1), (5, O.INDEX_ADD1), (2, O.INDEX_ADD4), (9, O.INDEX_OR1)])
+@pytest.mark.parametrize("ranks,mode", [(1, O.INDEX_OR1), (3, O.INDEX_OR1), (5, O.INDEX_ADD1), (2, O.INDEX_ADD4), (9, O.INDEX_OR1),
+                                        (8, O.INDEX_ADD4), (9, O.INDEX_ADD4)])
 def test_merged_by_the_layout(words, ranks, mode):
     print("\n[case] small index words=%d ranks=%d mode=%d" % (words, ranks, mode), flush=True)
     n = 32 * words - 5  # (padding bits at the end)
@@ -30,7 +31,8 @@ def test_merged_by_the_layout(words, ranks, mode):
     finally:
         B.tagc_profile_enable(False)
     bytes_ = ranks * words * (16 if mode == O.INDEX_ADD4 else 4)
-    assert ("index_or" in B.tagc_profile_read()) == (words > 4096 or bytes_ > 128 * 1024)
+    assert ("index_or" in B.tagc_profile_read()) == (words > 4096 or bytes_ > 128 * 1024 or
+                                                            (mode == O.INDEX_ADD4 and ranks > 8))
     compare_all(b, ores, tb, exact_values=True)
     tb.close()
 
