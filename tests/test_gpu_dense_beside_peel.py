@@ -11,6 +11,24 @@ from tests.helpers import run_both, compare_all
 pytestmark = pytest.mark.gpu
 
 
+def _took(tb, fused):
+    """The kernels of a decode into a filled output, which is then what the unknowns and their values say."""
+    from paper_2504_05638_amd import binding as B
+    tb.out_dense.view(torch.int32).fill_(-1)
+    torch.cuda.synchronize()
+    B.tagc_profile_enable(True)
+    try:
+        (tb.reduce_decompress if fused else tb.decompress)()
+        torch.cuda.synchronize()
+    finally:
+        B.tagc_profile_enable(False)
+    idx, val = tb.outputs()
+    want = np.zeros(tb.sizes.n_c, np.float32)
+    want[idx] = val
+    assert np.array_equal(tb.dense().view(np.uint32), want.view(np.uint32))
+    return set(B.tagc_profile_read())
+
+
 @pytest.mark.parametrize("n", [1, 33, 511, 513, 8191, 8193, 100_003])
 @pytest.mark.parametrize("ranks,fused", [(1, False), (3, True), (31, True), (32, True)])
 def test_every_entry_is_written(n, ranks, fused):
@@ -22,14 +40,7 @@ def test_every_entry_is_written(n, ranks, fused):
     for g in grads:  # (of the second segment little is kept all the same: zeros never are)
         g[n:2 * n][torch.from_numpy(rng.random(n) < 0.9)] = 0
     ores, tb = run_both(b, grads, seed=5, fused=fused)
-    tb.out_dense.view(torch.int32).fill_(-1)
-    (tb.reduce_decompress if fused else tb.decompress)()
-    torch.cuda.synchronize()
-    tb.status()
-    idx, val = tb.outputs()
-    want = np.zeros(tb.sizes.n_c, np.float32)
-    want[idx] = val
-    assert np.array_equal(tb.dense().view(np.uint32), want.view(np.uint32))
+    assert ("dense" in _took(tb, fused)) == (ranks > 31)  # (32 ranks leave no room for the output's address)
     tb.run([g.cuda() for g in grads], fused=fused)
     torch.cuda.synchronize()
     compare_all(b, ores, tb, exact_values=True)
@@ -44,6 +55,7 @@ def test_nothing_kept():
     tb.run([torch.zeros(300_000, device="cuda")] * 2, fused=True)
     torch.cuda.synchronize()
     assert tb.header()["U"] == 0 and not tb.dense().view(np.uint32).any()
+    assert "dense" not in _took(tb, True)
     tb.close()
 
 
@@ -61,6 +73,7 @@ def test_a_launch_of_its_own(words, ppm):
     tb.run([g.cuda()])
     torch.cuda.synchronize()
     compare_all(b, ores, tb, exact_values=True)
+    assert "dense" in _took(tb, False)
     tb.close()
 
 
@@ -142,24 +155,6 @@ def test_in_the_place_of_what_was_read(fused, where, n, P, T):
     assert "dense" in B.tagc_profile_read()
     assert np.array_equal(tb.dense(), want)  # (an entry that cancels may be a zero of either sign)
     tb.close()
-
-
-def _took(tb, fused):
-    """The kernels of a decode into a filled output, which is then what the unknowns and their values say."""
-    from paper_2504_05638_amd import binding as B
-    tb.out_dense.view(torch.int32).fill_(-1)
-    torch.cuda.synchronize()
-    B.tagc_profile_enable(True)
-    try:
-        (tb.reduce_decompress if fused else tb.decompress)()
-        torch.cuda.synchronize()
-    finally:
-        B.tagc_profile_enable(False)
-    idx, val = tb.outputs()
-    want = np.zeros(tb.sizes.n_c, np.float32)
-    want[idx] = val
-    assert np.array_equal(tb.dense().view(np.uint32), want.view(np.uint32))
-    return set(B.tagc_profile_read())
 
 
 # Where the lines lie: what a writing workgroup may have (partitions of 32 unknowns, 200 of them, 56 workgroups left, some

@@ -6,15 +6,16 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import tagc_oracle as O
 from paper_2504_05638_amd import binding as B
 from synth import gradients as G
-from tests.helpers import run_both, compare_all
+from tests.helpers import run_both, compare_all, oracle_config, oracle_segments
 
 pytestmark = pytest.mark.gpu
 
 
-def _run(segs, n, dtype, zeros, ranks=2, ties=False, error_feedback=False):
-    """`zeros`: segments left with three non-zeros, by rank."""
+def _run(segs, n, dtype, zeros, ranks=2, ties=False, one=True):
+    """`zeros`: segments left with three non-zeros, by rank; `one`: whether one launch takes them."""
     b = G.Bucket("small", dtype, ranks, segs, n, 1500)
     rng = np.random.default_rng(n)
     td = torch.float32 if dtype == G.F32 else torch.bfloat16
@@ -28,8 +29,14 @@ def _run(segs, n, dtype, zeros, ranks=2, ties=False, error_feedback=False):
     ores, tb = run_both(b, grads, seed=6)
     compare_all(b, ores, tb, exact_values=True)
     for _ in range(2):  # the counters are back where they were
-        tb.run([g.cuda() for g in grads])
-        torch.cuda.synchronize()
+        B.tagc_profile_enable(True)
+        try:
+            tb.run([g.cuda() for g in grads])
+            torch.cuda.synchronize()
+        finally:
+            B.tagc_profile_enable(False)
+        took = B.tagc_profile_read()
+        assert ("small" in took, "place" in took) == (one, not one), took
         compare_all(b, ores, tb, exact_values=True)
     tb.close()
 
@@ -56,7 +63,7 @@ def test_segments_that_fall_short(dtype, zeros, ties):
 def test_many_segments(dtype, zeros, count):
     print("\n[case] small plan, %d segments dtype=%d zeros=%s" % (count, dtype, zeros), flush=True)
     segs, n = _segments([33 + 7 * (i % 5) for i in range(count)], [200_000, 400_000], gap=1)
-    _run(segs, n, dtype, zeros)
+    _run(segs, n, dtype, zeros, one=count <= 64)
 
 
 @pytest.mark.parametrize("dtype,most", [(G.F32, 32768), (G.BF16, 65535)])
@@ -65,7 +72,7 @@ def test_the_largest_segment_and_one_more(dtype, most, more):
     print("\n[case] small plan dtype=%d n=%d" % (dtype, most + more), flush=True)
     segs = [G.Seg(1, most + more, 30_000, 1, "a"), G.Seg(most + 5, 0, 30_000, 1, "b"), G.Seg(most + 5, 999, 0, 1, "c"),
             G.Seg(most + 1007, 31, 1_000_000, 1, "d")]
-    _run(segs, most + 1038, dtype, ((0,), ()))
+    _run(segs, most + 1038, dtype, ((0,), ()), one=not more)
 
 
 @pytest.mark.parametrize("dtype", [G.F32, G.BF16])
@@ -147,3 +154,49 @@ def test_what_one_wave_leaves(dtype, alone, at):
         compare_all(b, ores, tb, exact_values=True)
         tb.close()
         assert "small" in _took(segs, at0, dtype, 3)
+
+
+# With an accumulator: the launch before replaces the gradient by the sum, read through the Index that this one then writes
+# anew; bit for bit the oracle's over a few steps, the scale changing between them
+@pytest.mark.parametrize("dtype", [G.F32, G.BF16])
+@pytest.mark.parametrize("index_mode", [O.INDEX_OR1, O.INDEX_ADD4])
+def test_with_an_accumulator(dtype, index_mode):
+    from paper_2504_05638_amd.bucket import TagcBucket
+    print("\n[case] small plan, accumulator dtype=%d mode=%d" % (dtype, index_mode), flush=True)
+    segs, n = _segments([4097, 1023, 20_001, 777, 31], [20_000, 300_000, 50_000, 0], gap=3)
+    n = segs[-1].offset + segs[-1].length
+    ranks, td = 2, torch.float32 if dtype == G.F32 else torch.bfloat16
+    b = G.Bucket("small", dtype, ranks, segs, n, 1500)
+    cfg, osegs = oracle_config(b, seed=3, index_mode=index_mode), oracle_segments(b)
+    tb = TagcBucket(segs, dtype, ranks, sizing_milli=1500, seed=3, error_feedback=True, index_mode=index_mode)
+    acc = [np.zeros(n, np.uint16 if dtype == G.BF16 else np.float32) for _ in range(ranks)]
+    B.tagc_profile_enable(True)
+    try:
+        for step, scale in enumerate([1.0, 1.0, 100.0, 1e-3, 1.0]):
+            gen = torch.Generator().manual_seed(step)
+            grads = [(torch.randn(n, generator=gen) * scale).to(td) for _ in range(ranks)]
+            states = []
+            for r in range(ranks):
+                state, acc[r] = O.error_feedback_step(G.to_numpy_raw(grads[r]), acc[r], cfg, osegs)
+                states.append(state)
+            tb.run([g.cuda() for g in grads])
+            torch.cuda.synchronize()
+            for r in range(ranks):
+                idx, val = tb.rank_pairs(r)
+                assert np.array_equal(idx, states[r].idx), (step, r)
+                assert np.array_equal(val.view(np.uint32), states[r].val.view(np.uint32)), (step, r)
+                local = states[r].bitmap[:tb.sizes.bitmap_words]
+                assert np.array_equal(tb.rank_bitmap(r), O.index_widen4(local) if index_mode == O.INDEX_ADD4 else local)
+                if step % 2:  # (the next step does not depend on it)
+                    tb.feedback_apply(r)
+                    torch.cuda.synchronize()
+                    got = tb.rank_acc(r)[:n]
+                    keep = np.zeros(n, bool)
+                    for s in segs:
+                        keep[s.offset:s.offset + s.length] = True
+                    assert np.array_equal(got[keep], acc[r].view(got.dtype)[keep]), (step, r)
+    finally:
+        B.tagc_profile_enable(False)
+    took = B.tagc_profile_read()
+    assert {"accumulate", "small"} <= set(took) and "place" not in took, took
+    tb.close()
