@@ -300,12 +300,12 @@ __device__ __forceinline__ void queue_first(const PartLds<kPacked> &p, uint32_t 
 // up the whole wave (decoders of 2 ranks of 202 M entries with a tenth kept 647 -> 612 us, of 4 ranks of 9 M with two
 // fifths 108 -> 104.5).  A wave that is alone with a round (kAlone: 64 entries at most) adds natively at once: a
 // partition that gets stuck after 40 rounds, most of them such, 35.7 -> 34.1.  (In all rounds: sixteen waves' adds
-// take 49 clocks each, a swap is not felt.)  A wave with one entry takes 1100 clocks for it, 16 full ones 2100 and a barrier
-// 400, before that change: latency and the wave's own 130 instructions (fewer vector instructions, 87
-// for 110, changed nothing).  Rounds of a partition, clocks, before the arrays were as in PartLds and failed swaps
-// repeated alone, and after: 8192 unknowns in 12288 cells (11 rounds) 38.8 K -> 32.0 K; in 10776 cells (21
-// rounds) 51.1 K -> 43.3 K.  (A queue for every wave, without a shared count: 826 us where 647 were, every wave then
-// has a few entries of every small round.)
+// take 49 clocks each, a swap is not felt.)  Measured while failed swaps were still made again: a wave with one entry
+// takes 1100 clocks for it, 16 full ones 2100 and a barrier 400, which is latency and the wave's own 130 instructions
+// (fewer vector instructions, 87 for 110, changed nothing); a queue for every wave, without a shared count, 826 us where
+// 647 were, since every wave then has a few entries of every small round; the arrays as in PartLds, and failed swaps
+// made again alone and not both, took a partition's rounds from 38.8 K clocks to 32.0 K (8192 unknowns in 12288 cells, 11
+// rounds) and from 51.1 K to 43.3 K (in 10776 cells, 21 rounds).
 template <bool kAlone, bool kPacked, typename Room>
 __device__ __forceinline__ uint32_t resolve_unknown(const PartLds<kPacked> &p, uint32_t entry, Room &&room)
 {
@@ -759,12 +759,13 @@ __device__ __forceinline__ void write_dense(const PartLds<true> &p, uint32_t tid
     } while (piece.next());
 }
 
-// The zeros of the dense output, by workgroup `b` of `n` that have no partition: the entries whose Index bit is not
-// set, and no others, so that nobody has to wait for whom writes the others; all of them where there is no partition
-// (after an overflow, when bits are set all the same).  A wave takes 16 words at a time, the next of which are on
-// their way.
+// The zeros of the dense output, by workgroup `b` of `n` that have no partition: the entries whose Index bit is
+// not set, and no others, so that nobody has to wait for whom writes the others; all of them where there is no
+// partition (after an overflow, when bits are set all the same).  A wave takes 16 words at a time, the next of
+// which are on their way.
 constexpr uint32_t kZeroWords = 16;
-__device__ __forceinline__ void write_zeros(const IndexView &index, uint32_t b, uint32_t n, bool all, float *__restrict__ out)
+__device__ __forceinline__ void write_zeros(const IndexView &index, uint32_t b, uint32_t n, bool all,
+                                            float *__restrict__ out)
 {
     const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t step = n * (kDecodeThreads / 64) * kZeroWords;
@@ -798,10 +799,10 @@ __device__ __forceinline__ void write_zeros(const IndexView &index, uint32_t b, 
 // kLoop: over any number of ranks, or the summed sketch, added up as they come.  For grids that have a workgroup for
 // every partition: there is no next partition whose sum could run beside the rounds, as
 // sum_peel_kernel has it (40 partitions of 8 ranks: 27.7 us, 28.9 in that kernel; 51 of 5: 27.5, 30.1; 159 of 8: 31.1,
-// 31.3; 239 of 8: 35.6, 34.5; 233 of 12: 39.8, 41.4).  Nor is there one before, whose rounds its cells could travel behind: the Index words are requested first
-// and the unknowns enumerated, joined and looked through for the first queue, none of which needs a value, while the
-// cells travel (8 ranks of 25 M entries 40.4 -> 38.0, 3 of 36 thousand, one partition, 18.6 -> 15.9, 4 of 1 M 20.8 ->
-// 17.9, a summed sketch in 236 partitions 32.0 -> 29.4).
+// 31.3; 239 of 8: 35.6, 34.5; 233 of 12: 39.8, 41.4).  Nor is there one before, whose rounds its cells could travel
+// behind: the Index words are requested first and the unknowns enumerated, joined and looked through for the first queue,
+// none of which needs a value, while the cells travel (8 ranks of 25 M entries 40.4 -> 38.0, 3 of 36 thousand, one
+// partition, 18.6 -> 15.9, 4 of 1 M 20.8 -> 17.9, a summed sketch in 236 partitions 32.0 -> 29.4).
 constexpr uint32_t kIndexPre = 6;  // groups of Index words a wave requests ahead
 constexpr uint32_t kHeldRanks = 4;  // kRanks of the form for few ranks
 constexpr uint32_t kListGroups = 256;  // groups of Index words per partition beyond which its unknowns are listed first
@@ -919,14 +920,14 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
     if (kListed) pre_list.put(part.word(0), Pa, tid);
     else pre_index.enumerate(index, part.word(0), Pa, rho0, wave);
     auto stage_cells = [&] {
-    add_cells(1, n_in);
-    const uint32_t to = part.base + PartLds<kPacked>::kValue + 4 * kFour * tid;
+        add_cells(1, n_in);
+        const uint32_t to = part.base + PartLds<kPacked>::kValue + 4 * kFour * tid;
 #pragma unroll
-    for (uint32_t q = 0; q < kCellPre; q += kFour) {
-        const uint32_t c = kFour * tid + q * kDecodeThreads, at = to + 4 * q * kDecodeThreads;
-        if (kFour == 4) stage_four(at, pre_cell[0] + q, c, cells);
-        else if (c < cells) *lds_at<float>(at) = pre_cell[0][q];
-    }
+        for (uint32_t q = 0; q < kCellPre; q += kFour) {
+            const uint32_t c = kFour * tid + q * kDecodeThreads, at = to + 4 * q * kDecodeThreads;
+            if (kFour == 4) stage_four(at, pre_cell[0] + q, c, cells);
+            else if (c < cells) *lds_at<float>(at) = pre_cell[0][q];
+        }
     };
     if (!kLoop) stage_cells();
     else if (n_in > kRanks) request_more(kRanks, tile0);
@@ -986,14 +987,15 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
             const uint32_t u = tid + q * kDecodeThreads;
             val[q] = u < Pa ? unknown_value(part, u, mode) : 0.0f;
             if (u < Pa) val_out[rho0 + u] = val[q];
-            // (a word of the partition that no set bit has filled holds anything, should the Index have changed since it
-            // was merged: nothing lands outside the output)
+            // (a word of the partition that no set bit has filled holds anything, should the Index have changed
+            // since it was merged: nothing lands outside the output)
             if (kLoop && idx[q] < 32 * index.n_words) dense_row()[idx[q]] = val[q];
         }
         // all c-indices lie in a partition's range, those before the first unknown in the first one's
         // (read again: kept, the bounds take a vector register to spill)
         const uint32_t a = at.a - at.step;
-        const uint32_t lo = !kLoop && a ? index.bounds[a] : 0u, hi = kLoop ? 0u : min(index.bounds[a + 1], 32 * index.n_words);
+        const uint32_t lo = !kLoop && a ? index.bounds[a] : 0u;
+        const uint32_t hi = kLoop ? 0u : min(index.bounds[a + 1], 32 * index.n_words);
         if (!kLoop && dense_by_decoder(A, gridDim.x, 32 * index.n_words, hi - lo)) {
             __syncthreads();
             write_dense<kDecodeThreads, kIdxPre>(part, tid, idx, val, lo, hi, dense_row());
@@ -1021,12 +1023,12 @@ peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index, const uint32_t
 // kPeelWaves peel the current one in LDS as peel_kernel does.  The two groups meet once per
 // partition, at a hardware barrier: when the peelers are done with the LDS.  The loaders then
 // write the summed cells there, say so in an LDS word, and go on; the peelers enumerate, join and queue the
-// partition's unknowns, none of which needs a value, and look at that word before the rounds.  (With a second barrier
-// there, the peelers of a workgroup's first partition began with the unknowns when its cells had been summed.  us, that
-// way / this: 8 ranks of 7 M entries, 325 partitions, 47.7 / 41.4, of 67 M, 433, 77.1 / 67.5, 16 of 202 M, 3640, 551 / 552.)  The peelers' own barriers (after
-// the unknowns joined their cells, one per round) must not hold up the loaders, which have
-// no part in them and may be waiting for memory: they are counted in an LDS word instead
-// (peel_barrier).
+// partition's unknowns, none of which needs a value, and look at that word before the rounds.  (With a
+// second barrier there, the peelers of a workgroup's first partition began with the unknowns when its cells
+// had been summed.  us, that way / this: 8 ranks of 7 M entries, 325 partitions, 47.7 / 41.4, of 67 M, 433,
+// 77.1 / 67.5, 16 of 202 M, 3640, 551 / 552.)  The peelers' own barriers (after the unknowns joined their
+// cells, one per round) must not hold up the loaders, which have no part in them and may be waiting for
+// memory: they are counted in an LDS word instead (peel_barrier).
 constexpr uint32_t kLoadWaves = 4, kPeelWaves = kDecodeThreads / 64 - kLoadWaves;
 constexpr uint32_t kLoadThreads = kLoadWaves * 64, kPeelThreads = kPeelWaves * 64;
 constexpr uint32_t kLoadCells = (kDefaultPartCells + kLoadThreads - 1) / kLoadThreads;  // per thread
@@ -1183,9 +1185,9 @@ sum_peel_kernel(const RankPtrs, uint32_t n_in, const IndexView index,
 // builds any four consecutive outputs on its own -- the rank of a set bit is the word's
 // count plus a popcount -- so the output goes out in plain contiguous 16-byte stores.
 constexpr uint32_t kDenseStage = 8192;
-// Words of a workgroup of dense_kernel.  Bound by the stores; whole chunks, two workgroups of 1024 threads to a compute unit,
-// ended in a turn that was half empty (us, 256 / 512 / 1024 words: 7 M entries 8.9 / 9.1 / 9.6, 25 M 20.1 / 20.4 / 22.1,
-// 67 M 50.4 / 50.9 / 51.5, 202 M 151 / 162 / 155).
+// Words of a workgroup of dense_kernel.  Bound by the stores; whole chunks, two workgroups of 1024 threads to a
+// compute unit, ended in a turn that was half empty (us, 256 / 512 / 1024 words: 7 M entries 8.9 / 9.1 / 9.6,
+// 25 M 20.1 / 20.4 / 22.1, 67 M 50.4 / 50.9 / 51.5, 202 M 151 / 162 / 155).
 constexpr uint32_t kDenseWords = 256;
 
 template <uint32_t NT>
@@ -1324,18 +1326,23 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     constexpr uint32_t kI0 = (kDefaultPartUnknowns + kDecodeThreads - 1) / kDecodeThreads;
     constexpr uint32_t kC1 = (kMaxPartCells + kDecodeThreads - 1) / kDecodeThreads;
     constexpr uint32_t kI1 = (kMaxPartUnknowns + kDecodeThreads - 1) / kDecodeThreads;
-    // Partitions that span much of the Index, because little of it can be set: the one workgroup
-    // of a partition would go through all of that, most of the device having nothing to do, so a
-    // kernel over the whole Index lists the unknowns first.  Decoder alone, us, walking / listing
-    // (enumerate and peel): 2 ranks of 202 M entries, 80 thousand unknowns in 10 partitions 189 / 36; 8 ranks
-    // of 67 M in 112 partitions, 290 groups each, 45 / 47 (from the summed sketch 37 / 33); in 164, 200 groups,
-    // 45 / 50 (35 / 35); of 7 M in 103, 33 groups, 35 / 45 (29 / 33).
+    // Partitions that span much of the Index, because little of it can be set: the one workgroup of a partition
+    // would go through all of that, most of the device having nothing to do, so a kernel over the whole Index
+    // lists the unknowns first.  Decoder alone, us, walking / listing (enumerate and peel), three ranks, by
+    // groups a partition: 4 partitions, 64, 128, 192, 256, 400, 600 groups 23.6 / 26.5, 26.1 / 26.2, 27.9 /
+    // 26.4, 30.3 / 27.0, 33.6 / 26.2, 38.8 / 26.0; 30, the same 26.1 / 29.3, 27.9 / 28.2, 29.5 / 28.0, 31.6 /
+    // 28.3, 35.6 / 28.4, 41.3 / 29.6; 100, 128, 256, 400 29.6 / 30.7, 33.3 / 32.3, 37.3 / 33.8; 164, 256, 320,
+    // 400 34.9 / 36.2, 36.3 / 37.2, 39.1 / 37.9; 250, 256, 400 37.9 / 42.0, 43.0 / 46.4; 400, 256 69.3 / 69.7.
+    // 8 ranks and one summed sketch the same within 3 %.  So the line is a little high for few partitions and
+    // low for those that nearly fill the device; and with the dense output, whose zeros are written beside the
+    // walking form only, it is low for 100 partitions (8 ranks, 256, 400 groups 1.34, 0.96 of walking's time)
+    // and the same for 4 and 250.
     const bool listed = 16ull * n_chunks > kListGroups * p->A_cap;
     // A workgroup per partition, whatever is summed; else one summed sketch; up to four ranks; any number.
-    // (Decoder alone, us, sixteen waves peeling / sum_peel_kernel, of whose sixteen four sum: 202 M entries with a
-    // tenth kept, 2 ranks 464 / 507, 4 ranks 900 / 922; 20 to 40 M, 1 to 4 ranks, 25 to 390 partitions, 3 to 4 us
-    // less; 4 ranks of 40 M with 5 % 122 / 122, of 9 M with two fifths 126 / 123.  More ranks' cells do not fit
-    // the registers beside the rounds.)
+    // (Decoder alone, us, up to four ranks, sixteen waves peeling / sum_peel_kernel, of whose sixteen four sum:
+    // one rank of 25, 74, 164 M entries in 300, 900, 2000 partitions 50.5 / 54.9, 98 / 106, 188 / 204; two 51.9
+    // / 55.0, 100 / 107, 192 / 208; three 53.4 / 54.8, 102 / 108, 194 / 213; four 55.3 / 55.1, 107 / 112, 200 /
+    // 218, of 94 M in 3955 378 / 418.  More ranks' cells do not fit the registers beside the rounds.)
     const uint32_t form = grid == p->A_cap && !listed && packed_slots(p->T_cap, p->P_cap) ? 3u
                           : !fused                ? (packed_slots(p->T_cap, p->P_cap) ? 1u : 0u)
                           : n_ranks <= kHeldRanks ? 2u
@@ -1348,11 +1355,12 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
                : form == 1 ? peel_kernel<kC0, kI0, true, 1, false, kList, false>
                            : peel_kernel<kC1, kI1, false, 1, false, kList, false>;
     };
-    // A dense output that begins before the last partition is decoded must lie apart from what is still read by then; a
-    // launch behind the decoder may put it in the place of a sketch, say.
+    // A dense output that begins before the last partition is decoded must lie apart from what is still read by
+    // then; a launch behind the decoder may put it in the place of a sketch, say.
     auto dense_apart = [&] {
         const uint64_t bytes = 4 * p->n_c;
-        bool apart = !overlap(dense_out, bytes, idx_out, 4 * p->U_cap) && !overlap(dense_out, bytes, sh->bounds, p->sizes.shared_bounds_bytes);
+        bool apart = !overlap(dense_out, bytes, idx_out, 4 * p->U_cap) &&
+                     !overlap(dense_out, bytes, sh->bounds, p->sizes.shared_bounds_bytes);
         for (uint32_t r = 0; r < n_ranks; ++r) apart &= !overlap(dense_out, bytes, rp.p[r], 4 * p->m_cap);
         return apart;
     };
@@ -1367,26 +1375,29 @@ int launch_decode(const tagc_plan_t *p, const tagc_shared_buffers *sh,
     // (782) 132 / 133; 200 M nearly all zeros, two partitions, 338 / 341 (6584 by their two workgroups).
     const bool with_dense = early && (form == 1 || form == 2) && p->A_cap >= 3ull * grid &&
                             p->K >= uint64_t(grid) * p->P_cap;
-    // Where there are fewer partitions than compute units, workgroups on the others write the dense output's zeros
-    // meanwhile, and the decoder its values among them.  Such a workgroup stores 7.7 thousand entries a us, so it may have
-    // as many as that makes of what the peel and dense_kernel would take: 100 Ki, 16 for each unknown of a partition,
-    // and a 180th of the output (1.4 M entries a us).  Decoder and dense output, us, dense_kernel / this way, by the
-    // share of that limit that such a workgroup has, the summed sketch, partitions of 8192: 0.2 32.6 / 28.8 (80
-    // partitions of 3 M entries), 0.5 41.6 / 36.6 (156 of 16 M), 0.7 61.2 / 40.3 (100 of 41 M), 0.8 54.3 / 44.3 (157 of
-    // 32 M), 0.9 83.4 / 74.6 (131 of 67 M), 1.0 45.9 / 46.3 (200 of 19 M), 1.15 46.1 / 50.0 (200 of 21 M), 1.3 60.4 /
-    // 71.3 (187 of 39 M); of 2048 unknowns 0.7 24.8 / 21.4, 1.1 27.9 / 29.8 (200 of 8, 12 M); of 512 0.8 19.9 / 17.2, 1.1
-    // 22.2 / 25.6 (200 of 7, 11 M); of 32 0.8 19.4 / 16.2, 1.1 21.3 / 24.2 (200 of 6, 10 M).
-    // The sum of many ranks needs the memory itself, and where there is some to write, but not so much that the launch behind
-    // it takes long, loses what that would take: 8 ranks, 0.8 M entries 37.7 / 31.1, 3 M 39.1 / 35.2, 6 M 35.1 /
-    // 36.0, 8 M 37.3 / 38.7, 12 M 41.6 / 44.8, 16 M 46.4 / 46.4, 19 M 51.5 / 48.7, 24 M 52.9 / 47.6; 16 ranks, 3 M 41.7 /
-    // 39.6, 6 M 42.7 / 45.0, 10 M 53.9 / 56.4, 16 M 51.1 / 48.2; 4 ranks, 6 M 34.3 / 34.5, 8 M 38.1 / 38.1, 12 M 38.8 / 37.8.
+    // Where there are fewer partitions than compute units, workgroups on the others write the dense output's
+    // zeros meanwhile, and the decoder its values among them.  Such a workgroup stores 7.7 thousand entries a
+    // us, so it may have as many as that makes of what the peel and dense_kernel would take: 100 Ki, 16 for
+    // each unknown of a partition, and a 180th of the output (1.4 M entries a us).  Decoder and dense output,
+    // us, dense_kernel / this way, by the share of that limit that such a workgroup has, the summed sketch,
+    // partitions of 8192: 0.2 32.6 / 28.8 (80 partitions of 3 M entries), 0.5 41.6 / 36.6 (156 of 16 M), 0.7
+    // 61.2 / 40.3 (100 of 41 M), 0.8 54.3 / 44.3 (157 of 32 M), 0.9 83.4 / 74.6 (131 of 67 M), 1.0 45.9 / 46.3
+    // (200 of 19 M), 1.15 46.1 / 50.0 (200 of 21 M), 1.3 60.4 / 71.3 (187 of 39 M); of 2048 unknowns 0.7 24.8 /
+    // 21.4, 1.1 27.9 / 29.8 (200 of 8, 12 M); of 512 0.8 19.9 / 17.2, 1.1 22.2 / 25.6 (200 of 7, 11 M); of 32
+    // 0.8 19.4 / 16.2, 1.1 21.3 / 24.2 (200 of 6, 10 M).
+    // The sum of many ranks needs the memory itself, and where there is some to write, but not so much that the
+    // launch behind it takes long, loses what that would take: 8 ranks, 0.8 M entries 37.7 / 31.1, 3 M 39.1 /
+    // 35.2, 6 M 35.1 / 36.0, 8 M 37.3 / 38.7, 12 M 41.6 / 44.8, 16 M 46.4 / 46.4, 19 M 51.5 / 48.7, 24 M 52.9 /
+    // 47.6; 16 ranks, 3 M 41.7 / 39.6, 6 M 42.7 / 45.0, 10 M 53.9 / 56.4, 16 M 51.1 / 48.2; 4 ranks, 6 M 34.3 /
+    // 34.5, 8 M 38.1 / 38.1, 12 M 38.8 / 37.8.
     // (Plans whose unknowns are listed have no such decoder: it would be one form more.)
     const uint32_t cus = uint32_t(device_cu_count());
     const uint32_t spare = early && form == 3 && p->A_cap < cus ? cus - uint32_t(p->A_cap) : 0u;
     const uint64_t share = 100 * 1024 + 16ull * p->P_cap + p->n_c / 180;
     const bool crowded = n_ranks > kHeldRanks && p->n_c >= 4u << 20 && p->n_c < 16u << 20;
     const bool with_zeros = n_words && n_ranks <= kDenseRow && p->n_c <= spare * share && !crowded;
-    if (with_zeros) grid += std::min(spare, (n_words + kZeroWords * (kDecodeThreads / 64) - 1) / (kZeroWords * (kDecodeThreads / 64)));
+    constexpr uint32_t kZeroTurn = kZeroWords * (kDecodeThreads / 64);  // words of a workgroup
+    if (with_zeros) grid += std::min(spare, (n_words + kZeroTurn - 1) / kZeroTurn);
     const auto kernel = with_zeros ? peel_kernel<kC0, kI0, true, kHeldRanks, true, false, true>
                         : with_dense ? (form == 2 ? peel_kernel<kC0, kI0, true, kHeldRanks, false, false, true>
                                                 : peel_kernel<kC0, kI0, true, 1, false, false, true>)

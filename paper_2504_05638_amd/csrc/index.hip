@@ -253,13 +253,13 @@ constexpr uint32_t kNoLink = 0xFFFFu;
 constexpr uint32_t kFilterBits = 64;      // per cell of a sub-table
 constexpr uint32_t kSecondWords = 1024;   // second filter, cleared a word per thread
 static_assert(kSecondWords == kSaltThreads, "every thread clears its word");
-// Index words up to which the layout merges the ranks' Indexes itself: four of each to a thread, kept in LDS, where
-// everything that is looked up in the merged Index then is.  Every workgroup merges them all, so they are few and read
-// little.  us of the Index aggregation, merge and layout / layout alone: 33 thousand entries from 1, 8, 16 ranks 14.5, 15.7,
-// 17.2 / 11.1, 11.9, 12.4, 66 thousand 16.6, 19.9, 23.4 / 12.3, 13.3, 13.6, 131 thousand from 1, 4, 8 ranks 16.8, 17.1, 17.5 /
-// 13.1, 13.4, 13.9; in 52 partitions 15.9 / 11.8 (4 ranks).  4-bit counters: a thread has four vectors of a rank, and more
-// than eight ranks' go out in too many trips: 8 thousand entries from 8, 16, 32 ranks 15.3, 15.6, 16.6 / 13.7, 16.5, 21.3, 33
-// thousand from 8 18.2 / 15.3.
+// Index words up to which the layout merges the ranks' Indexes itself: four of each to a thread, kept in LDS,
+// where everything that is looked up in the merged Index then is.  Every workgroup merges them all, so they are
+// few and read little.  us of the Index aggregation, merge and layout / layout alone: 33 thousand entries from
+// 1, 8, 16 ranks 14.5, 15.7, 17.2 / 11.1, 11.9, 12.4, 66 thousand 16.6, 19.9, 23.4 / 12.3, 13.3, 13.6, 131
+// thousand from 1, 4, 8 ranks 16.8, 17.1, 17.5 / 13.1, 13.4, 13.9; in 52 partitions 15.9 / 11.8 (4 ranks).
+// 4-bit counters: a thread has four vectors of a rank, and more than eight ranks' go out in too many trips: 8
+// thousand entries from 8, 16, 32 ranks 15.3, 15.6, 16.6 / 13.7, 16.5, 21.3, 33 thousand from 8 18.2 / 15.3.
 constexpr uint32_t kMergeWords = 4 * kSaltThreads;
 constexpr uint32_t kMergeMost = 64;             // partitions of the plan at most
 constexpr uint32_t kMergeBytes = 128 * 1024;    // of all ranks' Indexes

@@ -140,17 +140,18 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
         delete p;
         return TAGC_ENOMEM;
     }
-    // One launch for all of it (see small_kernel), where no gradient makes it slower than the three that it takes the place
-    // of: segments that a workgroup's registers hold, of which ...
-    // (a) not so much is kept that one workgroup takes longer over its pairs than the device does.  One segment, us,
-    // three launches / one: fp32, 33 thousand entries with a tenth, two fifths, all kept 23.1 / 20.1, 24.0 / 23.1,
-    // 23.8 / 26.8; bf16, 66 thousand with 5, 10, 20 % 22.9 / 20.8, 23.3 / 22.6, 23.4 / 25.4 (and, behind
-    // another, with 5, 10 % 25.5 / 25.0, 25.8 / 28.3), 33 thousand with two fifths, seven tenths 21.4 / 20.0, 22.2 /
-    // 22.4.  bf16 with everything kept is slow from 12 thousand entries on: with 95, 100 % 20.1 / 17.7, 20.2 / 21.6,
-    // with 8 thousand 21.0 / 15.5, 20.5 / 18.2.
-    // (b) a workgroup can go through all that lies before its own, should it be zeros.  Segments alike but for the last,
-    // one entry in 2000 not zero, eight ranks: 3 to 17 segments, 128 KiB before the last 0.67 to 0.86 of the three launches'
-    // time, 192 KiB 0.78 to 0.93, 256 KiB 0.85 to 1.13, 512 KiB 1.2 to 1.5; gradients without zeros 0.5 to 0.8.
+    // One launch for all of it (see small_kernel), where no gradient makes it slower than the three that it
+    // takes the place of: segments that a workgroup's registers hold, of which ...
+    // (a) not so much is kept that one workgroup takes longer over its pairs than the device does.  One segment,
+    // us, three launches / one: fp32, 33 thousand entries with a tenth, two fifths, all kept 23.1 / 20.1, 24.0 /
+    // 23.1, 23.8 / 26.8; bf16, 66 thousand with 5, 10, 20 % 22.9 / 20.8, 23.3 / 22.6, 23.4 / 25.4 (and, behind
+    // another, with 5, 10 % 25.5 / 25.0, 25.8 / 28.3), 33 thousand with two fifths, seven tenths 21.4 / 20.0,
+    // 22.2 / 22.4.  bf16 with everything kept is slow from 12 thousand entries on: with 95, 100 % 20.1 / 17.7,
+    // 20.2 / 21.6, with 8 thousand 21.0 / 15.5, 20.5 / 18.2.
+    // (b) a workgroup can go through all that lies before its own, should it be zeros.  Segments alike but for
+    // the last, one entry in 2000 not zero, eight ranks: 3 to 17 segments, 128 KiB before the last 0.67 to 0.86
+    // of the three launches' time, 192 KiB 0.78 to 0.93, 256 KiB 0.85 to 1.13, 512 KiB 1.2 to 1.5; gradients
+    // without zeros 0.5 to 0.8.
     // (c) the launch's workgroups have a compute unit each (launch_sparsify).
     const SegDev *last = nullptr;
     uint64_t before = 0;

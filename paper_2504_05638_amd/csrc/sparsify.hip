@@ -1122,8 +1122,9 @@ __device__ __forceinline__ SelDev select_small(uint32_t l, const SegDev &sd, con
     const uint32_t in_bin = get(prefix);
     __syncthreads();  // everybody has read h16
     if (in_bin <= 64) {
-        // fp32, and no more entries in the threshold's bin than a wave has lanes, as nearly always: every wave compares them
-        // all with each other (the two rounds below are sixteen barriers: small_kernel of 11 thousand entries 16.1 us, 13.5 this way)
+        // fp32, and no more entries in the threshold's bin than a wave has lanes, as nearly always: every wave
+        // compares them all with each other (the two rounds below are sixteen barriers: small_kernel of 11
+        // thousand entries 16.1 us, 13.5 this way)
         const uint32_t lane = tid & 63, want = sd.k - above;
         if (tid == 0) smem[33] = 0;
         __syncthreads();
@@ -1331,14 +1332,15 @@ hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t n
 
 // ------------------------------------------------------------------ small
 
-// Few short segments (tagc_plan says which) take one launch from
-// the gradient to pairs, Index and counts: a workgroup that has found its segment's threshold has all its entries at hand.
-// What it cannot know is how many pairs the segments before it emit: as many as they are to keep, unless one has
-// fewer non-zeros than that.  So it looks, a wave a segment, at their first entries until it has seen so many
-// non-zeros, which is one trip of 512 (bf16: 1024) entries where few are kept, and all of them where nearly all are zeros:
-// what eight trips have not settled is left to all waves, four times as wide (a wave to its end: 36 us where this
-// takes 18 and hist1, count and place 20, two segments of 25 thousand zeros before the last, eight ranks).  Nobody waits
-// for anybody.  us: hist1, count and place of five segments of 72 to 11 thousand fp32 entries, three ranks, 23.5; this 13.5.
+// Few short segments (tagc_plan says which) take one launch from the gradient to pairs, Index and counts: a
+// workgroup that has found its segment's threshold has all its entries at hand.  What it cannot know is how many
+// pairs the segments before it emit: as many as they are to keep, unless one has fewer non-zeros than that.  So
+// it looks, a wave a segment, at their first entries until it has seen so many non-zeros, which is one trip of
+// 512 (bf16: 1024) entries where few are kept, and all of them where nearly all are zeros: what eight trips have
+// not settled is left to all waves, four times as wide (a wave to its end: 35 us where this takes 19 and hist1,
+// count and place 20, two segments of 25 thousand zeros before the last, eight ranks).  Nobody waits for anybody.
+// us: hist1, count and place of five segments of 72 to 11 thousand fp32 entries, three ranks, 23.5; this 13.5.
+
 // The segment's pairs from position `base` of the rank's list on; and its Index words.
 template <int DTYPE>
 __device__ __forceinline__ void emit_small(const SegDev &sd, const uint4 (&v)[kSmallVecs], const SelDev &se, uint32_t base,
@@ -1432,7 +1434,9 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
     constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
     __shared__ uint32_t h[kBins1 / 2];
     __shared__ uint32_t smem[40];
-    __shared__ uint32_t s_base, s_more, s_which[kSmallSegments], s_at[kSmallSegments], s_seen[kSmallSegments];
+    __shared__ uint32_t s_base;
+    // segments left to all waves: how many, which, from which entry on, their non-zeros so far
+    __shared__ uint32_t s_more, s_which[kSmallSegments], s_at[kSmallSegments], s_seen[kSmallSegments];
     const RankView rv = rank_view();
     const char *grad = rv.src();
     const uint32_t L = wl.L, l = blockIdx.x, tid = threadIdx.x;
@@ -2724,9 +2728,9 @@ int launch_sparsify_t(const tagc_plan_t *p, const void *const *grads, const tagc
         return hip_ok(hipGetLastError());
     }
     const bool acc = ranks[0].acc != nullptr;
-    // (with a compute unit for every workgroup: 32 ranks of 9, 12, 20 segments with a little under 200 KiB each, nearly all
-    // zeros, three launches / one 28.1 / 33.4, 29.4 / 38.2, 31.8 / 43.6 us, of 7 segments 0.9; 32 of 28 short
-    // ones without zeros 40 / 51, 8 of them 0.8)
+    // (with a compute unit for every workgroup: 32 ranks of 9, 12, 20 segments with a little under 200 KiB
+    // each, nearly all zeros, three launches / one 28.1 / 33.4, 29.4 / 38.2, 31.8 / 43.6 us, of 7 segments 0.9;
+    // 32 of 28 short ones without zeros 40 / 51, 8 of them 0.8)
     const bool one = p->all_small && uint64_t(L) * n <= uint64_t(device_cu_count());
     SparsifyBatch sb{};
     SparsifyBatch part{};  // the ranks whose thresholds are launched next
