@@ -1434,9 +1434,11 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
     constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
     __shared__ uint32_t h[kBins1 / 2];
     __shared__ uint32_t smem[40];
-    __shared__ uint32_t s_base;
-    // segments left to all waves: how many, which, from which entry on, their non-zeros so far
-    __shared__ uint32_t s_more, s_which[kSmallSegments], s_at[kSmallSegments], s_seen[kSmallSegments];
+    // pairs before the segment's own, and from bit 24 on how many segments are left to all waves; which, from which
+    // entry on, their non-zeros so far
+    constexpr uint32_t kOneLeft = 1u << 24;
+    static_assert(kSmallSegments * kSmallPairs < kOneLeft && kSmallSegments < 256, "both fit a word");
+    __shared__ uint32_t s_base, s_which[kSmallSegments], s_at[kSmallSegments], s_seen[kSmallSegments];
     const RankView rv = rank_view();
     const char *grad = rv.src();
     const uint32_t L = wl.L, l = blockIdx.x, tid = threadIdx.x;
@@ -1446,7 +1448,7 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
     const SegDev sd = segs[l];
     uint4 v[kSmallVecs];
     load_small<DTYPE>(v, sd, grad + sd.offset * EB);
-    if (tid == 0) s_base = s_more = 0;
+    if (tid == 0) s_base = 0;
     uint32_t dense = 0;  // segments that keep something (lane i has looked at segment i: they are 64 at most)
     if (l == L - 1) {
         const SegDev row = segs[min(lane_id(), L - 1)];
@@ -1466,7 +1468,7 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
             if (at == ALONE || (before.n > ALONE && n * (ALONE / TRIP) < before.k * (at / TRIP))) break;
         }
         if (lane_id() == 0 && at < before.n && n < before.k) {
-            const uint32_t j = atomicAdd(&s_more, 1u);
+            const uint32_t j = atomicAdd(&s_base, kOneLeft) / kOneLeft;
             s_which[j] = i;
             s_at[j] = at;
             s_seen[j] = n;
@@ -1492,10 +1494,10 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
         }
         came = atomicAdd(&ts.arrive[0], nonfinite ? 1u + kSome : 1u);
     }
-    __syncthreads();  // h, s_base, s_more
+    __syncthreads();  // h, s_base
     // ---- what such waves have left over, by all of them
-    const uint32_t more = __builtin_amdgcn_readfirstlane(s_more);
-    if (more) {
+    uint32_t base = s_base;
+    if (const uint32_t more = __builtin_amdgcn_readfirstlane(base / kOneLeft)) {
         for (uint32_t j = 0, turn = wave; j < more; ++j) {
             const SegDev before = segs[__builtin_amdgcn_readfirstlane(s_which[j])];
             const uint32_t from = __builtin_amdgcn_readfirstlane(s_at[j]);
@@ -1510,8 +1512,8 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
         __syncthreads();
         if (tid < more) atomicAdd(&s_base, min(s_seen[tid], segs[s_which[tid]].k));
         __syncthreads();
+        base = s_base % kOneLeft;
     }
-    const uint32_t base = s_base;
     if (sd.n) emit_small<DTYPE>(sd, v, r, base, rv.idx, rv.val, rv.bitmap, h);  // uniform
     if (tid == 0) {
         rv.cnt[TAGC_CNT_SEG0 + l] = r.cnt;
