@@ -148,21 +148,12 @@ extern "C" int tagc_plan(const tagc_config *cfg, const tagc_segment *segs, uint3
     // another, with 5, 10 % 25.5 / 25.0, 25.8 / 28.3), 33 thousand with two fifths, seven tenths 21.4 / 20.0,
     // 22.2 / 22.4.  bf16 with everything kept is slow from 12 thousand entries on: with 95, 100 % 20.1 / 17.7,
     // 20.2 / 21.6, with 8 thousand 21.0 / 15.5, 20.5 / 18.2.
-    // (b) a workgroup can go through all that lies before its own, should it be zeros.  Segments alike but for
-    // the last, one entry in 2000 not zero, eight ranks: 3 to 17 segments, 128 KiB before the last 0.67 to 0.86
-    // of the three launches' time, 192 KiB 0.78 to 0.93, 256 KiB 0.85 to 1.13, 512 KiB 1.2 to 1.5; gradients
-    // without zeros 0.5 to 0.8.
-    // (c) the launch's workgroups have a compute unit each (launch_sparsify).
-    const SegDev *last = nullptr;
-    uint64_t before = 0;
+    // (b) the launch's workgroups are few turns of the compute units (launch_sparsify).
     p->all_small = K != 0 && p->table.size() <= kSmallSegments;
     for (const SegDev &d : p->table) {
         const bool nearly_all = p->elem_bytes == 2 && d.k > 8192 && 20ull * d.k > 19ull * d.n;
         p->all_small &= small(d.n) && d.n + 4ull * d.k <= kSmallPairs && !nearly_all;
-        if (last && last->k) before += uint64_t(last->n) * p->elem_bytes;
-        last = &d;
     }
-    p->all_small &= before <= kSmallBefore;
     if (c >= (1ull << 32)) {
         delete p;
         return TAGC_ESIZE;

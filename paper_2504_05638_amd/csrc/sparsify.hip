@@ -1087,9 +1087,11 @@ __device__ __forceinline__ void load_small(uint4 (&v)[kSmallVecs], const SegDev 
     for (uint32_t i = 0; i < kSmallVecs; ++i)
         v[i] = load_vec<DTYPE>(base, (i * kSmallThreads + threadIdx.x) * VEC, sd.n);
 }
-template <int DTYPE>
+// `counted` gets the segment's non-zeros as soon as they are known.
+template <int DTYPE, typename Counted>
 __device__ __forceinline__ SelDev select_small(uint32_t l, const SegDev &sd, const uint4 (&v)[kSmallVecs],
-                                               const TableState ts, uint32_t *h16, uint32_t *smem, bool leaves)
+                                               const TableState ts, uint32_t *h16, uint32_t *smem, bool leaves,
+                                               Counted &&counted)
 {
     constexpr uint32_t NT = kSmallThreads;
     const uint32_t tid = threadIdx.x;
@@ -1116,6 +1118,7 @@ __device__ __forceinline__ SelDev select_small(uint32_t l, const SegDev &sd, con
     BinFound f[2];
     auto get = [&](uint32_t b) { return (h16[b >> 1] >> (16 * (b & 1u))) & 0xFFFFu; };
     select_top<NT, BPT>(get, own, {sd.k, carried_count(sd)}, f, &total, smem);
+    counted(total);
     SelDev r = dense_selection<DTYPE>(l, sd, f[0], f[1], total, smem[32], ts, leaves && tid == 0);
     if (DTYPE == kBF16 || f[0].bin == kNoBin) return r;  // uniform
     uint32_t above = f[0].above, prefix = f[0].bin;  // key >> shift of the bin looked into
@@ -1220,7 +1223,7 @@ hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t n
         if (sd.k != 0 && (sd.flags & kSegSmall)) {
             uint4 v[kSmallVecs];
             load_small<DTYPE>(v, sd, grad + sd.offset * EB);
-            const SelDev r = select_small<DTYPE>(l, sd, v, ts, h, smem, true);
+            const SelDev r = select_small<DTYPE>(l, sd, v, ts, h, smem, true, [](uint32_t) {});
             if (tid == 0) sel[l] = r;
         }
         return;
@@ -1335,39 +1338,39 @@ hist1_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl, uint32_t n
 // Few short segments (tagc_plan says which) take one launch from the gradient to pairs, Index and counts: a
 // workgroup that has found its segment's threshold has all its entries at hand.  What it cannot know is how many
 // pairs the segments before it emit: as many as they are to keep, unless one has fewer non-zeros than that.  So
-// it looks, a wave a segment, at their first entries until it has seen so many non-zeros, which is one trip of
-// 512 (bf16: 1024) entries where few are kept, and all of them where nearly all are zeros: what eight trips have
-// not settled is left to all waves, four times as wide (a wave to its end: 35 us where this takes 19 and hist1,
-// count and place 20, two segments of 25 thousand zeros before the last, eight ranks).  Nobody waits for anybody.
-// us: hist1, count and place of five segments of 72 to 11 thousand fp32 entries, three ranks, 23.5; this 13.5.
+// every workgroup tells, with its histogram's total, before it has its threshold; and whoever finds a segment's
+// word missing behind its own all the same, because that workgroup has had no compute unit yet, counts the
+// segment itself.  Nobody waits for anybody: workgroups that did could wait for good, for some that they keep
+// out, where launches of several streams fill the device.  (Every workgroup counting all before its own, a wave a
+// segment: 64 of 32 thousand entries nearly all zeros, eight ranks, 416 us; this 69, the three launches 66.)
+// us: hist1, count and place of five segments of 72 to 11 thousand fp32 entries, three ranks, 23.5; this 13.1.
 
-// The segment's pairs from position `base` of the rank's list on; and its Index words.
-template <int DTYPE>
-__device__ __forceinline__ void emit_small(const SegDev &sd, const uint4 (&v)[kSmallVecs], const SelDev &se, uint32_t base,
-                                           uint32_t *idx, float *val, uint32_t *bitmap, uint32_t *s_rows /* [kSmallVecs * NT / 64] */)
+// The segment's pairs, from the position of the rank's list on that one wave's `look` leaves in `base`; and its
+// Index words.
+template <int DTYPE, typename Look>
+__device__ __forceinline__ void emit_small(const SegDev &sd, uint4 (&v)[kSmallVecs], const SelDev &se,
+                                           const uint32_t *base, uint32_t *idx, float *val, uint32_t *bitmap,
+                                           uint32_t *s_rows /* [kSmallVecs * NT / 64] */, Look &&look)
 {
     constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4, NT = kSmallThreads, NWV = NT / 64, LPW = 32 / VEC;
     static_assert(kSmallVecs * NWV == 128, "two counts a lane");
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // entries above the threshold, and at it << 16, of a vector (a segment has fewer than 65536)
-    auto marks = [&](const uint4 &q, uint32_t &gt, uint32_t &eq) {
-        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-        gt = eq = 0;
+    // which entries of a vector are above the threshold, and << 16 which are at it; how many (a segment has fewer
+    // than 65536)
+    uint32_t marks[kSmallVecs], inc[kSmallVecs];
+    auto own = [&](uint32_t i) { return uint32_t(__popc(marks[i] & 0xFFFFu)) | (uint32_t(__popc(marks[i] >> 16)) << 16); };
+#pragma unroll
+    for (uint32_t i = 0; i < kSmallVecs; ++i) {
+        const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+        uint32_t gt = 0, eq = 0;
 #pragma unroll
         for (uint32_t e = 0; e < VEC; ++e) {
             const uint32_t key = vec_elem_bits<DTYPE>(w, e) & 0x7FFFFFFFu;
             gt |= uint32_t(key > se.T) << e;
             eq |= uint32_t(key == se.T) << e;
         }
-        if (!se.quota) eq = 0;
-    };
-    uint32_t own[kSmallVecs], inc[kSmallVecs];
-#pragma unroll
-    for (uint32_t i = 0; i < kSmallVecs; ++i) {
-        uint32_t gt, eq;
-        marks(v[i], gt, eq);
-        own[i] = __popc(gt) | (__popc(eq) << 16);
-        inc[i] = wave_incl_scan<uint32_t>(own[i]);
+        marks[i] = gt | (se.quota ? eq << 16 : 0u);
+        inc[i] = wave_incl_scan<uint32_t>(own(i));
         if (lane == 63) s_rows[i * NWV + wave] = inc[i];
     }
     __syncthreads();
@@ -1377,20 +1380,24 @@ __device__ __forceinline__ void emit_small(const SegDev &sd, const uint4 (&v)[kS
         s_rows[2 * lane] = before;
         s_rows[2 * lane + 1] = before + a;
     }
+    if (wave == 1) look();
     __syncthreads();
+    const uint32_t from = *base;
 #pragma unroll
     for (uint32_t i = 0; i < kSmallVecs; ++i) {
         if (i * NT * VEC >= sd.n) break;  // uniform
-        const uint32_t at = s_rows[i * NWV + wave] + inc[i] - own[i], rel = (i * NT + tid) * VEC;
-        uint32_t gb = at & 0xFFFFu, eb = at >> 16, gt, eq;
-        marks(v[i], gt, eq);
+        const uint32_t at = s_rows[i * NWV + wave] + inc[i] - own(i), rel = (i * NT + tid) * VEC;
+        uint32_t gb = at & 0xFFFFu, eb = at >> 16;
+        const uint32_t gt = marks[i] & 0xFFFFu, eq = marks[i] >> 16;
+        // (unpacked anew: the entries, kept since the marks were made, take registers that are not there)
+        asm volatile("" : "+v"(v[i].x), "+v"(v[i].y), "+v"(v[i].z), "+v"(v[i].w));
         const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
         uint32_t kept = gt;
         for (uint32_t m = gt | eq; m; m &= m - 1) {
             const uint32_t e = uint32_t(__builtin_ctz(m));
             const bool above = (gt >> e) & 1u;
             if (above || eb < se.quota) {
-                const uint32_t pos = base + gb + min(eb, se.quota);
+                const uint32_t pos = from + gb + min(eb, se.quota);
                 // (a register cannot be named by a number that is not known)
                 uint32_t bits = 0;
 #pragma unroll
@@ -1410,22 +1417,25 @@ __device__ __forceinline__ void emit_small(const SegDev &sd, const uint4 (&v)[kS
     }
 }
 
-// By a wave: the non-zeros among a segment's entries `at` .. and so on, TURN vectors to a lane.
-template <int DTYPE, uint32_t TURN>
-__device__ inline uint32_t nonzeros_small(const SegDev &sd, const char *base, uint32_t at)
+// By a wave: the pairs a segment emits, its non-zeros or what it is to keep.
+template <int DTYPE>
+__device__ inline uint32_t emitted_small(const SegDev &sd, const char *base)
 {
-    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4;
-    uint32_t own = 0;
-    uint4 v[TURN];
+    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4, TURN = 4;
+    uint32_t n = 0;
+    for (uint32_t at = 0; at < sd.n && n < sd.k; at += TURN * 64 * VEC) {
+        uint32_t own = 0;
+        uint4 v[TURN];
 #pragma unroll
-    for (uint32_t i = 0; i < TURN; ++i) v[i] = load_vec<DTYPE>(base, at + (i * 64 + lane_id()) * VEC, sd.n);
+        for (uint32_t i = 0; i < TURN; ++i) v[i] = load_vec<DTYPE>(base, at + (i * 64 + lane_id()) * VEC, sd.n);
 #pragma unroll
-    for (uint32_t i = 0; i < TURN; ++i) for_keys<DTYPE>(v[i], [&](uint32_t, uint32_t) { ++own; });
-    return __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(own), 63);
+        for (uint32_t i = 0; i < TURN; ++i) for_keys<DTYPE>(v[i], [&](uint32_t, uint32_t) { ++own; });
+        n += __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(own), 63);
+    }
+    return min(n, sd.k);
 }
 
-constexpr uint32_t kSmallAlone = 8;  // trips of a wave alone, two vectors a lane each
-constexpr uint32_t kSmallTurn = 8;   // vectors a lane of a turn of all waves
+constexpr uint32_t kSmallTries = 4;  // looks at the others' words before one is done without
 
 template <int DTYPE>
 __global__ void __launch_bounds__(kSmallThreads)
@@ -1434,96 +1444,74 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
     constexpr uint32_t EB = DTYPE == kBF16 ? 2 : 4;
     __shared__ uint32_t h[kBins1 / 2];
     __shared__ uint32_t smem[40];
-    // pairs before the segment's own, and from bit 24 on how many segments are left to all waves; which, from which
-    // entry on, their non-zeros so far
-    constexpr uint32_t kOneLeft = 1u << 24;
-    static_assert(kSmallSegments * kSmallPairs < kOneLeft && kSmallSegments < 256, "both fit a word");
-    __shared__ uint32_t s_base, s_which[kSmallSegments], s_at[kSmallSegments], s_seen[kSmallSegments];
+    __shared__ uint32_t s_base;  // pairs of the segments before
+    static_assert(kSmallSegments <= 64, "a lane a segment");
     const RankView rv = rank_view();
     const char *grad = rv.src();
-    const uint32_t L = wl.L, l = blockIdx.x, tid = threadIdx.x;
+    const uint32_t L = wl.L, l = blockIdx.x, tid = threadIdx.x, lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const SegDev *segs = reinterpret_cast<const SegDev *>(table + 8);
     const TableState ts = table_state(table, L, rv.slot);
     const SegDev sd = segs[l];
     uint4 v[kSmallVecs];
     load_small<DTYPE>(v, sd, grad + sd.offset * EB);
-    if (tid == 0) s_base = 0;
     uint32_t dense = 0;  // segments that keep something (lane i has looked at segment i: they are 64 at most)
     if (l == L - 1) {
-        const SegDev row = segs[min(lane_id(), L - 1)];
-        dense = uint32_t(__popcll(__ballot(lane_id() < L && row.k && row.n)));
-    }
-    __syncthreads();
-    // ---- the pairs before the segment's own: a wave a segment, until it has seen k non-zeros, or so few that it
-    // would not see them in ALONE entries
-    constexpr uint32_t NWV = kSmallThreads / 64, TRIP = 2 * 64 * 16 / EB, TURN = kSmallTurn * 64 * 16 / EB;
-    constexpr uint32_t ALONE = kSmallAlone * TRIP;
-    for (uint32_t i = wave; i < l; i += NWV) {
-        const SegDev before = segs[i];
-        uint32_t n = 0, at = 0;
-        while (at < before.n && n < before.k) {
-            n += nonzeros_small<DTYPE, 2>(before, grad + before.offset * EB, at);
-            at += TRIP;
-            if (at == ALONE || (before.n > ALONE && n * (ALONE / TRIP) < before.k * (at / TRIP))) break;
-        }
-        if (lane_id() == 0 && at < before.n && n < before.k) {
-            const uint32_t j = atomicAdd(&s_base, kOneLeft) / kOneLeft;
-            s_which[j] = i;
-            s_at[j] = at;
-            s_seen[j] = n;
-        } else if (lane_id() == 0 && n) {
-            atomicAdd(&s_base, min(n, before.k));
-        }
+        const SegDev row = segs[min(lane, L - 1)];
+        dense = uint32_t(__popcll(__ballot(lane < L && row.k && row.n)));
     }
     const bool keeps = sd.k != 0 && sd.n != 0;
     SelDev r{};  // (no entry is above the largest key)
     r.T = 0xFFFFFFFFu;
-    if (tid == 0) smem[32] = 0;
-    if (keeps) r = select_small<DTYPE>(l, sd, v, ts, h, smem, false);
+    // how many pairs the segment emits, for those behind it (the word is zero between the launches)
+    auto tell = [&](uint32_t nonzeros) {
+        if (tid == 64 && l != L - 1) atomicAdd(&ts.arrive_d[l], min(nonzeros, sd.k) + 1u);
+    };
+    if (keeps) r = select_small<DTYPE>(l, sd, v, ts, h, smem, false, tell);
+    else tell(0);
+    __syncthreads();  // h
     // The entries that are not finite are counted by the last one to say that it has found its segment's, which
     // only has to look if somebody had some; the others' counts are the plan's.
     constexpr uint32_t kSome = 1u << 16;
     static_assert(kSmallSegments < kSome, "arrivals");
     uint32_t came = 0, nonfinite = 0;
-    if (tid == 0) {
-        nonfinite = keeps ? smem[32] : 0u;
-        if (nonfinite) {
-            atomicAdd(&ts.glob[1], nonfinite);
-            wait_own_memory_ops();
-        }
-        came = atomicAdd(&ts.arrive[0], nonfinite ? 1u + kSome : 1u);
-    }
-    __syncthreads();  // h, s_base
-    // ---- what such waves have left over, by all of them
-    uint32_t base = s_base;
-    if (const uint32_t more = __builtin_amdgcn_readfirstlane(base / kOneLeft)) {
-        for (uint32_t j = 0, turn = wave; j < more; ++j) {
-            const SegDev before = segs[__builtin_amdgcn_readfirstlane(s_which[j])];
-            const uint32_t from = __builtin_amdgcn_readfirstlane(s_at[j]);
-            for (uint32_t at = from + turn % NWV * TURN; at < before.n; at += NWV * TURN) {
-                if (__hip_atomic_load(&s_seen[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= before.k) break;
-                const uint32_t n = nonzeros_small<DTYPE, kSmallTurn>(before, grad + before.offset * EB, at);
-                if (n && lane_id() == 0) atomicAdd(&s_seen[j], n);
+    auto look = [&] {
+        uint32_t word = lane < l ? 0u : 1u;
+        for (uint32_t tries = 0;; ++tries) {
+            if (int32_t(word) <= 0) word = __hip_atomic_load(&ts.arrive_d[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t untold = __ballot(int32_t(word) <= 0);
+            if (!untold) break;
+            if (tries < kSmallTries) {
+                __builtin_amdgcn_s_sleep(4);
+                continue;
             }
-            // (the next one's first turn is for the wave behind the last turn's)
-            turn += NWV - (before.n - from + TURN - 1) / TURN % NWV;
+            const uint32_t i = uint32_t(__builtin_ctzll(untold));
+            const SegDev before = segs[i];
+            const uint32_t n = emitted_small<DTYPE>(before, grad + before.offset * EB);
+            if (lane == i) word = n + 1;
         }
-        __syncthreads();
-        if (tid < more) atomicAdd(&s_base, min(s_seen[tid], segs[s_which[tid]].k));
-        __syncthreads();
-        base = s_base % kOneLeft;
-    }
-    if (sd.n) emit_small<DTYPE>(sd, v, r, base, rv.idx, rv.val, rv.bitmap, h);  // uniform
+        const uint32_t pairs = wave_sum<uint32_t>(word - 1u);
+        if (lane == 0) {
+            s_base = pairs;
+            nonfinite = keeps ? smem[32] : 0u;
+            if (nonfinite) atomicAdd(&ts.glob[1], nonfinite);
+            wait_own_memory_ops();  // (what the last one looks at, and the word that it clears)
+            came = atomicAdd(&ts.arrive[0], nonfinite ? 1u + kSome : 1u);
+        }
+    };
+    emit_small<DTYPE>(sd, v, r, &s_base, rv.idx, rv.val, rv.bitmap, h, look);
     if (tid == 0) {
         rv.cnt[TAGC_CNT_SEG0 + l] = r.cnt;
         if (l == L - 1) {
-            rv.cnt[TAGC_CNT_TOTAL] = base + r.cnt;
+            rv.cnt[TAGC_CNT_TOTAL] = s_base + r.cnt;
             rv.cnt[TAGC_CNT_FLAGS] = 0;
             rv.cnt[TAGC_CNT_DENSE] = dense;
             rv.cnt[TAGC_CNT_RESERVED] = 0;
         }
-        if ((came & (kSome - 1)) == L - 1) {
+    }
+    if (wave == 1 && (__builtin_amdgcn_readfirstlane(came) & (kSome - 1)) == L - 1) {  // everybody has told and looked
+        if (lane < L) ts.arrive_d[lane] = 0;
+        if (lane == 0) {
             uint32_t all = 0;
             if (came >= kSome || nonfinite) {
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -2730,10 +2718,13 @@ int launch_sparsify_t(const tagc_plan_t *p, const void *const *grads, const tagc
         return hip_ok(hipGetLastError());
     }
     const bool acc = ranks[0].acc != nullptr;
-    // (with a compute unit for every workgroup: 32 ranks of 9, 12, 20 segments with a little under 200 KiB
-    // each, nearly all zeros, three launches / one 28.1 / 33.4, 29.4 / 38.2, 31.8 / 43.6 us, of 7 segments 0.9;
-    // 32 of 28 short ones without zeros 40 / 51, 8 of them 0.8)
-    const bool one = p->all_small && uint64_t(L) * n <= uint64_t(device_cu_count());
+    // One launch for short segments: a workgroup fills a compute unit, so as long as they are two turns of them
+    // (bf16) or four.  PHASE_INDEX, us, three launches / one, gradients nearly all zeros (the same without zeros,
+    // 1 % kept), by workgroups: bf16 448 24.5 / 22.5 (24.7 / 22.8), 512 24.7 / 22.7 (26.2 / 23.2), 640 29.9 / 32.2 (30.6
+    // / 33.0), 1024 36.8 / 43.4 (39.4 / 44.1); fp32 512 25.5 / 18.5 (39.0 / 20.2), 640 26.0 / 25.6 (40.1 / 29.2), 896
+    // 31.9 / 33.0 (50.7 / 38.1), 1024 33.7 / 34.1 (50.8 / 38.3), 2048 57.6 / 66.3 (94.1 / 74.0).
+    const uint32_t turns = DTYPE == kBF16 ? 2 : 4;
+    const bool one = p->all_small && uint64_t(L) * n <= turns * uint64_t(device_cu_count());
     SparsifyBatch sb{};
     SparsifyBatch part{};  // the ranks whose thresholds are launched next
     uint32_t n_part = 0;

@@ -22,8 +22,7 @@ constexpr uint32_t kSmallThreads = 1024;  // ... of a plan with segments one wor
 constexpr uint32_t kDenseRows = 4;        // 16-byte vectors per thread and tile of it
 constexpr uint32_t kSmallVecs = 8;        // 16-byte vectors per thread such a segment has at most
 constexpr uint32_t kSmallSegments = 64;   // segments up to which a plan of such segments takes one launch, ...
-constexpr uint32_t kSmallPairs = 80 * 1024;    // ... entries and four times those kept of each, ...
-constexpr uint32_t kSmallBefore = 192 * 1024;  // ... and bytes before the last (see tagc_plan)
+constexpr uint32_t kSmallPairs = 80 * 1024;    // ... entries and four times those kept of each (see tagc_plan)
 constexpr uint32_t kHistWindow = 4096;
 constexpr uint32_t kCandRows = 4;        // 16-byte vectors per lane per candidate chunk
 constexpr uint32_t kCandChunksPerSuper = 32;  // chunks that a wave of place takes
@@ -135,7 +134,7 @@ struct TableState {
     uint32_t *watch;     // [L] calls that still follow the falling trend after a miss
     uint32_t *prev;      // [L] the bin above which 1.3 k entries lay at the last call
     uint32_t *arrive;    // [L] workgroups of the scan that are done with the segment
-    uint32_t *arrive_d;  // [L] the same for the dense route's histogram
+    uint32_t *arrive_d;  // [L] the same for the dense route's histogram; small_kernel: pairs of the segment + 1
     uint32_t *raised;    // [L] highest pre-threshold a wave of the scan used
     uint32_t *reroute;   // [L] a chunk overflowed its slots
     uint32_t *glob;      // [8] flags, non-finite inputs, dense-route segments of the call
@@ -175,7 +174,7 @@ struct tagc_plan_s {
     bool static_dense;                        // some segment with k > 0 never takes the candidate route
     bool any_fast;                            // some segment takes it
     bool small_dense;                         // some dense-route segment is kSegSmall
-    bool all_small;                           // a workgroup a segment is the faster sparsifier if all run at once
+    bool all_small;                           // a workgroup a segment is the faster sparsifier if there are not too many
     uint64_t span_dense;                      // entries of the dense-route segments that are not
     uint64_t dense_pairs;                     // pairs the dense-route segments emit at most
     uint64_t n_real, n_c, K, U_cap, A_cap, m_cap;

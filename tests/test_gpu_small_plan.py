@@ -109,15 +109,14 @@ def _took(segs, n, dtype, ranks):
 
 
 # Lengths, kept (ppm), ranks; whether one launch takes them.  What a workgroup would be slower over than the device
-# is left to the device: too many pairs of a segment, too much in front of the last (all of which has to be looked
-# through if it is zeros), more workgroups than compute units; and a plan that keeps nothing.
+# is left to the device: too many pairs of a segment, more than two turns of workgroups (fp32: four); and a plan that keeps nothing.
 @pytest.mark.parametrize("dtype,lengths,ppm,ranks,one", [
     (G.F32, [32768], 375_000, 1, True), (G.F32, [32768], 376_000, 1, False),
     (G.BF16, [65535], 62_000, 1, True), (G.BF16, [65535], 63_000, 1, False),
     (G.BF16, [8192], 1_000_000, 1, True), (G.BF16, [8193], 1_000_000, 1, False), (G.BF16, [8700], 945_000, 1, True),
-    (G.F32, [24576, 24576, 30_000], 20_000, 2, True), (G.F32, [24576, 24577, 300], 20_000, 2, False),
-    (G.BF16, [49152, 49152, 30_000], 20_000, 2, True), (G.BF16, [49152, 49153, 300], 20_000, 2, False),
-    (G.F32, [700] * 8, 20_000, 32, True), (G.F32, [700] * 9, 20_000, 32, False),
+    (G.F32, [32768] * 64, 20_000, 2, True), (G.BF16, [65535] * 64, 20_000, 2, True), (G.F32, [32768] * 64, 20_000, 16, True),
+    (G.F32, [700] * 32, 20_000, 32, True), (G.F32, [700] * 33, 20_000, 32, False),
+    (G.BF16, [700] * 16, 20_000, 32, True), (G.BF16, [700] * 17, 20_000, 32, False),
     (G.F32, [700] * 64, 20_000, 4, True), (G.F32, [700] * 65, 20_000, 1, False), (G.BF16, [40] * 7, 20_000, 2, False)])
 def test_which_plans_take_one_launch(dtype, lengths, ppm, ranks, one):
     print("\n[case] small plan, route dtype=%d lengths=%s ppm=%d ranks=%d" % (dtype, lengths[:3], ppm, ranks), flush=True)
@@ -126,17 +125,33 @@ def test_which_plans_take_one_launch(dtype, lengths, ppm, ranks, one):
     assert ("small" in took, "place" in took) == (one, not one), took
 
 
-# What a wave has not settled in eight trips (4096 entries, bf16 8192) all waves look through: non-zeros before and behind
-# that, exactly as many as are kept up to an edge of it and one fewer, several such segments at once
-@pytest.mark.parametrize("dtype,alone", [(G.F32, 4096), (G.BF16, 8192)])
-@pytest.mark.parametrize("at", ["front", "spread", "behind", "end", "none"])
-def test_what_one_wave_leaves(dtype, alone, at):
-    print("\n[case] small plan, left to all waves dtype=%d at=%s" % (dtype, at), flush=True)
-    lengths = [alone, alone + 1, alone + 77, 3 * alone - 5, 5000, 18_003 if dtype == G.F32 else 30_003, 901]
+# What the workgroups of a launch tell each other, a word a segment behind the table's rows, is there long before anybody
+# looks.  Below zero before the launch, it counts as not there, as if that workgroup had not started yet: the others look
+# through the segment then, eight 16-byte vectors a lane of sixteen waves at a time, and all words are zero behind the launch.
+_WIN_WORDS = 1544  # per segment, of the candidate histograms in front of the counters
+
+
+def _untold(tb, n_seg, which):
+    """Marks the words of the segments `which`, of every rank; returns a view of all words."""
+    slot = n_seg * _WIN_WORDS + 8 + (7 * n_seg + 7) // 8 * 8
+    state = tb.table.view(torch.int32)[8 + 8 * n_seg:][:slot * min(tb.n_ranks, 32)].view(-1, slot)
+    words = state[:, n_seg * _WIN_WORDS + 8 + 4 * n_seg:][:, :n_seg]
+    assert not words.any().item()
+    words[:, which] = -1 << 31
+    return words
+
+
+@pytest.mark.parametrize("dtype", [G.F32, G.BF16])
+@pytest.mark.parametrize("at", ["spread", "end", "none", "dense"])
+@pytest.mark.parametrize("which", [[], [0], [1, 3, 4], [0, 1, 2, 3, 4, 5, 6]])
+def test_segments_nobody_has_told_of(dtype, at, which):
+    print("\n[case] small plan, untold dtype=%d at=%s which=%s" % (dtype, at, which), flush=True)
+    turn = 2048 if dtype == G.F32 else 4096  # entries of a wave's turn
+    lengths = [turn, 16 * turn if dtype == G.F32 else 65_535, turn + 1, 3 * turn - 5, 77, 9 * turn + 3, 901]
     for kept in (60, 700):
         segs, at0 = [], 0
         for i, n in enumerate(lengths):
-            segs.append(G.Seg(at0, n, 1_000_000 * kept // n + 1, 1, "s%d" % i))
+            segs.append(G.Seg(at0, n, 1_000_000 * min(kept, n) // n, 1, "s%d" % i))
             at0 += n
         b = G.Bucket("small", dtype, 3, segs, at0, 1500)
         rng = np.random.default_rng(kept)
@@ -145,15 +160,25 @@ def test_what_one_wave_leaves(dtype, alone, at):
             x = np.zeros(at0)
             for s in segs:
                 k = s.length * s.keep_ppm // 1_000_000
-                n = 0 if at == "none" else k - 1 + r
-                lo, hi = {"front": (0, n), "behind": (alone, s.length), "end": (s.length - n, s.length)}.get(at, (0, s.length))
-                lo = min(lo, s.length - n)
-                x[s.offset + rng.choice(np.arange(lo, max(hi, lo + n)), n, replace=False)] = rng.integers(1, 120, n)
+                n = {"none": 0, "dense": s.length}.get(at, min(k - 1 + r, s.length))
+                lo = s.length - n if at == "end" else 0
+                x[s.offset + rng.choice(np.arange(lo, s.length), n, replace=False)] = rng.integers(1, 120, n)
             grads.append(torch.from_numpy(x.astype(np.float32)).to(torch.float32 if dtype == G.F32 else torch.bfloat16))
         ores, tb = run_both(b, grads, seed=6)
-        compare_all(b, ores, tb, exact_values=True)
+        for _ in range(2):
+            words = _untold(tb, len(segs), which)
+            for t in tb._rk_tensors:
+                t["idx"].fill_(0xFF)
+            B.tagc_profile_enable(True)
+            try:
+                tb.run([g.cuda() for g in grads])
+                torch.cuda.synchronize()
+            finally:
+                B.tagc_profile_enable(False)
+            assert "small" in B.tagc_profile_read()
+            assert not words.any().item()
+            compare_all(b, ores, tb, exact_values=True)
         tb.close()
-        assert "small" in _took(segs, at0, dtype, 3)
 
 
 # With an accumulator: the launch before replaces the gradient by the sum, read through the Index that this one then writes
