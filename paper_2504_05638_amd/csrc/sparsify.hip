@@ -1417,25 +1417,24 @@ __device__ __forceinline__ void emit_small(const SegDev &sd, uint4 (&v)[kSmallVe
     }
 }
 
-// By a wave: the pairs a segment emits, its non-zeros or what it is to keep.
+// By a wave: the pairs a segment emits, its non-zeros or what it is to keep, if its `word` does not say so meanwhile.
+// (Rarely needed: short, and not wide.)
 template <int DTYPE>
-__device__ inline uint32_t emitted_small(const SegDev &sd, const char *base)
+__device__ inline uint32_t emitted_small(const SegDev &sd, const char *base, const uint32_t *word)
 {
-    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4, TURN = 4;
+    constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4;
     uint32_t n = 0;
-    for (uint32_t at = 0; at < sd.n && n < sd.k; at += TURN * 64 * VEC) {
+    for (uint32_t at = 0; at < sd.n && n < sd.k; at += 64 * VEC) {
+        const uint32_t told = __builtin_amdgcn_readfirstlane(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         uint32_t own = 0;
-        uint4 v[TURN];
-#pragma unroll
-        for (uint32_t i = 0; i < TURN; ++i) v[i] = load_vec<DTYPE>(base, at + (i * 64 + lane_id()) * VEC, sd.n);
-#pragma unroll
-        for (uint32_t i = 0; i < TURN; ++i) for_keys<DTYPE>(v[i], [&](uint32_t, uint32_t) { ++own; });
+        for_keys<DTYPE>(load_vec<DTYPE>(base, at + lane_id() * VEC, sd.n), [&](uint32_t, uint32_t) { ++own; });
+        if (int32_t(told) > 0) return told - 1;
         n += __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(own), 63);
     }
     return min(n, sd.k);
 }
 
-constexpr uint32_t kSmallTries = 4;  // looks at the others' words before one is done without
+constexpr uint32_t kSmallTries = 4;  // looks at the others' words, after the first, before one is done without
 
 template <int DTYPE>
 __global__ void __launch_bounds__(kSmallThreads)
@@ -1475,22 +1474,26 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
     constexpr uint32_t kSome = 1u << 16;
     static_assert(kSmallSegments < kSome, "arrivals");
     uint32_t came = 0, nonfinite = 0;
+    uint32_t word = 1, most = 0;
+    if (wave == 1 && lane < l) {
+        word = __hip_atomic_load(&ts.arrive_d[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        most = segs[lane].k;
+    }
     auto look = [&] {
-        uint32_t word = lane < l ? 0u : 1u;
         for (uint32_t tries = 0;; ++tries) {
-            if (int32_t(word) <= 0) word = __hip_atomic_load(&ts.arrive_d[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const uint64_t untold = __ballot(int32_t(word) <= 0);
             if (!untold) break;
             if (tries < kSmallTries) {
-                __builtin_amdgcn_s_sleep(4);
+                if (int32_t(word) <= 0) word = __hip_atomic_load(&ts.arrive_d[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 continue;
             }
             const uint32_t i = uint32_t(__builtin_ctzll(untold));
             const SegDev before = segs[i];
-            const uint32_t n = emitted_small<DTYPE>(before, grad + before.offset * EB);
+            const uint32_t n = emitted_small<DTYPE>(before, grad + before.offset * EB, ts.arrive_d + i);
             if (lane == i) word = n + 1;
         }
-        const uint32_t pairs = wave_sum<uint32_t>(word - 1u);
+        // (nothing lands outside the list, whatever the words hold)
+        const uint32_t pairs = __builtin_amdgcn_readlane(wave_incl_scan<uint32_t>(min(word - 1u, most)), 63);
         if (lane == 0) {
             s_base = pairs;
             nonfinite = keeps ? smem[32] : 0u;
@@ -2720,9 +2723,9 @@ int launch_sparsify_t(const tagc_plan_t *p, const void *const *grads, const tagc
     const bool acc = ranks[0].acc != nullptr;
     // One launch for short segments: a workgroup fills a compute unit, so as long as they are two turns of them
     // (bf16) or four.  PHASE_INDEX, us, three launches / one, gradients nearly all zeros (the same without zeros,
-    // 1 % kept), by workgroups: bf16 448 24.5 / 22.5 (24.7 / 22.8), 512 24.7 / 22.7 (26.2 / 23.2), 640 29.9 / 32.2 (30.6
-    // / 33.0), 1024 36.8 / 43.4 (39.4 / 44.1); fp32 512 25.5 / 18.5 (39.0 / 20.2), 640 26.0 / 25.6 (40.1 / 29.2), 896
-    // 31.9 / 33.0 (50.7 / 38.1), 1024 33.7 / 34.1 (50.8 / 38.3), 2048 57.6 / 66.3 (94.1 / 74.0).
+    // 1 % kept), by workgroups: bf16 448 24.4 / 21.8 (24.8 / 22.0), 512 24.4 / 22.3 (25.9 / 22.7), 640 29.9 / 32.2 (30.6
+    // / 33.0), 1024 36.8 / 43.4 (39.4 / 44.1); fp32 512 25.5 / 18.0 (38.8 / 19.8), 640 26.0 / 24.7 (40.1 / 28.3), 896
+    // 31.9 / 31.7 (50.6 / 37.0), 1024 40.8 / 35.2 (51.0 / 37.6), 2048 57.6 / 66.3 (94.1 / 74.0).
     const uint32_t turns = DTYPE == kBF16 ? 2 : 4;
     const bool one = p->all_small && uint64_t(L) * n <= turns * uint64_t(device_cu_count());
     SparsifyBatch sb{};
