@@ -1425,7 +1425,8 @@ __device__ inline uint32_t emitted_small(const SegDev &sd, const char *base, con
     constexpr uint32_t VEC = DTYPE == kBF16 ? 8 : 4;
     uint32_t n = 0;
     for (uint32_t at = 0; at < sd.n && n < sd.k; at += 64 * VEC) {
-        const uint32_t told = __builtin_amdgcn_readfirstlane(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const uint32_t told =
+            __builtin_amdgcn_readfirstlane(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         uint32_t own = 0;
         for_keys<DTYPE>(load_vec<DTYPE>(base, at + lane_id() * VEC, sd.n), [&](uint32_t, uint32_t) { ++own; });
         if (int32_t(told) > 0) return told - 1;
@@ -1484,7 +1485,8 @@ small_kernel(const SparsifyBatch, uint32_t *table, const WsLayout wl)
             const uint64_t untold = __ballot(int32_t(word) <= 0);
             if (!untold) break;
             if (tries < kSmallTries) {
-                if (int32_t(word) <= 0) word = __hip_atomic_load(&ts.arrive_d[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (int32_t(word) <= 0)
+                    word = __hip_atomic_load(&ts.arrive_d[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 continue;
             }
             const uint32_t i = uint32_t(__builtin_ctzll(untold));
